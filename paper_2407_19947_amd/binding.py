@@ -10,7 +10,7 @@ import numpy as np
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libstairs.so")
-_SOURCES = [os.path.join(_HERE, "csrc", f) for f in ("stairs_kernels.hip", "stairs_api.hip")]
+_SOURCES = [os.path.join(_HERE, "csrc", f) for f in ("stairs_kernels.hip", "stairs_block.hip", "stairs_api.hip")]
 
 STAIRS_MAX_ROWS = 32
 DTYPE_FP32, DTYPE_BF16 = 0, 1

@@ -238,5 +238,6 @@ void launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream_t st)
 
 // opt in to large dynamic LDS for the kernels that need it (once per process/device)
 hipError_t configure_kernels();
+hipError_t configure_block_kernels();   // (called by configure_kernels)
 
 }  // namespace stairs
