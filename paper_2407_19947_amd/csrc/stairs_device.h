@@ -26,7 +26,10 @@ __device__ __forceinline__ uint32_t bf16_pack2_rne(float a, float b) {
   const f32x2_t v = {a, b};
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
+// (contraction off here and in split_half8: the remainder must not be fused with a product in front of it in one
+// instantiation and left alone in another, or a row's bits would depend on how many rows its kernel was built for)
 __device__ __forceinline__ void bf16_split2(float a, float b, uint32_t& hi, uint32_t& lo) {
+#pragma clang fp contract(off)
   hi = bf16_pack2_rne(a, b);
   lo = bf16_pack2_rne(a - __uint_as_float(hi << 16), b - __uint_as_float(hi & 0xFFFF0000u));
 }
@@ -171,11 +174,14 @@ __device__ __forceinline__ float2 rope_rotate(float a, float b, float2 cs) {
 typedef __attribute__((ext_vector_type(8))) _Float16 f16x8;
 
 __device__ __forceinline__ void split_half8(const float* v, f16x8& hi, f16x8& lo) {
+#pragma clang fp contract(off)
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    const _Float16 h = (_Float16)v[e];
+    float x = v[e];
+    asm("" : "+v"(x));       // a product in front must be rounded to float first: its conversion would else become one
+    const _Float16 h = (_Float16)x;   // instruction with a single rounding in some instantiations and not in others
     hi[e] = h;
-    lo[e] = (_Float16)(v[e] - (float)h);
+    lo[e] = (_Float16)(x - (float)h);
   }
 }
 

@@ -2033,11 +2033,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
         // the chunk's sum of exponentials (a wave without keys has weight 0 and sum 0: it adds nothing); no branch
         // around the LDS reads
         const float l0 = s_l[0][jj], l1 = s_l[1][jj], l2 = s_l[2][jj], l3 = s_l[3][jj];
-        float lc = 0.f;
-        lc += f0 * l0;
-        lc += f1 * l1;
-        lc += f2 * l2;
-        lc += f3 * l3;
+        const float lc = __fadd_rn(__fadd_rn(__fadd_rn(__fmul_rn(f0, l0), __fmul_rn(f1, l1)), __fmul_rn(f2, l2)), __fmul_rn(f3, l3));
         if (single) {
           float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
           if (pos0 + m * step >= 0) res = make_float4(o0 / lc, o1 / lc, o2 / lc, o3 / lc);

@@ -529,6 +529,25 @@ def test_adaptive_draft_length_on_gpu():
         assert np.array_equal(toks, plain) and st.tokens == 40
 
 
+@pytest.mark.parametrize("P", [2049, 6000, 30000])
+def test_row_bits_do_not_depend_on_the_query_tiles(P):
+    """Stair batches of 16 and 1 rows (one 16-row query tile per work-group) and of 17 and 32 rows (two) from the same state:
+    the rows they share have the same bits.  (The query's high part used to be rounded once from the exact product in one
+    instantiation and twice in the other.)"""
+    w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=256, n_heads=2, d_ffn=256, vocab=512),
+                           draft=dict(kind="prefix", n_layers=1), P=P, G=1)
+    target, draft = si.make_pair(w)
+    prompt = si.make_prompt(w)
+    d = np.random.default_rng([7, P]).integers(0, 512, 31).astype(np.int32)
+    want = None
+    with pkg.Stairs(target, draft, k_max=31, max_seq=P + 40) as s:
+        for k in (31, 16, 15, 0):
+            s.prefill(prompt)
+            _, _, lg = s.verify_tokens(d[:k], logits=True)
+            want = lg.copy() if want is None else want
+            assert np.array_equal(lg, want[:k + 1]), k
+
+
 def test_longest_context_stair_batches(monkeypatch):
     """max_seq = 60000 (the most the library takes: 469 attention chunks, the stand-alone chunk merge with its
     largest table).  The 32-row stair batch is compared with the oracle's logits stored by
