@@ -87,9 +87,10 @@ struct stairs_ctx {
   uint4 *xf = nullptr, *af = nullptr, *hf = nullptr;
   // block prefill (bf16 models, env STAIRS_NO_BLOCK_PREFILL=1 turns it off): [kPfRows, .] workspaces
   bool block_prefill = false;
-  float *pf_x = nullptr, *pf_y = nullptr, *pf_q = nullptr, *pf_attn = nullptr;
-  uint4* pf_frag = nullptr;    // block fragments of the activation in front of the current projection
-  float* pf_part = nullptr;    // k-split results of block GEMMs with few rows (short prompts, forwards of many sequences)
+  float *pf_x = nullptr, *pf_q = nullptr, *pf_attn = nullptr, *pf_ssq = nullptr;
+  uint4 *pf_fa = nullptr, *pf_fb = nullptr;   // block fragments: of x (with the next norm's gain), of attention output / hidden activations
+  int2* pf_rowinfo = nullptr;  // (slot, position) of the block's rows
+  float* pf_part = nullptr;    // k pieces of block GEMMs with few rows
   size_t pf_part_floats = 0;
   float2* pf_cs = nullptr;
   // encoder-decoder contexts: source tokens and the encoder's activations [max_src, .]
@@ -491,7 +492,7 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
                m->layers[0].attn_norm);
   SYNCPOINT();
   const RowNorm none{nullptr, nullptr, 0, 0.f};
-  AttnMode amode{0.f, nullptr, 0, 0, 0, fr ? c->af : nullptr};
+  AttnMode amode{0.f, nullptr, 0, 0, 0, fr ? c->af : nullptr, 0};
   for (int l = 0; l < g.n_layers; ++l) {
     const Layer& ly = m->layers[l];
     char* Kl = m->Kc + slot_off + l * m->kv_layer_bytes;
@@ -558,14 +559,65 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
 #undef SYNCPOINT
 }
 
-// A forward of 33 .. kMaxBlockRows rows of several sequences (pos.rps rows per slot) on the block kernels: the
-// projections run on the MFMA-bound GEMM of the prompt ingestion over all rows at once, attention on the decode
-// kernel (one grid slice per slot, each against its own cache), the rest is element-wise.  Every output has one order
-// of additions whatever the number of rows, so a sequence's results do not depend on which others share the forward
-// (they are not the bits of the decode kernels, whose additions go chunk by chunk).  All rows' logits -> c->logits.
+// The layers of a decoder-only model on a block of R rows (c->pf_rowinfo / pf_cs: where they sit; c->pf_x, pf_fa, pf_ssq:
+// their embeddings, left by launch_blk_embed): four projections per layer on the block GEMM, whose epilogues do the
+// work in between (rotation and append, residual, SwiGLU, the next projection's fragments), and attention.
+// attend(l, K cache, V cache): from c->pf_q into the fragments c->pf_fb.
+template <typename F>
+int block_layers(stairs_ctx* c, Model* m, int R, bool pieced, F attend) {
+  const stairs_model_cfg& g = m->cfg;
+  const int d = g.d_model, f = g.d_ffn;
+  hipStream_t st = c->st;
+  BlkGemm p{};
+  p.RT = pf_col_tiles(R);
+  p.R = R;
+  p.ssq_n = d / kBlkSsqCols;
+  p.eps = g.rms_eps;
+  p.rows = c->pf_rowinfo;
+  p.cs = c->pf_cs;
+  p.slot_stride = (size_t)g.n_layers * m->kv_layer_bytes / m->esz();
+  p.cap = m->cap;
+  p.hd = m->hd;
+  p.da = d;
+  auto gemm = [&](int kind, const void* W, int N, int K, const uint4* in, const float* ssq, float* out, uint4* frag_out, const float* gain) {
+    p.kind = kind;
+    p.W = static_cast<const uint4*>(W);
+    p.NTILES = N / 16;
+    p.K = K;
+    p.XF = in;
+    p.ssq = ssq;
+    p.out = out;
+    p.ldo = N;
+    p.frag_out = frag_out;
+    p.gain = gain;
+    p.ssq_out = kind == kBlkResid ? c->pf_ssq : nullptr;
+    launch_blk_gemm(p, pieced, st, c->pf_part, c->pf_part_floats);
+    return c->sync_launches ? hipStreamSynchronize(st) : hipSuccess;
+  };
+  for (int l = 0; l < g.n_layers; ++l) {
+    const Layer& ly = m->layers[l];
+    char* Kl = m->Kc + l * m->kv_layer_bytes;
+    char* Vl = m->Vc + l * m->kv_layer_bytes;
+    p.Kc = reinterpret_cast<_Float16*>(Kl);
+    p.Vc = reinterpret_cast<_Float16*>(Vl);
+    HIPCHK(c, gemm(kBlkQKV, ly.wqkv, 3 * d, d, c->pf_fa, c->pf_ssq, c->pf_q, nullptr, nullptr));
+    attend(Kl, Vl);
+    if (c->sync_launches) HIPCHK(c, hipStreamSynchronize(st));
+    HIPCHK(c, gemm(kBlkResid, ly.wo, d, d, c->pf_fb, nullptr, c->pf_x, c->pf_fa, ly.ffn_norm));
+    HIPCHK(c, gemm(kBlkSwiglu, ly.wgu, 2 * f, d, c->pf_fa, c->pf_ssq, nullptr, c->pf_fb, nullptr));
+    HIPCHK(c, gemm(kBlkResid, ly.wdown, d, f, c->pf_fb, nullptr, c->pf_x, c->pf_fa, l + 1 < g.n_layers ? m->layers[l + 1].attn_norm : m->final_norm));
+  }
+  HIPCHK(c, hipGetLastError());
+  return STAIRS_OK;
+}
+
+// A forward of more rows of several sequences (pos.rps rows per slot) than the decode kernels take, on the block
+// kernels; attention on the decode kernel (one grid slice per slot, each against its own cache).  Every output has one
+// order of additions whatever the number of rows, so a sequence's results do not depend on which others share the
+// forward (they are not the bits of the decode kernels, whose additions go chunk by chunk).  All rows' logits -> c->logits.
 int forward_block(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows) {
   const stairs_model_cfg& g = m->cfg;
-  const int d = g.d_model, f = g.d_ffn, H = g.n_heads, V = g.vocab;
+  const int d = g.d_model, H = g.n_heads, V = g.vocab;
   hipStream_t st = c->st;
   if (!c->block_prefill || !m->bf16 || m->encdec || !pos.rps || M % pos.rps || M > kMaxBlockRows || M > c->pf_rows || M > c->rows_cap ||
       (logits_rows != 0 && logits_rows != M))
@@ -573,32 +625,31 @@ int forward_block(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int lo
   const int nslots = M / pos.rps;
   if (nchunk < 1 || nchunk > c->nchunk_cap || nslots > c->n_slots || nslots * H > kAttnCounters)
     return fail(c, STAIRS_EINVAL, "forward: launch shape outside the workspaces");
-  const size_t slot_bytes = (size_t)g.n_layers * m->kv_layer_bytes;
-  const size_t slot_stride = slot_bytes / m->esz();
-  // (the gather also leaves sum-of-squares partials nobody needs here: into pf_y, which is scratch until the first GEMM)
-  launch_embed(m->tok_emb, 1, c->tokens, c->tok_stride, c->tok_stride, V, pos, M, d, c->pf_x, c->pf_y, m->hd, g.rope_theta, c->pf_cs, st);
-  const AttnMode amode{0.f, nullptr, 0, 0, 0, nullptr};
-  for (int l = 0; l < g.n_layers; ++l) {
-    const Layer& ly = m->layers[l];
-    char* Kl = m->Kc + l * m->kv_layer_bytes;
-    char* Vl = m->Vc + l * m->kv_layer_bytes;
-    launch_pf_norm_split(c->pf_x, ly.attn_norm, g.rms_eps, M, d, c->pf_frag, st);
-    launch_gemm_block(ly.wqkv, 3 * d, d, c->pf_frag, M, c->pf_y, 3 * d, kPermQKV, d, m->hd, 0, st, c->pf_part, c->pf_part_floats);
-    launch_pf_rope_kv_rows(c->pf_y, M, d, H, pos, slot_stride, c->pf_cs, c->pf_q, reinterpret_cast<_Float16*>(Kl),
-                           reinterpret_cast<_Float16*>(Vl), m->cap, st);
+  const size_t slot_stride = (size_t)g.n_layers * m->kv_layer_bytes / m->esz();
+  launch_blk_rows_pos(pos, M, m->hd, g.rope_theta, c->pf_rowinfo, c->pf_cs, st);
+  launch_blk_embed(static_cast<const uint16_t*>(m->tok_emb), c->tokens, c->tok_stride, c->tok_stride, V, c->pf_rowinfo, M, d, c->pf_x,
+                   m->layers[0].attn_norm, c->pf_fa, c->pf_ssq, st);
+  const AttnMode amode{0.f, nullptr, 0, 0, 0, c->pf_fb, pf_col_tiles(M)};
+  int rc = block_layers(c, m, M, true, [&](const char* Kl, const char* Vl) {
     launch_attention(c->pf_q, Kl, Vl, 1, m->cap, d, H, pos.rps, pos, nslots, slot_stride, nchunk, c->nchunk_cap, c->part_o,
                      c->part_ml, c->counters + kGemmCounters, c->pf_attn, st, amode);
-    launch_pf_norm_split(c->pf_attn, nullptr, 0.f, M, d, c->pf_frag, st);
-    launch_gemm_block(ly.wo, d, d, c->pf_frag, M, c->pf_x, d, kPermNone, 0, 0, 1, st, c->pf_part, c->pf_part_floats);
-    launch_pf_norm_split(c->pf_x, ly.ffn_norm, g.rms_eps, M, d, c->pf_frag, st);
-    launch_gemm_block(ly.wgu, 2 * f, d, c->pf_frag, M, c->pf_y, 2 * f, kPermGateUp, f, 0, 0, st, c->pf_part, c->pf_part_floats);
-    launch_pf_swiglu_split(c->pf_y, M, f, c->pf_frag, st);
-    launch_gemm_block(ly.wdown, d, f, c->pf_frag, M, c->pf_x, d, kPermNone, 0, 0, 1, st, c->pf_part, c->pf_part_floats);
-    if (c->sync_launches) HIPCHK(c, hipStreamSynchronize(st));
-  }
+  });
+  if (rc) return rc;
   if (logits_rows > 0) {
-    launch_pf_norm_split(c->pf_x, m->final_norm, g.rms_eps, M, d, c->pf_frag, st);
-    launch_gemm_block(m->lm_head, V, d, c->pf_frag, M, c->logits, V, kPermNone, 0, 0, 0, st, c->pf_part, c->pf_part_floats);
+    BlkGemm p{};
+    p.W = static_cast<const uint4*>(m->lm_head);
+    p.NTILES = V / 16;
+    p.K = d;
+    p.XF = c->pf_fa;
+    p.RT = pf_col_tiles(M);
+    p.R = M;
+    p.kind = kBlkPlain;
+    p.out = c->logits;
+    p.ldo = V;
+    p.ssq = c->pf_ssq;
+    p.ssq_n = d / kBlkSsqCols;
+    p.eps = g.rms_eps;
+    launch_blk_gemm(p, true, st, c->pf_part, c->pf_part_floats);
   }
   HIPCHK(c, hipGetLastError());
   return STAIRS_OK;
@@ -657,8 +708,8 @@ int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logit
                m->dec[0].attn_norm);
   SYNCPOINT();
   const RowNorm none{nullptr, nullptr, 0, 0.f};
-  const AttnMode self_mode{1.f, m->dec_bias, m->cap, m->cap - 1, 0, af};
-  const AttnMode cross_mode{1.f, nullptr, 0, 0, c->S, af};
+  const AttnMode self_mode{1.f, m->dec_bias, m->cap, m->cap - 1, 0, af, 0};
+  const AttnMode cross_mode{1.f, nullptr, 0, 0, c->S, af, 0};
   auto normed = [&](const float* gain) {
     RowNorm n{gain, c->ssq, sn, g.rms_eps};
     return n;
@@ -732,7 +783,7 @@ int encode_model(stairs_ctx* c, Model* m) {
   const int nch = chunks_for(S);
   if (S < 1 || S > m->max_src || nch > c->nchunk_cap) return fail(c, STAIRS_EINVAL, "encode: source outside the workspaces");
   const RowNorm none{nullptr, nullptr, 0, 0.f};
-  const AttnMode mode{1.f, m->enc_bias, 2 * m->max_src - 1, m->max_src - 1, S};
+  const AttnMode mode{1.f, m->enc_bias, 2 * m->max_src - 1, m->max_src - 1, S, nullptr, 0};
   auto rows_of = [&](int b) { return std::min(kMaxRows, S - b); };
   auto epi_for = [&](int b, char* K, char* V, float* out) {
     GemmEpi e{};
@@ -782,58 +833,32 @@ int encode_model(stairs_ctx* c, Model* m) {
   return STAIRS_OK;
 }
 
-// Positions [from, to) of sequence slot `slot` into a model's cache in blocks of up to kPfRows rows: the four
-// projections of a layer run on the MFMA-bound block GEMM over the whole block (the residual additions inside it),
-// attention on k_attn_flash (its keys include the block's own rows, appended just before), the rest is element-wise.
+// Positions [from, to) of sequence slot `slot` into a model's cache in blocks of up to kPfRows rows; attention on
+// k_attn_flash (its keys include the block's own rows, appended just before).
 int ingest_blocks(stairs_ctx* c, Model* m, int from, int to, int slot) {
   const stairs_model_cfg& g = m->cfg;
-  const int d = g.d_model, f = g.d_ffn, H = g.n_heads;
-  hipStream_t st = c->st;
-  const size_t slot_bytes = (size_t)g.n_layers * m->kv_layer_bytes;
-  const int* tokens = c->tokens + (size_t)slot * c->tok_stride;
-#define PF_SYNC()                                               \
-  do {                                                          \
-    if (c->sync_launches) HIPCHK(c, hipStreamSynchronize(st));  \
-  } while (0)
-  for (int p0 = from; p0 < to; p0 += kPfRows) {
-    const int R = std::min(kPfRows, to - p0);
-    launch_pf_embed(static_cast<const uint16_t*>(m->tok_emb), tokens, p0, c->tok_stride, g.vocab, R, d, c->pf_x, st);
-    PF_SYNC();
-    launch_pf_rope_table(p0, R, m->hd, g.rope_theta, c->pf_cs, st);
-    PF_SYNC();
-    for (int l = 0; l < g.n_layers; ++l) {
-      const Layer& ly = m->layers[l];
-      char* Kl = m->Kc + (size_t)slot * slot_bytes + l * m->kv_layer_bytes;
-      char* Vl = m->Vc + (size_t)slot * slot_bytes + l * m->kv_layer_bytes;
-      launch_pf_norm_split(c->pf_x, ly.attn_norm, g.rms_eps, R, d, c->pf_frag, st);
-      PF_SYNC();
-      launch_gemm_block(ly.wqkv, 3 * d, d, c->pf_frag, R, c->pf_y, 3 * d, kPermQKV, d, m->hd, 0, st, c->pf_part, c->pf_part_floats);
-      PF_SYNC();
-      launch_pf_rope_kv(c->pf_y, R, d, H, p0, c->pf_cs, c->pf_q, reinterpret_cast<_Float16*>(Kl), reinterpret_cast<_Float16*>(Vl),
-                        m->cap, st);
-      PF_SYNC();
-      launch_attention_flash(c->pf_q, Kl, Vl, m->cap, d, H, R, p0, c->pf_attn, st);
-      PF_SYNC();
-      launch_pf_norm_split(c->pf_attn, nullptr, 0.f, R, d, c->pf_frag, st);
-      PF_SYNC();
-      launch_gemm_block(ly.wo, d, d, c->pf_frag, R, c->pf_x, d, kPermNone, 0, 0, 1, st, c->pf_part, c->pf_part_floats);
-      PF_SYNC();
-      launch_pf_norm_split(c->pf_x, ly.ffn_norm, g.rms_eps, R, d, c->pf_frag, st);
-      PF_SYNC();
-      launch_gemm_block(ly.wgu, 2 * f, d, c->pf_frag, R, c->pf_y, 2 * f, kPermGateUp, f, 0, 0, st, c->pf_part, c->pf_part_floats);
-      PF_SYNC();
-      launch_pf_swiglu_split(c->pf_y, R, f, c->pf_frag, st);
-      PF_SYNC();
-      launch_gemm_block(ly.wdown, d, f, c->pf_frag, R, c->pf_x, d, kPermNone, 0, 0, 1, st, c->pf_part, c->pf_part_floats);
-      PF_SYNC();
-    }
-    HIPCHK(c, hipGetLastError());
+  const int d = g.d_model, H = g.n_heads;
+  const size_t slot_stride = (size_t)g.n_layers * m->kv_layer_bytes / m->esz();
+  for (int p0 = from; p0 < to; p0 += c->pf_rows) {
+    BlkSegs segs;
+    segs.n = 1;
+    segs.row0[0] = 0;
+    segs.len[0] = std::min(c->pf_rows, to - p0);
+    segs.slot[0] = slot;
+    segs.pos0[0] = p0;
+    const int R = segs.len[0];
+    launch_blk_rows(segs, R, m->hd, g.rope_theta, c->pf_rowinfo, c->pf_cs, c->st);
+    launch_blk_embed(static_cast<const uint16_t*>(m->tok_emb), c->tokens, c->tok_stride, c->tok_stride, g.vocab, c->pf_rowinfo, R, d,
+                     c->pf_x, m->layers[0].attn_norm, c->pf_fa, c->pf_ssq, c->st);
+    int rc = block_layers(c, m, R, R <= kBlkPiecedRows, [&](const char* Kl, const char* Vl) {
+      launch_attention_flash(c->pf_q, Kl, Vl, m->cap, d, H, slot_stride, c->pf_rowinfo, R, c->pf_fb, c->st);
+    });
+    if (rc) return rc;
   }
-#undef PF_SYNC
   return STAIRS_OK;
 }
 
-constexpr int kBlockPrefillMin = 64;   // fewer rows than this go through the decode kernels
+constexpr int kBlockPrefillMin = 17;   // fewer rows than this go through the decode kernels
 
 // ingest positions [from, to) of sequence slot `slot` into a model's cache, no logits
 int ingest(stairs_ctx* c, Model* m, int from, int to, int slot = 0) {
@@ -1185,17 +1210,20 @@ static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
     // rows per block: what the longest sequence needs, at most kPfRows
     const int rows = std::min(kPfRows, (capmax + kBlkRows - 1) / kBlkRows * kBlkRows);
     c->pf_rows = rows;
-    const size_t wide = std::max<size_t>(3 * (size_t)dmax, 2 * (size_t)fmax), inner = std::max<size_t>(dmax, fmax);
-    if ((rc = dev_alloc(c, &c->pf_x, (size_t)rows * dmax)) || (rc = dev_alloc(c, &c->pf_y, (size_t)rows * wide)) ||
-        (rc = dev_alloc(c, &c->pf_q, (size_t)rows * dmax)) || (rc = dev_alloc(c, &c->pf_attn, (size_t)rows * dmax)) ||
-        (rc = dev_alloc(c, &c->pf_frag, pf_frag_bytes(rows, (int)inner) / sizeof(uint4))) ||
+    const int inner = std::max(dmax, fmax);
+    if ((rc = dev_alloc(c, &c->pf_x, (size_t)rows * dmax)) || (rc = dev_alloc(c, &c->pf_q, (size_t)rows * dmax)) ||
+        (rc = dev_alloc(c, &c->pf_ssq, (size_t)rows * (dmax / kBlkSsqCols))) || (rc = dev_alloc(c, &c->pf_rowinfo, (size_t)rows)) ||
+        (rc = dev_alloc(c, &c->pf_attn, (size_t)std::min(rows, kMaxBlockRows) * dmax)) ||
+        (rc = dev_alloc(c, &c->pf_fa, pf_frag_bytes(rows, dmax) / sizeof(uint4))) ||
+        (rc = dev_alloc(c, &c->pf_fb, pf_frag_bytes(rows, inner) / sizeof(uint4))) ||
         (rc = dev_alloc(c, &c->pf_cs, (size_t)rows * 64)))
       return bail(rc);
     // blocks of few rows have too few (feature, row) tiles for the chip: their GEMMs cut k and need room for the pieces
     c->pf_part_floats = (size_t)16 << 20;
     if ((rc = dev_alloc(c, &c->pf_part, c->pf_part_floats))) return bail(rc);
     // rows of a block past its last one are read by the GEMM (and their results dropped): they must hold numbers
-    if (hipMemsetAsync(c->pf_frag, 0, pf_frag_bytes(rows, (int)inner), c->st) != hipSuccess) return bail(STAIRS_EHIP);
+    if (hipMemsetAsync(c->pf_fa, 0, pf_frag_bytes(rows, dmax), c->st) != hipSuccess) return bail(STAIRS_EHIP);
+    if (hipMemsetAsync(c->pf_fb, 0, pf_frag_bytes(rows, inner), c->st) != hipSuccess) return bail(STAIRS_EHIP);
   }
   // every slot of the token array always holds a valid id: a diagnostic forward may run at positions the current
   // sequence has not reached, and the embedding gather takes whatever id it finds there

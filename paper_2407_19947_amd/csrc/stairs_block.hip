@@ -8,16 +8,547 @@
 
 namespace stairs {
 
-// Attention of a prefill block (R consecutive rows at positions p0 .. p0+R-1 of one sequence) without partial
-// results: a wave owns 16 query rows (a work-group 64) of one head and
-// walks over the keys 0 .. its last row's position, 32 at a time, keeping the running maximum, the running sum and the
+// ---------------------------------------------------------------------------------------
+// rows of a block: where they sit, their rotation entries, their embeddings
+// ---------------------------------------------------------------------------------------
+// rows[r] = (slot, position) of row r, position < 0: a padding row; cs[r][i] = (cos, sin)(position * theta^(-2i/hd)),
+// angle in double (theta <= 0: the identity rotation)
+__device__ __forceinline__ void blk_row_entry(int r, int slot, int p, int hd, double theta, int2* rows, float2* cs) {
+  const int i = threadIdx.x;
+  if (i == 0) rows[r] = make_int2(slot, p);
+  if (i >= hd / 2) return;
+  float2 v = make_float2(1.f, 0.f);
+  if (theta > 0.0 && p >= 0) {
+    const double ang = (double)p * pow(theta, -2.0 * (double)i / (double)hd);
+    v = make_float2((float)cos(ang), (float)sin(ang));
+  }
+  cs[r * 64 + i] = v;
+}
+__global__ __launch_bounds__(64) void k_blk_rows(BlkSegs segs, int hd, double theta, int2* __restrict__ rows, float2* __restrict__ cs) {
+  const int r = blockIdx.x;
+  int s = 0;
+  while (s + 1 < segs.n && r >= segs.row0[s + 1]) ++s;
+  const int i = r - segs.row0[s];
+  blk_row_entry(r, segs.slot[s], i < segs.len[s] ? segs.pos0[s] + i : -1, hd, theta, rows, cs);
+}
+__global__ __launch_bounds__(64) void k_blk_rows_pos(PosRef pos, int hd, double theta, int2* __restrict__ rows, float2* __restrict__ cs) {
+  const int r = blockIdx.x;
+  blk_row_entry(r, slot_of(pos, r), pos_of(pos, r), hd, theta, rows, cs);
+}
+void launch_blk_rows(const BlkSegs& segs, int R, int hd, float theta, int2* rows, float2* cs, hipStream_t st) {
+  hipLaunchKernelGGL(k_blk_rows, dim3(R), dim3(64), 0, st, segs, hd, (double)theta, rows, cs);
+}
+void launch_blk_rows_pos(PosRef pos, int R, int hd, float theta, int2* rows, float2* cs, hipStream_t st) {
+  hipLaunchKernelGGL(k_blk_rows_pos, dim3(R), dim3(64), 0, st, pos, hd, (double)theta, rows, cs);
+}
+
+// Activations of a row block as MFMA B-operand fragments, written once by their producer: [k-step of 32][column tile
+// of 16 rows][high, low][lane] x 16 bytes (lane r + 16 g: x[16 ct + r][32 kt + 8 g .. + 8] as bf16 high part / bf16 of
+// the remainders).  RT = column tiles the buffer is laid out for (rows rounded up to a multiple of kBlkRows).
+// (blk_store_frag4 in stairs_device.h)
+
+// x[r][:] = the row's embedding (zeros for a padding row, a position outside [0, tok_cap) or an id outside [0, vocab)),
+// frag = the fragments of x * gain, ssq[r][g] = sum of squares of columns 32 g .. 32 g + 31.  A wave takes 16 rows x 32
+// columns, i.e. one high and one low fragment, which it writes as two whole KiB (a row per work-group left 16-byte pieces
+// of a line to eight XCDs: 36 us for 2048 rows of 4096 columns, 14 this way).
+__global__ __launch_bounds__(256) void k_blk_embed(const uint16_t* __restrict__ emb, const int* __restrict__ tokens, int tok_stride,
+                                                   int tok_cap, int vocab, const int2* __restrict__ rows, int R, int d, float* __restrict__ x,
+                                                   const float* __restrict__ gain, uint4* __restrict__ frag, int RT, float* __restrict__ ssq) {
+  const int lane = threadIdx.x & 63, kt = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int r = blockIdx.y * 16 + (lane & 15), c = kt * 32 + (lane >> 4) * 8;
+  if (kt * 32 >= d) return;                          // (whole waves)
+  const int2 w = r < R ? rows[r] : make_int2(0, -1);
+  const int id = (w.y >= 0 && w.y < tok_cap) ? tokens[(size_t)w.x * tok_stride + w.y] : -1;
+  uint4 b = make_uint4(0u, 0u, 0u, 0u);
+  if (id >= 0 && id < vocab) b = *reinterpret_cast<const uint4*>(emb + (size_t)id * d + c);
+  const uint32_t u[4] = {b.x, b.y, b.z, b.w};
+  float v[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = bf16_bits_to_float((u[i >> 1] >> (16 * (i & 1))) & 0xFFFFu);
+  const float4 g0 = *reinterpret_cast<const float4*>(gain + c), g1 = *reinterpret_cast<const float4*>(gain + c + 4);
+  uint4 hi, lo;
+  bf16_split2(v[0] * g0.x, v[1] * g0.y, hi.x, lo.x);
+  bf16_split2(v[2] * g0.z, v[3] * g0.w, hi.y, lo.y);
+  bf16_split2(v[4] * g1.x, v[5] * g1.y, hi.z, lo.z);
+  bf16_split2(v[6] * g1.z, v[7] * g1.w, hi.w, lo.w);
+  uint4* dst = frag + ((size_t)kt * RT + blockIdx.y) * 128 + lane;
+  dst[0] = hi;
+  dst[64] = lo;
+  float ss = sumsq4(v[0], v[1], v[2], v[3]) + sumsq4(v[4], v[5], v[6], v[7]);
+  ss += __shfl_xor(ss, 16);
+  ss += __shfl_xor(ss, 32);
+  if (r >= R) return;
+  float4* xr = reinterpret_cast<float4*>(x + (size_t)r * d + c);
+  xr[0] = make_float4(v[0], v[1], v[2], v[3]);
+  xr[1] = make_float4(v[4], v[5], v[6], v[7]);
+  if (lane < 16) ssq[(size_t)r * (d / kBlkSsqCols) + kt] = ss;
+}
+void launch_blk_embed(const uint16_t* emb, const int* tokens, int tok_stride, int tok_cap, int vocab, const int2* rows, int R, int d,
+                      float* x, const float* gain, uint4* frag, float* ssq, hipStream_t st) {
+  hipLaunchKernelGGL(k_blk_embed, dim3((d + 127) / 128, (R + 15) / 16), dim3(256), 0, st, emb, tokens, tok_stride, tok_cap, vocab, rows, R, d,
+                     x, gain, frag, pf_col_tiles(R), ssq);
+}
+
+// ---------------------------------------------------------------------------------------
+// block GEMM
+// ---------------------------------------------------------------------------------------
+// 1 / rms of row `row` of the input, by 4 lanes (q = 0 .. 3; `near` and `far` are their two lane distances)
+__device__ __forceinline__ float blk_row_rstd(const BlkGemm& p, int row, int q, int near, int far) {
+  const float* src = p.ssq + (size_t)row * p.ssq_n;
+  float ss = 0.f;
+  for (int i = q * 4; i < p.ssq_n; i += 16) {          // (ssq_n is a multiple of 8)
+    const float4 v = *reinterpret_cast<const float4*>(src + i);
+    ss += (v.x + v.y) + (v.z + v.w);
+  }
+  ss += __shfl_xor(ss, near);
+  ss += __shfl_xor(ss, far);
+  return 1.0f / sqrtf(ss / (float)p.K + p.eps);
+}
+
+// What a launch does with its sums (BlkGemm::kind): a wave holds NT weight tiles x CT column tiles as the MFMA leaves
+// them, lane = 16 g + j: outputs 16 (tile0 + t) + 4 g .. + 3 of row row0 + 16 ct (row0 includes j).  Both the GEMM and
+// the kernel that adds up k pieces end here, so the bits do not depend on which of the two a launch takes.  What has to
+// be read (old x, rotation entries, positions) is requested ahead of the stores of a whole column tile: the compiler
+// may not move loads over stores, and one after the other they cost a work-group as much as its k loop.
+template <int NT, int CT>
+__device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sums)[NT][CT], int tile0, int row0, int g, const float (&rs)[CT]) {
+  // (rs is 1 where nothing is normalised; single floats from here on: exchanged as parts of the MFMAs' register
+  // quadruples the accumulators of the larger tiles spill)
+  float acc[NT][CT][4];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[t][ct][i] = sums[t][ct][i] * rs[ct];
+  if (p.kind == kBlkSwiglu || p.kind == kBlkQKV) {
+    // Columns 0..7 and 8..15 of a tile belong together (gate / up, the halves of rotation pairs).  The lower half of the
+    // wave holds the first eight, the upper half the second: after exchanging the upper half of column tile ct with the
+    // lower half of ct + 1, acc[t][ct] is the first and acc[t][ct + 1] the second member of every lane's pairs; the
+    // lower half works on column tile ct, the upper half on ct + 1.
+    const bool up = g >= 2;
+    g &= 1;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int ct = 0; ct < CT; ct += 2)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[t][ct][i]), __float_as_uint(acc[t][ct + 1][i]), false, false);
+          acc[t][ct][i] = __uint_as_float(r[0]);
+          acc[t][ct + 1][i] = __uint_as_float(r[1]);
+        }
+    if (p.kind == kBlkSwiglu) {
+#pragma unroll
+      for (int ct = 0; ct < CT; ct += 2) {
+        const int row = row0 + (ct + (up ? 1 : 0)) * 16;
+        if (row < p.R)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            const float (&a)[4] = acc[t][ct], (&b)[4] = acc[t][ct + 1];
+            if (tile0 + t < p.NTILES)
+              blk_store_frag4(p.frag_out, p.RT, row, (tile0 + t) * 8 + 4 * g,
+                              make_float4(swiglu(a[0], b[0]), swiglu(a[1], b[1]), swiglu(a[2], b[2]), swiglu(a[3], b[3])));
+            __builtin_amdgcn_sched_barrier(0);         // (here and below: else the tiles' work is interleaved until it spills)
+          }
+      }
+      return;
+    }
+    const int hd = p.hd, half = hd >> 1;
+    constexpr int G = NT == 4 ? 4 : 2;                 // tiles whose rotation entries are requested together
+    int2 at[CT / 2];
+#pragma unroll
+    for (int c2 = 0; c2 < CT / 2; ++c2) at[c2] = p.rows[min(row0 + (2 * c2 + (up ? 1 : 0)) * 16, p.R - 1)];
+#pragma unroll
+    for (int c2 = 0; c2 < CT / 2; ++c2) {
+      const int row = row0 + (2 * c2 + (up ? 1 : 0)) * 16;
+      const bool cached = row < p.R && at[c2].y >= 0 && at[c2].y < p.cap;
+#pragma unroll
+      for (int t0 = 0; t0 < NT; t0 += G) {
+      float4 cs[G][2];
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        const int n = min(tile0 + t0 + q, p.NTILES - 1) * 16, w = n % p.da % hd;
+        const float4* src = reinterpret_cast<const float4*>(p.cs + min(row, p.R - 1) * 64 + (w >> 4) * 8 + 4 * g);
+        cs[q][0] = src[0];
+        cs[q][1] = src[1];
+      }
+#pragma unroll
+      for (int q = 0; q < G; ++q) {
+        const int t = t0 + q;
+        if (tile0 + t >= p.NTILES) continue;
+        const float (&a)[4] = acc[t][2 * c2], (&b)[4] = acc[t][2 * c2 + 1];
+        const int n = (tile0 + t) * 16, part = n / p.da, c = n - part * p.da, h = c / hd, w = c - h * hd;
+        const size_t off = (size_t)at[c2].x * p.slot_stride + (size_t)h * p.cap * hd;
+        if (part == 2) {
+          if (cached)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              store_kv(p.Vc + off + v_cache_off(at[c2].y, w + 4 * g + i, hd), a[i]);
+              store_kv(p.Vc + off + v_cache_off(at[c2].y, w + 8 + 4 * g + i, hd), b[i]);
+            }
+          continue;
+        }
+        const int e = (w >> 4) * 8 + 4 * g;
+        const float2 r0 = rope_rotate(a[0], b[0], make_float2(cs[q][0].x, cs[q][0].y)), r1 = rope_rotate(a[1], b[1], make_float2(cs[q][0].z, cs[q][0].w));
+        const float2 r2 = rope_rotate(a[2], b[2], make_float2(cs[q][1].x, cs[q][1].y)), r3 = rope_rotate(a[3], b[3], make_float2(cs[q][1].z, cs[q][1].w));
+        if (part == 0) {
+          if (row < p.R) {
+            float* dst = p.out + (size_t)row * p.da + h * hd + e;
+            *reinterpret_cast<float4*>(dst) = make_float4(r0.x, r1.x, r2.x, r3.x);
+            *reinterpret_cast<float4*>(dst + half) = make_float4(r0.y, r1.y, r2.y, r3.y);
+          }
+        } else if (cached) {
+          store_kv4(p.Kc + off + k_cache_off(at[c2].y, e, hd), make_float4(r0.x, r1.x, r2.x, r3.x));
+          store_kv4(p.Kc + off + k_cache_off(at[c2].y, e + half, hd), make_float4(r0.y, r1.y, r2.y, r3.y));
+        }
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    return;
+  }
+  if (p.kind == kBlkResid) {
+    constexpr int G = NT == 4 ? 4 : 2;                 // tiles whose old values are requested together
+#pragma unroll
+    for (int t0 = 0; t0 < NT; t0 += G) {
+      float4 gain[G];
+      if (p.frag_out)
+#pragma unroll
+        for (int q = 0; q < G; ++q) gain[q] = *reinterpret_cast<const float4*>(p.gain + min(tile0 + t0 + q, p.NTILES - 1) * 16 + 4 * g);
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const int row = row0 + ct * 16;
+        float* xr = p.out + (size_t)min(row, p.R - 1) * p.ldo + 4 * g;
+        float4 old[G];
+#pragma unroll
+        for (int q = 0; q < G; ++q) old[q] = *reinterpret_cast<const float4*>(xr + min(tile0 + t0 + q, p.NTILES - 1) * 16);
+#pragma unroll
+        for (int q2 = 0; q2 < G; q2 += 2) {
+          const int tile = tile0 + t0 + q2;
+          const bool ok = row < p.R && tile < p.NTILES;  // (N is a multiple of 256: tiles come in pairs)
+          float ss = 0.f;
+#pragma unroll
+          for (int q = q2; q < q2 + 2; ++q) {
+            const float (&a)[4] = acc[t0 + q][ct];
+            const float4 o = old[q], v = make_float4(o.x + a[0], o.y + a[1], o.z + a[2], o.w + a[3]);
+            if (ok) {
+              const int n = (tile0 + t0 + q) * 16;
+              *reinterpret_cast<float4*>(xr + n) = v;
+              if (p.frag_out)
+                blk_store_frag4(p.frag_out, p.RT, row, n + 4 * g, make_float4(v.x * gain[q].x, v.y * gain[q].y, v.z * gain[q].z, v.w * gain[q].w));
+            }
+            ss += sumsq4(v.x, v.y, v.z, v.w);
+          }
+          if (p.ssq_out) {
+            ss += __shfl_xor(ss, 16);
+            ss += __shfl_xor(ss, 32);
+            if (g == 0 && ok) p.ssq_out[(size_t)row * (p.ldo / kBlkSsqCols) + tile / 2] = ss;
+          }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+    return;
+  }
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      const int row = row0 + ct * 16, n = (tile0 + t) * 16 + 4 * g;
+      const float (&v)[4] = acc[t][ct];
+      if (row >= p.R || tile0 + t >= p.NTILES) continue;
+      if (p.kind == kBlkRelu)
+        blk_store_frag4(p.frag_out, p.RT, row, n, make_float4(fmaxf(v[0], 0.f), fmaxf(v[1], 0.f), fmaxf(v[2], 0.f), fmaxf(v[3], 0.f)));
+      else
+        *reinterpret_cast<float4*>(p.out + (size_t)row * p.ldo + n) = make_float4(v[0], v[1], v[2], v[3]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+}
+
+// Sums[R, N] = X[R, K] . W[N, K]^T for row blocks of up to thousands of rows: the MFMA-bound regime.
+//   W: the operand-tile layout of the decode kernels (1 KiB MFMA A operands); X: block fragments (above, 1 KiB B operands).
+//   Work-group = WF x WR waves, each NT weight tiles x CT column tiles of fp32 accumulators; a k-step of 32 is
+//   WF*NT + 2*WR*CT KiB-sized operands, copied from memory straight into LDS (global_load_lds, 16 bytes per lane: no
+//   staging registers, and every weight tile enters the CU once instead of once per row half), ST k-steps deep, and
+//   read from there as they lie (ds_read_b128, no bank conflicts: the layouts are lane order).
+//   One barrier per k-step: the wave waits for its own copies of k-step s (the copies of the following ST - 2 k-steps
+//   stay in flight: the waits count instructions), the barrier makes everybody's visible and says that nobody reads
+//   the buffer of s - 1 any more, which then takes the copies of s + ST - 1.
+//   k pieces: the k range is cut into p.pieces parts that are summed separately (k ascending, high before low) and added
+//   up in order: by different work-groups and k_blk_reduce (gridDim.z = pieces), or one after the other by the same
+//   work-group with a second set of accumulators (PIECED).  The bits depend on p.pieces alone, not on R, the tile shape
+//   or the grid.
+//   What bounds it: the matrix pipes at 1.3 .. 1.47 PFLOP/s issued where the tiles fill whole rounds of the chip (a
+//   library product of two 8192-wide matrices: 1.49 on the same card), LDS bandwidth for the smaller tiles (a 64 x 64
+//   wave tile reads 12 KiB per 32 MFMAs), rounds that are not full otherwise; weights' way from memory at <= 64 rows.
+//   Plain stores, against the kernel before (weights through registers, 256 x 128 tiles only), 7B projections, us:
+//   2047 rows: QKV 384 -> 312, out 115 -> 105, gate/up 712 -> 564, down 297 -> 288; 333 rows: 111 -> 81, 45 -> 33,
+//   198 -> 133, 96 -> 70; 60 rows: 45 -> 33, 23 -> 18, 78 -> 46, 38 -> 33.  With the epilogues inside a 2047-row layer
+//   takes 1.47 ms of projections where projections and the kernels between them took 1.84.
+template <int N> __device__ __forceinline__ void wait_copies_and_sync() {
+  asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
+}
+__device__ __forceinline__ void copy_to_lds_16(const uint4* src, uint4* lds_base) {      // lane l: lds_base[l] = *src
+  __builtin_amdgcn_global_load_lds(reinterpret_cast<const __attribute__((address_space(1))) uint32_t*>(reinterpret_cast<uintptr_t>(src)),
+                                   reinterpret_cast<__attribute__((address_space(3))) uint32_t*>(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base))), 16, 0, 0);
+}
+constexpr int blk_lds_bytes(int WF, int WR, int NT, int CT, int ST) { return ST * (WF * NT + 2 * WR * CT) * 1024 + WR * CT * 64; }
+
+template <int WF, int WR, int NT, int CT, int ST, bool PIECED>
+__global__ __launch_bounds__(64 * WF * WR) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks) {
+  constexpr int NW = WF * WR, AT = WF * NT, BT = 2 * WR * CT, STAGE = (AT + BT) * 64;   // uint4 per LDS stage
+  constexpr int PER = (AT + BT + NW - 1) / NW;                                          // copies per wave and k-step
+  static_assert((ST - 2) * PER < 64, "countable by vmcnt");
+  extern __shared__ uint4 lds[];                       // [ST][weight tiles AT | fragments BT][64], then the rows' 1/rms
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fw = wave % WF, rw = wave / WF;
+  const int j = lane & 15, g = lane >> 4;
+  // Work-groups go round-robin to the 8 XCDs: each XCD takes a contiguous run of (feature block, row block) pairs, row
+  // blocks fastest, so that the row blocks that share weight tiles meet in one L2.
+  const int lin = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if (lin >= nblocks) return;                          // (whole work-groups, before any barrier)
+  const int fb = lin / RB, rb = lin - fb * RB;
+  const int ksteps = p.K >> 5, P = p.pieces;
+  // (the pieces differ by at most one k-step; every piece has at least 8: launch_blk_gemm)
+  const int piece0 = PIECED ? 0 : (int)blockIdx.z, npieces = PIECED ? P : (int)gridDim.z;
+  const int ks0 = ksteps * piece0 / npieces, ks_end = PIECED ? ksteps : ksteps * (piece0 + 1) / npieces;
+
+  // copies of k-step s into LDS buffer buf: every NW-th operand of the stage is this wave's (tiles past the matrix and
+  // column tiles past the fragment buffer repeat the last one, their results are dropped; where the operands are no
+  // multiple of the waves, some waves copy one of theirs twice, so that the counts are everybody's)
+  const int units_total = p.K / kUnitK;
+  auto request = [&](int s, int buf) {
+    const int c = s >> 4, kk = s & 15;
+    const int ksteps_c = min(kSliceUnits, units_total - c * kSliceUnits) * 8;
+    const uint4* wbase = p.W + ((size_t)c * p.NTILES * (kSliceUnits * 8) + kk) * 64 + lane;
+    const uint4* xbase = p.XF + (size_t)s * p.RT * 128 + lane;
+    uint4* dst = lds + buf * STAGE;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      int i = wave + q * NW;
+      if (PER * NW > AT + BT && i >= AT + BT) i -= NW;
+      const uint4* src = i < AT ? wbase + (size_t)min(p.tile_first + fb * AT + i, p.NTILES - 1) * ksteps_c * 64
+                                : xbase + (size_t)min(rb * BT + i - AT, 2 * p.RT - 1) * 64;
+      copy_to_lds_16(src, dst + i * 64);
+    }
+  };
+  f32x4 acc[NT][CT], tot[PIECED ? NT : 1][PIECED ? CT : 1];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto compute = [&](int buf) {
+    const uint4* sa = lds + buf * STAGE + fw * NT * 64 + lane;
+    const uint4* sb = lds + buf * STAGE + (AT + rw * CT * 2) * 64 + lane;
+    bf16x8 vh[CT], vl[CT], av[3];
+    av[0] = __builtin_bit_cast(bf16x8, sa[0]);
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      vh[ct] = __builtin_bit_cast(bf16x8, sb[(ct * 2) * 64]);
+      vl[ct] = __builtin_bit_cast(bf16x8, sb[(ct * 2 + 1) * 64]);
+    }
+    av[1] = __builtin_bit_cast(bf16x8, sa[64]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (t + 2 < NT) av[(t + 2) % 3] = __builtin_bit_cast(bf16x8, sa[(t + 2) * 64]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[t % 3], vh[ct], acc[t][ct], 0, 0, 0);
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[t % 3], vl[ct], acc[t][ct], 0, 0, 0);
+    }
+  };
+  // the rows' 1/rms, while the first copies are on their way (its loads go first, so the counted waits cover them)
+  float* s_rstd = reinterpret_cast<float*>(lds + ST * STAGE);
+  if (p.ssq && part == nullptr)
+    for (int r = tid >> 2; r < WR * CT * 16; r += 16 * NW) {
+      const float v = blk_row_rstd(p, min(rb * WR * CT * 16 + r, p.R - 1), tid & 3, 1, 2);
+      if ((tid & 3) == 0) s_rstd[r] = v;
+    }
+#pragma unroll
+  for (int i = 0; i < ST - 1; ++i) request(min(ks0 + i, ks_end - 1), i);
+  int buf = 0, nbuf = ST - 1, piece = 0, bound = PIECED ? ksteps / P : 0;
+  auto fold = [&](int ks) {                            // PIECED: a piece ends in front of k-step ks
+    if constexpr (PIECED) {
+      if (ks == bound) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            tot[t][ct] = piece == 0 ? acc[t][ct] : tot[t][ct] + acc[t][ct];
+            acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+          }
+        ++piece;
+        bound = ksteps * (piece + 1) / P;
+      }
+    }
+  };
+  for (int ks = ks0; ks < ks_end - (ST - 1); ++ks) {
+    fold(ks);
+    wait_copies_and_sync<(ST - 2) * PER>();
+    request(ks + ST - 1, nbuf);
+    compute(buf);
+    buf = buf + 1 == ST ? 0 : buf + 1;
+    nbuf = nbuf + 1 == ST ? 0 : nbuf + 1;
+  }
+  // the last ST - 1 k-steps: nothing more to request, so the waits count down (a piece is longer than that)
+  static_assert(ST == 2 || ST == 3, "tail written for these");
+  if constexpr (ST >= 3) {
+    fold(ks_end - 2);
+    wait_copies_and_sync<PER>();
+    compute(buf);
+    buf = buf + 1 == ST ? 0 : buf + 1;
+  }
+  fold(ks_end - 1);
+  wait_copies_and_sync<0>();
+  compute(buf);
+  if constexpr (PIECED) {
+    if (piece > 0) {
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) acc[t][ct] = tot[t][ct] + acc[t][ct];
+    }
+  }
+
+  const int tile0 = p.tile_first + fb * AT + fw * NT, row0 = (rb * WR + rw) * CT * 16 + j;   // column tile ct: row0 + 16 ct
+  if (part) {                                          // one piece: its sums as they lie, [piece][tile][column tile][lane]
+    const int ntiles = p.NTILES - p.tile_first, cts = (p.R + 15) >> 4;
+    float4* dst = reinterpret_cast<float4*>(part) + ((size_t)piece0 * ntiles + (tile0 - p.tile_first)) * cts * 64 + lane;
+    const int ct0 = (rb * WR + rw) * CT;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+        if (tile0 + t < p.NTILES && ct0 + ct < cts)
+          dst[((size_t)t * cts + ct0 + ct) * 64] = make_float4(acc[t][ct][0], acc[t][ct][1], acc[t][ct][2], acc[t][ct][3]);
+    return;
+  }
+  float rs[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) rs[ct] = p.ssq ? s_rstd[rw * CT * 16 + ct * 16 + j] : 1.f;
+  blk_epilogue<NT, CT>(p, acc, tile0, row0, g, rs);
+}
+
+// The k pieces of a launch with few rows added up in order, then the launch's epilogue: a wave takes two weight tiles x
+// two column tiles.
+__global__ __launch_bounds__(256) void k_blk_reduce(BlkGemm p, const float* __restrict__ part) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
+  const int ntiles = p.NTILES - p.tile_first, cts = (p.R + 15) >> 4;
+  const int t0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 2, ct0 = blockIdx.y * 2;
+  if (t0 >= ntiles) return;                            // (whole waves; no barriers)
+  const float4* src = reinterpret_cast<const float4*>(part) + lane;
+  f32x4 acc[2][2];
+  for (int z = 0; z < p.pieces; ++z)
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int ct = 0; ct < 2; ++ct) {
+        const float4 v = src[(((size_t)z * ntiles + min(t0 + t, ntiles - 1)) * cts + min(ct0 + ct, cts - 1)) * 64];
+        const f32x4 u = {v.x, v.y, v.z, v.w};
+        acc[t][ct] = z == 0 ? u : acc[t][ct] + u;
+      }
+  float rs[2] = {1.f, 1.f};
+  const int row0 = ct0 * 16 + j;
+  if (p.ssq)
+#pragma unroll
+    for (int ct = 0; ct < 2; ++ct) rs[ct] = blk_row_rstd(p, min(row0 + ct * 16, p.R - 1), g, 16, 32);
+  blk_epilogue<2, 2>(p, acc, p.tile_first + t0, row0, g, rs);
+}
+
+// Tile shapes: features x rows of a work-group, threads, how many of its kind a CU holds, and the microseconds a k-step
+// takes with one such work-group on the CU and with the chip full of them (7B projections, 60 .. 2047 rows).
+struct BlkShape { int feat, rows, threads, per_cu; float t_one, t_full; };
+constexpr int kBlkShapeCount = 4;
+constexpr BlkShape kBlkShapes[kBlkShapeCount] = {
+    {256, 256, 512, 1, 1.24f, 1.46f},
+    {192, 128, 256, 2, 0.80f, 1.18f},
+    {128, 128, 256, 2, 0.52f, 0.84f},
+    {256, 64, 256, 2, 0.58f, 0.86f}};
+
+void launch_blk_gemm_as(int shape, bool split, const BlkGemm& p, hipStream_t st, float* part) {
+  const BlkShape& b = kBlkShapes[shape];
+  const int N = (p.NTILES - p.tile_first) * 16;
+  const int FB = (N + b.feat - 1) / b.feat, RB = (p.R + b.rows - 1) / b.rows;
+  const int blocks = FB * RB, per_xcd = (blocks + 7) / 8;
+  const dim3 grid(per_xcd * 8, 1, split ? p.pieces : 1), block(b.threads);
+  float* dst = split ? part : nullptr;
+#define STAIRS_BLK(WF, WR, NT, CT, ST)                                                                                                  \
+  do {                                                                                                                                  \
+    if (p.pieces > 1 && !split)                                                                                                         \
+      hipLaunchKernelGGL((k_gemm_bf16_block<WF, WR, NT, CT, ST, true>), grid, block, blk_lds_bytes(WF, WR, NT, CT, ST), st, p, dst, RB, per_xcd, blocks);  \
+    else                                                                                                                                \
+      hipLaunchKernelGGL((k_gemm_bf16_block<WF, WR, NT, CT, ST, false>), grid, block, blk_lds_bytes(WF, WR, NT, CT, ST), st, p, dst, RB, per_xcd, blocks); \
+  } while (0)
+  switch (shape) {
+    case 0:
+      hipLaunchKernelGGL((k_gemm_bf16_block<2, 4, 8, 4, 3, false>), grid, block, blk_lds_bytes(2, 4, 8, 4, 3), st, p, dst, RB, per_xcd, blocks);
+      break;
+    case 1: STAIRS_BLK(2, 2, 6, 4, 2); break;
+    case 2: STAIRS_BLK(2, 2, 4, 4, 3); break;
+    default: STAIRS_BLK(4, 1, 4, 4, 3); break;
+  }
+#undef STAIRS_BLK
+  if (split) {
+    hipLaunchKernelGGL(k_blk_reduce, dim3((N / 16 + 7) / 8, (p.R + 31) / 32), dim3(256), 0, st, p, part);
+  }
+}
+
+// Pieces of a k range for blocks of rows that belong to sequences of at most kBlkPiecedRows rows each: a function of K
+// alone, so that a row's bits are the same in whatever block it is computed.  About 32 k-steps a piece, at least 4 pieces:
+// between the best counts measured at 60 .. 333 rows (K = 2048: 5 .. 8, 4096: 3 .. 10, 8192: 10 .. 17, 11008: 5 .. 15,
+// all within 10 % of the best); beyond 1024 rows no launch gains from cutting k.
+static int blk_pieces(int K) {
+  const int ksteps = K / 32;
+  return std::min(ksteps / 8, std::max(4, ksteps / 32));
+}
+
+// The tile shape and the way the pieces are summed, by a model of the launch's time: rounds of work-groups over the 256
+// CUs, each k-step at the rate of the shape's occupancy, the matrix at the rate memory delivers it, and for a split
+// launch the pieces' way through memory and the second kernel.
+void launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t part_floats) {
+  p.pieces = pieced ? blk_pieces(p.K) : 1;
+  const int N = (p.NTILES - p.tile_first) * 16, ksteps = p.K / 32;
+  int best = 2;
+  bool best_split = false;
+  float best_us = 1e30f;
+  for (int s = 0; s < kBlkShapeCount; ++s) {
+    const BlkShape& b = kBlkShapes[s];
+    const int blocks = ((N + b.feat - 1) / b.feat) * ((p.R + b.rows - 1) / b.rows);
+    for (int split = 0; split < 2; ++split) {
+      if (split ? (p.pieces == 1 || !part || (size_t)p.pieces * ((p.R + 15) / 16 * 16) * N > part_floats) : (s == 0 && p.pieces > 1)) continue;
+      const int wgs = split ? blocks * p.pieces : blocks, slots = 256 * b.per_cu;
+      const int full = wgs / slots, rem = wgs - full * slots;
+      float rounds = full * b.t_full;
+      if (rem > 0) rounds += rem <= 256 ? b.t_one : b.t_one + (b.t_full - b.t_one) * (rem - 256) / (slots - 256 + 1);
+      float us = 5.f + rounds * (split ? (float)ksteps / p.pieces : (float)ksteps);
+      us = std::max(us, 5.f + (float)N * p.K * 2 / 5.5e6f);
+      if (split) us += 4.f + (2.f * p.pieces + 1.f) * p.R * N * 4 / 6e6f;
+      if (us < best_us) {
+        best_us = us;
+        best = s;
+        best_split = split != 0;
+      }
+    }
+  }
+  launch_blk_gemm_as(best, best_split, p, st, part);
+}
+
+// Attention of a row block without partial results (the rows of a 16-row tile belong to one sequence, see BlkSegs): a
+// wave owns 16 query rows of one head and walks over the keys 0 .. its last row's position (kv_fixed > 0: over the keys
+// 0 .. kv_fixed - 1 whatever the row, encoder), 32 at a time, keeping the running maximum, the running sum and the
 // running output of its rows in registers (rescaled whenever the maximum grows).  Same operands and splits as
 // k_attn_f16 (scores^T = K q^T with q as half high + low, out^T = V^T p^T with p as half high + low); the order of
-// the additions differs from the decode kernels, which only ever see their own results.
-template <int HD>
+// the additions differs from the decode kernels, which only ever see their own results.  The output is left as the
+// block fragments the output projection reads.
+template <int HD, bool BIAS>
 __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__ q, const _Float16* __restrict__ Kc,
-                                                    const _Float16* __restrict__ Vc, int cap, int d, int H, int R, int p0,
-                                                    float scale, float* __restrict__ out) {
+                                                    const _Float16* __restrict__ Vc, int cap, int d, size_t slot_stride,
+                                                    const int2* __restrict__ rows, int R, float scale, AttnMode am,
+                                                    uint4* __restrict__ frag, int RT) {
   constexpr int KK = HD / 32, ET = HD / 16;
   const int h = blockIdx.x;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -25,9 +556,15 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
   const int r0 = blockIdx.y * 64 + wave * 16;         // first row of this wave's tile
   if (r0 >= R) return;                                // no barriers in this kernel: waves are independent
   const int row = r0 + j;
-  const bool row_ok = row < R;
-  const int p_row = p0 + row;
-  const int tile_last = p0 + min(r0 + 15, R - 1);     // last position of the tile = last key any of its rows sees
+  const int2 at = row < R ? rows[row] : make_int2(0, -1);
+  const int slot = rows[r0].x;
+  const int pos = at.y;
+  const bool row_ok = pos >= 0;
+  const int seen_to = am.kv_fixed > 0 ? am.kv_fixed - 1 : pos;   // last key this lane's row sees
+  int tile_last = row_ok ? seen_to : -1;                         // last key any row of the tile sees
+#pragma unroll
+  for (int off = 1; off < 16; off <<= 1) tile_last = max(tile_last, __shfl_xor(tile_last, off));
+  tile_last = __builtin_amdgcn_readfirstlane(tile_last);
   f16x8 qh[KK], ql[KK];
 #pragma unroll
   for (int kk = 0; kk < KK; ++kk) {
@@ -40,8 +577,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
     const float v[8] = {a.x * scale, a.y * scale, a.z * scale, a.w * scale, b.x * scale, b.y * scale, b.z * scale, b.w * scale};
     split_half8(v, qh[kk], ql[kk]);
   }
-  const uint4* Kh = reinterpret_cast<const uint4*>(Kc + (size_t)h * cap * HD) + lane;
-  const uint4* Vh = reinterpret_cast<const uint4*>(Vc + (size_t)h * cap * HD) + lane;
+  const float* brow = BIAS ? am.bias + (size_t)h * am.bias_ld + am.bias_zero - pos : nullptr;   // bias by key position - query position
+  const uint4* Kh = reinterpret_cast<const uint4*>(Kc + slot * slot_stride + (size_t)h * cap * HD) + lane;
+  const uint4* Vh = reinterpret_cast<const uint4*>(Vc + slot * slot_stride + (size_t)h * cap * HD) + lane;
   f32x4 oacc[ET];
 #pragma unroll
   for (int et = 0; et < ET; ++et) oacc[et] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -70,7 +608,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
         const int key = kb + t * 16 + g * 4 + v;
-        sc[t * 4 + v] = (row_ok && key <= p_row) ? sacc[v] : -INFINITY;
+        const bool seen = row_ok && key <= seen_to;
+        const float bv = (BIAS && seen) ? brow[key] : 0.f;
+        sc[t * 4 + v] = seen ? sacc[v] + bv : -INFINITY;
       }
     }
     float mx = sc[0];
@@ -109,351 +649,30 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
     if (kb + 64 <= tile_last) load_kv(kb + 64, kA, vA);
     step(kb + 32, kB, vB);
   }
-  if (row_ok) {
-    const float inv = 1.0f / l_run;
+  if (row < R) {
+    const float inv = row_ok ? 1.0f / l_run : 0.f;    // (a padding row sees no key: zeros)
 #pragma unroll
     for (int et = 0; et < ET; ++et)
-      *reinterpret_cast<float4*>(out + (size_t)row * d + h * HD + et * 16 + g * 4) =
-          make_float4(oacc[et][0] * inv, oacc[et][1] * inv, oacc[et][2] * inv, oacc[et][3] * inv);
+      blk_store_frag4(frag, RT, row, h * HD + et * 16 + g * 4,
+                      make_float4(oacc[et][0] * inv, oacc[et][1] * inv, oacc[et][2] * inv, oacc[et][3] * inv));
   }
 }
 
-void launch_attention_flash(const float* q, const void* Kc, const void* Vc, int cap, int d, int H, int R, int p0, float* out,
-                            hipStream_t st) {
+void launch_attention_flash(const float* q, const void* Kc, const void* Vc, int cap, int d, int H, size_t slot_stride, const int2* rows,
+                            int R, uint4* frag, hipStream_t st, const AttnMode& am) {
   const int hd = d / H;
-  const float scale = 1.0f / sqrtf((float)hd);
+  const float scale = am.scale > 0.f ? am.scale : 1.0f / sqrtf((float)hd);
   const _Float16* K = static_cast<const _Float16*>(Kc);
   const _Float16* V = static_cast<const _Float16*>(Vc);
   dim3 grid(H, (R + 63) / 64);
-  if (hd == 128)
-    hipLaunchKernelGGL((k_attn_flash<128>), grid, dim3(256), 0, st, q, K, V, cap, d, H, R, p0, scale, out);
-  else
-    hipLaunchKernelGGL((k_attn_flash<64>), grid, dim3(256), 0, st, q, K, V, cap, d, H, R, p0, scale, out);
-}
-
-// ---------------------------------------------------------------------------------------
-// prompt ingestion in large row blocks: an MFMA-bound GEMM and the element-wise work around it
-// ---------------------------------------------------------------------------------------
-// Activations of a row block as MFMA B-operand fragments, written once by their producer: [k-step of 32][column tile
-// of 16 rows][high, low][lane] x 16 bytes (lane r + 16 g: x[16 ct + r][32 kt + 8 g .. + 8] as bf16 high part / bf16 of
-// the remainders).  RT = column tiles the buffer is laid out for (rows rounded up to a multiple of kBlkRows).
-__device__ __forceinline__ void pf_store_frag4(uint4* frag, int RT, int r, int k, const float (&v)[4]) {
-  uint2 hi, lo;
-  bf16_split2(v[0], v[1], hi.x, lo.x);
-  bf16_split2(v[2], v[3], hi.y, lo.y);
-  const size_t u4 = (((size_t)(k >> 5) * RT + (r >> 4)) * 2) * 64 + (r & 15) + 16 * ((k & 31) >> 3);
-  uint2* dst = reinterpret_cast<uint2*>(frag) + u4 * 2 + ((k & 7) >> 2);
-  dst[0] = hi;
-  dst[128] = lo;
-}
-
-// Y[R, N] (+)= X[R, K] . W[N, K]^T for row blocks of up to thousands of rows: the MFMA-bound regime.
-//   W: the operand-tile layout of the decode kernels (read as the MFMA A operand straight from memory, 1 KiB per load);
-//   X: block fragments (above), staged through LDS one k-step at a time, double-buffered, shared by the 8 waves.
-//   Work-group = 256 output features (16 weight tiles) x 128 rows (8 column tiles) on 8 waves, each 4 weight tiles x
-//   4 column tiles: a wave's k-step is 4 KiB of weights from memory, 8 KiB of fragments from LDS and 32 MFMAs (high and
-//   low part of x), fp32 accumulators [4][4] tiles.  Output columns are stored in natural order (the row permutation of the weight layout is undone:
-//   4 consecutive permuted rows are 4 consecutive features).  accumulate: Y += (the residual connections).
-//   One order of additions per output (k ascending, high before low): results do not depend on R or on the grid.
-constexpr int kBlkKs = 2;                              // k-steps per stage (the unit the k splits are counted in)
-constexpr int kBlkStageU4 = (kBlkRows / 16) * 2 * 64;  // uint4 per LDS buffer (one k-step): 1024 (16 KiB)
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_gemm_bf16_block(const uint4* __restrict__ Wsw, int NTILES, int K,
-                                                         const uint4* __restrict__ XF, int RT, int R,
-                                                         float* __restrict__ Y, int ldy, int perm, int p0, int p1,
-                                                         int accumulate, int stages_per_split, size_t split_stride) {
-  // 8 waves: wave = (row half rh, feature group fw); a wave owns 4 weight tiles x 4 column tiles (64 x 64 outputs)
-  // blockIdx.z = k split: with few rows and few features there are too few (feature, row) blocks to fill the chip, so
-  // the k range is cut into gridDim.z pieces whose results go to Y + z * split_stride and are added up, in split
-  // order, by k_block_reduce
-  constexpr int NT = 4, CT = kBlkRows / 32, CTW = kBlkRows / 16;
-  extern __shared__ uint4 lds[];                       // [2][kBlkStageU4]
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int fw = wave & 3, rh = wave >> 2;
-  const int j = lane & 15, g = lane >> 4;
-  const int tile0 = (blockIdx.x * 4 + fw) * NT;
-  const int ct0 = blockIdx.y * CTW;                    // first column tile of the work-group
-  const int units_total = K / kUnitK;
-  const int nstages_all = (K >> 5) / kBlkKs;           // K is a multiple of 256: whole stages
-  const int stage0 = blockIdx.z * stages_per_split;
-  const int nstages = min(nstages_all, stage0 + stages_per_split);     // this split's stages: [stage0, nstages)
-  Y += blockIdx.z * split_stride;
-  int tile_c[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) tile_c[t] = min(tile0 + t, NTILES - 1);
-
-  // this split's k-steps: [ks0, ks_end), a multiple of 4 (K is a multiple of 256 and a split an even number of stages)
-  const int ks0 = stage0 * kBlkKs, ks_end = nstages * kBlkKs, ks_last = ks_end - 1;
-  // weights of k-step s (past the split's end the last one is read again): 4 tiles x 1 KiB
-  auto load_a = [&](uint4 (&a)[NT], int s_) {
-    const int s = min(s_, ks_last), c = s >> 4, kk = s & 15;
-    const int ksteps_c = min(kSliceUnits, units_total - c * kSliceUnits) * 8;
-    const uint4* wbase = Wsw + (size_t)c * NTILES * (kSliceUnits * 8) * 64 + (size_t)kk * 64 + lane;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) a[t] = wbase[(size_t)tile_c[t] * ksteps_c * 64];
-  };
-  f32x4 acc[NT][CT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  // one k-step: the work-group's 8 column tiles x (high, low) are 1024 consecutive uint4 of LDS buffer buf
-  auto compute = [&](const uint4 (&a)[NT], int buf) {
-    const uint4* src = lds + buf * kBlkStageU4 + (rh * CT * 2) * 64 + lane;
-#pragma unroll
-    for (int ct = 0; ct < CT; ++ct) {
-      const bf16x8 vh = __builtin_bit_cast(bf16x8, src[(ct * 2) * 64]);
-      const bf16x8 vl = __builtin_bit_cast(bf16x8, src[(ct * 2 + 1) * 64]);
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const bf16x8 av = __builtin_bit_cast(bf16x8, a[t]);
-        acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, vh, acc[t][ct], 0, 0, 0);
-      }
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const bf16x8 av = __builtin_bit_cast(bf16x8, a[t]);
-        acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, vl, acc[t][ct], 0, 0, 0);
-      }
-    }
-  };
-  // Rings of four k-steps in registers, for the weights (4 x 16) and for the fragments on their way to LDS (4 x 8):
-  // before the arithmetic of k-step s, weights and fragments of k-step s + 3 are requested, so a request has three
-  // k-steps' arithmetic to come back in (with one stage of two k-steps the waves spent nearly half their cycles waiting for memory, also at
-  // thousands of rows); after the arithmetic the fragments of k-step s + 1 go to the other LDS buffer.  Four k-steps
-  // per turn of the loop name the rings' registers statically; a split's k-steps are a multiple of four, so no turn
-  // ends early.  All requests are unconditional.  Two waves per SIMD fill each other's waits for LDS and memory.
-  uint4 a0[NT], a1[NT], a2[NT], a3[NT];
-  uint4 b0_0, b0_1, b1_0, b1_1, b2_0, b2_1, b3_0, b3_1;    // (plain variables: small arrays ended up in scratch memory)
-#define STAIRS_LOAD_B(b, s_)                                                                      \
-  do {                                                                                            \
-    const uint4* src_ = XF + ((size_t)min((s_), ks_last) * RT + ct0) * 2 * 64 + tid;              \
-    b##_0 = src_[0];                                                                              \
-    b##_1 = src_[512];                                                                            \
-  } while (0)
-#define STAIRS_STORE_B(buf, b)                               \
-  do {                                                       \
-    uint4* dst_ = lds + (buf) * kBlkStageU4 + tid;           \
-    dst_[0] = b##_0;                                         \
-    dst_[512] = b##_1;                                       \
-  } while (0)
-  // k-step s in LDS buffer buf: ac = its weights, an / bn = the ring slots for k-step s + 3, bs = the fragments of s + 1
-#define STAIRS_BLOCK_STEP(ac, an, bn, bs, s, buf)            \
-  do {                                                       \
-    STAIRS_LOAD_B(bn, (s) + 3);                              \
-    load_a(an, (s) + 3);                                     \
-    __builtin_amdgcn_sched_barrier(0);                       \
-    compute(ac, buf);                                        \
-    STAIRS_STORE_B((buf) ^ 1, bs);                           \
-    __syncthreads();                                         \
-  } while (0)
-  STAIRS_LOAD_B(b0, ks0);
-  load_a(a0, ks0);
-  STAIRS_LOAD_B(b1, ks0 + 1);
-  load_a(a1, ks0 + 1);
-  STAIRS_LOAD_B(b2, ks0 + 2);
-  load_a(a2, ks0 + 2);
-  STAIRS_STORE_B(0, b0);
-  __syncthreads();
-  for (int ks = ks0; ks < ks_end; ks += 4) {
-    STAIRS_BLOCK_STEP(a0, a3, b3, b1, ks, 0);
-    STAIRS_BLOCK_STEP(a1, a0, b0, b2, ks + 1, 1);
-    STAIRS_BLOCK_STEP(a2, a1, b1, b3, ks + 2, 0);
-    STAIRS_BLOCK_STEP(a3, a2, b2, b0, ks + 3, 1);
+#define STAIRS_FLASH(hdv, bias) \
+  hipLaunchKernelGGL((k_attn_flash<hdv, bias>), grid, dim3(256), 0, st, q, K, V, cap, d, slot_stride, rows, R, scale, am, frag, pf_col_tiles(R))
+  if (hd == 128) {
+    if (am.bias) STAIRS_FLASH(128, true); else STAIRS_FLASH(128, false);
+  } else {
+    if (am.bias) STAIRS_FLASH(64, true); else STAIRS_FLASH(64, false);
   }
-#undef STAIRS_BLOCK_STEP
-#undef STAIRS_LOAD_B
-#undef STAIRS_STORE_B
-
-#pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    if (tile0 + t < NTILES) {
-      const size_t col = perm_row((tile0 + t) * 16 + 4 * g, perm, p0, p1);
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) {
-        const int row = (ct0 + rh * CT + ct) * 16 + j;
-        if (row < R) {
-          float4* dst = reinterpret_cast<float4*>(Y + (size_t)row * ldy + col);
-          float4 v = make_float4(acc[t][ct][0], acc[t][ct][1], acc[t][ct][2], acc[t][ct][3]);
-          if (accumulate) {
-            const float4 o = *dst;
-            v.x = v.x + o.x; v.y = v.y + o.y; v.z = v.z + o.z; v.w = v.w + o.w;
-          }
-          *dst = v;
-        }
-      }
-    }
-  }
-}
-
-// Y = (accumulate ? Y : 0) + part[0] + part[1] + ... (in that order): the k splits of a block GEMM with few rows
-__global__ __launch_bounds__(256) void k_block_reduce(const float* __restrict__ part, int nsplit, size_t split_stride, int R, int N,
-                                                      float* __restrict__ Y, int ldy, int accumulate) {
-  const int r = blockIdx.y, c = (blockIdx.x * 256 + threadIdx.x) * 4;
-  if (c >= N) return;
-  float4* dst = reinterpret_cast<float4*>(Y + (size_t)r * ldy + c);
-  float4 a = accumulate ? *dst : make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int z = 0; z < nsplit; ++z) {
-    const float4 v = *reinterpret_cast<const float4*>(part + z * split_stride + (size_t)r * N + c);
-    a.x = a.x + v.x; a.y = a.y + v.y; a.z = a.z + v.z; a.w = a.w + v.w;
-  }
-  *dst = a;
-}
-
-void launch_gemm_block(const void* W, int N, int K, const uint4* xfrag, int R, float* Y, int ldy, int perm, int p0, int p1,
-                       int accumulate, hipStream_t st, float* part, size_t part_floats) {
-  const int NTILES = N / 16;
-  const int FB = (NTILES + 15) / 16, RB = (R + kBlkRows - 1) / kBlkRows;
-  const int nstages = (K / 32) / kBlkKs;
-  // few (feature, row) blocks: cut k into pieces until about every CU has a work-group (each piece at least 8 stages
-  // and an even number of them), as far as the scratch for the pieces' results reaches
-  int nsplit = 1;
-  if (part && FB * RB < 160) {
-    nsplit = std::min({(256 + FB * RB - 1) / (FB * RB), nstages / 8, (int)(part_floats / ((size_t)R * N))});
-    nsplit = std::max(nsplit, 1);
-  }
-  int per = (nstages + nsplit - 1) / nsplit;
-  per += per & 1;
-  nsplit = (nstages + per - 1) / per;
-  dim3 grid(FB, RB, nsplit), block(512);
-  const size_t lds = 2 * kBlkStageU4 * sizeof(uint4);
-  if (nsplit == 1) {
-    hipLaunchKernelGGL(k_gemm_bf16_block, grid, block, lds, st, static_cast<const uint4*>(W), NTILES, K, xfrag, pf_col_tiles(R), R, Y,
-                       ldy, perm, p0, p1, accumulate, per, (size_t)0);
-    return;
-  }
-  const size_t stride = (size_t)R * N;
-  hipLaunchKernelGGL(k_gemm_bf16_block, grid, block, lds, st, static_cast<const uint4*>(W), NTILES, K, xfrag, pf_col_tiles(R), R, part,
-                     N, perm, p0, p1, 0, per, stride);
-  hipLaunchKernelGGL(k_block_reduce, dim3((N / 4 + 255) / 256, R), dim3(256), 0, st, part, nsplit, stride, R, N, Y, ldy, accumulate);
-}
-
-__global__ __launch_bounds__(256) void k_pf_embed(const uint16_t* __restrict__ emb, const int* __restrict__ tokens, int p0,
-                                                  int tok_cap, int vocab, int d, float* __restrict__ x) {
-  const int r = blockIdx.y, c = (blockIdx.x * 256 + threadIdx.x) * 4;
-  if (c >= d) return;
-  const int p = p0 + r;
-  const int id = (p >= 0 && p < tok_cap) ? tokens[p] : -1;     // as k_embed: never outside the array or the table
-  float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-  if (id >= 0 && id < vocab) {
-    const uint16_t* row = emb + (size_t)id * d + c;
-    v = make_float4(load_kv(row), load_kv(row + 1), load_kv(row + 2), load_kv(row + 3));
-  }
-  *reinterpret_cast<float4*>(x + (size_t)r * d + c) = v;
-}
-void launch_pf_embed(const uint16_t* emb, const int* tokens, int p0, int tok_cap, int vocab, int R, int d, float* x,
-                     hipStream_t st) {
-  hipLaunchKernelGGL(k_pf_embed, dim3((d + 1023) / 1024, R), dim3(256), 0, st, emb, tokens, p0, tok_cap, vocab, d, x);
-}
-
-__global__ __launch_bounds__(256) void k_pf_norm_split(const float* __restrict__ x, const float* __restrict__ gain, float eps,
-                                                       int d, uint4* __restrict__ frag, int RT) {
-  __shared__ float sm[4];
-  const int r = blockIdx.x, tid = threadIdx.x;
-  const float* row = x + (size_t)r * d;
-  float rstd = 1.0f;
-  if (gain) {
-    float ss = 0.f;
-    for (int c = tid * 4; c < d; c += 1024) {
-      const float4 v = *reinterpret_cast<const float4*>(row + c);
-      ss += sumsq4(v.x, v.y, v.z, v.w);
-    }
-    ss = block_sum_256(ss, sm);
-    rstd = 1.0f / sqrtf(ss / (float)d + eps);
-  }
-  for (int c = tid * 4; c < d; c += 1024) {
-    const float4 v = *reinterpret_cast<const float4*>(row + c);
-    float e[4] = {v.x, v.y, v.z, v.w};
-    if (gain) {
-      const float4 g = *reinterpret_cast<const float4*>(gain + c);
-      e[0] = e[0] * rstd * g.x; e[1] = e[1] * rstd * g.y; e[2] = e[2] * rstd * g.z; e[3] = e[3] * rstd * g.w;
-    }
-    pf_store_frag4(frag, RT, r, c, e);
-  }
-}
-void launch_pf_norm_split(const float* x, const float* gain, float eps, int R, int d, uint4* frag, hipStream_t st) {
-  hipLaunchKernelGGL(k_pf_norm_split, dim3(R), dim3(256), 0, st, x, gain, eps, d, frag, pf_col_tiles(R));
-}
-
-__global__ void k_pf_rope_table(int p0, int hd, double theta, float2* __restrict__ cs) {
-  const int r = blockIdx.x, i = threadIdx.x;
-  if (i >= hd / 2) return;
-  const double ang = (double)(p0 + r) * pow(theta, -2.0 * (double)i / (double)hd);
-  cs[r * 64 + i] = make_float2((float)cos(ang), (float)sin(ang));
-}
-void launch_pf_rope_table(int p0, int R, int hd, float theta, float2* cs, hipStream_t st) {
-  hipLaunchKernelGGL(k_pf_rope_table, dim3(R), dim3(64), 0, st, p0, hd, (double)theta, cs);
-}
-
-__global__ __launch_bounds__(256) void k_pf_rope_kv(const float* __restrict__ y, int d, int H, int hd, int p0,
-                                                    const float2* __restrict__ cs, float* __restrict__ q_rot,
-                                                    _Float16* __restrict__ Kc, _Float16* __restrict__ Vc, int cap) {
-  // thread = (row r, head h, pair e < hd/2)
-  const int r = blockIdx.y, half = hd >> 1;
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= H * half) return;
-  const int h = idx / half, e = idx - h * half;
-  const int p = p0 + r;
-  const float* yr = y + (size_t)r * 3 * d + h * hd;
-  const float2 c = cs[r * 64 + e];
-  const float2 q = rope_rotate(yr[e], yr[e + half], c);
-  q_rot[(size_t)r * d + h * hd + e] = q.x;
-  q_rot[(size_t)r * d + h * hd + e + half] = q.y;
-  const float2 k = rope_rotate(yr[d + e], yr[d + e + half], c);
-  _Float16* kd = Kc + (size_t)h * cap * hd;
-  store_kv(kd + k_cache_off(p, e, hd), k.x);
-  store_kv(kd + k_cache_off(p, e + half, hd), k.y);
-  _Float16* vd = Vc + (size_t)h * cap * hd;
-  store_kv(vd + v_cache_off(p, e, hd), yr[2 * d + e]);
-  store_kv(vd + v_cache_off(p, e + half, hd), yr[2 * d + e + half]);
-}
-// The same for rows that sit wherever `pos` puts them (several sequences: row r belongs to slot slot_of(pos, r), whose
-// caches start kv_slot_stride elements after the previous slot's); a row without a position writes nothing.
-__global__ __launch_bounds__(256) void k_pf_rope_kv_rows(const float* __restrict__ y, int d, int H, int hd, PosRef pos,
-                                                         size_t kv_slot_stride, const float2* __restrict__ cs,
-                                                         float* __restrict__ q_rot, _Float16* __restrict__ Kc,
-                                                         _Float16* __restrict__ Vc, int cap) {
-  const int r = blockIdx.y, half = hd >> 1;
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= H * half) return;
-  const int h = idx / half, e = idx - h * half;
-  const int p = pos_of(pos, r);
-  const float* yr = y + (size_t)r * 3 * d + h * hd;
-  const float2 c = cs[r * 64 + e];
-  const float2 q = rope_rotate(yr[e], yr[e + half], c);
-  q_rot[(size_t)r * d + h * hd + e] = q.x;
-  q_rot[(size_t)r * d + h * hd + e + half] = q.y;
-  if (p < 0 || p >= cap) return;
-  const size_t off = (size_t)slot_of(pos, r) * kv_slot_stride + (size_t)h * cap * hd;
-  const float2 k = rope_rotate(yr[d + e], yr[d + e + half], c);
-  store_kv(Kc + off + k_cache_off(p, e, hd), k.x);
-  store_kv(Kc + off + k_cache_off(p, e + half, hd), k.y);
-  store_kv(Vc + off + v_cache_off(p, e, hd), yr[2 * d + e]);
-  store_kv(Vc + off + v_cache_off(p, e + half, hd), yr[2 * d + e + half]);
-}
-void launch_pf_rope_kv_rows(const float* y, int R, int d, int H, PosRef pos, size_t kv_slot_stride, const float2* cs,
-                            float* q_rot, _Float16* Kc, _Float16* Vc, int cap, hipStream_t st) {
-  const int hd = d / H;
-  hipLaunchKernelGGL(k_pf_rope_kv_rows, dim3((H * hd / 2 + 255) / 256, R), dim3(256), 0, st, y, d, H, hd, pos, kv_slot_stride, cs,
-                     q_rot, Kc, Vc, cap);
-}
-
-void launch_pf_rope_kv(const float* y, int R, int d, int H, int p0, const float2* cs, float* q_rot, _Float16* Kc,
-                       _Float16* Vc, int cap, hipStream_t st) {
-  const int hd = d / H;
-  hipLaunchKernelGGL(k_pf_rope_kv, dim3((H * hd / 2 + 255) / 256, R), dim3(256), 0, st, y, d, H, hd, p0, cs, q_rot, Kc, Vc, cap);
-}
-
-__global__ __launch_bounds__(256) void k_pf_swiglu_split(const float* __restrict__ y, int f, uint4* __restrict__ frag, int RT) {
-  const int r = blockIdx.y, c = (blockIdx.x * 256 + threadIdx.x) * 4;
-  if (c >= f) return;
-  const float4 g = *reinterpret_cast<const float4*>(y + (size_t)r * 2 * f + c);
-  const float4 u = *reinterpret_cast<const float4*>(y + (size_t)r * 2 * f + f + c);
-  const float e[4] = {swiglu(g.x, u.x), swiglu(g.y, u.y), swiglu(g.z, u.z), swiglu(g.w, u.w)};
-  pf_store_frag4(frag, RT, r, c, e);
-}
-void launch_pf_swiglu_split(const float* y, int R, int f, uint4* frag, hipStream_t st) {
-  hipLaunchKernelGGL(k_pf_swiglu_split, dim3((f + 1023) / 1024, R), dim3(256), 0, st, y, f, frag, pf_col_tiles(R));
+#undef STAIRS_FLASH
 }
 
 hipError_t configure_block_kernels() {
@@ -462,7 +681,15 @@ hipError_t configure_block_kernels() {
     const hipError_t r = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (r != hipSuccess) e = r;
   };
-  optin((const void*)k_gemm_bf16_block, 2 * kBlkStageU4 * sizeof(uint4));
+#define STAIRS_OPTIN_BLK(WF, WR, NT, CT, ST, P) optin((const void*)k_gemm_bf16_block<WF, WR, NT, CT, ST, P>, blk_lds_bytes(WF, WR, NT, CT, ST))
+  STAIRS_OPTIN_BLK(2, 4, 8, 4, 3, false);
+  STAIRS_OPTIN_BLK(2, 2, 6, 4, 2, false);
+  STAIRS_OPTIN_BLK(2, 2, 6, 4, 2, true);
+  STAIRS_OPTIN_BLK(2, 2, 4, 4, 3, false);
+  STAIRS_OPTIN_BLK(2, 2, 4, 4, 3, true);
+  STAIRS_OPTIN_BLK(4, 1, 4, 4, 3, false);
+  STAIRS_OPTIN_BLK(4, 1, 4, 4, 3, true);
+#undef STAIRS_OPTIN_BLK
   return e;
 }
 

@@ -67,6 +67,24 @@ __device__ __forceinline__ void store_kv(uint16_t* p, float v) { *p = (uint16_t)
 __device__ __forceinline__ float load_kv(const _Float16* p) { return (float)*p; }
 __device__ __forceinline__ void store_kv(_Float16* p, float v) { *p = (_Float16)fminf(fmaxf(v, -65504.f), 65504.f); }
 
+// four adjacent halves of a key tile (one 8-byte store)
+__device__ __forceinline__ void store_kv4(_Float16* p, float4 v) {
+  _Float16 h[4];
+  store_kv(h, v.x); store_kv(h + 1, v.y); store_kv(h + 2, v.z); store_kv(h + 3, v.w);
+  *reinterpret_cast<uint2*>(p) = *reinterpret_cast<const uint2*>(h);
+}
+
+// Fragments of a row block (stairs_block.hip): row r, columns k .. k+3 (k a multiple of 4) of a buffer of RT column tiles
+__device__ __forceinline__ void blk_store_frag4(uint4* frag, int RT, int r, int k, float4 v) {
+  uint2 hi, lo;
+  bf16_split2(v.x, v.y, hi.x, lo.x);
+  bf16_split2(v.z, v.w, hi.y, lo.y);
+  const size_t u4 = (((size_t)(k >> 5) * RT + (r >> 4)) * 2) * 64 + (r & 15) + 16 * ((k & 31) >> 3);
+  uint2* dst = reinterpret_cast<uint2*>(frag) + u4 * 2 + ((k & 7) >> 2);
+  dst[0] = hi;
+  dst[128] = lo;
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);

@@ -154,11 +154,12 @@ struct AttnMode {
   int bias_ld, bias_zero;
   int kv_fixed;       // > 0: no causal mask, every row sees the keys 0 .. kv_fixed-1 (nchunk_launch must cover them)
   uint4* frag_out;    // half caches: also leave the output's activation fragments here (nullptr: none)
+  int frag_rt;        // 0: fragments in the decode kernels' layout; > 0: block fragments of that many column tiles
 };
 void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv_half, int cap, int d, int H, int M,
                       PosRef pos, int nslots, size_t kv_slot_stride, int nchunk_launch, int nchunk_cap, float* part_o,
                       float* part_ml, int* counters, float* out, hipStream_t st,
-                      const AttnMode& am = AttnMode{0.f, nullptr, 0, 0, 0, nullptr});
+                      const AttnMode& am = AttnMode{0.f, nullptr, 0, 0, 0, nullptr, 0});
 // out[o(r)] = argmax_v logits[row0 + r * row_stride][v], ties -> lowest v, r < nrows.  One sequence:
 // o(r) = *out_pos.base + out_pos.offset + r (base == nullptr: r).  Several: o(r) = s * out_slot_stride + position of
 // out_pos for row r, nothing written for a slot that is not active.
@@ -195,43 +196,70 @@ void launch_sample(const float* logits, int V, const SampleParams* sp, int strea
 void launch_accept_sampled(int* tokens, const float* tl, const float* dl, int ld, int V, int k, const float* lse,
                            const SampleParams* sp, int* state, int* emitted, SampleWs* ws, hipStream_t st);
 
-// ---- prompt ingestion in large row blocks (bf16 models) ------------------------------------------------
-// The projections of a block of up to kPfRows prompt rows run on the MFMA-bound kernel k_gemm_bf16_block: the weights
-// in the decode kernels' layout, the activations as fragments (bf16 high + low parts in operand order) written by
-// the element-wise kernel in front of each projection.
+// ---- row blocks (bf16 models): prompts, forwards of many sequences, encoders -------------------------------------
+// The projections of a block of up to kPfRows rows run on the MFMA-bound kernel k_gemm_bf16_block: the weights in the
+// decode kernels' layout, the activations as fragments (bf16 high + low parts in operand order).  Every producer of an
+// activation writes the next projection's fragments itself, with the gain of the norm in between folded in; the rows'
+// 1/rms multiplies the finished sums (partial sums of squares travel beside x).
 constexpr int kPfRows = 2048;
-constexpr int kBlkRows = 128;       // rows of one GEMM work-group; fragment buffers are laid out for whole groups
+constexpr int kBlkRows = 128;       // fragment buffers are laid out for whole groups of this many rows
+constexpr int kBlkSegRows = 16;     // a sequence's rows start at a multiple of this (one attention tile, one column tile)
+constexpr int kBlkSsqCols = 32;     // columns of x per sum-of-squares partial
+constexpr int kBlkPiecedRows = 1024;   // rows of sequences up to this long are summed in k pieces (launch_blk_gemm)
 inline int pf_col_tiles(int R) { return (R + kBlkRows - 1) / kBlkRows * (kBlkRows / 16); }
 // bytes of the fragments of a [R, K] activation block
 inline size_t pf_frag_bytes(int R, int K) { return (size_t)(K / 32) * pf_col_tiles(R) * 2 * 1024; }
-// Y[R, N] = (accumulate ? Y : 0) + X . W^T; W [N, K] in the operand-tile layout with row permutation (perm, p0, p1)
-// as given to launch_swizzle_bf16 (Y's columns are in natural order), xfrag the fragments of X [R, K]
-// part (optional, part_floats floats): scratch that lets a launch with few rows cut k into pieces for more work-groups
-// (the pieces' results are added in a fixed order by a second kernel)
-void launch_gemm_block(const void* W, int N, int K, const uint4* xfrag, int R, float* Y, int ldy, int perm, int p0, int p1,
-                       int accumulate, hipStream_t st, float* part = nullptr, size_t part_floats = 0);
-// x[r][:] = emb[tokens[p0 + r]][:] as float, r < R (zeros for a position outside [0, tok_cap) or an id outside [0, vocab))
-void launch_pf_embed(const uint16_t* emb, const int* tokens, int p0, int tok_cap, int vocab, int R, int d, float* x,
-                     hipStream_t st);
-// one row per work-group: v = x (gain == nullptr) or x * rstd * gain with rstd = 1/sqrt(mean(x^2) + eps);
-// frag = the block fragments of v (bf16(v) and bf16(v - bf16(v)))
-void launch_pf_norm_split(const float* x, const float* gain, float eps, int R, int d, uint4* frag, hipStream_t st);
-// cs[r][i] = (cos, sin)((p0 + r) * theta^(-2i/hd)), angle in double
-void launch_pf_rope_table(int p0, int R, int hd, float theta, float2* cs, hipStream_t st);
-// y = [R, 3d] (q | k | v, natural column order): rotate q and k, q -> q_rot [R, d] float, k and v -> the tiled half
-// caches of one layer at positions p0 .. p0+R-1
-void launch_pf_rope_kv(const float* y, int R, int d, int H, int p0, const float2* cs, float* q_rot, _Float16* Kc,
-                       _Float16* Vc, int cap, hipStream_t st);
-// the same for R rows positioned by `pos` (several sequences: slot s's caches start s * kv_slot_stride elements in);
-// rows without a position write nothing to the caches
-void launch_pf_rope_kv_rows(const float* y, int R, int d, int H, PosRef pos, size_t kv_slot_stride, const float2* cs,
-                            float* q_rot, _Float16* Kc, _Float16* Vc, int cap, hipStream_t st);
-// attention of a prefill block: R consecutive rows at positions p0.. of ONE sequence against its half caches (keys
-// 0 .. own position), q and out [R, d]; running softmax in registers (no partial results, no merge), a wave per 16 rows
-void launch_attention_flash(const float* q, const void* Kc, const void* Vc, int cap, int d, int H, int R, int p0, float* out,
-                            hipStream_t st);
-// y = [R, 2f] (gate | up): h = silu(gate) * up, written as block fragments of [R, f]
-void launch_pf_swiglu_split(const float* y, int R, int f, uint4* frag, hipStream_t st);
+
+// Where a block's rows sit: segment s is len[s] consecutive positions from pos0[s] on of sequence slot slot[s], at rows
+// row0[s] .. (row0[0] = 0, row0 ascending multiples of kBlkSegRows); rows behind a segment's last are padding.
+constexpr int kBlkMaxSegs = 128;
+struct BlkSegs {
+  int n;
+  int row0[kBlkMaxSegs], len[kBlkMaxSegs], slot[kBlkMaxSegs], pos0[kBlkMaxSegs];
+};
+// rows[r] = (slot, position; < 0 for padding), cs[r][i] = (cos, sin)(position * theta^(-2i/hd)), theta <= 0: (1, 0)
+void launch_blk_rows(const BlkSegs& segs, int R, int hd, float theta, int2* rows, float2* cs, hipStream_t st);
+void launch_blk_rows_pos(PosRef pos, int R, int hd, float theta, int2* rows, float2* cs, hipStream_t st);
+// x = the rows' embeddings, frag = fragments of x * gain, ssq [R][d / kBlkSsqCols]
+void launch_blk_embed(const uint16_t* emb, const int* tokens, int tok_stride, int tok_cap, int vocab, const int2* rows, int R, int d,
+                      float* x, const float* gain, uint4* frag, float* ssq, hipStream_t st);
+
+// What a block projection does with its sums (after the rows' 1/rms, when ssq is given):
+//   Plain : out[row][n] = sum (W without row permutation)
+//   Resid : out = x [R, ldo] += sum; frag_out (optional) = fragments of x * gain; ssq_out (optional) = its partials
+//   Swiglu: W = gate/up tiles; frag_out = fragments of silu(gate) * up
+//   QKV   : W = q | k | v tiles of da columns each; out = rotated q [R, da]; k, v -> the tiled half caches at rows[r]
+//   Relu  : frag_out = fragments of max(sum, 0)
+enum { kBlkPlain = 0, kBlkResid, kBlkSwiglu, kBlkQKV, kBlkRelu };
+struct BlkGemm {
+  const uint4* W;              // operand tiles of [N, K]
+  int NTILES, tile_first, K;   // N / 16; output tiles before tile_first are left out
+  const uint4* XF;             // fragments of the input [R, K]
+  int RT, R;                   // column tiles the fragment buffers (XF, frag_out) are laid out for; rows
+  int kind;
+  float* out;
+  int ldo;
+  const float* ssq;            // partials of the input's rows [R][ssq_n], or nullptr: no normalisation
+  int ssq_n;
+  float eps;
+  uint4* frag_out;
+  const float* gain;
+  float* ssq_out;
+  const int2* rows;
+  const float2* cs;
+  _Float16 *Kc, *Vc;
+  size_t slot_stride;          // elements between the caches of consecutive slots
+  int cap, hd, da;
+  int pieces;                  // set by launch_blk_gemm
+};
+// pieced: the k range is summed in a number of pieces that depends on K alone (rows of sequences of at most
+// kBlkPiecedRows rows: their results are the same bits in whatever block they are computed), else in one.
+// part (part_floats floats): scratch that lets different work-groups take the pieces.
+void launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t part_floats);
+// attention of the block's rows against their sequences' half caches (slot_stride elements apart), output as block
+// fragments; am: scale, bias, kv_fixed as for launch_attention
+void launch_attention_flash(const float* q, const void* Kc, const void* Vc, int cap, int d, int H, size_t slot_stride, const int2* rows,
+                            int R, uint4* frag, hipStream_t st, const AttnMode& am = AttnMode{0.f, nullptr, 0, 0, 0, nullptr, 0});
 
 // dst[0..bytes) = src[0..bytes), bytes a multiple of 16: reads `bytes` and writes `bytes` of HBM
 void launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream_t st);

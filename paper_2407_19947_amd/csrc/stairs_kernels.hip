@@ -1640,6 +1640,12 @@ __global__ void k_attn_combine(const float* __restrict__ part_o, const float* __
 //   (p as half hi+lo).  The four waves are merged in LDS in wave order, the chunks of a head by the
 //   work-group that arrives last at the head's counter, in chunk order.
 // ---------------------------------------------------------------------------------------
+// the attention output's fragments, in the layout the next projection reads (AttnMode::frag_rt)
+__device__ __forceinline__ void store_attn_frag4(uint4* frag, int frag_rt, int m, int k, float4 v) {
+  if (frag_rt > 0) blk_store_frag4(frag, frag_rt, m, k, v);
+  else store_frag4(frag, m, k, v, nullptr);
+}
+
 // Merge of the chunk partials of one head (one slot): out[m] = sum_c w_c o_c / sum_c w_c l_c with w_c = exp(max_c - max).
 // Step A: all (max, sum) pairs of all rows go to LDS in one round trip, then the row maxima and, in place of the chunk
 // maxima, the weights w_c (one exp per row and chunk; formed per thread they made up most of the merge's time).
@@ -1697,7 +1703,7 @@ __device__ __forceinline__ void attn_merge_table(const float* part_ml, int H, in
 template <int HD, int CB, int IPT>
 __device__ __forceinline__ void attn_merge_direct(const float* part_o, const float* part_ml, int H, int h, int M, int pos0,
                                                   int step, int nch_max, int nchunk_cap, int nch_lds, float* out, int d,
-                                                  float* s_ml, uint4* frag, int frag_row0) {
+                                                  float* s_ml, uint4* frag, int frag_rt, int frag_row0) {
   constexpr int QPR = HD / 4;                         // threads per row
   const int tid = threadIdx.x, items = M * QPR;
   float2 va[IPT][CB], vb[IPT][CB];
@@ -1745,7 +1751,7 @@ __device__ __forceinline__ void attn_merge_direct(const float* part_o, const flo
           res = make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
         }
         *reinterpret_cast<float4*>(out + (size_t)m * d + h * HD + e) = res;
-        if (frag) store_frag4(frag, frag_row0 + m, h * HD + e, res, nullptr);
+        if (frag) store_attn_frag4(frag, frag_rt, frag_row0 + m, h * HD + e, res);
       }
     }
   }
@@ -1755,15 +1761,15 @@ __device__ __forceinline__ void attn_merge_direct(const float* part_o, const flo
 template <int HD>
 __device__ __forceinline__ void attn_merge(const float* part_o, const float* part_ml, int H, int h, int M, int pos0, int step,
                                            int kv_len, int nchunk_cap, int nch_lds, int rows_per_pass, float* out, int d,
-                                           float* s_ml, uint4* frag, int frag_row0) {
+                                           float* s_ml, uint4* frag, int frag_rt, int frag_row0) {
   const int tid = threadIdx.x;
   const int nch_max = (kv_len > 0) ? (kv_len - 1) / kAttnChunkH + 1 : 0;
   if (nch_max <= kMergeCB / 2)                        // (no chunk at all: every row gets zeros)
     return attn_merge_direct<HD, kMergeCB / 2, 2>(part_o, part_ml, H, h, M, pos0, step, nch_max, nchunk_cap, nch_lds, out, d,
-                                                  s_ml, frag, frag_row0);
+                                                  s_ml, frag, frag_rt, frag_row0);
   if (nch_max <= kMergeCB)
     return attn_merge_direct<HD, kMergeCB, 1>(part_o, part_ml, H, h, M, pos0, step, nch_max, nchunk_cap, nch_lds, out, d,
-                                              s_ml, frag, frag_row0);
+                                              s_ml, frag, frag_rt, frag_row0);
   // more chunks: groups of kMergeCB chunks summed in parallel, the group sums added in group order
   float* grp = s_ml + (size_t)M * nch_lds * 2 + kMaxRows;   // (kMaxRows floats after the table stay unused)
   attn_merge_table(part_ml, H, h, M, pos0, step, nch_max, nchunk_cap, nch_lds, s_ml);
@@ -1822,7 +1828,7 @@ __device__ __forceinline__ void attn_merge(const float* part_o, const float* par
         res = make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
       }
       *reinterpret_cast<float4*>(out + (size_t)m * d + h * HD + e) = res;
-      if (frag) store_frag4(frag, frag_row0 + m, h * HD + e, res, nullptr);
+      if (frag) store_attn_frag4(frag, frag_rt, frag_row0 + m, h * HD + e, res);
     }
     __syncthreads();
   }
@@ -2038,7 +2044,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
           float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
           if (pos0 + m * step >= 0) res = make_float4(o0 / lc, o1 / lc, o2 / lc, o3 / lc);
           *reinterpret_cast<float4*>(out + (size_t)m * d + h * HD + e) = res;
-          if (am.frag_out) store_frag4(am.frag_out, row0 + m, h * HD + e, res, nullptr);
+          if (am.frag_out) store_attn_frag4(am.frag_out, am.frag_rt, row0 + m, h * HD + e, res);
         } else {
           float* po = &part_o[(((size_t)m * H + h) * nchunk_cap + c) * HD + e];
           st_dev2(po, o0, o1);
@@ -2055,7 +2061,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
   if (!last_arrival(&counters[h], (int)gridDim.x, &s_last)) return;
   extern __shared__ float s_ml[];
   attn_merge<HD>(part_o, part_ml, H, h, M, pos0, step, kv_len, nchunk_cap, (int)gridDim.x, rows_per_pass, out, d, s_ml,
-                 am.frag_out, row0);
+                 am.frag_out, am.frag_rt, row0);
   if (tid == 0) counters[h] = 0;
 }
 
@@ -2063,14 +2069,14 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
 template <int HD>
 __global__ __launch_bounds__(256) void k_attn_merge(const float* part_o, const float* part_ml, int d, int H, int M, PosRef pos,
                                                     int kv_fixed, int nchunk_cap, int nch_lds, int rows_per_pass,
-                                                    float* __restrict__ out, uint4* frag) {
+                                                    float* __restrict__ out, uint4* frag, int frag_rt) {
   extern __shared__ float s_ml[];
   const int h = blockIdx.x, row0 = blockIdx.y * M;
   const bool fixed = kv_fixed > 0;
   const int pos0 = fixed ? kv_fixed - 1 : pos_of(pos, row0);
   attn_merge<HD>(part_o + (size_t)row0 * H * nchunk_cap * HD, part_ml + (size_t)row0 * H * nchunk_cap * 2, H, h, M, pos0,
                  fixed ? 0 : 1, pos0 + (fixed ? 1 : M), nchunk_cap, nch_lds, rows_per_pass, out + (size_t)row0 * d, d, s_ml,
-                 frag, row0);
+                 frag, frag_rt, row0);
 }
 
 template <typename KV, int HD>
@@ -2122,7 +2128,7 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
     hipLaunchKernelGGL((k_attn_f16<hdv, ct, false>), grid, block, 0, st, q_rot, K, V, cap, d, H, M, pos, kv_slot_stride,    \
                        scale, am, nchunk_cap, rpp, part_o, part_ml, counters, out);                                         \
     hipLaunchKernelGGL((k_attn_merge<hdv>), dim3(H, nslots), dim3(256), lds, st, part_o, part_ml, d, H, M, pos,             \
-                       am.kv_fixed, nchunk_cap, nchunk_launch, rpp, out, am.frag_out);                                      \
+                       am.kv_fixed, nchunk_cap, nchunk_launch, rpp, out, am.frag_out, am.frag_rt);                                      \
   }
     if (hd == 128) {
       if (M <= 16) STAIRS_ATTN16(128, 1) else STAIRS_ATTN16(128, 2)
