@@ -841,26 +841,31 @@ int encode_model(stairs_ctx* c, Model* m) {
   return STAIRS_OK;
 }
 
-// Positions [from, to) of sequence slot `slot` into a model's cache in blocks of up to kPfRows rows; attention on
-// k_attn_flash (its keys include the block's own rows, appended just before).
-int ingest_blocks(stairs_ctx* c, Model* m, int from, int to, int slot) {
+// The rows of `segs` (R rows with their padding) into a model's caches; attention on k_attn_flash (its keys include the
+// block's own rows, appended just before).
+int ingest_segs(stairs_ctx* c, Model* m, const BlkSegs& segs, int R, bool pieced) {
   const stairs_model_cfg& g = m->cfg;
   const int d = g.d_model, H = g.n_heads;
   const size_t slot_stride = (size_t)g.n_layers * m->kv_layer_bytes / m->esz();
-  for (int p0 = from; p0 < to; p0 += c->pf_rows) {
+  launch_blk_rows(segs, R, m->hd, g.rope_theta, c->pf_rowinfo, c->pf_cs, c->st);
+  launch_blk_embed(static_cast<const uint16_t*>(m->tok_emb), c->tokens, c->tok_stride, c->tok_stride, g.vocab, c->pf_rowinfo, R, d,
+                   c->pf_x, m->layers[0].attn_norm, c->pf_fa, c->pf_ssq, c->st);
+  return block_layers(c, m, R, pieced, false, [&](const char* Kl, const char* Vl) {
+    launch_attention_flash(c->pf_q, Kl, Vl, m->cap, d, H, slot_stride, c->pf_rowinfo, R, c->pf_fb, c->st);
+  });
+}
+
+// Positions [from, to) of sequence slot `slot` into a model's cache in blocks of up to kPfRows rows
+int ingest_blocks(stairs_ctx* c, Model* m, int from, int to, int slot) {
+  const int rows = std::min(kPfRows, c->pf_rows);
+  for (int p0 = from; p0 < to; p0 += rows) {
     BlkSegs segs;
     segs.n = 1;
     segs.row0[0] = 0;
-    segs.len[0] = std::min(c->pf_rows, to - p0);
+    segs.len[0] = std::min(rows, to - p0);
     segs.slot[0] = slot;
     segs.pos0[0] = p0;
-    const int R = segs.len[0];
-    launch_blk_rows(segs, R, m->hd, g.rope_theta, c->pf_rowinfo, c->pf_cs, c->st);
-    launch_blk_embed(static_cast<const uint16_t*>(m->tok_emb), c->tokens, c->tok_stride, c->tok_stride, g.vocab, c->pf_rowinfo, R, d,
-                     c->pf_x, m->layers[0].attn_norm, c->pf_fa, c->pf_ssq, c->st);
-    int rc = block_layers(c, m, R, R <= kBlkPiecedRows, false, [&](const char* Kl, const char* Vl) {
-      launch_attention_flash(c->pf_q, Kl, Vl, m->cap, d, H, slot_stride, c->pf_rowinfo, R, c->pf_fb, c->st);
-    });
+    const int rc = ingest_segs(c, m, segs, segs.len[0], segs.len[0] <= kBlkPiecedRows);
     if (rc) return rc;
   }
   return STAIRS_OK;
@@ -884,6 +889,43 @@ int ingest(stairs_ctx* c, Model* m, int from, int to, int slot = 0) {
   }
   if (slot == 0 && to > m->valid) m->valid = to;
   return STAIRS_OK;
+}
+
+// Whether ingest() takes `rows` rows of one sequence in one block whose k range is summed in pieces: then they give the
+// same bits in a block they share with other sequences.
+bool shares_blocks(const stairs_ctx* c, const Model* m, int rows) {
+  return c->block_prefill && (!c->sync_launches || c->sync_blocks) && m->bf16 && !m->encdec && rows >= kBlockPrefillMin &&
+         rows <= std::min(kBlkPiecedRows, c->pf_rows);
+}
+
+// The prompts of slots 0 .. B-1 (P[b] - 1 rows each, from position 0) into a model's caches.  Prompts of up to
+// kBlkPiecedRows rows share blocks, so the weights are read and the tiles are filled once for as many of them as fit
+// (16 prompts of 40 .. 300 tokens one by one: 180 block GEMMs of 68 us); longer and very short ones go one by one.
+int ingest_prompts(stairs_ctx* c, Model* m, const int32_t* P, int B) {
+  BlkSegs segs;
+  int R = 0, rc;
+  segs.n = 0;
+  auto flush = [&]() {
+    const int r = segs.n ? ingest_segs(c, m, segs, R, true) : STAIRS_OK;
+    segs.n = R = 0;
+    return r;
+  };
+  for (int b = 0; b < B; ++b) {
+    const int rows = P[b] - 1;
+    if (!shares_blocks(c, m, rows)) {
+      if ((rc = ingest(c, m, 0, rows, b))) return rc;
+      continue;
+    }
+    if ((segs.n == kBlkMaxSegs || R + rows > c->pf_rows) && (rc = flush())) return rc;
+    segs.row0[segs.n] = R;
+    segs.len[segs.n] = rows;
+    segs.slot[segs.n] = b;
+    segs.pos0[segs.n] = 0;
+    ++segs.n;
+    R += (rows + kBlkSegRows - 1) / kBlkSegRows * kBlkSegRows;
+    R = std::min(R, c->pf_rows);                        // (the last one's padding past the buffers is left out)
+  }
+  return flush();
 }
 
 // Enqueue the draft's k greedy steps.  Positions are taken relative to the device-side sequence
@@ -1186,6 +1228,47 @@ int stairs_init(stairs_ctx** out, const stairs_model_cfg* tcfg, const stairs_wei
   return STAIRS_OK;
 }
 
+static void release(stairs_ctx* c, void* p) {
+  auto it = std::find(c->owned.begin(), c->owned.end(), p);
+  if (it != c->owned.end()) c->owned.erase(it);
+  (void)hipFree(p);
+}
+
+// the block workspaces, for blocks of `rows` rows; earlier ones are given back (nothing may be running on them)
+static int alloc_block_rows(stairs_ctx* c, int rows) {
+  int dmax = c->T.cfg.d_model, inner = std::max(dmax, c->T.cfg.d_ffn);
+  if (c->have_draft) {
+    dmax = std::max(dmax, c->D.cfg.d_model);
+    inner = std::max({inner, dmax, c->D.cfg.d_ffn});
+  }
+  float *x = nullptr, *q = nullptr, *ssq = nullptr, *attn = nullptr;
+  int2* info = nullptr;
+  uint4 *fa = nullptr, *fb = nullptr;
+  float2* cs = nullptr;
+  int rc;
+  if ((rc = dev_alloc(c, &x, (size_t)rows * dmax)) || (rc = dev_alloc(c, &q, (size_t)rows * dmax)) ||
+      (rc = dev_alloc(c, &ssq, (size_t)rows * (dmax / kBlkSsqCols))) || (rc = dev_alloc(c, &info, (size_t)rows)) ||
+      (rc = dev_alloc(c, &attn, (size_t)std::min(rows, kMaxBlockRows) * dmax)) ||
+      (rc = dev_alloc(c, &fa, pf_frag_bytes(rows, dmax) / sizeof(uint4))) ||
+      (rc = dev_alloc(c, &fb, pf_frag_bytes(rows, inner) / sizeof(uint4))) || (rc = dev_alloc(c, &cs, (size_t)rows * 64)))
+    return rc;
+  // rows of a block past its last one are read by the GEMM (and their results dropped): they must hold numbers
+  HIPCHK(c, hipMemsetAsync(fa, 0, pf_frag_bytes(rows, dmax), c->st));
+  HIPCHK(c, hipMemsetAsync(fb, 0, pf_frag_bytes(rows, inner), c->st));
+  for (void* old : {(void*)c->pf_x, (void*)c->pf_q, (void*)c->pf_ssq, (void*)c->pf_rowinfo, (void*)c->pf_attn, (void*)c->pf_fa, (void*)c->pf_fb, (void*)c->pf_cs})
+    if (old) release(c, old);
+  c->pf_x = x;
+  c->pf_q = q;
+  c->pf_ssq = ssq;
+  c->pf_rowinfo = info;
+  c->pf_attn = attn;
+  c->pf_fa = fa;
+  c->pf_fb = fb;
+  c->pf_cs = cs;
+  c->pf_rows = rows;
+  return STAIRS_OK;
+}
+
 // workspaces, token array, state, counters, pinned host mirror, events
 static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
   int rc;
@@ -1216,22 +1299,10 @@ static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
     return bail(rc);
   if (c->block_prefill) {
     // rows per block: what the longest sequence needs, at most kPfRows
-    const int rows = std::min(kPfRows, (capmax + kBlkRows - 1) / kBlkRows * kBlkRows);
-    c->pf_rows = rows;
-    const int inner = std::max(dmax, fmax);
-    if ((rc = dev_alloc(c, &c->pf_x, (size_t)rows * dmax)) || (rc = dev_alloc(c, &c->pf_q, (size_t)rows * dmax)) ||
-        (rc = dev_alloc(c, &c->pf_ssq, (size_t)rows * (dmax / kBlkSsqCols))) || (rc = dev_alloc(c, &c->pf_rowinfo, (size_t)rows)) ||
-        (rc = dev_alloc(c, &c->pf_attn, (size_t)std::min(rows, kMaxBlockRows) * dmax)) ||
-        (rc = dev_alloc(c, &c->pf_fa, pf_frag_bytes(rows, dmax) / sizeof(uint4))) ||
-        (rc = dev_alloc(c, &c->pf_fb, pf_frag_bytes(rows, inner) / sizeof(uint4))) ||
-        (rc = dev_alloc(c, &c->pf_cs, (size_t)rows * 64)))
-      return bail(rc);
+    if ((rc = alloc_block_rows(c, std::min(kPfRows, (capmax + kBlkRows - 1) / kBlkRows * kBlkRows)))) return bail(rc);
     // blocks of few rows have too few (feature, row) tiles for the chip: their GEMMs cut k and need room for the pieces
     c->pf_part_floats = (size_t)16 << 20;
     if ((rc = dev_alloc(c, &c->pf_part, c->pf_part_floats))) return bail(rc);
-    // rows of a block past its last one are read by the GEMM (and their results dropped): they must hold numbers
-    if (hipMemsetAsync(c->pf_fa, 0, pf_frag_bytes(rows, dmax), c->st) != hipSuccess) return bail(STAIRS_EHIP);
-    if (hipMemsetAsync(c->pf_fb, 0, pf_frag_bytes(rows, inner), c->st) != hipSuccess) return bail(STAIRS_EHIP);
   }
   // every slot of the token array always holds a valid id: a diagnostic forward may run at positions the current
   // sequence has not reached, and the embedding gather takes whatever id it finds there
@@ -1636,11 +1707,6 @@ int stairs_reserve_batch(stairs_ctx* c, int32_t max_batch) {
   for (auto& g : c->graphs) (void)hipGraphExecDestroy(g.exec);
   c->graphs.clear();
   // new, larger arrays; the old ones are released
-  auto release = [&](void* p) {
-    auto it = std::find(c->owned.begin(), c->owned.end(), p);
-    if (it != c->owned.end()) c->owned.erase(it);
-    (void)hipFree(p);
-  };
   int rc;
   for (Model* m : {&c->T, &c->D}) {
     if (m == &c->D && !c->have_draft) continue;
@@ -1649,8 +1715,8 @@ int stairs_reserve_batch(stairs_ctx* c, int32_t max_batch) {
     if ((rc = dev_alloc(c, &K, bytes)) || (rc = dev_alloc(c, &V, bytes))) return rc;
     HIPCHK(c, hipMemsetAsync(K, 0, bytes, c->st));
     HIPCHK(c, hipMemsetAsync(V, 0, bytes, c->st));
-    release(m->Kc);
-    release(m->Vc);
+    release(c, m->Kc);
+    release(c, m->Vc);
     m->Kc = K;
     m->Vc = V;
     m->valid = 0;
@@ -1671,15 +1737,20 @@ int stairs_reserve_batch(stairs_ctx* c, int32_t max_batch) {
         (rc = dev_alloc(c, &po, (size_t)want_rows * Hmax * c->nchunk_cap * 128)) ||
         (rc = dev_alloc(c, &pm, (size_t)want_rows * Hmax * c->nchunk_cap * 2)) || (rc = dev_alloc(c, &tt, (size_t)want_rows)))
       return rc;
-    release(c->logits);
-    release(c->part_o);
-    release(c->part_ml);
-    release(c->tgt_tok);
+    release(c, c->logits);
+    release(c, c->part_o);
+    release(c, c->part_ml);
+    release(c, c->tgt_tok);
     c->logits = lg;
     c->part_o = po;
     c->part_ml = pm;
     c->tgt_tok = tt;
     c->rows_cap = want_rows;
+  }
+  // the prompts of several sequences share blocks: rows for as many as fit kPfRows
+  if (c->block_prefill) {
+    const long want = std::min<long>(kPfRows, ((long)max_batch * ((c->tok_cap + kBlkSegRows - 1) / kBlkSegRows * kBlkSegRows) + kBlkRows - 1) / kBlkRows * kBlkRows);
+    if (want > c->pf_rows && (rc = alloc_block_rows(c, (int)want))) return rc;
   }
   if (max_batch >= 2) {
     int kmax = std::max(c->T.cfg.d_model, c->T.cfg.d_ffn);
@@ -1691,8 +1762,8 @@ int stairs_reserve_batch(stairs_ctx* c, int32_t max_batch) {
     return rc;
   HIPCHK(c, hipMemsetAsync(tok, 0, (size_t)max_batch * c->tok_stride * sizeof(int), c->st));
   HIPCHK(c, hipMemsetAsync(state, 0, (size_t)(max_batch + 1) * kSlotState * sizeof(int), c->st));
-  release(c->tokens);
-  release(c->state);
+  release(c, c->tokens);
+  release(c, c->state);
   c->tokens = tok;
   c->state = state;
   int* hp = nullptr;
@@ -1738,8 +1809,11 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
   HIPCHK(c, hipEventRecord(c->ev[0], c->st));
   std::vector<int> L(B), L0(B), hstate((size_t)B * kSlotState);
   std::vector<char> active(B, 1), ended(B, 0);
+  // all prompts in one copy, padded to the longest (the positions behind a prompt are written before they are read)
+  const int Pmax = *std::max_element(P, P + B);
+  std::vector<int> packed((size_t)B * Pmax, 0);
   for (int b = 0; b < B; ++b) {
-    HIPCHK(c, hipMemcpyAsync(c->tokens + (size_t)b * c->tok_stride, prompts[b], (size_t)P[b] * sizeof(int), hipMemcpyHostToDevice, c->st));
+    memcpy(packed.data() + (size_t)b * Pmax, prompts[b], (size_t)P[b] * sizeof(int));
     L[b] = L0[b] = P[b];
     hstate[b * kSlotState + 0] = P[b];
     hstate[b * kSlotState + 1] = 0;
@@ -1747,14 +1821,14 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
     hstate[b * kSlotState + 3] = G > 0 ? 1 : 0;
     active[b] = G > 0;
   }
+  HIPCHK(c, hipMemcpy2DAsync(c->tokens, (size_t)c->tok_stride * sizeof(int), packed.data(), (size_t)Pmax * sizeof(int), (size_t)Pmax * sizeof(int), B,
+                             hipMemcpyHostToDevice, c->st));
   HIPCHK(c, hipMemcpyAsync(c->state, hstate.data(), hstate.size() * sizeof(int), hipMemcpyHostToDevice, c->st));
   HIPCHK(c, hipStreamSynchronize(c->st));
-  // prompt ingestion, one sequence at a time (rows of one slot per forward)
-  for (int b = 0; b < B; ++b)
-    for (Model* m : {&c->T, &c->D}) {
-      if (m == &c->D && !c->have_draft) continue;
-      if ((rc = ingest(c, m, 0, P[b] - 1, b))) return rc;
-    }
+  for (Model* m : {&c->T, &c->D}) {
+    if (m == &c->D && !c->have_draft) continue;
+    if ((rc = ingest_prompts(c, m, P, B))) return rc;
+  }
   c->T.valid = c->D.valid = 0;     // nothing the single-sequence calls could rely on
   HIPCHK(c, hipEventRecord(c->ev[1], c->st));
   int n_active = G > 0 ? B : 0;
@@ -1809,10 +1883,7 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
         hstate[b * kSlotState + 0] = L[b];
         hstate[b * kSlotState + 3] = active[b];
       }
-      // only the active flags change on the device (L is already there)
-      for (int b = 0; b < B; ++b)
-        if (!active[b])
-          HIPCHK(c, hipMemcpyAsync(c->state + b * kSlotState + 3, &hstate[b * kSlotState + 3], sizeof(int), hipMemcpyHostToDevice, c->st));
+      HIPCHK(c, hipMemcpyAsync(c->state, hstate.data(), hstate.size() * sizeof(int), hipMemcpyHostToDevice, c->st));
       HIPCHK(c, hipStreamSynchronize(c->st));
     }
     float a = 0.f, bms = 0.f;
@@ -1827,14 +1898,22 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
   HIPCHK(c, hipEventElapsedTime(&s.ms_prefill, c->ev[0], c->ev[1]));
   HIPCHK(c, hipEventElapsedTime(&s.ms_decode, c->ev[1], c->ev[2]));
   s.tokens = 0;
-  for (int b = 0; b < B && G > 0; ++b) {
-    const int got = std::min(G, L[b] - L0[b]);
-    s.tokens += got;
-    HIPCHK(c, hipMemcpyAsync(tokens_out + (size_t)b * G, c->tokens + (size_t)b * c->tok_stride + L0[b], (size_t)got * sizeof(int),
-                             hipMemcpyDeviceToHost, c->st));
-    for (int i = got; i < G; ++i) tokens_out[(size_t)b * G + i] = c->eos_id;
+  if (G > 0) {                                          // the answers in one copy: the columns any of them lies in
+    const int first = *std::min_element(L0.begin(), L0.end());
+    int end = first;
+    for (int b = 0; b < B; ++b) end = std::max(end, L0[b] + std::min(G, L[b] - L0[b]));
+    const int cols = end - first;
+    std::vector<int> got((size_t)B * cols);
+    HIPCHK(c, hipMemcpy2DAsync(got.data(), (size_t)cols * sizeof(int), c->tokens + first, (size_t)c->tok_stride * sizeof(int),
+                               (size_t)cols * sizeof(int), B, hipMemcpyDeviceToHost, c->st));
+    HIPCHK(c, hipStreamSynchronize(c->st));
+    for (int b = 0; b < B; ++b) {
+      const int n = std::min(G, L[b] - L0[b]);
+      s.tokens += n;
+      memcpy(tokens_out + (size_t)b * G, got.data() + (size_t)b * cols + (L0[b] - first), (size_t)n * sizeof(int));
+      for (int i = n; i < G; ++i) tokens_out[(size_t)b * G + i] = c->eos_id;
+    }
   }
-  HIPCHK(c, hipStreamSynchronize(c->st));
   if (stats) *stats = s;
   return STAIRS_OK;
 }

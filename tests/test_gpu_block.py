@@ -30,3 +30,20 @@ def test_block_rows_against_decode_kernels(d, heads, f, rows, monkeypatch):
             got[mode] = s.verify(0, logits=True)[2].astype(np.float64)
     rms = np.sqrt(np.mean(got["rows"] ** 2))
     assert np.max(np.abs(got["block"] - got["rows"])) < 2e-3 * rms
+
+
+@pytest.mark.parametrize("lens", [[18, 33, 34, 49, 300, 18], [17, 200, 5, 1025, 1026, 65, 1300], [700, 700, 700, 129]])
+def test_prompts_of_a_batch_share_blocks(lens):
+    """Prompts that share a block (17 .. 1024 rows: the smallest, ends on and beside multiples of 16 rows, more than one block's
+    worth), too short, and too long to share one: every sequence's tokens are the bits of the sequence generated alone."""
+    w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=512, n_heads=4, d_ffn=768, vocab=1040),
+                           draft=dict(kind="prefix", n_layers=1), P=2, G=1)
+    target, draft = si.make_pair(w)
+    rng = np.random.default_rng(len(lens))
+    prompts = [rng.integers(0, 1040, P).astype(np.int32) for P in lens]
+    with pkg.Stairs(target, draft, k_max=2, max_seq=max(lens) + 32) as s:
+        alone = [s.generate(p, 12, 2)[0].copy() for p in prompts]
+        s.reserve_batch(len(lens))
+        toks, _ = s.generate_batch(prompts, 12, 2)
+    for b, want in enumerate(alone):
+        assert np.array_equal(toks[b], want), lens[b]
