@@ -93,11 +93,10 @@ struct stairs_ctx {
   float* pf_part = nullptr;    // k pieces of block GEMMs with few rows
   size_t pf_part_floats = 0;
   float2* pf_cs = nullptr;
-  // encoder-decoder contexts: source tokens and the encoder's activations [max_src, .]
+  // encoder-decoder contexts: source tokens (the encoder runs on the block workspaces)
   bool encdec = false;
   int start_token = 0, S = 0;   // S = length of the encoded source
   int* src_tok = nullptr;
-  float *enc_x = nullptr, *enc_ssq = nullptr, *enc_q = nullptr;
   // sampling variant: parameters on the device, the assistant's logits rows of the pending proposal, log-sum-exps
   SampleParams* samp = nullptr;
   SampleWs* samp_ws = nullptr;
@@ -666,12 +665,10 @@ PosRef abs_pos(const stairs_ctx* c, int p) { return PosRef{c->state + 2, p}; }  
 PosRef rel_pos(const stairs_ctx* c, int off) { return PosRef{c->state, off}; }     // state[0] == L, kept on the device
 int chunks_for(int kv_len) { return (std::max(kv_len, 1) + kAttnChunk - 1) / kAttnChunk; }
 
-// The feed-forward block of an encoder-decoder layer on M rows of x (ssq = their sum-of-squares partials):
-// x += W_out relu(W_in norm(x)); h = workspace [M, f].
+// The feed-forward block of a decoder layer on the M rows of c->x: x += W_out relu(W_in norm(x)).
 // frags: x comes with its activation fragments in c->xf (gain of ffn_norm folded in), the hidden activations leave
 // theirs in c->hf and the result its own in c->xf with next_gain folded in (forwards of more than 4 rows)
-void launch_ed_ffn(stairs_ctx* c, const Model* m, const EdLayer& ly, float* x, float* ssq, int M, bool frags = false,
-                   const float* next_gain = nullptr) {
+void launch_ed_ffn(stairs_ctx* c, const Model* m, const EdLayer& ly, int M, bool frags, const float* next_gain) {
   const int d = m->cfg.d_model, f = m->cfg.d_ffn, sn = ssq_groups(d, 1);
   const RowNorm none{nullptr, nullptr, 0, 0.f};
   GemmEpi e{};
@@ -681,11 +678,11 @@ void launch_ed_ffn(stairs_ctx* c, const Model* m, const EdLayer& ly, float* x, f
   e.out = c->h;
   e.act = kActRelu;
   e.frag_out = frags ? c->hf : nullptr;
-  RowNorm fn{ly.ffn_norm, ssq, sn, m->cfg.rms_eps};
-  launch_gemm(kRoleHead, 1, ly.w_in, f, d, x, d, M, fn, c->partial, e, c->st, frags ? c->xf : nullptr);
+  RowNorm fn{ly.ffn_norm, c->ssq, sn, m->cfg.rms_eps};
+  launch_gemm(kRoleHead, 1, ly.w_in, f, d, c->x, d, M, fn, c->partial, e, c->st, frags ? c->xf : nullptr);
   e.act = kActNone;
-  e.out = x;
-  e.ssq_out = ssq;
+  e.out = c->x;
+  e.ssq_out = c->ssq;
   e.frag_out = frags ? c->xf : nullptr;
   e.frag_gain = next_gain;
   launch_gemm(kRoleDown, 1, ly.w_out, d, f, c->h, f, M, none, c->partial, e, c->st, frags ? c->hf : nullptr);
@@ -761,7 +758,7 @@ int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logit
     e.frag_gain = ly.ffn_norm;
     launch_gemm(kRoleWo, 1, ly.co, d, a, c->attn_out, a, M, none, c->partial, e, st, af);
     SYNCPOINT();
-    launch_ed_ffn(c, m, ly, c->x, c->ssq, M, fr, l + 1 < g.n_layers ? m->dec[l + 1].attn_norm : m->final_norm);
+    launch_ed_ffn(c, m, ly, M, fr, l + 1 < g.n_layers ? m->dec[l + 1].attn_norm : m->final_norm);
     SYNCPOINT();
   }
   if (logits_rows > 0) {
@@ -779,64 +776,66 @@ int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logit
   return STAIRS_OK;
 }
 
-// Encoder of one model over the c->S source tokens in c->src_tok, 32 rows at a time through the decode kernels:
-// per layer first the keys and values of all rows (every row attends to every source position), then attention
-// with the two-sided position bias, output projection and feed-forward block by block.  Afterwards the
-// cross-attention keys and values of every decoder layer are formed from the normalised encoder output.
+// Encoder of one model over the c->S source tokens in c->src_tok, all rows in one block: per layer the keys and values of
+// all rows (every row attends to every source position) by the QKV projection's epilogue, attention with the two-sided
+// position bias, output projection and feed-forward.  Afterwards the cross-attention keys and values of every decoder
+// layer are formed from the normalised encoder output.  (Through the decode kernels, 32 rows at a time, every weight was
+// streamed once per 32 rows: 777 tokens through 3 + 1 layers of the wide shape 11 ms, 3 layers' projections 15 .. 27 us
+// per 32 rows each.)
 int encode_model(stairs_ctx* c, Model* m) {
   const stairs_model_cfg& g = m->cfg;
-  const int d = g.d_model, a = m->da, H = g.n_heads, S = c->S;
-  const int sn = ssq_groups(d, 1);
+  const int d = g.d_model, a = m->da, f = g.d_ffn, H = g.n_heads, S = c->S;
   hipStream_t st = c->st;
-  const int nch = chunks_for(S);
-  if (S < 1 || S > m->max_src || nch > c->nchunk_cap) return fail(c, STAIRS_EINVAL, "encode: source outside the workspaces");
-  const RowNorm none{nullptr, nullptr, 0, 0.f};
+  if (S < 1 || S > m->max_src || S > c->pf_rows) return fail(c, STAIRS_EINVAL, "encode: source outside the workspaces");
+  BlkSegs segs;
+  segs.n = 1;
+  segs.row0[0] = segs.slot[0] = segs.pos0[0] = 0;
+  segs.len[0] = S;
+  launch_blk_rows(segs, S, m->hd, 0.f, c->pf_rowinfo, c->pf_cs, st);
+  launch_blk_embed(static_cast<const uint16_t*>(m->tok_emb), c->src_tok, 0, S, g.vocab, c->pf_rowinfo, S, d, c->pf_x, m->enc[0].attn_norm,
+                   c->pf_fa, c->pf_ssq, st);
   const AttnMode mode{1.f, m->enc_bias, 2 * m->max_src - 1, m->max_src - 1, S, nullptr, 0};
-  auto rows_of = [&](int b) { return std::min(kMaxRows, S - b); };
-  auto epi_for = [&](int b, char* K, char* V, float* out) {
-    GemmEpi e{};
-    e.counters = c->counters;
-    e.stream_weights = m->stream_weights;
-    e.rope_cs = c->rope_cs;
-    e.pos = abs_pos(c, b);
-    e.Kc = reinterpret_cast<_Float16*>(K);
-    e.Vc = reinterpret_cast<_Float16*>(V);
-    e.cap = m->cap_src;
-    e.H = H;
-    e.hd = m->hd;
-    e.ssq_out = c->enc_ssq + (size_t)b * sn;
-    e.out = out;
-    return e;
+  BlkGemm p{};
+  p.RT = pf_col_tiles(S);
+  p.R = S;
+  p.ssq_n = d / kBlkSsqCols;
+  p.eps = g.rms_eps;
+  p.rows = c->pf_rowinfo;
+  p.cs = c->pf_cs;
+  p.cap = m->cap_src;
+  p.hd = m->hd;
+  p.da = a;
+  auto gemm = [&](int kind, const void* W, int N, int K, int tile_first, const uint4* in, const float* ssq, float* out, uint4* frag_out, const float* gain) {
+    p.kind = kind;
+    p.W = static_cast<const uint4*>(W);
+    p.NTILES = N / 16;
+    p.tile_first = tile_first;
+    p.K = K;
+    p.XF = in;
+    p.ssq = ssq;
+    p.out = out;
+    p.ldo = N;
+    p.frag_out = frag_out;
+    p.gain = gain;
+    p.ssq_out = kind == kBlkResid ? c->pf_ssq : nullptr;
+    launch_blk_gemm(p, S <= kBlkPiecedRows, st, c->pf_part, c->pf_part_floats);
+    return c->sync_launches ? hipStreamSynchronize(st) : hipSuccess;
   };
-  auto normed = [&](const float* gain, int b, int M) {
-    RowNorm n{gain, c->enc_ssq + (size_t)b * sn, sn, g.rms_eps};
-    return n;
-  };
-  for (int b = 0; b < S; b += kMaxRows)
-    launch_embed(m->tok_emb, 1, c->src_tok, 0, S, g.vocab, abs_pos(c, b), rows_of(b), d, c->enc_x + (size_t)b * d,
-                 c->enc_ssq + (size_t)b * sn, m->hd, 0.f, c->rope_cs, st);
   for (size_t l = 0; l < m->enc.size(); ++l) {
     const EdLayer& ly = m->enc[l];
-    for (int b = 0; b < S; b += kMaxRows) {
-      const int M = rows_of(b);
-      launch_gemm(kRoleQKV, 1, ly.wqkv, 3 * a, d, c->enc_x + (size_t)b * d, d, M, normed(ly.attn_norm, b, M), c->partial,
-                  epi_for(b, m->Ke, m->Ve, c->enc_q + (size_t)b * a), st);
-    }
-    for (int b = 0; b < S; b += kMaxRows) {
-      const int M = rows_of(b);
-      launch_attention(c->enc_q + (size_t)b * a, m->Ke, m->Ve, 1, m->cap_src, a, H, M, abs_pos(c, b), 1, 0, nch, c->nchunk_cap,
-                       c->part_o, c->part_ml, c->counters + kGemmCounters, c->attn_out, st, mode);
-      launch_gemm(kRoleWo, 1, ly.wo, d, a, c->attn_out, a, M, none, c->partial, epi_for(b, m->Ke, m->Ve, c->enc_x + (size_t)b * d), st);
-      launch_ed_ffn(c, m, ly, c->enc_x + (size_t)b * d, c->enc_ssq + (size_t)b * sn, M);
-    }
-    if (c->sync_launches) HIPCHK(c, hipStreamSynchronize(st));
+    p.Kc = reinterpret_cast<_Float16*>(m->Ke);
+    p.Vc = reinterpret_cast<_Float16*>(m->Ve);
+    HIPCHK(c, gemm(kBlkQKV, ly.wqkv, 3 * a, d, 0, c->pf_fa, c->pf_ssq, c->pf_q, nullptr, nullptr));
+    launch_attention_flash(c->pf_q, m->Ke, m->Ve, m->cap_src, a, H, 0, c->pf_rowinfo, S, c->pf_fb, st, mode);
+    HIPCHK(c, gemm(kBlkResid, ly.wo, d, a, 0, c->pf_fb, nullptr, c->pf_x, c->pf_fa, ly.ffn_norm));
+    HIPCHK(c, gemm(kBlkRelu, ly.w_in, f, d, 0, c->pf_fa, c->pf_ssq, nullptr, c->pf_fb, nullptr));
+    HIPCHK(c, gemm(kBlkResid, ly.w_out, d, f, 0, c->pf_fb, nullptr, c->pf_x, c->pf_fa, l + 1 < m->enc.size() ? m->enc[l + 1].attn_norm : m->enc_final_norm));
   }
-  for (size_t l = 0; l < m->dec.size(); ++l)
-    for (int b = 0; b < S; b += kMaxRows) {
-      const int M = rows_of(b);
-      launch_gemm(kRoleQKV, 1, m->dec[l].cqkv, 3 * a, d, c->enc_x + (size_t)b * d, d, M, normed(m->enc_final_norm, b, M), c->partial,
-                  epi_for(b, m->Kx + l * m->kvx_layer_bytes, m->Vx + l * m->kvx_layer_bytes, c->enc_q + (size_t)b * a), st);
-    }
+  for (size_t l = 0; l < m->dec.size(); ++l) {         // (the q tiles are left out)
+    p.Kc = reinterpret_cast<_Float16*>(m->Kx + l * m->kvx_layer_bytes);
+    p.Vc = reinterpret_cast<_Float16*>(m->Vx + l * m->kvx_layer_bytes);
+    HIPCHK(c, gemm(kBlkQKV, m->dec[l].cqkv, 3 * a, d, a / 16, c->pf_fa, c->pf_ssq, c->pf_q, nullptr, nullptr));
+  }
   HIPCHK(c, hipGetLastError());
   return STAIRS_OK;
 }
@@ -1236,17 +1235,18 @@ static void release(stairs_ctx* c, void* p) {
 
 // the block workspaces, for blocks of `rows` rows; earlier ones are given back (nothing may be running on them)
 static int alloc_block_rows(stairs_ctx* c, int rows) {
-  int dmax = c->T.cfg.d_model, inner = std::max(dmax, c->T.cfg.d_ffn);
+  int dmax = c->T.cfg.d_model, wide = std::max(dmax, c->T.da), inner = std::max(wide, c->T.cfg.d_ffn);
   if (c->have_draft) {
     dmax = std::max(dmax, c->D.cfg.d_model);
-    inner = std::max({inner, dmax, c->D.cfg.d_ffn});
+    wide = std::max({wide, dmax, c->D.da});
+    inner = std::max({inner, wide, c->D.cfg.d_ffn});
   }
   float *x = nullptr, *q = nullptr, *ssq = nullptr, *attn = nullptr;
   int2* info = nullptr;
   uint4 *fa = nullptr, *fb = nullptr;
   float2* cs = nullptr;
   int rc;
-  if ((rc = dev_alloc(c, &x, (size_t)rows * dmax)) || (rc = dev_alloc(c, &q, (size_t)rows * dmax)) ||
+  if ((rc = dev_alloc(c, &x, (size_t)rows * dmax)) || (rc = dev_alloc(c, &q, (size_t)rows * wide)) ||
       (rc = dev_alloc(c, &ssq, (size_t)rows * (dmax / kBlkSsqCols))) || (rc = dev_alloc(c, &info, (size_t)rows)) ||
       (rc = dev_alloc(c, &attn, (size_t)std::min(rows, kMaxBlockRows) * dmax)) ||
       (rc = dev_alloc(c, &fa, pf_frag_bytes(rows, dmax) / sizeof(uint4))) ||
@@ -1278,11 +1278,7 @@ static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
   c->nchunk_cap = (std::max(capmax, w.srcmax) + kAttnChunk - 1) / kAttnChunk;
   c->tok_cap = capmax;
   c->tok_stride = capmax + kMaxRows;
-  if (w.srcmax > 0 &&
-      ((rc = dev_alloc(c, &c->src_tok, (size_t)w.srcmax + kMaxRows)) || (rc = dev_alloc(c, &c->enc_x, (size_t)w.srcmax * dmax)) ||
-       (rc = dev_alloc(c, &c->enc_ssq, (size_t)w.srcmax * ssq_groups(dmax, 1))) ||
-       (rc = dev_alloc(c, &c->enc_q, (size_t)w.srcmax * w.amax))))
-    return rc;
+  if (w.srcmax > 0 && (rc = dev_alloc(c, &c->src_tok, (size_t)w.srcmax + kMaxRows))) return rc;
   // (activations and their fragments for kMaxFwdRows rows: a few MB; what grows with the context or the vocabulary
   // is sized for rows_cap rows and enlarged by stairs_reserve_batch)
   if (frag_bytes(std::max(wide, fmax)) > kFragHalfU4 * 16) return fail(c, STAIRS_EINVAL, "d_model / d_ffn too large for the activation fragment blocks");
@@ -1297,9 +1293,10 @@ static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
       (rc = dev_alloc(c, &c->rope_cs, (size_t)kMaxFwdRows * 64)) || (rc = dev_alloc(c, &c->tokens, (size_t)c->tok_cap + kMaxRows)) ||
       (rc = dev_alloc(c, &c->tgt_tok, (size_t)kMaxRows)) || (rc = dev_alloc(c, &c->counters, (size_t)kCounters)) || (rc = dev_alloc(c, &c->state, 2 * kSlotState)))
     return bail(rc);
-  if (c->block_prefill) {
-    // rows per block: what the longest sequence needs, at most kPfRows
-    if ((rc = alloc_block_rows(c, std::min(kPfRows, (capmax + kBlkRows - 1) / kBlkRows * kBlkRows)))) return bail(rc);
+  if (c->block_prefill || c->encdec) {
+    // rows per block: what the longest sequence needs, at most kPfRows; encoders take the whole source as one block
+    const int rows = ((c->encdec ? w.srcmax : capmax) + kBlkRows - 1) / kBlkRows * kBlkRows;
+    if ((rc = alloc_block_rows(c, c->encdec ? rows : std::min(kPfRows, rows)))) return bail(rc);
     // blocks of few rows have too few (feature, row) tiles for the chip: their GEMMs cut k and need room for the pieces
     c->pf_part_floats = (size_t)16 << 20;
     if ((rc = dev_alloc(c, &c->pf_part, c->pf_part_floats))) return bail(rc);
