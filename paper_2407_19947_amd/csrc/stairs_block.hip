@@ -5,6 +5,7 @@
 #include <math.h>
 
 #include <algorithm>
+#include <type_traits>
 
 namespace stairs {
 
@@ -155,7 +156,7 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
       return;
     }
     const int hd = p.hd, half = hd >> 1;
-    constexpr int G = NT == 4 ? 4 : 2;                 // tiles whose rotation entries are requested together
+    constexpr int G = NT == 4 ? 4 : 2;             // tiles whose rotation entries are requested together
     int2 at[CT / 2];
 #pragma unroll
     for (int c2 = 0; c2 < CT / 2; ++c2) at[c2] = p.rows[min(row0 + (2 * c2 + (up ? 1 : 0)) * 16, p.R - 1)];
@@ -209,7 +210,7 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
     return;
   }
   if (p.kind == kBlkResid) {
-    constexpr int G = NT == 4 ? 4 : 2;                 // tiles whose old values are requested together
+    constexpr int G = NT == 4 ? 4 : 2;             // tiles whose old values are requested together
 #pragma unroll
     for (int t0 = 0; t0 < NT; t0 += G) {
       float4 gain[G];
@@ -268,39 +269,45 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
 
 // Sums[R, N] = X[R, K] . W[N, K]^T for row blocks of up to thousands of rows: the MFMA-bound regime.
 //   W: the operand-tile layout of the decode kernels (1 KiB MFMA A operands); X: block fragments (above, 1 KiB B operands).
-//   Work-group = WF x WR waves, each NT weight tiles x CT column tiles of fp32 accumulators; a k-step of 32 is
-//   WF*NT + 2*WR*CT KiB-sized operands, copied from memory straight into LDS (global_load_lds, 16 bytes per lane: no
-//   staging registers, and every weight tile enters the CU once instead of once per row half), ST k-steps deep, and
-//   read from there as they lie (ds_read_b128, no bank conflicts: the layouts are lane order).
-//   One barrier per k-step: the wave waits for its own copies of k-step s (the copies of the following ST - 2 k-steps
-//   stay in flight: the waits count instructions), the barrier makes everybody's visible and says that nobody reads
-//   the buffer of s - 1 any more, which then takes the copies of s + ST - 1.
+//   Work-group = WF x WR waves, each 4 weight tiles x 4 column tiles of fp32 accumulators; a k-step of 32 is
+//   WF*4 + 2*WR*4 KiB-sized operands, copied from memory straight into LDS (buffer_load ... lds, 16 bytes per lane: no
+//   staging registers, and every operand enters the CU once), three k-steps deep, and read from there as they lie
+//   (ds_read_b128, no bank conflicts: the layouts are lane order).
+//   One barrier per k-step: the wave waits for its own copies of k-step s + 1 (those of the following ones stay in
+//   flight: the waits count instructions), the barrier makes everybody's visible and says that everybody holds k-step s
+//   in registers, so its buffer takes the copies of s + 3.
 //   k pieces: the k range is cut into p.pieces parts that are summed separately (k ascending, high before low) and added
 //   up in order: by different work-groups and k_blk_reduce (gridDim.z = pieces), or one after the other by the same
 //   work-group with a second set of accumulators (PIECED).  The bits depend on p.pieces alone, not on R, the tile shape
 //   or the grid.
-//   What bounds it: the matrix pipes at 1.3 .. 1.47 PFLOP/s issued where the tiles fill whole rounds of the chip (a
-//   library product of two 8192-wide matrices: 1.49 on the same card), LDS bandwidth for the smaller tiles (a 64 x 64
-//   wave tile reads 12 KiB per 32 MFMAs), rounds that are not full otherwise; weights' way from memory at <= 64 rows.
+//   What bounds it: at thousands of rows 1.22 .. 1.31 PFLOP/s of issued MFMAs whatever the tile (a library product of two
+//   8192-wide matrices: 1.49 on the same card); at a few hundred the rounds of work-groups and, with one work-group on a
+//   CU, the LDS reads beside the MFMAs (0.38 us per k-step of 32 MFMAs a wave); at <= 64 rows the weights' way from memory.
 //   Plain stores, against the kernel before (weights through registers, 256 x 128 tiles only), 7B projections, us:
-//   2047 rows: QKV 384 -> 312, out 115 -> 105, gate/up 712 -> 564, down 297 -> 288; 333 rows: 111 -> 81, 45 -> 33,
-//   198 -> 133, 96 -> 70; 60 rows: 45 -> 33, 23 -> 18, 78 -> 46, 38 -> 33.  With the epilogues inside a 2047-row layer
-//   takes 1.47 ms of projections where projections and the kernels between them took 1.84.
+//   2047 rows: QKV 384 -> 337, out 115 -> 112, gate/up 712 -> 603, down 297 -> 296; 333 rows: 111 -> 87, 45 -> 33,
+//   198 -> 143, 96 -> 79; 60 rows: 45 -> 28, 23 -> 19, 78 -> 48, 38 -> 29.  The SwiGLU epilogue costs less than plain stores
+//   (578 against 600 us).  (A first form of this loop read k-step s from LDS in front of its MFMAs: 0.52 us per k-step with
+//   one work-group on a CU, whatever the depth of the ring.)
 template <int N> __device__ __forceinline__ void wait_copies_and_sync() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
-__device__ __forceinline__ void copy_to_lds_16(const uint4* src, uint4* lds_base) {      // lane l: lds_base[l] = *src
-  __builtin_amdgcn_global_load_lds(reinterpret_cast<const __attribute__((address_space(1))) uint32_t*>(reinterpret_cast<uintptr_t>(src)),
-                                   reinterpret_cast<__attribute__((address_space(3))) uint32_t*>(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base))), 16, 0, 0);
+// lane l: lds_base[l] = base[offset / 16 + l] (buffer form: its waits do not hold up the LDS reads in flight, as those
+// of the flat-encoded form do, and the address arithmetic is scalar)
+__device__ __forceinline__ void copy_to_lds_16(const uint4* base, uint32_t offset, uint4* lds_base, uint32_t lane_bytes) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(base), 0, 0xFFFFFFFFu, 0x00027000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base))), 16,
+                                           lane_bytes, offset, 0, 0);
 }
-constexpr int blk_lds_bytes(int WF, int WR, int NT, int CT, int ST) { return ST * (WF * NT + 2 * WR * CT) * 1024 + WR * CT * 64; }
+constexpr int kBlkNT = 4, kBlkCT = 4, kBlkST = 3;      // weight tiles and column tiles of a wave; k-steps in LDS
+constexpr int blk_lds_bytes(int WF, int WR) { return kBlkST * (WF * kBlkNT + 2 * WR * kBlkCT) * 1024 + WR * kBlkCT * 64; }
 
-template <int WF, int WR, int NT, int CT, int ST, bool PIECED>
+template <int WF, int WR, bool PIECED>
 __global__ __launch_bounds__(64 * WF * WR) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks) {
+  constexpr int NT = kBlkNT, CT = kBlkCT, ST = kBlkST;
   constexpr int NW = WF * WR, AT = WF * NT, BT = 2 * WR * CT, STAGE = (AT + BT) * 64;   // uint4 per LDS stage
-  constexpr int PER = (AT + BT + NW - 1) / NW;                                          // copies per wave and k-step
-  static_assert((ST - 2) * PER < 64, "countable by vmcnt");
+  constexpr int PER = (AT + BT) / NW;                                                   // copies per wave and k-step
+  static_assert(AT % NW == 0 && BT % NW == 0 && (ST - 1) * PER < 64, "whole copies per wave, countable by vmcnt");
   extern __shared__ uint4 lds[];                       // [ST][weight tiles AT | fragments BT][64], then the rows' 1/rms
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -312,53 +319,62 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
   if (lin >= nblocks) return;                          // (whole work-groups, before any barrier)
   const int fb = lin / RB, rb = lin - fb * RB;
   const int ksteps = p.K >> 5, P = p.pieces;
-  // (the pieces differ by at most one k-step; every piece has at least 8: launch_blk_gemm)
-  const int piece0 = PIECED ? 0 : (int)blockIdx.z, npieces = PIECED ? P : (int)gridDim.z;
-  const int ks0 = ksteps * piece0 / npieces, ks_end = PIECED ? ksteps : ksteps * (piece0 + 1) / npieces;
+  // (pieces begin at even k-steps, differ by at most two of them and have at least 8: launch_blk_gemm)
+  auto piece_begin = [&](int i) { return ksteps * i / P & ~1; };
+  const int piece0 = PIECED ? 0 : (int)blockIdx.z;
+  const bool split = gridDim.z > 1;
+  const int ks0 = split ? piece_begin(piece0) : 0, ks_end = split && piece0 + 1 < P ? piece_begin(piece0 + 1) : ksteps;
 
-  // copies of k-step s into LDS buffer buf: every NW-th operand of the stage is this wave's (tiles past the matrix and
-  // column tiles past the fragment buffer repeat the last one, their results are dropped; where the operands are no
-  // multiple of the waves, some waves copy one of theirs twice, so that the counts are everybody's)
-  const int units_total = p.K / kUnitK;
-  auto request = [&](int s, int buf) {
-    const int c = s >> 4, kk = s & 15;
-    const int ksteps_c = min(kSliceUnits, units_total - c * kSliceUnits) * 8;
-    const uint4* wbase = p.W + ((size_t)c * p.NTILES * (kSliceUnits * 8) + kk) * 64 + lane;
-    const uint4* xbase = p.XF + (size_t)s * p.RT * 128 + lane;
-    uint4* dst = lds + buf * STAGE;
+  // copies of the next k-step into LDS buffer buf: every NW-th operand of the stage is this wave's (tiles past the matrix
+  // and column tiles past the fragment buffer repeat the last one, their results are dropped)
+  const int full_chunks = ksteps >> 4;                 // (the last chunk may be half as long)
+  uint32_t off[PER];                                   // bytes from the chunk's (weights) or the k-step's (fragments) start
 #pragma unroll
-    for (int q = 0; q < PER; ++q) {
-      int i = wave + q * NW;
-      if (PER * NW > AT + BT && i >= AT + BT) i -= NW;
-      const uint4* src = i < AT ? wbase + (size_t)min(p.tile_first + fb * AT + i, p.NTILES - 1) * ksteps_c * 64
-                                : xbase + (size_t)min(rb * BT + i - AT, 2 * p.RT - 1) * 64;
-      copy_to_lds_16(src, dst + i * 64);
-    }
+  for (int q = 0; q < PER; ++q) {
+    const int i = wave + q * NW;
+    off[q] = q < AT / NW ? (uint32_t)min(p.tile_first + fb * AT + i, p.NTILES - 1) * (kSliceUnits * 8 * 1024u)
+                         : (uint32_t)min(rb * BT + i - AT, 2 * p.RT - 1) * 1024u;
+  }
+  int rs_ = ks0;                                       // the next k-step
+  const uint4* wp = p.W + ((size_t)(ks0 >> 4) * p.NTILES * (kSliceUnits * 8) + (ks0 & 15)) * 64;
+  const uint4* xp = p.XF + (size_t)ks0 * p.RT * 128;
+  const size_t wskip = (size_t)(p.NTILES - 1) * (kSliceUnits * 8) * 64, xstep = (size_t)p.RT * 128;
+  auto request = [&](int buf) {
+    const int half = __builtin_amdgcn_readfirstlane((rs_ >> 4) >= full_chunks ? 1 : 0);
+    uint4* dst = lds + buf * STAGE + wave * 64;
+#pragma unroll
+    for (int q = 0; q < PER; ++q) copy_to_lds_16(q < AT / NW ? wp : xp, q < AT / NW ? off[q] >> half : off[q], dst + q * NW * 64, lane * 16);
+    ++rs_;
+    wp += 64;
+    if ((rs_ & 15) == 0) wp += wskip;
+    xp += xstep;
   };
   f32x4 acc[NT][CT], tot[PIECED ? NT : 1][PIECED ? CT : 1];
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
-  auto compute = [&](int buf) {
+  struct Frags {
+    bf16x8 a[NT], h[CT], l[CT];
+  };
+  auto read = [&](Frags& f, int buf) {
     const uint4* sa = lds + buf * STAGE + fw * NT * 64 + lane;
     const uint4* sb = lds + buf * STAGE + (AT + rw * CT * 2) * 64 + lane;
-    bf16x8 vh[CT], vl[CT], av[3];
-    av[0] = __builtin_bit_cast(bf16x8, sa[0]);
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
-      vh[ct] = __builtin_bit_cast(bf16x8, sb[(ct * 2) * 64]);
-      vl[ct] = __builtin_bit_cast(bf16x8, sb[(ct * 2 + 1) * 64]);
+      f.h[ct] = __builtin_bit_cast(bf16x8, sb[(ct * 2) * 64]);
+      f.l[ct] = __builtin_bit_cast(bf16x8, sb[(ct * 2 + 1) * 64]);
     }
-    av[1] = __builtin_bit_cast(bf16x8, sa[64]);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) f.a[t] = __builtin_bit_cast(bf16x8, sa[t * 64]);
+  };
+  auto multiply = [&](const Frags& f) {
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      if (t + 2 < NT) av[(t + 2) % 3] = __builtin_bit_cast(bf16x8, sa[(t + 2) * 64]);
-      __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[t % 3], vh[ct], acc[t][ct], 0, 0, 0);
+      for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[t], f.h[ct], acc[t][ct], 0, 0, 0);
 #pragma unroll
-      for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[t % 3], vl[ct], acc[t][ct], 0, 0, 0);
+      for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[t], f.l[ct], acc[t][ct], 0, 0, 0);
     }
   };
   // the rows' 1/rms, while the first copies are on their way (its loads go first, so the counted waits cover them)
@@ -368,9 +384,7 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
       const float v = blk_row_rstd(p, min(rb * WR * CT * 16 + r, p.R - 1), tid & 3, 1, 2);
       if ((tid & 3) == 0) s_rstd[r] = v;
     }
-#pragma unroll
-  for (int i = 0; i < ST - 1; ++i) request(min(ks0 + i, ks_end - 1), i);
-  int buf = 0, nbuf = ST - 1, piece = 0, bound = PIECED ? ksteps / P : 0;
+  int piece = 0, bound = PIECED ? piece_begin(1) : 0;
   auto fold = [&](int ks) {                            // PIECED: a piece ends in front of k-step ks
     if constexpr (PIECED) {
       if (ks == bound) {
@@ -382,29 +396,70 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
             acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
           }
         ++piece;
-        bound = ksteps * (piece + 1) / P;
+        bound = piece_begin(piece + 1);
       }
     }
   };
-  for (int ks = ks0; ks < ks_end - (ST - 1); ++ks) {
-    fold(ks);
+  // The fragments of k-step s + 1 are read from LDS while the MFMAs of k-step s run (two register sets), so buffer
+  // s % ST is free again at the barrier in front of k-step s and takes the copies of s + ST.  With one or two waves on a
+  // SIMD everything that is not an MFMA has to be issued in their shadow: requests and LDS reads are dealt out between
+  // them (all in front of them, a lone work-group took 0.52 us per k-step of 32 MFMAs a wave whatever the depth of the
+  // ring; see kBlkShapes).
+  Frags f0, f1;
+#pragma unroll
+  for (int i = 0; i < ST; ++i) request(i);    // (a piece has at least 8 k-steps)
+  wait_copies_and_sync<(ST - 1) * PER>();
+  read(f0, 0);
+  int s = ks0, rbuf = 1, wbuf = 0;                     // buffers of k-steps s + 1 and s + ST
+  auto advance = [&]() {
+    rbuf = rbuf + 1 == ST ? 0 : rbuf + 1;
+    wbuf = wbuf + 1 == ST ? 0 : wbuf + 1;
+    ++s;
+  };
+  constexpr int MFMAS = 2 * NT * CT, READS = NT + 2 * CT, GAP = (MFMAS - PER) / READS;
+  static_assert(GAP >= 1, "an MFMA in front of every request and read");
+  auto step = [&](const Frags& cur, Frags& next) {     // any k-step but the last ST
     wait_copies_and_sync<(ST - 2) * PER>();
-    request(ks + ST - 1, nbuf);
-    compute(buf);
-    buf = buf + 1 == ST ? 0 : buf + 1;
-    nbuf = nbuf + 1 == ST ? 0 : nbuf + 1;
+    request(wbuf);
+    read(next, rbuf);
+    multiply(cur);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < READS; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, GAP, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, MFMAS - PER - READS * GAP, 0);
+    advance();
+  };
+  while (s + 1 + ST < ks_end) {
+    fold(s);                                           // (pieces begin at even k-steps, and none among the last 8)
+    step(f0, f1);
+    step(f1, f0);
   }
-  // the last ST - 1 k-steps: nothing more to request, so the waits count down (a piece is longer than that)
-  static_assert(ST == 2 || ST == 3, "tail written for these");
-  if constexpr (ST >= 3) {
-    fold(ks_end - 2);
-    wait_copies_and_sync<PER>();
-    compute(buf);
-    buf = buf + 1 == ST ? 0 : buf + 1;
+  // ST or ST + 1 k-steps are left: their number decides which register set holds the first of the last ST; nothing
+  // more to request, so the waits count down
+  auto last = [&](auto self, auto I, Frags& x, Frags& y) -> void {
+    constexpr int i = decltype(I)::value;
+    if constexpr (i < ST - 1) {
+      wait_copies_and_sync<(ST - 2 - i) * PER>();
+      read(y, rbuf);
+    }
+    multiply(x);
+    advance();
+    if constexpr (i < ST - 1) self(self, std::integral_constant<int, i + 1>{}, y, x);
+  };
+  fold(s);
+  if (s + ST < ks_end) {
+    step(f0, f1);
+    last(last, std::integral_constant<int, 0>{}, f1, f0);
+  } else {
+    last(last, std::integral_constant<int, 0>{}, f0, f1);
   }
-  fold(ks_end - 1);
-  wait_copies_and_sync<0>();
-  compute(buf);
   if constexpr (PIECED) {
     if (piece > 0) {
 #pragma unroll
@@ -427,10 +482,19 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
           dst[((size_t)t * cts + ct0 + ct) * 64] = make_float4(acc[t][ct][0], acc[t][ct][1], acc[t][ct][2], acc[t][ct][3]);
     return;
   }
-  float rs[CT];
 #pragma unroll
-  for (int ct = 0; ct < CT; ++ct) rs[ct] = p.ssq ? s_rstd[rw * CT * 16 + ct * 16 + j] : 1.f;
-  blk_epilogue<NT, CT>(p, acc, tile0, row0, g, rs);
+  for (int ct = 0; ct < CT; ct += 2) {                 // (two column tiles at a time: more at once spill)
+    f32x4 part2[NT][2];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      part2[t][0] = acc[t][ct];
+      part2[t][1] = acc[t][ct + 1];
+    }
+    const float* sr = s_rstd + (rw * CT + ct) * 16 + j;
+    const float rs[2] = {p.ssq ? sr[0] : 1.f, p.ssq ? sr[16] : 1.f};
+    blk_epilogue<NT, 2>(p, part2, tile0, row0 + ct * 16, g, rs);
+    __builtin_amdgcn_sched_barrier(0);
+  }
 }
 
 // The k pieces of a launch with few rows added up in order, then the launch's epilogue: a wave takes two weight tiles x
@@ -459,42 +523,32 @@ __global__ __launch_bounds__(256) void k_blk_reduce(BlkGemm p, const float* __re
   blk_epilogue<2, 2>(p, acc, p.tile_first + t0, row0, g, rs);
 }
 
-// Tile shapes: features x rows of a work-group, threads, how many of its kind a CU holds, and the microseconds a k-step
-// takes with one such work-group on the CU and with the chip full of them (7B projections, 60 .. 2047 rows).
-struct BlkShape { int feat, rows, threads, per_cu; float t_one, t_full; };
-constexpr int kBlkShapeCount = 4;
-constexpr BlkShape kBlkShapes[kBlkShapeCount] = {
-    {256, 256, 512, 1, 1.24f, 1.46f},
-    {192, 128, 256, 2, 0.80f, 1.18f},
-    {128, 128, 256, 2, 0.52f, 0.84f},
-    {256, 64, 256, 2, 0.58f, 0.86f}};
+// Tile shapes: features x rows of a work-group (two fit a CU), and the microseconds a k-step takes with one work-group on
+// the CU and with two (7B and 1B projections, 60 .. 2047 rows).  Shapes with larger wave tiles (256 x 256 on 8 waves,
+// 256 x 128 and 192 x 128 on 4) were no faster at 2047 rows (7B gate/up 588, 633 and 617 us against 602) and lose to
+// these wherever rounds of work-groups do not come out even.
+struct BlkShape { int feat, rows; };
+constexpr int kBlkShapeCount = 2;
+constexpr BlkShape kBlkShapes[kBlkShapeCount] = {{128, 128}, {256, 64}};
+constexpr float kBlkOne = 0.38f, kBlkTwo = 0.84f;
 
 void launch_blk_gemm_as(int shape, bool split, const BlkGemm& p, hipStream_t st, float* part) {
   const BlkShape& b = kBlkShapes[shape];
   const int N = (p.NTILES - p.tile_first) * 16;
   const int FB = (N + b.feat - 1) / b.feat, RB = (p.R + b.rows - 1) / b.rows;
   const int blocks = FB * RB, per_xcd = (blocks + 7) / 8;
-  const dim3 grid(per_xcd * 8, 1, split ? p.pieces : 1), block(b.threads);
+  const dim3 grid(per_xcd * 8, 1, split ? p.pieces : 1), block(256);
   float* dst = split ? part : nullptr;
-#define STAIRS_BLK(WF, WR, NT, CT, ST)                                                                                                  \
-  do {                                                                                                                                  \
-    if (p.pieces > 1 && !split)                                                                                                         \
-      hipLaunchKernelGGL((k_gemm_bf16_block<WF, WR, NT, CT, ST, true>), grid, block, blk_lds_bytes(WF, WR, NT, CT, ST), st, p, dst, RB, per_xcd, blocks);  \
-    else                                                                                                                                \
-      hipLaunchKernelGGL((k_gemm_bf16_block<WF, WR, NT, CT, ST, false>), grid, block, blk_lds_bytes(WF, WR, NT, CT, ST), st, p, dst, RB, per_xcd, blocks); \
-  } while (0)
-  switch (shape) {
-    case 0:
-      hipLaunchKernelGGL((k_gemm_bf16_block<2, 4, 8, 4, 3, false>), grid, block, blk_lds_bytes(2, 4, 8, 4, 3), st, p, dst, RB, per_xcd, blocks);
-      break;
-    case 1: STAIRS_BLK(2, 2, 6, 4, 2); break;
-    case 2: STAIRS_BLK(2, 2, 4, 4, 3); break;
-    default: STAIRS_BLK(4, 1, 4, 4, 3); break;
+#define STAIRS_BLK(WF, WR, PIECED) \
+  hipLaunchKernelGGL((k_gemm_bf16_block<WF, WR, PIECED>), grid, block, blk_lds_bytes(WF, WR), st, p, dst, RB, per_xcd, blocks)
+  const bool pieced = p.pieces > 1 && !split;
+  if (shape == 0) {
+    if (pieced) STAIRS_BLK(2, 2, true); else STAIRS_BLK(2, 2, false);
+  } else {
+    if (pieced) STAIRS_BLK(4, 1, true); else STAIRS_BLK(4, 1, false);
   }
 #undef STAIRS_BLK
-  if (split) {
-    hipLaunchKernelGGL(k_blk_reduce, dim3((N / 16 + 7) / 8, (p.R + 31) / 32), dim3(256), 0, st, p, part);
-  }
+  if (split) hipLaunchKernelGGL(k_blk_reduce, dim3((N / 16 + 7) / 8, (p.R + 31) / 32), dim3(256), 0, st, p, part);
 }
 
 // Pieces of a k range for blocks of rows that belong to sequences of at most kBlkPiecedRows rows each: a function of K
@@ -512,21 +566,19 @@ static int blk_pieces(int K) {
 void launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t part_floats) {
   p.pieces = pieced ? blk_pieces(p.K) : 1;
   const int N = (p.NTILES - p.tile_first) * 16, ksteps = p.K / 32;
-  int best = 2;
+  int best = 0;
   bool best_split = false;
   float best_us = 1e30f;
   for (int s = 0; s < kBlkShapeCount; ++s) {
     const BlkShape& b = kBlkShapes[s];
     const int blocks = ((N + b.feat - 1) / b.feat) * ((p.R + b.rows - 1) / b.rows);
     for (int split = 0; split < 2; ++split) {
-      if (split ? (p.pieces == 1 || !part || (size_t)p.pieces * ((p.R + 15) / 16 * 16) * N > part_floats) : (s == 0 && p.pieces > 1)) continue;
-      const int wgs = split ? blocks * p.pieces : blocks, slots = 256 * b.per_cu;
-      const int full = wgs / slots, rem = wgs - full * slots;
-      float rounds = full * b.t_full;
-      if (rem > 0) rounds += rem <= 256 ? b.t_one : b.t_one + (b.t_full - b.t_one) * (rem - 256) / (slots - 256 + 1);
-      float us = 5.f + rounds * (split ? (float)ksteps / p.pieces : (float)ksteps);
-      us = std::max(us, 5.f + (float)N * p.K * 2 / 5.5e6f);
-      if (split) us += 4.f + (2.f * p.pieces + 1.f) * p.R * N * 4 / 6e6f;
+      if (split && (p.pieces == 1 || !part || (size_t)p.pieces * ((p.R + 15) / 16 * 16) * N > part_floats)) continue;
+      const int wgs = split ? blocks * p.pieces : blocks, full = wgs / 512, rem = wgs - full * 512;
+      const float rounds = full * kBlkTwo + (rem == 0 ? 0.f : rem <= 256 ? kBlkOne : kBlkOne + (kBlkTwo - kBlkOne) * (rem - 256) / 256);
+      float us = rounds * (split ? (float)ksteps / p.pieces : (float)ksteps);
+      us = std::max(us, (float)N * p.K * 2 / 5.5e6f);
+      if (split) us += 3.f + (2.f * p.pieces + 1.f) * p.R * N * 4 / 8e6f;
       if (us < best_us) {
         best_us = us;
         best = s;
@@ -681,15 +733,10 @@ hipError_t configure_block_kernels() {
     const hipError_t r = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (r != hipSuccess) e = r;
   };
-#define STAIRS_OPTIN_BLK(WF, WR, NT, CT, ST, P) optin((const void*)k_gemm_bf16_block<WF, WR, NT, CT, ST, P>, blk_lds_bytes(WF, WR, NT, CT, ST))
-  STAIRS_OPTIN_BLK(2, 4, 8, 4, 3, false);
-  STAIRS_OPTIN_BLK(2, 2, 6, 4, 2, false);
-  STAIRS_OPTIN_BLK(2, 2, 6, 4, 2, true);
-  STAIRS_OPTIN_BLK(2, 2, 4, 4, 3, false);
-  STAIRS_OPTIN_BLK(2, 2, 4, 4, 3, true);
-  STAIRS_OPTIN_BLK(4, 1, 4, 4, 3, false);
-  STAIRS_OPTIN_BLK(4, 1, 4, 4, 3, true);
-#undef STAIRS_OPTIN_BLK
+  optin((const void*)k_gemm_bf16_block<2, 2, false>, blk_lds_bytes(2, 2));
+  optin((const void*)k_gemm_bf16_block<2, 2, true>, blk_lds_bytes(2, 2));
+  optin((const void*)k_gemm_bf16_block<4, 1, false>, blk_lds_bytes(4, 1));
+  optin((const void*)k_gemm_bf16_block<4, 1, true>, blk_lds_bytes(4, 1));
   return e;
 }
 
