@@ -56,6 +56,7 @@ struct Model {
   char *Kx = nullptr, *Vx = nullptr;   // cross-attention keys/values: [decoder layers][H][cap_src][hd]
   size_t kvx_layer_bytes = 0;
   const void* tok_emb = nullptr;    // row-major, cfg dtype
+  float2* rope_tab = nullptr;       // [cap][64] rotation entries of every position (decoder-only models)
   const void* lm_head = nullptr;    // GEMM layout
   const float* final_norm = nullptr;
   std::vector<Layer> layers;
@@ -277,6 +278,9 @@ int build_model(stairs_ctx* c, Model* m, const stairs_model_cfg* cfg, const stai
     one[0] = w->w_down[l];
     if ((rc = upload_matrix(c, m->bf16, one, 1, d, f, KIND_DOWN, m->hd, staging, &ly.wdown))) return rc;
   }
+  if ((rc = dev_alloc(c, &m->rope_tab, (size_t)m->cap * 64))) return rc;
+  launch_rope_table(m->cap, m->hd, cfg->rope_theta, m->rope_tab, c->st);
+  HIPCHK(c, hipGetLastError());
   m->stream_weights = m->bf16 && ((size_t)cfg->n_layers * (4 * (size_t)d * d + 3 * (size_t)d * f) + (size_t)V * d) * 2 > kStreamHintBytes;
   m->kv_layer_bytes = (size_t)cfg->n_heads * m->cap * m->hd * m->esz();
   if ((rc = dev_alloc(c, &m->Kc, m->kv_layer_bytes * cfg->n_layers))) return rc;
@@ -487,7 +491,7 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
   if (M > kMaxRows && !(fr && gemm_takes_rows(M, std::max(d, f))))
     return fail(c, STAIRS_EINVAL, "forward: more rows than the weight-streaming kernels take for this model");
   launch_embed(m->tok_emb, b, c->tokens + (pos.rps ? 0 : (size_t)slot * c->tok_stride), pos.rps ? c->tok_stride : 0,
-               c->tok_stride, V, pos, M, d, c->x, c->ssq, m->hd, g.rope_theta, c->rope_cs, st, fr ? c->xf : nullptr,
+               c->tok_stride, V, pos, M, d, c->x, c->ssq, m->hd, m->rope_tab, m->cap, c->rope_cs, st, fr ? c->xf : nullptr,
                m->layers[0].attn_norm);
   SYNCPOINT();
   const RowNorm none{nullptr, nullptr, 0, 0.f};
@@ -632,7 +636,7 @@ int forward_block(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int lo
   if (nchunk < 1 || nchunk > c->nchunk_cap || nslots > c->n_slots || nslots * H > kAttnCounters)
     return fail(c, STAIRS_EINVAL, "forward: launch shape outside the workspaces");
   const size_t slot_stride = (size_t)g.n_layers * m->kv_layer_bytes / m->esz();
-  launch_blk_rows_pos(pos, M, m->hd, g.rope_theta, c->pf_rowinfo, c->pf_cs, st);
+  launch_blk_rows_pos(pos, M, m->hd, m->rope_tab, m->cap, c->pf_rowinfo, c->pf_cs, st);
   launch_blk_embed(static_cast<const uint16_t*>(m->tok_emb), c->tokens, c->tok_stride, c->tok_stride, V, c->pf_rowinfo, M, d, c->pf_x,
                    m->layers[0].attn_norm, c->pf_fa, c->pf_ssq, st);
   const AttnMode amode{0.f, nullptr, 0, 0, 0, c->pf_fb, pf_col_tiles(M)};
@@ -708,7 +712,7 @@ int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logit
   const bool fr = M > 4;
   uint4* const xf = fr ? c->xf : nullptr;
   uint4* const af = fr ? c->af : nullptr;
-  launch_embed(m->tok_emb, 1, c->tokens, 0, c->tok_stride, V, pos, M, d, c->x, c->ssq, m->hd, 0.f, c->rope_cs, st, xf,
+  launch_embed(m->tok_emb, 1, c->tokens, 0, c->tok_stride, V, pos, M, d, c->x, c->ssq, m->hd, nullptr, 0, c->rope_cs, st, xf,
                m->dec[0].attn_norm);
   SYNCPOINT();
   const RowNorm none{nullptr, nullptr, 0, 0.f};
@@ -791,7 +795,7 @@ int encode_model(stairs_ctx* c, Model* m) {
   segs.n = 1;
   segs.row0[0] = segs.slot[0] = segs.pos0[0] = 0;
   segs.len[0] = S;
-  launch_blk_rows(segs, S, m->hd, 0.f, c->pf_rowinfo, c->pf_cs, st);
+  launch_blk_rows(segs, S, m->hd, nullptr, 0, c->pf_rowinfo, c->pf_cs, st);
   launch_blk_embed(static_cast<const uint16_t*>(m->tok_emb), c->src_tok, 0, S, g.vocab, c->pf_rowinfo, S, d, c->pf_x, m->enc[0].attn_norm,
                    c->pf_fa, c->pf_ssq, st);
   const AttnMode mode{1.f, m->enc_bias, 2 * m->max_src - 1, m->max_src - 1, S, nullptr, 0};
@@ -846,7 +850,7 @@ int ingest_segs(stairs_ctx* c, Model* m, const BlkSegs& segs, int R, bool pieced
   const stairs_model_cfg& g = m->cfg;
   const int d = g.d_model, H = g.n_heads;
   const size_t slot_stride = (size_t)g.n_layers * m->kv_layer_bytes / m->esz();
-  launch_blk_rows(segs, R, m->hd, g.rope_theta, c->pf_rowinfo, c->pf_cs, c->st);
+  launch_blk_rows(segs, R, m->hd, m->rope_tab, m->cap, c->pf_rowinfo, c->pf_cs, c->st);
   launch_blk_embed(static_cast<const uint16_t*>(m->tok_emb), c->tokens, c->tok_stride, c->tok_stride, g.vocab, c->pf_rowinfo, R, d,
                    c->pf_x, m->layers[0].attn_norm, c->pf_fa, c->pf_ssq, c->st);
   return block_layers(c, m, R, pieced, false, [&](const char* Kl, const char* Vl) {
@@ -2125,7 +2129,7 @@ int stairs_time_kernel(stairs_ctx* c, int32_t which, int32_t M, int32_t ctx_len,
   RowNorm none{nullptr, nullptr, 0, 0.f};
   double bytes = 0;
   const PosRef tpos = abs_pos(c, which == 1 ? ctx_len - M : 0);
-  if (which == 1) launch_rope_table(tpos, M, m->hd, g.rope_theta, c->rope_cs, c->st);
+  if (which == 1) launch_rope_rows(tpos, M, m->hd, m->rope_tab, m->cap, c->rope_cs, c->st);
   // more than 4 rows: the projections read activation fragments, as inside a forward (whatever the workspaces hold)
   const bool fr = b && M > 4 && which <= 4;
   if (fr) {

@@ -12,35 +12,31 @@ namespace stairs {
 // ---------------------------------------------------------------------------------------
 // rows of a block: where they sit, their rotation entries, their embeddings
 // ---------------------------------------------------------------------------------------
-// rows[r] = (slot, position) of row r, position < 0: a padding row; cs[r][i] = (cos, sin)(position * theta^(-2i/hd)),
-// angle in double (theta <= 0: the identity rotation)
-__device__ __forceinline__ void blk_row_entry(int r, int slot, int p, int hd, double theta, int2* rows, float2* cs) {
+// rows[r] = (slot, position) of row r, position < 0: a padding row; cs[r] = the rotation table's entries of the position
+// (tab == nullptr: the identity rotation)
+__device__ __forceinline__ void blk_row_entry(int r, int slot, int p, int hd, const float2* tab, int tab_len, int2* rows, float2* cs) {
   const int i = threadIdx.x;
   if (i == 0) rows[r] = make_int2(slot, p);
-  if (i >= hd / 2) return;
-  float2 v = make_float2(1.f, 0.f);
-  if (theta > 0.0 && p >= 0) {
-    const double ang = (double)p * pow(theta, -2.0 * (double)i / (double)hd);
-    v = make_float2((float)cos(ang), (float)sin(ang));
-  }
-  cs[r * 64 + i] = v;
+  if (i < hd / 2) cs[r * 64 + i] = tab && p >= 0 && p < tab_len ? tab[(size_t)p * 64 + i] : make_float2(1.f, 0.f);
 }
-__global__ __launch_bounds__(64) void k_blk_rows(BlkSegs segs, int hd, double theta, int2* __restrict__ rows, float2* __restrict__ cs) {
+__global__ __launch_bounds__(64) void k_blk_rows(BlkSegs segs, int hd, const float2* __restrict__ tab, int tab_len, int2* __restrict__ rows,
+                                                 float2* __restrict__ cs) {
   const int r = blockIdx.x;
   int s = 0;
   while (s + 1 < segs.n && r >= segs.row0[s + 1]) ++s;
   const int i = r - segs.row0[s];
-  blk_row_entry(r, segs.slot[s], i < segs.len[s] ? segs.pos0[s] + i : -1, hd, theta, rows, cs);
+  blk_row_entry(r, segs.slot[s], i < segs.len[s] ? segs.pos0[s] + i : -1, hd, tab, tab_len, rows, cs);
 }
-__global__ __launch_bounds__(64) void k_blk_rows_pos(PosRef pos, int hd, double theta, int2* __restrict__ rows, float2* __restrict__ cs) {
+__global__ __launch_bounds__(64) void k_blk_rows_pos(PosRef pos, int hd, const float2* __restrict__ tab, int tab_len, int2* __restrict__ rows,
+                                                     float2* __restrict__ cs) {
   const int r = blockIdx.x;
-  blk_row_entry(r, slot_of(pos, r), pos_of(pos, r), hd, theta, rows, cs);
+  blk_row_entry(r, slot_of(pos, r), pos_of(pos, r), hd, tab, tab_len, rows, cs);
 }
-void launch_blk_rows(const BlkSegs& segs, int R, int hd, float theta, int2* rows, float2* cs, hipStream_t st) {
-  hipLaunchKernelGGL(k_blk_rows, dim3(R), dim3(64), 0, st, segs, hd, (double)theta, rows, cs);
+void launch_blk_rows(const BlkSegs& segs, int R, int hd, const float2* tab, int tab_len, int2* rows, float2* cs, hipStream_t st) {
+  hipLaunchKernelGGL(k_blk_rows, dim3(R), dim3(64), 0, st, segs, hd, tab, tab_len, rows, cs);
 }
-void launch_blk_rows_pos(PosRef pos, int R, int hd, float theta, int2* rows, float2* cs, hipStream_t st) {
-  hipLaunchKernelGGL(k_blk_rows_pos, dim3(R), dim3(64), 0, st, pos, hd, (double)theta, rows, cs);
+void launch_blk_rows_pos(PosRef pos, int R, int hd, const float2* tab, int tab_len, int2* rows, float2* cs, hipStream_t st) {
+  hipLaunchKernelGGL(k_blk_rows_pos, dim3(R), dim3(64), 0, st, pos, hd, tab, tab_len, rows, cs);
 }
 
 // Activations of a row block as MFMA B-operand fragments, written once by their producer: [k-step of 32][column tile

@@ -24,6 +24,9 @@ constexpr int kSpwRows = 9;         // 9..16 rows: a split-K work-group takes tw
 constexpr size_t kRowsPathMaxLds = 68 * 1024;
 constexpr size_t kRowsPathMaxLdsWide = 150 * 1024;
 constexpr size_t kWideMaxLds = 150 * 1024;      // chunk sums of k_gemm_bf16_wide: chunks * rows * 16 NT * 4 bytes
+// one column tile, one weight tile and one k chunk per wave (small models at 5..16 rows): the whole chunk in flight, one
+// round trip to memory instead of two or three (7.2 -> 6 us a launch at 125M and at the large encoder-decoder shape)
+constexpr int kWideDepthChunk = 16;
 constexpr int kWideDepth8 = 2, kWideDepth6 = 2, kWideDepth4 = 3, kWideDepth3 = 4, kWideDepth2 = 5, kWideDepth1 = 8;   // k-steps in flight per wave at 4 / 2 / 1 tiles per wave
 constexpr size_t kRowsPathSmallMatrix = 16u << 20;   // residual-writing projections with fewer tiles than CUs: up to this many bytes
 
@@ -136,13 +139,15 @@ void set_gemm_launch_events(hipEvent_t start, hipEvent_t stop);
 
 // ---- small kernels ----------------------------------------------------------------------
 // x[m][:] = emb[tokens[pos+m]][:] (row of zeros if pos+m lies outside [0, tok_cap) or the id found there outside
-// [0, vocab)), plus sum-of-squares partials; the same launch fills the rotation table cs of the M positions (see
-// launch_rope_table); theta <= 0: the identity rotation (1, 0).  tok_cap = ints one sequence's token array holds.
+// [0, vocab)), plus sum-of-squares partials; the same launch copies the M positions' rotation entries from tab (tab_len
+// positions; nullptr: the identity rotation (1, 0)) to cs.  tok_cap = ints one sequence's token array holds.
 void launch_embed(const void* emb, int emb_bf16, const int* tokens, int tok_slot_stride, int tok_cap, int vocab, PosRef pos,
-                  int M, int d, float* x, float* ssq_part, int hd, float theta, float2* cs, hipStream_t st,
+                  int M, int d, float* x, float* ssq_part, int hd, const float2* tab, int tab_len, float2* cs, hipStream_t st,
                   uint4* frag = nullptr, const float* frag_gain = nullptr);   // bf16: also the fragments of x * frag_gain
-// cs[m][i] = (cos, sin)((pos+m) * theta^(-2i/hd)), angle formed in double
-void launch_rope_table(PosRef pos, int M, int hd, float theta, float2* cs, hipStream_t st);
+// tab[p][i] = (cos, sin)(p * theta^(-2i/hd)), p < len, angle formed in double: [len][64], once per model
+void launch_rope_table(int len, int hd, float theta, float2* tab, hipStream_t st);
+// cs[m] = tab's entries of the positions of rows 0 .. M-1
+void launch_rope_rows(PosRef pos, int M, int hd, const float2* tab, int tab_len, float2* cs, hipStream_t st);
 // split-KV attention of M query rows at positions pos..pos+M-1 against keys 0..pos+M-1
 // (kv_half: half caches in the tiled layout; else float caches [H][cap][hd]); counters: one int per (slot, head).
 // Several sequences (pos.rps > 0, half caches only): M = pos.rps rows per slot, nslots slots, caches kv_slot_stride
@@ -217,9 +222,9 @@ struct BlkSegs {
   int n;
   int row0[kBlkMaxSegs], len[kBlkMaxSegs], slot[kBlkMaxSegs], pos0[kBlkMaxSegs];
 };
-// rows[r] = (slot, position; < 0 for padding), cs[r][i] = (cos, sin)(position * theta^(-2i/hd)), theta <= 0: (1, 0)
-void launch_blk_rows(const BlkSegs& segs, int R, int hd, float theta, int2* rows, float2* cs, hipStream_t st);
-void launch_blk_rows_pos(PosRef pos, int R, int hd, float theta, int2* rows, float2* cs, hipStream_t st);
+// rows[r] = (slot, position; < 0 for padding), cs[r] = tab's entries of the position (tab as for launch_embed)
+void launch_blk_rows(const BlkSegs& segs, int R, int hd, const float2* tab, int tab_len, int2* rows, float2* cs, hipStream_t st);
+void launch_blk_rows_pos(PosRef pos, int R, int hd, const float2* tab, int tab_len, int2* rows, float2* cs, hipStream_t st);
 // x = the rows' embeddings, frag = fragments of x * gain, ssq [R][d / kBlkSsqCols]
 void launch_blk_embed(const uint16_t* emb, const int* tokens, int tok_stride, int tok_cap, int vocab, const int2* rows, int R, int d,
                       float* x, const float* gain, uint4* frag, float* ssq, hipStream_t st);

@@ -623,11 +623,17 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
   // the roles whose epilogue loads nothing from memory request the next tile's first units before it (a load in
   // the epilogue would have to wait for them)
   constexpr bool kPrefetchNextTile = ROLE == kRoleGateUp || ROLE == kRoleHead || ROLE == kRoleQKV;
-  // (QKV: what its epilogue loads -- the row's position, the rotation entry -- is requested before that)
+  // (QKV: the row's position is requested here, once for all tiles)
   int q_pos = 0;
   if (ROLE == kRoleQKV && tid < R * 8) q_pos = pos_of(epi.pos, tid >> 3);
   for (;;) {
   const int tile = cur_tile;
+  // what the epilogue reads (old x, the rotation entry) is requested ahead of the arithmetic: behind it it was a round
+  // trip of its own at the end of every launch
+  float x_old = 0.f;
+  if ((ROLE == kRoleWo || ROLE == kRoleDown) && tid < R * 16) x_old = epi.out[(size_t)(tid >> 4) * N + tile * 16 + (tid & 15)];
+  float2 q_cs = make_float2(1.f, 0.f);
+  if (ROLE == kRoleQKV && tid < R * 8) q_cs = epi.rope_cs[qkv_rope_index(tid >> 3, tile * 16 + (tid & 7), N / 3, epi.hd)];
   for (int u = 0; u < nu; u += 2) {                        // one chunk per pass
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
     mfma_unit(wb0, u, acc);
@@ -648,9 +654,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
       dst[0] = acc[0]; dst[1] = acc[1]; dst[2] = acc[2]; dst[3] = acc[3];
     }
   }
-  float2 q_cs = make_float2(1.f, 0.f);
-  if (ROLE == kRoleQKV && tid < R * 8) q_cs = epi.rope_cs[qkv_rope_index(tid >> 3, tile * 16 + (tid & 7), N / 3, epi.hd)];
-  __builtin_amdgcn_sched_barrier(0);                       // these requests stay in front of the next tile's
+  __builtin_amdgcn_sched_barrier(0);
   const int next_tile = tile + (int)gridDim.x;
   if (kPrefetchNextTile && next_tile < NTILES) {
     cur_tile = next_tile;
@@ -665,9 +669,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
       const int m = tid >> 4, n = tid & 15;
       float a = lds_chunk_sum(csum + (m << 4) + n, R * 16, nchunks);
       if (has_stats) a *= s_rstd[m];
-      float* xp = epi.out + (size_t)m * N + tile * 16 + n;
-      a += *xp;
-      *xp = a;
+      a += x_old;
+      epi.out[(size_t)m * N + tile * 16 + n] = a;
       sq[tid] = a;
     }
     __syncthreads();
@@ -773,7 +776,7 @@ __device__ __forceinline__ void rows_rstd_any(const RowNorm& nrm, int M, int K, 
 // run by all threads of the work-group.  The additions are those of slice_sum<true>: chunk pairs first.
 template <int ROLE, int W>
 __device__ __forceinline__ void gemm_epilogue_lds(const float* csum, int nchunks, int M, int N, int c0, const GemmEpi& epi,
-                                                  const float* rs) {
+                                                  const float* rs, float4 x_first) {
   const int tid = threadIdx.x, nth = blockDim.x;
   const int cstride = M * W;
   auto sum4 = [&](int m, int lc) {
@@ -819,7 +822,7 @@ __device__ __forceinline__ void gemm_epilogue_lds(const float* csum, int nchunks
         float4 a = sum4(m, lc);
         if (rs) { const float q = rs[m]; a.x *= q; a.y *= q; a.z *= q; a.w *= q; }
         float4* xp = reinterpret_cast<float4*>(epi.out + (size_t)m * N + col);
-        const float4 r = *xp;
+        const float4 r = idx0 == 0 ? x_first : *xp;   // (the first pass' were requested ahead of the k loop)
         a.x += r.x; a.y += r.y; a.z += r.z; a.w += r.w;
         *xp = a;
         ss = sumsq4(a.x, a.y, a.z, a.w);
@@ -867,7 +870,7 @@ template <int CT, int NT, int DEPTH, bool STREAM>
 __global__ __launch_bounds__(512) void k_gemm_bf16_wide(const uint4* __restrict__ Wsw, int NTILES,
                                                         const uint4* __restrict__ XF, int M, RowNorm nrm, int K, int N,
                                                         int role, GemmEpi epi) {
-  constexpr int RING = DEPTH + 1;
+  constexpr int RING = DEPTH < kWideDepthChunk ? DEPTH + 1 : DEPTH;
   constexpr int W = NT * 16;
   extern __shared__ float csum[];                          // [chunk][M][W]
   __shared__ float s_rstd[kMaxFwdRows];
@@ -947,14 +950,20 @@ __global__ __launch_bounds__(512) void k_gemm_bf16_wide(const uint4* __restrict_
 #pragma unroll
     for (int i = 0; i < DEPTH; ++i) load_stage(st[i], min(s_begin + i, s_end - 1));
   }
-  // the rows' 1/rms, needed by the epilogue only: its loads go out behind the first weight requests and come back
-  // (from L2) long before those
+  // needed by the epilogue only, requested behind the first weights: the old x (first pass of the epilogue's threads) and
+  // the rows' 1/rms
+  float4 x_first = make_float4(0.f, 0.f, 0.f, 0.f);
+  if (role == kRoleWo || role == kRoleDown) {
+    const int m = tid / (W / 4), col = tile0 * 16 + (tid - m * (W / 4)) * 4;
+    if (m < M && col < N) x_first = *reinterpret_cast<const float4*>(epi.out + (size_t)m * N + col);
+  }
   if (has_stats) rows_rstd_any(nrm, M, K, s_rstd);
   if (work) {
     // whole turns of the ring without a condition around a request (a branch would make the compiler assume the
     // fewest outstanding loads at every join and wait for nearly all of them); the last DEPTH or fewer k-steps have
     // been requested by then
     int s = s_begin;
+    if constexpr (DEPTH < kWideDepthChunk)             // (else the wave's only chunk has been requested as a whole)
     for (; s + RING <= s_end; s += RING) {
 #pragma unroll
       for (int i = 0; i < RING; ++i) {
@@ -972,11 +981,11 @@ __global__ __launch_bounds__(512) void k_gemm_bf16_wide(const uint4* __restrict_
   const float* rs = has_stats ? s_rstd : nullptr;
   const int c0 = tile0 * 16;
   switch (role) {
-    case kRoleQKV: gemm_epilogue_lds<kRoleQKV, W>(csum, nchunks, M, N, c0, epi, rs); break;
+    case kRoleQKV: gemm_epilogue_lds<kRoleQKV, W>(csum, nchunks, M, N, c0, epi, rs, x_first); break;
     case kRoleWo:
-    case kRoleDown: gemm_epilogue_lds<kRoleWo, W>(csum, nchunks, M, N, c0, epi, rs); break;
-    case kRoleGateUp: gemm_epilogue_lds<kRoleGateUp, W>(csum, nchunks, M, N, c0, epi, rs); break;
-    default: gemm_epilogue_lds<kRoleHead, W>(csum, nchunks, M, N, c0, epi, rs); break;
+    case kRoleDown: gemm_epilogue_lds<kRoleWo, W>(csum, nchunks, M, N, c0, epi, rs, x_first); break;
+    case kRoleGateUp: gemm_epilogue_lds<kRoleGateUp, W>(csum, nchunks, M, N, c0, epi, rs, x_first); break;
+    default: gemm_epilogue_lds<kRoleHead, W>(csum, nchunks, M, N, c0, epi, rs, x_first); break;
   }
 }
 
@@ -1263,6 +1272,7 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
     else if (wc.nt == 3) { STAIRS_WIDE_CT2(3, kWideDepth3); }
     else if (wc.nt == 4) { STAIRS_WIDE_CT(4, kWideDepth4); }
     else if (wc.nt == 2) { STAIRS_WIDE_CT(2, kWideDepth2); }
+    else if (CT == 1 && nchunks <= wc.nw) STAIRS_WIDE(1, 1, kWideDepthChunk);
     else { STAIRS_WIDE_CT(1, kWideDepth1); }
 #undef STAIRS_WIDE_CT
 #undef STAIRS_WIDE_CT2
@@ -1429,7 +1439,7 @@ template <typename E, int GW>
 __global__ __launch_bounds__(256) void k_embed(const E* __restrict__ emb, const int* __restrict__ tokens,
                                                int tok_slot_stride, int tok_cap, int vocab, PosRef pos, int d,
                                                float* __restrict__ x, float* __restrict__ ssq_part, int ssq_n, int hd,
-                                               double theta, float2* __restrict__ cs, uint4* frag,
+                                               const float2* __restrict__ tab, int tab_len, float2* __restrict__ cs, uint4* frag,
                                                const float* __restrict__ frag_gain) {
   __shared__ float sm[4];
   const int m = blockIdx.y;
@@ -1437,10 +1447,7 @@ __global__ __launch_bounds__(256) void k_embed(const E* __restrict__ emb, const 
   tokens += (size_t)slot_of(pos, m) * tok_slot_stride;
   if (blockIdx.x == gridDim.x - 1) {
     const int i = threadIdx.x;
-    if (i < hd / 2) {
-      const double ang = (double)p * pow(theta, -2.0 * (double)i / (double)hd);
-      cs[m * 64 + i] = theta > 0.0 ? make_float2((float)cos(ang), (float)sin(ang)) : make_float2(1.f, 0.f);
-    }
+    if (i < hd / 2) cs[m * 64 + i] = tab && p >= 0 && p < tab_len ? tab[(size_t)p * 64 + i] : make_float2(1.f, 0.f);
     return;
   }
   const int c = (blockIdx.x * 256 + threadIdx.x) * 4;
@@ -1467,29 +1474,35 @@ __global__ __launch_bounds__(256) void k_embed(const E* __restrict__ emb, const 
 }
 
 void launch_embed(const void* emb, int emb_bf16, const int* tokens, int tok_slot_stride, int tok_cap, int vocab, PosRef pos,
-                  int M, int d, float* x, float* ssq_part, int hd, float theta, float2* cs, hipStream_t st, uint4* frag,
+                  int M, int d, float* x, float* ssq_part, int hd, const float2* tab, int tab_len, float2* cs, hipStream_t st, uint4* frag,
                   const float* frag_gain) {
   dim3 grid((d + 1023) / 1024 + 1, M), block(256);
   const int sn = ssq_groups(d, emb_bf16);
   if (emb_bf16)
     hipLaunchKernelGGL((k_embed<uint16_t, 16>), grid, block, 0, st, static_cast<const uint16_t*>(emb), tokens,
-                       tok_slot_stride, tok_cap, vocab, pos, d, x, ssq_part, sn, hd, (double)theta, cs, frag, frag_gain);
+                       tok_slot_stride, tok_cap, vocab, pos, d, x, ssq_part, sn, hd, tab, tab_len, cs, frag, frag_gain);
   else
     hipLaunchKernelGGL((k_embed<float, 1024>), grid, block, 0, st, static_cast<const float*>(emb), tokens,
-                       tok_slot_stride, tok_cap, vocab, pos, d, x, ssq_part, sn, hd, (double)theta, cs, nullptr, nullptr);
+                       tok_slot_stride, tok_cap, vocab, pos, d, x, ssq_part, sn, hd, tab, tab_len, cs, nullptr, nullptr);
 }
 
-__global__ void k_rope_table(PosRef pos, int hd, double theta, float2* __restrict__ cs) {
-  const int m = blockIdx.x, i = threadIdx.x;
+// tab[p][i] = (cos, sin)(p * theta^(-2i/hd)), angle in double, once per model: formed in front of every forward the
+// double-precision power, sine and cosine were most of the embedding kernel's 4.3 us
+__global__ void k_rope_table(int hd, double theta, float2* __restrict__ tab) {
+  const int p = blockIdx.x, i = threadIdx.x;
   if (i >= hd / 2) return;
-  const double p = (double)(*pos.base + pos.offset + m);
-  const double inv_freq = pow(theta, -2.0 * (double)i / (double)hd);
-  const double ang = p * inv_freq;
-  cs[m * 64 + i] = make_float2((float)cos(ang), (float)sin(ang));
+  const double ang = (double)p * pow(theta, -2.0 * (double)i / (double)hd);
+  tab[(size_t)p * 64 + i] = make_float2((float)cos(ang), (float)sin(ang));
 }
-
-void launch_rope_table(PosRef pos, int M, int hd, float theta, float2* cs, hipStream_t st) {
-  hipLaunchKernelGGL(k_rope_table, dim3(M), dim3(64), 0, st, pos, hd, (double)theta, cs);
+void launch_rope_table(int len, int hd, float theta, float2* tab, hipStream_t st) {
+  hipLaunchKernelGGL(k_rope_table, dim3(len), dim3(64), 0, st, hd, (double)theta, tab);
+}
+__global__ void k_rope_rows(PosRef pos, int hd, const float2* __restrict__ tab, int tab_len, float2* __restrict__ cs) {
+  const int m = blockIdx.x, i = threadIdx.x, p = pos_of(pos, m);
+  if (i < hd / 2) cs[m * 64 + i] = p >= 0 && p < tab_len ? tab[(size_t)p * 64 + i] : make_float2(1.f, 0.f);
+}
+void launch_rope_rows(PosRef pos, int M, int hd, const float2* tab, int tab_len, float2* cs, hipStream_t st) {
+  hipLaunchKernelGGL(k_rope_rows, dim3(M), dim3(64), 0, st, pos, hd, tab, tab_len, cs);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1839,7 +1852,7 @@ template <int HD, int CT, bool FUSED>
 __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q, const _Float16* __restrict__ Kc,
                                                   const _Float16* __restrict__ Vc, int cap, int d, int H, int M,
                                                   PosRef pos, size_t kv_slot_stride, float scale, AttnMode am, int nchunk_cap,
-                                                  int rows_per_pass, float* part_o, float* part_ml, int* counters,
+                                                  int sure_chunks, int rows_per_pass, float* part_o, float* part_ml, int* counters,
                                                   float* __restrict__ out) {
   constexpr int KK = HD / 32;   // k-steps of the score MFMA
   constexpr int ET = HD / 16;   // output-dim tiles of the value MFMA
@@ -1859,6 +1872,58 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
   counters += blockIdx.z * H;
   Kc += blockIdx.z * kv_slot_stride;
   Vc += blockIdx.z * kv_slot_stride;
+  // a wave owns 64 keys of the chunk as two blocks of 32 (the tiles of the cache layout)
+  const int kb = c * kAttnChunkH + wave * 64;         // first key of this wave
+  // The first query tile's rows are requested before the keys and values (they come from L2 and are converted while the
+  // cache tiles are still on their way), and the wave's whole share of the chunk at once (keys and values of both
+  // blocks: 16 KiB at head_dim 128).  Chunks the launch is sure to need (the host's lower bound of the length) are
+  // requested before the rows' position has come back from memory, a round trip less in front of every head; blocks
+  // past the last key hold finite numbers and meet probability 0, blocks past the cache re-read its last.
+  float4 qa0[KK], qb0[KK];
+  uint4 kreg[2][2][KK], vreg[2][ET];
+  auto request = [&](bool first, bool second) {
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      qa0[kk] = make_float4(0.f, 0.f, 0.f, 0.f);
+      qb0[kk] = qa0[kk];
+      if (first && j < M) {
+        const float4* qp = reinterpret_cast<const float4*>(q + (size_t)j * d + h * HD + kk * 32 + g * 8);
+        qa0[kk] = qp[0];
+        qb0[kk] = qp[1];
+      }
+    }
+    const uint4* Kh = reinterpret_cast<const uint4*>(Kc + (size_t)h * cap * HD);
+    const uint4* Vh = reinterpret_cast<const uint4*>(Vc + (size_t)h * cap * HD);
+#pragma unroll
+    for (int sb = 0; sb < 2; ++sb) {
+#pragma unroll
+      for (int t = 0; t < 2; ++t)
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) kreg[sb][t][kk] = make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+      for (int et = 0; et < ET; ++et) vreg[sb][et] = make_uint4(0u, 0u, 0u, 0u);
+      if (sb ? second : first) {
+        const int kbs = min(kb + 32 * sb, cap - 32);
+        // (the two-kernel form runs at long contexts only, where a layer's keys and values exceed what the memory-side
+        // cache could keep until the next forward: streaming loads there, as for the weights of a large model)
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+#pragma unroll
+          for (int kk = 0; kk < KK; ++kk) {
+            const uint4* p = &Kh[((size_t)((kbs >> 4) + t) * KK + kk) * 64 + lane];
+            kreg[sb][t][kk] = FUSED ? *p : ld_nt(p);
+          }
+#pragma unroll
+        for (int et = 0; et < ET; ++et) {
+          const uint4* p = &Vh[((size_t)(kbs >> 5) * ET + et) * 64 + lane];
+          vreg[sb][et] = FUSED ? *p : ld_nt(p);
+        }
+      }
+    }
+  };
+  // (one request site: with a second one for the other chunks the registers of both spill)
+  const int len0 = c < sure_chunks ? 0x7fffffff : am.kv_fixed > 0 ? am.kv_fixed : pos_of(pos, row0) + M;
+  request(kb < len0, kb + 32 < len0);
   // causal: row i sees the keys 0 .. qpos0 + i; fixed key set (am.kv_fixed > 0): every row sees the keys 0 .. kv_fixed-1
   const int qpos0 = pos_of(pos, row0);
   const bool fixed = am.kv_fixed > 0;   // (then also for rows that sit nowhere: their result is unused)
@@ -1866,60 +1931,11 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
   const int step = fixed ? 0 : 1;
   const int kv_len = pos0 + (fixed ? 1 : M);
   const float* brow = am.bias ? am.bias + (size_t)h * am.bias_ld + am.bias_zero : nullptr;
-  // a wave owns 64 keys of the chunk as two blocks of 32 (the tiles of the cache layout)
-  const int kb = c * kAttnChunkH + wave * 64;         // first key of this wave
   const bool have_keys = kb < kv_len;
-  const bool have_second = kb + 32 < kv_len;
   // all keys in the first chunk: its work-group writes the result itself (what the merge would give for one chunk:
   // weight exp(0) = 1), the others have nothing to do; no partial results, no ticket
   const bool single = FUSED && kv_len <= kAttnChunkH;
   if (single && c > 0) return;
-
-  // the first query tile's rows are requested before the keys and values: they come from L2 and are
-  // converted while the cache tiles are still on their way
-  float4 qa0[KK], qb0[KK];
-#pragma unroll
-  for (int kk = 0; kk < KK; ++kk) {
-    qa0[kk] = make_float4(0.f, 0.f, 0.f, 0.f);
-    qb0[kk] = qa0[kk];
-    if (have_keys && j < M) {
-      const float4* qp = reinterpret_cast<const float4*>(q + (size_t)j * d + h * HD + kk * 32 + g * 8);
-      qa0[kk] = qp[0];
-      qb0[kk] = qp[1];
-    }
-  }
-
-  // the wave's whole share of the chunk is requested at once (keys and values of both blocks: 16 KiB at head_dim 128)
-  uint4 kreg[2][2][KK], vreg[2][ET];
-#pragma unroll
-  for (int sb = 0; sb < 2; ++sb) {
-    const bool ok = sb ? have_second : have_keys;
-#pragma unroll
-    for (int t = 0; t < 2; ++t)
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kreg[sb][t][kk] = make_uint4(0u, 0u, 0u, 0u);
-#pragma unroll
-    for (int et = 0; et < ET; ++et) vreg[sb][et] = make_uint4(0u, 0u, 0u, 0u);   // (a block without keys meets probability 0)
-    if (ok) {
-      const uint4* Kh = reinterpret_cast<const uint4*>(Kc + (size_t)h * cap * HD);
-      const uint4* Vh = reinterpret_cast<const uint4*>(Vc + (size_t)h * cap * HD);
-      const int kbs = kb + 32 * sb;
-#pragma unroll
-      // (the two-kernel form runs at long contexts only, where a layer's keys and values exceed what the memory-side
-      // cache could keep until the next forward: streaming loads there, as for the weights of a large model)
-      for (int t = 0; t < 2; ++t)
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) {
-          const uint4* p = &Kh[((size_t)((kbs >> 4) + t) * KK + kk) * 64 + lane];
-          kreg[sb][t][kk] = FUSED ? *p : ld_nt(p);
-        }
-#pragma unroll
-      for (int et = 0; et < ET; ++et) {
-        const uint4* p = &Vh[((size_t)(kbs >> 5) * ET + et) * 64 + lane];
-        vreg[sb][et] = FUSED ? *p : ld_nt(p);
-      }
-    }
-  }
 
 #pragma unroll
   for (int ct = 0; ct < CT; ++ct) {
@@ -2108,8 +2124,11 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
     const _Float16* K = static_cast<const _Float16*>(Kc);
     const _Float16* V = static_cast<const _Float16*>(Vc);
     // the half-cache kernels take 256-key chunks: half as many work-groups as the 128-key units the callers count in
+    const int units = nchunk_launch;
     nchunk_launch = (nchunk_launch * kAttnChunk + kAttnChunkH - 1) / kAttnChunkH;
     dim3 grid(nchunk_launch, H, nslots), block(256);
+    // chunks every row block of this launch has keys in: callers round the 128-key units up to a multiple of 4 at most
+    const int sure = am.kv_fixed > 0 ? nchunk_launch : nslots > 1 ? 1 : std::max(1, ((units - 4) * kAttnChunk + 1) / kAttnChunkH);
     // merge step's LDS: (max, sum) table, row maxima, and for more than kMergeCB chunks the group sums of as many
     // rows per pass as fit in 48 KiB, less when the table is large (the whole stays under kAttnMergeMaxLds)
     const int G = (nchunk_launch + kMergeCB - 1) / kMergeCB;
@@ -2123,10 +2142,10 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
 #define STAIRS_ATTN16(hdv, ct)                                                                                              \
   if (fused)                                                                                                                \
     hipLaunchKernelGGL((k_attn_f16<hdv, ct, true>), grid, block, lds, st, q_rot, K, V, cap, d, H, M, pos, kv_slot_stride,   \
-                       scale, am, nchunk_cap, rpp, part_o, part_ml, counters, out);                                         \
+                       scale, am, nchunk_cap, sure, rpp, part_o, part_ml, counters, out);                                         \
   else {                                                                                                                    \
     hipLaunchKernelGGL((k_attn_f16<hdv, ct, false>), grid, block, 0, st, q_rot, K, V, cap, d, H, M, pos, kv_slot_stride,    \
-                       scale, am, nchunk_cap, rpp, part_o, part_ml, counters, out);                                         \
+                       scale, am, nchunk_cap, sure, rpp, part_o, part_ml, counters, out);                                         \
     hipLaunchKernelGGL((k_attn_merge<hdv>), dim3(H, nslots), dim3(256), lds, st, part_o, part_ml, d, H, M, pos,             \
                        am.kv_fixed, nchunk_cap, nchunk_launch, rpp, out, am.frag_out, am.frag_rt);                                      \
   }
@@ -2471,6 +2490,7 @@ hipError_t configure_kernels() {
   STAIRS_OPTIN_WIDE(1, 4, kWideDepth4); STAIRS_OPTIN_WIDE(2, 4, kWideDepth4);
   STAIRS_OPTIN_WIDE(1, 2, kWideDepth2); STAIRS_OPTIN_WIDE(2, 2, kWideDepth2);
   STAIRS_OPTIN_WIDE(1, 1, kWideDepth1); STAIRS_OPTIN_WIDE(2, 1, kWideDepth1);
+  STAIRS_OPTIN_WIDE_(1, 1, kWideDepthChunk);
   STAIRS_OPTIN_WIDE(3, 4, kWideDepth4); STAIRS_OPTIN_WIDE(4, 4, kWideDepth4);
   STAIRS_OPTIN_WIDE(3, 2, kWideDepth2); STAIRS_OPTIN_WIDE(4, 2, kWideDepth2);
   STAIRS_OPTIN_WIDE(3, 1, kWideDepth1); STAIRS_OPTIN_WIDE(4, 1, kWideDepth1);
