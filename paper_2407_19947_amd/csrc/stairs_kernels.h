@@ -120,6 +120,10 @@ struct GemmEpi {
 void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const float* X, int ldx, int M,
                  RowNorm nrm, float* partial, const GemmEpi& epi, hipStream_t st, const uint4* xfrag = nullptr);
 
+// Y [M <= 32, N] = X [M, K] . W^T with W [N, K] row-major bf16 read as it is, one kernel (M > 4: two), the bits launch_gemm
+// gives for the laid-out matrix; frag: frag_bytes(K) of scratch.  false: the shape takes the split-K kernel, nothing done.
+bool launch_gemm_rowmajor(const uint16_t* W, int N, int K, const float* X, int M, float* Y, uint4* frag, hipStream_t st);
+
 // Activation fragments of a [M <= 32, K] block: K / 32 k-steps x 2 column tiles x (high, low) x 1 KiB
 // (+ kFragChunkPad uint4 after every 16 k-steps: the k chunks the waves of a work-group read at the same time then do
 // not sit a power of two apart)

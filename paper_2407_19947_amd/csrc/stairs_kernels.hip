@@ -286,10 +286,10 @@ __device__ __forceinline__ uint4 ld_nt(const uint4* p) {
 // load forms cost the whole gain in the kernels' prologues): weights of a model far larger than the
 // 256 MB memory-side cache are read once per forward and gain from the streaming hint (a bare 2 GB read: 6.2 -> 7.05
 // TB/s); a model that about fits that cache is served from it forward after forward and must keep plain loads.
-template <bool STREAM>
+template <bool STREAM, int STEP = 64>
 __device__ __forceinline__ void load_unit(const uint4* p, uint4 (&wb)[8]) {
 #pragma unroll
-  for (int i = 0; i < 8; ++i) wb[i] = STREAM ? ld_nt(&p[i * 64]) : p[i * 64];
+  for (int i = 0; i < 8; ++i) wb[i] = STREAM ? ld_nt(&p[i * STEP]) : p[i * STEP];
 }
 
 template <int CT, int NT, int ROLE, int SPW, bool STREAM>
@@ -474,7 +474,10 @@ __device__ __forceinline__ float lds_chunk_sum(const float* base, int stride, in
   return a;
 }
 
-template <int R, int ROLE, int NW, int GP, bool STREAM>
+// ROWMAJOR: W as the caller has it, [N, K] row-major: lane r + 16 g reads row 16 tile + r, k 32 kt + 8 g .. + 8, the very
+// operand the tile layout holds in one piece (a wave's load is then 16 runs of 64 bytes; for a matrix used once that is
+// far less than laying it out first).
+template <int R, int ROLE, int NW, int GP, bool STREAM, bool ROWMAJOR = false>
 __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restrict__ Wsw, int NTILES,
                                                             const float* __restrict__ X, int ldx, RowNorm nrm,
                                                             int K, int N, GemmEpi epi) {
@@ -493,8 +496,10 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
   const int nu = min(units_total, c_end * kSliceUnits) - c_begin * kSliceUnits;   // this wave's units (<= 0: none)
 
   // address of unit u of this wave: chunk c_begin + u/2 (= split-K slice), unit u%2 inside it
+  const uint4* const wrow = Wsw + (size_t)(lane & 15) * (K >> 3) + (lane >> 4);      // ROWMAJOR: this lane's row of tile 0
   auto unit_ptr = [&](int u) {
     const int c = c_begin + (u >> 1);
+    if (ROWMAJOR) return wrow + (size_t)cur_tile * 16 * (K >> 3) + (c * kSliceUnits + (u & 1)) * 32;
     const int units_c = min(kSliceUnits, units_total - c * kSliceUnits);
     return Wsw + (size_t)c * NTILES * (kSliceUnits * 8) * 64 + ((size_t)cur_tile * units_c + (u & 1)) * 8 * 64 + lane;
   };
@@ -545,10 +550,12 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
   // (a macro, not a lambda: register arrays a lambda captures by reference end up in scratch memory)
 #define STAIRS_FIRST_UNITS()                                                                                              \
   do {                                                                                                                    \
-    const uint4* p0 = (nu > 0) ? unit_ptr(0) : Wsw + (size_t)cur_tile * min(kSliceUnits, units_total) * 8 * 64 + lane;   \
+    const uint4* p0 = (nu > 0) ? unit_ptr(0)                                                                              \
+                      : ROWMAJOR ? wrow + (size_t)cur_tile * 16 * (K >> 3)                                                \
+                                 : Wsw + (size_t)cur_tile * min(kSliceUnits, units_total) * 8 * 64 + lane;                 \
     const uint4* p1 = (nu > 1) ? unit_ptr(1) : p0;                                                                        \
-    load_unit<STREAM>(p0, wb0);                                                                                           \
-    load_unit<STREAM>(p1, wb1);                                                                                           \
+    load_unit<STREAM, ROWMAJOR ? 4 : 64>(p0, wb0);                                                                                           \
+    load_unit<STREAM, ROWMAJOR ? 4 : 64>(p1, wb1);                                                                                           \
   } while (0)
   STAIRS_FIRST_UNITS();
   uint4* xhi = lds;
@@ -639,13 +646,13 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
     mfma_unit(wb0, u, acc);
     if (u + 2 < nu) {
       const uint4* p = unit_ptr(u + 2);
-      load_unit<STREAM>(p, wb0);
+      load_unit<STREAM, ROWMAJOR ? 4 : 64>(p, wb0);
     }
     if (u + 1 < nu) {
       mfma_unit(wb1, u + 1, acc);
       if (u + 3 < nu) {
         const uint4* p = unit_ptr(u + 3);
-        load_unit<STREAM>(p, wb1);
+        load_unit<STREAM, ROWMAJOR ? 4 : 64>(p, wb1);
       }
     }
     const int m = lane & 15;
@@ -750,7 +757,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
 // ---------------------------------------------------------------------------------------
 // 1/rms of the rows for a work-group of any size: half a wave per row, the additions in the order of rows_rstd
 __device__ __forceinline__ void rows_rstd_any(const RowNorm& nrm, int M, int K, float* s_rstd) {
-  const int pl = threadIdx.x & 31, hw = threadIdx.x >> 5, nhw = blockDim.x >> 5;
+  // (the last waves first: with a short k the first ones have the k chunks and the others nothing to wait for)
+  const int pl = threadIdx.x & 31, nhw = blockDim.x >> 5, hw = nhw - 1 - (threadIdx.x >> 5);
   for (int m = hw; m < M; m += nhw) {
     const float* sp = nrm.ssq_part + (size_t)m * nrm.ssq_n;
     float v[8];
@@ -776,7 +784,7 @@ __device__ __forceinline__ void rows_rstd_any(const RowNorm& nrm, int M, int K, 
 // run by all threads of the work-group.  The additions are those of slice_sum<true>: chunk pairs first.
 template <int ROLE, int W>
 __device__ __forceinline__ void gemm_epilogue_lds(const float* csum, int nchunks, int M, int N, int c0, const GemmEpi& epi,
-                                                  const float* rs, float4 x_first) {
+                                                  const float* rs, float4 x_first, int p_first, float2 cs_first) {
   const int tid = threadIdx.x, nth = blockDim.x;
   const int cstride = M * W;
   auto sum4 = [&](int m, int lc) {
@@ -860,13 +868,14 @@ __device__ __forceinline__ void gemm_epilogue_lds(const float* csum, int nchunks
         float a = sum1(m, lc);
         float b = sum1(m, lc + 8);
         if (rs) { a *= rs[m]; b *= rs[m]; }
-        qkv_pair(a, b, m, col, N / 3, epi);
+        if (idx < nth) qkv_pair_at(a, b, m, col, N / 3, epi, p_first, cs_first);   // (requested ahead of the k loop)
+        else qkv_pair(a, b, m, col, N / 3, epi);
       }
     }
   }
 }
 
-template <int CT, int NT, int DEPTH, bool STREAM>
+template <int CT, int NT, int DEPTH, bool STREAM, bool ROWMAJOR = false>     // (ROWMAJOR as above)
 __global__ __launch_bounds__(512) void k_gemm_bf16_wide(const uint4* __restrict__ Wsw, int NTILES,
                                                         const uint4* __restrict__ XF, int M, RowNorm nrm, int K, int N,
                                                         int role, GemmEpi epi) {
@@ -900,7 +909,8 @@ __global__ __launch_bounds__(512) void k_gemm_bf16_wide(const uint4* __restrict_
     const uint4* wbase = Wsw + (size_t)c * NTILES * (kSliceUnits * 8) * 64 + (size_t)kk * 64 + lane;
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
-      const uint4* p = wbase + (size_t)tile_c[t] * ksteps_c * 64;
+      const uint4* p = ROWMAJOR ? Wsw + (size_t)(tile_c[t] * 16 + (lane & 15)) * (K >> 3) + s * 4 + (lane >> 4)
+                                : wbase + (size_t)tile_c[t] * ksteps_c * 64;
       st.a[t] = STREAM ? ld_nt(p) : *p;
     }
     const uint4* xb = XF + (size_t)s * 4 * 64 + (size_t)c * kFragChunkPad + lane;
@@ -957,6 +967,15 @@ __global__ __launch_bounds__(512) void k_gemm_bf16_wide(const uint4* __restrict_
     const int m = tid / (W / 4), col = tile0 * 16 + (tid - m * (W / 4)) * 4;
     if (m < M && col < N) x_first = *reinterpret_cast<const float4*>(epi.out + (size_t)m * N + col);
   }
+  int p_first = 0;                                         // QKV: the row's position and rotation entry
+  float2 cs_first = make_float2(1.f, 0.f);
+  if (role == kRoleQKV) {
+    const int m = tid / (W / 2), r = tid - m * (W / 2), col = tile0 * 16 + 16 * (r >> 3) + (r & 7);
+    if (m < M && col < N) {
+      p_first = pos_of(epi.pos, m);
+      cs_first = epi.rope_cs[qkv_rope_index(m, col, N / 3, epi.hd)];
+    }
+  }
   if (has_stats) rows_rstd_any(nrm, M, K, s_rstd);
   if (work) {
     // whole turns of the ring without a condition around a request (a branch would make the compiler assume the
@@ -981,11 +1000,11 @@ __global__ __launch_bounds__(512) void k_gemm_bf16_wide(const uint4* __restrict_
   const float* rs = has_stats ? s_rstd : nullptr;
   const int c0 = tile0 * 16;
   switch (role) {
-    case kRoleQKV: gemm_epilogue_lds<kRoleQKV, W>(csum, nchunks, M, N, c0, epi, rs, x_first); break;
+    case kRoleQKV: gemm_epilogue_lds<kRoleQKV, W>(csum, nchunks, M, N, c0, epi, rs, x_first, p_first, cs_first); break;
     case kRoleWo:
-    case kRoleDown: gemm_epilogue_lds<kRoleWo, W>(csum, nchunks, M, N, c0, epi, rs, x_first); break;
-    case kRoleGateUp: gemm_epilogue_lds<kRoleGateUp, W>(csum, nchunks, M, N, c0, epi, rs, x_first); break;
-    default: gemm_epilogue_lds<kRoleHead, W>(csum, nchunks, M, N, c0, epi, rs, x_first); break;
+    case kRoleDown: gemm_epilogue_lds<kRoleWo, W>(csum, nchunks, M, N, c0, epi, rs, x_first, p_first, cs_first); break;
+    case kRoleGateUp: gemm_epilogue_lds<kRoleGateUp, W>(csum, nchunks, M, N, c0, epi, rs, x_first, p_first, cs_first); break;
+    default: gemm_epilogue_lds<kRoleHead, W>(csum, nchunks, M, N, c0, epi, rs, x_first, p_first, cs_first); break;
   }
 }
 
@@ -1085,6 +1104,45 @@ static WideCfg wide_cfg(int role, int M, int NTILES, int K) {
     if (c.nt == 3) c.nt = 4;
   }
   return c;
+}
+
+// Y [M, N] = X . W^T with W [N, K] as the caller has it (bf16, row-major); frag: scratch for M > 4.  Returns false,
+// launching nothing, for shapes that need the split-K kernel (few tiles with a long k; LDS).
+bool launch_gemm_rowmajor(const uint16_t* W, int N, int K, const float* X, int M, float* Y, uint4* frag, hipStream_t st) {
+  const int NTILES = N / 16, nchunks = gemm_slices(K, 1);
+  const RowNorm none{nullptr, nullptr, 0, 0.f};
+  GemmEpi e{};
+  e.out = Y;
+  e.hd = 64;
+  const uint4* Wr = reinterpret_cast<const uint4*>(W);
+  const size_t rl = rows_path_lds(kRoleHead, M, N, K);
+  if (rl && M <= 4) {
+#define STAIRS_ROWM(r) \
+  hipLaunchKernelGGL((k_gemm_bf16_rows<r, kRoleHead, 4, 2, false, true>), dim3(NTILES), dim3(256), rl, st, Wr, NTILES, X, K, none, K, N, e)
+    if (M == 1) STAIRS_ROWM(1);
+    else if (M == 2) STAIRS_ROWM(2);
+    else if (M == 3) STAIRS_ROWM(3);
+    else STAIRS_ROWM(4);
+#undef STAIRS_ROWM
+    return true;
+  }
+  const WideCfg wc = wide_cfg(kRoleHead, M, NTILES, K);
+  const int nt = NTILES <= 256 ? 1 : 2, nw = std::min(8, nchunks);
+  const size_t lds = (size_t)nchunks * M * nt * 16 * sizeof(float);
+  if (M <= 4 || wc.nt == 0 || lds > kWideMaxLds) return false;
+  launch_split_frag(X, K, M, K, nullptr, frag, st);
+  const dim3 grid((NTILES + nt - 1) / nt), block(64 * nw);
+#define STAIRS_WIDEM(ct, nt, dp) \
+  hipLaunchKernelGGL((k_gemm_bf16_wide<ct, nt, dp, false, true>), grid, block, lds, st, Wr, NTILES, frag, M, none, K, N, (int)kRoleHead, e)
+  if (M <= 16) {
+    if (nt == 1) STAIRS_WIDEM(1, 1, kWideDepth1);
+    else STAIRS_WIDEM(1, 2, kWideDepth2);
+  } else {
+    if (nt == 1) STAIRS_WIDEM(2, 1, wide_depth2(kWideDepth1));
+    else STAIRS_WIDEM(2, 2, wide_depth2(kWideDepth2));
+  }
+#undef STAIRS_WIDEM
+  return true;
 }
 
 // fp32 weights, row-major: one wave per output feature, lanes stride over k.
@@ -2491,6 +2549,14 @@ hipError_t configure_kernels() {
   STAIRS_OPTIN_WIDE(1, 2, kWideDepth2); STAIRS_OPTIN_WIDE(2, 2, kWideDepth2);
   STAIRS_OPTIN_WIDE(1, 1, kWideDepth1); STAIRS_OPTIN_WIDE(2, 1, kWideDepth1);
   STAIRS_OPTIN_WIDE_(1, 1, kWideDepthChunk);
+  optin((const void*)k_gemm_bf16_rows<1, kRoleHead, 4, 2, false, true>, kRowsPathMaxLds);
+  optin((const void*)k_gemm_bf16_rows<2, kRoleHead, 4, 2, false, true>, kRowsPathMaxLds);
+  optin((const void*)k_gemm_bf16_rows<3, kRoleHead, 4, 2, false, true>, kRowsPathMaxLds);
+  optin((const void*)k_gemm_bf16_rows<4, kRoleHead, 4, 2, false, true>, kRowsPathMaxLds);
+  optin((const void*)k_gemm_bf16_wide<1, 1, kWideDepth1, false, true>, kWideMaxLds);
+  optin((const void*)k_gemm_bf16_wide<1, 2, kWideDepth2, false, true>, kWideMaxLds);
+  optin((const void*)k_gemm_bf16_wide<2, 1, wide_depth2(kWideDepth1), false, true>, kWideMaxLds);
+  optin((const void*)k_gemm_bf16_wide<2, 2, wide_depth2(kWideDepth2), false, true>, kWideMaxLds);
   STAIRS_OPTIN_WIDE(3, 4, kWideDepth4); STAIRS_OPTIN_WIDE(4, 4, kWideDepth4);
   STAIRS_OPTIN_WIDE(3, 2, kWideDepth2); STAIRS_OPTIN_WIDE(4, 2, kWideDepth2);
   STAIRS_OPTIN_WIDE(3, 1, kWideDepth1); STAIRS_OPTIN_WIDE(4, 1, kWideDepth1);

@@ -74,3 +74,12 @@ def test_shapes_beyond_the_fixed_scratch_are_rejected():
     with pytest.raises(pkg.StairsError) as ei:
         pkg.stairs_gemm_device(1, p, p, p, 33, 16, 256, None)       # shape rules as stairs_gemm_host
     assert ei.value.code == -1
+
+
+@pytest.mark.parametrize("N,K", [(16, 256), (272, 768), (4112, 256), (1024, 2048), (256, 4096), (256, 4352)])
+@pytest.mark.parametrize("M", [1, 4, 5, 16, 17, 32])
+def test_weights_read_where_they_lie_give_the_bits_of_the_laid_out_matrix(N, K, M):
+    """The row-major forms of the kernels (one and two weight tiles per wave, one and two column tiles, a short last k chunk)
+    and, with the longest k, the shape that still lays the matrix out, against the laid-out matrix."""
+    W, X = _inputs(N, K, M, True, 7)
+    assert np.array_equal(_device_gemm(W, X), pkg.stairs_gemm_host(W, X))
