@@ -1031,6 +1031,10 @@ static size_t rows_path_lds(int role, int M, int N, int K) {
   const size_t bytes = (size_t)K * M * 4 + (size_t)(gemm_slices(K, 1) + 1) * M * 16 * 4;
   // 5..7 rows (at 8 the fragment-reading kernel is as fast): the block takes more than half a CU's LDS, so one work-group per CU walks through the tiles; only
   // with a k chunk for each of its waves (k >= 2048) does that beat the fragment-reading kernel
+  // 5..7 rows of small models (up to two work-groups per CU; feed-forward outputs: k up to 4096, one staging pass): 4.9 ..
+  // 7.5 us a launch at 125M and at the large encoder-decoder shape where the fragment-reading kernel took 6.8 .. 9.5
+  if (M > 4 && role != kRoleDown && K < 2048 && N / 16 <= 512 && bytes <= kRowsPathMaxLds) return bytes;
+  if (M > 4 && role == kRoleDown && K <= 4096 && N / 16 <= 128 && bytes <= kRowsPathMaxLdsWide) return bytes;
   if (M > 4)
     return (role != kRoleDown && bytes <= kRowsPathMaxLdsWide && N / 16 >= 192 && K >= 2048) ? std::max(bytes, (size_t)81 * 1024) : 0;
   if (role == kRoleWo || role == kRoleDown) {
@@ -1291,8 +1295,11 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
     else if (role == kRoleGateUp) { STAIRS_ROWS_ROLE(kRoleGateUp, 4, 2); }
     else if (role == kRoleHead) { STAIRS_ROWS_ROLE(kRoleHead, 4, 2); }
     else if (role == kRoleWo) { STAIRS_ROWS_ROLE(kRoleWo, 8, 1); }
-    else if (NTILES < 192 && (size_t)N * K * 2 > kRowsPathSmallMatrix) { STAIRS_ROWS_ROLE4(kRoleDown, 16, 1); }
-    else { STAIRS_ROWS_ROLE4(kRoleDown, 8, 3); }           // (down never takes this path beyond 4 rows: its k is long)
+    else if (M <= 4 && NTILES < 192 && (size_t)N * K * 2 > kRowsPathSmallMatrix) { STAIRS_ROWS_ROLE4(kRoleDown, 16, 1); }
+    else if (M == 5) STAIRS_ROWS(5, kRoleDown, 8, 1);
+    else if (M == 6) STAIRS_ROWS(6, kRoleDown, 8, 1);
+    else if (M == 7) STAIRS_ROWS(7, kRoleDown, 8, 1);
+    else { STAIRS_ROWS_ROLE4(kRoleDown, 8, 3); }
 #undef STAIRS_ROWS_ROLE
 #undef STAIRS_ROWS_ROLE4
 #undef STAIRS_ROWS
@@ -2530,6 +2537,7 @@ hipError_t configure_kernels() {
   optin((const void*)k_gemm_bf16_rows<r, kRoleQKV, 4, 2, st>, kRowsPathMaxLdsWide);                \
   optin((const void*)k_gemm_bf16_rows<r, kRoleGateUp, 4, 2, st>, kRowsPathMaxLdsWide);             \
   optin((const void*)k_gemm_bf16_rows<r, kRoleHead, 4, 2, st>, kRowsPathMaxLdsWide);               \
+  optin((const void*)k_gemm_bf16_rows<r, kRoleDown, 8, 1, st>, kRowsPathMaxLdsWide);               \
   optin((const void*)k_gemm_bf16_rows<r, kRoleWo, 8, 1, st>, kRowsPathMaxLdsWide)
   STAIRS_OPTIN(5);
   STAIRS_OPTIN(6);
