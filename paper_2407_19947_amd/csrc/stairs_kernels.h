@@ -113,8 +113,8 @@ struct GemmEpi {
 };
 
 // ---- skinny GEMM + epilogue ---------------------------------------------------------------
-// bf16: W is swizzled, split-K slices of 512 k, epilogue fused; fp32: W row-major, epilogue in a
-// second kernel.  partial: scratch of gemm_slices() * M * N floats.
+// bf16: W is swizzled, split-K slices of 512 k, epilogue fused; fp32: W row-major,
+// epilogue fused, the row norm gathered from X itself (nrm.ssq_part unused).  partial (bf16): scratch of gemm_slices() * M * N floats.
 // xfrag (bf16, M > 4): the fragments of X with nrm.gain folded in, left by X's producer or by launch_split_frag; with
 // them the launch takes the hand-off-free kernel k_gemm_bf16_wide (no partial sums), without them the split-K kernel.
 void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const float* X, int ldx, int M,

@@ -1149,43 +1149,105 @@ bool launch_gemm_rowmajor(const uint16_t* W, int N, int K, const float* X, int M
   return true;
 }
 
-// fp32 weights, row-major: one wave per output feature, lanes stride over k.
-template <int MR>
+// fp32 weights, row-major: a wave takes the two output features an epilogue combines (rotation pairs, gate and up, else
+// neighbours) for all rows, lanes stride over k, and runs the epilogue itself.  The sum of squares of a normalised input
+// is gathered on the way (every wave reads the whole row anyway).  What bounds it: the launch and one round trip to
+// memory (models of this type are tiny).  With the epilogues in kernels of their own, the attention's merge in another
+// and a branch around every row's loads a layer was 10 launches, now 5 (d 256, 4 layers + 2 of draft, 32 + 64 tokens:
+// 12.6 -> 7.4 ms; residual-writing projection at 1 / 5 rows: 3.35 + 2.4 / 6.9 + 2.4 -> 2.4 / 4.9 us).
+constexpr int kRoleLogits = 5;           // kRoleHead with a normalised input
+template <int MR, int ROLE>
 __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ W, int N, int K,
-                                                  const float* __restrict__ X, int ldx, int M, RowNorm nrm,
-                                                  float* __restrict__ partial) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n = blockIdx.x * 4 + wave;
-  if (n >= N) return;
-  float rs[MR], acc[MR];
-#pragma unroll
-  for (int i = 0; i < MR; ++i) {
-    acc[i] = 0.f;
-    rs[i] = (nrm.gain && nrm.ssq_part && i < M) ? row_rstd(nrm, i, K) : 1.0f;
+                                                  const float* __restrict__ X, int ldx, int M, RowNorm nrm, GemmEpi epi) {
+  constexpr bool NORMED = ROLE == kRoleQKV || ROLE == kRoleGateUp || ROLE == kRoleLogits;
+  const int lane = threadIdx.x & 63;
+  const int pr = blockIdx.x * 4 + (threadIdx.x >> 6);                 // feature pair
+  if (pr >= N / 2) return;
+  const int d = N / 3, half = epi.hd >> 1;
+  int n0, n1, part = 0, h = 0, e = 0;
+  if (ROLE == kRoleQKV) {                                              // (e, e + hd/2) of one head of q, k or v
+    part = pr / (d >> 1);
+    const int c = pr - part * (d >> 1);
+    h = c / half;
+    e = c - h * half;
+    n0 = part * d + h * epi.hd + e;
+    n1 = n0 + half;
+  } else if (ROLE == kRoleGateUp) {
+    n0 = pr;
+    n1 = pr + N / 2;
+  } else {
+    n0 = 2 * pr;
+    n1 = n0 + 1;
   }
+  // lane i finishes row i: what it needs beside the sums is requested first
+  const bool mine = lane < M && lane < MR;
+  float2 old = make_float2(0.f, 0.f), cs = make_float2(1.f, 0.f);
+  int pos = 0;
+  if (mine) {
+    if (ROLE == kRoleWo || ROLE == kRoleDown) old = *reinterpret_cast<const float2*>(epi.out + (size_t)lane * N + n0);
+    if (ROLE == kRoleQKV) {
+      pos = *epi.pos.base + epi.pos.offset + lane;
+      if (part < 2) cs = epi.rope_cs[lane * 64 + e];
+    }
+  }
+  float a0[MR], a1[MR], ss[MR];
+#pragma unroll
+  for (int i = 0; i < MR; ++i) a0[i] = a1[i] = ss[i] = 0.f;
+  // rows past the last are read as the last one and dropped: a branch per row would put one round trip after another
+  const float* xr[MR];
+#pragma unroll
+  for (int i = 0; i < MR; ++i) xr[i] = X + (size_t)min(i, M - 1) * ldx;
+#pragma unroll 2
   for (int k = lane * 4; k < K; k += 256) {
-    const float4 w = *reinterpret_cast<const float4*>(W + (size_t)n * K + k);
-    float4 g = make_float4(1.f, 1.f, 1.f, 1.f);
-    if (nrm.gain) g = *reinterpret_cast<const float4*>(nrm.gain + k);
+    const float4 w0 = *reinterpret_cast<const float4*>(W + (size_t)n0 * K + k), w1 = *reinterpret_cast<const float4*>(W + (size_t)n1 * K + k);
+    float4 g = make_float4(1.f, 1.f, 1.f, 1.f), x[MR];
+    if (NORMED && nrm.gain) g = *reinterpret_cast<const float4*>(nrm.gain + k);
+#pragma unroll
+    for (int i = 0; i < MR; ++i) x[i] = *reinterpret_cast<const float4*>(xr[i] + k);
 #pragma unroll
     for (int i = 0; i < MR; ++i) {
-      if (i < M) {
-        const float4 x = *reinterpret_cast<const float4*>(X + (size_t)i * ldx + k);
-        float a = acc[i];
-        a = fmaf(w.x, x.x * rs[i] * g.x, a);
-        a = fmaf(w.y, x.y * rs[i] * g.y, a);
-        a = fmaf(w.z, x.z * rs[i] * g.z, a);
-        a = fmaf(w.w, x.w * rs[i] * g.w, a);
-        acc[i] = a;
+      float4 y = x[i];
+      if (NORMED) {
+        ss[i] = fmaf(y.w, y.w, fmaf(y.z, y.z, fmaf(y.y, y.y, fmaf(y.x, y.x, ss[i]))));
+        y = make_float4(__fmul_rn(y.x, g.x), __fmul_rn(y.y, g.y), __fmul_rn(y.z, g.z), __fmul_rn(y.w, g.w));
       }
+      a0[i] = fmaf(w0.w, y.w, fmaf(w0.z, y.z, fmaf(w0.y, y.y, fmaf(w0.x, y.x, a0[i]))));
+      a1[i] = fmaf(w1.w, y.w, fmaf(w1.z, y.z, fmaf(w1.y, y.y, fmaf(w1.x, y.x, a1[i]))));
     }
   }
+  // (1/rms goes onto the lanes' sums, not onto the finished one: 64 roundings that average out instead of one that stays)
+  if (NORMED && nrm.gain) {
+#pragma unroll
+    for (int i = 0; i < MR; ++i) {
+      const float r = 1.0f / sqrtf(wave_sum(ss[i]) / (float)K + nrm.eps);
+      a0[i] = __fmul_rn(a0[i], r);
+      a1[i] = __fmul_rn(a1[i], r);
+    }
+  }
+  float v0 = 0.f, v1 = 0.f;
 #pragma unroll
   for (int i = 0; i < MR; ++i) {
-    if (i < M) {
-      const float v = wave_sum(acc[i]);
-      if (lane == 0) partial[(size_t)i * N + n] = v;
+    const float s0 = wave_sum(a0[i]), s1 = wave_sum(a1[i]);
+    v0 = lane == i ? s0 : v0;
+    v1 = lane == i ? s1 : v1;
+  }
+  if (!mine) return;
+  if (ROLE == kRoleWo || ROLE == kRoleDown) {
+    *reinterpret_cast<float2*>(epi.out + (size_t)lane * N + n0) = make_float2(__fadd_rn(old.x, v0), __fadd_rn(old.y, v1));
+  } else if (ROLE == kRoleGateUp) {
+    epi.out[(size_t)lane * (N / 2) + pr] = swiglu(v0, v1);
+  } else if (ROLE == kRoleHead || ROLE == kRoleLogits) {
+    *reinterpret_cast<float2*>(epi.out + (size_t)lane * N + n0) = make_float2(v0, v1);
+  } else if (pos >= 0) {
+    if (part < 2) {
+      const float2 r = rope_rotate(v0, v1, cs);
+      v0 = r.x;
+      v1 = r.y;
     }
+    float* dst = part == 0 ? epi.out + (size_t)lane * d + h * epi.hd + e
+                           : (part == 1 ? epi.Kc32 : epi.Vc32) + ((size_t)h * epi.cap + pos) * epi.hd + e;
+    dst[0] = v0;
+    dst[half] = v1;
   }
 }
 
@@ -1195,16 +1257,8 @@ static int pick_nt(int NTILES, int SG, int want_wgs) {
   return ((size_t)((NTILES + 7) / 8) * SG >= (size_t)want_wgs) ? 2 : 1;
 }
 
-// forward declarations of the unfused epilogues (fp32 models)
-void launch_fin_plain(const float* partial, int S, int M, int N, float* out, int ldo, hipStream_t st);
-void launch_fin_resid(const float* partial, int S, int M, int N, float* x, float* ssq_part, hipStream_t st);
-void launch_fin_swiglu(const float* partial, int S, int M, int f, float* h, hipStream_t st);
-void launch_fin_qkv_rope_f32(const float* partial, int S, int M, int d, int H, const float2* rope_cs, PosRef pos,
-                             float* q_rot, float* Kc, float* Vc, int cap, hipStream_t st);
-
 // Events the next GEMM launch records at the kernel's own start and end (set_gemm_launch_events): lets a measurement
-// take one kernel's duration inside a running forward without event records around it in the stream.  (fp32 models
-// run two kernels per projection: there the events are recorded around the pair.)
+// take one kernel's duration inside a running forward without event records around it in the stream.
 // (per thread: a context is used by one thread at a time)
 static thread_local hipEvent_t g_gemm_ev_start = nullptr, g_gemm_ev_stop = nullptr;
 void set_gemm_launch_events(hipEvent_t start, hipEvent_t stop) {
@@ -1228,29 +1282,32 @@ bool gemm_takes_rows(int M, int K) {
 void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const float* X, int ldx, int M, RowNorm nrm,
                  float* partial, const GemmEpi& epi, hipStream_t st, const uint4* xfrag) {
   if (!dtype_bf16) {
-    dim3 grid((N + 3) / 4), block(256);
+    const dim3 grid((N / 2 + 3) / 4), block(256);
     const float* Wf = static_cast<const float*>(W);
-    // two kernels here: requested launch events become records around the pair
-    hipEvent_t ev_stop = nullptr;
-    if (g_gemm_ev_start && g_gemm_ev_stop) {
-      (void)hipEventRecord(g_gemm_ev_start, st);
-      ev_stop = g_gemm_ev_stop;
-      g_gemm_ev_start = g_gemm_ev_stop = nullptr;
-    }
-    if (M <= 4) hipLaunchKernelGGL(k_gemm_f32<4>, grid, block, 0, st, Wf, N, K, X, ldx, M, nrm, partial);
-    else if (M <= 16) hipLaunchKernelGGL(k_gemm_f32<16>, grid, block, 0, st, Wf, N, K, X, ldx, M, nrm, partial);
-    else hipLaunchKernelGGL(k_gemm_f32<32>, grid, block, 0, st, Wf, N, K, X, ldx, M, nrm, partial);
+#define STAIRS_F32(mr, role) launch_gemm_kernel(k_gemm_f32<mr, role>, grid, block, (size_t)0, st, Wf, N, K, X, ldx, M, nrm, epi)
+#define STAIRS_F32_ROLE(role)               \
+  do {                                      \
+    if (M <= 1) STAIRS_F32(1, role);        \
+    else if (M <= 2) STAIRS_F32(2, role);   \
+    else if (M <= 3) STAIRS_F32(3, role);   \
+    else if (M <= 4) STAIRS_F32(4, role);   \
+    else if (M <= 6) STAIRS_F32(6, role);   \
+    else if (M <= 8) STAIRS_F32(8, role);   \
+    else if (M <= 16) STAIRS_F32(16, role); \
+    else STAIRS_F32(32, role);              \
+  } while (0)
     switch (role) {
-      case kRoleQKV:
-        launch_fin_qkv_rope_f32(partial, 1, M, N / 3, epi.H, epi.rope_cs, epi.pos, epi.out, static_cast<float*>(epi.Kc32),
-                                static_cast<float*>(epi.Vc32), epi.cap, st);
-        break;
+      case kRoleQKV: STAIRS_F32_ROLE(kRoleQKV); break;
       case kRoleWo:
-      case kRoleDown: launch_fin_resid(partial, 1, M, N, epi.out, epi.ssq_out, st); break;
-      case kRoleGateUp: launch_fin_swiglu(partial, 1, M, N / 2, epi.out, st); break;
-      default: launch_fin_plain(partial, 1, M, N, epi.out, N, st); break;
+      case kRoleDown: STAIRS_F32_ROLE(kRoleWo); break;
+      case kRoleGateUp: STAIRS_F32_ROLE(kRoleGateUp); break;
+      default:
+        if (nrm.gain) STAIRS_F32_ROLE(kRoleLogits);
+        else STAIRS_F32_ROLE(kRoleHead);
+        break;
     }
-    if (ev_stop) (void)hipEventRecord(ev_stop, st);
+#undef STAIRS_F32_ROLE
+#undef STAIRS_F32
     return;
   }
   const int S = gemm_slices(K, 1);
@@ -1384,129 +1441,19 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
 }
 
 // ---------------------------------------------------------------------------------------
-// GEMM epilogues
-// ---------------------------------------------------------------------------------------
-__device__ __forceinline__ float4 sum_slices4(const float* partial, int S, int M, int N, int m, int n) {
-  float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s = 0; s < S; ++s) {
-    const float4 p = *reinterpret_cast<const float4*>(partial + ((size_t)s * M + m) * N + n);
-    a.x += p.x; a.y += p.y; a.z += p.z; a.w += p.w;
-  }
-  return a;
-}
-__device__ __forceinline__ float sum_slices1(const float* partial, int S, int M, int N, int m, int n) {
-  float a = 0.f;
-  for (int s = 0; s < S; ++s) a += partial[((size_t)s * M + m) * N + n];
-  return a;
-}
-
-__global__ __launch_bounds__(256) void k_fin_plain(const float* __restrict__ partial, int S, int M, int N,
-                                                   float* __restrict__ out, int ldo) {
-  const int n = (blockIdx.x * 256 + threadIdx.x) * 4, m = blockIdx.y;
-  if (n >= N) return;
-  *reinterpret_cast<float4*>(out + (size_t)m * ldo + n) = sum_slices4(partial, S, M, N, m, n);
-}
-
-__global__ __launch_bounds__(256) void k_fin_resid(const float* __restrict__ partial, int S, int M, int N,
-                                                   float* __restrict__ x, float* __restrict__ ssq_part) {
-  __shared__ float sm[4];
-  const int n = (blockIdx.x * 256 + threadIdx.x) * 4, m = blockIdx.y;
-  float ss = 0.f;
-  if (n < N) {
-    float4 a = sum_slices4(partial, S, M, N, m, n);
-    float4* xp = reinterpret_cast<float4*>(x + (size_t)m * N + n);
-    const float4 r = *xp;
-    a.x += r.x; a.y += r.y; a.z += r.z; a.w += r.w;
-    *xp = a;
-    ss = (a.x * a.x + a.y * a.y) + (a.z * a.z + a.w * a.w);
-  }
-  ss = block_sum_256(ss, sm);
-  if (threadIdx.x == 0) ssq_part[m * gridDim.x + blockIdx.x] = ss;
-}
-
-__global__ __launch_bounds__(256) void k_fin_swiglu(const float* __restrict__ partial, int S, int M, int f,
-                                                    float* __restrict__ h) {
-  const int j = (blockIdx.x * 256 + threadIdx.x) * 4, m = blockIdx.y;
-  if (j >= f) return;
-  const float4 g = sum_slices4(partial, S, M, 2 * f, m, j);
-  const float4 u = sum_slices4(partial, S, M, 2 * f, m, f + j);
-  float4 o;
-  o.x = g.x / (1.0f + expf(-g.x)) * u.x;
-  o.y = g.y / (1.0f + expf(-g.y)) * u.y;
-  o.z = g.z / (1.0f + expf(-g.z)) * u.z;
-  o.w = g.w / (1.0f + expf(-g.w)) * u.w;
-  *reinterpret_cast<float4*>(h + (size_t)m * f + j) = o;
-}
-
-template <typename KV>
-__global__ __launch_bounds__(256) void k_fin_qkv_rope(const float* __restrict__ partial, int S, int M, int d, int H,
-                                                      const float2* __restrict__ rope_cs, PosRef pos,
-                                                      float* __restrict__ q_rot, KV* __restrict__ Kc,
-                                                      KV* __restrict__ Vc, int cap) {
-  const int hd = d / H, half = hd / 2;
-  const int per_row = 3 * H * half;
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  const int m = blockIdx.y;
-  if (idx >= per_row) return;
-  const int e = idx % half;
-  const int h = (idx / half) % H;
-  const int which = idx / (half * H);
-  const int p = *pos.base + pos.offset + m;
-  if (p < 0) return;
-  const int N = 3 * d;
-  const int col = which * d + h * hd + e;
-  const float a = sum_slices1(partial, S, M, N, m, col);
-  const float b = sum_slices1(partial, S, M, N, m, col + half);
-  if (which == 2) {
-    KV* dst = Vc + ((size_t)h * cap + p) * hd + e;
-    store_kv(dst, a);
-    store_kv(dst + half, b);
-    return;
-  }
-  const float2 cs = rope_cs[m * 64 + e];
-  const float ra = a * cs.x - b * cs.y;
-  const float rb = b * cs.x + a * cs.y;
-  if (which == 0) {
-    q_rot[(size_t)m * d + h * hd + e] = ra;
-    q_rot[(size_t)m * d + h * hd + e + half] = rb;
-  } else {
-    KV* dst = Kc + ((size_t)h * cap + p) * hd + e;
-    store_kv(dst, ra);
-    store_kv(dst + half, rb);
-  }
-}
-
-void launch_fin_plain(const float* partial, int S, int M, int N, float* out, int ldo, hipStream_t st) {
-  hipLaunchKernelGGL(k_fin_plain, dim3((N / 4 + 255) / 256, M), dim3(256), 0, st, partial, S, M, N, out, ldo);
-}
-void launch_fin_resid(const float* partial, int S, int M, int N, float* x, float* ssq_part, hipStream_t st) {
-  hipLaunchKernelGGL(k_fin_resid, dim3(ssq_groups(N, 0), M), dim3(256), 0, st, partial, S, M, N, x, ssq_part);
-}
-void launch_fin_swiglu(const float* partial, int S, int M, int f, float* h, hipStream_t st) {
-  hipLaunchKernelGGL(k_fin_swiglu, dim3((f / 4 + 255) / 256, M), dim3(256), 0, st, partial, S, M, f, h);
-}
-void launch_fin_qkv_rope_f32(const float* partial, int S, int M, int d, int H, const float2* rope_cs, PosRef pos,
-                             float* q_rot, float* Kc, float* Vc, int cap, hipStream_t st) {
-  const int per_row = 3 * H * (d / H / 2);
-  dim3 grid((per_row + 255) / 256, M), block(256);
-  hipLaunchKernelGGL(k_fin_qkv_rope<float>, grid, block, 0, st, partial, S, M, d, H, rope_cs, pos, q_rot, Kc, Vc, cap);
-}
-
-// ---------------------------------------------------------------------------------------
 // embedding gather, rope table
 // ---------------------------------------------------------------------------------------
-// GW = residual columns per sum-of-squares partial: 1024 (one per block) or 16 (one per 4 lanes)
+// bf16 models: a sum-of-squares partial per 16 residual columns (the fp32 GEMM gathers its own)
 // The block column after the last embedding column fills the row's rotation table instead:
 // cs[m][i] = (cos, sin)(position * theta^(-2i/hd)), the angle formed in double.
 // A row whose position lies outside [0, tok_cap) or whose token id lies outside [0, vocab) becomes a row of zeros:
 // the gather never leaves the token array or the embedding table, whatever the array holds.
-template <typename E, int GW>
+template <typename E>
 __global__ __launch_bounds__(256) void k_embed(const E* __restrict__ emb, const int* __restrict__ tokens,
                                                int tok_slot_stride, int tok_cap, int vocab, PosRef pos, int d,
                                                float* __restrict__ x, float* __restrict__ ssq_part, int ssq_n, int hd,
                                                const float2* __restrict__ tab, int tab_len, float2* __restrict__ cs, uint4* frag,
                                                const float* __restrict__ frag_gain) {
-  __shared__ float sm[4];
   const int m = blockIdx.y;
   const int p = pos_of(pos, m);
   tokens += (size_t)slot_of(pos, m) * tok_slot_stride;
@@ -1528,10 +1475,7 @@ __global__ __launch_bounds__(256) void k_embed(const E* __restrict__ emb, const 
     ss = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
     if (frag) store_frag4(frag, m, c, v, frag_gain);
   }
-  if (GW == 1024) {
-    ss = block_sum_256(ss, sm);
-    if (threadIdx.x == 0) ssq_part[m * ssq_n + blockIdx.x] = ss;
-  } else {
+  if (sizeof(E) == 2) {
     ss += __shfl_xor(ss, 1);
     ss += __shfl_xor(ss, 2);
     if ((threadIdx.x & 3) == 0 && c < d) ssq_part[m * ssq_n + c / 16] = ss;
@@ -1544,10 +1488,10 @@ void launch_embed(const void* emb, int emb_bf16, const int* tokens, int tok_slot
   dim3 grid((d + 1023) / 1024 + 1, M), block(256);
   const int sn = ssq_groups(d, emb_bf16);
   if (emb_bf16)
-    hipLaunchKernelGGL((k_embed<uint16_t, 16>), grid, block, 0, st, static_cast<const uint16_t*>(emb), tokens,
+    hipLaunchKernelGGL((k_embed<uint16_t>), grid, block, 0, st, static_cast<const uint16_t*>(emb), tokens,
                        tok_slot_stride, tok_cap, vocab, pos, d, x, ssq_part, sn, hd, tab, tab_len, cs, frag, frag_gain);
   else
-    hipLaunchKernelGGL((k_embed<float, 1024>), grid, block, 0, st, static_cast<const float*>(emb), tokens,
+    hipLaunchKernelGGL((k_embed<float>), grid, block, 0, st, static_cast<const float*>(emb), tokens,
                        tok_slot_stride, tok_cap, vocab, pos, d, x, ssq_part, sn, hd, tab, tab_len, cs, nullptr, nullptr);
 }
 
@@ -1571,80 +1515,91 @@ void launch_rope_rows(PosRef pos, int M, int hd, const float2* tab, int tab_len,
 }
 
 // ---------------------------------------------------------------------------------------
-// KV-cache attention: work-group = (128-key chunk, head, group of up to 16 query rows).
-// The chunk's keys, then its values, are staged in LDS once and used by all the rows.
-// Chunk boundaries are absolute key positions and chunks are combined in index order.
+// fp32 caches: work-group = (128-key chunk, head, MR query rows: one up to 8 rows, where work-groups are few, else 16).
+// The chunk's keys, then its values, are staged in LDS; every load of a chunk is in flight at once (with a loop over the
+// staged pieces a chunk was 8 round trips to memory in a row), the values while the scores are formed.
+// Chunk boundaries are absolute key positions and chunks are combined in index order; a launch of one chunk writes
+// the result itself, with the bits the merge of one chunk has.  Neither MR nor the launch changes a row's bits.
+// (4 heads of 64, contexts up to 96, 1 / 5 rows: 6.7 / 12.3 us and 3.3 us of merge -> 4.7 us)
 // ---------------------------------------------------------------------------------------
-template <typename KV, int HD, int MR>
-__global__ __launch_bounds__(128) void k_attn(const float* __restrict__ q, const KV* __restrict__ Kc,
-                                              const KV* __restrict__ Vc, int cap, int d, int H, int M, PosRef pos,
+template <int HD, int MR, bool DIRECT>
+__global__ __launch_bounds__(256) void k_attn(const float* __restrict__ q, const float* __restrict__ Kc,
+                                              const float* __restrict__ Vc, int cap, int d, int H, int M, PosRef pos,
                                               float scale, int nchunk_cap, float* __restrict__ part_o,
-                                              float* __restrict__ part_ml) {
-  constexpr int EPV = 16 / sizeof(KV);     // elements per 16-byte vector
-  constexpr int ROW = HD + EPV;            // padded LDS row
+                                              float* __restrict__ part_ml, float* __restrict__ out) {
+  constexpr int ROW = HD + 4;              // padded LDS row
+  constexpr int VPR = HD / 4;              // 16-byte vectors per key
+  constexpr int VPT = VPR / 2;             // vectors per thread of a chunk
+  constexpr int PARTS = 256 / HD;          // the keys of a chunk are summed in that many runs, added in order
   extern __shared__ uint4 smem_u4[];
-  KV* s_kv = reinterpret_cast<KV*>(smem_u4);                                   // [128][ROW]
-  float* s_q = reinterpret_cast<float*>(s_kv + 128 * ROW);                     // [MR][HD]
+  float* s_kv = reinterpret_cast<float*>(smem_u4);                             // [128][ROW]
+  float* s_q = s_kv + 128 * ROW;                                               // [MR][HD]
   float* s_p = s_q + MR * HD;                                                  // [MR][128]
   float* s_ml = s_p + MR * 128;                                                // [MR][2]
+  float* s_o = s_ml + MR * 2 + 2 * (MR & 1);                                   // [MR][256]
 
-  const int c = blockIdx.x, h = blockIdx.y, row0 = blockIdx.z * 16;
+  const int c = blockIdx.x, h = blockIdx.y, row0 = blockIdx.z * MR;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int pos0 = *pos.base + pos.offset;
-  const int kv_len = pos0 + M;
-  const int key0 = c * kAttnChunk;
-  if (key0 >= kv_len) return;
-  const int nkeys = min(kAttnChunk, kv_len - key0);
   const int rows = min(MR, M - row0);      // valid query rows of this group
+  const int kv_len = MR == 1 ? pos0 + row0 + 1 : pos0 + M;
+  const int key0 = c * kAttnChunk;
+  if (key0 >= kv_len) {
+    if (DIRECT && tid < HD)                // no position of these rows exists
+      for (int i = 0; i < rows; ++i) out[(size_t)(row0 + i) * d + h * HD + tid] = 0.f;
+    return;
+  }
+  const int nkeys = min(kAttnChunk, kv_len - key0);
 
-  for (int idx = tid; idx < MR * HD; idx += 128) {
+  float4 kr[VPT], vr[VPT];
+  const float4* ksrc = reinterpret_cast<const float4*>(Kc + ((size_t)h * cap + key0) * HD);
+  const float4* vsrc = reinterpret_cast<const float4*>(Vc + ((size_t)h * cap + key0) * HD);
+  const int nvec = nkeys * VPR;            // (vectors past the last key are read as the last vector)
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) kr[u] = ksrc[min(u * 256 + tid, nvec - 1)];
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) vr[u] = vsrc[min(u * 256 + tid, nvec - 1)];
+  for (int idx = tid; idx < MR * HD; idx += 256) {
     const int i = idx / HD, e = idx - i * HD;
     s_q[idx] = (i < rows) ? q[(size_t)(row0 + i) * d + h * HD + e] : 0.f;
   }
-  {
-    const uint4* src = reinterpret_cast<const uint4*>(Kc + ((size_t)h * cap + key0) * HD);
-    constexpr int VPR = HD / EPV;
-    for (int idx = tid; idx < nkeys * VPR; idx += 128) {
-      const int r = idx / VPR, cc = idx - r * VPR;
-      *reinterpret_cast<uint4*>(s_kv + r * ROW + cc * EPV) = src[idx];
-    }
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const int idx = u * 256 + tid, r = idx / VPR, cc = idx - r * VPR;
+    *reinterpret_cast<float4*>(s_kv + r * ROW + cc * 4) = kr[u];
   }
   __syncthreads();
 
-  float sacc[MR];
+  {                                        // two neighbouring lanes per key, alternate quadruples of the dimensions
+    const int key = tid >> 1, part = tid & 1;
+    float sacc[MR];
 #pragma unroll
-  for (int i = 0; i < MR; ++i) sacc[i] = 0.f;
-  if (tid < nkeys) {
-    const KV* krow = s_kv + tid * ROW;
-    for (int e0 = 0; e0 < HD; e0 += EPV) {
-      float kf[EPV];
-#pragma unroll
-      for (int j = 0; j < EPV; ++j) kf[j] = load_kv(krow + e0 + j);
+    for (int i = 0; i < MR; ++i) sacc[i] = 0.f;
+    const float* krow = s_kv + key * ROW + part * 4;
+#pragma unroll 4
+    for (int e0 = 0; e0 < HD; e0 += 8) {
+      const float4 kf = *reinterpret_cast<const float4*>(krow + e0);
 #pragma unroll
       for (int i = 0; i < MR; ++i) {
-        float a = sacc[i];
-#pragma unroll
-        for (int j = 0; j < EPV; ++j) a = fmaf(s_q[i * HD + e0 + j], kf[j], a);
-        sacc[i] = a;
+        const float4 qf = *reinterpret_cast<const float4*>(s_q + i * HD + part * 4 + e0);
+        sacc[i] = fmaf(qf.w, kf.w, fmaf(qf.z, kf.z, fmaf(qf.y, kf.y, fmaf(qf.x, kf.x, sacc[i]))));
       }
     }
-  }
 #pragma unroll
-  for (int i = 0; i < MR; ++i) {
-    const bool ok = (tid < nkeys) && (i < rows) && (key0 + tid <= pos0 + row0 + i);
-    s_p[i * 128 + tid] = ok ? sacc[i] * scale : -INFINITY;
+    for (int i = 0; i < MR; ++i) {
+      const float sum = __fadd_rn(sacc[i], __shfl_xor(sacc[i], 1));
+      const bool ok = (key < nkeys) && (i < rows) && (key0 + key <= pos0 + row0 + i);
+      if (part == 0) s_p[i * 128 + key] = ok ? sum * scale : -INFINITY;
+    }
   }
   __syncthreads();   // everybody is done with the keys; scores are in LDS
 
-  {
-    const uint4* src = reinterpret_cast<const uint4*>(Vc + ((size_t)h * cap + key0) * HD);
-    constexpr int VPR = HD / EPV;
-    for (int idx = tid; idx < nkeys * VPR; idx += 128) {
-      const int r = idx / VPR, cc = idx - r * VPR;
-      *reinterpret_cast<uint4*>(s_kv + r * ROW + cc * EPV) = src[idx];
-    }
+#pragma unroll
+  for (int u = 0; u < VPT; ++u) {
+    const int idx = u * 256 + tid, r = idx / VPR, cc = idx - r * VPR;
+    *reinterpret_cast<float4*>(s_kv + r * ROW + cc * 4) = idx < nvec ? vr[u] : make_float4(0.f, 0.f, 0.f, 0.f);
   }
-  for (int i = wave; i < MR; i += 2) {
+  for (int i = wave; i < MR; i += 4) {
     const float a = s_p[i * 128 + lane], b = s_p[i * 128 + lane + 64];
     const float mx = wave_max(fmaxf(a, b));
     float pa = 0.f, pb = 0.f;
@@ -1662,20 +1617,36 @@ __global__ __launch_bounds__(128) void k_attn(const float* __restrict__ q, const
   }
   __syncthreads();
 
-  if (tid < HD) {
+  {
+    const int e = tid % HD, t0 = tid / HD * (128 / PARTS);
     float o[MR];
 #pragma unroll
     for (int i = 0; i < MR; ++i) o[i] = 0.f;
-    for (int t = 0; t < nkeys; ++t) {
-      const float v = load_kv(s_kv + t * ROW + tid);
+#pragma unroll 2
+    for (int t = t0; t < t0 + 128 / PARTS; t += 8) {   // (keys past the last one: probability 0, values 0)
+      float v[8];
 #pragma unroll
-      for (int i = 0; i < MR; ++i) o[i] = fmaf(s_p[i * 128 + t], v, o[i]);
+      for (int j = 0; j < 8; ++j) v[j] = s_kv[(t + j) * ROW + e];
+#pragma unroll
+      for (int i = 0; i < MR; ++i) {
+        const float4 p0 = *reinterpret_cast<const float4*>(s_p + i * 128 + t), p1 = *reinterpret_cast<const float4*>(s_p + i * 128 + t + 4);
+        o[i] = fmaf(p0.w, v[3], fmaf(p0.z, v[2], fmaf(p0.y, v[1], fmaf(p0.x, v[0], o[i]))));
+        o[i] = fmaf(p1.w, v[7], fmaf(p1.z, v[6], fmaf(p1.y, v[5], fmaf(p1.x, v[4], o[i]))));
+      }
     }
 #pragma unroll
-    for (int i = 0; i < MR; ++i)
-      if (i < rows) part_o[(((size_t)(row0 + i) * H + h) * nchunk_cap + c) * HD + tid] = o[i];
+    for (int i = 0; i < MR; ++i) s_o[i * 256 + tid] = o[i];
   }
-  if (tid < rows) {
+  __syncthreads();
+  if (tid < HD)
+    for (int i = 0; i < rows; ++i) {
+      float o = s_o[i * 256 + tid];
+#pragma unroll
+      for (int part = 1; part < PARTS; ++part) o = __fadd_rn(o, s_o[i * 256 + part * HD + tid]);
+      if (DIRECT) out[(size_t)(row0 + i) * d + h * HD + tid] = pos0 + row0 + i < 0 ? 0.f : o / s_ml[i * 2 + 1];
+      else part_o[(((size_t)(row0 + i) * H + h) * nchunk_cap + c) * HD + tid] = o;
+    }
+  if (!DIRECT && tid < rows) {
     float* ml = part_ml + (((size_t)(row0 + tid) * H + h) * nchunk_cap + c) * 2;
     ml[0] = s_ml[tid * 2];
     ml[1] = s_ml[tid * 2 + 1];
@@ -2160,24 +2131,25 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* part_o, const f
                  frag, frag_rt, row0);
 }
 
-template <typename KV, int HD>
-static void attn_dispatch(const float* q, const void* Kc, const void* Vc, int cap, int d, int H, int M, PosRef pos,
-                          int nchunk_launch, int nchunk_cap, float* part_o, float* part_ml, hipStream_t st) {
+template <int HD>
+static void attn_dispatch(const float* q, const float* K, const float* V, int cap, int d, int H, int M, PosRef pos,
+                          int nchunk_launch, int nchunk_cap, float* part_o, float* part_ml, float* out, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)HD);
-  const KV* K = static_cast<const KV*>(Kc);
-  const KV* V = static_cast<const KV*>(Vc);
-  dim3 grid(nchunk_launch, H, (M + 15) / 16), block(128);
-  constexpr int EPV = 16 / sizeof(KV);
-#define STAIRS_ATTN(mr)                                                                                   \
-  {                                                                                                       \
-    const size_t lds = (size_t)128 * (HD + EPV) * sizeof(KV) + (size_t)(mr) * (HD + 128 + 2) * sizeof(float); \
-    hipLaunchKernelGGL((k_attn<KV, HD, mr>), grid, block, lds, st, q, K, V, cap, d, H, M, pos, scale,       \
-                       nchunk_cap, part_o, part_ml);                                                      \
+  const int mr = M <= 8 ? 1 : 16;
+  const dim3 grid(nchunk_launch, H, (M + mr - 1) / mr), block(256);
+  const size_t lds = (size_t)(128 * (HD + 4) + mr * (HD + 128 + 2 + 256) + 2) * sizeof(float);
+#define STAIRS_ATTN(mrv, direct)                                                                                          \
+  hipLaunchKernelGGL((k_attn<HD, mrv, direct>), grid, block, lds, st, q, K, V, cap, d, H, M, pos, scale, nchunk_cap, part_o, \
+                     part_ml, out)
+  if (nchunk_launch == 1) {
+    if (mr == 1) STAIRS_ATTN(1, true);
+    else STAIRS_ATTN(16, true);
+    return;
   }
-  if (M <= 2) STAIRS_ATTN(2)
-  else if (M <= 8) STAIRS_ATTN(8)
-  else STAIRS_ATTN(16)
+  if (mr == 1) STAIRS_ATTN(1, false);
+  else STAIRS_ATTN(16, false);
 #undef STAIRS_ATTN
+  hipLaunchKernelGGL(k_attn_combine<HD>, dim3(H, M), dim3(HD), 0, st, part_o, part_ml, H, pos, nchunk_cap, out, d);
 }
 
 void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv_half, int cap, int d, int H, int M,
@@ -2222,12 +2194,9 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
 #undef STAIRS_ATTN16
     return;
   }
-  if (hd == 128) attn_dispatch<float, 128>(q_rot, Kc, Vc, cap, d, H, M, pos, nchunk_launch, nchunk_cap, part_o, part_ml, st);
-  else attn_dispatch<float, 64>(q_rot, Kc, Vc, cap, d, H, M, pos, nchunk_launch, nchunk_cap, part_o, part_ml, st);
-  if (hd == 128)
-    hipLaunchKernelGGL(k_attn_combine<128>, dim3(H, M), dim3(128), 0, st, part_o, part_ml, H, pos, nchunk_cap, out, d);
-  else
-    hipLaunchKernelGGL(k_attn_combine<64>, dim3(H, M), dim3(64), 0, st, part_o, part_ml, H, pos, nchunk_cap, out, d);
+  const float *K = static_cast<const float*>(Kc), *V = static_cast<const float*>(Vc);
+  if (hd == 128) attn_dispatch<128>(q_rot, K, V, cap, d, H, M, pos, nchunk_launch, nchunk_cap, part_o, part_ml, out, st);
+  else attn_dispatch<64>(q_rot, K, V, cap, d, H, M, pos, nchunk_launch, nchunk_cap, part_o, part_ml, out, st);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2573,6 +2542,10 @@ hipError_t configure_kernels() {
   if (configure_block_kernels() != hipSuccess) e = hipErrorInvalidValue;
   // the stand-alone attention merge keeps a table of all chunks in LDS: large for long contexts (the fused
   // merge runs for at most kAttnFusedMaxChunks chunks and stays small)
+  optin((const void*)k_attn<128, 1, true>, 128 * 1024);
+  optin((const void*)k_attn<128, 1, false>, 128 * 1024);
+  optin((const void*)k_attn<128, 16, true>, 128 * 1024);
+  optin((const void*)k_attn<128, 16, false>, 128 * 1024);
   optin((const void*)k_attn_merge<128>, kAttnMergeMaxLds);
   optin((const void*)k_attn_merge<64>, kAttnMergeMaxLds);
   return e;

@@ -548,6 +548,43 @@ def test_row_bits_do_not_depend_on_the_query_tiles(P):
             assert np.array_equal(lg, want[:k + 1]), k
 
 
+@pytest.mark.parametrize("d,heads,ffn,vocab", [(2048, 16, 4096, 512), (1792, 14, 4096, 8192), (1792, 14, 4352, 8208)])
+def test_five_to_seven_rows_of_small_models_have_the_bits_of_any_other_count(d, heads, ffn, vocab):
+    """Around the limits of the LDS-resident GEMM at 5..7 rows (k below 2048 and 512 tiles; down projection: 4096 and 128):
+    stair batches of 16, 7, 6, 5, 4 and 1 rows from the same state share their rows' bits."""
+    w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=d, n_heads=heads, d_ffn=ffn, vocab=vocab),
+                           draft=dict(kind="prefix", n_layers=1), P=21, G=1)
+    target, draft = si.make_pair(w)
+    prompt = si.make_prompt(w)
+    dr = np.random.default_rng([8, d, ffn]).integers(0, vocab, 15).astype(np.int32)
+    want = None
+    with pkg.Stairs(target, draft, k_max=15, max_seq=64) as s:
+        for k in (15, 6, 5, 4, 3, 0):
+            s.prefill(prompt)
+            _, _, lg = s.verify_tokens(dr[:k], logits=True)
+            want = lg.copy() if want is None else want
+            assert np.array_equal(lg, want[:k + 1]), k
+
+
+@pytest.mark.parametrize("heads,P", [(h, p) for h in (2, 4) for p in (1, 96, 119, 120, 121, 127, 128, 129, 250)])
+def test_fp32_rows_do_not_depend_on_their_number(heads, P):
+    """fp32, head size 128 and 64, contexts around the 128-key chunks (one chunk: the attention kernel writes the result, more:
+    the merge): stair batches of 1..8 rows (one row per work-group) and of 9..32 rows (16) share their rows' bits."""
+    w = si.scaled_workload("cfg1_tiny_fp32", target=dict(n_layers=2, d_model=256, n_heads=heads, d_ffn=260, vocab=516), P=P, G=1)
+    target, draft = si.make_pair(w)
+    prompt = si.make_prompt(w)
+    dr = np.random.default_rng([9, P]).integers(0, 516, 31).astype(np.int32)
+    ref = so.forward_full(so.OracleModel(target, np.float64), np.concatenate([prompt, dr]))[-32:]
+    want = None
+    with pkg.Stairs(target, draft, k_max=31, max_seq=P + 40) as s:
+        for k in (31, 15, 8, 7, 5, 4, 3, 2, 1, 0):
+            s.prefill(prompt)
+            _, _, lg = s.verify_tokens(dr[:k], logits=True)
+            want = lg.copy() if want is None else want
+            assert np.array_equal(lg, want[:k + 1]), k
+    assert np.max(np.abs(want - ref)) < 2e-4
+
+
 def test_longest_context_stair_batches(monkeypatch):
     """max_seq = 60000 (the most the library takes: 469 attention chunks, the stand-alone chunk merge with its
     largest table).  The 32-row stair batch is compared with the oracle's logits stored by
