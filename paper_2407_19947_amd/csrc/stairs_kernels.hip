@@ -1103,7 +1103,10 @@ static WideCfg wide_cfg(int role, int M, int NTILES, int K) {
     if ((f.nt == 0 || f.nt == 1 || f.nt == 2 || f.nt == 3 || f.nt == 4 || f.nt == 6 || f.nt == 8) && f.nw >= 1 && f.nw <= 8) c = f;
   }
   if (M > 2 * 16) {                      // 33..64 rows: this kernel only (split-K stops at two column tiles)
-    if (c.nt == 0) c = {1, 4};
+    // one work-group per CU (its chunk sums fill the LDS): 8 waves, two a SIMD, cover each other's waits for the fragments,
+    // which outweigh the weights here (64 rows, 1376 and 2000 tiles x 8 chunks, mean of both: 62.2 -> 57.8 us with 4 -> 8 waves)
+    if (c.nt == 0) c = {1, 8};
+    c.nw = std::min(8, nchunks);
     if (c.nt > 4) c.nt = 4;                 // (the three- and four-column-tile forms exist for 1, 2 and 4 tiles per wave)
     if (c.nt == 3) c.nt = 4;
   }
@@ -2164,8 +2167,11 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
     const int units = nchunk_launch;
     nchunk_launch = (nchunk_launch * kAttnChunk + kAttnChunkH - 1) / kAttnChunkH;
     dim3 grid(nchunk_launch, H, nslots), block(256);
-    // chunks every row block of this launch has keys in: callers round the 128-key units up to a multiple of 4 at most
-    const int sure = am.kv_fixed > 0 ? nchunk_launch : nslots > 1 ? 1 : std::max(1, ((units - 4) * kAttnChunk + 1) / kAttnChunkH);
+    // chunks every row block of this launch has keys in: callers round the 128-key units up to a multiple of 4 at most.
+    // Several sequences: their lengths differ, and with many heads at once the launch is bound by the bytes, so each
+    // work-group looks up its length first and requests no more (64 slots of 16 heads, 3 rows, contexts of 16..210 keys:
+    // 27.3 -> 17.9 us; 16 of 32, 4 rows, 40..350 keys: 19.7 -> 15.8 us against requesting the first chunk whole)
+    const int sure = am.kv_fixed > 0 ? nchunk_launch : nslots > 1 ? 0 : std::max(1, ((units - 4) * kAttnChunk + 1) / kAttnChunkH);
     // merge step's LDS: (max, sum) table, row maxima, and for more than kMergeCB chunks the group sums of as many
     // rows per pass as fit in 48 KiB, less when the table is large (the whole stays under kAttnMergeMaxLds)
     const int G = (nchunk_launch + kMergeCB - 1) / kMergeCB;
