@@ -112,7 +112,7 @@ void stairs_free(stairs_ctx *ctx);
 
 /* Start a new sequence S = prompt[0..P) (the text both models start from, Sec. 3.3 first
  * paragraph): both models ingest prompt[0..P-2] into their KV caches; the last prompt token is
- * the first row of the first stair batch.  Prompts of 64 rows and more are ingested in blocks of
+ * the first row of the first stair batch.  Prompts of 18 tokens and more are ingested in blocks of
  * up to 2048 rows (bf16 models; the library's own MFMA block GEMM on the same weight tiles the
  * decode kernels read), shorter ones with the decode kernels.  Requires 1 <= P and
  * P + k_max + 1 <= max_seq of both models.
@@ -293,7 +293,7 @@ int stairs_gemm_host(int32_t dtype, const void *W, const float *X, float *Y, int
 /* stairs_gemm_host for callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): the same kernels, but W [N, K] (row-major, `dtype`), X [M, K] and Y [M, N]
  * (float) are DEVICE pointers the caller owns, and everything stairs_gemm_host allocates per call (hand-off counters,
- * partial sums, the re-laid-out bf16 weights, the activation fragments) lives in a fixed device array inside the
+ * partial sums, the bf16 weights of the few shapes that are re-laid out, the activation fragments) lives in a fixed device array inside the
  * library (about 9.3 MiB per GPU the call is used on, held until the process ends).  The call allocates nothing,
  * frees nothing and does not wait: the work is enqueued on hip_stream (a hipStream_t or NULL) and Y is valid once
  * that stream has reached the end of it.  Limits (ECAPACITY beyond them): K <= STAIRS_GEMM_DEVICE_MAX_K; bf16:
