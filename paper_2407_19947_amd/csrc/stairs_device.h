@@ -95,13 +95,6 @@ __device__ __forceinline__ float wave_max(float v) {
   for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
   return v;
 }
-// sum over a 256-thread block, fixed order; sm: 4 floats of LDS
-__device__ __forceinline__ float block_sum_256(float v, float* sm) {
-  v = wave_sum(v);
-  if ((threadIdx.x & 63) == 0) sm[threadIdx.x >> 6] = v;
-  __syncthreads();
-  return (sm[0] + sm[1]) + (sm[2] + sm[3]);
-}
 
 // Data handed from one work-group to another inside a kernel (split-K partial sums, attention chunk
 // partials) is written and read with relaxed device-scope atomic accesses: they write through to / read
