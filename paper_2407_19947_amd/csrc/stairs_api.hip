@@ -598,8 +598,8 @@ int block_layers(stairs_ctx* c, Model* m, int R, bool pieced, bool outputs, F at
     p.frag_out = frag_out;
     p.gain = gain;
     p.ssq_out = kind == kBlkResid ? c->pf_ssq : nullptr;
-    launch_blk_gemm(p, pieced, st, c->pf_part, c->pf_part_floats);
-    return c->sync_launches ? hipStreamSynchronize(st) : hipSuccess;
+    const hipError_t e = launch_blk_gemm(p, pieced, st, c->pf_part, c->pf_part_floats);
+    return e == hipSuccess && c->sync_launches ? hipStreamSynchronize(st) : e;
   };
   for (int l = 0; l < g.n_layers; ++l) {
     const Layer& ly = m->layers[l];
@@ -659,7 +659,7 @@ int forward_block(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int lo
     p.ssq = c->pf_ssq;
     p.ssq_n = d / kBlkSsqCols;
     p.eps = g.rms_eps;
-    launch_blk_gemm(p, true, st, c->pf_part, c->pf_part_floats);
+    HIPCHK(c, launch_blk_gemm(p, true, st, c->pf_part, c->pf_part_floats));
   }
   HIPCHK(c, hipGetLastError());
   return STAIRS_OK;
@@ -822,8 +822,8 @@ int encode_model(stairs_ctx* c, Model* m) {
     p.frag_out = frag_out;
     p.gain = gain;
     p.ssq_out = kind == kBlkResid ? c->pf_ssq : nullptr;
-    launch_blk_gemm(p, S <= kBlkPiecedRows, st, c->pf_part, c->pf_part_floats);
-    return c->sync_launches ? hipStreamSynchronize(st) : hipSuccess;
+    const hipError_t e = launch_blk_gemm(p, S <= kBlkPiecedRows, st, c->pf_part, c->pf_part_floats);
+    return e == hipSuccess && c->sync_launches ? hipStreamSynchronize(st) : e;
   };
   for (size_t l = 0; l < m->enc.size(); ++l) {
     const EdLayer& ly = m->enc[l];

@@ -528,9 +528,29 @@ constexpr int kBlkShapeCount = 2;
 constexpr BlkShape kBlkShapes[kBlkShapeCount] = {{128, 128}, {256, 64}};
 constexpr float kBlkOne = 0.38f, kBlkTwo = 0.84f;
 
-void launch_blk_gemm_as(int shape, bool split, const BlkGemm& p, hipStream_t st, float* part) {
+// floats the pieces of a split launch take
+static size_t blk_part_floats(const BlkGemm& p) { return (size_t)p.pieces * ((p.R + 15) / 16 * 16) * ((p.NTILES - p.tile_first) * 16); }
+
+// The kernel's prologue requests the first kBlkST k-steps of its piece unasked and its loop ends on the last kBlkST + 1: a
+// piece shorter than that would copy k-steps that are not its own, at the end of the range operands past the matrix (the
+// copies carry no bounds).  Pieces as k_gemm_bf16_block cuts them, whole units of the weight layout (256 k).
+bool blk_pieces_fit(int K, int pieces) {
+  const int ksteps = K / 32;
+  if (K < 256 || K % 256 || pieces < 1) return false;
+  for (int i = 0; i < pieces; ++i) {
+    const int end = i + 1 < pieces ? (int)((long)ksteps * (i + 1) / pieces & ~1L) : ksteps;
+    if (end - (int)((long)ksteps * i / pieces & ~1L) < 8) return false;
+  }
+  return true;
+}
+
+hipError_t launch_blk_gemm_as(int shape, bool split, const BlkGemm& p, hipStream_t st, float* part, size_t part_floats) {
+  if (shape < 0 || shape >= kBlkShapeCount || p.R < 1 || p.RT * 16 < p.R || p.tile_first < 0 || p.tile_first >= p.NTILES ||
+      !blk_pieces_fit(p.K, p.pieces))
+    return hipErrorInvalidValue;
   const BlkShape& b = kBlkShapes[shape];
   const int N = (p.NTILES - p.tile_first) * 16;
+  if (split && (p.pieces == 1 || !part || blk_part_floats(p) > part_floats)) return hipErrorInvalidValue;
   const int FB = (N + b.feat - 1) / b.feat, RB = (p.R + b.rows - 1) / b.rows;
   const int blocks = FB * RB, per_xcd = (blocks + 7) / 8;
   const dim3 grid(per_xcd * 8, 1, split ? p.pieces : 1), block(256);
@@ -545,13 +565,14 @@ void launch_blk_gemm_as(int shape, bool split, const BlkGemm& p, hipStream_t st,
   }
 #undef STAIRS_BLK
   if (split) hipLaunchKernelGGL(k_blk_reduce, dim3((N / 16 + 7) / 8, (p.R + 31) / 32), dim3(256), 0, st, p, part);
+  return hipSuccess;
 }
 
 // Pieces of a k range for blocks of rows that belong to sequences of at most kBlkPiecedRows rows each: a function of K
 // alone, so that a row's bits are the same in whatever block it is computed.  About 32 k-steps a piece, at least 4 pieces:
 // between the best counts measured at 60 .. 333 rows (K = 2048: 5 .. 8, 4096: 3 .. 10, 8192: 10 .. 17, 11008: 5 .. 15,
 // all within 10 % of the best); beyond 1024 rows no launch gains from cutting k.
-static int blk_pieces(int K) {
+int blk_pieces(int K) {
   const int ksteps = K / 32;
   return std::min(ksteps / 8, std::max(4, ksteps / 32));
 }
@@ -559,7 +580,7 @@ static int blk_pieces(int K) {
 // The tile shape and the way the pieces are summed, by a model of the launch's time: rounds of work-groups over the 256
 // CUs, each k-step at the rate of the shape's occupancy, the matrix at the rate memory delivers it, and for a split
 // launch the pieces' way through memory and the second kernel.
-void launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t part_floats) {
+hipError_t launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t part_floats) {
   p.pieces = pieced ? blk_pieces(p.K) : 1;
   const int N = (p.NTILES - p.tile_first) * 16, ksteps = p.K / 32;
   int best = 0;
@@ -569,7 +590,7 @@ void launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t
     const BlkShape& b = kBlkShapes[s];
     const int blocks = ((N + b.feat - 1) / b.feat) * ((p.R + b.rows - 1) / b.rows);
     for (int split = 0; split < 2; ++split) {
-      if (split && (p.pieces == 1 || !part || (size_t)p.pieces * ((p.R + 15) / 16 * 16) * N > part_floats)) continue;
+      if (split && (p.pieces == 1 || !part || blk_part_floats(p) > part_floats)) continue;
       const int wgs = split ? blocks * p.pieces : blocks, full = wgs / 512, rem = wgs - full * 512;
       const float rounds = full * kBlkTwo + (rem == 0 ? 0.f : rem <= 256 ? kBlkOne : kBlkOne + (kBlkTwo - kBlkOne) * (rem - 256) / 256);
       float us = rounds * (split ? (float)ksteps / p.pieces : (float)ksteps);
@@ -583,7 +604,7 @@ void launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t
       }
     }
   }
-  launch_blk_gemm_as(best, best_split, p, st, part);
+  return launch_blk_gemm_as(best, best_split, p, st, part, part_floats);
 }
 
 // Attention of a row block without partial results (the rows of a 16-row tile belong to one sequence, see BlkSegs): a

@@ -264,7 +264,13 @@ struct BlkGemm {
 // pieced: the k range is summed in a number of pieces that depends on K alone (rows of sequences of at most
 // kBlkPiecedRows rows: their results are the same bits in whatever block they are computed), else in one.
 // part (part_floats floats): scratch that lets different work-groups take the pieces.
-void launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t part_floats);
+// hipErrorInvalidValue, nothing launched: a shape the kernel does not take (launch_blk_gemm_as).
+hipError_t launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t part_floats);
+// The same with the tile shape (0: 128 features x 128 rows, 1: 256 x 64) and the way the p.pieces are summed (split:
+// different work-groups, through part) given by the caller; results do not depend on either.
+hipError_t launch_blk_gemm_as(int shape, bool split, const BlkGemm& p, hipStream_t st, float* part, size_t part_floats);
+int blk_pieces(int K);                          // pieces of a pieced launch
+bool blk_pieces_fit(int K, int pieces);         // whether every one is long enough for the kernel
 // attention of the block's rows against their sequences' half caches (slot_stride elements apart), output as block
 // fragments; am: scale, bias, kv_fixed as for launch_attention
 void launch_attention_flash(const float* q, const void* Kc, const void* Vc, int cap, int d, int H, size_t slot_stride, const int2* rows,

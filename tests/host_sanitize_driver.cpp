@@ -18,6 +18,7 @@
 #include <vector>
 
 #include "../include/stairs.h"
+#include "../paper_2407_19947_amd/csrc/stairs_kernels.h"
 
 static int g_failed = 0;
 #define CHECK(cond)                                                          \
@@ -377,8 +378,40 @@ static void part2_encoder_decoder() {
   stairs_free(c);
 }
 
+// ---- part 1, the rules that choose launches (host functions of csrc/stairs_kernels.h) -------------------------------
+// Every k range the API accepts is cut into pieces the block GEMM's ring can take, and a launch with shorter pieces, with
+// rows past its fragments or with more pieces than its scratch holds is refused before anything runs.
+static void part1_block_gemm_launches() {
+  for (int K = 256; K <= 131072; K += 256) CHECK(stairs::blk_pieces(K) >= 1 && stairs::blk_pieces_fit(K, stairs::blk_pieces(K)));
+  CHECK(stairs::blk_pieces_fit(4096, 16));           // 128 k-steps: 8 each
+  CHECK(!stairs::blk_pieces_fit(4096, 17) && !stairs::blk_pieces_fit(4096, 128) && !stairs::blk_pieces_fit(512, 3));
+  CHECK(!stairs::blk_pieces_fit(0, 1) && !stairs::blk_pieces_fit(4096 + 32, 1) && !stairs::blk_pieces_fit(4096, 0));
+  stairs::BlkGemm p{};
+  p.NTILES = 16;
+  p.K = 4096;
+  p.RT = 8;
+  p.R = 128;
+  float part = 0.f;
+  auto refused = [&](int shape, bool split, size_t floats) {
+    return stairs::launch_blk_gemm_as(shape, split, p, nullptr, &part, floats) == hipErrorInvalidValue;
+  };
+  for (int pieces : {0, -1, 17, 64}) {
+    p.pieces = pieces;
+    CHECK(refused(0, true, (size_t)1 << 40) && refused(1, false, 0));
+  }
+  p.pieces = 4;
+  CHECK(refused(2, false, 0) && refused(-1, false, 0));
+  CHECK(refused(0, true, (size_t)4 * 128 * 256 - 1));
+  p.R = 129;                                         // one row more than the fragments are laid out for
+  CHECK(refused(0, false, 0));
+  p.R = 128;
+  p.tile_first = 16;
+  CHECK(refused(0, false, 0));
+}
+
 int main() {
   part1_without_gpu();
+  part1_block_gemm_launches();
   std::printf("part 1 (no GPU): %d failed checks\n", g_failed);
   std::fflush(stdout);
   int ndev = 0;

@@ -12,7 +12,7 @@ import __graft_entry__ as entry
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SOURCES = [os.path.join(ROOT, "paper_2407_19947_amd", "csrc", n) for n in
-           ("stairs_kernels.hip", "stairs_kernels.h", "stairs_api.hip")] + \
+           ("stairs_kernels.hip", "stairs_block.hip", "stairs_api.hip", "stairs_kernels.h", "stairs_device.h")] + \
           [os.path.join(ROOT, "include", "stairs.h"), entry.SANITIZE_DRIVER + ".cpp"]
 ENV = dict(os.environ, ASAN_OPTIONS="detect_leaks=0", UBSAN_OPTIONS="print_stacktrace=1:halt_on_error=1")
 
