@@ -112,9 +112,9 @@ void stairs_free(stairs_ctx *ctx);
 
 /* Start a new sequence S = prompt[0..P) (the text both models start from, Sec. 3.3 first
  * paragraph): both models ingest prompt[0..P-2] into their KV caches; the last prompt token is
- * the first row of the first stair batch.  Prompts of 18 tokens and more are ingested in blocks of
- * up to 2048 rows (bf16 models; the library's own MFMA block GEMM on the same weight tiles the
- * decode kernels read), shorter ones with the decode kernels.  Requires 1 <= P and
+ * the first row of the first stair batch.  Prompts of 34 tokens and more (18 and more on a context that
+ * has reserved several sequences) are ingested in blocks of up to 2048 rows (bf16 models; the library's own
+ * MFMA block GEMM on the same weight tiles the decode kernels read), shorter ones with the decode kernels.  Requires 1 <= P and
  * P + k_max + 1 <= max_seq of both models.
  * Errors: EINVAL (NULL, P < 1, token id outside [0, vocab)), ECAPACITY. */
 int stairs_prefill(stairs_ctx *ctx, const int32_t *prompt, int32_t P);
@@ -176,7 +176,8 @@ int stairs_decode_adaptive(stairs_ctx *ctx, int32_t G, int32_t k_first, int32_t 
  * own key/value caches, length and acceptance (Sec. 3.3 applied per sequence).  Up to STAIRS_MAX_STREAM_ROWS rows per
  * forward run on the kernels of the single-sequence path (models with d_model, d_ffn <= 16384; else STAIRS_MAX_ROWS)
  * and each sequence's output is bit for bit what stairs_generate gives
- * for it alone; forwards of more rows (up to STAIRS_MAX_BATCH_ROWS) run on the block kernels of the prompt ingestion
+ * for it alone on the same context (before the reservation a prompt of 18 .. 33 tokens takes other kernels, see
+ * stairs_prefill, whose sums round differently in the last bits); forwards of more rows (up to STAIRS_MAX_BATCH_ROWS) run on the block kernels of the prompt ingestion
  * (one order of additions per output whatever the batch, so a sequence's output does not depend on which others share
  * the forward; against the sequence alone it is the same greedy choice up to near-ties of the logits).
  * stairs_reserve_batch makes room for up to max_batch sequences (caches and token arrays grow max_batch-fold;

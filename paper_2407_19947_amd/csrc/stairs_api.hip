@@ -874,13 +874,20 @@ int ingest_blocks(stairs_ctx* c, Model* m, int from, int to, int slot) {
   return STAIRS_OK;
 }
 
-constexpr int kBlockPrefillMin = 17;   // fewer rows than this go through the decode kernels
+// Fewest rows of a prompt that go through the block kernels.  One sequence: more than one forward of the decode kernels
+// takes.  A layer is four or five launches of 5 .. 20 us there and eight on the block kernels, whose smallest tile is 64
+// rows (17 / 32 rows through whole models, decode kernels against blocks: 125M 495 / 550 us against 652 / 653, 1B 1.66 /
+// 1.82 ms against 2.04 / 2.06, 7B 3.65 / 3.86 against 4.21 / 4.26); 33 rows are two forwards (813 us, 2.76 and 6.25 ms
+// against 681 us, 2.14 and 4.43).  Several sequences: prompts share blocks, which pays from 17 rows on (16 prompts of 18 ..
+// 40 tokens: 125M 0.63 ms in blocks, 3.2 one by one; 7B, 2 + 1 layers, 0.91 against 2.5), and a sequence alone takes the
+// same kernels there, so that its bits are those it has in a batch.
+static int block_prefill_min(const stairs_ctx* c) { return c->n_slots > 1 ? 17 : kMaxRows + 1; }
 
 // ingest positions [from, to) of sequence slot `slot` into a model's cache, no logits
 int ingest(stairs_ctx* c, Model* m, int from, int to, int slot = 0) {
   // (STAIRS_SYNC_LAUNCHES=1, a wait after every launch for a counter-collecting profiler: the decode kernels
   // ingest the prompt; =2 keeps the block kernels)
-  if (c->block_prefill && (!c->sync_launches || c->sync_blocks) && m->bf16 && !m->encdec && to - from >= kBlockPrefillMin) {
+  if (c->block_prefill && (!c->sync_launches || c->sync_blocks) && m->bf16 && !m->encdec && to - from >= block_prefill_min(c)) {
     int rc = ingest_blocks(c, m, from, to, slot);
     if (rc) return rc;
   } else {
@@ -897,7 +904,7 @@ int ingest(stairs_ctx* c, Model* m, int from, int to, int slot = 0) {
 // Whether ingest() takes `rows` rows of one sequence in one block whose k range is summed in pieces: then they give the
 // same bits in a block they share with other sequences.
 bool shares_blocks(const stairs_ctx* c, const Model* m, int rows) {
-  return c->block_prefill && (!c->sync_launches || c->sync_blocks) && m->bf16 && !m->encdec && rows >= kBlockPrefillMin &&
+  return c->block_prefill && (!c->sync_launches || c->sync_blocks) && m->bf16 && !m->encdec && rows >= block_prefill_min(c) &&
          rows <= std::min(kBlkPiecedRows, c->pf_rows);
 }
 

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("d,heads,f", [(256, 2, 256), (1280, 10, 2816), (2048, 32, 1024)])
 @pytest.mark.parametrize("rows", [17, 33, 64, 65, 127, 129, 256, 1024, 1025, 2048, 2049])
 def test_block_rows_against_decode_kernels(d, heads, f, rows, monkeypatch):
-    """The smallest block, edges of the 64-, 128- and 256-row tiles, the largest block whose k range is summed in pieces and
+    """A prompt of one forward and the smallest block (33 rows), edges of the 64-, 128- and 256-row tiles, the largest block whose k range is summed in pieces and
     the smallest that is not, a full block and one row more: the stair logits behind a prompt ingested in blocks against
     those behind the same prompt ingested by the decode kernels (same inputs, another order of additions: 1e-5 of the
     logits' size measured; keys and values are rounded to half in both, so single roundings can fall differently)."""
@@ -47,3 +47,40 @@ def test_prompts_of_a_batch_share_blocks(lens):
         toks, _ = s.generate_batch(prompts, 12, 2)
     for b, want in enumerate(alone):
         assert np.array_equal(toks[b], want), lens[b]
+
+
+@pytest.mark.parametrize("rows", [16, 17, 24, 31, 32])
+def test_prompts_of_one_forward_take_the_decode_kernels(rows, monkeypatch):
+    """A prompt that one forward of the decode kernels holds goes through those (they are faster there): the stair logits
+    behind it are the bits of the context that has no block kernels for prompts."""
+    w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=512, n_heads=4, d_ffn=768, vocab=1040),
+                           draft=dict(kind="prefix", n_layers=1), P=rows + 1, G=1)
+    target, _ = si.make_pair(w)
+    prompt = si.make_prompt(w)
+    got = []
+    for off in (None, "1"):
+        if off:
+            monkeypatch.setenv("STAIRS_NO_BLOCK_PREFILL", off)
+        with pkg.Stairs(target, None, k_max=0, max_seq=rows + 16) as s:
+            s.prefill(prompt)
+            got.append(s.verify(0, logits=True)[2].copy())
+    assert np.array_equal(got[0], got[1])
+
+
+@pytest.mark.parametrize("B,k", [(8, 2), (22, 2)])
+def test_short_prompts_of_a_batch(B, k):
+    """Prompts of 17 rows and more share blocks, in forwards of 24 rows (decode kernels) and of 66 (block kernels).  A
+    sequence's tokens depend neither on its neighbours nor on their order; they are those of the sequence alone on the
+    reserved context, where it takes the same kernels."""
+    w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=512, n_heads=4, d_ffn=768, vocab=1040),
+                           draft=dict(kind="prefix", n_layers=1), P=2, G=1)
+    target, draft = si.make_pair(w)
+    rng = np.random.default_rng(22)
+    prompts = [rng.integers(0, 1040, P).astype(np.int32) for P in ([17, 18, 19, 25, 32, 33, 34, 60] * 3)[:B]]
+    with pkg.Stairs(target, draft, k_max=k, max_seq=96) as s:
+        s.reserve_batch(B)
+        alone = np.stack([s.generate(p, 12, k)[0].copy() for p in prompts])
+        first, _ = s.generate_batch(prompts, 12, k)
+        turned, _ = s.generate_batch(prompts[::-1], 12, k)
+    assert np.array_equal(first, turned[::-1])
+    assert np.array_equal(first, alone)
