@@ -780,6 +780,59 @@ int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logit
   return STAIRS_OK;
 }
 
+// Encoder of one model over c->S <= kEncodeRowsMax source tokens through the decode kernels, all rows in one forward (see
+// encode_model for what it computes).  The limit, decode kernels against blocks: 24 layers of the large shape (d 1024, 16
+// heads of 64, 4096) 0.92 / 1.10 / 1.14 / 1.39 / 1.48 ms at 1 / 8 / 16 / 24 / 32 rows against 1.62 .. 1.72; 12 layers of the
+// wide one (32 heads of 128, 16384) 0.67 / 0.80 / 0.88 / 1.20 / 1.32 against 1.17 .. 1.26, which is past even at 28.
+constexpr int kEncodeRowsMax = 24;
+int encode_rows(stairs_ctx* c, Model* m) {
+  const stairs_model_cfg& g = m->cfg;
+  const int d = g.d_model, a = m->da, H = g.n_heads, S = c->S;
+  const int sn = ssq_groups(d, 1), nch = chunks_for(S);
+  hipStream_t st = c->st;
+  if (nch > c->nchunk_cap) return fail(c, STAIRS_EINVAL, "encode: source outside the workspaces");
+  const bool fr = S > 4;                               // (fragments beside the activations as in forward_ed)
+  uint4* const xf = fr ? c->xf : nullptr;
+  uint4* const af = fr ? c->af : nullptr;
+  const PosRef pos = abs_pos(c, 0);
+  launch_embed(m->tok_emb, 1, c->src_tok, 0, S, g.vocab, pos, S, d, c->x, c->ssq, m->hd, nullptr, 0, c->rope_cs, st, xf, m->enc[0].attn_norm);
+  const RowNorm none{nullptr, nullptr, 0, 0.f};
+  const AttnMode mode{1.f, m->enc_bias, 2 * m->max_src - 1, m->max_src - 1, S, af, 0};
+  GemmEpi e{};
+  e.counters = c->counters;
+  e.stream_weights = m->stream_weights;
+  e.rope_cs = c->rope_cs;
+  e.pos = pos;
+  e.cap = m->cap_src;
+  e.H = H;
+  e.hd = m->hd;
+  e.ssq_out = c->ssq;
+  auto keys_values = [&](const void* W, const float* gain, char* K, char* V) {
+    e.Kc = reinterpret_cast<_Float16*>(K);
+    e.Vc = reinterpret_cast<_Float16*>(V);
+    e.out = c->q_rot;
+    e.frag_out = nullptr;
+    e.frag_gain = nullptr;
+    launch_gemm(kRoleQKV, 1, W, 3 * a, d, c->x, d, S, RowNorm{gain, c->ssq, sn, g.rms_eps}, c->partial, e, st, xf);
+  };
+  for (size_t l = 0; l < m->enc.size(); ++l) {
+    const EdLayer& ly = m->enc[l];
+    keys_values(ly.wqkv, ly.attn_norm, m->Ke, m->Ve);
+    launch_attention(c->q_rot, m->Ke, m->Ve, 1, m->cap_src, a, H, S, pos, 1, 0, nch, c->nchunk_cap, c->part_o, c->part_ml,
+                     c->counters + kGemmCounters, c->attn_out, st, mode);
+    e.out = c->x;
+    e.frag_out = xf;
+    e.frag_gain = ly.ffn_norm;
+    launch_gemm(kRoleWo, 1, ly.wo, d, a, c->attn_out, a, S, none, c->partial, e, st, af);
+    launch_ed_ffn(c, m, ly, S, fr, l + 1 < m->enc.size() ? m->enc[l + 1].attn_norm : m->enc_final_norm);
+    if (c->sync_launches) HIPCHK(c, hipStreamSynchronize(st));
+  }
+  for (size_t l = 0; l < m->dec.size(); ++l)
+    keys_values(m->dec[l].cqkv, m->enc_final_norm, m->Kx + l * m->kvx_layer_bytes, m->Vx + l * m->kvx_layer_bytes);
+  HIPCHK(c, hipGetLastError());
+  return STAIRS_OK;
+}
+
 // Encoder of one model over the c->S source tokens in c->src_tok, all rows in one block: per layer the keys and values of
 // all rows (every row attends to every source position) by the QKV projection's epilogue, attention with the two-sided
 // position bias, output projection and feed-forward.  Afterwards the cross-attention keys and values of every decoder
@@ -791,6 +844,7 @@ int encode_model(stairs_ctx* c, Model* m) {
   const int d = g.d_model, a = m->da, f = g.d_ffn, H = g.n_heads, S = c->S;
   hipStream_t st = c->st;
   if (S < 1 || S > m->max_src || S > c->pf_rows) return fail(c, STAIRS_EINVAL, "encode: source outside the workspaces");
+  if (S <= kEncodeRowsMax) return encode_rows(c, m);
   BlkSegs segs;
   segs.n = 1;
   segs.row0[0] = segs.slot[0] = segs.pos0[0] = 0;

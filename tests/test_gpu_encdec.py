@@ -1,6 +1,8 @@
 """GPU parity of the encoder-decoder path: the HIP library through its C ABI against the CPU oracle, stair logits
 element by element and tokens one by one (teacher-forced onto the GPU's prefix), plus the invariants that hold at
 any size (stairs == plain greedy on the same kernels, graph replay == one-by-one launches)."""
+import time
+
 import numpy as np
 import pytest
 
@@ -39,6 +41,31 @@ def test_source_lengths(S):
     _log(f"encdec source length S={S}")
     res = run_encdec_side_by_side(t, d, src[:S], 12, 3, LOGIT_TOL_BF16)
     assert res["max_logit_err"] < 5e-3
+
+
+@pytest.mark.parametrize("S", [3, 4, 5, 8, 9, 16, 17, 24, 25])
+def test_short_sources(S):
+    """Rows where the encoder's kernels change: 4 | 5 (activation fragments), 8 | 9, 16 | 17 (column tiles), 24 | 25 (decode
+    kernels, then one block); attention width 512 beside d_model 256."""
+    w, t, d, src = _pair(S=32, target=dict(n_enc_layers=2, n_dec_layers=2, d_model=256, n_heads=4, head_dim=128))
+    res = run_encdec_side_by_side(t, d, src[:S], 8, 3, LOGIT_TOL_BF16)
+    assert res["max_logit_err"] < 5e-3
+
+
+def test_short_source_costs_less_than_a_block():
+    """8 source tokens through 8 layers of the large shape against 64, which fill the smallest block: through the decode
+    kernels 0.6 of its time, through the block kernels 0.9 (medians of 30 calls in turn; the bound lies between)."""
+    w, t, _, src = _pair(S=64, target=dict(n_enc_layers=8, n_dec_layers=1, d_model=1024, n_heads=16, head_dim=64, d_ffn=4096))
+    took = {8: [], 64: []}
+    with pkg.StairsEncDec(t, None, k_max=0, max_src=64, max_seq=16) as s:
+        for i in range(35):
+            for S in took:
+                t0 = time.perf_counter()
+                s.encode(src[:S])
+                if i >= 5:
+                    took[S].append(time.perf_counter() - t0)
+    _log({S: float(np.median(v)) for S, v in took.items()})
+    assert np.median(took[8]) < 0.78 * np.median(took[64])
 
 
 def test_long_source_takes_the_stand_alone_merge():
