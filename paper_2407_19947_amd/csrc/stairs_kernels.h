@@ -169,6 +169,9 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
                       PosRef pos, int nslots, size_t kv_slot_stride, int nchunk_launch, int nchunk_cap, float* part_o,
                       float* part_ml, int* counters, float* out, hipStream_t st,
                       const AttnMode& am = AttnMode{0.f, nullptr, 0, 0, 0, nullptr, 0});
+// keys of a launch over `units` 128-key units that its work-groups request before they know the rows' position (half
+// caches, causal; a fixed key set is known to the launch)
+int attn_early_keys(int units, int nslots);
 // out[o(r)] = argmax_v logits[row0 + r * row_stride][v], ties -> lowest v, r < nrows.  One sequence:
 // o(r) = *out_pos.base + out_pos.offset + r (base == nullptr: r).  Several: o(r) = s * out_slot_stride + position of
 // out_pos for row r, nothing written for a slot that is not active.

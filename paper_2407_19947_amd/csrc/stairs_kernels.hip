@@ -1891,7 +1891,7 @@ template <int HD, int CT, bool FUSED>
 __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q, const _Float16* __restrict__ Kc,
                                                   const _Float16* __restrict__ Vc, int cap, int d, int H, int M,
                                                   PosRef pos, size_t kv_slot_stride, float scale, AttnMode am, int nchunk_cap,
-                                                  int sure_chunks, int rows_per_pass, float* part_o, float* part_ml, int* counters,
+                                                  int early_keys, int rows_per_pass, float* part_o, float* part_ml, int* counters,
                                                   float* __restrict__ out) {
   constexpr int KK = HD / 32;   // k-steps of the score MFMA
   constexpr int ET = HD / 16;   // output-dim tiles of the value MFMA
@@ -1915,9 +1915,9 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
   const int kb = c * kAttnChunkH + wave * 64;         // first key of this wave
   // The first query tile's rows are requested before the keys and values (they come from L2 and are converted while the
   // cache tiles are still on their way), and the wave's whole share of the chunk at once (keys and values of both
-  // blocks: 16 KiB at head_dim 128).  Chunks the launch is sure to need (the host's lower bound of the length) are
-  // requested before the rows' position has come back from memory, a round trip less in front of every head; blocks
-  // past the last key hold finite numbers and meet probability 0, blocks past the cache re-read its last.
+  // blocks: 16 KiB at head_dim 128).  Keys below early_keys (attn_early_keys) are requested before the rows' position has
+  // come back from memory, a round trip less in front of every head; blocks past the last key hold finite numbers and
+  // meet probability 0, blocks past the cache re-read its last.
   float4 qa0[KK], qb0[KK];
   uint4 kreg[2][2][KK], vreg[2][ET];
   auto request = [&](bool first, bool second) {
@@ -1961,7 +1961,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
     }
   };
   // (one request site: with a second one for the other chunks the registers of both spill)
-  const int len0 = c < sure_chunks ? 0x7fffffff : am.kv_fixed > 0 ? am.kv_fixed : pos_of(pos, row0) + M;
+  const int len0 = am.kv_fixed > 0 ? am.kv_fixed : kb + 32 < early_keys ? early_keys : pos_of(pos, row0) + M;
   request(kb < len0, kb + 32 < len0);
   // causal: row i sees the keys 0 .. qpos0 + i; fixed key set (am.kv_fixed > 0): every row sees the keys 0 .. kv_fixed-1
   const int qpos0 = pos_of(pos, row0);
@@ -2155,6 +2155,14 @@ static void attn_dispatch(const float* q, const float* K, const float* V, int ca
   hipLaunchKernelGGL(k_attn_combine<HD>, dim3(H, M), dim3(HD), 0, st, part_o, part_ml, H, pos, nchunk_cap, out, d);
 }
 
+// Callers round the 128-key units of a launch up to a multiple of 4 at most, so its rows see more than (units - 4) of them:
+// what lies below that is requested before the length is known, nothing else.  (The first chunk whole at any length: 3 rows
+// at contexts of 16 / 64 / 130 / 256 keys, 16 heads of 128: 5.2 / 5.1 / 5.2 / 5.2 us, now 4.7 / 4.7 / 4.8 / 5.2; 12 heads of
+// 64: 4.3 / 4.4 / 4.2 / 4.3, now 4.0 / 4.2 / 4.2 / 4.3; a head's chunk is 128 and 64 KiB.)  Several sequences: their lengths
+// differ, so each work-group looks its own up (64 slots of 16 heads, 3 rows, contexts of 16..210 keys: 27.3 -> 17.9 us; 16
+// of 32, 4 rows, 40..350 keys: 19.7 -> 15.8 us against requesting the first chunk whole).
+int attn_early_keys(int units, int nslots) { return nslots > 1 ? 0 : std::max(0, (units - 4) * kAttnChunk + 1); }
+
 void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv_half, int cap, int d, int H, int M,
                       PosRef pos, int nslots, size_t kv_slot_stride, int nchunk_launch, int nchunk_cap, float* part_o,
                       float* part_ml, int* counters, float* out, hipStream_t st, const AttnMode& am) {
@@ -2167,11 +2175,7 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
     const int units = nchunk_launch;
     nchunk_launch = (nchunk_launch * kAttnChunk + kAttnChunkH - 1) / kAttnChunkH;
     dim3 grid(nchunk_launch, H, nslots), block(256);
-    // chunks every row block of this launch has keys in: callers round the 128-key units up to a multiple of 4 at most.
-    // Several sequences: their lengths differ, and with many heads at once the launch is bound by the bytes, so each
-    // work-group looks up its length first and requests no more (64 slots of 16 heads, 3 rows, contexts of 16..210 keys:
-    // 27.3 -> 17.9 us; 16 of 32, 4 rows, 40..350 keys: 19.7 -> 15.8 us against requesting the first chunk whole)
-    const int sure = am.kv_fixed > 0 ? nchunk_launch : nslots > 1 ? 0 : std::max(1, ((units - 4) * kAttnChunk + 1) / kAttnChunkH);
+    const int early = attn_early_keys(units, nslots);
     // merge step's LDS: (max, sum) table, row maxima, and for more than kMergeCB chunks the group sums of as many
     // rows per pass as fit in 48 KiB, less when the table is large (the whole stays under kAttnMergeMaxLds)
     const int G = (nchunk_launch + kMergeCB - 1) / kMergeCB;
@@ -2185,10 +2189,10 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
 #define STAIRS_ATTN16(hdv, ct)                                                                                              \
   if (fused)                                                                                                                \
     hipLaunchKernelGGL((k_attn_f16<hdv, ct, true>), grid, block, lds, st, q_rot, K, V, cap, d, H, M, pos, kv_slot_stride,   \
-                       scale, am, nchunk_cap, sure, rpp, part_o, part_ml, counters, out);                                         \
+                       scale, am, nchunk_cap, early, rpp, part_o, part_ml, counters, out);                                         \
   else {                                                                                                                    \
     hipLaunchKernelGGL((k_attn_f16<hdv, ct, false>), grid, block, 0, st, q_rot, K, V, cap, d, H, M, pos, kv_slot_stride,    \
-                       scale, am, nchunk_cap, sure, rpp, part_o, part_ml, counters, out);                                         \
+                       scale, am, nchunk_cap, early, rpp, part_o, part_ml, counters, out);                                         \
     hipLaunchKernelGGL((k_attn_merge<hdv>), dim3(H, nslots), dim3(256), lds, st, part_o, part_ml, d, H, M, pos,             \
                        am.kv_fixed, nchunk_cap, nchunk_launch, rpp, out, am.frag_out, am.frag_rt);                                      \
   }

@@ -409,9 +409,23 @@ static void part1_block_gemm_launches() {
   CHECK(refused(0, false, 0));
 }
 
+// Attention requests no key before its launch knows the length unless every length the launch serves covers it: callers
+// count 128-key units and round them up to a multiple of 4 (a captured iteration serves all lengths of a multiple).
+static void part1_attention_early_keys() {
+  for (int len = 1; len <= 8300; ++len) {
+    const int exact = (len + stairs::kAttnChunk - 1) / stairs::kAttnChunk;
+    for (int units = exact; units <= (exact + 3) / 4 * 4; ++units) {
+      CHECK(stairs::attn_early_keys(units, 1) <= len);
+      CHECK(stairs::attn_early_keys(units, 2) == 0);
+    }
+  }
+  CHECK(stairs::attn_early_keys(64, 1) > 60 * stairs::kAttnChunk);
+}
+
 int main() {
   part1_without_gpu();
   part1_block_gemm_launches();
+  part1_attention_early_keys();
   std::printf("part 1 (no GPU): %d failed checks\n", g_failed);
   std::fflush(stdout);
   int ndev = 0;
