@@ -1916,8 +1916,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
   // The first query tile's rows are requested before the keys and values (they come from L2 and are converted while the
   // cache tiles are still on their way), and the wave's whole share of the chunk at once (keys and values of both
   // blocks: 16 KiB at head_dim 128).  Keys below early_keys (attn_early_keys) are requested before the rows' position has
-  // come back from memory, a round trip less in front of every head; blocks past the last key hold finite numbers and
-  // meet probability 0, blocks past the cache re-read its last.
+  // come back from memory, a round trip less in front of every head; positions of a block past the last key hold finite
+  // numbers and meet probability 0.
   float4 qa0[KK], qb0[KK];
   uint4 kreg[2][2][KK], vreg[2][ET];
   auto request = [&](bool first, bool second) {
@@ -1942,7 +1942,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
 #pragma unroll
       for (int et = 0; et < ET; ++et) vreg[sb][et] = make_uint4(0u, 0u, 0u, 0u);
       if (sb ? second : first) {
-        const int kbs = min(kb + 32 * sb, cap - 32);
+        const int kbs = kb + 32 * sb;
         // (the two-kernel form runs at long contexts only, where a layer's keys and values exceed what the memory-side
         // cache could keep until the next forward: streaming loads there, as for the weights of a large model)
 #pragma unroll
