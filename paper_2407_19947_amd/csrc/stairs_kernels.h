@@ -172,6 +172,8 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
 // keys of a launch over `units` 128-key units that its work-groups request before they know the rows' position (half
 // caches, causal; a fixed key set is known to the launch)
 int attn_early_keys(int units, int nslots);
+// query rows per work-group of a launch over `units` 128-key chunks (fp32 caches)
+int attn_f32_rows(int units, int H, int M);
 // out[o(r)] = argmax_v logits[row0 + r * row_stride][v], ties -> lowest v, r < nrows.  One sequence:
 // o(r) = *out_pos.base + out_pos.offset + r (base == nullptr: r).  Several: o(r) = s * out_slot_stride + position of
 // out_pos for row r, nothing written for a slot that is not active.

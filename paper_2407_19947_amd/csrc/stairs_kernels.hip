@@ -1518,7 +1518,7 @@ void launch_rope_rows(PosRef pos, int M, int hd, const float2* tab, int tab_len,
 }
 
 // ---------------------------------------------------------------------------------------
-// fp32 caches: work-group = (128-key chunk, head, MR query rows: one up to 8 rows, where work-groups are few, else 16).
+// fp32 caches: work-group = (128-key chunk, head, MR query rows: attn_f32_rows).
 // The chunk's keys, then its values, are staged in LDS; every load of a chunk is in flight at once (with a loop over the
 // staged pieces a chunk was 8 round trips to memory in a row), the values while the scores are formed.
 // Chunk boundaries are absolute key positions and chunks are combined in index order; a launch of one chunk writes
@@ -2134,11 +2134,17 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* part_o, const f
                  frag, frag_rt, row0);
 }
 
+// Query rows a work-group of the fp32 attention takes.  Up to 8 rows: one, as long as that makes fewer than 1024 groups (four
+// per CU): the loads of a chunk are what a group waits for.  With more of them the chunk is read once per row, and 4 rows
+// share it (32 heads of 64, 8 rows at 1024 / 2048 / 4096 / 8192 keys: 18.9 / 37.2 / 97.4 / 185 us by single rows, 14.5 /
+// 26.8 / 48.5 / 86.1 by four; 16 heads, 5 rows, 512 keys: 8.7 against 9.9).
+int attn_f32_rows(int units, int H, int M) { return M > 8 ? 16 : M > 1 && units > 1 && units * H * M >= 1024 ? 4 : 1; }
+
 template <int HD>
 static void attn_dispatch(const float* q, const float* K, const float* V, int cap, int d, int H, int M, PosRef pos,
                           int nchunk_launch, int nchunk_cap, float* part_o, float* part_ml, float* out, hipStream_t st) {
   const float scale = 1.0f / sqrtf((float)HD);
-  const int mr = M <= 8 ? 1 : 16;
+  const int mr = attn_f32_rows(nchunk_launch, H, M);
   const dim3 grid(nchunk_launch, H, (M + mr - 1) / mr), block(256);
   const size_t lds = (size_t)(128 * (HD + 4) + mr * (HD + 128 + 2 + 256) + 2) * sizeof(float);
 #define STAIRS_ATTN(mrv, direct)                                                                                          \
@@ -2150,6 +2156,7 @@ static void attn_dispatch(const float* q, const float* K, const float* V, int ca
     return;
   }
   if (mr == 1) STAIRS_ATTN(1, false);
+  else if (mr == 4) STAIRS_ATTN(4, false);
   else STAIRS_ATTN(16, false);
 #undef STAIRS_ATTN
   hipLaunchKernelGGL(k_attn_combine<HD>, dim3(H, M), dim3(HD), 0, st, part_o, part_ml, H, pos, nchunk_cap, out, d);
@@ -2554,6 +2561,7 @@ hipError_t configure_kernels() {
   // merge runs for at most kAttnFusedMaxChunks chunks and stays small)
   optin((const void*)k_attn<128, 1, true>, 128 * 1024);
   optin((const void*)k_attn<128, 1, false>, 128 * 1024);
+  optin((const void*)k_attn<128, 4, false>, 128 * 1024);
   optin((const void*)k_attn<128, 16, true>, 128 * 1024);
   optin((const void*)k_attn<128, 16, false>, 128 * 1024);
   optin((const void*)k_attn_merge<128>, kAttnMergeMaxLds);

@@ -422,10 +422,25 @@ static void part1_attention_early_keys() {
   CHECK(stairs::attn_early_keys(64, 1) > 60 * stairs::kAttnChunk);
 }
 
+// fp32 attention: at up to 8 rows fewer than 1024 work-groups of one row; a launch of
+// one chunk has no four-row form.
+static void part1_fp32_attention_rows() {
+  for (int H : {1, 4, 8, 16, 32, 128})
+    for (int units = 1; units <= 512; ++units)
+      for (int M = 1; M <= 32; ++M) {
+        const int mr = stairs::attn_f32_rows(units, H, M);
+        CHECK(mr == 1 || mr == 4 || mr == 16);
+        if (M > 1 && M <= 8 && units > 1) CHECK(mr == 4 || units * H * M < 1024);
+        if (M > 8) CHECK(mr == 16);
+        if (units == 1 && M <= 8) CHECK(mr == 1);
+      }
+}
+
 int main() {
   part1_without_gpu();
   part1_block_gemm_launches();
   part1_attention_early_keys();
+  part1_fp32_attention_rows();
   std::printf("part 1 (no GPU): %d failed checks\n", g_failed);
   std::fflush(stdout);
   int ndev = 0;

@@ -566,6 +566,24 @@ def test_five_to_seven_rows_of_small_models_have_the_bits_of_any_other_count(d, 
             assert np.array_equal(lg, want[:k + 1]), k
 
 
+@pytest.mark.parametrize("heads,P", [(16, 1020), (16, 1300), (8, 1300), (8, 2400)])
+def test_fp32_rows_do_not_depend_on_their_number_at_long_contexts(heads, P):
+    """fp32, head size 64 and 128, contexts at which stair batches of a few rows go from one to four rows per work-group
+    (chunks * heads * rows around 1024), with a last group of one to three rows: the rows' bits stay."""
+    w = si.scaled_workload("cfg1_tiny_fp32", target=dict(n_layers=1, d_model=1024, n_heads=heads, d_ffn=260, vocab=516),
+                           draft=dict(kind="prefix", n_layers=1), P=P, G=1)
+    target, draft = si.make_pair(w)
+    prompt = si.make_prompt(w)
+    dr = np.random.default_rng([10, P]).integers(0, 516, 15).astype(np.int32)
+    want = None
+    with pkg.Stairs(target, draft, k_max=15, max_seq=P + 24) as s:
+        for k in (15, 7, 6, 5, 4, 3, 2, 1, 0):
+            s.prefill(prompt)
+            _, _, lg = s.verify_tokens(dr[:k], logits=True)
+            want = lg.copy() if want is None else want
+            assert np.array_equal(lg, want[:k + 1]), k
+
+
 @pytest.mark.parametrize("heads,P", [(h, p) for h in (2, 4) for p in (1, 96, 119, 120, 121, 127, 128, 129, 250)])
 def test_fp32_rows_do_not_depend_on_their_number(heads, P):
     """fp32, head size 128 and 64, contexts around the 128-key chunks (one chunk: the attention kernel writes the result, more:
