@@ -1025,18 +1025,21 @@ void launch_split_frag(const float* X, int ldx, int M, int K, const float* gain,
 // LDS bytes of k_gemm_bf16_rows, or 0 if this shape does not take that path.  The residual-writing projections
 // have few weight tiles (N = d_model): they run one 8-wave work-group per CU and only when the tiles about
 // cover the chip.
-static size_t rows_path_lds(int role, int M, int N, int K) {
+size_t rows_path_lds(int role, int M, int N, int K) {
   static const int max_rows = [] { const char* e = getenv("STAIRS_ROWS_MAX"); return e ? atoi(e) : 7; }();   // tuning aid
   if (M > 7 || M > max_rows) return 0;
   const size_t bytes = (size_t)K * M * 4 + (size_t)(gemm_slices(K, 1) + 1) * M * 16 * 4;
-  // 5..7 rows (at 8 the fragment-reading kernel is as fast): the block takes more than half a CU's LDS, so one work-group per CU walks through the tiles; only
-  // with a k chunk for each of its waves (k >= 2048) does that beat the fragment-reading kernel
-  // 5..7 rows of small models (up to two work-groups per CU; feed-forward outputs: k up to 4096, one staging pass): 4.9 ..
-  // 7.5 us a launch at 125M and at the large encoder-decoder shape where the fragment-reading kernel took 6.8 .. 9.5
-  if (M > 4 && role != kRoleDown && K < 2048 && N / 16 <= 512 && bytes <= kRowsPathMaxLds) return bytes;
-  if (M > 4 && role == kRoleDown && K <= 4096 && N / 16 <= 128 && bytes <= kRowsPathMaxLdsWide) return bytes;
-  if (M > 4)
-    return (role != kRoleDown && bytes <= kRowsPathMaxLdsWide && N / 16 >= 192 && K >= 2048) ? std::max(bytes, (size_t)81 * 1024) : 0;
+  // 5..7 rows (at 8 the fragment-reading kernel is as fast), three cases:
+  // k below 2048, a work-group per tile and no more than CUs: 4.5 .. 5.2 us a launch at 125M and at the large
+  // encoder-decoder shape, where the fragment-reading kernel takes 5.1 .. 5.4.  With more tiles one work-group per CU walks
+  // through them, and its waves have no k chunk each to wait for: 512 tiles, k = 512, 5 / 7 rows: 5.5 / 5.9 against 5.1 /
+  // 5.0; 384 tiles, k = 768: 5.5 / 6.0 against 5.7 / 5.7.
+  if (M > 4 && role != kRoleDown && K < 2048) return N / 16 <= 256 && bytes <= kRowsPathMaxLds ? bytes : 0;
+  // feed-forward outputs with k up to 4096 (one staging pass) and few tiles: 5.0 .. 5.5 against 7.0 us at 125M
+  if (M > 4 && role == kRoleDown) return K <= 4096 && N / 16 <= 128 && bytes <= kRowsPathMaxLdsWide ? bytes : 0;
+  // k of 2048 and more, a chunk for each wave: the block takes more than half a CU's LDS, so one work-group per CU walks
+  // through the tiles
+  if (M > 4) return bytes <= kRowsPathMaxLdsWide && N / 16 >= 192 ? std::max(bytes, (size_t)81 * 1024) : 0;
   if (role == kRoleWo || role == kRoleDown) {
     // few tiles: only matrices so small that the launch is latency-bound anyway (no partial sums, no hand-off)
     if (N / 16 < 192) {

@@ -436,11 +436,27 @@ static void part1_fp32_attention_rows() {
       }
 }
 
+// The GEMM with the activation block in LDS at 5..7 rows: a work-group per tile where k is short, walking ones only where
+// every wave has a k chunk; the LDS it asks for exists.
+static void part1_rows_gemm() {
+  for (int role : {stairs::kRoleQKV, stairs::kRoleWo, stairs::kRoleGateUp, stairs::kRoleDown, stairs::kRoleHead})
+    for (int K = 256; K <= 16384; K += 256)
+      for (int N = 256; N <= 32768; N += 256)
+        for (int M = 1; M <= 9; ++M) {
+          const size_t lds = stairs::rows_path_lds(role, M, N, K);
+          CHECK(lds <= stairs::kRowsPathMaxLdsWide);
+          if (M > 7) CHECK(lds == 0);
+          if (M > 4 && K < 2048 && N / 16 > 256) CHECK(lds == 0);
+          if (M > 4 && M <= 7 && role != stairs::kRoleDown && K < 2048 && N / 16 <= 256) CHECK(lds > 0);
+        }
+}
+
 int main() {
   part1_without_gpu();
   part1_block_gemm_launches();
   part1_attention_early_keys();
   part1_fp32_attention_rows();
+  part1_rows_gemm();
   std::printf("part 1 (no GPU): %d failed checks\n", g_failed);
   std::fflush(stdout);
   int ndev = 0;

@@ -548,9 +548,9 @@ def test_row_bits_do_not_depend_on_the_query_tiles(P):
             assert np.array_equal(lg, want[:k + 1]), k
 
 
-@pytest.mark.parametrize("d,heads,ffn,vocab", [(2048, 16, 4096, 512), (1792, 14, 4096, 8192), (1792, 14, 4352, 8208)])
+@pytest.mark.parametrize("d,heads,ffn,vocab", [(2048, 16, 4096, 512), (1792, 14, 4096, 8192), (1792, 14, 4352, 8208), (512, 4, 2048, 4096), (512, 4, 2304, 4112)])
 def test_five_to_seven_rows_of_small_models_have_the_bits_of_any_other_count(d, heads, ffn, vocab):
-    """Around the limits of the LDS-resident GEMM at 5..7 rows (k below 2048 and 512 tiles; down projection: 4096 and 128):
+    """Around the limits of the LDS-resident GEMM at 5..7 rows (k below 2048 and 256 tiles; down projection: 4096 and 128):
     stair batches of 16, 7, 6, 5, 4 and 1 rows from the same state share their rows' bits."""
     w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=d, n_heads=heads, d_ffn=ffn, vocab=vocab),
                            draft=dict(kind="prefix", n_layers=1), P=21, G=1)
