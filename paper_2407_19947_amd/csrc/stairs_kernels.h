@@ -25,8 +25,11 @@ constexpr size_t kRowsPathMaxLds = 68 * 1024;
 constexpr size_t kRowsPathMaxLdsWide = 150 * 1024;
 constexpr size_t kWideMaxLds = 150 * 1024;      // chunk sums of k_gemm_bf16_wide: chunks * rows * 16 NT * 4 bytes
 // one column tile, one weight tile and one k chunk per wave (small models at 5..16 rows): the whole chunk in flight, one
-// round trip to memory instead of two or three (7.2 -> 6.8 us a launch at 125M and at the large encoder-decoder shape)
-constexpr int kWideDepthChunk = 16;
+// round trip to memory instead of two or three (7.2 -> 6.8 us a launch at 125M and at the large encoder-decoder shape).
+// Up to 4 chunks: with more the weights' way from memory is the bound, and 16 k-steps in flight a wave only take registers
+// (8 chunks x 256 tiles, 8 / 16 rows: 10.9 us, with 8 in flight 10.1 / 10.2; 6 x 48: 6.8 / 6.9 and 6.6).
+constexpr int kWideDepthChunk = 16, kWideWholeChunkMax = 4;
+inline bool wide_whole_chunk(int M, int nchunks, int nw) { return M <= 16 && nchunks <= nw && nchunks <= kWideWholeChunkMax; }
 constexpr int kWideDepth8 = 2, kWideDepth6 = 2, kWideDepth4 = 3, kWideDepth3 = 4, kWideDepth2 = 5, kWideDepth1 = 8;   // k-steps in flight per wave at 4 / 2 / 1 tiles per wave
 constexpr size_t kRowsPathSmallMatrix = 16u << 20;   // residual-writing projections with fewer tiles than CUs: up to this many bytes
 

@@ -1400,7 +1400,7 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
     else if (wc.nt == 3) { STAIRS_WIDE_CT2(3, kWideDepth3); }
     else if (wc.nt == 4) { STAIRS_WIDE_CT(4, kWideDepth4); }
     else if (wc.nt == 2) { STAIRS_WIDE_CT(2, kWideDepth2); }
-    else if (CT == 1 && nchunks <= wc.nw) STAIRS_WIDE(1, 1, kWideDepthChunk);
+    else if (wide_whole_chunk(M, nchunks, wc.nw)) STAIRS_WIDE(1, 1, kWideDepthChunk);
     else { STAIRS_WIDE_CT(1, kWideDepth1); }
 #undef STAIRS_WIDE_CT
 #undef STAIRS_WIDE_CT2

@@ -445,6 +445,9 @@ static void part1_rows_gemm() {
         for (int M = 1; M <= 9; ++M) {
           const size_t lds = stairs::rows_path_lds(role, M, N, K);
           CHECK(lds <= stairs::kRowsPathMaxLdsWide);
+          const int chunks = stairs::gemm_slices(K, 1);
+          CHECK(!stairs::wide_whole_chunk(M, chunks, 8) || chunks <= 4);   // (long k: the ring, not the whole chunk)
+          CHECK(chunks > 4 || stairs::wide_whole_chunk(M, chunks, 8));
           if (M > 7) CHECK(lds == 0);
           if (M > 4 && K < 2048 && N / 16 > 256) CHECK(lds == 0);
           if (M > 4 && M <= 7 && role != stairs::kRoleDown && K < 2048 && N / 16 <= 256) CHECK(lds > 0);
