@@ -126,6 +126,10 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
 // dynamic LDS of the kernel that keeps the whole activation block of up to 7 rows in LDS; 0: the projection does not take it
 size_t rows_path_lds(int role, int M, int N, int K);
 
+// launch shape of the GEMM that reads fragments (5..64 rows): weight tiles per wave, waves; nt == 0: the split-K kernel
+struct WideCfg { int nt, nw; };
+WideCfg wide_cfg(int role, int M, int NTILES, int K);
+
 // Y [M <= 32, N] = X [M, K] . W^T with W [N, K] row-major bf16 read as it is, one kernel (M > 4: two), the bits launch_gemm
 // gives for the laid-out matrix; frag: frag_bytes(K) of scratch.  false: the shape takes the split-K kernel, nothing done.
 bool launch_gemm_rowmajor(const uint16_t* W, int N, int K, const float* X, int M, float* Y, uint4* frag, hipStream_t st);

@@ -1062,11 +1062,10 @@ size_t rows_path_lds(int role, int M, int N, int K) {
 // 32 (21 / 34).  More tiles per wave means fewer fragment reads and fewer, longer-lived waves per weight byte; with
 // few tiles (N = d_model) that leaves too few work-groups, and for a long k at up to 16 rows split-K's extra
 // parallelism still wins.
-struct WideCfg { int nt, nw; };
 constexpr int wide_depth2(int depth1) { return depth1 <= 2 ? 1 : depth1 <= 3 ? 2 : depth1 <= 5 ? 3 : 5; }   // ring depth at two column tiles
 constexpr int wide_depth3(int depth1) { return depth1 <= 3 ? 1 : depth1 <= 5 ? 2 : 3; }                      // at three (33..48 rows)
 constexpr int wide_depth4(int depth1) { return depth1 <= 3 ? 1 : 2; }                                        // at four (49..64 rows; 3 spills at one tile)
-static WideCfg wide_cfg(int role, int M, int NTILES, int K) {
+WideCfg wide_cfg(int role, int M, int NTILES, int K) {
   // STAIRS_WIDE_CFG="nt/nw,nt/nw,nt/nw,nt/nw,nt/nw" (QKV, out, gate-up, down, head; nt = 0: split-K) overrides the
   // choice: tuning aid
   static const std::vector<WideCfg> forced = [] {
@@ -1101,15 +1100,19 @@ static WideCfg wide_cfg(int role, int M, int NTILES, int K) {
     const int nt = kNts[i];
     c = {nt, std::min(nt == 1 ? 8 : 4, nchunks)};
   }
+  bool free_nw = true;
   if ((int)forced.size() == 5) {
     const WideCfg f = forced[role];
-    if ((f.nt == 0 || f.nt == 1 || f.nt == 2 || f.nt == 3 || f.nt == 4 || f.nt == 6 || f.nt == 8) && f.nw >= 1 && f.nw <= 8) c = f;
+    if ((f.nt == 0 || f.nt == 1 || f.nt == 2 || f.nt == 3 || f.nt == 4 || f.nt == 6 || f.nt == 8) && f.nw >= 1 && f.nw <= 8) {
+      c = f;
+      free_nw = c.nt == 0;
+    }
   }
   if (M > 2 * 16) {                      // 33..64 rows: this kernel only (split-K stops at two column tiles)
     // one work-group per CU (its chunk sums fill the LDS): 8 waves, two a SIMD, cover each other's waits for the fragments,
     // which outweigh the weights here (64 rows, 1376 and 2000 tiles x 8 chunks, mean of both: 62.2 -> 57.8 us with 4 -> 8 waves)
-    if (c.nt == 0) c = {1, 8};
-    c.nw = std::min(8, nchunks);
+    if (c.nt == 0) c.nt = 1;
+    if (free_nw) c.nw = std::min(8, nchunks);
     if (c.nt > 4) c.nt = 4;                 // (the three- and four-column-tile forms exist for 1, 2 and 4 tiles per wave)
     if (c.nt == 3) c.nt = 4;
   }

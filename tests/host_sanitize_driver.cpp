@@ -454,7 +454,14 @@ static void part1_rows_gemm() {
         }
 }
 
-int main() {
+int main(int argc, char** argv) {
+  if (argc > 1 && !std::strcmp(argv[1], "wide-cfg")) {     // the launch shapes under the caller's STAIRS_WIDE_CFG
+    for (int M : {8, 16, 17, 32, 33, 48, 64}) {
+      const stairs::WideCfg c = stairs::wide_cfg(stairs::kRoleQKV, M, 768, 4096);
+      std::printf("%d rows: %d/%d\n", M, c.nt, c.nw);
+    }
+    return 0;
+  }
   part1_without_gpu();
   part1_block_gemm_launches();
   part1_attention_early_keys();

@@ -17,6 +17,12 @@ SOURCES = [os.path.join(ROOT, "paper_2407_19947_amd", "csrc", n) for n in
 ENV = dict(os.environ, ASAN_OPTIONS="detect_leaks=0", UBSAN_OPTIONS="print_stacktrace=1:halt_on_error=1")
 
 
+def _build_if_stale():
+    exe = entry.SANITIZE_DRIVER
+    if not os.path.exists(exe) or any(os.path.getmtime(s) > os.path.getmtime(exe) for s in SOURCES):
+        entry.build_sanitize_driver()
+
+
 def _run(timeout):
     res = subprocess.run([entry.SANITIZE_DRIVER], capture_output=True, text=True, env=ENV, timeout=timeout)
     print(res.stdout[-2000:], res.stderr[-6000:], flush=True)
@@ -25,12 +31,27 @@ def _run(timeout):
 
 def test_argument_checks_under_host_sanitizers():
     """No GPU: (re)build the instrumented driver when it is missing or older than a source, run part 1."""
-    exe = entry.SANITIZE_DRIVER
-    if not os.path.exists(exe) or any(os.path.getmtime(s) > os.path.getmtime(exe) for s in SOURCES):
-        entry.build_sanitize_driver()
+    _build_if_stale()
     res = _run(120)
     assert res.returncode == 0
     assert "part 1 (no GPU): 0 failed checks" in res.stdout
+
+
+@pytest.mark.parametrize("forced,want", [
+    (None, {8: "3/4", 16: "3/4", 17: "3/4", 32: "3/4", 33: "4/8", 48: "4/8", 64: "4/8"}),
+    ("2/3", {8: "2/3", 16: "2/3", 17: "2/3", 32: "2/3", 33: "2/3", 48: "2/3", 64: "2/3"}),
+    ("0/5", {8: "0/5", 16: "0/5", 17: "0/5", 32: "0/5", 33: "1/8", 48: "1/8", 64: "1/8"}),
+])
+def test_forced_launch_shapes_reach_every_row_count(forced, want):
+    """STAIRS_WIDE_CFG sets tiles per wave and waves of the fragment-reading GEMM at every row count (768 tiles, 8 chunks);
+    its 0 (split-K) does not exist beyond 32 rows."""
+    _build_if_stale()
+    env = dict(ENV)
+    env.pop("STAIRS_WIDE_CFG", None)
+    if forced:
+        env["STAIRS_WIDE_CFG"] = ",".join([forced] * 5)
+    out = subprocess.run([entry.SANITIZE_DRIVER, "wide-cfg"], capture_output=True, text=True, env=env, timeout=60).stdout
+    assert out.split("\n")[:-1] == [f"{rows} rows: {shape}" for rows, shape in want.items()]
 
 
 @pytest.mark.gpu
