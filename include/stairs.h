@@ -190,7 +190,8 @@ int stairs_reserve_batch(stairs_ctx *ctx, int32_t max_batch);
  * tokens_out is [B][G] row-major.  Requires B <= reserved batch, max(B * (k+1), B * 2) <= STAIRS_MAX_STREAM_ROWS (or, with
  * more than STAIRS_MAX_ROWS / 2 sequences reserved, <= STAIRS_MAX_BATCH_ROWS), P[b] + G + k + 1 <= max_seq.  stats (optional): iterations = batched iterations, tokens = B * G,
  * accepted / accept_hist summed over sequences.  Afterwards the context holds no current sequence for the
- * single-sequence calls (stairs_prefill starts one).  Errors: EINVAL, ESTATE (k > 0 without a draft), ECAPACITY, EHIP. */
+ * single-sequence calls (stairs_prefill starts one).  Errors: EINVAL, ESTATE (k > 0 without a draft), ECAPACITY, ENOMEM
+ * (host memory for the prompts; nothing has happened then), EHIP. */
 int stairs_generate_batch(stairs_ctx *ctx, const int32_t *const *prompts, const int32_t *P, int32_t B, int32_t G,
                           int32_t k, int32_t *tokens_out, stairs_stats *stats);
 

@@ -9,6 +9,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <memory>
 #include <new>
 #include <string>
 #include <vector>
@@ -1862,6 +1863,10 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
     for (int i = 0; i < P[b]; ++i)
       if (prompts[b][i] < 0 || prompts[b][i] >= c->T.cfg.vocab) return fail(c, STAIRS_EINVAL, "prompt token outside the vocabulary");
   }
+  // the prompts on their way in, the answers on their way out: one host array for all sequences
+  const int Pmin = *std::min_element(P, P + B), Pmax = *std::max_element(P, P + B);
+  std::unique_ptr<int[]> packed(new (std::nothrow) int[(size_t)B * std::max(Pmax, Pmax - Pmin + G)]());
+  if (!packed) return fail(c, STAIRS_ENOMEM, "no host memory for the prompts");
   stairs_stats s;
   memset(&s, 0, sizeof(s));
   c->prefilled = false;            // the single-sequence state (slot 0) is overwritten
@@ -1872,10 +1877,8 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
   std::vector<int> L(B), L0(B), hstate((size_t)B * kSlotState);
   std::vector<char> active(B, 1), ended(B, 0);
   // all prompts in one copy, padded to the longest (the positions behind a prompt are written before they are read)
-  const int Pmax = *std::max_element(P, P + B);
-  std::vector<int> packed((size_t)B * Pmax, 0);
   for (int b = 0; b < B; ++b) {
-    memcpy(packed.data() + (size_t)b * Pmax, prompts[b], (size_t)P[b] * sizeof(int));
+    memcpy(packed.get() + (size_t)b * Pmax, prompts[b], (size_t)P[b] * sizeof(int));
     L[b] = L0[b] = P[b];
     hstate[b * kSlotState + 0] = P[b];
     hstate[b * kSlotState + 1] = 0;
@@ -1883,7 +1886,7 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
     hstate[b * kSlotState + 3] = G > 0 ? 1 : 0;
     active[b] = G > 0;
   }
-  HIPCHK(c, hipMemcpy2DAsync(c->tokens, (size_t)c->tok_stride * sizeof(int), packed.data(), (size_t)Pmax * sizeof(int), (size_t)Pmax * sizeof(int), B,
+  HIPCHK(c, hipMemcpy2DAsync(c->tokens, (size_t)c->tok_stride * sizeof(int), packed.get(), (size_t)Pmax * sizeof(int), (size_t)Pmax * sizeof(int), B,
                              hipMemcpyHostToDevice, c->st));
   HIPCHK(c, hipMemcpyAsync(c->state, hstate.data(), hstate.size() * sizeof(int), hipMemcpyHostToDevice, c->st));
   HIPCHK(c, hipStreamSynchronize(c->st));
@@ -1961,18 +1964,16 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
   HIPCHK(c, hipEventElapsedTime(&s.ms_decode, c->ev[1], c->ev[2]));
   s.tokens = 0;
   if (G > 0) {                                          // the answers in one copy: the columns any of them lies in
-    const int first = *std::min_element(L0.begin(), L0.end());
-    int end = first;
+    int end = Pmin;
     for (int b = 0; b < B; ++b) end = std::max(end, L0[b] + std::min(G, L[b] - L0[b]));
-    const int cols = end - first;
-    std::vector<int> got((size_t)B * cols);
-    HIPCHK(c, hipMemcpy2DAsync(got.data(), (size_t)cols * sizeof(int), c->tokens + first, (size_t)c->tok_stride * sizeof(int),
+    const int cols = end - Pmin;                        // (at most Pmax - Pmin + G)
+    HIPCHK(c, hipMemcpy2DAsync(packed.get(), (size_t)cols * sizeof(int), c->tokens + Pmin, (size_t)c->tok_stride * sizeof(int),
                                (size_t)cols * sizeof(int), B, hipMemcpyDeviceToHost, c->st));
     HIPCHK(c, hipStreamSynchronize(c->st));
     for (int b = 0; b < B; ++b) {
       const int n = std::min(G, L[b] - L0[b]);
       s.tokens += n;
-      memcpy(tokens_out + (size_t)b * G, got.data() + (size_t)b * cols + (L0[b] - first), (size_t)n * sizeof(int));
+      memcpy(tokens_out + (size_t)b * G, packed.get() + (size_t)b * cols + (L0[b] - Pmin), (size_t)n * sizeof(int));
       for (int i = n; i < G; ++i) tokens_out[(size_t)b * G + i] = c->eos_id;
     }
   }

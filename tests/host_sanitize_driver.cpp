@@ -15,6 +15,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "../include/stairs.h"
@@ -28,6 +29,17 @@ static int g_failed = 0;
       ++g_failed;                                                            \
     }                                                                        \
   } while (0)
+
+// host memory that runs out: arrays of g_refuse bytes and more are refused (0: none) to whoever asks without exceptions
+static size_t g_refuse = 0;
+void* operator new[](size_t n, const std::nothrow_t&) noexcept {
+  if (g_refuse && n >= g_refuse) return nullptr;
+  try {
+    return ::operator new[](n);
+  } catch (...) {
+    return nullptr;
+  }
+}
 
 struct Rng {
   uint64_t s;
@@ -270,6 +282,10 @@ static void part2_decoder_only() {
   CHECK(stairs_reserve_batch(c, 6) == STAIRS_OK);
   CHECK(stairs_generate_batch(c, pp.data(), PP.data(), 6, G, 3, both.data(), &st) == STAIRS_OK);
   CHECK(both == alone && st.tokens == 6 * G);
+  g_refuse = 6 * 129 * sizeof(int32_t);  // host memory for the prompts runs out: an error code, and the context goes on
+  CHECK(stairs_generate_batch(c, pp.data(), PP.data(), 6, G, 3, both.data(), &st) == STAIRS_ENOMEM);
+  g_refuse = 0;
+  CHECK(stairs_generate_batch(c, pp.data(), PP.data(), 6, G, 3, both.data(), &st) == STAIRS_OK && both == alone);
   CHECK(stairs_generate_batch(c, pp.data(), PP.data(), 7, G, 3, both.data(), &st) == STAIRS_EINVAL);
   CHECK(stairs_reserve_batch(c, STAIRS_MAX_BATCH + 1) == STAIRS_EINVAL);
   CHECK(stairs_reserve_batch(c, 24) == STAIRS_OK);
