@@ -443,9 +443,9 @@ size_t max_matrix_bytes(const stairs_model_cfg* m) {
 }
 
 size_t max_partial_floats(const stairs_model_cfg* m) {
-  const int b = m->dtype == STAIRS_DTYPE_BF16;
+  if (m->dtype != STAIRS_DTYPE_BF16) return 0;         // (only split-K writes partial sums)
   const size_t d = m->d_model, f = m->d_ffn, V = m->vocab;
-  const size_t sd = gemm_slices(m->d_model, b), sf = gemm_slices(m->d_ffn, b);
+  const size_t sd = gemm_slices(m->d_model, 1), sf = gemm_slices(m->d_ffn, 1);
   return kMaxRows * std::max({sd * 3 * d, sd * 2 * f, sf * d, sd * V});
 }
 
@@ -471,7 +471,7 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
   const stairs_model_cfg& g = m->cfg;
   const int d = g.d_model, f = g.d_ffn, H = g.n_heads, V = g.vocab;
   const int b = m->bf16 ? 1 : 0;
-  const int sn = ssq_groups(d, b);
+  const int sn = ssq_groups(d);
   hipStream_t st = c->st;
   if (nchunk < 1 || nchunk > c->nchunk_cap || M < 1 || M > c->fwd_rows || M > c->rows_cap || (M > kMaxRows && !b))
     return fail(c, STAIRS_EINVAL, "forward: launch shape outside the workspaces");
@@ -674,7 +674,7 @@ int chunks_for(int kv_len) { return (std::max(kv_len, 1) + kAttnChunk - 1) / kAt
 // frags: x comes with its activation fragments in c->xf (gain of ffn_norm folded in), the hidden activations leave
 // theirs in c->hf and the result its own in c->xf with next_gain folded in (forwards of more than 4 rows)
 void launch_ed_ffn(stairs_ctx* c, const Model* m, const EdLayer& ly, int M, bool frags, const float* next_gain) {
-  const int d = m->cfg.d_model, f = m->cfg.d_ffn, sn = ssq_groups(d, 1);
+  const int d = m->cfg.d_model, f = m->cfg.d_ffn, sn = ssq_groups(d);
   const RowNorm none{nullptr, nullptr, 0, 0.f};
   GemmEpi e{};
   e.counters = c->counters;
@@ -699,7 +699,7 @@ void launch_ed_ffn(stairs_ctx* c, const Model* m, const EdLayer& ly, int M, bool
 int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows, float* logits_dst) {
   const stairs_model_cfg& g = m->cfg;
   const int d = g.d_model, a = m->da, H = g.n_heads, V = g.vocab;
-  const int sn = ssq_groups(d, 1);
+  const int sn = ssq_groups(d);
   hipStream_t st = c->st;
   const int nch_src = chunks_for(c->S);
   if (nchunk < 1 || nchunk > c->nchunk_cap || nch_src > c->nchunk_cap || M < 1 || M > kMaxRows || c->S < 1)
@@ -789,7 +789,7 @@ constexpr int kEncodeRowsMax = 24;
 int encode_rows(stairs_ctx* c, Model* m) {
   const stairs_model_cfg& g = m->cfg;
   const int d = g.d_model, a = m->da, H = g.n_heads, S = c->S;
-  const int sn = ssq_groups(d, 1), nch = chunks_for(S);
+  const int sn = ssq_groups(d), nch = chunks_for(S);
   hipStream_t st = c->st;
   if (nch > c->nchunk_cap) return fail(c, STAIRS_EINVAL, "encode: source outside the workspaces");
   const bool fr = S > 4;                               // (fragments beside the activations as in forward_ed)
@@ -1348,7 +1348,7 @@ static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
   // (activations and their fragments for kMaxFwdRows rows: a few MB; what grows with the context or the vocabulary
   // is sized for rows_cap rows and enlarged by stairs_reserve_batch)
   if (frag_bytes(std::max(wide, fmax)) > kFragHalfU4 * 16) return fail(c, STAIRS_EINVAL, "d_model / d_ffn too large for the activation fragment blocks");
-  if ((rc = dev_alloc(c, &c->x, (size_t)kMaxFwdRows * dmax)) || (rc = dev_alloc(c, &c->ssq, (size_t)kMaxFwdRows * ssq_groups(dmax, 1))) ||
+  if ((rc = dev_alloc(c, &c->x, (size_t)kMaxFwdRows * dmax)) || (rc = dev_alloc(c, &c->ssq, (size_t)kMaxFwdRows * ssq_groups(dmax))) ||
       (rc = dev_alloc(c, &c->q_rot, (size_t)kMaxFwdRows * wide)) || (rc = dev_alloc(c, &c->attn_out, (size_t)kMaxFwdRows * wide)) ||
       (rc = dev_alloc(c, &c->h, (size_t)kMaxFwdRows * fmax)) || (rc = dev_alloc(c, &c->logits, (size_t)kMaxRows * w.vocab)) ||
       (rc = dev_alloc(c, &c->partial, w.partial_floats)) ||
@@ -2040,8 +2040,9 @@ int stairs_gemm_host(int32_t dtype, const void* W, const float* X, float* Y, int
 
 // ---- stairs_gemm_device: stairs_gemm_host for callers that cannot allocate ---------------------------------------
 // Everything stairs_gemm_host allocates per call lives in one file-scope device array instead; every GPU the library
-// runs on holds its own copy at its own address until the process ends.  Layout (bytes): hand-off counters, split-K /
-// fp32 partial sums, the re-laid-out bf16 weights, the activation fragments.
+// runs on holds its own copy at its own address until the process ends.  Layout (bytes): hand-off counters, split-K
+// partial sums, the re-laid-out bf16 weights, the activation fragments.  (fp32 products use none of it; their documented
+// limits stay.)
 constexpr size_t kNaCounterBytes = (size_t)kGemmCounters * sizeof(int);
 constexpr size_t kNaPartialBytes = (size_t)STAIRS_GEMM_DEVICE_MAX_PARTIAL;
 constexpr size_t kNaWeightBytes = (size_t)STAIRS_GEMM_DEVICE_MAX_WEIGHT;

@@ -276,8 +276,9 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
 //   up in order: by different work-groups and k_blk_reduce (gridDim.z = pieces), or one after the other by the same
 //   work-group with a second set of accumulators (PIECED).  The bits depend on p.pieces alone, not on R, the tile shape
 //   or the grid.
-//   What bounds it: at thousands of rows 1.22 .. 1.31 PFLOP/s of issued MFMAs whatever the tile (a library product of two
-//   8192-wide matrices: 1.49 on the same card); at a few hundred the rounds of work-groups and, with one work-group on a
+//   What bounds it: at thousands of rows the issue of MFMAs, 1.20 .. 1.30 PFLOP/s with plain stores in launches by
+//   themselves (2047 rows, 7B projections; a library product of two 8192-wide matrices: 1.49 on the same card) and 1.07 over
+//   a profiled 2048-token prompt with its epilogues; at a few hundred the rounds of work-groups and, with one work-group on a
 //   CU, the LDS reads beside the MFMAs (0.38 us per k-step of 32 MFMAs a wave); at <= 64 rows the weights' way from memory.
 //   Plain stores, against the kernel before (weights through registers, 256 x 128 tiles only), 7B projections, us:
 //   2047 rows: QKV 384 -> 337, out 115 -> 112, gate/up 712 -> 603, down 297 -> 296; 333 rows: 111 -> 87, 45 -> 33,
@@ -569,9 +570,12 @@ hipError_t launch_blk_gemm_as(int shape, bool split, const BlkGemm& p, hipStream
 }
 
 // Pieces of a k range for blocks of rows that belong to sequences of at most kBlkPiecedRows rows each: a function of K
-// alone, so that a row's bits are the same in whatever block it is computed.  About 32 k-steps a piece, at least 4 pieces:
-// between the best counts measured at 60 .. 333 rows (K = 2048: 5 .. 8, 4096: 3 .. 10, 8192: 10 .. 17, 11008: 5 .. 15,
-// all within 10 % of the best); beyond 1024 rows no launch gains from cutting k.
+// alone, so that a row's bits are the same in whatever block it is computed.  K / 256 below 1024 (1..3), 4 from there to
+// 5119, then K / 1024 (8 for 8192, 10 for 11008).  No count is best at all row counts.  Rule against the best of 1 .. 17 at 60
+// / 128 / 333 rows, us (N x K): 6144 x 2048 14.1 / 16.1 / 29.9 against 14.1 / 16.1 / 27.9 (4, 5, 3 pieces), 4096 x 4096 19.5
+// / 21.2 / 35.0 against 16.5 / 19.3 / 33.9 (9, 7, 5), 12288 x 4096 26.9 / 39.3 / 86.7 against 26.9 / 36.4 / 83.9 (4, 2, 3),
+// 2048 x 8192 23.5 / 26.6 / 37.5 against 19.4 / 21.4 / 32.0 (11, 11, 5), 4096 x 11008 28.0 / 40.5 / 77.0 against 27.5 / 32.3
+// / 66.1 (9, 8, 5).  Beyond 1024 rows no launch gains from cutting k.
 int blk_pieces(int K) {
   const int ksteps = K / 32;
   return std::min(ksteps / 8, std::max(4, ksteps / 32));

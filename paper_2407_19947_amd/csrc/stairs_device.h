@@ -11,14 +11,9 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 // ---------------------------------------------------------------------------------------
 // helpers
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t bf16_bits_rne(float x) {
-  uint32_t u = __float_as_uint(x);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return u >> 16;
-}
 __device__ __forceinline__ float bf16_bits_to_float(uint32_t b) { return __uint_as_float(b << 16); }
 // Two floats -> a packed pair of bf16 (a in the low half), round to nearest even, by the conversion instruction of
-// gfx950 (one instruction for the pair; same bits as bf16_bits_rne for every value that is not a NaN), and the split
+// gfx950 (one instruction for the pair), and the split
 // of the pair into that high part and the bf16 of the remainders.
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -58,13 +53,10 @@ __device__ __forceinline__ void store_frag4(uint4* frag, int m, int k, float4 v,
   dst[0] = hi;
   dst[128] = lo;                                               // the low fragment follows 64 lanes x 16 bytes later
 }
-__device__ __forceinline__ float load_kv(const float* p) { return *p; }
-__device__ __forceinline__ float load_kv(const uint16_t* p) { return bf16_bits_to_float(*p); }
-__device__ __forceinline__ void store_kv(float* p, float v) { *p = v; }
-__device__ __forceinline__ void store_kv(uint16_t* p, float v) { *p = (uint16_t)bf16_bits_rne(v); }
+__device__ __forceinline__ float load_elem(const float* p) { return *p; }
+__device__ __forceinline__ float load_elem(const uint16_t* p) { return bf16_bits_to_float(*p); }
 // keys/values of bf16 models are cached as IEEE half: same bytes as bf16, 8x smaller rounding step
 // (bf16 storage alone moves 1B-class logits by 1.7e-2); saturates at the half range
-__device__ __forceinline__ float load_kv(const _Float16* p) { return (float)*p; }
 __device__ __forceinline__ void store_kv(_Float16* p, float v) { *p = (_Float16)fminf(fmaxf(v, -65504.f), 65504.f); }
 
 // four adjacent halves of a key tile (one 8-byte store)
@@ -133,12 +125,6 @@ __device__ __forceinline__ bool last_arrival(int* counter, int expected, int* s_
   __syncthreads();
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
   return *s_flag != 0;
-}
-
-__device__ __forceinline__ float row_rstd(const RowNorm& nrm, int m, int K) {
-  float ss = 0.f;
-  for (int p = 0; p < nrm.ssq_n; ++p) ss += nrm.ssq_part[m * nrm.ssq_n + p];
-  return 1.0f / sqrtf(ss / (float)K + nrm.eps);
 }
 
 // Row order of the re-laid-out matrix.  Output column n' of the GEMM is source row perm(n'):

@@ -14,8 +14,7 @@ constexpr int kAttnChunk = 128;     // keys per attention work-group of the fp32
 constexpr int kAttnChunkH = 256;    // keys per attention work-group of the half-cache kernels (a wave owns 64)
 constexpr int kAttnFusedMaxChunks = 24;   // more chunks per head than this: the chunk merge runs as a second kernel
 constexpr size_t kAttnMergeMaxLds = 150 * 1024;   // most dynamic LDS the chunk merge may take
-constexpr int kSsqGroupF32 = 1024;  // residual columns per sum-of-squares partial, fp32 models
-constexpr int kSsqGroupBf16 = 16;   // ... bf16 models (= one weight tile of the residual-writing GEMMs)
+constexpr int kSsqGroup = 16;       // residual columns per sum-of-squares partial, bf16 models (= one weight tile of the residual-writing GEMMs)
 constexpr int kUnitK = 256;         // k extent of one weight "unit" (8 MFMA k-steps of 32)
 constexpr int kSliceUnits = 2;      // units per split-K slice (512 k)
 constexpr int kSpwRows = 9;         // 9..16 rows: a split-K work-group takes two k chunks (see launch_gemm)
@@ -65,10 +64,7 @@ struct RowNorm {
   float eps;
 };
 
-inline int ssq_groups(int d, int bf16) {
-  const int g = bf16 ? kSsqGroupBf16 : kSsqGroupF32;
-  return (d + g - 1) / g;
-}
+inline int ssq_groups(int d) { return (d + kSsqGroup - 1) / kSsqGroup; }
 inline int gemm_slices(int K, int dtype_bf16) {
   if (!dtype_bf16) return 1;
   int units = K / kUnitK;

@@ -1453,8 +1453,8 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
 // embedding gather, rope table
 // ---------------------------------------------------------------------------------------
 // bf16 models: a sum-of-squares partial per 16 residual columns (the fp32 GEMM gathers its own)
-// The block column after the last embedding column fills the row's rotation table instead:
-// cs[m][i] = (cos, sin)(position * theta^(-2i/hd)), the angle formed in double.
+// The block column after the last embedding column copies the rotation entries of the row's position from the model's
+// table instead (identity without one, and outside it).
 // A row whose position lies outside [0, tok_cap) or whose token id lies outside [0, vocab) becomes a row of zeros:
 // the gather never leaves the token array or the embedding table, whatever the array holds.
 template <typename E>
@@ -1478,7 +1478,7 @@ __global__ __launch_bounds__(256) void k_embed(const E* __restrict__ emb, const 
     const int id = (p >= 0 && p < tok_cap) ? tokens[p] : -1;
     if (id >= 0 && id < vocab) {
       const E* row = emb + (size_t)id * d + c;
-      v.x = load_kv(row); v.y = load_kv(row + 1); v.z = load_kv(row + 2); v.w = load_kv(row + 3);
+      v.x = load_elem(row); v.y = load_elem(row + 1); v.z = load_elem(row + 2); v.w = load_elem(row + 3);
     }
     *reinterpret_cast<float4*>(x + (size_t)m * d + c) = v;
     ss = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
@@ -1495,7 +1495,7 @@ void launch_embed(const void* emb, int emb_bf16, const int* tokens, int tok_slot
                   int M, int d, float* x, float* ssq_part, int hd, const float2* tab, int tab_len, float2* cs, hipStream_t st, uint4* frag,
                   const float* frag_gain) {
   dim3 grid((d + 1023) / 1024 + 1, M), block(256);
-  const int sn = ssq_groups(d, emb_bf16);
+  const int sn = ssq_groups(d);
   if (emb_bf16)
     hipLaunchKernelGGL((k_embed<uint16_t>), grid, block, 0, st, static_cast<const uint16_t*>(emb), tokens,
                        tok_slot_stride, tok_cap, vocab, pos, d, x, ssq_part, sn, hd, tab, tab_len, cs, frag, frag_gain);
