@@ -1,4 +1,6 @@
 """GPU: row blocks on the block kernels at the row counts and widths where their launches change."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
@@ -8,12 +10,11 @@ import synth_inputs as si
 pytestmark = pytest.mark.gpu
 
 
-# widths with a ragged last k chunk (1280, 2816), an odd number of unembedding tiles (528 / 16 = 33), features that end
-# inside a 256-, 192- and 128-feature work-group
+# widths with a ragged last k chunk (1280, 2816), features that end inside a 256- and a 128-feature work-group
 @pytest.mark.parametrize("d,heads,f", [(256, 2, 256), (1280, 10, 2816), (2048, 32, 1024)])
 @pytest.mark.parametrize("rows", [17, 33, 64, 65, 127, 129, 256, 1024, 1025, 2048, 2049])
 def test_block_rows_against_decode_kernels(d, heads, f, rows, monkeypatch):
-    """A prompt of one forward and the smallest block (33 rows), edges of the 64-, 128- and 256-row tiles, the largest block whose k range is summed in pieces and
+    """A prompt of one forward and the smallest block (33 rows), edges of the 64- and 128-row tiles, the largest block whose k range is summed in pieces and
     the smallest that is not, a full block and one row more: the stair logits behind a prompt ingested in blocks against
     those behind the same prompt ingested by the decode kernels (same inputs, another order of additions: 1e-5 of the
     logits' size measured; keys and values are rounded to half in both, so single roundings can fall differently)."""
@@ -35,7 +36,8 @@ def test_block_rows_against_decode_kernels(d, heads, f, rows, monkeypatch):
 @pytest.mark.parametrize("lens", [[18, 33, 34, 49, 300, 18], [17, 200, 5, 1025, 1026, 65, 1300], [700, 700, 700, 129]])
 def test_prompts_of_a_batch_share_blocks(lens):
     """Prompts that share a block (17 .. 1024 rows: the smallest, ends on and beside multiples of 16 rows, more than one block's
-    worth), too short, and too long to share one: every sequence's tokens are the bits of the sequence generated alone."""
+    worth), too short, and too long to share one: every sequence's tokens are those of the sequence generated alone, before the
+    reservation (there prompts of up to 32 rows take the decode kernels)."""
     w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=512, n_heads=4, d_ffn=768, vocab=1040),
                            draft=dict(kind="prefix", n_layers=1), P=2, G=1)
     target, draft = si.make_pair(w)
@@ -47,6 +49,22 @@ def test_prompts_of_a_batch_share_blocks(lens):
         toks, _ = s.generate_batch(prompts, 12, 2)
     for b, want in enumerate(alone):
         assert np.array_equal(toks[b], want), lens[b]
+
+
+@pytest.mark.parametrize("f", [8192, 11008])
+def test_more_than_four_pieces(f):
+    """k = 8192 is summed in 8 pieces, 11008 in 10 of unequal length: prompts whose down projection spreads them over
+    work-groups alone (40 rows) and keeps them in registers in the block they share (1900 rows) give the same tokens."""
+    w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=512, n_heads=4, d_ffn=f, vocab=1040),
+                           draft=dict(kind="prefix", n_layers=1), P=2, G=1)
+    target, draft = si.make_pair(w)
+    rng = np.random.default_rng(f)
+    prompts = [rng.integers(0, 1040, P).astype(np.int32) for P in (41, 1000, 18, 500, 35, 300)]
+    with pkg.Stairs(target, draft, k_max=2, max_seq=1040) as s:
+        s.reserve_batch(len(prompts))
+        alone = np.stack([s.generate(p, 12, 2)[0].copy() for p in prompts])
+        toks, _ = s.generate_batch(prompts, 12, 2)
+    assert np.array_equal(toks, alone)
 
 
 @pytest.mark.parametrize("rows", [16, 17, 24, 31, 32])
@@ -84,3 +102,59 @@ def test_short_prompts_of_a_batch(B, k):
         turned, _ = s.generate_batch(prompts[::-1], 12, k)
     assert np.array_equal(first, turned[::-1])
     assert np.array_equal(first, alone)
+
+
+class _BlkGemm(C.Structure):
+    """struct BlkGemm of csrc/stairs_kernels.h"""
+    _fields_ = [("W", C.c_void_p), ("NTILES", C.c_int), ("tile_first", C.c_int), ("K", C.c_int), ("XF", C.c_void_p),
+                ("RT", C.c_int), ("R", C.c_int), ("kind", C.c_int), ("out", C.c_void_p), ("ldo", C.c_int),
+                ("ssq", C.c_void_p), ("ssq_n", C.c_int), ("eps", C.c_float), ("frag_out", C.c_void_p), ("gain", C.c_void_p),
+                ("ssq_out", C.c_void_p), ("rows", C.c_void_p), ("cs", C.c_void_p), ("Kc", C.c_void_p), ("Vc", C.c_void_p),
+                ("slot_stride", C.c_size_t), ("cap", C.c_int), ("hd", C.c_int), ("da", C.c_int), ("pieces", C.c_int)]
+
+
+def _cxx(name, restype, *argtypes):
+    """a host function of the library's C++ side, by its mangled name"""
+    f = getattr(pkg.lib(), name)
+    f.restype, f.argtypes = restype, argtypes
+    return f
+
+
+@pytest.mark.parametrize("R", [17, 65, 129, 256])
+@pytest.mark.parametrize("K,pieces", [(768, 3), (2048, 4), (8192, 8), (11008, 10)])
+def test_block_gemm_forms_have_the_same_bits(K, pieces, R):
+    """One product by both tile shapes, its k pieces added up in registers and through memory: the same bits, and those of
+    a 64-bit product but for the roundings of K single-precision additions (operands carry bf16 high + low parts).  Widths:
+    pieces of unequal length (11008), a last k chunk of half the length (768, 11008), an odd number of weight tiles, rows
+    on both sides of the 64- and 128-row tiles."""
+    import torch
+    assert _cxx("_ZN6stairs17configure_kernelsEv", C.c_int)() == 0
+    assert _cxx("_ZN6stairs10blk_piecesEi", C.c_int, C.c_int)(K) == pieces
+    launch = _cxx("_ZN6stairs18launch_blk_gemm_asEibRKNS_7BlkGemmEP12ihipStream_tPfm", C.c_int, C.c_int, C.c_bool,
+                  C.POINTER(_BlkGemm), C.c_void_p, C.c_void_p, C.c_size_t)
+    NT, RT, ks = 33, (R + 127) // 128 * 8, K // 32
+    g = torch.Generator().manual_seed(K + R)
+    w = torch.randn(NT * 16, K, generator=g).to(torch.bfloat16)
+    x = torch.randn(RT * 16, K, generator=g)
+    hi = x.to(torch.bfloat16)
+    lo = (x - hi.float()).to(torch.bfloat16)
+    # operand tiles [chunk of 16 k-steps][tile][k-step][lane r + 16 g][8], the last chunk as long as is left
+    t = w.view(NT, 16, ks, 4, 8).permute(0, 2, 3, 1, 4)                      # [tile][k-step][g][r][8]
+    W = torch.cat([t[:, c:c + 16].reshape(-1) for c in range(0, ks, 16)]).cuda()
+    # fragments [k-step][column tile][high, low][lane][8]
+    X = torch.stack([v.view(RT, 16, ks, 4, 8).permute(2, 0, 3, 1, 4) for v in (hi, lo)], 2).reshape(-1).cuda()
+    part = torch.empty(pieces * ((R + 15) // 16 * 16) * NT * 16, device="cuda")
+    outs = []
+    for shape in (0, 1):
+        for split in (False, True):
+            y = torch.full((R, NT * 16), float("nan"), device="cuda")
+            p = _BlkGemm(W=W.data_ptr(), NTILES=NT, K=K, XF=X.data_ptr(), RT=RT, R=R, out=y.data_ptr(), ldo=NT * 16, pieces=pieces)
+            torch.cuda.synchronize()
+            assert launch(shape, split, C.byref(p), None, part.data_ptr(), part.numel()) == 0
+            torch.cuda.synchronize()
+            outs.append(y.cpu())
+    for y in outs[1:]:
+        assert torch.equal(y, outs[0])
+    xs = hi.double()[:R] + lo.double()[:R]
+    want, size = xs @ w.double().t(), xs.abs() @ w.double().abs().t()
+    assert ((outs[0].double() - want).abs() <= 2 * K * 2.0 ** -24 * size).all()

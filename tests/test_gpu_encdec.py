@@ -36,7 +36,7 @@ def test_tiny_pair_against_the_oracle(k):
 
 @pytest.mark.parametrize("S", [1, 2, 31, 33, 127, 128, 129, 300])
 def test_source_lengths(S):
-    """Source ends before / on / after a 32-row encoder block and a 128-key attention chunk; max_src == S."""
+    """Source ends before / on / after a 32-row group and a 128-key attention chunk; max_src == 300."""
     w, t, d, src = _pair(S=300)
     _log(f"encdec source length S={S}")
     res = run_encdec_side_by_side(t, d, src[:S], 12, 3, LOGIT_TOL_BF16)
@@ -49,6 +49,15 @@ def test_short_sources(S):
     kernels, then one block); attention width 512 beside d_model 256."""
     w, t, d, src = _pair(S=32, target=dict(n_enc_layers=2, n_dec_layers=2, d_model=256, n_heads=4, head_dim=128))
     res = run_encdec_side_by_side(t, d, src[:S], 8, 3, LOGIT_TOL_BF16)
+    assert res["max_logit_err"] < 5e-3
+
+
+@pytest.mark.parametrize("S", [1023, 1024, 1025, 4096])
+def test_source_lengths_where_the_sums_change(S):
+    """Sources of up to 1024 rows are summed in k pieces, longer ones in one run; the longest a context takes.  Attention
+    width 512 beside d_model 256, feed-forward 1024 (four pieces)."""
+    w, t, d, src = _pair(S=4096, target=dict(n_enc_layers=2, n_dec_layers=1, d_model=256, n_heads=4, head_dim=128, d_ffn=1024))
+    res = run_encdec_side_by_side(t, d, src[:S], 4, 2, LOGIT_TOL_BF16)
     assert res["max_logit_err"] < 5e-3
 
 
@@ -69,8 +78,8 @@ def test_short_source_costs_less_than_a_block():
 
 
 def test_long_source_takes_the_stand_alone_merge():
-    """3300 source positions = 26 attention chunks: above the limit of the fused chunk merge, so the encoder's
-    attention (bias, fixed key set) and the cross-attention run the merge as a kernel of its own."""
+    """3300 source positions: the encoder takes them as one block (26 groups of 128 rows, one run over k); the decoder's
+    cross-attention (fixed key set) is 13 chunks of 256 keys, which its last work-group merges."""
     w, t, d, src = _pair(S=3300)
     _log("encdec long source S=3300")
     res = run_encdec_side_by_side(t, d, src, 10, 3, LOGIT_TOL_BF16)

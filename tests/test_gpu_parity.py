@@ -458,12 +458,12 @@ def test_batch_limits_and_errors():
 
 
 def test_block_prefill_against_row_prefill_and_oracle(monkeypatch):
-    """Prompts of 64 rows and more are ingested in blocks on the block GEMM; the first stair batch after either
+    """Prompts of 33 rows and more are ingested in blocks on the block GEMM; the first stair batch after either
     kind of prefill must agree with the oracle, and the two kinds with each other far inside the tolerance."""
     w = si.scaled_workload("cfg2_125m", target=dict(n_layers=3, d_model=256, n_heads=4, d_ffn=768, vocab=2048),
                            draft=dict(kind="prefix", n_layers=1), P=600, G=8)
     target, draft = si.make_pair(w)
-    prompt = si.make_prompt(w)                 # 599 rows: one full block of 512 and a ragged one
+    prompt = si.make_prompt(w)                 # 599 rows: ends inside a 64- and a 128-row tile
     d_tokens = [3, 1, 4]
     T = so.OracleModel(target, np.float64)
     ref = so.forward_full(T, np.concatenate([prompt, d_tokens]))[len(prompt) - 1:]
@@ -481,8 +481,7 @@ def test_block_prefill_against_row_prefill_and_oracle(monkeypatch):
 
 @pytest.mark.parametrize("P", [64, 65, 66, 97, 129, 513, 514, 545, 577])
 def test_block_prefill_row_counts(P, monkeypatch):
-    """Block ingestion at the row counts where its pieces change: the smallest block (P - 1 = 64 rows; one row fewer goes through the decode kernels), whole
-    32-row groups with and without a ragged group, one row past a 512-row block; against the row prefill."""
+    """Block ingestion on both sides of the 64- and 128-row tiles and of whole 32-row groups; against the row prefill."""
     w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=256, n_heads=4, d_ffn=512, vocab=2048),
                            draft=dict(kind="prefix", n_layers=1), P=P, G=8)
     target, draft = si.make_pair(w)
