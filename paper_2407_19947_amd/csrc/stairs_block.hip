@@ -534,16 +534,9 @@ static size_t blk_part_floats(const BlkGemm& p) { return (size_t)p.pieces * ((p.
 
 // The kernel's prologue requests the first kBlkST k-steps of its piece unasked and its loop ends on the last kBlkST + 1: a
 // piece shorter than that would copy k-steps that are not its own, at the end of the range operands past the matrix (the
-// copies carry no bounds).  Pieces as k_gemm_bf16_block cuts them, whole units of the weight layout (256 k).
-bool blk_pieces_fit(int K, int pieces) {
-  const int ksteps = K / 32;
-  if (K < 256 || K % 256 || pieces < 1) return false;
-  for (int i = 0; i < pieces; ++i) {
-    const int end = i + 1 < pieces ? (int)((long)ksteps * (i + 1) / pieces & ~1L) : ksteps;
-    if (end - (int)((long)ksteps * i / pieces & ~1L) < 8) return false;
-  }
-  return true;
-}
+// copies carry no bounds).  K is whole units of the weight layout (256 k); pieces end at ksteps * i / pieces rounded down
+// to even, which moves an end by less than two: all of them have 8 k-steps exactly if 8 * pieces <= ksteps.
+bool blk_pieces_fit(int K, int pieces) { return K >= 256 && K % 256 == 0 && pieces >= 1 && pieces <= K / 256; }
 
 hipError_t launch_blk_gemm_as(int shape, bool split, const BlkGemm& p, hipStream_t st, float* part, size_t part_floats) {
   if (shape < 0 || shape >= kBlkShapeCount || p.R < 1 || p.RT * 16 < p.R || p.tile_first < 0 || p.tile_first >= p.NTILES ||

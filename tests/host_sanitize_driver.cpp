@@ -399,7 +399,14 @@ static void part2_encoder_decoder() {
 // rows past its fragments or with more pieces than its scratch holds is refused before anything runs.
 static void part1_block_gemm_launches() {
   for (int K = 256; K <= 131072; K += 256) CHECK(stairs::blk_pieces(K) >= 1 && stairs::blk_pieces_fit(K, stairs::blk_pieces(K)));
-  CHECK(stairs::blk_pieces_fit(4096, 16));           // 128 k-steps: 8 each
+  for (int K = 256; K <= 16384; K += 256)            // the rule against the pieces as the kernel cuts them
+    for (int pieces = 1; pieces <= 70; ++pieces) {
+      const int ksteps = K / 32;
+      bool fit = true;
+      for (int i = 0; i < pieces; ++i)
+        fit = fit && (i + 1 < pieces ? ksteps * (i + 1) / pieces & ~1 : ksteps) - (ksteps * i / pieces & ~1) >= 8;
+      CHECK(stairs::blk_pieces_fit(K, pieces) == fit);
+    }
   CHECK(!stairs::blk_pieces_fit(4096, 17) && !stairs::blk_pieces_fit(4096, 128) && !stairs::blk_pieces_fit(512, 3));
   CHECK(!stairs::blk_pieces_fit(0, 1) && !stairs::blk_pieces_fit(4096 + 32, 1) && !stairs::blk_pieces_fit(4096, 0));
   stairs::BlkGemm p{};
