@@ -1,6 +1,6 @@
 // Host-sanitizer driver for the C ABI of include/stairs.h.
 //
-// Built together with the library's two sources as ONE executable whose host code is instrumented with
+// Built together with the library's sources as ONE executable whose host code is instrumented with
 // AddressSanitizer and UndefinedBehaviorSanitizer (device code is not instrumented; build line in
 // tests/test_host_sanitizers.py).  Part 1 needs no GPU: the argument checks and host-only routines of every entry
 // point.  Part 2 runs when a GPU is visible: a tiny random bf16 model pair through every kind of call (prefill in
