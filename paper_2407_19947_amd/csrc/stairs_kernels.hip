@@ -2168,8 +2168,9 @@ static void attn_dispatch(const float* q, const float* K, const float* V, int ca
   hipLaunchKernelGGL(k_attn_combine<HD>, dim3(H, M), dim3(HD), 0, st, part_o, part_ml, H, pos, nchunk_cap, out, d);
 }
 
-// Callers round the 128-key units of a launch up to a multiple of 4 at most, so its rows see more than (units - 4) of them:
-// what lies below that is requested before the length is known, nothing else.  (The first chunk whole at any length: 3 rows
+// Callers round the 128-key units of a launch up to a multiple of 4 at most, so its rows see more than (units - 4) of them
+// (the early steps of a proposal, whose launches are sized for its last, up to k - 1 keys fewer: inside the cache all the
+// same).  What lies below that is requested before the length is known, nothing else.  (The first chunk whole at any length: 3 rows
 // at contexts of 16 / 64 / 130 / 256 keys, 16 heads of 128: 5.2 / 5.1 / 5.2 / 5.2 us, now 4.7 / 4.7 / 4.8 / 5.2; 12 heads of
 // 64: 4.3 / 4.4 / 4.2 / 4.3, now 4.0 / 4.2 / 4.2 / 4.3; a head's chunk is 128 and 64 KiB.)  Several sequences: their lengths
 // differ, so each work-group looks its own up (64 slots of 16 heads, 3 rows, contexts of 16..210 keys: 27.3 -> 17.9 us; 16
