@@ -351,10 +351,10 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
         }
       }
     }
-    // the norm gain of this thread's k group (every item of a thread has kg = lane)
+    // the norm gain of this thread's k group (every item of a thread has kg = lane modulo the 64 or 32 groups of the chunk)
     float4 g0 = make_float4(1.f, 1.f, 1.f, 1.f), g1 = g0;
     if (nrm.gain && units > 0) {
-      const float4* gp = reinterpret_cast<const float4*>(nrm.gain + k0 + min(lane, kgs - 1) * 8);
+      const float4* gp = reinterpret_cast<const float4*>(nrm.gain + k0 + (lane & (kgs - 1)) * 8);
       g0 = gp[0];
       g1 = gp[1];
     }

@@ -565,6 +565,30 @@ def test_five_to_seven_rows_of_small_models_have_the_bits_of_any_other_count(d, 
             assert np.array_equal(lg, want[:k + 1]), k
 
 
+@pytest.mark.parametrize("d,heads", [(4352, 34), (4608, 36)])
+def test_gains_of_a_short_last_chunk(d, heads):
+    """Norm gains that differ from column to column, k with a last chunk of half the length (4352) and without (4608), 4 and
+    more rows through the split-K kernel (whose odd rows took the gain of one k group for half of that chunk), up to 3 through the
+    LDS-resident one: the rows they share have the same bits."""
+    w = si.scaled_workload("cfg2_125m", target=dict(n_layers=1, d_model=d, n_heads=heads, d_ffn=512, vocab=528),
+                           draft=dict(kind="prefix", n_layers=1), P=9, G=1)
+    target, _ = si.make_pair(w)
+    g = np.random.default_rng([12, d])
+    for ly in target.layers:
+        ly["attn_norm"], ly["ffn_norm"] = (g.uniform(0.5, 2.0, d).astype(np.float32) for _ in range(2))
+    target.final_norm = g.uniform(0.5, 2.0, d).astype(np.float32)
+    prompt = si.make_prompt(w)
+    dr = g.integers(0, 528, 4).astype(np.int32)
+    want = None
+    with pkg.Stairs(target, target, k_max=4, max_seq=32) as s:
+        for k in (2, 1, 0, 3, 4):
+            s.prefill(prompt)
+            _, _, lg = s.verify_tokens(dr[:k], logits=True)
+            want = lg.copy() if want is None else want
+            n = min(len(want), k + 1)
+            assert np.array_equal(lg[:n], want[:n]), k
+
+
 @pytest.mark.parametrize("heads,P", [(16, 1020), (16, 1300), (8, 1300), (8, 2400)])
 def test_fp32_rows_do_not_depend_on_their_number_at_long_contexts(heads, P):
     """fp32, head size 64 and 128, contexts at which stair batches of a few rows go from one to four rows per work-group
