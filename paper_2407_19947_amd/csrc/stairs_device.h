@@ -53,6 +53,17 @@ __device__ __forceinline__ void store_frag4(uint4* frag, int m, int k, float4 v,
   dst[0] = hi;
   dst[128] = lo;                                               // the low fragment follows 64 lanes x 16 bytes later
 }
+// base + a byte offset of 32 bits: one address register beside a scalar base
+template <typename T>
+__device__ __forceinline__ T ld_at(const void* base, uint32_t bytes) {
+  return *reinterpret_cast<const T*>(static_cast<const char*>(base) + bytes);
+}
+// A kernel argument wanted in a register now: all of a kernel's arguments then come in one round trip at its start instead
+// of one in front of each part that uses some of them.
+template <typename T>
+__device__ __forceinline__ void want(const T& v) {
+  asm volatile("" ::"s"(v));
+}
 __device__ __forceinline__ float load_elem(const float* p) { return *p; }
 __device__ __forceinline__ float load_elem(const uint16_t* p) { return bf16_bits_to_float(*p); }
 // keys/values of bf16 models are cached as IEEE half: same bytes as bf16, 8x smaller rounding step
@@ -75,6 +86,26 @@ __device__ __forceinline__ void blk_store_frag4(uint4* frag, int RT, int r, int 
   uint2* dst = reinterpret_cast<uint2*>(frag) + u4 * 2 + ((k & 7) >> 2);
   dst[0] = hi;
   dst[128] = lo;
+}
+
+// Butterfly sums without the LDS unit (a ds_bpermute of __shfl_xor is a round trip of 100 cycles and more, a swap or a
+// rotation one instruction): x + x of the lane at distance 16, 8, 4, 2, 1, in that order, the additions and the bits of the
+// __shfl_xor form.  (A rotation by 8 in a row of 16 is the exchange of its halves; after it the row repeats every 8
+// lanes, so a rotation by 4 is the next exchange, and so on.)
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+constexpr int kDppRor8 = 0x128, kDppRor4 = 0x124, kDppXor2 = 0x4E, kDppXor1 = 0xB1;   // (quad_perm [2,3,0,1], [1,0,3,2])
+constexpr int kDppHalfMirror = 0x141;                            // lane ^ 7: the other quad of eight lanes
+constexpr int kDppQuad0 = 0x00, kDppQuad1 = 0x55, kDppQuad2 = 0xAA, kDppQuad3 = 0xFF;   // a lane of the quad in all four
+__device__ __forceinline__ float half_wave_sum(float v) {      // over lanes 0 .. 31 and 32 .. 63
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  v += dpp<kDppRor8>(v);
+  v += dpp<kDppRor4>(v);
+  v += dpp<kDppXor2>(v);
+  return v + dpp<kDppXor1>(v);
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -163,6 +194,15 @@ __device__ __forceinline__ float swiglu(float g, float u) {
 __device__ __forceinline__ float sumsq4(float x, float y, float z, float w) {
 #pragma clang fp contract(off)
   return (x * x + y * y) + (z * z + w * w);
+}
+// the same partial with the 16 values in 16 adjacent lanes, one each
+__device__ __forceinline__ float tile_sumsq(float x) {
+#pragma clang fp contract(off)
+  float s = x * x;
+  s = s + dpp<kDppXor1>(s);
+  s = s + dpp<kDppXor2>(s);                                      // sumsq4 of a quad's values in each of its lanes
+  s = s + dpp<kDppHalfMirror>(s);
+  return s + dpp<kDppRor8>(s);
 }
 __device__ __forceinline__ float2 rope_rotate(float a, float b, float2 cs) {
 #pragma clang fp contract(off)

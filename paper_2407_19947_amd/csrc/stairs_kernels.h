@@ -290,7 +290,7 @@ void launch_attention_flash(const float* q, const void* Kc, const void* Vc, int 
 // dst[0..bytes) = src[0..bytes), bytes a multiple of 16: reads `bytes` and writes `bytes` of HBM
 void launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream_t st);
 
-// opt in to large dynamic LDS for the kernels that need it (once per process/device)
+// opt in to large dynamic LDS for the kernels that need it (the first call on a device does it)
 hipError_t configure_kernels();
 hipError_t configure_block_kernels();   // (called by configure_kernels)
 

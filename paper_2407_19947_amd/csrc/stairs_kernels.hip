@@ -15,6 +15,7 @@
 #include <stdlib.h>
 
 #include <algorithm>
+#include <mutex>
 #include <vector>
 
 namespace stairs {
@@ -292,6 +293,18 @@ __device__ __forceinline__ void load_unit(const uint4* p, uint4 (&wb)[8]) {
   for (int i = 0; i < 8; ++i) wb[i] = STREAM ? ld_nt(&p[i * STEP]) : p[i * STEP];
 }
 
+// The same with a base that is the same in all lanes: lane l reads base + off + i * STEP * 16 bytes; what lies outside
+// [base, base + span) is not fetched and reads as zeros.
+template <bool STREAM, int STEP>
+__device__ __forceinline__ void load_unit_in(const uint4* base, uint32_t off, uint32_t span, uint4 (&wb)[8]) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(base), 0, span, 0x00027000);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const u32x4_t v = __builtin_amdgcn_raw_buffer_load_b128(r, off + i * (STEP * 16), 0, STREAM ? 2 : 0);
+    wb[i] = make_uint4(v.x, v.y, v.z, v.w);
+  }
+}
+
 template <int CT, int NT, int ROLE, int SPW, bool STREAM>
 __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw, int KT, int NTILES,
                                                    const float* __restrict__ X, int ldx, int M,
@@ -451,12 +464,21 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
 }
 
 // ---------------------------------------------------------------------------------------
-// The same GEMM for R <= 4 rows when the whole X block fits in LDS (K * R * 4 bytes): one work-group owns ONE
-// 16-row weight tile over the whole k range, its four waves split the 512-wide k chunks between them, the chunk
+// The same GEMM for R <= 7 rows when the whole X block fits in LDS (K * R * 4 bytes): one work-group owns ONE
+// 16-row weight tile over the whole k range, its waves split the 512-wide k chunks between them, the chunk
 // sums meet in LDS and the epilogue follows in the same work-group.  No partial sums in memory and no hand-off
 // between work-groups, so the tail of one work-group overlaps the streaming of the others.  Chunk boundaries,
 // the MFMA order inside a chunk and the order in which the chunk sums are added are those of the split-K
 // kernel: both give the same bits for a row.
+//   What bounds it: large matrices, the weights' way from memory; small ones the chain launch (1.6 us for an empty kernel
+//   in a graph, 1.9 with a load and a store) - arguments - x and weights - conversion - arithmetic - epilogue, i.e. round
+//   trips and the number of instructions one wave runs one after the other (4 cycles each).  So the arguments come in one
+//   round trip (want), a thread stages no more of x than there is for it (GP, Q), waves without a k chunk fetch no weights,
+//   the row statistics are summed beside the arithmetic by the waves with the least of it, everything that depends on the
+//   tile alone is scalar, and sums over lanes stay out of the LDS unit.  Layers of five launches in a graph, 200 keys,
+//   before / now, us: d 768 (ffn 3072) 1 / 3 / 5 rows 23.4 / 26.0 / 27.3 -> 21.7 / 22.6 / 24.5, d 1024 (ffn 4096) 23.9 /
+//   26.5 / 28.3 -> 22.0 / 22.9 / 24.7, d 2048 (ffn 8192) 1 / 3 rows 40.5 / 43.8 -> 39.9 / 42.2; unembedding of 32000 x 768
+//   10.9 / 14.1 / 11.7 -> 9.6 / 9.7 / 10.1; d 4096 as before.
 //   LDS: X high parts [K/8][R] uint4, X low parts [K/8][R] uint4, chunk sums float [chunks][R][16]
 // ---------------------------------------------------------------------------------------
 // Sum of one element's chunk sums held in LDS (stride floats apart), in the order of slice_sum<true>: pairs first.
@@ -477,140 +499,168 @@ __device__ __forceinline__ float lds_chunk_sum(const float* base, int stride, in
 // ROWMAJOR: W as the caller has it, [N, K] row-major: lane r + 16 g reads row 16 tile + r, k 32 kt + 8 g .. + 8, the very
 // operand the tile layout holds in one piece (a wave's load is then 16 runs of 64 bytes; for a matrix used once that is
 // far less than laying it out first).
-template <int R, int ROLE, int NW, int GP, bool STREAM, bool ROWMAJOR = false>
+// GP, Q: k groups (of 8 k) a thread stages in its first pass, threads that share the rows of a k group (covers
+// K <= 8 * 64 * NW * GP / Q: rows_kernel).  WALK: a work-group takes several tiles; else its only one is blockIdx.x.
+template <int R, int ROLE, int NW, int GP, int Q, bool WALK, bool STREAM, bool ROWMAJOR = false>
 __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restrict__ Wsw, int NTILES,
                                                             const float* __restrict__ X, int ldx, RowNorm nrm,
                                                             int K, int N, GemmEpi epi) {
-  // NW waves; GP = k groups a thread takes in the first staging pass (covers K <= 8 * 64 * NW * GP)
-  constexpr int NTH = 64 * NW;
+  constexpr int NTH = 64 * NW, NG = NTH / Q, RP = (R + Q - 1) / Q;
+  constexpr bool NORMED = ROLE != kRoleWo && ROLE != kRoleDown;      // (the residual-writing projections' inputs are not)
   extern __shared__ uint4 lds[];
   __shared__ float s_rstd[8];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  want(Wsw); want(NTILES); want(X); want(ldx); want(K); want(N); want(epi.out);
+  if (NORMED) { want(nrm.gain); want(nrm.ssq_part); want(nrm.ssq_n); }
+  if (ROLE == kRoleQKV) { want(epi.rope_cs); want(epi.pos.base); want(epi.pos.offset); want(epi.pos.rps); want(epi.Kc); want(epi.Vc); want(epi.cap); want(epi.hd); }
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // a work-group takes the tiles blockIdx.x, blockIdx.x + gridDim.x, ...: the X block is staged once for all of them
   int cur_tile = blockIdx.x;
   const int KG = K >> 3;                                   // groups of 8 k per row
-  const int units_total = K / kUnitK;
-  const int nchunks = (units_total + kSliceUnits - 1) / kSliceUnits;
-  const int cpw = (nchunks + NW - 1) / NW;                 // chunks per wave
+  const int units_total = (unsigned)K / kUnitK;
+  const int nchunks = (unsigned)(units_total + kSliceUnits - 1) / kSliceUnits;
+  const int cpw = (unsigned)(nchunks + NW - 1) / NW;       // chunks per wave
   const int c_begin = min(wave * cpw, nchunks), c_end = min(nchunks, c_begin + cpw);
   const int nu = min(units_total, c_end * kSliceUnits) - c_begin * kSliceUnits;   // this wave's units (<= 0: none)
 
-  // address of unit u of this wave: chunk c_begin + u/2 (= split-K slice), unit u%2 inside it
-  const uint4* const wrow = Wsw + (size_t)(lane & 15) * (K >> 3) + (lane >> 4);      // ROWMAJOR: this lane's row of tile 0
+  // address of unit u of this wave: chunk c_begin + u/2 (= split-K slice), unit u%2 inside it (the same in all lanes)
   auto unit_ptr = [&](int u) {
     const int c = c_begin + (u >> 1);
-    if (ROWMAJOR) return wrow + (size_t)cur_tile * 16 * (K >> 3) + (c * kSliceUnits + (u & 1)) * 32;
+    if (ROWMAJOR) return Wsw + (size_t)cur_tile * 16 * (K >> 3) + (c * kSliceUnits + (u & 1)) * 32;
     const int units_c = min(kSliceUnits, units_total - c * kSliceUnits);
-    return Wsw + (size_t)c * NTILES * (kSliceUnits * 8) * 64 + ((size_t)cur_tile * units_c + (u & 1)) * 8 * 64 + lane;
+    return Wsw + (size_t)c * NTILES * (kSliceUnits * 8) * 64 + ((size_t)cur_tile * units_c + (u & 1)) * 8 * 64;
   };
+  const uint32_t lane_off = ROWMAJOR ? (uint32_t)((lane & 15) * (K >> 3) + (lane >> 4)) * 16u : (uint32_t)lane * 16u;
+  // bytes a unit spans from its first lane's on; 0 for a unit this wave does not have: its loads then fetch nothing
+  const uint32_t unit_span = ROWMAJOR ? (uint32_t)(15 * (K >> 3) + 32) * 16u : 8u * 1024u;
 
-  // first pass over the X block: a thread takes all R rows of k group kg (the gain is per k, so it is fetched
-  // once).  These loads (x, gain, row statistics) go out before the weights, so they are not queued behind them.
-  float4 xa[GP][R], xb[GP][R], ga[GP], gb[GP];
+  // first pass over the X block: a thread takes RP rows of k group kg (the gain is per k, so it is fetched once).  These
+  // loads (x, gain, row statistics) go out before the weights, so they are not queued behind them.
+  const bool scale = NORMED && nrm.gain != nullptr;
+  float4 xa[GP][RP], xb[GP][RP], ga[GP], gb[GP];
+  const int kg0 = tid & (NG - 1), m0 = tid / NG;           // this thread's first k group and first row (rows m0, m0 + Q, ...)
 #pragma unroll
   for (int j = 0; j < GP; ++j) {
-    const int kg = tid + NTH * j;
     ga[j] = make_float4(1.f, 1.f, 1.f, 1.f);
     gb[j] = ga[j];
-#pragma unroll
-    for (int m = 0; m < R; ++m) {
-      xa[j][m] = make_float4(0.f, 0.f, 0.f, 0.f);
-      xb[j][m] = xa[j][m];
-    }
     // no condition around the loads (a k group past the end re-reads the last one and is dropped later): the
     // compiler can then count them exactly and later waits do not have to cover the weight loads as well
-    const int kgc = min(kg, KG - 1);
-#pragma unroll
-    for (int m = 0; m < R; ++m) {
-      const float4* xp = reinterpret_cast<const float4*>(X + (size_t)m * ldx + kgc * 8);
-      xa[j][m] = xp[0];
-      xb[j][m] = xp[1];
+    const uint32_t k4 = (uint32_t)min(kg0 + NG * j, KG - 1) * 32u;
+    if (scale) {
+      ga[j] = ld_at<float4>(nrm.gain, k4);
+      gb[j] = ld_at<float4>(nrm.gain, k4 + 16u);
     }
-    if (nrm.gain) {
-      const float4* gp = reinterpret_cast<const float4*>(nrm.gain + kgc * 8);
-      ga[j] = gp[0];
-      gb[j] = gp[1];
+#pragma unroll
+    for (int i = 0; i < RP; ++i) {
+      const uint32_t off = (uint32_t)min(m0 + Q * i, R - 1) * (uint32_t)ldx * 4u + k4;
+      xa[j][i] = ld_at<float4>(X, off);
+      xb[j][i] = ld_at<float4>(X, off + 16u);
     }
   }
-  // row statistics: half a wave per row (R <= 8 rows: the first (R + 1) / 2 waves).  The first 256 partials of the row are
-  // requested here, without conditions (indices clamped, values masked later), and added up after the conversion of
-  // the X block, in the order rows_rstd uses: the 1/rms multiplies the finished sums in the epilogue.
-  const bool has_stats = nrm.gain && nrm.ssq_part;
-  const int st_row = 2 * wave + (lane >> 5), st_pl = lane & 31;
+  // row statistics: half a wave per row, the last waves first (with a short k those have no weights to multiply).  The
+  // first 256 partials of the row are requested here (indices clamped, values masked later); they are added up beside the
+  // arithmetic, in the order rows_rstd uses: the 1/rms multiplies the finished sums in the epilogue.
+  const bool has_stats = scale && nrm.ssq_part;
+  const int st_row = 2 * NW - 1 - (tid >> 5), st_pl = lane & 31;
   float sv[8];
   if (has_stats) {
-    const float* sp = nrm.ssq_part + (size_t)min(st_row, R - 1) * nrm.ssq_n;
+    const uint32_t row = (uint32_t)min(st_row, R - 1) * nrm.ssq_n;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sv[i] = sp[min(st_pl + 32 * i, nrm.ssq_n - 1)];
+    for (int i = 0; i < 2; ++i) sv[i] = ld_at<float>(nrm.ssq_part, (row + min(st_pl + 32 * i, nrm.ssq_n - 1)) * 4u);
+    if (nrm.ssq_n > 64) {
+#pragma unroll
+      for (int i = 2; i < 8; ++i) sv[i] = ld_at<float>(nrm.ssq_part, (row + min(st_pl + 32 * i, nrm.ssq_n - 1)) * 4u);
+    }
   }
 
-  // the wave's first two weight units, again without conditions: a wave with fewer units (short K) loads a valid
-  // unit it will not use
+  // what the epilogue reads -- old x (residual-writing roles), the row's position, the rotation entry: requested ahead of the
+  // arithmetic (behind it they were a round trip of their own at the end of every launch), by all threads (a condition
+  // around a load would make the waits for what was requested before it cover the weights as well)
+  const int half = epi.hd >> 1, hd_log = 31 - __builtin_clz(epi.hd), part_tiles = (unsigned)NTILES / 3u;
+  float x_old = 0.f;
+  int q_pos = 0;
+  float2 q_cs = make_float2(1.f, 0.f);
+  auto request_operands = [&](int tile) {
+    if (!NORMED) x_old = ld_at<float>(epi.out, ((uint32_t)min(tid >> 4, R - 1) * N + tile * 16 + (tid & 15)) * 4u);
+    if (ROLE == kRoleQKV) {                                // (v tiles: some valid entry)
+      const int c = (tile - (tile >= part_tiles ? part_tiles : 0) - (tile >= 2 * part_tiles ? part_tiles : 0)) * 16;
+      q_cs = ld_at<float2>(epi.rope_cs, (uint32_t)(min(tid >> 3, R - 1) * 64 + ((c & (epi.hd - 1)) >> 4) * 8 + (tid & 7)) * 8u);
+    }
+  };
+  if (ROLE == kRoleQKV) q_pos = pos_of(epi.pos, min(tid >> 3, R - 1));
+  if (!WALK) request_operands(cur_tile);
+  // the wave's first two weight units, again without conditions: a unit the wave does not have (short K) is requested with
+  // an empty range, which fetches nothing (as repeated reads of a valid unit they were most of a short-K launch's traffic:
+  // 6 of 8 waves at K = 768)
   uint4 wb0[8], wb1[8];
   // (a macro, not a lambda: register arrays a lambda captures by reference end up in scratch memory)
 #define STAIRS_FIRST_UNITS()                                                                                              \
   do {                                                                                                                    \
-    const uint4* p0 = (nu > 0) ? unit_ptr(0)                                                                              \
-                      : ROWMAJOR ? wrow + (size_t)cur_tile * 16 * (K >> 3)                                                \
-                                 : Wsw + (size_t)cur_tile * min(kSliceUnits, units_total) * 8 * 64 + lane;                 \
-    const uint4* p1 = (nu > 1) ? unit_ptr(1) : p0;                                                                        \
-    load_unit<STREAM, ROWMAJOR ? 4 : 64>(p0, wb0);                                                                                           \
-    load_unit<STREAM, ROWMAJOR ? 4 : 64>(p1, wb1);                                                                                           \
+    load_unit_in<STREAM, ROWMAJOR ? 4 : 64>(nu > 0 ? unit_ptr(0) : Wsw, lane_off, nu > 0 ? unit_span : 0u, wb0);          \
+    load_unit_in<STREAM, ROWMAJOR ? 4 : 64>(nu > 1 ? unit_ptr(1) : Wsw, lane_off, nu > 1 ? unit_span : 0u, wb1);          \
   } while (0)
   STAIRS_FIRST_UNITS();
   uint4* xhi = lds;
   uint4* xlo = lds + KG * R;
   float* csum = reinterpret_cast<float*>(lds + 2 * KG * R); // [chunk][R][16]
-  float* sq = csum + nchunks * R * 16;                      // [R][16], residual-writing roles only
-  const bool scale = nrm.gain != nullptr;
 #pragma unroll
   for (int j = 0; j < GP; ++j) {
-    const int kg = tid + NTH * j;
+    const int kg = kg0 + NG * j;
     if (kg < KG) {
 #pragma unroll
-      for (int m = 0; m < R; ++m) {
+      for (int i = 0; i < RP; ++i) {
+        const int m = m0 + Q * i;
+        if (R % Q && m >= R) continue;
         uint4 hi, lo;
-        split_bf16x8(xa[j][m], xb[j][m], ga[j], gb[j], scale, hi, lo);
+        split_bf16x8(xa[j][i], xb[j][i], ga[j], gb[j], scale, hi, lo);
         xhi[kg * R + m] = hi;
         xlo[kg * R + m] = lo;
       }
     }
   }
   // further passes (longer K): same thing, loads and conversion back to back
-  for (int kg = NTH * GP + tid; kg < KG; kg += NTH) {
-    float4 g0 = make_float4(1.f, 1.f, 1.f, 1.f), g1 = g0;
-    if (scale) {
-      const float4* gp = reinterpret_cast<const float4*>(nrm.gain + kg * 8);
-      g0 = gp[0];
-      g1 = gp[1];
-    }
+  if (Q == 1 && (GP > 1 || NW > 4))
+    for (int kg = NTH * GP + tid; kg < KG; kg += NTH) {
+      float4 g0 = make_float4(1.f, 1.f, 1.f, 1.f), g1 = g0;
+      if (scale) {
+        g0 = ld_at<float4>(nrm.gain, kg * 32u);
+        g1 = ld_at<float4>(nrm.gain, kg * 32u + 16u);
+      }
 #pragma unroll
-    for (int m = 0; m < R; ++m) {
-      const float4* xp = reinterpret_cast<const float4*>(X + (size_t)m * ldx + kg * 8);
-      uint4 hi, lo;
-      split_bf16x8(xp[0], xp[1], g0, g1, scale, hi, lo);
-      xhi[kg * R + m] = hi;
-      xlo[kg * R + m] = lo;
-    }
-  }
-  if (has_stats && wave < (R + 1) / 2) {                   // wave-uniform
-    float ss = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) ss += (st_pl + 32 * i < nrm.ssq_n) ? sv[i] : 0.f;
-    if (st_row < R) {
-      for (int p0 = st_pl + 256; p0 < nrm.ssq_n; p0 += 256) {
-        float v[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) v[i] = (p0 + 32 * i < nrm.ssq_n) ? nrm.ssq_part[st_row * nrm.ssq_n + p0 + 32 * i] : 0.f;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) ss += v[i];
+      for (int m = 0; m < R; ++m) {
+        const uint32_t off = (uint32_t)m * (uint32_t)ldx * 4u + kg * 32u;
+        uint4 hi, lo;
+        split_bf16x8(ld_at<float4>(X, off), ld_at<float4>(X, off + 16u), g0, g1, scale, hi, lo);
+        xhi[kg * R + m] = hi;
+        xlo[kg * R + m] = lo;
       }
     }
+  auto row_stats = [&]() {
+    if (has_stats && wave >= NW - (R + 1) / 2) {           // (whole waves)
+      float ss = 0.f;
 #pragma unroll
-    for (int off = 16; off >= 1; off >>= 1) ss += __shfl_xor(ss, off);
-    if (st_pl == 0 && st_row < R) s_rstd[st_row] = 1.0f / sqrtf(ss / (float)K + nrm.eps);
-  }
+      for (int i = 0; i < 2; ++i) ss += (st_pl + 32 * i < nrm.ssq_n) ? sv[i] : 0.f;
+      if (nrm.ssq_n > 64) {
+#pragma unroll
+        for (int i = 2; i < 8; ++i) ss += (st_pl + 32 * i < nrm.ssq_n) ? sv[i] : 0.f;
+        if (nrm.ssq_n > 256 && st_row < R) {
+          for (int p0 = st_pl + 256; p0 < nrm.ssq_n; p0 += 256) {
+            float v[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) v[i] = (p0 + 32 * i < nrm.ssq_n) ? nrm.ssq_part[st_row * nrm.ssq_n + p0 + 32 * i] : 0.f;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ss += v[i];
+          }
+        }
+      }
+      ss = half_wave_sum(ss);
+      if (st_pl == 0 && st_row < R) s_rstd[st_row] = 1.0f / sqrtf(ss / (float)K + nrm.eps);
+    }
+  };
+  // (long k: in front of the barrier, every wave has weights to multiply behind it)
+  constexpr bool kStatsFirst = GP > 1;
+  if (kStatsFirst) row_stats();
   __syncthreads();
+  if (!kStatsFirst) row_stats();
 
   // B fragment of lane l at k-step kt: row (l & 15) of X (lanes of rows >= R take row 0; their columns of the
   // result are never read), k group kt*4 + (l >> 4)
@@ -627,33 +677,23 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
       acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bl, acc, 0, 0, 0);
     }
   };
-  // the roles whose epilogue loads nothing from memory request the next tile's first units before it (a load in
-  // the epilogue would have to wait for them)
-  constexpr bool kPrefetchNextTile = ROLE == kRoleGateUp || ROLE == kRoleHead || ROLE == kRoleQKV;
-  // (QKV: the row's position is requested here, once for all tiles)
-  int q_pos = 0;
-  if (ROLE == kRoleQKV && tid < R * 8) q_pos = pos_of(epi.pos, tid >> 3);
+  // sum of one element's chunk sums (lds_chunk_sum; one or two chunks without its loop)
+  auto chunk_sum = [&](int m, int n) {
+    const float* src = csum + (m << 4) + n;
+    if (nchunks == 1) return 0.f + src[0];
+    if (nchunks == 2) return 0.f + (src[0] + src[R * 16]);
+    return lds_chunk_sum(src, R * 16, nchunks);
+  };
   for (;;) {
   const int tile = cur_tile;
-  // what the epilogue reads (old x, the rotation entry) is requested ahead of the arithmetic: behind it it was a round
-  // trip of its own at the end of every launch
-  float x_old = 0.f;
-  if ((ROLE == kRoleWo || ROLE == kRoleDown) && tid < R * 16) x_old = epi.out[(size_t)(tid >> 4) * N + tile * 16 + (tid & 15)];
-  float2 q_cs = make_float2(1.f, 0.f);
-  if (ROLE == kRoleQKV && tid < R * 8) q_cs = epi.rope_cs[qkv_rope_index(tid >> 3, tile * 16 + (tid & 7), N / 3, epi.hd)];
+  if (WALK) request_operands(tile);
   for (int u = 0; u < nu; u += 2) {                        // one chunk per pass
     f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
     mfma_unit(wb0, u, acc);
-    if (u + 2 < nu) {
-      const uint4* p = unit_ptr(u + 2);
-      load_unit<STREAM, ROWMAJOR ? 4 : 64>(p, wb0);
-    }
+    if (u + 2 < nu) load_unit_in<STREAM, ROWMAJOR ? 4 : 64>(unit_ptr(u + 2), lane_off, unit_span, wb0);
     if (u + 1 < nu) {
       mfma_unit(wb1, u + 1, acc);
-      if (u + 3 < nu) {
-        const uint4* p = unit_ptr(u + 3);
-        load_unit<STREAM, ROWMAJOR ? 4 : 64>(p, wb1);
-      }
+      if (u + 3 < nu) load_unit_in<STREAM, ROWMAJOR ? 4 : 64>(unit_ptr(u + 3), lane_off, unit_span, wb1);
     }
     const int m = lane & 15;
     if (m < R) {
@@ -662,49 +702,40 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
     }
   }
   __builtin_amdgcn_sched_barrier(0);
+  // the next tile's first units are requested ahead of the epilogue, which loads nothing from memory
   const int next_tile = tile + (int)gridDim.x;
-  if (kPrefetchNextTile && next_tile < NTILES) {
+  if (WALK && next_tile < NTILES) {
     cur_tile = next_tile;
     STAIRS_FIRST_UNITS();
   }
   __syncthreads();
 
   if (ROLE == kRoleWo || ROLE == kRoleDown) {
-    // a thread takes one element of the tile; then one thread per row adds the 16 squares up in the order of
+    // a thread takes one element of the tile; the 16 squares of a row, in 16 adjacent lanes, are added up in the order of
     // the split-K kernel's epilogue
     if (tid < R * 16) {
       const int m = tid >> 4, n = tid & 15;
-      float a = lds_chunk_sum(csum + (m << 4) + n, R * 16, nchunks);
-      if (has_stats) a *= s_rstd[m];
-      a += x_old;
+      const float a = chunk_sum(m, n) + x_old;
       epi.out[(size_t)m * N + tile * 16 + n] = a;
-      sq[tid] = a;
-    }
-    __syncthreads();
-    if (tid < R) {
-      const float* q = sq + tid * 16;
-      const float s0 = sumsq4(q[0], q[1], q[2], q[3]), s1 = sumsq4(q[4], q[5], q[6], q[7]);
-      const float s2 = sumsq4(q[8], q[9], q[10], q[11]), s3 = sumsq4(q[12], q[13], q[14], q[15]);
-      epi.ssq_out[tid * (N >> 4) + tile] = (s0 + s1) + (s2 + s3);
-    }
-    // more than 4 rows: the next projection may take the kernel that reads activation fragments
-    if (R > 4 && epi.frag_out && tid >= 64 && tid < 64 + R * 4) {
-      const int t = tid - 64, m = t >> 2, q = (t & 3) * 4;
-      const float* v = sq + m * 16 + q;
-      store_frag4(epi.frag_out, m, tile * 16 + q, make_float4(v[0], v[1], v[2], v[3]), epi.frag_gain);
+      const float sq = tile_sumsq(a);
+      if (n == 0) epi.ssq_out[m * (N >> 4) + tile] = sq;
+      // more than 4 rows: the next projection may take the kernel that reads activation fragments
+      if (R > 4 && epi.frag_out) {
+        const float4 v = make_float4(dpp<kDppQuad0>(a), dpp<kDppQuad1>(a), dpp<kDppQuad2>(a), dpp<kDppQuad3>(a));
+        if ((n & 3) == 0) store_frag4(epi.frag_out, m, tile * 16 + n, v, epi.frag_gain);
+      }
     }
   } else if (tid < R * 8) {                                // a thread takes row m, columns j and j+8 of the tile
     const int m = tid >> 3, j = tid & 7;
-    float a = lds_chunk_sum(csum + (m << 4) + j, R * 16, nchunks);
-    float b = lds_chunk_sum(csum + (m << 4) + j + 8, R * 16, nchunks);
+    float a = chunk_sum(m, j);
+    float b = chunk_sum(m, j + 8);
     if (has_stats) {
       a *= s_rstd[m];
       b *= s_rstd[m];
     }
     const int col = tile * 16 + j;
-    // (more than 4 rows: also the result's activation fragments -- the four threads of columns 4q .. 4q+3 sit in
-    // adjacent lanes of wave 0, which holds all R * 8 <= 64 threads of this branch)
-    const int l4 = lane & ~3;
+    // (more than 4 rows: also the result's activation fragments -- the four threads of columns 4q .. 4q+3 are a quad of
+    // wave 0, which holds all R * 8 <= 64 threads of this branch)
     if (ROLE == kRoleHead) {
       const bool relu = epi.act == kActRelu;
       if (relu) {
@@ -714,8 +745,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
       epi.out[(size_t)m * N + col] = a;
       epi.out[(size_t)m * N + col + 8] = b;
       if (R > 4 && epi.frag_out) {
-        const float4 va = make_float4(__shfl(a, l4), __shfl(a, l4 + 1), __shfl(a, l4 + 2), __shfl(a, l4 + 3));
-        const float4 vb = make_float4(__shfl(b, l4), __shfl(b, l4 + 1), __shfl(b, l4 + 2), __shfl(b, l4 + 3));
+        const float4 va = make_float4(dpp<kDppQuad0>(a), dpp<kDppQuad1>(a), dpp<kDppQuad2>(a), dpp<kDppQuad3>(a));
+        const float4 vb = make_float4(dpp<kDppQuad0>(b), dpp<kDppQuad1>(b), dpp<kDppQuad2>(b), dpp<kDppQuad3>(b));
         if ((j & 3) == 0) {
           store_frag4(epi.frag_out, m, col, va, epi.frag_gain);
           store_frag4(epi.frag_out, m, col + 8, vb, epi.frag_gain);
@@ -725,18 +756,32 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
       const float o = swiglu(a, b);
       epi.out[(size_t)m * (N >> 1) + tile * 8 + j] = o;
       if (R > 4 && epi.frag_out) {
-        const float4 vo = make_float4(__shfl(o, l4), __shfl(o, l4 + 1), __shfl(o, l4 + 2), __shfl(o, l4 + 3));
+        const float4 vo = make_float4(dpp<kDppQuad0>(o), dpp<kDppQuad1>(o), dpp<kDppQuad2>(o), dpp<kDppQuad3>(o));
         if ((j & 3) == 0) store_frag4(epi.frag_out, m, tile * 8 + j, vo, nullptr);
       }
-    } else {
-      qkv_pair_at(a, b, m, col, N / 3, epi, q_pos, q_cs);
+    } else if (q_pos >= 0) {
+      // qkv_pair_at with everything that depends on the tile alone in scalar registers
+      const int part = (tile >= part_tiles) + (tile >= 2 * part_tiles), c = (tile - part * part_tiles) * 16;
+      const int h = c >> hd_log, w = c & (epi.hd - 1);
+      const size_t head = (size_t)slot_of(epi.pos, m) * epi.kv_slot_stride + (size_t)h * epi.cap * epi.hd;
+      if (part == 2) {
+        store_kv(epi.Vc + head + v_cache_off(q_pos, w + j, epi.hd), a);
+        store_kv(epi.Vc + head + v_cache_off(q_pos, w + j + 8, epi.hd), b);
+      } else {
+        const int e = (w >> 4) * 8 + j;
+        const float2 r = rope_rotate(a, b, q_cs);
+        if (part == 0) {
+          float* dst = epi.out + (size_t)m * (part_tiles * 16) + h * epi.hd + e;
+          dst[0] = r.x;
+          dst[half] = r.y;
+        } else {
+          store_kv(epi.Kc + head + k_cache_off(q_pos, e, epi.hd), r.x);
+          store_kv(epi.Kc + head + k_cache_off(q_pos, e + half, epi.hd), r.y);
+        }
+      }
     }
   }
-  if (next_tile >= NTILES) break;
-  if (!kPrefetchNextTile) {
-    cur_tile = next_tile;
-    STAIRS_FIRST_UNITS();
-  }
+  if (!WALK || next_tile >= NTILES) break;
   __syncthreads();                                         // the chunk sums are free for the next tile
   }
 #undef STAIRS_FIRST_UNITS
@@ -1030,10 +1075,8 @@ size_t rows_path_lds(int role, int M, int N, int K) {
   if (M > 7 || M > max_rows) return 0;
   const size_t bytes = (size_t)K * M * 4 + (size_t)(gemm_slices(K, 1) + 1) * M * 16 * 4;
   // 5..7 rows (at 8 the fragment-reading kernel is as fast), three cases:
-  // k below 2048, a work-group per tile and no more than CUs: 4.5 .. 5.2 us a launch at 125M and at the large
-  // encoder-decoder shape, where the fragment-reading kernel takes 5.1 .. 5.4.  With more tiles one work-group per CU walks
-  // through them, and its waves have no k chunk each to wait for: 512 tiles, k = 512, 5 / 7 rows: 5.5 / 5.9 against 5.1 /
-  // 5.0; 384 tiles, k = 768: 5.5 / 6.0 against 5.7 / 5.7.
+  // k below 2048, a work-group per tile and no more than CUs (more: rows_many_tiles_lds): 4.5 .. 5.2 us a launch at 125M and
+  // at the large encoder-decoder shape, where the fragment-reading kernel takes 5.1 .. 5.4.
   if (M > 4 && role != kRoleDown && K < 2048) return N / 16 <= 256 && bytes <= kRowsPathMaxLds ? bytes : 0;
   // feed-forward outputs with k up to 4096 (one staging pass) and few tiles: 5.0 .. 5.5 against 7.0 us at 125M
   if (M > 4 && role == kRoleDown) return K <= 4096 && N / 16 <= 128 && bytes <= kRowsPathMaxLdsWide ? bytes : 0;
@@ -1053,6 +1096,14 @@ size_t rows_path_lds(int role, int M, int N, int K) {
     return bytes <= kRowsPathMaxLdsWide ? std::max(bytes, (size_t)81 * 1024) : 0;   // > half a CU's LDS: one per CU
   }
   return bytes <= kRowsPathMaxLds ? bytes : 0;
+}
+
+// The same for 5..7 rows, short k and more tiles than CUs: a work-group per tile here as well (the fragment-reading kernel at
+// 5 / 7 rows: 384 tiles, k = 768 7.2 / 7.8 us of a layer, 5.6 / 5.9 this way; 2000 tiles, k = 1024 14.7 / 15.6 against 12.8 /
+// 13.4; with work-groups that walk through the tiles it was the slower one).
+static size_t rows_many_tiles_lds(int role, int M, int N, int K) {
+  const size_t bytes = (size_t)K * M * 4 + (size_t)(gemm_slices(K, 1) + 1) * M * 16 * 4;
+  return M > 4 && M <= 7 && role != kRoleDown && K < 2048 && N / 16 > 256 && bytes <= kRowsPathMaxLds ? bytes : 0;
 }
 
 // Launch shape of k_gemm_bf16_wide: NT weight tiles per wave and NW waves that split the k chunks; nt == 0: the
@@ -1119,6 +1170,18 @@ WideCfg wide_cfg(int role, int M, int NTILES, int K) {
   return c;
 }
 
+// The form of k_gemm_bf16_rows for a k range, and for work-groups of one tile or several.
+template <int R, int ROLE, int NW, int GP, bool STREAM, bool ROWMAJOR = false>
+static auto rows_kernel(int K, bool walk) {
+  constexpr int reach = 8 * 64 * NW;       // k a work-group's threads cover with one k group each
+  constexpr bool walks = ROLE != kRoleDown && !ROWMAJOR;    // (down projections of 5..7 rows: at most 128 tiles)
+  if (walks && walk) return &k_gemm_bf16_rows<R, ROLE, NW, GP, 1, walks, STREAM, ROWMAJOR>;
+  if (R > 2 && K <= reach / 4) return &k_gemm_bf16_rows<R, ROLE, NW, 1, (R > 2 ? 4 : 1), false, STREAM, ROWMAJOR>;
+  if (R > 1 && K <= reach / 2) return &k_gemm_bf16_rows<R, ROLE, NW, 1, (R > 1 ? 2 : 1), false, STREAM, ROWMAJOR>;
+  if (GP > 1 && K <= reach) return &k_gemm_bf16_rows<R, ROLE, NW, 1, 1, false, STREAM, ROWMAJOR>;
+  return &k_gemm_bf16_rows<R, ROLE, NW, GP, 1, false, STREAM, ROWMAJOR>;
+}
+
 // Y [M, N] = X . W^T with W [N, K] as the caller has it (bf16, row-major); frag: scratch for M > 4.  Returns false,
 // launching nothing, for shapes that need the split-K kernel (few tiles with a long k; LDS).
 bool launch_gemm_rowmajor(const uint16_t* W, int N, int K, const float* X, int M, float* Y, uint4* frag, hipStream_t st) {
@@ -1131,7 +1194,7 @@ bool launch_gemm_rowmajor(const uint16_t* W, int N, int K, const float* X, int M
   const size_t rl = rows_path_lds(kRoleHead, M, N, K);
   if (rl && M <= 4) {
 #define STAIRS_ROWM(r) \
-  hipLaunchKernelGGL((k_gemm_bf16_rows<r, kRoleHead, 4, 2, false, true>), dim3(NTILES), dim3(256), rl, st, Wr, NTILES, X, K, none, K, N, e)
+  hipLaunchKernelGGL((rows_kernel<r, kRoleHead, 4, 2, false, true>(K, false)), dim3(NTILES), dim3(256), rl, st, Wr, NTILES, X, K, none, K, N, e)
     if (M == 1) STAIRS_ROWM(1);
     else if (M == 2) STAIRS_ROWM(2);
     else if (M == 3) STAIRS_ROWM(3);
@@ -1322,7 +1385,9 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
   const int S = gemm_slices(K, 1);
   const int NTILES = N / 16, KT = K / 32;
   const uint4* Wsw = static_cast<const uint4*>(W);
-  if (const size_t rl = rows_path_lds(role, M, N, K)) {
+  size_t rl = rows_path_lds(role, M, N, K);
+  if (!rl) rl = rows_many_tiles_lds(role, M, N, K);
+  if (rl) {
     // gate/up has several times more tiles than the chip has CUs: one work-group per CU that walks through its
     // share of the tiles (X block staged once, the next tile's first units requested before the epilogue, all
     // work-groups resident from the start and done together) streams better than a work-group per tile (7B, 1376
@@ -1330,7 +1395,7 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
     // work-groups on some CUs and one on others is the worst case; the unembedding's 2000 tiles and, with its
     // epilogue's loads requested early, QKV's 768 gain nothing)
     int tpw = 1;
-    if ((role == kRoleGateUp && NTILES >= 4 * 256) || (M > 4 && NTILES > 256)) tpw = (NTILES + 255) / 256;
+    if ((role == kRoleGateUp && NTILES >= 4 * 256) || (M > 4 && NTILES > 256 && K >= 2048)) tpw = (NTILES + 255) / 256;
     {
       static const int forced = [] { const char* e = getenv("STAIRS_ROWS_TPW"); return e ? atoi(e) : 0; }();
       if (forced > 0 && (role == kRoleGateUp || role == kRoleHead)) tpw = forced;    // tuning aid
@@ -1338,15 +1403,9 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
     const dim3 rgrid((NTILES + tpw - 1) / tpw);
     // (walking work-groups ask for more than half a CU's LDS, so that no CU gets two of them while another has none)
     const size_t rl_launch = tpw > 1 ? std::max(rl, (size_t)81 * 1024) : rl;
-#define STAIRS_ROWS(r, role, nw, gp)                                                                                  \
-  do {                                                                                                                 \
-  if (epi.stream_weights)                                                                                            \
-    launch_gemm_kernel(k_gemm_bf16_rows<r, role, nw, gp, true>, rgrid, dim3(64 * nw), rl_launch, st, Wsw, NTILES, X,    \
-                       ldx, nrm, K, N, epi);                                                                            \
-  else                                                                                                                 \
-    launch_gemm_kernel(k_gemm_bf16_rows<r, role, nw, gp, false>, rgrid, dim3(64 * nw), rl_launch, st, Wsw, NTILES, X,   \
-                       ldx, nrm, K, N, epi);                                                                            \
-  } while (0)
+#define STAIRS_ROWS(r, role, nw, gp)                                                                                    \
+  launch_gemm_kernel(epi.stream_weights ? rows_kernel<r, role, nw, gp, true>(K, tpw > 1) : rows_kernel<r, role, nw, gp, false>(K, tpw > 1), rgrid, \
+                     dim3(64 * nw), rl_launch, st, Wsw, NTILES, X, ldx, nrm, K, N, epi)
 #define STAIRS_ROWS_ROLE4(role, nw, gp)          \
   if (M <= 1) STAIRS_ROWS(1, role, nw, gp);      \
   else if (M == 2) STAIRS_ROWS(2, role, nw, gp); \
@@ -2505,36 +2564,49 @@ void launch_copy_probe(const void* src, void* dst, size_t bytes, hipStream_t st)
                      static_cast<const uint4*>(src), static_cast<uint4*>(dst), n);
 }
 
+// Once per device: a function's attributes belong to the device, and some 200 calls of 40 us were part of every
+// stairs_init (tens of ms for a small model's).
 hipError_t configure_kernels() {
-  hipError_t e = hipSuccess;
+  static std::mutex mu;
+  static bool done[64] = {};
+  int dev = -1;
+  hipError_t e = hipGetDevice(&dev);
+  if (e != hipSuccess) return e;
+  const bool counted = dev >= 0 && dev < 64;
+  const std::lock_guard<std::mutex> lock(mu);
+  if (counted && done[dev]) return hipSuccess;
+  std::vector<const void*> seen;             // (one kernel serves several k)
   auto optin = [&](const void* fn, size_t bytes) {
+    if (std::find(seen.begin(), seen.end(), fn) != seen.end()) return;
+    seen.push_back(fn);
     const hipError_t r = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (r != hipSuccess) e = r;
   };
-#define STAIRS_OPTIN2(r, st)                                                                       \
-  optin((const void*)k_gemm_bf16_rows<r, kRoleQKV, 4, 2, st>, kRowsPathMaxLds);                    \
-  optin((const void*)k_gemm_bf16_rows<r, kRoleGateUp, 4, 2, st>, kRowsPathMaxLdsWide);             \
-  optin((const void*)k_gemm_bf16_rows<r, kRoleHead, 4, 2, st>, kRowsPathMaxLds);                   \
-  optin((const void*)k_gemm_bf16_rows<r, kRoleWo, 8, 1, st>, kRowsPathMaxLdsWide);                 \
-  optin((const void*)k_gemm_bf16_rows<r, kRoleDown, 8, 3, st>, kRowsPathMaxLdsWide);               \
-  optin((const void*)k_gemm_bf16_rows<r, kRoleDown, 16, 1, st>, kRowsPathMaxLdsWide)
-#define STAIRS_OPTIN(r)    \
-  STAIRS_OPTIN2(r, true);  \
-  STAIRS_OPTIN2(r, false)
-  STAIRS_OPTIN(1);
-  STAIRS_OPTIN(2);
-  STAIRS_OPTIN(3);
-  STAIRS_OPTIN(4);
-#undef STAIRS_OPTIN2
-#define STAIRS_OPTIN2(r, st)                                                                       \
-  optin((const void*)k_gemm_bf16_rows<r, kRoleQKV, 4, 2, st>, kRowsPathMaxLdsWide);                \
-  optin((const void*)k_gemm_bf16_rows<r, kRoleGateUp, 4, 2, st>, kRowsPathMaxLdsWide);             \
-  optin((const void*)k_gemm_bf16_rows<r, kRoleHead, 4, 2, st>, kRowsPathMaxLdsWide);               \
-  optin((const void*)k_gemm_bf16_rows<r, kRoleDown, 8, 1, st>, kRowsPathMaxLdsWide);               \
-  optin((const void*)k_gemm_bf16_rows<r, kRoleWo, 8, 1, st>, kRowsPathMaxLdsWide)
-  STAIRS_OPTIN(5);
-  STAIRS_OPTIN(6);
-  STAIRS_OPTIN(7);
+  // (forms for k up to 2048 only where the launch asks for more than the block needs, i.e. for more than half a CU's LDS)
+#define STAIRS_OPTIN1(r, role, nw, gp, st, lds, ...) \
+  for (int K : {__VA_ARGS__}) optin((const void*)rows_kernel<r, role, nw, gp, st>(K, false), lds)
+#define STAIRS_OPTIN2(r, st, lds)                                                                           \
+  STAIRS_OPTIN1(r, kRoleQKV, 4, 2, st, lds, (r > 4 ? 2048 : 1 << 20), 1 << 20);                             \
+  STAIRS_OPTIN1(r, kRoleGateUp, 4, 2, st, kRowsPathMaxLdsWide, (r > 4 ? 2048 : 1 << 20), 1 << 20);          \
+  STAIRS_OPTIN1(r, kRoleHead, 4, 2, st, lds, (r > 4 ? 2048 : 1 << 20), 1 << 20);                            \
+  STAIRS_OPTIN1(r, kRoleWo, 8, 1, st, kRowsPathMaxLdsWide, 1024, 2048, 1 << 20);                            \
+  STAIRS_OPTIN1(r, kRoleDown, 8, (r > 4 ? 1 : 3), st, kRowsPathMaxLdsWide, 1024, 2048, 4096, 1 << 20);      \
+  STAIRS_OPTIN1((r > 4 ? 4 : r), kRoleDown, 16, 1, st, kRowsPathMaxLdsWide, 1 << 20);                       \
+  optin((const void*)rows_kernel<r, kRoleQKV, 4, 2, st>(1 << 20, true), kRowsPathMaxLdsWide);               \
+  optin((const void*)rows_kernel<r, kRoleGateUp, 4, 2, st>(1 << 20, true), kRowsPathMaxLdsWide);            \
+  optin((const void*)rows_kernel<r, kRoleHead, 4, 2, st>(1 << 20, true), kRowsPathMaxLdsWide);              \
+  optin((const void*)rows_kernel<r, kRoleWo, 8, 1, st>(1 << 20, true), kRowsPathMaxLdsWide)
+#define STAIRS_OPTIN(r, lds)    \
+  STAIRS_OPTIN2(r, true, lds);  \
+  STAIRS_OPTIN2(r, false, lds)
+  STAIRS_OPTIN(1, kRowsPathMaxLds);
+  STAIRS_OPTIN(2, kRowsPathMaxLds);
+  STAIRS_OPTIN(3, kRowsPathMaxLds);
+  STAIRS_OPTIN(4, kRowsPathMaxLds);
+  STAIRS_OPTIN(5, kRowsPathMaxLdsWide);
+  STAIRS_OPTIN(6, kRowsPathMaxLdsWide);
+  STAIRS_OPTIN(7, kRowsPathMaxLdsWide);
+#undef STAIRS_OPTIN1
 #undef STAIRS_OPTIN2
 #undef STAIRS_OPTIN
 #define STAIRS_OPTIN_WIDE(ct, nt, dp0)                                                                   \
@@ -2550,10 +2622,10 @@ hipError_t configure_kernels() {
   STAIRS_OPTIN_WIDE(1, 2, kWideDepth2); STAIRS_OPTIN_WIDE(2, 2, kWideDepth2);
   STAIRS_OPTIN_WIDE(1, 1, kWideDepth1); STAIRS_OPTIN_WIDE(2, 1, kWideDepth1);
   STAIRS_OPTIN_WIDE_(1, 1, kWideDepthChunk);
-  optin((const void*)k_gemm_bf16_rows<1, kRoleHead, 4, 2, false, true>, kRowsPathMaxLds);
-  optin((const void*)k_gemm_bf16_rows<2, kRoleHead, 4, 2, false, true>, kRowsPathMaxLds);
-  optin((const void*)k_gemm_bf16_rows<3, kRoleHead, 4, 2, false, true>, kRowsPathMaxLds);
-  optin((const void*)k_gemm_bf16_rows<4, kRoleHead, 4, 2, false, true>, kRowsPathMaxLds);
+  optin((const void*)rows_kernel<1, kRoleHead, 4, 2, false, true>(1 << 20, false), kRowsPathMaxLds);
+  optin((const void*)rows_kernel<2, kRoleHead, 4, 2, false, true>(1 << 20, false), kRowsPathMaxLds);
+  optin((const void*)rows_kernel<3, kRoleHead, 4, 2, false, true>(1 << 20, false), kRowsPathMaxLds);
+  optin((const void*)rows_kernel<4, kRoleHead, 4, 2, false, true>(1 << 20, false), kRowsPathMaxLds);
   optin((const void*)k_gemm_bf16_wide<1, 1, kWideDepth1, false, true>, kWideMaxLds);
   optin((const void*)k_gemm_bf16_wide<1, 2, kWideDepth2, false, true>, kWideMaxLds);
   optin((const void*)k_gemm_bf16_wide<2, 1, wide_depth2(kWideDepth1), false, true>, kWideMaxLds);
@@ -2573,6 +2645,7 @@ hipError_t configure_kernels() {
   optin((const void*)k_attn<128, 16, false>, 128 * 1024);
   optin((const void*)k_attn_merge<128>, kAttnMergeMaxLds);
   optin((const void*)k_attn_merge<64>, kAttnMergeMaxLds);
+  if (counted && e == hipSuccess) done[dev] = true;
   return e;
 }
 

@@ -589,6 +589,29 @@ def test_gains_of_a_short_last_chunk(d, heads):
             assert np.array_equal(lg[:n], want[:n]), k
 
 
+@pytest.mark.parametrize("d,heads,ffn", [(256, 2, 512), (512, 4, 768), (768, 6, 1024), (1024, 8, 1280), (1280, 10, 2048), (2048, 16, 2304),
+                                         (2304, 18, 4096), (4352, 34, 4352)])
+def test_rows_have_the_same_bits_in_every_staging_form(d, heads, ffn):
+    """k on both sides of the limits (512, 1024, 2048, 4096) at which 1..7 rows are staged by one, two or four threads a k group and
+    in one or more passes, and of the 4096 columns whose row statistics are requested at once: stair batches of 1..7 rows share
+    their rows' bits with one of 16 rows, which another kernel computes."""
+    w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=d, n_heads=heads, d_ffn=ffn, vocab=528),
+                           draft=dict(kind="prefix", n_layers=1), P=21, G=1)
+    target, draft = si.make_pair(w)
+    prompt = si.make_prompt(w)
+    g = np.random.default_rng([11, d])
+    for ly in target.layers:
+        ly["attn_norm"], ly["ffn_norm"] = (g.uniform(0.5, 2.0, d).astype(np.float32) for _ in range(2))
+    dr = g.integers(0, 528, 15).astype(np.int32)
+    want = None
+    with pkg.Stairs(target, draft, k_max=15, max_seq=64) as s:
+        for k in (15, 6, 5, 4, 3, 2, 1, 0):
+            s.prefill(prompt)
+            _, _, lg = s.verify_tokens(dr[:k], logits=True)
+            want = lg.copy() if want is None else want
+            assert np.array_equal(lg, want[:k + 1]), k
+
+
 @pytest.mark.parametrize("heads,P", [(16, 1020), (16, 1300), (8, 1300), (8, 2400)])
 def test_fp32_rows_do_not_depend_on_their_number_at_long_contexts(heads, P):
     """fp32, head size 64 and 128, contexts at which stair batches of a few rows go from one to four rows per work-group
