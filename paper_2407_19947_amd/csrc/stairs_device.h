@@ -108,15 +108,19 @@ __device__ __forceinline__ float half_wave_sum(float v) {      // over lanes 0 .
   return v + dpp<kDppXor1>(v);
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-  return v;
+__device__ __forceinline__ float wave_sum(float v) {           // (distance 32 first)
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  return half_wave_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
 __device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-  return v;
+  auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+  v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  v = fmaxf(v, dpp<kDppRor8>(v));
+  v = fmaxf(v, dpp<kDppRor4>(v));
+  v = fmaxf(v, dpp<kDppXor2>(v));
+  return fmaxf(v, dpp<kDppXor1>(v));
 }
 
 // Data handed from one work-group to another inside a kernel (split-K partial sums, attention chunk
