@@ -118,7 +118,7 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
     for (int t = 0; t < NT; ++t)
 #pragma unroll
       for (int i = 0; i < 4; ++i) acc[t][ct][i] = sums[t][ct][i] * rs[ct];
-  if (p.kind == kBlkSwiglu || p.kind == kBlkQKV) {
+  if constexpr (CT % 2 == 0) if (p.kind == kBlkSwiglu || p.kind == kBlkQKV) {
     // Columns 0..7 and 8..15 of a tile belong together (gate / up, the halves of rotation pairs).  The lower half of the
     // wave holds the first eight, the upper half the second: after exchanging the upper half of column tile ct with the
     // lower half of ct + 1, acc[t][ct] is the first and acc[t][ct + 1] the second member of every lane's pairs; the
@@ -152,7 +152,7 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
       return;
     }
     const int hd = p.hd, half = hd >> 1;
-    constexpr int G = NT == 4 ? 4 : 2;             // tiles whose rotation entries are requested together
+    constexpr int G = NT;                          // tiles whose rotation entries are requested together
     int2 at[CT / 2];
 #pragma unroll
     for (int c2 = 0; c2 < CT / 2; ++c2) at[c2] = p.rows[min(row0 + (2 * c2 + (up ? 1 : 0)) * 16, p.R - 1)];
@@ -205,8 +205,8 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
     }
     return;
   }
-  if (p.kind == kBlkResid) {
-    constexpr int G = NT == 4 ? 4 : 2;             // tiles whose old values are requested together
+  if constexpr (NT % 2 == 0) if (p.kind == kBlkResid) {
+    constexpr int G = NT;                          // tiles whose old values are requested together
 #pragma unroll
     for (int t0 = 0; t0 < NT; t0 += G) {
       float4 gain[G];
@@ -265,13 +265,13 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
 
 // Sums[R, N] = X[R, K] . W[N, K]^T for row blocks of up to thousands of rows: the MFMA-bound regime.
 //   W: the operand-tile layout of the decode kernels (1 KiB MFMA A operands); X: block fragments (above, 1 KiB B operands).
-//   Work-group = WF x WR waves, each 4 weight tiles x 4 column tiles of fp32 accumulators; a k-step of 32 is
-//   WF*4 + 2*WR*4 KiB-sized operands, copied from memory straight into LDS (buffer_load ... lds, 16 bytes per lane: no
-//   staging registers, and every operand enters the CU once), three k-steps deep, and read from there as they lie
+//   Work-group = WF x WR waves, each 4 weight tiles x CT column tiles of fp32 accumulators; a k-step of 32 is
+//   WF*4 + 2*WR*CT KiB-sized operands, copied from memory straight into LDS (buffer_load ... lds, 16 bytes per lane: no
+//   staging registers, and every operand enters the CU once), ST k-steps deep, and read from there as they lie
 //   (ds_read_b128, no bank conflicts: the layouts are lane order).
 //   One barrier per k-step: the wave waits for its own copies of k-step s + 1 (those of the following ones stay in
 //   flight: the waits count instructions), the barrier makes everybody's visible and says that everybody holds k-step s
-//   in registers, so its buffer takes the copies of s + 3.
+//   in registers, so its buffer takes the copies of s + ST.
 //   k pieces: the k range is cut into p.pieces parts that are summed separately (k ascending, high before low) and added
 //   up in order: by different work-groups and k_blk_reduce (gridDim.z = pieces), or one after the other by the same
 //   work-group with a second set of accumulators (PIECED).  The bits depend on p.pieces alone, not on R, the tile shape
@@ -279,7 +279,7 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
 //   What bounds it: at thousands of rows the issue of MFMAs, 1.20 .. 1.30 PFLOP/s with plain stores in launches by
 //   themselves (2047 rows, 7B projections; a library product of two 8192-wide matrices: 1.49 on the same card) and 1.07 over
 //   a profiled 2048-token prompt with its epilogues; at a few hundred the rounds of work-groups and, with one work-group on a
-//   CU, the LDS reads beside the MFMAs (0.38 us per k-step of 32 MFMAs a wave); at <= 64 rows the weights' way from memory.
+//   CU, the pace of a single wave per SIMD (0.38 us per k-step of 32 MFMAs, 0.25 of 16); at <= 64 rows the weights' way from memory.
 //   Plain stores, against the kernel before (weights through registers, 256 x 128 tiles only), 7B projections, us:
 //   2047 rows: QKV 384 -> 337, out 115 -> 112, gate/up 712 -> 603, down 297 -> 296; 333 rows: 111 -> 87, 45 -> 33,
 //   198 -> 143, 96 -> 79; 60 rows: 45 -> 28, 23 -> 19, 78 -> 48, 38 -> 29.  The SwiGLU epilogue costs less than plain stores
@@ -295,13 +295,15 @@ __device__ __forceinline__ void copy_to_lds_16(const uint4* base, uint32_t offse
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base))), 16,
                                            lane_bytes, offset, 0, 0);
 }
-constexpr int kBlkNT = 4, kBlkCT = 4, kBlkST = 3;      // weight tiles and column tiles of a wave; k-steps in LDS
-constexpr int blk_lds_bytes(int WF, int WR) { return kBlkST * (WF * kBlkNT + 2 * WR * kBlkCT) * 1024 + WR * kBlkCT * 64; }
+constexpr int kBlkNT = 4;                              // weight tiles of a wave
+constexpr int blk_lds_bytes(int WF, int WR, int CT, int ST) { return ST * (WF * kBlkNT + 2 * WR * CT) * 1024 + WR * CT * 64; }
 
-template <int WF, int WR, bool PIECED>
+//   CT: column tiles of a wave, ST: k-steps in LDS.  4 and 3 for many rows (24 KiB a k-step); 2 and 4 (16 KiB) where half the
+//   rows a work-group make the rounds come out or all CUs have work: see kBlkShapes.
+template <int WF, int WR, int CT, int ST, bool PIECED>
 __global__ __launch_bounds__(64 * WF * WR) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks) {
-  constexpr int NT = kBlkNT, CT = kBlkCT, ST = kBlkST;
+  constexpr int NT = kBlkNT;
   constexpr int NW = WF * WR, AT = WF * NT, BT = 2 * WR * CT, STAGE = (AT + BT) * 64;   // uint4 per LDS stage
   constexpr int PER = (AT + BT) / NW;                                                   // copies per wave and k-step
   static_assert(AT % NW == 0 && BT % NW == 0 && (ST - 1) * PER < 64, "whole copies per wave, countable by vmcnt");
@@ -447,6 +449,14 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
       read(y, rbuf);
     }
     multiply(x);
+    if constexpr (i < ST - 1 && CT == 2) {             // (with 4 column tiles it spills)
+#pragma unroll
+      for (int q = 0; q < READS; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, MFMAS / READS, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, MFMAS % READS, 0);
+    }
     advance();
     if constexpr (i < ST - 1) self(self, std::integral_constant<int, i + 1>{}, y, x);
   };
@@ -494,52 +504,70 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
   }
 }
 
-// The k pieces of a launch with few rows added up in order, then the launch's epilogue: a wave takes two weight tiles x
-// two column tiles.
+// The k pieces of a launch with few rows added up in order, then the launch's epilogue: a wave takes two weight tiles x two
+// column tiles or, where that leaves SIMDs without a wave, the two its epilogue combines; up to four pieces are requested
+// together.  Bound by round trips (192 rows, 128 tiles, 4 / 8 pieces with the product: 17.4 -> 16.3 / 29.6 -> 28.5 us; 48 tiles
+// of 768: 10.9 -> 10.4).
+template <int NT, int CT>
 __global__ __launch_bounds__(256) void k_blk_reduce(BlkGemm p, const float* __restrict__ part) {
   const int lane = threadIdx.x & 63, g = lane >> 4, j = lane & 15;
   const int ntiles = p.NTILES - p.tile_first, cts = (p.R + 15) >> 4;
-  const int t0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * 2, ct0 = blockIdx.y * 2;
+  const int t0 = (blockIdx.x * 4 + (threadIdx.x >> 6)) * NT, ct0 = blockIdx.y * CT;
   if (t0 >= ntiles) return;                            // (whole waves; no barriers)
   const float4* src = reinterpret_cast<const float4*>(part) + lane;
-  f32x4 acc[2][2];
-  for (int z = 0; z < p.pieces; ++z)
+  f32x4 acc[NT][CT];
+  for (int z0 = 0; z0 < p.pieces; z0 += 4) {
+    float4 v[4][NT][CT];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int ct = 0; ct < 2; ++ct) {
-        const float4 v = src[(((size_t)z * ntiles + min(t0 + t, ntiles - 1)) * cts + min(ct0 + ct, cts - 1)) * 64];
-        const f32x4 u = {v.x, v.y, v.z, v.w};
-        acc[t][ct] = z == 0 ? u : acc[t][ct] + u;
-      }
-  float rs[2] = {1.f, 1.f};
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct)
+          v[i][t][ct] = src[(((size_t)min(z0 + i, p.pieces - 1) * ntiles + min(t0 + t, ntiles - 1)) * cts + min(ct0 + ct, cts - 1)) * 64];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (z0 + i < p.pieces)
+#pragma unroll
+        for (int t = 0; t < NT; ++t)
+#pragma unroll
+          for (int ct = 0; ct < CT; ++ct) {
+            const f32x4 u = {v[i][t][ct].x, v[i][t][ct].y, v[i][t][ct].z, v[i][t][ct].w};
+            acc[t][ct] = z0 + i == 0 ? u : acc[t][ct] + u;
+          }
+  }
+  float rs[CT];
   const int row0 = ct0 * 16 + j;
-  if (p.ssq)
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct) rs[ct] = blk_row_rstd(p, min(row0 + ct * 16, p.R - 1), g, 16, 32);
-  blk_epilogue<2, 2>(p, acc, p.tile_first + t0, row0, g, rs);
+  for (int ct = 0; ct < CT; ++ct) rs[ct] = p.ssq ? blk_row_rstd(p, min(row0 + ct * 16, p.R - 1), g, 16, 32) : 1.f;
+  blk_epilogue<NT, CT>(p, acc, p.tile_first + t0, row0, g, rs);
 }
 
-// Tile shapes: features x rows of a work-group (two fit a CU), and the microseconds a k-step takes with one work-group on
-// the CU and with two (7B and 1B projections, 60 .. 2047 rows).  Shapes with larger wave tiles (256 x 256 on 8 waves,
-// 256 x 128 and 192 x 128 on 4) were no faster at 2047 rows (7B gate/up 588, 633 and 617 us against 602) and lose to
-// these wherever rounds of work-groups do not come out even.
-struct BlkShape { int feat, rows; };
-constexpr int kBlkShapeCount = 2;
-constexpr BlkShape kBlkShapes[kBlkShapeCount] = {{128, 128}, {256, 64}};
-constexpr float kBlkOne = 0.38f, kBlkTwo = 0.84f;
+// Tile shapes: features x rows of a work-group (two fit a CU), and the microseconds of a k-step with one work-group on the CU
+// and with two: fitted to 17 projections of the 125M, 1B, 7B and wide encoder widths at 12 row counts from 40 to 2047, every
+// shape and way of summing timed.  The third shape does half the work a step of the others in 0.27 (0.48 for two) of a
+// microsecond where they take 0.44 (0.84): it wins wherever it puts work on more CUs or the rounds come out better (us, the best
+// of the other two in brackets: 192 rows, 6144 x 2048 22.5 (25.5); 128 rows, 16384 x 2048 24.4 (32.8), 16384 x 1024 15.7
+// (21.4), 12288 x 4096 41.2 (44.4); 64 rows, 32000 x 2048 27.9 (36.6); 333 rows, 6144 x 768 15.1 (16.7)).  Shapes with larger
+// wave tiles (256 x 256 on 8 waves, 256 x 128 and 192 x 128 on 4) were no faster at 2047 rows (7B gate/up 588, 633 and 617 us
+// against 602).  Two k-steps for each barrier (rings of two to four pairs) were slower in every shape (64 rows, 2048 x 8192
+// in one piece: 64 -> 77..83 us), deeper rings no faster.
+struct BlkShape { int feat, rows; float one, two; };
+// (numbers: bit 0 the orientation, bit 1 half the size; the half of 128 x 128 is not built)
+constexpr int kBlkShapeCount = 4;
+constexpr BlkShape kBlkShapes[kBlkShapeCount] = {{128, 128, 0.435f, 0.84f}, {256, 64, 0.434f, 0.839f}, {0, 0, 0.f, 0.f}, {128, 64, 0.273f, 0.477f}};
 
 // floats the pieces of a split launch take
 static size_t blk_part_floats(const BlkGemm& p) { return (size_t)p.pieces * ((p.R + 15) / 16 * 16) * ((p.NTILES - p.tile_first) * 16); }
 
-// The kernel's prologue requests the first kBlkST k-steps of its piece unasked and its loop ends on the last kBlkST + 1: a
+// The kernel's prologue requests the first ST (3 or 4) k-steps of its piece unasked and its loop ends on the last ST + 1: a
 // piece shorter than that would copy k-steps that are not its own, at the end of the range operands past the matrix (the
 // copies carry no bounds).  K is whole units of the weight layout (256 k); pieces end at ksteps * i / pieces rounded down
 // to even, which moves an end by less than two: all of them have 8 k-steps exactly if 8 * pieces <= ksteps.
 bool blk_pieces_fit(int K, int pieces) { return K >= 256 && K % 256 == 0 && pieces >= 1 && pieces <= K / 256; }
 
 hipError_t launch_blk_gemm_as(int shape, bool split, const BlkGemm& p, hipStream_t st, float* part, size_t part_floats) {
-  if (shape < 0 || shape >= kBlkShapeCount || p.R < 1 || p.RT * 16 < p.R || p.tile_first < 0 || p.tile_first >= p.NTILES ||
+  if (shape < 0 || shape >= kBlkShapeCount || !kBlkShapes[shape].feat || p.R < 1 || p.RT * 16 < p.R || p.tile_first < 0 || p.tile_first >= p.NTILES ||
       !blk_pieces_fit(p.K, p.pieces))
     return hipErrorInvalidValue;
   const BlkShape& b = kBlkShapes[shape];
@@ -549,16 +577,21 @@ hipError_t launch_blk_gemm_as(int shape, bool split, const BlkGemm& p, hipStream
   const int blocks = FB * RB, per_xcd = (blocks + 7) / 8;
   const dim3 grid(per_xcd * 8, 1, split ? p.pieces : 1), block(256);
   float* dst = split ? part : nullptr;
-#define STAIRS_BLK(WF, WR, PIECED) \
-  hipLaunchKernelGGL((k_gemm_bf16_block<WF, WR, PIECED>), grid, block, blk_lds_bytes(WF, WR), st, p, dst, RB, per_xcd, blocks)
+#define STAIRS_BLK(WF, WR, CT, ST)                                                                                        \
+  hipLaunchKernelGGL((pieced ? k_gemm_bf16_block<WF, WR, CT, ST, true> : k_gemm_bf16_block<WF, WR, CT, ST, false>), grid, block, \
+                     blk_lds_bytes(WF, WR, CT, ST), st, p, dst, RB, per_xcd, blocks)
   const bool pieced = p.pieces > 1 && !split;
-  if (shape == 0) {
-    if (pieced) STAIRS_BLK(2, 2, true); else STAIRS_BLK(2, 2, false);
-  } else {
-    if (pieced) STAIRS_BLK(4, 1, true); else STAIRS_BLK(4, 1, false);
-  }
+  if (shape == 0) STAIRS_BLK(2, 2, 4, 3);
+  else if (shape == 1) STAIRS_BLK(4, 1, 4, 3);
+  else STAIRS_BLK(2, 2, 2, 4);
 #undef STAIRS_BLK
-  if (split) hipLaunchKernelGGL(k_blk_reduce, dim3((N / 16 + 7) / 8, (p.R + 31) / 32), dim3(256), 0, st, p, part);
+  if (split) {
+    // (two by two tiles where that leaves every SIMD a wave: 333 rows, 768 tiles 92 against 100 us by halves)
+    const int cts = (p.R + 15) / 16;
+    if (N / 16 * cts >= 4096) hipLaunchKernelGGL((k_blk_reduce<2, 2>), dim3((N / 16 + 7) / 8, (p.R + 31) / 32), dim3(256), 0, st, p, part);
+    else if (p.kind == kBlkResid) hipLaunchKernelGGL((k_blk_reduce<2, 1>), dim3((N / 16 + 7) / 8, cts), dim3(256), 0, st, p, part);
+    else hipLaunchKernelGGL((k_blk_reduce<1, 2>), dim3((N / 16 + 3) / 4, (p.R + 31) / 32), dim3(256), 0, st, p, part);
+  }
   return hipSuccess;
 }
 
@@ -575,8 +608,10 @@ int blk_pieces(int K) {
 }
 
 // The tile shape and the way the pieces are summed, by a model of the launch's time: rounds of work-groups over the 256
-// CUs, each k-step at the rate of the shape's occupancy, the matrix at the rate memory delivers it, and for a split
-// launch the pieces' way through memory and the second kernel.
+// CUs, each k-step at the rate of the shape's occupancy (a CU with two work-groups sets the pace as soon as there is one; a last
+// round of few is partly hidden behind the one before), the matrix at the rate memory delivers it, and for a split launch the
+// pieces' way through memory and the second kernel.  Over the launches kBlkShapes was fitted to the choice costs 1 % against
+// the best of all; two shapes and the model before 12 %.
 hipError_t launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t part_floats) {
   p.pieces = pieced ? blk_pieces(p.K) : 1;
   const int N = (p.NTILES - p.tile_first) * 16, ksteps = p.K / 32;
@@ -585,15 +620,20 @@ hipError_t launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, 
   float best_us = 1e30f;
   for (int s = 0; s < kBlkShapeCount; ++s) {
     const BlkShape& b = kBlkShapes[s];
+    if (!b.feat) continue;
     const int blocks = ((N + b.feat - 1) / b.feat) * ((p.R + b.rows - 1) / b.rows);
     for (int split = 0; split < 2; ++split) {
       if (split && (p.pieces == 1 || !part || blk_part_floats(p) > part_floats)) continue;
       const int wgs = split ? blocks * p.pieces : blocks, full = wgs / 512, rem = wgs - full * 512;
-      const float rounds = full * kBlkTwo + (rem == 0 ? 0.f : rem <= 256 ? kBlkOne : kBlkOne + (kBlkTwo - kBlkOne) * (rem - 256) / 256);
+      float rounds = full * b.two;
+      if (rem > 256) rounds += b.one + (b.two - b.one) * (0.55f + 0.45f * (rem - 256) / 256);
+      else if (rem > 0) rounds += full > 0 ? 0.74f * b.one : b.one;
       float us = rounds * (split ? (float)ksteps / p.pieces : (float)ksteps);
-      us = std::max(us, (float)N * p.K * 2 / 5.5e6f);
-      if (split) us += 3.f + (2.f * p.pieces + 1.f) * p.R * N * 4 / 8e6f;
-      us += 0.005f * blocks;                // equal rounds: fewer blocks read fewer operands (192 rows, 1024 tiles: 34.6 -> 32.9 us)
+      us = std::max(us, (float)N * p.K * 2 / 5.9e6f);
+      if (split) us += 1.f + (2.f * p.pieces + 1.f) * p.R * N * 4 / 4.5e6f;
+      us += 0.001f * blocks;                // (equal rounds: fewer blocks read fewer operands)
+      // (the first two shapes are equal but for this: 2047 rows, 4096 features 122 / 298 us as squares, 125 / 303 the other way)
+      if (s == 0 && N <= 4096 && p.pieces == 1) us *= 0.98f;
       if (us < best_us) {
         best_us = us;
         best = s;
@@ -748,10 +788,13 @@ hipError_t configure_block_kernels() {
     const hipError_t r = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     if (r != hipSuccess) e = r;
   };
-  optin((const void*)k_gemm_bf16_block<2, 2, false>, blk_lds_bytes(2, 2));
-  optin((const void*)k_gemm_bf16_block<2, 2, true>, blk_lds_bytes(2, 2));
-  optin((const void*)k_gemm_bf16_block<4, 1, false>, blk_lds_bytes(4, 1));
-  optin((const void*)k_gemm_bf16_block<4, 1, true>, blk_lds_bytes(4, 1));
+#define STAIRS_OPTIN_BLK(WF, WR, CT, ST)                                                        \
+  optin((const void*)k_gemm_bf16_block<WF, WR, CT, ST, true>, blk_lds_bytes(WF, WR, CT, ST));   \
+  optin((const void*)k_gemm_bf16_block<WF, WR, CT, ST, false>, blk_lds_bytes(WF, WR, CT, ST))
+  STAIRS_OPTIN_BLK(2, 2, 4, 3);
+  STAIRS_OPTIN_BLK(4, 1, 4, 3);
+  STAIRS_OPTIN_BLK(2, 2, 2, 4);
+#undef STAIRS_OPTIN_BLK
   return e;
 }
 

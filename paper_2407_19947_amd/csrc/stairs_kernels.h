@@ -277,7 +277,7 @@ struct BlkGemm {
 // part (part_floats floats): scratch that lets different work-groups take the pieces.
 // hipErrorInvalidValue, nothing launched: a shape the kernel does not take (launch_blk_gemm_as).
 hipError_t launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t part_floats);
-// The same with the tile shape (0: 128 features x 128 rows, 1: 256 x 64) and the way the p.pieces are summed (split:
+// The same with the tile shape (0: 128 features x 128 rows, 1: 256 x 64, 3: 128 x 64) and the way the p.pieces are summed (split:
 // different work-groups, through part) given by the caller; results do not depend on either.
 hipError_t launch_blk_gemm_as(int shape, bool split, const BlkGemm& p, hipStream_t st, float* part, size_t part_floats);
 int blk_pieces(int K);                          // pieces of a pieced launch

@@ -120,6 +120,36 @@ def _cxx(name, restype, *argtypes):
     return f
 
 
+@pytest.mark.parametrize("R", [1, 63, 64, 65, 200, 1025])
+@pytest.mark.parametrize("K,pieces", [(256, 1), (768, 3), (1280, 4), (2048, 4), (11008, 10)])
+def test_small_block_gemm_shape_has_the_bits_of_the_large_one(K, pieces, R):
+    """The 128 x 64 shape, whose ring holds four k-steps, against 256 x 64: pieces of 8 k-steps, the shortest there are (256, 768,
+    2048 in 8), of 10 (1280) and of unequal length (11008), one piece beyond 1024 rows, rows around its tile."""
+    import torch
+    assert _cxx("_ZN6stairs17configure_kernelsEv", C.c_int)() == 0
+    launch = _cxx("_ZN6stairs18launch_blk_gemm_asEibRKNS_7BlkGemmEP12ihipStream_tPfm", C.c_int, C.c_int, C.c_bool,
+                  C.POINTER(_BlkGemm), C.c_void_p, C.c_void_p, C.c_size_t)
+    NT, RT = 19, (R + 127) // 128 * 8
+    g = torch.Generator().manual_seed(K + R)
+    W = (torch.randn(NT * 16 * K, generator=g) * 0.1).to(torch.bfloat16).cuda()
+    X = torch.randn(K // 32 * RT * 1024, generator=g).to(torch.bfloat16).cuda()
+    for P in ((1,) if R > 1024 else {pieces, min(8, K // 256)}):
+        part = torch.empty(P * ((R + 15) // 16 * 16) * NT * 16, device="cuda")
+        outs = []
+        for shape, split in ((1, False), (3, False), (3, True)):
+            if split and P == 1:
+                continue
+            y = torch.full((R, NT * 16), float("nan"), device="cuda")
+            p = _BlkGemm(W=W.data_ptr(), NTILES=NT, K=K, XF=X.data_ptr(), RT=RT, R=R, out=y.data_ptr(), ldo=NT * 16, pieces=P)
+            torch.cuda.synchronize()
+            assert launch(shape, split, C.byref(p), None, part.data_ptr(), part.numel()) == 0
+            torch.cuda.synchronize()
+            outs.append(y)
+        assert torch.isfinite(outs[0]).all()
+        for y in outs[1:]:
+            assert torch.equal(y, outs[0]), P
+
+
 @pytest.mark.parametrize("R", [17, 65, 129, 256])
 @pytest.mark.parametrize("K,pieces", [(768, 3), (2048, 4), (8192, 8), (11008, 10)])
 def test_block_gemm_forms_have_the_same_bits(K, pieces, R):
