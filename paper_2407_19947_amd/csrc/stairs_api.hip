@@ -443,10 +443,11 @@ size_t max_matrix_bytes(const stairs_model_cfg* m) {
 }
 
 size_t max_partial_floats(const stairs_model_cfg* m) {
-  if (m->dtype != STAIRS_DTYPE_BF16) return 0;         // (only split-K writes partial sums)
+  if (m->dtype != STAIRS_DTYPE_BF16) return 0;         // (only bf16 projections leave partial sums in memory)
   const size_t d = m->d_model, f = m->d_ffn, V = m->vocab;
   const size_t sd = gemm_slices(m->d_model, 1), sf = gemm_slices(m->d_ffn, 1);
-  return kMaxRows * std::max({sd * 3 * d, sd * 2 * f, sf * d, sd * V});
+  // (split-K: a chunk's sums of up to 32 rows each; launch_gemm_shared: a pair's of up to 64)
+  return kMaxRows * std::max({(sd + 1) * 3 * d, (sd + 1) * 2 * f, (sf + 1) * d, (sd + 1) * V});
 }
 
 // One forward of `M` rows at positions pos..pos+M-1 whose token ids are tokens[pos..pos+M-1].

@@ -644,6 +644,419 @@ hipError_t launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, 
   return launch_blk_gemm_as(best, best_split, p, st, part, part_floats);
 }
 
+// ---------------------------------------------------------------------------------------
+// 33..64 rows of several sequences, in the decode kernels' order of additions
+// ---------------------------------------------------------------------------------------
+// The contract of k_gemm_bf16_wide (decode fragments in, decode epilogue out, the same bits) with the loop of the block
+// GEMM: 128 features x 64 rows a work-group, weights and fragments copied into LDS once and read from there by the two waves
+// that need them.  In k_gemm_bf16_wide a wave that owns few tiles pulls 8 KiB of fragments through the CU's vector memory path
+// for 1..4 KiB of weights, and wider tiles do not fit the chunk sums into LDS; here the sums of a 512-wide chunk, of the chunk
+// in front of it and of the pairs so far are three sets of accumulators.  A launch of few tiles gives each pair of chunks to a
+// work-group of its own (SPLIT) and a second kernel adds the pairs up.
+// us at 64 rows, k_gemm_bf16_wide in brackets, in a layer: 7B QKV 32.6 (39), out 16.7 (20.8), gate/up 45 (66), down 30.6 (48.5),
+// unembedding 55 (80); 1B 16.7 (21.6), 12 (13.2), 22.4 (26.1), 18.8 (35.3), 31 (41).  A whole layer: 7B 191 -> 140, 1B 107 -> 84,
+// 125M 67 -> 56.  What bounds it: the weights' way from memory in the large projections (gate/up: 180 MB), else the pace of one
+// wave per SIMD (0.25 us a k-step) and, in split launches, the second kernel.
+// A wave's NT weight tiles x CT column tiles as the MFMA leaves them (see blk_epilogue), rs: the rows' 1/rms.
+template <int NT, int CT>
+__device__ __forceinline__ void shared_epilogue(int role, const GemmEpi& epi, int M, int N, const f32x4 (&sums)[NT][CT], int tile0, int row0,
+                                                int g, const float (&rs)[CT]) {
+  const int NTILES = N >> 4;
+  float acc[NT][CT][4];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct)
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) acc[t][ct][i] = sums[t][ct][i] * rs[ct];
+  if constexpr (CT % 2 == 0) {
+    if (role == kRoleGateUp || role == kRoleQKV) {       // pairs at columns (j, j + 8): exchanged as in blk_epilogue
+      const bool up = g >= 2;
+      g &= 1;
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+#pragma unroll
+        for (int ct = 0; ct < CT; ct += 2)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[t][ct][i]), __float_as_uint(acc[t][ct + 1][i]), false, false);
+            acc[t][ct][i] = __uint_as_float(r[0]);
+            acc[t][ct + 1][i] = __uint_as_float(r[1]);
+          }
+      const int d = N / 3, hd = epi.hd, half = hd >> 1, hd_log = 31 - __builtin_clz(hd), part_tiles = NTILES / 3;
+#pragma unroll
+      for (int ct = 0; ct < CT; ct += 2) {
+        const int row = row0 + (ct + (up ? 1 : 0)) * 16;
+        if (row >= M) continue;
+        if (role == kRoleGateUp) {
+#pragma unroll
+          for (int t = 0; t < NT; ++t) {
+            const float (&a)[4] = acc[t][ct], (&b)[4] = acc[t][ct + 1];
+            const int col = (tile0 + t) * 8 + 4 * g;
+            if (tile0 + t < NTILES) {
+              const float4 o = make_float4(swiglu(a[0], b[0]), swiglu(a[1], b[1]), swiglu(a[2], b[2]), swiglu(a[3], b[3]));
+              *reinterpret_cast<float4*>(epi.out + (size_t)row * (N >> 1) + col) = o;
+              if (epi.frag_out) store_frag4(epi.frag_out, row, col, o, nullptr);
+            }
+          }
+          continue;
+        }
+        const int pos = pos_of(epi.pos, row);
+        const size_t slot = (size_t)slot_of(epi.pos, row) * epi.kv_slot_stride;
+        float4 cs[NT][2];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const int w = min(tile0 + t, NTILES - 1) * 16 % d & (hd - 1);
+          const float4* src = reinterpret_cast<const float4*>(epi.rope_cs + row * 64 + (w >> 4) * 8 + 4 * g);
+          cs[t][0] = src[0];
+          cs[t][1] = src[1];
+        }
+        if (pos < 0) continue;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const int tile = tile0 + t;
+          if (tile >= NTILES) continue;
+          const float (&a)[4] = acc[t][ct], (&b)[4] = acc[t][ct + 1];
+          const int part = (tile >= part_tiles) + (tile >= 2 * part_tiles), c = (tile - part * part_tiles) * 16;
+          const int h = c >> hd_log, w = c & (hd - 1);
+          const size_t head = slot + (size_t)h * epi.cap * hd;
+          if (part == 2) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              store_kv(epi.Vc + head + v_cache_off(pos, w + 4 * g + i, hd), a[i]);
+              store_kv(epi.Vc + head + v_cache_off(pos, w + 8 + 4 * g + i, hd), b[i]);
+            }
+            continue;
+          }
+          const int e = (w >> 4) * 8 + 4 * g;
+          const float2 r0 = rope_rotate(a[0], b[0], make_float2(cs[t][0].x, cs[t][0].y)), r1 = rope_rotate(a[1], b[1], make_float2(cs[t][0].z, cs[t][0].w));
+          const float2 r2 = rope_rotate(a[2], b[2], make_float2(cs[t][1].x, cs[t][1].y)), r3 = rope_rotate(a[3], b[3], make_float2(cs[t][1].z, cs[t][1].w));
+          if (part == 0) {
+            float* dst = epi.out + (size_t)row * d + h * hd + e;
+            *reinterpret_cast<float4*>(dst) = make_float4(r0.x, r1.x, r2.x, r3.x);
+            *reinterpret_cast<float4*>(dst + half) = make_float4(r0.y, r1.y, r2.y, r3.y);
+          } else {
+            store_kv4(epi.Kc + head + k_cache_off(pos, e, hd), make_float4(r0.x, r1.x, r2.x, r3.x));
+            store_kv4(epi.Kc + head + k_cache_off(pos, e + half, hd), make_float4(r0.y, r1.y, r2.y, r3.y));
+          }
+        }
+      }
+      return;
+    }
+  }
+  if (role == kRoleHead) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        const int row = row0 + ct * 16, col = (tile0 + t) * 16 + 4 * g;
+        const float (&a)[4] = acc[t][ct];
+        if (row >= M || tile0 + t >= NTILES) continue;
+        const bool relu = epi.act == kActRelu;
+        const float4 v = relu ? make_float4(fmaxf(a[0], 0.f), fmaxf(a[1], 0.f), fmaxf(a[2], 0.f), fmaxf(a[3], 0.f)) : make_float4(a[0], a[1], a[2], a[3]);
+        *reinterpret_cast<float4*>(epi.out + (size_t)row * N + col) = v;
+        if (epi.frag_out) store_frag4(epi.frag_out, row, col, v, epi.frag_gain);
+      }
+    return;
+  }
+  float4 old[NT][CT];                                    // residual-writing roles
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct)
+      old[t][ct] = *reinterpret_cast<const float4*>(epi.out + (size_t)min(row0 + ct * 16, M - 1) * N + min(tile0 + t, NTILES - 1) * 16 + 4 * g);
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      const int row = row0 + ct * 16, col = (tile0 + t) * 16 + 4 * g;
+      const float (&a)[4] = acc[t][ct];
+      const float4 o = old[t][ct], v = make_float4(o.x + a[0], o.y + a[1], o.z + a[2], o.w + a[3]);
+      const bool ok = row < M && tile0 + t < NTILES;
+      if (ok) {
+        *reinterpret_cast<float4*>(epi.out + (size_t)row * N + col) = v;
+        if (epi.frag_out) store_frag4(epi.frag_out, row, col, v, epi.frag_gain);
+      }
+      float ss = sumsq4(v.x, v.y, v.z, v.w);
+      ss += __shfl_xor(ss, 16);
+      ss += __shfl_xor(ss, 32);
+      if (ok && g == 0) epi.ssq_out[(size_t)row * NTILES + tile0 + t] = ss;
+    }
+}
+
+// s_rstd[i] = 1/rms of row row0 + i, i < rows, by 4 waves: half a wave per row as in rows_rstd, the partials of four rows
+// requested together
+__device__ __forceinline__ void shared_rstd(RowNorm nrm, int row0, int rows, int K, float* s_rstd) {
+  const int pl = threadIdx.x & 31, hw = threadIdx.x >> 5, M = rows;
+  nrm.ssq_part += (size_t)row0 * nrm.ssq_n;
+#pragma unroll 1
+  for (int m0 = hw; m0 < M; m0 += 32) {
+    float v[4][8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const float* sp = nrm.ssq_part + (size_t)min(m0 + 8 * r, M - 1) * nrm.ssq_n;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[r][i] = sp[min(pl + 32 * i, nrm.ssq_n - 1)];
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int m = m0 + 8 * r;
+      const float* sp = nrm.ssq_part + (size_t)min(m, M - 1) * nrm.ssq_n;
+      float ss = 0.f;
+#pragma unroll
+      for (int i = 0; i < 8; ++i) ss += (pl + 32 * i < nrm.ssq_n) ? v[r][i] : 0.f;
+      for (int p0 = pl + 256; p0 < nrm.ssq_n; p0 += 256) {
+        float u[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) u[i] = (p0 + 32 * i < nrm.ssq_n) ? sp[p0 + 32 * i] : 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ss += u[i];
+      }
+      ss = half_wave_sum(ss);
+      if (pl == 0 && m < M) s_rstd[m] = 1.0f / sqrtf(ss / (float)K + nrm.eps);
+    }
+  }
+}
+
+constexpr int kShST = 4, kShLds = kShST * 16 * 1024;
+template <bool STREAM>
+__device__ __forceinline__ void copy_weights_to_lds(const uint4* base, uint32_t offset, uint4* lds_base, uint32_t lane_bytes) {
+  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(base), 0, 0xFFFFFFFFu, 0x00027000);
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(lds_base))), 16,
+                                           lane_bytes, offset, 0, STREAM ? 2 : 0);
+}
+template <bool SPLIT, bool STREAM>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
+void k_gemm_bf16_shared(const uint4* __restrict__ W, int NTILES, const uint4* __restrict__ XF, int M, RowNorm nrm, int K, int N, int role,
+                        float* part, GemmEpi epi) {
+  constexpr int NT = 4, CT = 2, ST = kShST, AT = 8, STAGE = 16 * 64, PER = 4;   // (a stage: 8 weight tiles, 2 x 4 fragments)
+  extern __shared__ uint4 lds[];
+  __shared__ float s_rstd[64];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int fw = wave & 1, rw = wave >> 1, j = lane & 15, g = lane >> 4;
+  const int fb = blockIdx.x, ksteps = K >> 5;
+  const int ks0 = SPLIT ? (int)blockIdx.z * 32 : 0, ks_end = SPLIT ? min(ksteps, ks0 + 32) : ksteps;   // (32 k-steps: a pair of chunks)
+  const int full_chunks = ksteps >> 4;                   // (the last chunk may be half as long)
+  uint32_t off[PER];                                     // bytes from the chunk's (weights) or the k-step's (fragments) start
+#pragma unroll
+  for (int q = 0; q < 2; ++q) off[q] = (uint32_t)min(fb * AT + wave + q * 4, NTILES - 1) * (kSliceUnits * 8 * 1024u);
+  off[2] = wave * 1024u;
+  off[3] = (uint32_t)(kFragHalfU4 * 16) + wave * 1024u;
+  int rs_ = ks0;                                         // the next k-step
+  const uint4* wp = W + (size_t)(ks0 >> 4) * NTILES * (kSliceUnits * 8) * 64;
+  const uint4* xp = XF + (size_t)ks0 * 256 + (size_t)(ks0 >> 4) * kFragChunkPad;
+  const size_t wskip = (size_t)(NTILES - 1) * (kSliceUnits * 8) * 64;
+  auto request = [&](int buf) {
+    const int half = __builtin_amdgcn_readfirstlane((rs_ >> 4) >= full_chunks ? 1 : 0);
+    uint4* dst = lds + buf * STAGE + wave * 64;
+#pragma unroll
+    for (int q = 0; q < 2; ++q) copy_weights_to_lds<STREAM>(wp, off[q] >> half, dst + q * 256, lane * 16);
+#pragma unroll
+    for (int q = 2; q < PER; ++q) copy_to_lds_16(xp, off[q], dst + q * 256, lane * 16);
+    ++rs_;
+    wp += 64;
+    xp += 256;
+    if ((rs_ & 15) == 0) {
+      wp += wskip;
+      xp += kFragChunkPad;
+    }
+  };
+  f32x4 acc[NT][CT], first[NT][CT], tot[NT][CT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[t][ct] = tot[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  struct Frags {
+    bf16x8 a[NT], h[CT], l[CT];
+  };
+  auto read = [&](Frags& f, int buf) {
+    const uint4* sa = lds + buf * STAGE + fw * NT * 64 + lane;
+    const uint4* sb = lds + buf * STAGE + (AT + rw * CT * 2) * 64 + lane;
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      f.h[ct] = __builtin_bit_cast(bf16x8, sb[(ct * 2) * 64]);
+      f.l[ct] = __builtin_bit_cast(bf16x8, sb[(ct * 2 + 1) * 64]);
+    }
+#pragma unroll
+    for (int t = 0; t < NT; ++t) f.a[t] = __builtin_bit_cast(bf16x8, sa[t * 64]);
+  };
+  auto multiply = [&](const Frags& f) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[t], f.h[ct], acc[t][ct], 0, 0, 0);
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[t], f.l[ct], acc[t][ct], 0, 0, 0);
+    }
+  };
+  // in front of k-step ks, where a chunk ends: the first of a pair is put aside, the second closes the pair
+  auto fold = [&](int ks) {
+    if ((ks & 15) || ks == ks0) return;
+    const bool second = (ks & 16) == 0;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) {
+        if (second) tot[t][ct] += first[t][ct] + acc[t][ct];
+        else first[t][ct] = acc[t][ct];
+        acc[t][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+  };
+  Frags f0, f1;
+#pragma unroll
+  for (int i = 0; i < ST; ++i) request(i);               // (a range has at least 8 k-steps)
+  const bool normed = !SPLIT && nrm.gain && nrm.ssq_part;
+  if (normed) shared_rstd(nrm, 0, M, K, s_rstd);            // (while the first copies are on their way; read behind barriers)
+  wait_copies_and_sync<(ST - 1) * PER>();
+  read(f0, 0);
+  int s = ks0, rbuf = 1, wbuf = 0;                       // the loop of k_gemm_bf16_block
+  auto advance = [&]() {
+    rbuf = rbuf + 1 == ST ? 0 : rbuf + 1;
+    wbuf = wbuf + 1 == ST ? 0 : wbuf + 1;
+    ++s;
+  };
+  constexpr int MFMAS = 2 * NT * CT, READS = NT + 2 * CT;
+  auto step = [&](const Frags& cur, Frags& next) {
+    wait_copies_and_sync<(ST - 2) * PER>();
+    request(wbuf);
+    read(next, rbuf);
+    multiply(cur);
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
+#pragma unroll
+    for (int i = 0; i < READS; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x008, MFMAS - PER - READS, 0);
+    advance();
+  };
+  while (s + ST < ks_end) {                              // (an even number of k-steps, ST even: ST are left)
+    fold(s);                                             // (chunks begin at even k-steps, and none among the last 7)
+    step(f0, f1);
+    step(f1, f0);
+  }
+  auto last = [&](auto self, auto I, Frags& x, Frags& y) -> void {
+    constexpr int i = decltype(I)::value;
+    if constexpr (i < ST - 1) {
+      wait_copies_and_sync<(ST - 2 - i) * PER>();
+      read(y, rbuf);
+    }
+    multiply(x);
+    if constexpr (i < ST - 1) {
+#pragma unroll
+      for (int q = 0; q < READS; ++q) {
+        __builtin_amdgcn_sched_group_barrier(0x008, MFMAS / READS, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+    }
+    advance();
+    if constexpr (i < ST - 1) self(self, std::integral_constant<int, i + 1>{}, y, x);
+  };
+  last(last, std::integral_constant<int, 0>{}, f0, f1);
+  const bool paired = ((ks_end - 1) >> 4) & 1;           // the last chunk is the second of a pair
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) {
+      if (paired) acc[t][ct] = first[t][ct] + acc[t][ct];
+      tot[t][ct] += acc[t][ct];
+    }
+  const int tile0 = fb * AT + fw * NT;
+  if constexpr (SPLIT) {                                 // the pair's sums as they lie, [pair][tile][column tile][lane]
+    const int cts = (M + 15) >> 4;
+    float4* dst = reinterpret_cast<float4*>(part) + ((size_t)blockIdx.z * NTILES + tile0) * cts * 64 + lane;
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct)
+        if (tile0 + t < NTILES && rw * CT + ct < cts)
+          dst[((size_t)t * cts + rw * CT + ct) * 64] = make_float4(acc[t][ct][0], acc[t][ct][1], acc[t][ct][2], acc[t][ct][3]);
+    return;
+  }
+  float rs[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) rs[ct] = normed ? s_rstd[min((rw * CT + ct) * 16 + j, 63)] : 1.f;
+  shared_epilogue<NT, CT>(role, epi, M, N, tot, tile0, rw * CT * 16 + j, g, rs);
+}
+
+// the pairs of a SPLIT launch added up in order, then its epilogue: a wave takes CT column tiles (two where the epilogue
+// exchanges between them) of a weight tile, the work-group's four waves those of adjacent tiles
+template <int CT>
+__global__ __launch_bounds__(256) void k_shared_reduce(const float* __restrict__ part, int pairs, int M, RowNorm nrm, int K, int N, int role,
+                                                       GemmEpi epi) {
+  __shared__ float s_rstd[16 * CT];
+  const int lane = threadIdx.x & 63, NTILES = N >> 4, cts = (M + 15) >> 4;
+  const int tile = min((int)(blockIdx.x * 4 + (threadIdx.x >> 6)), NTILES), ct0 = blockIdx.y * CT;
+  const float4* src = reinterpret_cast<const float4*>(part) + (size_t)min(tile, NTILES - 1) * cts * 64 + lane;
+  const size_t stride = (size_t)NTILES * cts * 64;
+  f32x4 sum[1][CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) sum[0][ct] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const bool normed = nrm.gain && nrm.ssq_part;
+  if (normed) shared_rstd(nrm, ct0 * 16, min(16 * CT, M - ct0 * 16), K, s_rstd);
+  for (int z0 = 0; z0 < pairs; z0 += 8) {
+    float4 v[8][CT];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+      for (int ct = 0; ct < CT; ++ct) v[i][ct] = src[min(z0 + i, pairs - 1) * stride + min(ct0 + ct, cts - 1) * 64];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+      if (z0 + i < pairs)
+#pragma unroll
+        for (int ct = 0; ct < CT; ++ct) sum[0][ct] += f32x4{v[i][ct].x, v[i][ct].y, v[i][ct].z, v[i][ct].w};
+  }
+  __syncthreads();
+  float rs[CT];
+#pragma unroll
+  for (int ct = 0; ct < CT; ++ct) rs[ct] = normed ? s_rstd[ct * 16 + (lane & 15)] : 1.f;
+  shared_epilogue<1, CT>(role, epi, M, N, sum, tile, ct0 * 16 + (lane & 15), lane >> 4, rs);   // (tile NTILES: nothing is stored)
+}
+
+// 33..64 rows, except residual-writing projections of few tiles with a short k (64 rows, 64 x 1024 9.3 us against 14.3; 128 x
+// 2048 12.9 against 13.6) and, below 48 rows, q | k | v of 1024-wide models (192 tiles, 33 / 40 / 48 / 64 rows 13.7 / 14.2 / 15.3 /
+// 18.5 against 14.3 / 14.6 / 14.8 / 15.7: one work-group per 128 features leaves most CUs idle).  17..32 rows, where half of
+// the column tiles are empty: only residual-writing projections with 16 chunks and more (17 / 32 rows: 128 tiles x 8192 20.7 /
+// 24.9 -> 16.8 / 17.2, 256 x 11008 32.4 / 32.7 -> 27.0 / 27.2; the other 7B projections 1..6 us slower).
+bool shared_takes(int role, int M, int NTILES, int K) {
+  const bool resid = role == kRoleWo || role == kRoleDown;
+  if (M <= 32) return M > 16 && resid && K > 15 * 512;
+  if (resid) return !(NTILES <= 128 && K <= 2048);
+  return !(role == kRoleQKV && M < 48 && K <= 1024 && NTILES > 144 && NTILES <= 256);
+}
+
+bool launch_gemm_shared(int role, const void* W, int N, int K, const uint4* xfrag, int M, RowNorm nrm, float* partial, const GemmEpi& epi,
+                        hipStream_t st) {
+  const int NTILES = N / 16, blocks = (NTILES + 7) / 8, ksteps = K / 32, pairs = (gemm_slices(K, 1) + 1) / 2;
+  const bool paired_ct = role == kRoleQKV || role == kRoleGateUp;
+  if (M > kMaxFwdRows || !shared_takes(role, M, NTILES, K)) return false;
+  auto steps_us = [](int wgs, float ks) {                // as in launch_blk_gemm
+    const BlkShape& b = kBlkShapes[3];
+    const int full = wgs / 512, rem = wgs % 512;
+    return ks * (full * b.two + (rem > 256 ? b.one + (b.two - b.one) * (0.55f + 0.45f * (rem - 256) / 256) : rem == 0 ? 0.f : full ? 0.74f * b.one : b.one));
+  };
+  const float one = steps_us(blocks, (float)ksteps);
+  const float two = pairs > 1 ? steps_us(blocks * pairs, 32.f) + 1.f + (2.f * pairs + 1.f) * M * N * 4 / 4.5e6f : 1e30f;
+  const uint4* Wsw = static_cast<const uint4*>(W);
+#define STAIRS_SHARED(split, stream, z)                                                                                            \
+  hipLaunchKernelGGL((k_gemm_bf16_shared<split, stream>), dim3(blocks, 1, z), dim3(256), kShLds, st, Wsw, NTILES, xfrag, M, nrm, K, N, role, \
+                     partial, epi)
+  if (two < one) {
+    if (epi.stream_weights) STAIRS_SHARED(true, true, pairs); else STAIRS_SHARED(true, false, pairs);
+    const dim3 grid((NTILES + 3) / 4, paired_ct ? (M + 31) / 32 : (M + 15) / 16);
+    hipLaunchKernelGGL(paired_ct ? k_shared_reduce<2> : k_shared_reduce<1>, grid, dim3(256), 0, st, partial, pairs, M, nrm, K, N, role, epi);
+  } else {
+    if (epi.stream_weights) STAIRS_SHARED(false, true, 1); else STAIRS_SHARED(false, false, 1);
+  }
+#undef STAIRS_SHARED
+  return true;
+}
+
 // Attention of a row block without partial results (the rows of a 16-row tile belong to one sequence, see BlkSegs): a
 // wave owns 16 query rows of one head and walks over the keys 0 .. its last row's position (kv_fixed > 0: over the keys
 // 0 .. kv_fixed - 1 whatever the row, encoder), 32 at a time, keeping the running maximum, the running sum and the
@@ -795,6 +1208,10 @@ hipError_t configure_block_kernels() {
   STAIRS_OPTIN_BLK(4, 1, 4, 3);
   STAIRS_OPTIN_BLK(2, 2, 2, 4);
 #undef STAIRS_OPTIN_BLK
+  optin((const void*)k_gemm_bf16_shared<true, true>, kShLds);
+  optin((const void*)k_gemm_bf16_shared<true, false>, kShLds);
+  optin((const void*)k_gemm_bf16_shared<false, true>, kShLds);
+  optin((const void*)k_gemm_bf16_shared<false, false>, kShLds);
   return e;
 }
 

@@ -113,7 +113,8 @@ struct GemmEpi {
 
 // ---- skinny GEMM + epilogue ---------------------------------------------------------------
 // bf16: W is swizzled, split-K slices of 512 k, epilogue fused; fp32: W row-major,
-// epilogue fused, the row norm gathered from X itself (nrm.ssq_part unused).  partial (bf16): scratch of gemm_slices() * M * N floats.
+// epilogue fused, the row norm gathered from X itself (nrm.ssq_part unused).  partial (bf16): scratch of gemm_slices() * M * N
+// floats (M > 16: see launch_gemm_shared as well).
 // xfrag (bf16, M > 4): the fragments of X with nrm.gain folded in, left by X's producer or by launch_split_frag; with
 // them the launch takes the hand-off-free kernel k_gemm_bf16_wide (no partial sums), without them the split-K kernel.
 void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const float* X, int ldx, int M,
@@ -125,6 +126,13 @@ size_t rows_path_lds(int role, int M, int N, int K);
 // launch shape of the GEMM that reads fragments (5..64 rows): weight tiles per wave, waves; nt == 0: the split-K kernel
 struct WideCfg { int nt, nw; };
 WideCfg wide_cfg(int role, int M, int NTILES, int K);
+
+// launch_gemm for 17..64 rows on the kernel that shares the activation fragments of a work-group through LDS; false: another
+// kernel is faster for the shape, nothing launched.  partial: room for (gemm_slices(K, 1) + 1) / 2 times M rounded up to 16
+// times N floats.  shared_takes: the rule.
+bool shared_takes(int role, int M, int NTILES, int K);
+bool launch_gemm_shared(int role, const void* W, int N, int K, const uint4* xfrag, int M, RowNorm nrm, float* partial, const GemmEpi& epi,
+                        hipStream_t st);
 
 // Y [M <= 32, N] = X [M, K] . W^T with W [N, K] row-major bf16 read as it is, one kernel (M > 4: two), the bits launch_gemm
 // gives for the laid-out matrix; frag: frag_bytes(K) of scratch.  false: the shape takes the split-K kernel, nothing done.

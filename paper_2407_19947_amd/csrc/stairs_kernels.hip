@@ -1159,12 +1159,11 @@ WideCfg wide_cfg(int role, int M, int NTILES, int K) {
       free_nw = c.nt == 0;
     }
   }
-  if (M > 2 * 16) {                      // 33..64 rows: this kernel only (split-K stops at two column tiles)
-    // one work-group per CU (its chunk sums fill the LDS): 8 waves, two a SIMD, cover each other's waits for the fragments,
-    // which outweigh the weights here (64 rows, 1376 and 2000 tiles x 8 chunks, mean of both: 62.2 -> 57.8 us with 4 -> 8 waves)
+  if (M > 2 * 16) {                      // 33..64 rows: never split-K, which stops at two column tiles
+    // 8 waves, two a SIMD, cover each other's waits for the fragments, which outweigh the weights here
     if (c.nt == 0) c.nt = 1;
     if (free_nw) c.nw = std::min(8, nchunks);
-    if (c.nt > 4) c.nt = 4;                 // (the three- and four-column-tile forms exist for 1, 2 and 4 tiles per wave)
+    if (c.nt > 4) c.nt = 4;
     if (c.nt == 3) c.nt = 4;
   }
   return c;
@@ -1430,8 +1429,11 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
 #undef STAIRS_ROWS
     return;
   }
+  // more than 16 rows with the activation fragments at hand: where it is faster, the kernel that shares them through LDS
+  if (M > 16 && xfrag && launch_gemm_shared(role, W, N, K, xfrag, M, nrm, partial, epi, st)) return;
   // more than 4 rows with the activation fragments at hand: the hand-off-free kernel
   WideCfg wc = wide_cfg(role, M, NTILES, K);
+  if (M > kMaxRows) wc.nt = 1;             // (what shared_takes leaves to this kernel has at most 256 tiles)
   const int nchunks = gemm_slices(K, 1);
   auto wide_lds = [&](int nt) { return (size_t)nchunks * M * nt * 16 * sizeof(float); };
   while (wc.nt > 1 && wide_lds(wc.nt) > kWideMaxLds) wc.nt = wc.nt == 6 ? 4 : wc.nt == 3 ? 2 : wc.nt / 2;   // very long k: fewer tiles per work-group
@@ -1449,7 +1451,7 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
                          role, epi);                                                                                     \
   } while (0)
   // (two column tiles hold one k-step less in flight: a deeper ring would not fit the 256 registers of a wave)
-  // (three and four column tiles: one more; 8 tiles per wave do not occur there, their chunk sums exceed the LDS)
+  // (three and four column tiles, one more: with one tile per wave only)
 #define STAIRS_WIDE_CT2(nt, dp)        \
   if (CT == 1) STAIRS_WIDE(1, nt, dp); \
   else STAIRS_WIDE(2, nt, wide_depth2(dp))
@@ -1460,8 +1462,8 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
     if (wc.nt == 8) { STAIRS_WIDE_CT2(8, kWideDepth8); }
     else if (wc.nt == 6) { STAIRS_WIDE_CT2(6, kWideDepth6); }
     else if (wc.nt == 3) { STAIRS_WIDE_CT2(3, kWideDepth3); }
-    else if (wc.nt == 4) { STAIRS_WIDE_CT(4, kWideDepth4); }
-    else if (wc.nt == 2) { STAIRS_WIDE_CT(2, kWideDepth2); }
+    else if (wc.nt == 4) { STAIRS_WIDE_CT2(4, kWideDepth4); }
+    else if (wc.nt == 2) { STAIRS_WIDE_CT2(2, kWideDepth2); }
     else if (wide_whole_chunk(M, nchunks, wc.nw)) STAIRS_WIDE(1, 1, kWideDepthChunk);
     else { STAIRS_WIDE_CT(1, kWideDepth1); }
 #undef STAIRS_WIDE_CT
@@ -2630,8 +2632,6 @@ hipError_t configure_kernels() {
   optin((const void*)k_gemm_bf16_wide<1, 2, kWideDepth2, false, true>, kWideMaxLds);
   optin((const void*)k_gemm_bf16_wide<2, 1, wide_depth2(kWideDepth1), false, true>, kWideMaxLds);
   optin((const void*)k_gemm_bf16_wide<2, 2, wide_depth2(kWideDepth2), false, true>, kWideMaxLds);
-  STAIRS_OPTIN_WIDE(3, 4, kWideDepth4); STAIRS_OPTIN_WIDE(4, 4, kWideDepth4);
-  STAIRS_OPTIN_WIDE(3, 2, kWideDepth2); STAIRS_OPTIN_WIDE(4, 2, kWideDepth2);
   STAIRS_OPTIN_WIDE(3, 1, kWideDepth1); STAIRS_OPTIN_WIDE(4, 1, kWideDepth1);
 #undef STAIRS_OPTIN_WIDE
 #undef STAIRS_OPTIN_WIDE_

@@ -565,6 +565,28 @@ def test_five_to_seven_rows_of_small_models_have_the_bits_of_any_other_count(d, 
             assert np.array_equal(lg, want[:k + 1]), k
 
 
+@pytest.mark.parametrize("d,heads,ffn,vocab", [(256, 2, 768, 1040), (1024, 16, 4096, 528), (1280, 10, 2304, 4112), (2304, 18, 8448, 1040), (512, 8, 8192, 8208)])
+@pytest.mark.parametrize("B,k", [(9, 1), (11, 2), (16, 2), (16, 3)])
+def test_forwards_of_33_to_64_rows_have_the_bits_of_one_row(d, heads, ffn, vocab, B, k):
+    """Batches of 18, 33, 48 and 64 rows per verification (and 9..16 or twice as many per draft step) on the kernel that shares the fragments
+    through LDS: k of 8 k-steps and more, last chunks of half the length, an odd number of chunks (split over work-groups and
+    not), tiles that end inside a work-group's eight, both head sizes, random gains.  Every sequence's tokens are those of the
+    sequence generated alone, whose forwards of 1..4 rows take other kernels."""
+    w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=d, n_heads=heads, d_ffn=ffn, vocab=vocab),
+                           draft=dict(kind="prefix", n_layers=1), P=2, G=1)
+    target, draft = si.make_pair(w)
+    g = np.random.default_rng([13, d, B])
+    for ly in target.layers:
+        ly["attn_norm"], ly["ffn_norm"] = (g.uniform(0.5, 2.0, d).astype(np.float32) for _ in range(2))
+    prompts = [g.integers(0, vocab, P).astype(np.int32) for P in g.integers(1, 15, B)]
+    with pkg.Stairs(target, draft, k_max=k, max_seq=40) as s:
+        s.reserve_batch(B)
+        alone = np.stack([s.generate(p, 12, k)[0].copy() for p in prompts])
+        toks, _ = s.generate_batch(prompts, 12, k)
+        s.prefill(np.concatenate([prompts[-1], toks[-1]]))
+    assert np.array_equal(toks, alone)
+
+
 @pytest.mark.parametrize("d,heads", [(4352, 34), (4608, 36)])
 def test_gains_of_a_short_last_chunk(d, heads):
     """Norm gains that differ from column to column, k with a last chunk of half the length (4352) and without (4608), 4 and
