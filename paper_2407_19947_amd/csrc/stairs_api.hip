@@ -115,13 +115,15 @@ struct stairs_ctx {
   int* tgt_tok = nullptr;      // [kMaxRows]
   int* state = nullptr;        // per slot kSlotState ints: [0] = L, [1] = n of last iteration, [2] = constant 0, [3] = active
   int eos_id = -1;             // end token of the generation loops (stairs_set_eos); -1: none
-  int* h_pinned = nullptr;     // pinned host: [0..1] state, [2..2+kMaxRows) target tokens; batch: [n_slots][kSlotState] state
+  int* h_pinned = nullptr;     // pinned host: [0..1] state, [2..2+kMaxRows) target tokens (decode_loop with two iterations in
+                               // flight: [2..3] the second one's state); batch: [n_slots][kSlotState] state
   int h_pinned_ints = 0;
   // host mirror
   int L = 0, P = 0;
   bool prefilled = false;
   int pending_k = -1;          // draft length of the outstanding proposal, -1 = none
-  hipEvent_t ev[8] = {};       // 0,1: general; 5,6,7: iteration start / after the proposal / after validation
+  hipEvent_t ev[16] = {};      // 0,1,2: general; 5,6,7: iteration of a batch: start / after the proposal / after validation;
+                               // 8..11, 12..15: iterations of one sequence, two in flight: the same and results on the host
   struct IterGraph { int half, k, nch, B; hipGraphExec_t exec; };   // B = 0: the single-sequence path, -1: its sampled variant
   std::vector<IterGraph> graphs;   // captured iterations, see iteration_graph()
   std::vector<hipEvent_t> probe_ev;   // stairs_time_kernel(8): event pairs around one projection inside a forward
@@ -1574,40 +1576,74 @@ static int decode_loop(stairs_ctx* c, int32_t G, int32_t k, bool adaptive, int32
   int L_end = -1;                  // length of the sequence up to and including the end token, once it was emitted
   int rc;
   HIPCHK(c, hipEventRecord(c->ev[1], c->st));
-  while (c->L - L0 < G) {
-    int n = 0;
-    if (k > 0 && c->D.valid < c->L - 2 && (rc = ingest(c, &c->D, c->D.valid, c->L - 2))) return rc;
-    HIPCHK(c, hipEventRecord(c->ev[5], c->st));
+  // Every launch takes its positions from the device, so the next iteration is launched while the one before it runs whenever
+  // it is needed whatever that one keeps (it emits k + 1 tokens at most): the host's turn -- results across, wake-up, two
+  // graph launches, 10..25 us an iteration -- then costs nothing (tiny fp32 pair 7.80 -> 7.54 ms, 125M pair 32.1 -> 31.1, 7B widths at
+  // k = 2 35.9 -> 35.2).
+  // Not with an end token or a draft length that follows the results, nor without graphs (attention grids are then exact).
+  const int depth = c->use_graphs && !adaptive && c->eos_id < 0 ? 2 : 1;
+  int in_flight = 0, oldest = 0;
+  auto enqueue = [&](int set, int L) -> int {      // L: the longest the sequence can be by then
+    hipEvent_t* const ev = c->ev + 8 + 4 * set;
+    HIPCHK(c, hipEventRecord(ev[0], c->st));
     if (c->use_graphs) {
-      const int nch = std::min((chunks_for(c->L + k) + 3) / 4 * 4, c->nchunk_cap);   // never past the partial buffers
+      const int nch = std::min((chunks_for(L + k) + 3) / 4 * 4, c->nchunk_cap);   // never past the partial buffers
       hipGraphExec_t gp = nullptr, gv = nullptr;
       const int gB = sampled ? -1 : 0;
       if (k > 0 && (rc = iteration_graph(c, 0, k, nch, &gp, gB))) return rc;
       if ((rc = iteration_graph(c, 1, k, nch, &gv, gB))) return rc;
       if (k > 0) HIPCHK(c, hipGraphLaunch(gp, c->st));
-      HIPCHK(c, hipEventRecord(c->ev[6], c->st));
+      HIPCHK(c, hipEventRecord(ev[1], c->st));
       HIPCHK(c, hipGraphLaunch(gv, c->st));
     } else {
-      if (k > 0 && (rc = sampled ? enqueue_propose_sampled(c, k, chunks_for(c->L + k - 1))
-                                 : enqueue_propose(c, k, chunks_for(c->L + k - 1))))
+      if (k > 0 && (rc = sampled ? enqueue_propose_sampled(c, k, chunks_for(L + k - 1)) : enqueue_propose(c, k, chunks_for(L + k - 1))))
         return rc;
-      HIPCHK(c, hipEventRecord(c->ev[6], c->st));
-      if ((rc = sampled ? enqueue_verify_sampled(c, k, chunks_for(c->L + k)) : enqueue_verify(c, k, chunks_for(c->L + k)))) return rc;
+      HIPCHK(c, hipEventRecord(ev[1], c->st));
+      if ((rc = sampled ? enqueue_verify_sampled(c, k, chunks_for(L + k)) : enqueue_verify(c, k, chunks_for(L + k)))) return rc;
     }
-    HIPCHK(c, hipEventRecord(c->ev[7], c->st));
-    if (k > 0) c->D.valid = c->L + k - 1;
-    if ((rc = finish_verify(c, k, &n))) return rc;
+    HIPCHK(c, hipEventRecord(ev[2], c->st));
+    HIPCHK(c, hipMemcpyAsync(c->h_pinned + 2 * set, c->state, 2 * sizeof(int), hipMemcpyDeviceToHost, c->st));
+    if (c->eos_id >= 0)                            // (one in flight: behind the state of the only set)
+      HIPCHK(c, hipMemcpyAsync(c->h_pinned + 2, c->tgt_tok, (k + 1) * sizeof(int), hipMemcpyDeviceToHost, c->st));
+    HIPCHK(c, hipEventRecord(ev[3], c->st));
+    return STAIRS_OK;
+  };
+  auto failed = [&](int code) {                    // what is in flight ends before the caller may touch the context
+    (void)hipStreamSynchronize(c->st);
+    return code;
+  };
+  for (;;) {
+    const int L_most = c->L + in_flight * (k + 1);
+    if (in_flight < depth && L_most - L0 < G) {
+      if (in_flight == 0 && k > 0 && c->D.valid < c->L - 2 && (rc = ingest(c, &c->D, c->D.valid, c->L - 2))) return rc;
+      if ((rc = enqueue((oldest + in_flight) & 1, L_most))) return failed(rc);
+      ++in_flight;
+      continue;
+    }
+    if (in_flight == 0) break;
+    hipEvent_t* const ev = c->ev + 8 + 4 * oldest;
+    const int* const res = c->h_pinned + 2 * oldest;
     float a = 0.f, b = 0.f;
-    HIPCHK(c, hipEventElapsedTime(&a, c->ev[5], c->ev[6]));
-    HIPCHK(c, hipEventElapsedTime(&b, c->ev[6], c->ev[7]));
+    const hipError_t e = hipEventSynchronize(ev[3]);
+    if (e != hipSuccess || hipEventElapsedTime(&a, ev[0], ev[1]) != hipSuccess || hipEventElapsedTime(&b, ev[1], ev[2]) != hipSuccess) {
+      c->err = std::string("waiting for an iteration: ") + hipGetErrorString(e);
+      return failed(STAIRS_EHIP);
+    }
+    --in_flight;
+    if (depth == 2) oldest ^= 1;
+    const int L = c->L, n = res[1];
+    if (res[0] != L + n + 1 || n < 0 || n > k) return failed(fail(c, STAIRS_EHIP, "device state out of sync with host"));
+    c->L = L + n + 1;
+    c->T.valid = L + n;                            // (as finish_verify)
+    if (k > 0) c->D.valid = L + k - 1;
+    if (c->have_draft) c->D.valid = std::min(c->D.valid, L + n);
     s.ms_draft += a;
     s.ms_verify += b;
     s.iterations += 1;
     s.accepted += n;
     s.accept_hist[n] += 1;
     if (adaptive) k = (n == k) ? std::min(k + 1, c->k_max) : std::max(1, n + 1);
-    // the end token closes the answer: what the iteration emitted after it is dropped (finish_verify left the
-    // n + 1 emitted tokens in the pinned buffer)
+    // the end token closes the answer: what the iteration emitted after it is dropped
     if (c->eos_id >= 0) {
       int j = 0;
       while (j <= n && c->h_pinned[2 + j] != c->eos_id) ++j;

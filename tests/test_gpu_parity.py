@@ -565,6 +565,31 @@ def test_five_to_seven_rows_of_small_models_have_the_bits_of_any_other_count(d, 
             assert np.array_equal(lg, want[:k + 1]), k
 
 
+@pytest.mark.parametrize("k", [0, 1, 4])
+def test_iterations_launched_ahead_change_nothing(k, monkeypatch):
+    """Answers that end with, one before and one after a full iteration, and the shortest: with graphs, where the next iteration is
+    launched before the last one's result is read, and without, the tokens, the number of iterations and what each kept are
+    the same, and so is what a second call on the same context goes on with."""
+    w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=512, n_heads=4, d_ffn=768, vocab=528),
+                           draft=dict(kind="prefix", n_layers=1), P=9, G=1)
+    target, draft = si.make_pair(w)
+    prompt = si.make_prompt(w)
+    got = {}
+    for off in (None, "1"):
+        if off:
+            monkeypatch.setenv("STAIRS_NO_GRAPH", off)
+        out = []
+        with pkg.Stairs(target, draft, k_max=4, max_seq=160) as s:
+            for G in (1, 2, k + 1, k + 2, 2 * k + 2, 2 * k + 3, 23):
+                s.prefill(prompt)
+                for n in (G, 7):
+                    toks, st = s.decode(n, k)
+                    out.append((toks.tolist(), st.iterations, st.accepted, list(st.accept_hist)))
+                out.append(s.tokens().tolist())
+        got[off] = out
+    assert got[None] == got["1"]
+
+
 @pytest.mark.parametrize("d,heads,ffn,vocab", [(256, 2, 768, 1040), (1024, 16, 4096, 528), (1280, 10, 2304, 4112), (2304, 18, 8448, 1040), (512, 8, 8192, 8208)])
 @pytest.mark.parametrize("B,k", [(9, 1), (11, 2), (16, 2), (16, 3)])
 def test_forwards_of_33_to_64_rows_have_the_bits_of_one_row(d, heads, ffn, vocab, B, k):
