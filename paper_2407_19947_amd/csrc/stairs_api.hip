@@ -458,14 +458,16 @@ size_t max_partial_floats(const stairs_model_cfg* m) {
 //              M = every row -> c->logits rows 0..M-1.
 // Several sequences: pos.rps > 0 rows per slot, M = rps * (number of slots), slots 0..M/rps-1; otherwise the
 // rows belong to sequence slot `slot`.
-int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows, float* logits_dst);
+int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows, float* logits_dst, bool embedded);
 int forward_block(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows);
 
-// logits_dst: where the logits rows go (nullptr: c->logits)
-int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows, int slot = 0, float* logits_dst = nullptr) {
+// logits_dst: where the logits rows go (nullptr: c->logits); embedded: the launch in front has left the row's embedding
+// (next_embed(m)), M = 1
+int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows, int slot = 0, float* logits_dst = nullptr,
+            bool embedded = false) {
   if (m->encdec) {
     if (slot != 0 || pos.rps) return fail(c, STAIRS_EINVAL, "forward: encoder-decoder models take one sequence");
-    return forward_ed(c, m, pos, nchunk, M, logits_rows, logits_dst);
+    return forward_ed(c, m, pos, nchunk, M, logits_rows, logits_dst, embedded);
   }
   if (M > c->fwd_rows) {                    // many sequences at once: the block kernels
     if (slot != 0 || logits_dst) return fail(c, STAIRS_EINVAL, "forward: launch shape outside the workspaces");
@@ -494,6 +496,7 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
   // more than kMaxRows rows exist only on the hand-off-free GEMM: every projection must fit it
   if (M > kMaxRows && !(fr && gemm_takes_rows(M, std::max(d, f))))
     return fail(c, STAIRS_EINVAL, "forward: more rows than the weight-streaming kernels take for this model");
+  if (!embedded)
   launch_embed(m->tok_emb, b, c->tokens + (pos.rps ? 0 : (size_t)slot * c->tok_stride), pos.rps ? c->tok_stride : 0,
                c->tok_stride, V, pos, M, d, c->x, c->ssq, m->hd, m->rope_tab, m->cap, c->rope_cs, st, fr ? c->xf : nullptr,
                m->layers[0].attn_norm);
@@ -699,7 +702,7 @@ void launch_ed_ffn(stairs_ctx* c, const Model* m, const EdLayer& ly, int M, bool
 // Decoder forward of an encoder-decoder model: M rows of the decoder sequence at pos.. (see forward()).  Per layer:
 // self-attention over the decoder's cache with the one-sided position bias, cross-attention over the keys and
 // values stairs_encode left for this layer (every row sees all c->S source positions), feed-forward.
-int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows, float* logits_dst) {
+int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows, float* logits_dst, bool embedded) {
   const stairs_model_cfg& g = m->cfg;
   const int d = g.d_model, a = m->da, H = g.n_heads, V = g.vocab;
   const int sn = ssq_groups(d);
@@ -716,6 +719,7 @@ int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logit
   const bool fr = M > 4;
   uint4* const xf = fr ? c->xf : nullptr;
   uint4* const af = fr ? c->af : nullptr;
+  if (!embedded)
   launch_embed(m->tok_emb, 1, c->tokens, 0, c->tok_stride, V, pos, M, d, c->x, c->ssq, m->hd, nullptr, 0, c->rope_cs, st, xf,
                m->dec[0].attn_norm);
   SYNCPOINT();
@@ -996,6 +1000,12 @@ int ingest_prompts(stairs_ctx* c, Model* m, const int32_t* P, int B) {
   return flush();
 }
 
+// where a forward of one row of model m (one sequence) finds its embedding, for the launch that decides the row's token
+NextEmbed next_embed(const stairs_ctx* c, const Model* m) {
+  return NextEmbed{m->tok_emb, m->bf16 ? 1 : 0, c->tok_stride, m->cfg.vocab, m->cfg.d_model, m->hd, c->x, c->ssq,
+                   m->encdec ? nullptr : m->rope_tab, m->encdec ? 0 : m->cap, c->rope_cs};
+}
+
 // Enqueue the draft's k greedy steps.  Positions are taken relative to the device-side sequence
 // length (state[0] == L), so the same launches can be replayed for any L; nch = attention chunks to launch.
 int enqueue_propose(stairs_ctx* c, int k, int nch) {
@@ -1005,11 +1015,14 @@ int enqueue_propose(stairs_ctx* c, int k, int nch) {
   // its argmax is d_1 -> tokens[L].  Steps 2..k: one row each.
   int rc = forward(c, m, rel_pos(c, -2), nch, 2, 1);
   if (rc) return rc;
-  launch_argmax(c->logits, V, V, 1, 0, 1, c->tokens, rel_pos(c, 0), 0, c->st);
+  auto decide = [&](int j) {                // d_{j+1}; for another step, its embedding too
+    launch_argmax(c->logits, V, V, 1, 0, 1, c->tokens, rel_pos(c, j), 0, c->st, j + 1 < k ? next_embed(c, m) : NextEmbed{});
+  };
+  decide(0);
   for (int j = 1; j < k; ++j) {
-    rc = forward(c, m, rel_pos(c, j - 1), nch, 1, 1);
+    rc = forward(c, m, rel_pos(c, j - 1), nch, 1, 1, 0, nullptr, true);
     if (rc) return rc;
-    launch_argmax(c->logits, V, V, 1, 0, 1, c->tokens, rel_pos(c, j), 0, c->st);
+    decide(j);
   }
   HIPCHK(c, hipGetLastError());
   return STAIRS_OK;
@@ -1034,11 +1047,15 @@ int enqueue_propose_sampled(stairs_ctx* c, int k, int nch) {
   const int V = m->cfg.vocab;
   int rc = forward(c, m, rel_pos(c, -2), nch, 2, 1, 0, c->dlogits);
   if (rc) return rc;
-  launch_sample(c->dlogits, V, c->samp, 0, c->tokens, rel_pos(c, 0), c->samp_ws, c->st);
+  auto decide = [&](int j) {
+    launch_sample(c->dlogits + (size_t)j * V, V, c->samp, 0, c->tokens, rel_pos(c, j), c->samp_ws, c->st,
+                  j + 1 < k ? next_embed(c, m) : NextEmbed{});
+  };
+  decide(0);
   for (int j = 1; j < k; ++j) {
-    rc = forward(c, m, rel_pos(c, j - 1), nch, 1, 1, 0, c->dlogits + (size_t)j * V);
+    rc = forward(c, m, rel_pos(c, j - 1), nch, 1, 1, 0, c->dlogits + (size_t)j * V, true);
     if (rc) return rc;
-    launch_sample(c->dlogits + (size_t)j * V, V, c->samp, 0, c->tokens, rel_pos(c, j), c->samp_ws, c->st);
+    decide(j);
   }
   HIPCHK(c, hipGetLastError());
   return STAIRS_OK;

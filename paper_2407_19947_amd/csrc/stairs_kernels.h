@@ -162,6 +162,17 @@ void set_gemm_launch_events(hipEvent_t start, hipEvent_t stop);
 void launch_embed(const void* emb, int emb_bf16, const int* tokens, int tok_slot_stride, int tok_cap, int vocab, PosRef pos,
                   int M, int d, float* x, float* ssq_part, int hd, const float2* tab, int tab_len, float2* cs, hipStream_t st,
                   uint4* frag = nullptr, const float* frag_gain = nullptr);   // bf16: also the fragments of x * frag_gain
+// Where the next forward of one row finds its embedding (launch_embed's outputs for M = 1): a launch that decides a token can
+// leave the token's row there itself.  emb == nullptr: it does not.
+struct NextEmbed {
+  const void* emb;
+  int bf16, tok_cap, vocab, d, hd;
+  float* x;
+  float* ssq_part;
+  const float2* tab;
+  int tab_len;
+  float2* cs;
+};
 // tab[p][i] = (cos, sin)(p * theta^(-2i/hd)), p < len, angle formed in double: [len][64], once per model
 void launch_rope_table(int len, int hd, float theta, float2* tab, hipStream_t st);
 // cs[m] = tab's entries of the positions of rows 0 .. M-1
@@ -190,9 +201,10 @@ int attn_early_keys(int units, int nslots);
 int attn_f32_rows(int units, int H, int M);
 // out[o(r)] = argmax_v logits[row0 + r * row_stride][v], ties -> lowest v, r < nrows.  One sequence:
 // o(r) = *out_pos.base + out_pos.offset + r (base == nullptr: r).  Several: o(r) = s * out_slot_stride + position of
-// out_pos for row r, nothing written for a slot that is not active.
+// out_pos for row r, nothing written for a slot that is not active.  next (one sequence, one row): also the embedding of the
+// forward whose only row is that token at that position.
 void launch_argmax(const float* logits, int ld, int V, int nrows, int row0, int row_stride, int* out, PosRef out_pos,
-                   int out_slot_stride, hipStream_t st);
+                   int out_slot_stride, hipStream_t st, const NextEmbed& next = NextEmbed{});
 // stairs validation on device, one block per slot s (one sequence: nslots = 1, strides unused): state = {L, n, 0,
 // active}.  n = longest run with tokens[L+i] == tgt[i]; tokens[L+n] = tgt[n]; state[0] = L+n+1; state[1] = n.
 // tokens of slot s start at s * tok_slot_stride, its tgt at s * (k+1), its state at s * kSlotState.
@@ -216,9 +228,10 @@ struct SampleWs {
 // lse[r] = log sum_v exp(row_r[v] * inv_temp) for the n_a rows of a followed by the n_b rows of b (row stride ld)
 void launch_row_lse(const float* a, int n_a, const float* b, int n_b, int ld, int V, const SampleParams* sp, float* lse,
                     hipStream_t st);
-// tokens[o] = one draw from softmax(logits / T) by Gumbel-max with the random numbers of (o, stream), o = out_pos
+// tokens[o] = one draw from softmax(logits / T) by Gumbel-max with the random numbers of (o, stream), o = out_pos; next: as for
+// launch_argmax
 void launch_sample(const float* logits, int V, const SampleParams* sp, int stream, int* tokens, PosRef out_pos,
-                   SampleWs* ws, hipStream_t st);
+                   SampleWs* ws, hipStream_t st, const NextEmbed& next = NextEmbed{});
 // keep / replace walk over a sampled stair batch of one sequence (see k_accept_sampled); lse = launch_row_lse over
 // the k+1 rows of tl followed by the k rows of dl
 void launch_accept_sampled(int* tokens, const float* tl, const float* dl, int ld, int V, int k, const float* lse,

@@ -1518,6 +1518,38 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
 // table instead (identity without one, and outside it).
 // A row whose position lies outside [0, tok_cap) or whose token id lies outside [0, vocab) becomes a row of zeros:
 // the gather never leaves the token array or the embedding table, whatever the array holds.
+// columns c .. c+3 (c < d, a multiple of 4; all lanes of a quad come along) of the row of token id
+template <typename E>
+__device__ __forceinline__ void embed_cols(const E* emb, int id, int vocab, int d, int c, float* x, float* ssq_part, uint4* frag, int m,
+                                           const float* frag_gain) {
+  float ss = 0.f;
+  if (c < d) {
+    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (id >= 0 && id < vocab) {
+      const E* row = emb + (size_t)id * d + c;
+      v.x = load_elem(row); v.y = load_elem(row + 1); v.z = load_elem(row + 2); v.w = load_elem(row + 3);
+    }
+    *reinterpret_cast<float4*>(x + c) = v;
+    ss = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);   // (squares of bf16 values are exact: contracted or not, the same)
+    if (frag) store_frag4(frag, m, c, v, frag_gain);
+  }
+  if (sizeof(E) == 2) {
+    ss += dpp<kDppXor1>(ss);
+    ss += dpp<kDppXor2>(ss);
+    if ((c & 12) == 0 && c < d) ssq_part[c / 16] = ss;
+  }
+}
+// The embedding the next forward of one row starts from, by a work-group of nth threads that all know the token: position p,
+// token id (kernel that decided them: no launch of its own, no round trip through the token array).
+__device__ __forceinline__ void next_embed(const NextEmbed& n, int p, int id, int nth) {
+  const int tid = threadIdx.x;
+  if (p < 0 || p >= n.tok_cap) id = -1;
+  if (tid < n.hd / 2) n.cs[tid] = n.tab && p >= 0 && p < n.tab_len ? n.tab[(size_t)p * 64 + tid] : make_float2(1.f, 0.f);
+  for (int c = tid * 4; c - tid * 4 < n.d; c += nth * 4) {
+    if (n.bf16) embed_cols(static_cast<const uint16_t*>(n.emb), id, n.vocab, n.d, c, n.x, n.ssq_part, nullptr, 0, nullptr);
+    else embed_cols(static_cast<const float*>(n.emb), id, n.vocab, n.d, c, n.x, n.ssq_part, nullptr, 0, nullptr);
+  }
+}
 template <typename E>
 __global__ __launch_bounds__(256) void k_embed(const E* __restrict__ emb, const int* __restrict__ tokens,
                                                int tok_slot_stride, int tok_cap, int vocab, PosRef pos, int d,
@@ -1532,24 +1564,8 @@ __global__ __launch_bounds__(256) void k_embed(const E* __restrict__ emb, const 
     if (i < hd / 2) cs[m * 64 + i] = tab && p >= 0 && p < tab_len ? tab[(size_t)p * 64 + i] : make_float2(1.f, 0.f);
     return;
   }
-  const int c = (blockIdx.x * 256 + threadIdx.x) * 4;
-  float ss = 0.f;
-  if (c < d) {
-    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-    const int id = (p >= 0 && p < tok_cap) ? tokens[p] : -1;
-    if (id >= 0 && id < vocab) {
-      const E* row = emb + (size_t)id * d + c;
-      v.x = load_elem(row); v.y = load_elem(row + 1); v.z = load_elem(row + 2); v.w = load_elem(row + 3);
-    }
-    *reinterpret_cast<float4*>(x + (size_t)m * d + c) = v;
-    ss = (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
-    if (frag) store_frag4(frag, m, c, v, frag_gain);
-  }
-  if (sizeof(E) == 2) {
-    ss += __shfl_xor(ss, 1);
-    ss += __shfl_xor(ss, 2);
-    if ((threadIdx.x & 3) == 0 && c < d) ssq_part[m * ssq_n + c / 16] = ss;
-  }
+  embed_cols(emb, p >= 0 && p < tok_cap ? tokens[p] : -1, vocab, d, (blockIdx.x * 256 + threadIdx.x) * 4, x + (size_t)m * d,
+             ssq_part + (size_t)m * ssq_n, frag, m, frag_gain);
 }
 
 void launch_embed(const void* emb, int emb_bf16, const int* tokens, int tok_slot_stride, int tok_cap, int vocab, PosRef pos,
@@ -2287,12 +2303,34 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
 // ---------------------------------------------------------------------------------------
 // per-row vocabulary argmax (ties -> lowest index) and stairs validation
 // ---------------------------------------------------------------------------------------
+// One work-group per row, bound by its chain: the row through one CU, compares, lane exchanges, the waves' results, the store.
+// The position is requested first, the exchanges stay out of the LDS unit and the last thread reads the waves' results at once
+// (32000 logits: 5.4 -> AFTER us).  NEXT: the same work-group goes on with the token's embedding (a launch of 3.7 .. 4.7 us less
+// per draft token).
+__device__ __forceinline__ void argmax_take(float& best, int& bi, float ov, int oi) {
+  if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+}
+template <int CTRL>
+__device__ __forceinline__ void argmax_dpp(float& best, int& bi) {
+  argmax_take(best, bi, dpp<CTRL>(best), __builtin_amdgcn_update_dpp(0, bi, CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ void argmax_swap(float& best, int& bi, bool far) {      // lanes at distance 32 or 16
+  const uint32_t b = __float_as_uint(best), i = (uint32_t)bi;
+  const auto rb = far ? __builtin_amdgcn_permlane32_swap(b, b, false, false) : __builtin_amdgcn_permlane16_swap(b, b, false, false);
+  const auto ri = far ? __builtin_amdgcn_permlane32_swap(i, i, false, false) : __builtin_amdgcn_permlane16_swap(i, i, false, false);
+  const bool second = threadIdx.x & (far ? 32 : 16);     // (this lane's own value is in the other half of the pair)
+  argmax_take(best, bi, __uint_as_float(second ? rb[0] : rb[1]), (int)(second ? ri[0] : ri[1]));
+}
+template <bool NEXT>
 __global__ __launch_bounds__(1024) void k_argmax(const float* __restrict__ logits, int ld, int V, int row0, int row_stride,
-                                                 int* __restrict__ out, PosRef out_pos, int out_slot_stride) {
-  __shared__ float sv[16];
-  __shared__ int si[16];
+                                                 int* __restrict__ out, PosRef out_pos, int out_slot_stride, NextEmbed next) {
+  __shared__ __align__(16) float sv[16];
+  __shared__ __align__(16) int si[16];
+  __shared__ int s_id;
   const int r = blockIdx.x, tid = threadIdx.x;
   const float* row = logits + (size_t)(row0 + r * row_stride) * ld;
+  // (several sequences: the slot's own token array, only while it is active)
+  const int o = out_pos.rps ? pos_of(out_pos, r) : (out_pos.base ? *out_pos.base : 0) + out_pos.offset + r;
   float best = -INFINITY;
   int bi = 0x7fffffff;
   // a thread walks its candidates in ascending index order, 8 loads in flight at a time
@@ -2314,46 +2352,66 @@ __global__ __launch_bounds__(1024) void k_argmax(const float* __restrict__ logit
       }
     }
   }
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) {
-    const float ov = __shfl_xor(best, off);
-    const int oi = __shfl_xor(bi, off);
-    if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-  }
+  argmax_swap(best, bi, true);
+  argmax_swap(best, bi, false);
+  argmax_dpp<kDppRor8>(best, bi);
+  argmax_dpp<kDppRor4>(best, bi);
+  argmax_dpp<kDppXor2>(best, bi);
+  argmax_dpp<kDppXor1>(best, bi);
   if ((tid & 63) == 0) { sv[tid >> 6] = best; si[tid >> 6] = bi; }
   __syncthreads();
   if (tid == 0) {
-    for (int w = 1; w < 16; ++w)
-      if (sv[w] > best || (sv[w] == best && si[w] < bi)) { best = sv[w]; bi = si[w]; }
-    if (out_pos.rps) {                     // several sequences: the slot's own token array, only while it is active
-      const int o = pos_of(out_pos, r);
+    float4 v[4];
+    int4 i4[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      v[q] = reinterpret_cast<const float4*>(sv)[q];
+      i4[q] = reinterpret_cast<const int4*>(si)[q];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (q > 0) argmax_take(best, bi, v[q].x, i4[q].x);
+      argmax_take(best, bi, v[q].y, i4[q].y);
+      argmax_take(best, bi, v[q].z, i4[q].z);
+      argmax_take(best, bi, v[q].w, i4[q].w);
+    }
+    if (out_pos.rps) {
       if (o >= 0) out[(size_t)slot_of(out_pos, r) * out_slot_stride + o] = bi;
     } else {
-      out[(out_pos.base ? *out_pos.base : 0) + out_pos.offset + r] = bi;
+      out[o] = bi;
     }
+    s_id = bi;
+  }
+  if constexpr (NEXT) {
+    __syncthreads();
+    next_embed(next, o, s_id, 1024);
   }
 }
 
 void launch_argmax(const float* logits, int ld, int V, int nrows, int row0, int row_stride, int* out, PosRef out_pos,
-                   int out_slot_stride, hipStream_t st) {
-  hipLaunchKernelGGL(k_argmax, dim3(nrows), dim3(1024), 0, st, logits, ld, V, row0, row_stride, out, out_pos, out_slot_stride);
+                   int out_slot_stride, hipStream_t st, const NextEmbed& next) {
+  hipLaunchKernelGGL(next.emb ? k_argmax<true> : k_argmax<false>, dim3(nrows), dim3(1024), 0, st, logits, ld, V, row0, row_stride, out, out_pos,
+                     out_slot_stride, next);
 }
 
-__global__ void k_accept(int* __restrict__ tokens, const int* __restrict__ tgt, int k, int* __restrict__ state,
-                         int tok_slot_stride) {
-  if (threadIdx.x != 0) return;
-  const int s = blockIdx.x;                 // slot
+// (a lane per draft token: one round trip behind the state's, whatever k)
+__global__ __launch_bounds__(64) void k_accept(int* __restrict__ tokens, const int* __restrict__ tgt, int k, int* __restrict__ state,
+                                               int tok_slot_stride) {
+  const int s = blockIdx.x, i = threadIdx.x;   // slot
   state += s * kSlotState;
-  if (!state[3]) return;                    // the slot is not generating (any more)
   tokens += (size_t)s * tok_slot_stride;
-  tgt += s * (k + 1);
+  const int t = tgt[s * (k + 1) + min(i, k)];
   const int L = state[0];
-  int n = 0;
-  while (n < k && tokens[L + n] == tgt[n]) ++n;
-  tokens[L + n] = tgt[n];
-  state[0] = L + n + 1;
-  state[1] = n;
+  if (!state[3]) return;                    // the slot is not generating (any more)
+  const unsigned long long differ = __ballot(i < k && tokens[L + min(i, k)] != t);
+  const int n = differ ? __builtin_ctzll(differ) : k;
+  if (i == n) {
+    tokens[L + n] = t;
+    state[0] = L + n + 1;
+    state[1] = n;
+  }
 }
+static_assert(kMaxRows <= 64, "k_accept: a lane per stair row");
 
 void launch_accept(int* tokens, const int* tgt, int k, int* state, int nslots, int tok_slot_stride, hipStream_t st) {
   hipLaunchKernelGGL(k_accept, dim3(nslots), dim3(64), 0, st, tokens, tgt, k, state, tok_slot_stride);
@@ -2452,7 +2510,8 @@ __global__ __launch_bounds__(1024) void k_row_lse(const float* __restrict__ a, i
 // tokens[o] = argmax_v(logits[v] / T + gumbel(o, stream, v)) with o = the position out_pos gives: one categorical
 // draw, one candidate per thread (grid-stride for very large vocabularies)
 __global__ __launch_bounds__(256) void k_sample(const float* __restrict__ logits, int V, const SampleParams* __restrict__ sp,
-                                                int stream, int* __restrict__ tokens, PosRef out_pos, SampleWs* ws) {
+                                                int stream, int* __restrict__ tokens, PosRef out_pos, SampleWs* ws, NextEmbed next) {
+  __shared__ int s_id;
   __shared__ double sv[4];
   __shared__ int si[4];
   __shared__ int s_flag;
@@ -2466,7 +2525,14 @@ __global__ __launch_bounds__(256) void k_sample(const float* __restrict__ logits
     if (sc > best || bi == 0x7fffffff) { best = sc; bi = v; }
   }
   if (!grid_argmax(best, bi, ws, sv, si, &s_flag)) return;
-  if (threadIdx.x == 0) tokens[o] = bi;
+  if (threadIdx.x == 0) {
+    tokens[o] = bi;
+    s_id = bi;
+  }
+  if (next.emb) {                                        // (the block that decided the token, as in k_argmax)
+    __syncthreads();
+    next_embed(next, o, s_id, 256);
+  }
 }
 
 // Validation of a sampled stair batch (one sequence).  tokens[L .. L+k) hold the assistant's draws d_1..d_k, dl[j-1]
@@ -2545,8 +2611,8 @@ void launch_row_lse(const float* a, int n_a, const float* b, int n_b, int ld, in
 }
 static int sample_blocks(int V) { return std::min(kSampleBlocksMax, (V + 255) / 256); }
 void launch_sample(const float* logits, int V, const SampleParams* sp, int stream, int* tokens, PosRef out_pos,
-                   SampleWs* ws, hipStream_t st) {
-  hipLaunchKernelGGL(k_sample, dim3(sample_blocks(V)), dim3(256), 0, st, logits, V, sp, stream, tokens, out_pos, ws);
+                   SampleWs* ws, hipStream_t st, const NextEmbed& next) {
+  hipLaunchKernelGGL(k_sample, dim3(sample_blocks(V)), dim3(256), 0, st, logits, V, sp, stream, tokens, out_pos, ws, next);
 }
 void launch_accept_sampled(int* tokens, const float* tl, const float* dl, int ld, int V, int k, const float* lse,
                            const SampleParams* sp, int* state, int* emitted, SampleWs* ws, hipStream_t st) {
