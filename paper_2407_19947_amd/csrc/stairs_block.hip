@@ -269,6 +269,11 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
 //   WF*4 + 2*WR*CT KiB-sized operands, copied from memory straight into LDS (buffer_load ... lds, 16 bytes per lane: no
 //   staging registers, and every operand enters the CU once), ST k-steps deep, and read from there as they lie
 //   (ds_read_b128, no bank conflicts: the layouts are lane order).
+//   Where each wave has weight tiles of its own (WR = 1), only the fragments go through LDS: a weight tile is loaded into the
+//   wave's registers two k-steps ahead, into those of the tile whose MFMAs were just issued.  LDS then takes 8 instead of 24
+//   KiB a k-step in and 32 instead of 48 out (busy 16 % of the cycles, 24 before), and a k-step's reads are 8, not 12.
+//   256 x 64 tiles, traced: 2048 rows, 7B QKV and gate/up 434 -> 408 us, 333 rows, pieces 101 -> 96 us; calls: 2048-token prompt
+//   1.01x, 333 1.02x.
 //   One barrier per k-step: the wave waits for its own copies of k-step s + 1 (those of the following ones stay in
 //   flight: the waits count instructions), the barrier makes everybody's visible and says that everybody holds k-step s
 //   in registers, so its buffer takes the copies of s + ST.
@@ -278,7 +283,8 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
 //   or the grid.
 //   What bounds it: at thousands of rows the issue of MFMAs, 1.20 .. 1.30 PFLOP/s with plain stores in launches by
 //   themselves (2047 rows, 7B projections; a library product of two 8192-wide matrices: 1.49 on the same card) and 1.07 over
-//   a profiled 2048-token prompt with its epilogues; at a few hundred the rounds of work-groups and, with one work-group on a
+//   a profiled 2048-token prompt with its epilogues (matrix cores busy in 0.69 of the cycles, at 1.74 GHz: the card lowers its
+//   clock under this load, so fewer idle cycles gain less than they save); at a few hundred the rounds of work-groups and, with one work-group on a
 //   CU, the pace of a single wave per SIMD (0.38 us per k-step of 32 MFMAs, 0.25 of 16); at <= 64 rows the weights' way from memory.
 //   Plain stores, against the kernel before (weights through registers, 256 x 128 tiles only), 7B projections, us:
 //   2047 rows: QKV 384 -> 337, out 115 -> 112, gate/up 712 -> 603, down 297 -> 296; 333 rows: 111 -> 87, 45 -> 33,
@@ -296,7 +302,9 @@ __device__ __forceinline__ void copy_to_lds_16(const uint4* base, uint32_t offse
                                            lane_bytes, offset, 0, 0);
 }
 constexpr int kBlkNT = 4;                              // weight tiles of a wave
-constexpr int blk_lds_bytes(int WF, int WR, int CT, int ST) { return ST * (WF * kBlkNT + 2 * WR * CT) * 1024 + WR * CT * 64; }
+constexpr int blk_lds_bytes(int WF, int WR, int CT, int ST) {
+  return ST * ((WR == 1 ? 0 : WF * kBlkNT) + 2 * WR * CT) * 1024 + WR * CT * 64;
+}
 
 //   CT: column tiles of a wave, ST: k-steps in LDS.  4 and 3 for many rows (24 KiB a k-step); 2 and 4 (16 KiB) where half the
 //   rows a work-group make the rounds come out or all CUs have work: see kBlkShapes.
@@ -304,9 +312,11 @@ template <int WF, int WR, int CT, int ST, bool PIECED>
 __global__ __launch_bounds__(64 * WF * WR) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks) {
   constexpr int NT = kBlkNT;
-  constexpr int NW = WF * WR, AT = WF * NT, BT = 2 * WR * CT, STAGE = (AT + BT) * 64;   // uint4 per LDS stage
-  constexpr int PER = (AT + BT) / NW;                                                   // copies per wave and k-step
-  static_assert(AT % NW == 0 && BT % NW == 0 && (ST - 1) * PER < 64, "whole copies per wave, countable by vmcnt");
+  constexpr bool DIRECT = WR == 1;                     // each wave loads its weight tiles itself, two k-steps ahead
+  constexpr int NW = WF * WR, AT = WF * NT, LT = DIRECT ? 0 : AT, BT = 2 * WR * CT, STAGE = (LT + BT) * 64;   // uint4 per LDS stage
+  constexpr int PER = (LT + BT) / NW;                                                   // copies per wave and k-step
+  static_assert(LT % NW == 0 && BT % NW == 0 && (ST - 1) * PER < 48, "whole copies per wave, countable by vmcnt");
+  static_assert(!DIRECT || (ST == 3 && CT == NT), "the order of requests the waits count");
   extern __shared__ uint4 lds[];                       // [ST][weight tiles AT | fragments BT][64], then the rows' 1/rms
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -331,21 +341,28 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
 #pragma unroll
   for (int q = 0; q < PER; ++q) {
     const int i = wave + q * NW;
-    off[q] = q < AT / NW ? (uint32_t)min(p.tile_first + fb * AT + i, p.NTILES - 1) * (kSliceUnits * 8 * 1024u)
-                         : (uint32_t)min(rb * BT + i - AT, 2 * p.RT - 1) * 1024u;
+    off[q] = q < LT / NW ? (uint32_t)min(p.tile_first + fb * AT + i, p.NTILES - 1) * (kSliceUnits * 8 * 1024u)
+                         : (uint32_t)min(rb * BT + i - LT, 2 * p.RT - 1) * 1024u;
   }
-  int rs_ = ks0;                                       // the next k-step
+  uint32_t aoff[DIRECT ? NT : 1];
+  if constexpr (DIRECT)
+#pragma unroll
+    for (int t = 0; t < NT; ++t) aoff[t] = (uint32_t)min(p.tile_first + fb * AT + fw * NT + t, p.NTILES - 1) * (kSliceUnits * 8 * 1024u);
+  int rs_ = ks0;                                       // the next k-step (DIRECT: of the weights)
   const uint4* wp = p.W + ((size_t)(ks0 >> 4) * p.NTILES * (kSliceUnits * 8) + (ks0 & 15)) * 64;
   const uint4* xp = p.XF + (size_t)ks0 * p.RT * 128;
   const size_t wskip = (size_t)(p.NTILES - 1) * (kSliceUnits * 8) * 64, xstep = (size_t)p.RT * 128;
+  auto next_weights = [&]() {
+    ++rs_;
+    wp += 64;
+    if ((rs_ & 15) == 0) wp += wskip;
+  };
   auto request = [&](int buf) {
     const int half = __builtin_amdgcn_readfirstlane((rs_ >> 4) >= full_chunks ? 1 : 0);
     uint4* dst = lds + buf * STAGE + wave * 64;
 #pragma unroll
-    for (int q = 0; q < PER; ++q) copy_to_lds_16(q < AT / NW ? wp : xp, q < AT / NW ? off[q] >> half : off[q], dst + q * NW * 64, lane * 16);
-    ++rs_;
-    wp += 64;
-    if ((rs_ & 15) == 0) wp += wskip;
+    for (int q = 0; q < PER; ++q) copy_to_lds_16(q < LT / NW ? wp : xp, q < LT / NW ? off[q] >> half : off[q], dst + q * NW * 64, lane * 16);
+    if constexpr (!DIRECT) next_weights();
     xp += xstep;
   };
   f32x4 acc[NT][CT], tot[PIECED ? NT : 1][PIECED ? CT : 1];
@@ -358,23 +375,31 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
   };
   auto read = [&](Frags& f, int buf) {
     const uint4* sa = lds + buf * STAGE + fw * NT * 64 + lane;
-    const uint4* sb = lds + buf * STAGE + (AT + rw * CT * 2) * 64 + lane;
+    const uint4* sb = lds + buf * STAGE + (LT + rw * CT * 2) * 64 + lane;
 #pragma unroll
     for (int ct = 0; ct < CT; ++ct) {
       f.h[ct] = __builtin_bit_cast(bf16x8, sb[(ct * 2) * 64]);
       f.l[ct] = __builtin_bit_cast(bf16x8, sb[(ct * 2 + 1) * 64]);
     }
+    if constexpr (!DIRECT)
 #pragma unroll
-    for (int t = 0; t < NT; ++t) f.a[t] = __builtin_bit_cast(bf16x8, sa[t * 64]);
+      for (int t = 0; t < NT; ++t) f.a[t] = __builtin_bit_cast(bf16x8, sa[t * 64]);
+  };
+  auto multiply_tile = [&](const Frags& f, int t) {
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[t], f.h[ct], acc[t][ct], 0, 0, 0);
+#pragma unroll
+    for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[t], f.l[ct], acc[t][ct], 0, 0, 0);
   };
   auto multiply = [&](const Frags& f) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t) {
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[t], f.h[ct], acc[t][ct], 0, 0, 0);
-#pragma unroll
-      for (int ct = 0; ct < CT; ++ct) acc[t][ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[t], f.l[ct], acc[t][ct], 0, 0, 0);
-    }
+    for (int t = 0; t < NT; ++t) multiply_tile(f, t);
+  };
+  // DIRECT: weight tile t of the next k-step not yet requested
+  auto load_weights = [&](Frags& f, int t) {
+    const int half = __builtin_amdgcn_readfirstlane((rs_ >> 4) >= full_chunks ? 1 : 0);
+    const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(wp), 0, 0xFFFFFFFFu, 0x00027000);
+    f.a[t] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(r, lane * 16, aoff[t] >> half, 0));
   };
   // the rows' 1/rms, while the first copies are on their way (its loads go first, so the counted waits cover them)
   float* s_rstd = reinterpret_cast<float*>(lds + ST * STAGE);
@@ -405,9 +430,23 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
   // them (all in front of them, a lone work-group took 0.52 us per k-step of 32 MFMAs a wave whatever the depth of the
   // ring; see kBlkShapes).
   Frags f0, f1;
+  // (a piece has at least 8 k-steps; DIRECT: in the order in which the loop requests them, the copies of k-step s + 3 and then
+  // the weights of s + 2)
+  constexpr int AHEAD = DIRECT ? 2 * NT : 0;           // weight loads younger than the copies a wait is for
 #pragma unroll
-  for (int i = 0; i < ST; ++i) request(i);    // (a piece has at least 8 k-steps)
-  wait_copies_and_sync<(ST - 1) * PER>();
+  for (int i = 0; i < ST; ++i) {
+    request(i);
+    if constexpr (DIRECT) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (i >= ST - 2) {
+#pragma unroll
+        for (int t = 0; t < NT; ++t) load_weights(i == ST - 2 ? f0 : f1, t);
+        next_weights();
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  }
+  wait_copies_and_sync<(ST - 1) * PER + AHEAD>();
   read(f0, 0);
   int s = ks0, rbuf = 1, wbuf = 0;                     // buffers of k-steps s + 1 and s + ST
   auto advance = [&]() {
@@ -415,10 +454,44 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
     wbuf = wbuf + 1 == ST ? 0 : wbuf + 1;
     ++s;
   };
-  constexpr int MFMAS = 2 * NT * CT, READS = NT + 2 * CT, GAP = (MFMAS - PER) / READS;
+  constexpr int MFMAS = 2 * NT * CT, READS = (DIRECT ? 0 : NT) + 2 * CT, GAP = (MFMAS - PER) / READS;
   static_assert(GAP >= 1, "an MFMA in front of every request and read");
-  auto step = [&](const Frags& cur, Frags& next) {     // any k-step but the last ST
-    wait_copies_and_sync<(ST - 2) * PER>();
+  // DIRECT: k-step s tile by tile; the registers of a weight tile take the tile of s + 2 as soon as its MFMAs are issued
+  auto step_direct = [&](Frags& cur, Frags& next, bool copies) {
+    const uint4* sb = lds + rbuf * STAGE + lane;
+    if (copies) request(wbuf);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      if (t > 0) load_weights(cur, t - 1);
+      if constexpr (DIRECT) {
+        next.h[t] = __builtin_bit_cast(bf16x8, sb[(t * 2) * 64]);
+        next.l[t] = __builtin_bit_cast(bf16x8, sb[(t * 2 + 1) * 64]);
+      }
+      multiply_tile(cur, t);
+#pragma unroll
+      for (int i = 0; i < (t > 0 ? 1 : copies ? PER : 0); ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 2, 0);
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, 2 * CT, 0);
+      __builtin_amdgcn_sched_barrier(0);               // (the waits count on the order of the requests)
+    }
+    load_weights(cur, NT - 1);
+    next_weights();
+    __builtin_amdgcn_sched_barrier(0);
+    advance();
+  };
+  auto step = [&](Frags& cur, Frags& next) {           // any k-step but the last ST
+    wait_copies_and_sync<(ST - 2) * PER + AHEAD>();
+    if constexpr (DIRECT) {
+      step_direct(cur, next, true);
+      return;
+    }
     request(wbuf);
     read(next, rbuf);
     multiply(cur);
@@ -440,14 +513,17 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
     step(f0, f1);
     step(f1, f0);
   }
-  // ST or ST + 1 k-steps are left: their number decides which register set holds the first of the last ST; nothing
-  // more to request, so the waits count down
+  // The number of k-steps is even (pieces begin at even ones, K is whole units of 8), so ST of them are left where ST is even,
+  // else ST + 1; nothing more to request for the last ST, so the waits count down
   auto last = [&](auto self, auto I, Frags& x, Frags& y) -> void {
     constexpr int i = decltype(I)::value;
-    if constexpr (i < ST - 1) {
-      wait_copies_and_sync<(ST - 2 - i) * PER>();
-      read(y, rbuf);
+    if constexpr (i < ST - 1) wait_copies_and_sync<(ST - 2 - i) * PER + AHEAD>();
+    if constexpr (DIRECT && i == 0) {
+      step_direct(x, y, false);
+      self(self, std::integral_constant<int, i + 1>{}, y, x);
+      return;
     }
+    if constexpr (i < ST - 1) read(y, rbuf);
     multiply(x);
     if constexpr (i < ST - 1 && CT == 2) {             // (with 4 column tiles it spills)
 #pragma unroll
@@ -461,7 +537,7 @@ void k_gemm_bf16_block(BlkGemm p, float* part, int RB, int per_xcd, int nblocks)
     if constexpr (i < ST - 1) self(self, std::integral_constant<int, i + 1>{}, y, x);
   };
   fold(s);
-  if (s + ST < ks_end) {
+  if constexpr (ST % 2 == 1) {
     step(f0, f1);
     last(last, std::integral_constant<int, 0>{}, f1, f0);
   } else {
