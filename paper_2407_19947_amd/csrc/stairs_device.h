@@ -112,6 +112,19 @@ __device__ __forceinline__ float wave_sum(float v) {           // (distance 32 f
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return half_wave_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
 }
+// Four of them together, a's in lanes 0 .. 15, b's in 16 .. 31, c's in 32 .. 47, d's in 48 .. 63: a swap with another value in
+// place of the value itself leaves the halves of two sums in one register.  The bits of wave_sum.
+__device__ __forceinline__ float wave_sums4(float a, float b, float c, float d) {
+  const auto ac = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(c), false, false);
+  const auto bd = __builtin_amdgcn_permlane32_swap(__float_as_uint(b), __float_as_uint(d), false, false);
+  const float x = __uint_as_float(ac[0]) + __uint_as_float(ac[1]), y = __uint_as_float(bd[0]) + __uint_as_float(bd[1]);
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+  float v = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+  v += dpp<kDppRor8>(v);
+  v += dpp<kDppRor4>(v);
+  v += dpp<kDppXor2>(v);
+  return v + dpp<kDppXor1>(v);
+}
 __device__ __forceinline__ float wave_max(float v) {
   auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   v = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));

@@ -1227,8 +1227,19 @@ bool launch_gemm_rowmajor(const uint16_t* W, int N, int K, const float* X, int M
 // and a branch around every row's loads a layer was 10 launches, now 5 (d 256, 4 layers + 2 of draft, 32 + 64 tokens:
 // 12.6 -> 7.4 ms; residual-writing projection at 1 / 5 rows: 3.35 + 2.4 / 6.9 + 2.4 -> 2.4 / 4.9 us).
 constexpr int kRoleLogits = 5;           // kRoleHead with a normalised input
+// The sums over the wave of rows q .. q + 3, row q + m's in lanes 16 m .. 16 m + 15 (one row: in all lanes).  Four rows share
+// the exchanges: 12 instructions a row and sum become 4, and a norm's square root and division are done once for four rows.
+// From 6 rows on the kernel asks for two waves a SIMD, no more: with the short reduction the compiler otherwise aims at more
+// waves and puts the loop's loads one after the other (54 .. 154 registers; 32 rows, 1000 x 2044 34.5 us).  Host call on device
+// buffers, row by row through the LDS unit -> now, us: 1000 x 2044 at 6 / 16 / 32 rows 7.6 / 16.9 / 21.5 -> 7.0 / 12.2 / 12.9,
+// 1024 x 1024 at 16 / 32 rows 10.7 / 14.0 -> 7.6 / 9.4, 256 x 256 at 32 rows 9.7 -> 6.7; the tiny pair 7.1 -> 6.2 ms.
+template <int MR>
+__device__ __forceinline__ float rows_sum4(const float (&v)[MR], int q) {
+  if constexpr (MR == 1) return wave_sum(v[0]);
+  return wave_sums4(v[q], q + 1 < MR ? v[min(q + 1, MR - 1)] : 0.f, q + 2 < MR ? v[min(q + 2, MR - 1)] : 0.f, q + 3 < MR ? v[min(q + 3, MR - 1)] : 0.f);
+}
 template <int MR, int ROLE>
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ W, int N, int K,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MR >= 6 ? 2 : 4, MR >= 6 ? 2 : 8))) void k_gemm_f32(const float* __restrict__ W, int N, int K,
                                                   const float* __restrict__ X, int ldx, int M, RowNorm nrm, GemmEpi epi) {
   constexpr bool NORMED = ROLE == kRoleQKV || ROLE == kRoleGateUp || ROLE == kRoleLogits;
   const int lane = threadIdx.x & 63;
@@ -1250,15 +1261,16 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ W, i
     n0 = 2 * pr;
     n1 = n0 + 1;
   }
-  // lane i finishes row i: what it needs beside the sums is requested first
-  const bool mine = lane < M && lane < MR;
+  // a row is finished by the lane where wave_sums4 leaves its sums: what it needs beside them is requested first
+  const int row = (lane & 15) * 4 + (lane >> 4);
+  const bool mine = row < M && row < MR;
   float2 old = make_float2(0.f, 0.f), cs = make_float2(1.f, 0.f);
   int pos = 0;
   if (mine) {
-    if (ROLE == kRoleWo || ROLE == kRoleDown) old = *reinterpret_cast<const float2*>(epi.out + (size_t)lane * N + n0);
+    if (ROLE == kRoleWo || ROLE == kRoleDown) old = *reinterpret_cast<const float2*>(epi.out + (size_t)row * N + n0);
     if (ROLE == kRoleQKV) {
-      pos = *epi.pos.base + epi.pos.offset + lane;
-      if (part < 2) cs = epi.rope_cs[lane * 64 + e];
+      pos = *epi.pos.base + epi.pos.offset + row;
+      if (part < 2) cs = epi.rope_cs[row * 64 + e];
     }
   }
   float a0[MR], a1[MR], ss[MR];
@@ -1268,7 +1280,8 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ W, i
   const float* xr[MR];
 #pragma unroll
   for (int i = 0; i < MR; ++i) xr[i] = X + (size_t)min(i, M - 1) * ldx;
-#pragma unroll 2
+  constexpr int UNROLL = MR > 16 ? 1 : 2;
+#pragma unroll UNROLL
   for (int k = lane * 4; k < K; k += 256) {
     const float4 w0 = *reinterpret_cast<const float4*>(W + (size_t)n0 * K + k), w1 = *reinterpret_cast<const float4*>(W + (size_t)n1 * K + k);
     float4 g = make_float4(1.f, 1.f, 1.f, 1.f), x[MR];
@@ -1289,33 +1302,37 @@ __global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ W, i
   // (1/rms goes onto the lanes' sums, not onto the finished one: 64 roundings that average out instead of one that stays)
   if (NORMED && nrm.gain) {
 #pragma unroll
-    for (int i = 0; i < MR; ++i) {
-      const float r = 1.0f / sqrtf(wave_sum(ss[i]) / (float)K + nrm.eps);
-      a0[i] = __fmul_rn(a0[i], r);
-      a1[i] = __fmul_rn(a1[i], r);
+    for (int q = 0; q < MR; q += 4) {
+      const float r4 = 1.0f / sqrtf(rows_sum4<MR>(ss, q) / (float)K + nrm.eps);
+#pragma unroll
+      for (int i = q; i < MR && i < q + 4; ++i) {
+        const float r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r4), (i - q) * 16));
+        a0[i] = __fmul_rn(a0[i], r);
+        a1[i] = __fmul_rn(a1[i], r);
+      }
     }
   }
   float v0 = 0.f, v1 = 0.f;
 #pragma unroll
-  for (int i = 0; i < MR; ++i) {
-    const float s0 = wave_sum(a0[i]), s1 = wave_sum(a1[i]);
-    v0 = lane == i ? s0 : v0;
-    v1 = lane == i ? s1 : v1;
+  for (int q = 0; q < MR; q += 4) {
+    const float s0 = rows_sum4<MR>(a0, q), s1 = rows_sum4<MR>(a1, q);
+    v0 = (lane & 15) * 4 == q ? s0 : v0;
+    v1 = (lane & 15) * 4 == q ? s1 : v1;
   }
   if (!mine) return;
   if (ROLE == kRoleWo || ROLE == kRoleDown) {
-    *reinterpret_cast<float2*>(epi.out + (size_t)lane * N + n0) = make_float2(__fadd_rn(old.x, v0), __fadd_rn(old.y, v1));
+    *reinterpret_cast<float2*>(epi.out + (size_t)row * N + n0) = make_float2(__fadd_rn(old.x, v0), __fadd_rn(old.y, v1));
   } else if (ROLE == kRoleGateUp) {
-    epi.out[(size_t)lane * (N / 2) + pr] = swiglu(v0, v1);
+    epi.out[(size_t)row * (N / 2) + pr] = swiglu(v0, v1);
   } else if (ROLE == kRoleHead || ROLE == kRoleLogits) {
-    *reinterpret_cast<float2*>(epi.out + (size_t)lane * N + n0) = make_float2(v0, v1);
+    *reinterpret_cast<float2*>(epi.out + (size_t)row * N + n0) = make_float2(v0, v1);
   } else if (pos >= 0) {
     if (part < 2) {
       const float2 r = rope_rotate(v0, v1, cs);
       v0 = r.x;
       v1 = r.y;
     }
-    float* dst = part == 0 ? epi.out + (size_t)lane * d + h * epi.hd + e
+    float* dst = part == 0 ? epi.out + (size_t)row * d + h * epi.hd + e
                            : (part == 1 ? epi.Kc32 : epi.Vc32) + ((size_t)h * epi.cap + pos) * epi.hd + e;
     dst[0] = v0;
     dst[half] = v1;
