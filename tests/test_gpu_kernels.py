@@ -44,6 +44,20 @@ def test_gemm_fp32(N, K, M):
     assert np.max(np.abs(Y - _ref(W, X))) < 2e-6 * np.sqrt(K)
 
 
+@pytest.mark.parametrize("M", [2, 3, 6, 7, 8, 9, 16, 31])
+def test_gemm_fp32_rows_share_their_sums(M):
+    """Four rows' sums over the lanes are formed together: for row counts around whole groups of four every row has the bits it has
+    alone (same additions in the same order), and that against a 64-bit product."""
+    rng = np.random.default_rng(M)
+    W = rng.standard_normal((136, 1028), dtype=np.float32)
+    X = rng.standard_normal((M, 1028), dtype=np.float32)
+    Y = pkg.stairs_gemm_host(W, X)
+    for i in range(M):
+        assert np.array_equal(Y[i], pkg.stairs_gemm_host(W, X[i:i + 1])[0]), i
+    W, X = W.astype(np.float64), X.astype(np.float64)
+    assert np.all(np.abs(Y - X @ W.T) <= 2 * 1028 * 2.0 ** -24 * (np.abs(X) @ np.abs(W).T))
+
+
 def test_gemm_rows_do_not_depend_on_batch():
     """Row i computed in a batch of M rows is bit-identical to row i computed alone."""
     rng = np.random.default_rng(5)
