@@ -1625,8 +1625,21 @@ static int decode_loop(stairs_ctx* c, int32_t G, int32_t k, bool adaptive, int32
     HIPCHK(c, hipEventRecord(ev[3], c->st));
     return STAIRS_OK;
   };
-  auto failed = [&](int code) {                    // what is in flight ends before the caller may touch the context
-    (void)hipStreamSynchronize(c->st);
+  // What is in flight ends before the caller may touch the context, and counts: the sequence is what the device holds then.
+  // If that is not known (or not as it has to be), there is no sequence any more.
+  auto failed = [&](int code, bool lost = false) {
+    lost |= hipMemcpyAsync(c->h_pinned, c->state, sizeof(int), hipMemcpyDeviceToHost, c->st) != hipSuccess;
+    lost |= hipStreamSynchronize(c->st) != hipSuccess;
+    const int L = c->h_pinned[0];
+    if (lost || L < c->L || L > L0 + G + k) {
+      c->prefilled = false;
+      c->T.valid = c->D.valid = 0;
+    } else if (L > c->L) {
+      c->L = L;
+      c->T.valid = L - 1;
+      if (k > 0) c->D.valid = L - 2;               // (everything kept: row L - 2 is not cached; otherwise it is, and computed again)
+      else if (c->have_draft) c->D.valid = std::min(c->D.valid, L - 1);
+    }
     return code;
   };
   for (;;) {
@@ -1641,15 +1654,17 @@ static int decode_loop(stairs_ctx* c, int32_t G, int32_t k, bool adaptive, int32
     hipEvent_t* const ev = c->ev + 8 + 4 * oldest;
     const int* const res = c->h_pinned + 2 * oldest;
     float a = 0.f, b = 0.f;
-    const hipError_t e = hipEventSynchronize(ev[3]);
-    if (e != hipSuccess || hipEventElapsedTime(&a, ev[0], ev[1]) != hipSuccess || hipEventElapsedTime(&b, ev[1], ev[2]) != hipSuccess) {
+    hipError_t e = hipEventSynchronize(ev[3]);
+    if (e == hipSuccess) e = hipEventElapsedTime(&a, ev[0], ev[1]);
+    if (e == hipSuccess) e = hipEventElapsedTime(&b, ev[1], ev[2]);
+    if (e != hipSuccess) {
       c->err = std::string("waiting for an iteration: ") + hipGetErrorString(e);
       return failed(STAIRS_EHIP);
     }
     --in_flight;
     if (depth == 2) oldest ^= 1;
     const int L = c->L, n = res[1];
-    if (res[0] != L + n + 1 || n < 0 || n > k) return failed(fail(c, STAIRS_EHIP, "device state out of sync with host"));
+    if (res[0] != L + n + 1 || n < 0 || n > k) return failed(fail(c, STAIRS_EHIP, "device state out of sync with host"), true);
     c->L = L + n + 1;
     c->T.valid = L + n;                            // (as finish_verify)
     if (k > 0) c->D.valid = L + k - 1;

@@ -11,6 +11,8 @@
 // greedy, same seed same run).  Exit status 0 = no check failed; a sanitizer report aborts the process.
 #include <hip/hip_runtime.h>
 
+#include <dlfcn.h>
+
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -39,6 +41,20 @@ void* operator new[](size_t n, const std::nothrow_t&) noexcept {
   } catch (...) {
     return nullptr;
   }
+}
+
+// a call of the runtime that is refused: the n-th from now on (0: none), without reaching the runtime
+static int g_refuse_launch = 0, g_refuse_time = 0;
+static bool refused(int& left) { return left > 0 && --left == 0; }
+extern "C" hipError_t hipGraphLaunch(hipGraphExec_t exec, hipStream_t st) {
+  if (refused(g_refuse_launch)) return hipErrorOutOfMemory;
+  static const auto real = reinterpret_cast<hipError_t (*)(hipGraphExec_t, hipStream_t)>(dlsym(RTLD_NEXT, "hipGraphLaunch"));
+  return real(exec, st);
+}
+extern "C" hipError_t hipEventElapsedTime(float* ms, hipEvent_t start, hipEvent_t stop) {
+  if (refused(g_refuse_time)) return hipErrorOutOfMemory;
+  static const auto real = reinterpret_cast<hipError_t (*)(float*, hipEvent_t, hipEvent_t)>(dlsym(RTLD_NEXT, "hipEventElapsedTime"));
+  return real(ms, start, stop);
 }
 
 struct Rng {
@@ -255,6 +271,27 @@ static void part2_decoder_only() {
     CHECK(s1 == s2);
     CHECK(stairs_generate_sampled(c, p.data(), P, G, 3, 0.f, 99, s2.data(), &st) == STAIRS_EINVAL);
   }
+  // an iteration that cannot be launched (its proposal, its verification; with none and with one in front of it) or whose
+  // time cannot be read: the error is the call's, what ended before it counts, and the sequence goes on from there
+  for (int k : {0, 3})
+    for (int at = 1; at <= 5; ++at) {
+      const int P = 70, per = k > 0 ? 2 : 1;             // graph launches per iteration
+      std::vector<int32_t> q = prompt_of(r, P, V), base(G), got(G), seq(P + 2 * G);
+      CHECK(stairs_generate(c, q.data(), P, G, 0, base.data(), &st) == STAIRS_OK);
+      CHECK(stairs_prefill(c, q.data(), P) == STAIRS_OK);
+      (at <= 4 ? g_refuse_launch : g_refuse_time) = at <= 4 ? at : 1;
+      CHECK(stairs_decode(c, G, k, got.data(), &st) == STAIRS_EHIP);
+      CHECK(g_refuse_launch == 0 && g_refuse_time == 0);
+      CHECK(std::strstr(stairs_last_error(c), hipGetErrorString(hipErrorOutOfMemory)) != nullptr);
+      int32_t len = 0;
+      CHECK(stairs_get_tokens(c, seq.data(), (int32_t)seq.size(), &len) == STAIRS_OK);
+      const int whole = at <= 4 ? (at - 1) / per : 2;    // iterations launched whole (two are in flight when the time is read)
+      CHECK(len >= P + whole && len <= P + whole * (k + 1));
+      for (int i = P; i < len && i < P + G; ++i) CHECK(seq[i] == base[i - P]);
+      const int left = P + G - len;
+      CHECK(stairs_decode(c, left, 3, got.data(), &st) == STAIRS_OK && st.tokens == left);
+      CHECK(std::memcmp(got.data(), base.data() + G - left, left * sizeof(int32_t)) == 0);
+    }
   // error paths on a live context
   std::vector<int32_t> p = prompt_of(r, cap, V), out(64);
   CHECK(stairs_prefill(c, p.data(), cap) == STAIRS_ECAPACITY);
