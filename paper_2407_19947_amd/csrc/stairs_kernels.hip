@@ -1075,9 +1075,11 @@ size_t rows_path_lds(int role, int M, int N, int K) {
   if (M > 7 || M > max_rows) return 0;
   const size_t bytes = (size_t)K * M * 4 + (size_t)(gemm_slices(K, 1) + 1) * M * 16 * 4;
   // 5..7 rows (at 8 the fragment-reading kernel is as fast), three cases:
-  // k below 2048, a work-group per tile and no more than CUs (more: rows_many_tiles_lds): 4.5 .. 5.2 us a launch at 125M and
-  // at the large encoder-decoder shape, where the fragment-reading kernel takes 5.1 .. 5.4.
-  if (M > 4 && role != kRoleDown && K < 2048) return N / 16 <= 256 && bytes <= kRowsPathMaxLds ? bytes : 0;
+  // k below 2048, a work-group per tile: up to as many as CUs 4.5 .. 5.2 us a launch at 125M and at the large encoder-decoder
+  // shape, where the fragment-reading kernel takes 5.1 .. 5.4; more at 5 / 7 rows: 384 tiles, k = 768 5.6 / 5.9 us of a layer
+  // against 7.2 / 7.8, 2000 tiles, k = 1024 12.8 / 13.4 against 14.7 / 15.6 (with work-groups that walk through the tiles it
+  // was the slower one).
+  if (M > 4 && role != kRoleDown && K < 2048) return bytes <= kRowsPathMaxLds ? bytes : 0;
   // feed-forward outputs with k up to 4096 (one staging pass) and few tiles: 5.0 .. 5.5 against 7.0 us at 125M
   if (M > 4 && role == kRoleDown) return K <= 4096 && N / 16 <= 128 && bytes <= kRowsPathMaxLdsWide ? bytes : 0;
   // k of 2048 and more, a chunk for each wave: the block takes more than half a CU's LDS, so one work-group per CU walks
@@ -1096,14 +1098,6 @@ size_t rows_path_lds(int role, int M, int N, int K) {
     return bytes <= kRowsPathMaxLdsWide ? std::max(bytes, (size_t)81 * 1024) : 0;   // > half a CU's LDS: one per CU
   }
   return bytes <= kRowsPathMaxLds ? bytes : 0;
-}
-
-// The same for 5..7 rows, short k and more tiles than CUs: a work-group per tile here as well (the fragment-reading kernel at
-// 5 / 7 rows: 384 tiles, k = 768 7.2 / 7.8 us of a layer, 5.6 / 5.9 this way; 2000 tiles, k = 1024 14.7 / 15.6 against 12.8 /
-// 13.4; with work-groups that walk through the tiles it was the slower one).
-static size_t rows_many_tiles_lds(int role, int M, int N, int K) {
-  const size_t bytes = (size_t)K * M * 4 + (size_t)(gemm_slices(K, 1) + 1) * M * 16 * 4;
-  return M > 4 && M <= 7 && role != kRoleDown && K < 2048 && N / 16 > 256 && bytes <= kRowsPathMaxLds ? bytes : 0;
 }
 
 // Launch shape of k_gemm_bf16_wide: NT weight tiles per wave and NW waves that split the k chunks; nt == 0: the
@@ -1401,9 +1395,7 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
   const int S = gemm_slices(K, 1);
   const int NTILES = N / 16, KT = K / 32;
   const uint4* Wsw = static_cast<const uint4*>(W);
-  size_t rl = rows_path_lds(role, M, N, K);
-  if (!rl) rl = rows_many_tiles_lds(role, M, N, K);
-  if (rl) {
+  if (const size_t rl = rows_path_lds(role, M, N, K)) {
     // gate/up has several times more tiles than the chip has CUs: one work-group per CU that walks through its
     // share of the tiles (X block staged once, the next tile's first units requested before the epilogue, all
     // work-groups resident from the start and done together) streams better than a work-group per tile (7B, 1376

@@ -18,6 +18,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <tuple>
 #include <vector>
 
 #include "../include/stairs.h"
@@ -496,8 +497,8 @@ static void part1_fp32_attention_rows() {
       }
 }
 
-// The GEMM with the activation block in LDS at 5..7 rows: a work-group per tile where k is short, walking ones only where
-// every wave has a k chunk; the LDS it asks for exists.
+// The GEMM with the activation block in LDS at 5..7 rows: with a short k whatever the number of tiles; the LDS it asks for
+// exists.
 static void part1_rows_gemm() {
   for (int role : {stairs::kRoleQKV, stairs::kRoleWo, stairs::kRoleGateUp, stairs::kRoleDown, stairs::kRoleHead})
     for (int K = 256; K <= 16384; K += 256)
@@ -509,8 +510,7 @@ static void part1_rows_gemm() {
           CHECK(!stairs::wide_whole_chunk(M, chunks, 8) || chunks <= 4);   // (long k: the ring, not the whole chunk)
           CHECK(chunks > 4 || stairs::wide_whole_chunk(M, chunks, 8));
           if (M > 7) CHECK(lds == 0);
-          if (M > 4 && K < 2048 && N / 16 > 256) CHECK(lds == 0);
-          if (M > 4 && M <= 7 && role != stairs::kRoleDown && K < 2048 && N / 16 <= 256) CHECK(lds > 0);
+          if (M > 4 && M <= 7 && role != stairs::kRoleDown && K < 2048) CHECK(lds > 0 && lds <= stairs::kRowsPathMaxLds);
         }
 }
 
@@ -519,6 +519,14 @@ int main(int argc, char** argv) {
     for (int M : {8, 16, 17, 32, 33, 48, 64}) {
       const stairs::WideCfg c = stairs::wide_cfg(stairs::kRoleQKV, M, 768, 4096);
       std::printf("%d rows: %d/%d\n", M, c.nt, c.nw);
+    }
+    return 0;
+  }
+  if (argc > 1 && !std::strcmp(argv[1], "rows-max")) {     // rows of the LDS-resident GEMM under the caller's STAIRS_ROWS_MAX
+    for (const auto& [role, N, K] : {std::tuple{stairs::kRoleQKV, 2304, 768}, {stairs::kRoleHead, 32000, 1024}, {stairs::kRoleGateUp, 22016, 4096}}) {
+      int rows = 0;
+      while (stairs::rows_path_lds(role, rows + 1, N, K)) ++rows;
+      std::printf("%d x %d: %d\n", N, K, rows);
     }
     return 0;
   }

@@ -54,6 +54,19 @@ def test_forced_launch_shapes_reach_every_row_count(forced, want):
     assert out.split("\n")[:-1] == [f"{rows} rows: {shape}" for rows, shape in want.items()]
 
 
+@pytest.mark.parametrize("limit,want", [(None, 7), ("4", 4), ("2", 2)])
+def test_row_limit_of_the_lds_resident_gemm(limit, want):
+    """STAIRS_ROWS_MAX limits the rows of the GEMM with the activations in LDS for every projection: few tiles and many with a
+    short k, a long k."""
+    _build_if_stale()
+    env = dict(ENV)
+    env.pop("STAIRS_ROWS_MAX", None)
+    if limit:
+        env["STAIRS_ROWS_MAX"] = limit
+    out = subprocess.run([entry.SANITIZE_DRIVER, "rows-max"], capture_output=True, text=True, env=env, timeout=60).stdout
+    assert out.split("\n")[:-1] == [f"{shape}: {want}" for shape in ("2304 x 768", "32000 x 1024", "22016 x 4096")]
+
+
 @pytest.mark.gpu
 def test_every_kind_of_call_under_host_sanitizers():
     """GPU: the prebuilt driver (built on the CPU beforehand, never here) through prefill, generation, batches,
