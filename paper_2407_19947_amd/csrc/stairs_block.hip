@@ -1100,6 +1100,7 @@ __global__ __launch_bounds__(256) void k_shared_reduce(const float* __restrict__
 // the column tiles are empty: only residual-writing projections with 16 chunks and more (17 / 32 rows: 128 tiles x 8192 20.7 /
 // 24.9 -> 16.8 / 17.2, 256 x 11008 32.4 / 32.7 -> 27.0 / 27.2; the other 7B projections 1..6 us slower).
 bool shared_takes(int role, int M, int NTILES, int K) {
+  if (wide_cfg_is_forced(role)) return false;
   const bool resid = role == kRoleWo || role == kRoleDown;
   if (M <= 32) return M > 16 && resid && K > 15 * 512;
   if (resid) return !(NTILES <= 128 && K <= 2048);

@@ -126,6 +126,7 @@ size_t rows_path_lds(int role, int M, int N, int K);
 // launch shape of the GEMM that reads fragments (5..64 rows): weight tiles per wave, waves; nt == 0: the split-K kernel
 struct WideCfg { int nt, nw; };
 WideCfg wide_cfg(int role, int M, int NTILES, int K);
+bool wide_cfg_is_forced(int role);            // by STAIRS_WIDE_CFG
 
 // launch_gemm for 17..64 rows on the kernel that shares the activation fragments of a work-group through LDS; false: another
 // kernel is faster for the shape, nothing launched.  partial: room for (gemm_slices(K, 1) + 1) / 2 times M rounded up to 16

@@ -1110,9 +1110,9 @@ size_t rows_path_lds(int role, int M, int N, int K) {
 constexpr int wide_depth2(int depth1) { return depth1 <= 2 ? 1 : depth1 <= 3 ? 2 : depth1 <= 5 ? 3 : 5; }   // ring depth at two column tiles
 constexpr int wide_depth3(int depth1) { return depth1 <= 3 ? 1 : depth1 <= 5 ? 2 : 3; }                      // at three (33..48 rows)
 constexpr int wide_depth4(int depth1) { return depth1 <= 3 ? 1 : 2; }                                        // at four (49..64 rows; 3 spills at one tile)
-WideCfg wide_cfg(int role, int M, int NTILES, int K) {
-  // STAIRS_WIDE_CFG="nt/nw,nt/nw,nt/nw,nt/nw,nt/nw" (QKV, out, gate-up, down, head; nt = 0: split-K) overrides the
-  // choice: tuning aid
+// STAIRS_WIDE_CFG="nt/nw,nt/nw,nt/nw,nt/nw,nt/nw" (QKV, out, gate-up, down, head; nt = 0: split-K) sends the role's projections
+// of more than 4 rows to this kernel with that shape: tuning aid.  nullptr: not set, or not a shape there is.
+static const WideCfg* wide_forced(int role) {
   static const std::vector<WideCfg> forced = [] {
     std::vector<WideCfg> v;
     if (const char* e = getenv("STAIRS_WIDE_CFG")) {
@@ -1125,6 +1125,14 @@ WideCfg wide_cfg(int role, int M, int NTILES, int K) {
     }
     return v;
   }();
+  if ((int)forced.size() != 5) return nullptr;
+  const WideCfg& f = forced[role];
+  const bool ok = (f.nt == 0 || f.nt == 1 || f.nt == 2 || f.nt == 3 || f.nt == 4 || f.nt == 6 || f.nt == 8) && f.nw >= 1 && f.nw <= 8;
+  return ok ? &f : nullptr;
+}
+bool wide_cfg_is_forced(int role) { return wide_forced(role) != nullptr; }
+
+WideCfg wide_cfg(int role, int M, int NTILES, int K) {
   const int nchunks = gemm_slices(K, 1);
   // Measured on the 125M, 1B and 7B workloads (5..32 rows): about one work-group per CU, i.e. the smallest number of
   // tiles per wave (1, 2, 3, 4, 6, 8) that covers the matrix with at most 256 work-groups, as long as about 170 remain
@@ -1145,20 +1153,12 @@ WideCfg wide_cfg(int role, int M, int NTILES, int K) {
     const int nt = kNts[i];
     c = {nt, std::min(nt == 1 ? 8 : 4, nchunks)};
   }
-  bool free_nw = true;
-  if ((int)forced.size() == 5) {
-    const WideCfg f = forced[role];
-    if ((f.nt == 0 || f.nt == 1 || f.nt == 2 || f.nt == 3 || f.nt == 4 || f.nt == 6 || f.nt == 8) && f.nw >= 1 && f.nw <= 8) {
-      c = f;
-      free_nw = c.nt == 0;
-    }
-  }
-  if (M > 2 * 16) {                      // 33..64 rows: never split-K, which stops at two column tiles
+  const WideCfg* const f = wide_forced(role);
+  if (f) c = *f;
+  if (M > 2 * 16) {                      // 33..64 rows: never split-K, which stops at two column tiles; one tile per wave is built
     // 8 waves, two a SIMD, cover each other's waits for the fragments, which outweigh the weights here
-    if (c.nt == 0) c.nt = 1;
-    if (free_nw) c.nw = std::min(8, nchunks);
-    if (c.nt > 4) c.nt = 4;
-    if (c.nt == 3) c.nt = 4;
+    if (!f || f->nt == 0) c.nw = std::min(8, nchunks);
+    c.nt = 1;
   }
   return c;
 }
@@ -1442,7 +1442,6 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
   if (M > 16 && xfrag && launch_gemm_shared(role, W, N, K, xfrag, M, nrm, partial, epi, st)) return;
   // more than 4 rows with the activation fragments at hand: the hand-off-free kernel
   WideCfg wc = wide_cfg(role, M, NTILES, K);
-  if (M > kMaxRows) wc.nt = 1;             // (what shared_takes leaves to this kernel has at most 256 tiles)
   const int nchunks = gemm_slices(K, 1);
   auto wide_lds = [&](int nt) { return (size_t)nchunks * M * nt * 16 * sizeof(float); };
   while (wc.nt > 1 && wide_lds(wc.nt) > kWideMaxLds) wc.nt = wc.nt == 6 ? 4 : wc.nt == 3 ? 2 : wc.nt / 2;   // very long k: fewer tiles per work-group

@@ -516,9 +516,15 @@ static void part1_rows_gemm() {
 
 int main(int argc, char** argv) {
   if (argc > 1 && !std::strcmp(argv[1], "wide-cfg")) {     // the launch shapes under the caller's STAIRS_WIDE_CFG
-    for (int M : {8, 16, 17, 32, 33, 48, 64}) {
-      const stairs::WideCfg c = stairs::wide_cfg(stairs::kRoleQKV, M, 768, 4096);
-      std::printf("%d rows: %d/%d\n", M, c.nt, c.nw);
+    for (const auto& [role, tiles, K] : {std::tuple{stairs::kRoleQKV, 768, 4096}, {stairs::kRoleDown, 256, 11008}}) {
+      std::printf("%d x %d:", tiles, K);
+      for (int M : {8, 16, 17, 32, 33, 48, 64}) {
+        const stairs::WideCfg c = stairs::wide_cfg(role, M, tiles, K);
+        if (M > 16 && stairs::shared_takes(role, M, tiles, K)) std::printf(" shared");
+        else if (c.nt == 0) std::printf(" split");
+        else std::printf(" %d/%d", c.nt, c.nw);
+      }
+      std::printf("\n");
     }
     return 0;
   }

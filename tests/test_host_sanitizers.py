@@ -37,21 +37,22 @@ def test_argument_checks_under_host_sanitizers():
     assert "part 1 (no GPU): 0 failed checks" in res.stdout
 
 
-@pytest.mark.parametrize("forced,want", [
-    (None, {8: "3/4", 16: "3/4", 17: "3/4", 32: "3/4", 33: "4/8", 48: "4/8", 64: "4/8"}),
-    ("2/3", {8: "2/3", 16: "2/3", 17: "2/3", 32: "2/3", 33: "2/3", 48: "2/3", 64: "2/3"}),
-    ("0/5", {8: "0/5", 16: "0/5", 17: "0/5", 32: "0/5", 33: "1/8", 48: "1/8", 64: "1/8"}),
+@pytest.mark.parametrize("forced,qkv,down", [
+    (None, "3/4 3/4 3/4 3/4 shared shared shared", "split split shared shared shared shared shared"),
+    ("2/3", "2/3 2/3 2/3 2/3 1/3 1/3 1/3", "2/3 2/3 2/3 2/3 1/3 1/3 1/3"),
+    ("0/5", "split split split split 1/8 1/8 1/8", "split split split split 1/8 1/8 1/8"),
 ])
-def test_forced_launch_shapes_reach_every_row_count(forced, want):
-    """STAIRS_WIDE_CFG sets tiles per wave and waves of the fragment-reading GEMM at every row count (768 tiles, 8 chunks);
-    its 0 (split-K) does not exist beyond 32 rows."""
+def test_forced_launch_shapes_reach_every_row_count(forced, qkv, down):
+    """STAIRS_WIDE_CFG sends projections of 8, 16, 17, 32, 33, 48 and 64 rows to the fragment-reading GEMM with its tiles per wave
+    and waves, whichever kernel they take without it (768 tiles, 8 chunks; 256 tiles, 22 chunks).  Beyond 32 rows a wave has one
+    tile, and there is no split-K (0)."""
     _build_if_stale()
     env = dict(ENV)
     env.pop("STAIRS_WIDE_CFG", None)
     if forced:
         env["STAIRS_WIDE_CFG"] = ",".join([forced] * 5)
     out = subprocess.run([entry.SANITIZE_DRIVER, "wide-cfg"], capture_output=True, text=True, env=env, timeout=60).stdout
-    assert out.split("\n")[:-1] == [f"{rows} rows: {shape}" for rows, shape in want.items()]
+    assert out.split("\n")[:-1] == ["768 x 4096: " + qkv, "256 x 11008: " + down]
 
 
 @pytest.mark.parametrize("limit,want", [(None, 7), ("4", 4), ("2", 2)])
