@@ -1107,23 +1107,28 @@ bool shared_takes(int role, int M, int NTILES, int K) {
   return !(role == kRoleQKV && M < 48 && K <= 1024 && NTILES > 144 && NTILES <= 256);
 }
 
-bool launch_gemm_shared(int role, const void* W, int N, int K, const uint4* xfrag, int M, RowNorm nrm, float* partial, const GemmEpi& epi,
-                        hipStream_t st) {
-  const int NTILES = N / 16, blocks = (NTILES + 7) / 8, ksteps = K / 32, pairs = (gemm_slices(K, 1) + 1) / 2;
-  const bool paired_ct = role == kRoleQKV || role == kRoleGateUp;
-  if (M > kMaxFwdRows || !shared_takes(role, M, NTILES, K)) return false;
-  auto steps_us = [](int wgs, float ks) {                // as in launch_blk_gemm
+// whether the pairs of chunks go to different work-groups: the cheaper of the two by the model of launch_blk_gemm
+bool shared_splits(int M, int NTILES, int K) {
+  const int blocks = (NTILES + 7) / 8, ksteps = K / 32, pairs = (gemm_slices(K, 1) + 1) / 2;
+  if (pairs == 1) return false;
+  auto steps_us = [](int wgs, float ks) {
     const BlkShape& b = kBlkShapes[3];
     const int full = wgs / 512, rem = wgs % 512;
     return ks * (full * b.two + (rem > 256 ? b.one + (b.two - b.one) * (0.55f + 0.45f * (rem - 256) / 256) : rem == 0 ? 0.f : full ? 0.74f * b.one : b.one));
   };
-  const float one = steps_us(blocks, (float)ksteps);
-  const float two = pairs > 1 ? steps_us(blocks * pairs, 32.f) + 1.f + (2.f * pairs + 1.f) * M * N * 4 / 4.5e6f : 1e30f;
+  return steps_us(blocks * pairs, 32.f) + 1.f + (2.f * pairs + 1.f) * M * (NTILES * 16) * 4 / 4.5e6f < steps_us(blocks, (float)ksteps);
+}
+
+bool launch_gemm_shared(int role, const void* W, int N, int K, const uint4* xfrag, int M, RowNorm nrm, float* partial, const GemmEpi& epi,
+                        hipStream_t st) {
+  const int NTILES = N / 16, blocks = (NTILES + 7) / 8, pairs = (gemm_slices(K, 1) + 1) / 2;
+  const bool paired_ct = role == kRoleQKV || role == kRoleGateUp;
+  if (M > kMaxFwdRows || !shared_takes(role, M, NTILES, K)) return false;
   const uint4* Wsw = static_cast<const uint4*>(W);
 #define STAIRS_SHARED(split, stream, z)                                                                                            \
   hipLaunchKernelGGL((k_gemm_bf16_shared<split, stream>), dim3(blocks, 1, z), dim3(256), kShLds, st, Wsw, NTILES, xfrag, M, nrm, K, N, role, \
                      partial, epi)
-  if (two < one) {
+  if (shared_splits(M, NTILES, K)) {
     if (epi.stream_weights) STAIRS_SHARED(true, true, pairs); else STAIRS_SHARED(true, false, pairs);
     const dim3 grid((NTILES + 3) / 4, paired_ct ? (M + 31) / 32 : (M + 15) / 16);
     hipLaunchKernelGGL(paired_ct ? k_shared_reduce<2> : k_shared_reduce<1>, grid, dim3(256), 0, st, partial, pairs, M, nrm, K, N, role, epi);

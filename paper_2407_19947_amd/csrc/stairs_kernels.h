@@ -130,8 +130,9 @@ bool wide_cfg_is_forced(int role);            // by STAIRS_WIDE_CFG
 
 // launch_gemm for 17..64 rows on the kernel that shares the activation fragments of a work-group through LDS; false: another
 // kernel is faster for the shape, nothing launched.  partial: room for (gemm_slices(K, 1) + 1) / 2 times M rounded up to 16
-// times N floats.  shared_takes: the rule.
+// times N floats.  shared_takes: the rule; shared_splits: whether it is two kernels with partial sums in between.
 bool shared_takes(int role, int M, int NTILES, int K);
+bool shared_splits(int M, int NTILES, int K);
 bool launch_gemm_shared(int role, const void* W, int N, int K, const uint4* xfrag, int M, RowNorm nrm, float* partial, const GemmEpi& epi,
                         hipStream_t st);
 

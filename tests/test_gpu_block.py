@@ -188,3 +188,158 @@ def test_block_gemm_forms_have_the_same_bits(K, pieces, R):
     xs = hi.double()[:R] + lo.double()[:R]
     want, size = xs @ w.double().t(), xs.abs() @ w.double().abs().t()
     assert ((outs[0].double() - want).abs() <= 2 * K * 2.0 ** -24 * size).all()
+
+
+PLAIN, RESID, SWIGLU, QKV, RELU = range(5)             # kinds of a block projection
+
+
+@pytest.mark.parametrize("R", [23, 40, 240, 250])
+@pytest.mark.parametrize("kind", [PLAIN, RESID, SWIGLU, QKV, RELU])
+def test_every_result_of_a_block_gemm_has_the_same_bits_in_every_form(kind, R):
+    """What each kind leaves (values, fragments, sums of squares, caches), with the rows normalised where a kind is ever used
+    so: by the three tile shapes, the pieces added up in registers and by the second kernel.  264 tiles: the second kernel takes
+    two by two tiles from 250 rows on (16 column tiles) and one by two or two by one below (15 and fewer, odd numbers too); rows
+    that end inside a column tile."""
+    import torch
+    assert _cxx("_ZN6stairs17configure_kernelsEv", C.c_int)() == 0
+    launch = _cxx("_ZN6stairs18launch_blk_gemm_asEibRKNS_7BlkGemmEP12ihipStream_tPfm", C.c_int, C.c_int, C.c_bool,
+                  C.POINTER(_BlkGemm), C.c_void_p, C.c_void_p, C.c_size_t)
+    NT, K, pieces, hd, slots, cap = 264, 768, 3, 128, 3, 256
+    N, RT, da = NT * 16, (R + 127) // 128 * 8, NT * 16 // 3
+    assert (NT * ((R + 15) // 16) >= 4096) == (R == 250)
+    g = torch.Generator().manual_seed(100 * kind + R)
+    rand = lambda *s: torch.randn(*s, generator=g)
+    W = (rand(N * K) * 0.05).to(torch.bfloat16).cuda()
+    X = rand(K // 32 * RT * 1024).to(torch.bfloat16).cuda()
+    ssq = (rand(R, K // 32) ** 2 * 32).cuda() if kind != RESID else None
+    x0, gain = rand(R, N).cuda(), (1 + 0.3 * rand(N)).cuda()
+    cs = rand(R, 64, 2).cuda()
+    # rows of three sequences and padding rows, which leave no keys and values
+    slot = torch.arange(R) * slots // R
+    pos = torch.arange(R) - (slot * R + slots - 1) // slots
+    pos[5::9] = -1
+    at = torch.stack([slot, pos], 1).int().contiguous().cuda()
+    part = torch.empty(pieces * ((R + 15) // 16 * 16) * N, device="cuda")
+    results = []
+    for shape, split in ((1, False), (0, False), (3, False), (0, True), (1, True), (3, True)):
+        out = x0.clone() if kind == RESID else torch.full((R, N), float("nan"), device="cuda")
+        frag = torch.zeros(N // 32 * RT * 1024, dtype=torch.bfloat16, device="cuda")
+        ss = torch.zeros(R, N // 32, device="cuda")
+        Kc, Vc = (torch.zeros(slots * cap * da, dtype=torch.float16, device="cuda") for _ in range(2))
+        p = _BlkGemm(W=W.data_ptr(), NTILES=NT, K=K, XF=X.data_ptr(), RT=RT, R=R, kind=kind, out=out.data_ptr(), ldo=N,
+                     ssq=ssq.data_ptr() if ssq is not None else None, ssq_n=K // 32, eps=1e-5, frag_out=frag.data_ptr(), gain=gain.data_ptr(),
+                     ssq_out=ss.data_ptr(), rows=at.data_ptr(), cs=cs.data_ptr(), Kc=Kc.data_ptr(), Vc=Vc.data_ptr(),
+                     slot_stride=cap * da, cap=cap, hd=hd, da=da, pieces=pieces)
+        torch.cuda.synchronize()
+        assert launch(shape, split, C.byref(p), None, part.data_ptr(), part.numel()) == 0
+        torch.cuda.synchronize()
+        results.append([t.view(torch.int16) for t in (out, frag, ss, Kc, Vc)])
+    for n, (name, first) in enumerate(zip(("out", "frag", "ssq", "K", "V"), results[0])):
+        for r in results[1:]:
+            assert torch.equal(r[n], first), name
+    written = {PLAIN: (0,), RESID: (0, 1, 2), SWIGLU: (1,), QKV: (0, 3, 4), RELU: (1,)}[kind]
+    for n in written:
+        assert torch.count_nonzero(results[0][n]) > 0
+
+
+class _PosRef(C.Structure):
+    _fields_ = [("base", C.c_void_p), ("offset", C.c_int), ("rps", C.c_int)]
+
+
+class _RowNorm(C.Structure):
+    _fields_ = [("gain", C.c_void_p), ("ssq_part", C.c_void_p), ("ssq_n", C.c_int), ("eps", C.c_float)]
+
+
+class _GemmEpi(C.Structure):
+    """struct GemmEpi of csrc/stairs_kernels.h"""
+    _fields_ = [("counters", C.c_void_p), ("out", C.c_void_p), ("ssq_out", C.c_void_p), ("rope_cs", C.c_void_p), ("pos", _PosRef),
+                ("Kc", C.c_void_p), ("Vc", C.c_void_p), ("Kc32", C.c_void_p), ("Vc32", C.c_void_p), ("cap", C.c_int), ("H", C.c_int),
+                ("hd", C.c_int), ("kv_slot_stride", C.c_size_t), ("frag_out", C.c_void_p), ("frag_gain", C.c_void_p), ("act", C.c_int),
+                ("stream_weights", C.c_int)]
+
+
+R_QKV, R_WO, R_GATEUP, R_DOWN, R_HEAD = range(5)       # roles of a decode projection
+
+
+# tiles that end inside a work-group's eight; k of half a chunk, ends on half a chunk and on a whole one, odd and even numbers of
+# chunks, more than 8 pairs; one launch (split False) and two
+@pytest.mark.parametrize("role,tiles,K,hd,split", [
+    (R_QKV, 48, 256, 64, False), (R_QKV, 264, 2304, 128, True), (R_QKV, 1872, 1536, 128, False), (R_QKV, 1872, 2304, 64, False),
+    (R_GATEUP, 20, 768, 64, False), (R_GATEUP, 20, 2304, 64, True), (R_GATEUP, 1860, 1280, 64, False),
+    (R_HEAD, 19, 1024, 64, False), (R_HEAD, 19, 8448, 64, True), (R_HEAD, 1860, 2304, 64, False),
+    (R_WO, 130, 768, 64, False), (R_WO, 20, 4096, 64, True), (R_WO, 1860, 1280, 64, False),
+    (R_DOWN, 20, 8448, 64, True), (R_DOWN, 20, 7936, 64, True), (R_DOWN, 1860, 2304, 64, False)])
+def test_projections_of_17_to_64_rows_have_the_bits_of_one_row(role, tiles, K, hd, split):
+    """The projections that go to the kernel that shares the fragments through LDS: all they leave (values, sums of squares, the
+    next projection's fragments, keys and values of several sequences, one of them not active) against the same projection of
+    each row alone, which takes another kernel."""
+    import torch
+    assert _cxx("_ZN6stairs17configure_kernelsEv", C.c_int)() == 0
+    takes = _cxx("_ZN6stairs12shared_takesEiiii", C.c_bool, *[C.c_int] * 4)
+    splits = _cxx("_ZN6stairs13shared_splitsEiii", C.c_bool, *[C.c_int] * 3)
+    gemm = _cxx("_ZN6stairs11launch_gemmEiiPKviiPKfiiNS_7RowNormEPfRKNS_7GemmEpiEP12ihipStream_tPK15HIP_vector_typeIjLj4EE", None,
+                C.c_int, C.c_int, C.c_void_p, C.c_int, C.c_int, C.c_void_p, C.c_int, C.c_int, _RowNorm, C.c_void_p,
+                C.POINTER(_GemmEpi), C.c_void_p, C.c_void_p)
+    to_frag = _cxx("_ZN6stairs17launch_split_fragEPKfiiiS1_P15HIP_vector_typeIjLj4EEP12ihipStream_t", None,
+                   C.c_void_p, C.c_int, C.c_int, C.c_int, C.c_void_p, C.c_void_p, C.c_void_p)
+    frag_u4 = lambda k: (4 << 20) // 16 + (k + 31) // 32 * 256 + (k // 512 + 1) * 272         # frag_alloc_bytes
+    N, cap = tiles * 16, 32
+    resid = role in (R_WO, R_DOWN)
+    d, width = N // 3, N // 2 if role == R_GATEUP else N // 3 if role == R_QKV else N
+    g = torch.Generator().manual_seed(role + tiles + K)
+    rand = lambda *s: torch.randn(*s, generator=g)
+    W = (rand(N * K) * 0.05).to(torch.bfloat16).cuda()
+    chunks = (K + 511) // 512
+    partial = torch.empty((chunks + 1) * 32 * N, device="cuda")
+    counters = torch.zeros(2048, dtype=torch.int32, device="cuda")
+    for M, rps in ((33, 3), (47, 47), (48, 4), (64, 8)) + (((17, 17), (32, 2)) if resid and K > 15 * 512 else ()):
+        assert takes(role, M, tiles, K) and splits(M, tiles, K) == split
+        X, gain, next_gain = rand(M, K).cuda(), (1 + 0.3 * rand(K)).cuda(), (1 + 0.3 * rand(N)).cuda()
+        ssq, x0 = (rand(M, K // 16) ** 2 * 16).cuda(), rand(M, width).cuda()
+        cs = rand(M, 64, 2).cuda()
+        slots = M // rps
+        state = torch.tensor([[int(torch.randint(0, max(1, cap - rps), (1,), generator=g)), 0, 0, int(s != 1)] for s in range(slots)],
+                             dtype=torch.int32)
+        cap_m = cap if rps <= cap else 64
+        dstate = state.cuda()
+        xf = torch.zeros(frag_u4(K) * 8, dtype=torch.bfloat16, device="cuda")
+        to_frag(X.data_ptr(), K, M, K, None if resid else gain.data_ptr(), xf.data_ptr(), None)
+
+        def fresh():
+            out = x0.clone() if resid else torch.full((M, width), float("nan"), device="cuda")
+            ss = torch.zeros(M, tiles, device="cuda")
+            frag = torch.zeros(frag_u4(width) * 8, dtype=torch.bfloat16, device="cuda")
+            Kc, Vc = (torch.zeros(slots * cap_m * d if role == R_QKV else 8, dtype=torch.float16, device="cuda") for _ in range(2))
+            return out, ss, frag, Kc, Vc
+
+        def launch(out, ss, frag, Kc, Vc, first, n):   # rows first .. first + n - 1: all of them or one
+            one = n == 1
+            s = first // rps if one else 0
+            where = state[s].clone()
+            where[0] += first % rps if one else 0
+            base = where.cuda() if one else dstate
+            e = _GemmEpi(counters=counters.data_ptr(), out=out.data_ptr() + first * width * 4, ssq_out=ss.data_ptr() + first * tiles * 4,
+                         rope_cs=cs.data_ptr() + first * 512, pos=_PosRef(base.data_ptr(), 0, 1 if one else rps),
+                         Kc=Kc.data_ptr() + (s * cap_m * d * 2 if role == R_QKV else 0), Vc=Vc.data_ptr() + (s * cap_m * d * 2 if role == R_QKV else 0),
+                         cap=cap_m, H=d // hd, hd=hd, kv_slot_stride=cap_m * d, frag_out=None if one or role == R_QKV else frag.data_ptr(),
+                         frag_gain=None if role == R_GATEUP else next_gain.data_ptr(), act=int(role == R_HEAD and M == 48),
+                         stream_weights=int(M in (17, 33)))
+            nrm = _RowNorm() if resid else _RowNorm(gain.data_ptr(), ssq.data_ptr() + first * (K // 16) * 4, K // 16, 1e-5)
+            gemm(role, 1, W.data_ptr(), N, K, X.data_ptr() + first * K * 4, K, n, nrm, partial.data_ptr(), C.byref(e), None,
+                 None if one else xf.data_ptr())
+            torch.cuda.synchronize()
+
+        got, want = fresh(), fresh()
+        torch.cuda.synchronize()
+        launch(*got, 0, M)
+        for r in range(M):
+            launch(*want, r, 1)
+        if role != R_QKV:
+            to_frag(want[0].data_ptr(), width, M, width, None if role == R_GATEUP else next_gain.data_ptr(), want[2].data_ptr(), None)
+            torch.cuda.synchronize()
+        for name, a, b in zip(("out", "ssq", "frag", "K", "V"), got, want):
+            assert torch.equal(a.view(torch.int16), b.view(torch.int16)), (name, M)
+        inactive = slice(rps, 2 * rps) if role == R_QKV and slots > 1 else slice(0, 0)
+        kept = torch.ones(M, dtype=torch.bool)
+        kept[inactive] = False
+        assert torch.isfinite(got[0][kept.cuda()]).all() and torch.isnan(got[0][~kept.cuda()]).all()

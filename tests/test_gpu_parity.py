@@ -379,9 +379,9 @@ def test_wide_batches_on_the_block_kernels():
 
 @pytest.mark.parametrize("B,k", [(12, 2), (16, 2), (13, 3), (16, 3), (9, 6), (7, 8)])
 def test_batches_of_33_to_64_rows_equal_each_sequence_alone(B, k):
-    """36, 48, 52, 64, 63 and 63 rows per verification (three and four column tiles of the hand-off-free GEMM, the
-    second fragment block, draft steps of 2 B rows): still the weight-streaming kernels with one order of additions
-    per row, so every sequence is bit for bit the sequence generated alone, and so is graph replay vs plain launches."""
+    """36, 48, 52, 64, 63 and 63 rows per verification (three and four column tiles, the second fragment block, draft
+    steps of 2 B rows): still kernels with one order of additions per row, so every sequence's tokens are those of the
+    sequence generated alone, and so is graph replay vs plain launches."""
     w, target, draft = _batch_pair()
     lengths = [40, 1, 129, 128, 5, 77, 64, 33, 2, 100, 17, 90, 31, 65, 8, 127][:B]
     prompts = _prompts(w, lengths)
