@@ -1094,17 +1094,30 @@ __global__ __launch_bounds__(256) void k_shared_reduce(const float* __restrict__
   shared_epilogue<1, CT>(role, epi, M, N, sum, tile, ct0 * 16 + (lane & 15), lane >> 4, rs);   // (tile NTILES: nothing is stored)
 }
 
-// 33..64 rows, except residual-writing projections of few tiles with a short k (64 rows, 64 x 1024 9.3 us against 14.3; 128 x
-// 2048 12.9 against 13.6) and, below 48 rows, q | k | v of 1024-wide models (192 tiles, 33 / 40 / 48 / 64 rows 13.7 / 14.2 / 15.3 /
-// 18.5 against 14.3 / 14.6 / 14.8 / 15.7: one work-group per 128 features leaves most CUs idle).  17..32 rows, where half of
-// the column tiles are empty: only residual-writing projections with 16 chunks and more (17 / 32 rows: 128 tiles x 8192 20.7 /
-// 24.9 -> 16.8 / 17.2, 256 x 11008 32.4 / 32.7 -> 27.0 / 27.2; the other 7B projections 1..6 us slower).
+// 17..32 rows, where half of the column tiles are empty: only residual-writing projections with 16 chunks and more (17 / 32
+// rows: 128 tiles x 8192 20.7 / 24.9 -> 16.8 / 17.2, 256 x 11008 32.4 / 32.7 -> 27.0 / 27.2; the other 7B projections 1..6 us
+// slower).
+// 33..64 rows: a launch costs about the pace of one wave per SIMD over its k range, or over one pair of chunks and then the
+// second kernel, so where there are few tiles or the k is short the fragment-reading kernel is ahead.  That one fetches the
+// fragments, fresh from the launch before it, once per work-group: it loses with more rows, and 1.2 .. 1.8 us more inside a
+// forward than in launches by themselves, so the lines are from forwards (decoder models 512 to 2560 wide; us a layer with the
+// fragment-reading kernel instead of this one, at 33 / 48 / 64 rows):
+//   residual-writing, 32 x 512 -2.2 / -2.2 / -1.2, 64 x 1024 -6.6 / -6.3 / -6.2, 128 x 2048 -3.3 / -3.5 / -2.2, 48 x 2304 -3.0 / -3.0 / -1.9, 144 x
+//     2304 -2.4 / -2.5 / -2.0; 48 x 3072 -0.6 / -0.4 / +1.2, 96 x 3072 -0.4 / -0.5 / +1.0, 160 x 2560 -1.5 / -1.5 / -0.3; 80 x 3584 +1.4 / +1.6 /
+//     +3.2, 64 x 4096 +2.7 / +2.7 / +4.4, 128 x 4096 +2.4 / +2.4 / +4.2;
+//   QKV, 96 x 512 +8.9 / +12.7 / +18.9 (one chunk: a wave has the whole k), 144 x 768 +0.2 / +1.9 / +5.2, 192 x 1024 -0.7 / +0.3 / +3.3 (39 rows
+//     -0.2), 240 x 1280 -3.4 / -2.3 / +0.6, 288 x 1536 +0.9 / +2.0 / +5.7;
+//   gate and up, 384 x 768 +0.9 / +3.0 / +6.0, 256 x 1024 -1.7 / -0.4 / +2.7, 352 x 1024 -0.3 / +1.2 / +4.2, 512 x 1024 -0.5 / +1.6 / +4.0, 448 x 1280
+//     -3.5 / -3.1 / -0.3, 512 x 1536 -2.8 / -1.1 / +1.6, 512 x 2048 -1.9 / -0.8 / +1.7, 640 x 1280 -0.6 / +0.8 / +4.3, 704 x 2048 +3.4 / +4.2 / +7.3;
+//     unembeddings of few tiles go with them (launches by themselves: 256 x 1280 9.3 / 10.2 / 12.4 us, this kernel 13.6 / 13.7 / 13.9);
+//   unembedding of 32000 x 768 +5.3 / +8.2 / +12.6, x 2560 +29 / +33 / +44.
 bool shared_takes(int role, int M, int NTILES, int K) {
   if (wide_cfg_is_forced(role)) return false;
-  const bool resid = role == kRoleWo || role == kRoleDown;
+  const bool resid = role == kRoleWo || role == kRoleDown, three = M <= 48;
   if (M <= 32) return M > 16 && resid && K > 15 * 512;
-  if (resid) return !(NTILES <= 128 && K <= 2048);
-  return !(role == kRoleQKV && M < 48 && K <= 1024 && NTILES > 144 && NTILES <= 256);
+  if (resid) return !(NTILES <= 160 && K <= (three ? 3072 : 2304));
+  if (role == kRoleQKV) return !(NTILES <= 256 && K > 768 && M <= (K <= 1024 ? 40 : 48));
+  return !(three && K >= 1024 && K <= 2048 && (NTILES <= 256 || (K >= 1280 && NTILES <= 512)));
 }
 
 // whether the pairs of chunks go to different work-groups: the cheaper of the two by the model of launch_blk_gemm

@@ -1155,10 +1155,10 @@ WideCfg wide_cfg(int role, int M, int NTILES, int K) {
   }
   const WideCfg* const f = wide_forced(role);
   if (f) c = *f;
-  if (M > 2 * 16) {                      // 33..64 rows: never split-K, which stops at two column tiles; one tile per wave is built
+  if (M > 2 * 16) {                      // 33..64 rows: never split-K, which stops at two column tiles; up to 48 rows one or two tiles per wave, then one
     // 8 waves, two a SIMD, cover each other's waits for the fragments, which outweigh the weights here
     if (!f || f->nt == 0) c.nw = std::min(8, nchunks);
-    c.nt = 1;
+    c.nt = M <= 3 * 16 && c.nt >= 2 ? 2 : 1;
   }
   return c;
 }
@@ -1459,7 +1459,7 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
                          role, epi);                                                                                     \
   } while (0)
   // (two column tiles hold one k-step less in flight: a deeper ring would not fit the 256 registers of a wave)
-  // (three and four column tiles, one more: with one tile per wave only)
+  // (three and four column tiles, one more: see shared_takes)
 #define STAIRS_WIDE_CT2(nt, dp)        \
   if (CT == 1) STAIRS_WIDE(1, nt, dp); \
   else STAIRS_WIDE(2, nt, wide_depth2(dp))
@@ -1471,6 +1471,7 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
     else if (wc.nt == 6) { STAIRS_WIDE_CT2(6, kWideDepth6); }
     else if (wc.nt == 3) { STAIRS_WIDE_CT2(3, kWideDepth3); }
     else if (wc.nt == 4) { STAIRS_WIDE_CT2(4, kWideDepth4); }
+    else if (wc.nt == 2 && CT == 3) { STAIRS_WIDE(3, 2, wide_depth3(kWideDepth2)); }
     else if (wc.nt == 2) { STAIRS_WIDE_CT2(2, kWideDepth2); }
     else if (wide_whole_chunk(M, nchunks, wc.nw)) STAIRS_WIDE(1, 1, kWideDepthChunk);
     else { STAIRS_WIDE_CT(1, kWideDepth1); }
@@ -2706,6 +2707,7 @@ hipError_t configure_kernels() {
   optin((const void*)k_gemm_bf16_wide<1, 2, kWideDepth2, false, true>, kWideMaxLds);
   optin((const void*)k_gemm_bf16_wide<2, 1, wide_depth2(kWideDepth1), false, true>, kWideMaxLds);
   optin((const void*)k_gemm_bf16_wide<2, 2, wide_depth2(kWideDepth2), false, true>, kWideMaxLds);
+  STAIRS_OPTIN_WIDE(3, 2, kWideDepth2);
   STAIRS_OPTIN_WIDE(3, 1, kWideDepth1); STAIRS_OPTIN_WIDE(4, 1, kWideDepth1);
 #undef STAIRS_OPTIN_WIDE
 #undef STAIRS_OPTIN_WIDE_

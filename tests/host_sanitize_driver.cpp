@@ -514,6 +514,31 @@ static void part1_rows_gemm() {
         }
 }
 
+// 33..64 rows: the projections of models up to about 1500 wide at which the fragment-reading GEMM is ahead stay with it, the others
+// (more tiles, longer k, k of one chunk) share the fragments.
+static void part1_shared_gemm() {
+  auto rows = [](int role, int N, int K) {           // row counts for which the projection shares the fragments, first .. last
+    int first = 0, last = 0, n = 0;
+    for (int M = 33; M <= 64; ++M)
+      if (stairs::shared_takes(role, M, N / 16, K)) {
+        if (!n++) first = M;
+        last = M;
+      }
+    CHECK(n == (n ? last - first + 1 : 0) && (!n || last == 64));
+    return n ? first : 65;
+  };
+  CHECK(rows(stairs::kRoleQKV, 2304, 768) == 33 && rows(stairs::kRoleWo, 768, 768) == 65 && rows(stairs::kRoleDown, 768, 3072) == 49);
+  CHECK(rows(stairs::kRoleQKV, 3072, 1024) == 41 && rows(stairs::kRoleGateUp, 8192, 1024) == 33 && rows(stairs::kRoleDown, 1024, 4096) == 33);
+  CHECK(rows(stairs::kRoleQKV, 3840, 1280) == 49 && rows(stairs::kRoleGateUp, 7168, 1280) == 49 && rows(stairs::kRoleDown, 1280, 3584) == 33);
+  CHECK(rows(stairs::kRoleQKV, 4608, 1536) == 33 && rows(stairs::kRoleGateUp, 6144, 1536) == 49 && rows(stairs::kRoleDown, 1536, 4352) == 33);
+  CHECK(rows(stairs::kRoleQKV, 6144, 2048) == 33 && rows(stairs::kRoleWo, 2048, 2048) == 65 && rows(stairs::kRoleGateUp, 16384, 2048) == 33 &&
+        rows(stairs::kRoleDown, 2048, 8192) == 33);
+  CHECK(rows(stairs::kRoleWo, 2560, 2560) == 49 && rows(stairs::kRoleQKV, 12288, 4096) == 33 && rows(stairs::kRoleWo, 4096, 4096) == 33 &&
+        rows(stairs::kRoleGateUp, 22016, 4096) == 33 && rows(stairs::kRoleDown, 4096, 11008) == 33);
+  for (int N : {4096, 32000})
+    for (int K : {256, 512}) CHECK(rows(stairs::kRoleHead, N, K) == 33);
+}
+
 int main(int argc, char** argv) {
   if (argc > 1 && !std::strcmp(argv[1], "wide-cfg")) {     // the launch shapes under the caller's STAIRS_WIDE_CFG
     for (const auto& [role, tiles, K] : {std::tuple{stairs::kRoleQKV, 768, 4096}, {stairs::kRoleDown, 256, 11008}}) {
@@ -541,6 +566,7 @@ int main(int argc, char** argv) {
   part1_attention_early_keys();
   part1_fp32_attention_rows();
   part1_rows_gemm();
+  part1_shared_gemm();
   std::printf("part 1 (no GPU): %d failed checks\n", g_failed);
   std::fflush(stdout);
   int ndev = 0;

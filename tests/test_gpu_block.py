@@ -262,17 +262,19 @@ R_QKV, R_WO, R_GATEUP, R_DOWN, R_HEAD = range(5)       # roles of a decode proje
 
 
 # tiles that end inside a work-group's eight; k of half a chunk, ends on half a chunk and on a whole one, odd and even numbers of
-# chunks, more than 8 pairs; one launch (split False) and two
+# chunks, more than 8 pairs; one launch (split False) and two.  None: the fragment-reading kernel, with one and with two tiles
+# a wave
 @pytest.mark.parametrize("role,tiles,K,hd,split", [
     (R_QKV, 48, 256, 64, False), (R_QKV, 264, 2304, 128, True), (R_QKV, 1872, 1536, 128, False), (R_QKV, 1872, 2304, 64, False),
-    (R_GATEUP, 20, 768, 64, False), (R_GATEUP, 20, 2304, 64, True), (R_GATEUP, 1860, 1280, 64, False),
-    (R_HEAD, 19, 1024, 64, False), (R_HEAD, 19, 8448, 64, True), (R_HEAD, 1860, 2304, 64, False),
-    (R_WO, 130, 768, 64, False), (R_WO, 20, 4096, 64, True), (R_WO, 1860, 1280, 64, False),
-    (R_DOWN, 20, 8448, 64, True), (R_DOWN, 20, 7936, 64, True), (R_DOWN, 1860, 2304, 64, False)])
+    (R_GATEUP, 268, 768, 64, False), (R_GATEUP, 268, 2304, 64, True), (R_GATEUP, 1860, 1280, 64, False),
+    (R_HEAD, 522, 1024, 64, False), (R_HEAD, 19, 8448, 64, True), (R_HEAD, 1860, 2304, 64, False),
+    (R_WO, 522, 768, 64, False), (R_WO, 98, 4096, 64, True), (R_WO, 1860, 1280, 64, False),
+    (R_DOWN, 20, 8448, 64, True), (R_DOWN, 20, 7936, 64, True), (R_DOWN, 1860, 2304, 64, False),
+    (R_QKV, 240, 1280, 128, None), (R_GATEUP, 448, 1280, 64, None), (R_HEAD, 341, 1280, 64, None), (R_DOWN, 47, 2304, 64, None)])
 def test_projections_of_17_to_64_rows_have_the_bits_of_one_row(role, tiles, K, hd, split):
-    """The projections that go to the kernel that shares the fragments through LDS: all they leave (values, sums of squares, the
-    next projection's fragments, keys and values of several sequences, one of them not active) against the same projection of
-    each row alone, which takes another kernel."""
+    """The projections that go to the kernel that shares the fragments through LDS, and some at those row counts that do not: all
+    they leave (values, sums of squares, the next projection's fragments, keys and values of several sequences, one of them not
+    active) against the same projection of each row alone, which takes another kernel."""
     import torch
     assert _cxx("_ZN6stairs17configure_kernelsEv", C.c_int)() == 0
     takes = _cxx("_ZN6stairs12shared_takesEiiii", C.c_bool, *[C.c_int] * 4)
@@ -293,7 +295,9 @@ def test_projections_of_17_to_64_rows_have_the_bits_of_one_row(role, tiles, K, h
     partial = torch.empty((chunks + 1) * 32 * N, device="cuda")
     counters = torch.zeros(2048, dtype=torch.int32, device="cuda")
     for M, rps in ((33, 3), (47, 47), (48, 4), (64, 8)) + (((17, 17), (32, 2)) if resid and K > 15 * 512 else ()):
-        assert takes(role, M, tiles, K) and splits(M, tiles, K) == split
+        if split is None and M == 64 and not resid:
+            continue                                   # (shared there)
+        assert takes(role, M, tiles, K) == (split is not None) and (split is None or splits(M, tiles, K) == split)
         X, gain, next_gain = rand(M, K).cuda(), (1 + 0.3 * rand(K)).cuda(), (1 + 0.3 * rand(N)).cuda()
         ssq, x0 = (rand(M, K // 16) ** 2 * 16).cuda(), rand(M, width).cuda()
         cs = rand(M, 64, 2).cuda()

@@ -39,13 +39,13 @@ def test_argument_checks_under_host_sanitizers():
 
 @pytest.mark.parametrize("forced,qkv,down", [
     (None, "3/4 3/4 3/4 3/4 shared shared shared", "split split shared shared shared shared shared"),
-    ("2/3", "2/3 2/3 2/3 2/3 1/3 1/3 1/3", "2/3 2/3 2/3 2/3 1/3 1/3 1/3"),
+    ("2/3", "2/3 2/3 2/3 2/3 2/3 2/3 1/3", "2/3 2/3 2/3 2/3 2/3 2/3 1/3"),
     ("0/5", "split split split split 1/8 1/8 1/8", "split split split split 1/8 1/8 1/8"),
 ])
 def test_forced_launch_shapes_reach_every_row_count(forced, qkv, down):
     """STAIRS_WIDE_CFG sends projections of 8, 16, 17, 32, 33, 48 and 64 rows to the fragment-reading GEMM with its tiles per wave
-    and waves, whichever kernel they take without it (768 tiles, 8 chunks; 256 tiles, 22 chunks).  Beyond 32 rows a wave has one
-    tile, and there is no split-K (0)."""
+    and waves, whichever kernel they take without it (768 tiles, 8 chunks; 256 tiles, 22 chunks).  Beyond 32 rows a wave has at
+    most two tiles, beyond 48 one, and there is no split-K (0)."""
     _build_if_stale()
     env = dict(ENV)
     env.pop("STAIRS_WIDE_CFG", None)
