@@ -493,13 +493,15 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
   // more than 4 rows (bf16): every producer of an activation also leaves its MFMA operand fragments, with the gain of
   // the norm in front of the next projection folded in, and the projections take the hand-off-free kernel
   const bool fr = b && M > 4;
-  // more than kMaxRows rows exist only on the hand-off-free GEMM: every projection must fit it
+  // more than kMaxRows rows exist only on the hand-off-free GEMMs: every projection must fit the one that keeps its chunk sums
+  // in LDS (few take it: shared_takes; all do under STAIRS_WIDE_CFG)
   if (M > kMaxRows && !(fr && gemm_takes_rows(M, std::max(d, f))))
     return fail(c, STAIRS_EINVAL, "forward: more rows than the weight-streaming kernels take for this model");
-  if (!embedded)
-  launch_embed(m->tok_emb, b, c->tokens + (pos.rps ? 0 : (size_t)slot * c->tok_stride), pos.rps ? c->tok_stride : 0,
-               c->tok_stride, V, pos, M, d, c->x, c->ssq, m->hd, m->rope_tab, m->cap, c->rope_cs, st, fr ? c->xf : nullptr,
-               m->layers[0].attn_norm);
+  if (!embedded) {
+    launch_embed(m->tok_emb, b, c->tokens + (pos.rps ? 0 : (size_t)slot * c->tok_stride), pos.rps ? c->tok_stride : 0,
+                 c->tok_stride, V, pos, M, d, c->x, c->ssq, m->hd, m->rope_tab, m->cap, c->rope_cs, st, fr ? c->xf : nullptr,
+                 m->layers[0].attn_norm);
+  }
   SYNCPOINT();
   const RowNorm none{nullptr, nullptr, 0, 0.f};
   AttnMode amode{0.f, nullptr, 0, 0, 0, fr ? c->af : nullptr, 0};
@@ -719,9 +721,10 @@ int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logit
   const bool fr = M > 4;
   uint4* const xf = fr ? c->xf : nullptr;
   uint4* const af = fr ? c->af : nullptr;
-  if (!embedded)
-  launch_embed(m->tok_emb, 1, c->tokens, 0, c->tok_stride, V, pos, M, d, c->x, c->ssq, m->hd, nullptr, 0, c->rope_cs, st, xf,
-               m->dec[0].attn_norm);
+  if (!embedded) {
+    launch_embed(m->tok_emb, 1, c->tokens, 0, c->tok_stride, V, pos, M, d, c->x, c->ssq, m->hd, nullptr, 0, c->rope_cs, st, xf,
+                 m->dec[0].attn_norm);
+  }
   SYNCPOINT();
   const RowNorm none{nullptr, nullptr, 0, 0.f};
   const AttnMode self_mode{1.f, m->dec_bias, m->cap, m->cap - 1, 0, af, 0};
@@ -1853,9 +1856,8 @@ int stairs_reserve_batch(stairs_ctx* c, int32_t max_batch) {
     m->Vc = V;
     m->valid = 0;
   }
-  // several sequences: the decode kernels take forwards of up to kMaxFwdRows rows (the hand-off-free GEMM holds the
-  // chunk sums of all rows in LDS: k up to 16384), the block kernels up to kMaxBlockRows: logits, target tokens and
-  // attention partial results for that many rows
+  // several sequences: the decode kernels take forwards of up to kMaxFwdRows rows (k up to 16384: gemm_takes_rows), the block
+  // kernels up to kMaxBlockRows: logits, target tokens and attention partial results for that many rows
   const int want_rows = max_batch > kMaxRows / 2 ? kMaxBlockRows : max_batch >= 2 ? kMaxFwdRows : kMaxRows;
   if (c->rows_cap < want_rows) {
     const int Hmax = std::max(c->T.cfg.n_heads, c->have_draft ? c->D.cfg.n_heads : 0);

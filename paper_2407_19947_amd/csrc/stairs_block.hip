@@ -281,15 +281,15 @@ __device__ __forceinline__ void blk_epilogue(const BlkGemm& p, const f32x4 (&sum
 //   up in order: by different work-groups and k_blk_reduce (gridDim.z = pieces), or one after the other by the same
 //   work-group with a second set of accumulators (PIECED).  The bits depend on p.pieces alone, not on R, the tile shape
 //   or the grid.
-//   What bounds it: at thousands of rows the issue of MFMAs, 1.20 .. 1.30 PFLOP/s with plain stores in launches by
+//   What bounds it: at thousands of rows the issue of MFMAs, 1.23 .. 1.30 PFLOP/s with plain stores in launches by
 //   themselves (2047 rows, 7B projections; a library product of two 8192-wide matrices: 1.49 on the same card) and 1.07 over
 //   a profiled 2048-token prompt with its epilogues (matrix cores busy in 0.69 of the cycles, at 1.74 GHz: the card lowers its
 //   clock under this load, so fewer idle cycles gain less than they save); at a few hundred the rounds of work-groups and, with one work-group on a
-//   CU, the pace of a single wave per SIMD (0.38 us per k-step of 32 MFMAs, 0.25 of 16); at <= 64 rows the weights' way from memory.
+//   CU, the pace of a single wave per SIMD (kBlkShapes); at <= 64 rows the weights' way from memory.
 //   Plain stores, against the kernel before (weights through registers, 256 x 128 tiles only), 7B projections, us:
-//   2047 rows: QKV 384 -> 337, out 115 -> 112, gate/up 712 -> 603, down 297 -> 296; 333 rows: 111 -> 87, 45 -> 33,
-//   198 -> 143, 96 -> 79; 60 rows: 45 -> 28, 23 -> 19, 78 -> 48, 38 -> 29.  The SwiGLU epilogue costs less than plain stores
-//   (578 against 600 us).  (A first form of this loop read k-step s from LDS in front of its MFMAs: 0.52 us per k-step with
+//   2047 rows: QKV 384 -> 323, out 115 -> 107, gate/up 712 -> 600, down 297 -> 284; 333 rows: 111 -> 83, 45 -> 35,
+//   198 -> 140, 96 -> 75; 60 (now 64) rows: 45 -> 28, 23 -> 17, 78 -> 40, 38 -> 28.  The SwiGLU epilogue costs less than plain
+//   stores.  (A first form of this loop read k-step s from LDS in front of its MFMAs: 0.52 us per k-step with
 //   one work-group on a CU, whatever the depth of the ring.)
 template <int N> __device__ __forceinline__ void wait_copies_and_sync() {
   asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
@@ -621,10 +621,12 @@ __global__ __launch_bounds__(256) void k_blk_reduce(BlkGemm p, const float* __re
 
 // Tile shapes: features x rows of a work-group (two fit a CU), and the microseconds of a k-step with one work-group on the CU
 // and with two: fitted to 17 projections of the 125M, 1B, 7B and wide encoder widths at 12 row counts from 40 to 2047, every
-// shape and way of summing timed.  The third shape does half the work a step of the others in 0.27 (0.48 for two) of a
-// microsecond where they take 0.44 (0.84): it wins wherever it puts work on more CUs or the rounds come out better (us, the best
-// of the other two in brackets: 192 rows, 6144 x 2048 22.5 (25.5); 128 rows, 16384 x 2048 24.4 (32.8), 16384 x 1024 15.7
-// (21.4), 12288 x 4096 41.2 (44.4); 64 rows, 32000 x 2048 27.9 (36.6); 333 rows, 6144 x 768 15.1 (16.7)).  Shapes with larger
+// shape and way of summing timed, while the 256 x 64 shape still copied its weights into LDS.  Whole launches of 100 to 256
+// work-groups, k of 2048 and more, take 0.39 .. 0.57 (0.34 .. 0.57 since 256 x 64 loads its weights itself) and, the third
+// shape, 0.25 .. 0.42 us a k-step with their start and end.  The third shape does half the work a step of the others in a little
+// more than half the time: it wins wherever it puts work on more CUs or the rounds come out better (us, the best of the other two in
+// brackets: 192 rows, 6144 x 2048 21.1 (24.9); 128 rows, 16384 x 2048 22.7 (31.0), 16384 x 1024 14.8 (19.8), 12288 x 4096 37.7
+// (40.1); 64 rows, 32000 x 2048 26.8 (35.2); 333 rows, 6144 x 768 14.8 (15.2)).  Shapes with larger
 // wave tiles (256 x 256 on 8 waves, 256 x 128 and 192 x 128 on 4) were no faster at 2047 rows (7B gate/up 588, 633 and 617 us
 // against 602).  Two k-steps for each barrier (rings of two to four pairs) were slower in every shape (64 rows, 2048 x 8192
 // in one piece: 64 -> 77..83 us), deeper rings no faster.
@@ -686,8 +688,9 @@ int blk_pieces(int K) {
 // The tile shape and the way the pieces are summed, by a model of the launch's time: rounds of work-groups over the 256
 // CUs, each k-step at the rate of the shape's occupancy (a CU with two work-groups sets the pace as soon as there is one; a last
 // round of few is partly hidden behind the one before), the matrix at the rate memory delivers it, and for a split launch the
-// pieces' way through memory and the second kernel.  Over the launches kBlkShapes was fitted to the choice costs 1 % against
-// the best of all; two shapes and the model before 12 %.
+// pieces' way through memory and the second kernel.  Over 247 launches (19 projections, 40 to 2047 rows, timed with the kernels as
+// they are) the choice costs 0.8 % against the best of all, 18 % at most (768 x 3072, 777 rows: 20.6 against 17.4 us; 12288 x
+// 4096, 160 rows: 59.0 against 51.9); two shapes and the model before cost 12 %.
 hipError_t launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, size_t part_floats) {
   p.pieces = pieced ? blk_pieces(p.K) : 1;
   const int N = (p.NTILES - p.tile_first) * 16, ksteps = p.K / 32;
@@ -708,7 +711,9 @@ hipError_t launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, 
       us = std::max(us, (float)N * p.K * 2 / 5.9e6f);
       if (split) us += 1.f + (2.f * p.pieces + 1.f) * p.R * N * 4 / 4.5e6f;
       us += 0.001f * blocks;                // (equal rounds: fewer blocks read fewer operands)
-      // (the first two shapes are equal but for this: 2047 rows, 4096 features 122 / 298 us as squares, 125 / 303 the other way)
+      // (next to equal to the model; one piece, 2047 rows, as squares / the other way, us: 4096 x 4096 107 / 110, 2048 x 8192 112 /
+      // 114, but 4096 x 11008 284 / 280, 2048 x 2048 31.9 / 29.5.  Before the second shape loaded its weights itself 122 / 125 and
+      // 298 / 303 in the two 4096-feature ones)
       if (s == 0 && N <= 4096 && p.pieces == 1) us *= 0.98f;
       if (us < best_us) {
         best_us = us;

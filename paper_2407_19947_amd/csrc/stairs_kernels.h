@@ -149,7 +149,8 @@ constexpr size_t kFragHalfU4 = (4u << 20) / 16;
 inline size_t frag_bytes(int K) { return ((size_t)(K / 32) * 256 + (size_t)(K / 512 + 1) * kFragChunkPad) * 16; }   // one block of 32 rows
 inline size_t frag_alloc_bytes(int K) { return kFragHalfU4 * 16 + frag_bytes(K); }                                      // both blocks
 // frag = fragments of x [M, K] (row stride ldx) times gain (nullptr: none)
-// whether launch_gemm takes M > kMaxRows rows of a bf16 projection with k = K (the chunk sums of all rows fit the LDS)
+// whether launch_gemm takes M > kMaxRows rows of a bf16 projection with k = K (the chunk sums of all rows fit the LDS of
+// k_gemm_bf16_wide)
 bool gemm_takes_rows(int M, int K);
 void launch_split_frag(const float* X, int ldx, int M, int K, const float* gain, uint4* frag, hipStream_t st);
 

@@ -2254,9 +2254,11 @@ static void attn_dispatch(const float* q, const float* K, const float* V, int ca
   hipLaunchKernelGGL(k_attn_combine<HD>, dim3(H, M), dim3(HD), 0, st, part_o, part_ml, H, pos, nchunk_cap, out, d);
 }
 
-// Callers round the 128-key units of a launch up to a multiple of 4 at most, so its rows see more than (units - 4) of them
-// (the early steps of a proposal, whose launches are sized for its last, up to k - 1 keys fewer: inside the cache all the
-// same).  What lies below that is requested before the length is known, nothing else.  (The first chunk whole at any length: 3 rows
+// Callers round the 128-key units of a launch up to a multiple of 4 at most, so the longest rows it is sized for see more than
+// (units - 4) of them: what lies below that is requested before the length is known, nothing else.  Rows may see fewer, by up to
+// k - 1 keys in the early steps of a proposal, whose launches are sized for its last, and by up to k more in an iteration
+// launched while the one before it runs, which is sized for all of that one's tokens: those keys lie inside the cache all the
+// same, hold finite numbers and meet probability 0.  (The first chunk whole at any length: 3 rows
 // at contexts of 16 / 64 / 130 / 256 keys, 16 heads of 128: 5.2 / 5.1 / 5.2 / 5.2 us, now 4.7 / 4.7 / 4.8 / 5.2; 12 heads of
 // 64: 4.3 / 4.4 / 4.2 / 4.3, now 4.0 / 4.2 / 4.2 / 4.3; a head's chunk is 128 and 64 KiB.)  Several sequences: their lengths
 // differ, so each work-group looks its own up (64 slots of 16 heads, 3 rows, contexts of 16..210 keys: 27.3 -> 17.9 us; 16
@@ -2314,8 +2316,8 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
 // ---------------------------------------------------------------------------------------
 // One work-group per row, bound by its chain: the row through one CU, compares, lane exchanges, the waves' results, the store.
 // The position is requested first, the exchanges stay out of the LDS unit and the last thread reads the waves' results at once
-// (32000 logits: 5.4 -> AFTER us).  NEXT: the same work-group goes on with the token's embedding (a launch of 3.7 .. 4.7 us less
-// per draft token).
+// (32000 logits, launches of 1 and 5 rows inside a 125M call: 5.4 -> 4.8 us).  NEXT: the same work-group goes on with the token's
+// embedding (5.4 us and a launch of 4.6 become 6.4 per draft token).
 __device__ __forceinline__ void argmax_take(float& best, int& bi, float ov, int oi) {
   if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
 }

@@ -470,8 +470,10 @@ static void part1_block_gemm_launches() {
   CHECK(refused(0, false, 0));
 }
 
-// Attention requests no key before its launch knows the length unless every length the launch serves covers it: callers
-// count 128-key units and round them up to a multiple of 4 (a captured iteration serves all lengths of a multiple).
+// Attention requests no key before its launch knows the length unless every length the launch is sized for covers it: callers
+// count 128-key units and round them up to a multiple of 4 (a captured iteration serves all lengths of a multiple).  (Rows
+// shorter than that, of an early draft step or behind an iteration still running: the keys lie in the cache, whose room is
+// checked for the longest.)
 static void part1_attention_early_keys() {
   for (int len = 1; len <= 8300; ++len) {
     const int exact = (len + stairs::kAttnChunk - 1) / stairs::kAttnChunk;
