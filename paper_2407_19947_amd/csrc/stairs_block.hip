@@ -712,8 +712,10 @@ hipError_t launch_blk_gemm(BlkGemm p, bool pieced, hipStream_t st, float* part, 
       if (split) us += 1.f + (2.f * p.pieces + 1.f) * p.R * N * 4 / 4.5e6f;
       us += 0.001f * blocks;                // (equal rounds: fewer blocks read fewer operands)
       // (next to equal to the model; one piece, 2047 rows, as squares / the other way, us: 4096 x 4096 107 / 110, 2048 x 8192 112 /
-      // 114, but 4096 x 11008 284 / 280, 2048 x 2048 31.9 / 29.5.  Before the second shape loaded its weights itself 122 / 125 and
-      // 298 / 303 in the two 4096-feature ones)
+      // 114, but 4096 x 11008 284 / 280, 2048 x 2048 31.9 / 29.5.  From before the second shape loaded its weights itself: 122 / 125
+      // and 298 / 303 in the two 4096-feature ones.  By now about even: prompts of 1026 to 2048 tokens, ten widths from 768 to
+      // 4096, take 0.7 % less without this line on average, 4.1 % less at the most (4096 wide, 1600 tokens), 3.3 % more at the
+      // least (2560 wide, 1200))
       if (s == 0 && N <= 4096 && p.pieces == 1) us *= 0.98f;
       if (us < best_us) {
         best_us = us;
