@@ -910,8 +910,10 @@ __device__ __forceinline__ void copy_weights_to_lds(const uint4* base, uint32_t 
 }
 template <bool SPLIT, bool STREAM>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2)))
-void k_gemm_bf16_shared(const uint4* __restrict__ W, int NTILES, const uint4* __restrict__ XF, int M, RowNorm nrm, int K, int N, int role,
-                        float* part, GemmEpi epi) {
+void k_gemm_bf16_shared(const uint4* __restrict__ W, const uint4* __restrict__ XF, float* part, const float* __restrict__ gain, int K, int N,
+                        int M, int role, const float* __restrict__ ssq_part, int ssq_n, float eps, GemmEpi epi) {
+  const RowNorm nrm{gain, ssq_part, ssq_n, eps};
+  const int NTILES = N >> 4;
   constexpr int NT = 4, CT = 2, ST = kShST, AT = 8, STAGE = 16 * 64, PER = 4;   // (a stage: 8 weight tiles, 2 x 4 fragments)
   extern __shared__ uint4 lds[];
   __shared__ float s_rstd[64];
@@ -1146,8 +1148,8 @@ bool launch_gemm_shared(int role, const void* W, int N, int K, const uint4* xfra
   if (M > kMaxFwdRows || !shared_takes(role, M, NTILES, K)) return false;
   const uint4* Wsw = static_cast<const uint4*>(W);
 #define STAIRS_SHARED(split, stream, z)                                                                                            \
-  hipLaunchKernelGGL((k_gemm_bf16_shared<split, stream>), dim3(blocks, 1, z), dim3(256), kShLds, st, Wsw, NTILES, xfrag, M, nrm, K, N, role, \
-                     partial, epi)
+  hipLaunchKernelGGL((k_gemm_bf16_shared<split, stream>), dim3(blocks, 1, z), dim3(256), kShLds, st, Wsw, xfrag, partial, nrm.gain, K, N, \
+                     M, role, nrm.ssq_part, nrm.ssq_n, nrm.eps, epi)
   if (shared_splits(M, NTILES, K)) {
     if (epi.stream_weights) STAIRS_SHARED(true, true, pairs); else STAIRS_SHARED(true, false, pairs);
     const dim3 grid((NTILES + 3) / 4, paired_ct ? (M + 31) / 32 : (M + 15) / 16);

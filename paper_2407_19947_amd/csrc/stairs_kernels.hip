@@ -306,9 +306,11 @@ __device__ __forceinline__ void load_unit_in(const uint4* base, uint32_t off, ui
 }
 
 template <int CT, int NT, int ROLE, int SPW, bool STREAM>
-__global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw, int KT, int NTILES,
-                                                   const float* __restrict__ X, int ldx, int M,
-                                                   RowNorm nrm, int K, float* partial, int N, GemmEpi epi) {
+__global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw, const float* __restrict__ X,
+                                                  const float* __restrict__ gain, float* partial, int K, int N, int ldx, int M,
+                                                  const float* ssq_part, int ssq_n, float eps, GemmEpi epi) {
+  const RowNorm nrm{gain, ssq_part, ssq_n, eps};
+  const int KT = K >> 5, NTILES = N >> 4;
   // SPW = k chunks (512 wide) a work-group takes, one after the other through the same LDS buffer: 1, or 2 (then
   // it writes the sum of its two chunk sums, which halves the partial sums in memory; used for many rows)
   extern __shared__ uint4 lds[];   // [16 k-steps][CT][hi,lo][64 lanes]
@@ -472,8 +474,9 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
 // kernel: both give the same bits for a row.
 //   What bounds it: large matrices, the weights' way from memory; small ones the chain launch (1.6 us for an empty kernel
 //   in a graph, 1.9 with a load and a store) - arguments - x and weights - conversion - arithmetic - epilogue, i.e. round
-//   trips and the number of instructions one wave runs one after the other (4 cycles each).  So the arguments come in one
-//   round trip (want), a thread stages no more of x than there is for it (GP, Q), waves without a k chunk fetch no weights,
+//   trips and the number of instructions one wave runs one after the other (4 cycles each).  So what the first
+//   loads need comes in registers (the arguments in front of the structure: KERNEL_ARGS_IN_REGISTERS in binding.py; unembedding of one
+//   row and small layers 0.2 .. 0.3 us a launch), the rest in one round trip (want), a thread stages no more of x than there is for it (GP, Q), waves without a k chunk fetch no weights,
 //   the row statistics are summed beside the arithmetic by the waves with the least of it, everything that depends on the
 //   tile alone is scalar, and sums over lanes stay out of the LDS unit.  Layers of five launches in a graph, 200 keys,
 //   before / now, us: d 768 (ffn 3072) 1 / 3 / 5 rows 23.4 / 26.0 / 27.3 -> 21.7 / 22.6 / 24.5, d 1024 (ffn 4096) 23.9 /
@@ -502,15 +505,14 @@ __device__ __forceinline__ float lds_chunk_sum(const float* base, int stride, in
 // GP, Q: k groups (of 8 k) a thread stages in its first pass, threads that share the rows of a k group (covers
 // K <= 8 * 64 * NW * GP / Q: rows_kernel).  WALK: a work-group takes several tiles; else its only one is blockIdx.x.
 template <int R, int ROLE, int NW, int GP, int Q, bool WALK, bool STREAM, bool ROWMAJOR = false>
-__global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restrict__ Wsw, int NTILES,
-                                                            const float* __restrict__ X, int ldx, RowNorm nrm,
-                                                            int K, int N, GemmEpi epi) {
+__global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restrict__ Wsw, const float* __restrict__ X,
+                                                            const float* __restrict__ gain, const float* __restrict__ ssq_part,
+                                                            int K, int N, int ldx, int ssq_n, float* out, float eps, GemmEpi epi) {
   constexpr int NTH = 64 * NW, NG = NTH / Q, RP = (R + Q - 1) / Q;
   constexpr bool NORMED = ROLE != kRoleWo && ROLE != kRoleDown;      // (the residual-writing projections' inputs are not)
   extern __shared__ uint4 lds[];
   __shared__ float s_rstd[8];
-  want(Wsw); want(NTILES); want(X); want(ldx); want(K); want(N); want(epi.out);
-  if (NORMED) { want(nrm.gain); want(nrm.ssq_part); want(nrm.ssq_n); }
+  const int NTILES = N >> 4;
   if (ROLE == kRoleQKV) { want(epi.rope_cs); want(epi.pos.base); want(epi.pos.offset); want(epi.pos.rps); want(epi.Kc); want(epi.Vc); want(epi.cap); want(epi.hd); }
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // a work-group takes the tiles blockIdx.x, blockIdx.x + gridDim.x, ...: the X block is staged once for all of them
@@ -535,7 +537,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
 
   // first pass over the X block: a thread takes RP rows of k group kg (the gain is per k, so it is fetched once).  These
   // loads (x, gain, row statistics) go out before the weights, so they are not queued behind them.
-  const bool scale = NORMED && nrm.gain != nullptr;
+  const bool scale = NORMED && gain != nullptr;
   float4 xa[GP][RP], xb[GP][RP], ga[GP], gb[GP];
   const int kg0 = tid & (NG - 1), m0 = tid / NG;           // this thread's first k group and first row (rows m0, m0 + Q, ...)
 #pragma unroll
@@ -546,8 +548,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
     // compiler can then count them exactly and later waits do not have to cover the weight loads as well
     const uint32_t k4 = (uint32_t)min(kg0 + NG * j, KG - 1) * 32u;
     if (scale) {
-      ga[j] = ld_at<float4>(nrm.gain, k4);
-      gb[j] = ld_at<float4>(nrm.gain, k4 + 16u);
+      ga[j] = ld_at<float4>(gain, k4);
+      gb[j] = ld_at<float4>(gain, k4 + 16u);
     }
 #pragma unroll
     for (int i = 0; i < RP; ++i) {
@@ -559,16 +561,16 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
   // row statistics: half a wave per row, the last waves first (with a short k those have no weights to multiply).  The
   // first 256 partials of the row are requested here (indices clamped, values masked later); they are added up beside the
   // arithmetic, in the order rows_rstd uses: the 1/rms multiplies the finished sums in the epilogue.
-  const bool has_stats = scale && nrm.ssq_part;
+  const bool has_stats = scale && ssq_part;
   const int st_row = 2 * NW - 1 - (tid >> 5), st_pl = lane & 31;
   float sv[8];
   if (has_stats) {
-    const uint32_t row = (uint32_t)min(st_row, R - 1) * nrm.ssq_n;
+    const uint32_t row = (uint32_t)min(st_row, R - 1) * ssq_n;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) sv[i] = ld_at<float>(nrm.ssq_part, (row + min(st_pl + 32 * i, nrm.ssq_n - 1)) * 4u);
-    if (nrm.ssq_n > 64) {
+    for (int i = 0; i < 2; ++i) sv[i] = ld_at<float>(ssq_part, (row + min(st_pl + 32 * i, ssq_n - 1)) * 4u);
+    if (ssq_n > 64) {
 #pragma unroll
-      for (int i = 2; i < 8; ++i) sv[i] = ld_at<float>(nrm.ssq_part, (row + min(st_pl + 32 * i, nrm.ssq_n - 1)) * 4u);
+      for (int i = 2; i < 8; ++i) sv[i] = ld_at<float>(ssq_part, (row + min(st_pl + 32 * i, ssq_n - 1)) * 4u);
     }
   }
 
@@ -580,7 +582,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
   int q_pos = 0;
   float2 q_cs = make_float2(1.f, 0.f);
   auto request_operands = [&](int tile) {
-    if (!NORMED) x_old = ld_at<float>(epi.out, ((uint32_t)min(tid >> 4, R - 1) * N + tile * 16 + (tid & 15)) * 4u);
+    if (!NORMED) x_old = ld_at<float>(out, ((uint32_t)min(tid >> 4, R - 1) * N + tile * 16 + (tid & 15)) * 4u);
     if (ROLE == kRoleQKV) {                                // (v tiles: some valid entry)
       const int c = (tile - (tile >= part_tiles ? part_tiles : 0) - (tile >= 2 * part_tiles ? part_tiles : 0)) * 16;
       q_cs = ld_at<float2>(epi.rope_cs, (uint32_t)(min(tid >> 3, R - 1) * 64 + ((c & (epi.hd - 1)) >> 4) * 8 + (tid & 7)) * 8u);
@@ -622,8 +624,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
     for (int kg = NTH * GP + tid; kg < KG; kg += NTH) {
       float4 g0 = make_float4(1.f, 1.f, 1.f, 1.f), g1 = g0;
       if (scale) {
-        g0 = ld_at<float4>(nrm.gain, kg * 32u);
-        g1 = ld_at<float4>(nrm.gain, kg * 32u + 16u);
+        g0 = ld_at<float4>(gain, kg * 32u);
+        g1 = ld_at<float4>(gain, kg * 32u + 16u);
       }
 #pragma unroll
       for (int m = 0; m < R; ++m) {
@@ -638,22 +640,22 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
     if (has_stats && wave >= NW - (R + 1) / 2) {           // (whole waves)
       float ss = 0.f;
 #pragma unroll
-      for (int i = 0; i < 2; ++i) ss += (st_pl + 32 * i < nrm.ssq_n) ? sv[i] : 0.f;
-      if (nrm.ssq_n > 64) {
+      for (int i = 0; i < 2; ++i) ss += (st_pl + 32 * i < ssq_n) ? sv[i] : 0.f;
+      if (ssq_n > 64) {
 #pragma unroll
-        for (int i = 2; i < 8; ++i) ss += (st_pl + 32 * i < nrm.ssq_n) ? sv[i] : 0.f;
-        if (nrm.ssq_n > 256 && st_row < R) {
-          for (int p0 = st_pl + 256; p0 < nrm.ssq_n; p0 += 256) {
+        for (int i = 2; i < 8; ++i) ss += (st_pl + 32 * i < ssq_n) ? sv[i] : 0.f;
+        if (ssq_n > 256 && st_row < R) {
+          for (int p0 = st_pl + 256; p0 < ssq_n; p0 += 256) {
             float v[8];
 #pragma unroll
-            for (int i = 0; i < 8; ++i) v[i] = (p0 + 32 * i < nrm.ssq_n) ? nrm.ssq_part[st_row * nrm.ssq_n + p0 + 32 * i] : 0.f;
+            for (int i = 0; i < 8; ++i) v[i] = (p0 + 32 * i < ssq_n) ? ssq_part[st_row * ssq_n + p0 + 32 * i] : 0.f;
 #pragma unroll
             for (int i = 0; i < 8; ++i) ss += v[i];
           }
         }
       }
       ss = half_wave_sum(ss);
-      if (st_pl == 0 && st_row < R) s_rstd[st_row] = 1.0f / sqrtf(ss / (float)K + nrm.eps);
+      if (st_pl == 0 && st_row < R) s_rstd[st_row] = 1.0f / sqrtf(ss / (float)K + eps);
     }
   };
   // (long k: in front of the barrier, every wave has weights to multiply behind it)
@@ -716,7 +718,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
     if (tid < R * 16) {
       const int m = tid >> 4, n = tid & 15;
       const float a = chunk_sum(m, n) + x_old;
-      epi.out[(size_t)m * N + tile * 16 + n] = a;
+      out[(size_t)m * N + tile * 16 + n] = a;
       const float sq = tile_sumsq(a);
       if (n == 0) epi.ssq_out[m * (N >> 4) + tile] = sq;
       // more than 4 rows: the next projection may take the kernel that reads activation fragments
@@ -742,8 +744,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
         a = fmaxf(a, 0.f);
         b = fmaxf(b, 0.f);
       }
-      epi.out[(size_t)m * N + col] = a;
-      epi.out[(size_t)m * N + col + 8] = b;
+      out[(size_t)m * N + col] = a;
+      out[(size_t)m * N + col + 8] = b;
       if (R > 4 && epi.frag_out) {
         const float4 va = make_float4(dpp<kDppQuad0>(a), dpp<kDppQuad1>(a), dpp<kDppQuad2>(a), dpp<kDppQuad3>(a));
         const float4 vb = make_float4(dpp<kDppQuad0>(b), dpp<kDppQuad1>(b), dpp<kDppQuad2>(b), dpp<kDppQuad3>(b));
@@ -754,7 +756,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
       }
     } else if (ROLE == kRoleGateUp) {
       const float o = swiglu(a, b);
-      epi.out[(size_t)m * (N >> 1) + tile * 8 + j] = o;
+      out[(size_t)m * (N >> 1) + tile * 8 + j] = o;
       if (R > 4 && epi.frag_out) {
         const float4 vo = make_float4(dpp<kDppQuad0>(o), dpp<kDppQuad1>(o), dpp<kDppQuad2>(o), dpp<kDppQuad3>(o));
         if ((j & 3) == 0) store_frag4(epi.frag_out, m, tile * 8 + j, vo, nullptr);
@@ -771,7 +773,7 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
         const int e = (w >> 4) * 8 + j;
         const float2 r = rope_rotate(a, b, q_cs);
         if (part == 0) {
-          float* dst = epi.out + (size_t)m * (part_tiles * 16) + h * epi.hd + e;
+          float* dst = out + (size_t)m * (part_tiles * 16) + h * epi.hd + e;
           dst[0] = r.x;
           dst[half] = r.y;
         } else {
@@ -921,9 +923,11 @@ __device__ __forceinline__ void gemm_epilogue_lds(const float* csum, int nchunks
 }
 
 template <int CT, int NT, int DEPTH, bool STREAM, bool ROWMAJOR = false>     // (ROWMAJOR as above)
-__global__ __launch_bounds__(512) void k_gemm_bf16_wide(const uint4* __restrict__ Wsw, int NTILES,
-                                                        const uint4* __restrict__ XF, int M, RowNorm nrm, int K, int N,
-                                                        int role, GemmEpi epi) {
+__global__ __launch_bounds__(512) void k_gemm_bf16_wide(const uint4* __restrict__ Wsw, const uint4* __restrict__ XF,
+                                                        const float* __restrict__ gain, const float* __restrict__ ssq_part, int K, int N,
+                                                        int M, int role, int ssq_n, float eps, GemmEpi epi) {
+  const RowNorm nrm{gain, ssq_part, ssq_n, eps};
+  const int NTILES = N >> 4;
   constexpr int RING = DEPTH < kWideDepthChunk ? DEPTH + 1 : DEPTH;
   constexpr int W = NT * 16;
   extern __shared__ float csum[];                          // [chunk][M][W]
@@ -1187,7 +1191,7 @@ bool launch_gemm_rowmajor(const uint16_t* W, int N, int K, const float* X, int M
   const size_t rl = rows_path_lds(kRoleHead, M, N, K);
   if (rl && M <= 4) {
 #define STAIRS_ROWM(r) \
-  hipLaunchKernelGGL((rows_kernel<r, kRoleHead, 4, 2, false, true>(K, false)), dim3(NTILES), dim3(256), rl, st, Wr, NTILES, X, K, none, K, N, e)
+  hipLaunchKernelGGL((rows_kernel<r, kRoleHead, 4, 2, false, true>(K, false)), dim3(NTILES), dim3(256), rl, st, Wr, X, none.gain, none.ssq_part, K, N, K, none.ssq_n, e.out, none.eps, e)
     if (M == 1) STAIRS_ROWM(1);
     else if (M == 2) STAIRS_ROWM(2);
     else if (M == 3) STAIRS_ROWM(3);
@@ -1202,7 +1206,7 @@ bool launch_gemm_rowmajor(const uint16_t* W, int N, int K, const float* X, int M
   launch_split_frag(X, K, M, K, nullptr, frag, st);
   const dim3 grid((NTILES + nt - 1) / nt), block(64 * nw);
 #define STAIRS_WIDEM(ct, nt, dp) \
-  hipLaunchKernelGGL((k_gemm_bf16_wide<ct, nt, dp, false, true>), grid, block, lds, st, Wr, NTILES, frag, M, none, K, N, (int)kRoleHead, e)
+  hipLaunchKernelGGL((k_gemm_bf16_wide<ct, nt, dp, false, true>), grid, block, lds, st, Wr, frag, none.gain, none.ssq_part, K, N, M, (int)kRoleHead, none.ssq_n, none.eps, e)
   if (M <= 16) {
     if (nt == 1) STAIRS_WIDEM(1, 1, kWideDepth1);
     else STAIRS_WIDEM(1, 2, kWideDepth2);
@@ -1233,8 +1237,9 @@ __device__ __forceinline__ float rows_sum4(const float (&v)[MR], int q) {
   return wave_sums4(v[q], q + 1 < MR ? v[min(q + 1, MR - 1)] : 0.f, q + 2 < MR ? v[min(q + 2, MR - 1)] : 0.f, q + 3 < MR ? v[min(q + 3, MR - 1)] : 0.f);
 }
 template <int MR, int ROLE>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MR >= 6 ? 2 : 4, MR >= 6 ? 2 : 8))) void k_gemm_f32(const float* __restrict__ W, int N, int K,
-                                                  const float* __restrict__ X, int ldx, int M, RowNorm nrm, GemmEpi epi) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MR >= 6 ? 2 : 4, MR >= 6 ? 2 : 8))) void k_gemm_f32(const float* __restrict__ W, const float* __restrict__ X,
+                                                  const float* __restrict__ gain, float* out, int N, int K, int ldx, int M, const int* pos_base,
+                                                  float eps, GemmEpi epi) {
   constexpr bool NORMED = ROLE == kRoleQKV || ROLE == kRoleGateUp || ROLE == kRoleLogits;
   const int lane = threadIdx.x & 63;
   const int pr = blockIdx.x * 4 + (threadIdx.x >> 6);                 // feature pair
@@ -1261,9 +1266,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MR >= 6 ? 2
   float2 old = make_float2(0.f, 0.f), cs = make_float2(1.f, 0.f);
   int pos = 0;
   if (mine) {
-    if (ROLE == kRoleWo || ROLE == kRoleDown) old = *reinterpret_cast<const float2*>(epi.out + (size_t)row * N + n0);
+    if (ROLE == kRoleWo || ROLE == kRoleDown) old = *reinterpret_cast<const float2*>(out + (size_t)row * N + n0);
     if (ROLE == kRoleQKV) {
-      pos = *epi.pos.base + epi.pos.offset + row;
+      pos = *pos_base + epi.pos.offset + row;
       if (part < 2) cs = epi.rope_cs[row * 64 + e];
     }
   }
@@ -1279,7 +1284,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MR >= 6 ? 2
   for (int k = lane * 4; k < K; k += 256) {
     const float4 w0 = *reinterpret_cast<const float4*>(W + (size_t)n0 * K + k), w1 = *reinterpret_cast<const float4*>(W + (size_t)n1 * K + k);
     float4 g = make_float4(1.f, 1.f, 1.f, 1.f), x[MR];
-    if (NORMED && nrm.gain) g = *reinterpret_cast<const float4*>(nrm.gain + k);
+    if (NORMED && gain) g = *reinterpret_cast<const float4*>(gain + k);
 #pragma unroll
     for (int i = 0; i < MR; ++i) x[i] = *reinterpret_cast<const float4*>(xr[i] + k);
 #pragma unroll
@@ -1294,10 +1299,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MR >= 6 ? 2
     }
   }
   // (1/rms goes onto the lanes' sums, not onto the finished one: 64 roundings that average out instead of one that stays)
-  if (NORMED && nrm.gain) {
+  if (NORMED && gain) {
 #pragma unroll
     for (int q = 0; q < MR; q += 4) {
-      const float r4 = 1.0f / sqrtf(rows_sum4<MR>(ss, q) / (float)K + nrm.eps);
+      const float r4 = 1.0f / sqrtf(rows_sum4<MR>(ss, q) / (float)K + eps);
 #pragma unroll
       for (int i = q; i < MR && i < q + 4; ++i) {
         const float r = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(r4), (i - q) * 16));
@@ -1315,18 +1320,18 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MR >= 6 ? 2
   }
   if (!mine) return;
   if (ROLE == kRoleWo || ROLE == kRoleDown) {
-    *reinterpret_cast<float2*>(epi.out + (size_t)row * N + n0) = make_float2(__fadd_rn(old.x, v0), __fadd_rn(old.y, v1));
+    *reinterpret_cast<float2*>(out + (size_t)row * N + n0) = make_float2(__fadd_rn(old.x, v0), __fadd_rn(old.y, v1));
   } else if (ROLE == kRoleGateUp) {
-    epi.out[(size_t)row * (N / 2) + pr] = swiglu(v0, v1);
+    out[(size_t)row * (N / 2) + pr] = swiglu(v0, v1);
   } else if (ROLE == kRoleHead || ROLE == kRoleLogits) {
-    *reinterpret_cast<float2*>(epi.out + (size_t)row * N + n0) = make_float2(v0, v1);
+    *reinterpret_cast<float2*>(out + (size_t)row * N + n0) = make_float2(v0, v1);
   } else if (pos >= 0) {
     if (part < 2) {
       const float2 r = rope_rotate(v0, v1, cs);
       v0 = r.x;
       v1 = r.y;
     }
-    float* dst = part == 0 ? epi.out + (size_t)row * d + h * epi.hd + e
+    float* dst = part == 0 ? out + (size_t)row * d + h * epi.hd + e
                            : (part == 1 ? epi.Kc32 : epi.Vc32) + ((size_t)h * epi.cap + pos) * epi.hd + e;
     dst[0] = v0;
     dst[half] = v1;
@@ -1366,7 +1371,7 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
   if (!dtype_bf16) {
     const dim3 grid((N / 2 + 3) / 4), block(256);
     const float* Wf = static_cast<const float*>(W);
-#define STAIRS_F32(mr, role) launch_gemm_kernel(k_gemm_f32<mr, role>, grid, block, (size_t)0, st, Wf, N, K, X, ldx, M, nrm, epi)
+#define STAIRS_F32(mr, role) launch_gemm_kernel(k_gemm_f32<mr, role>, grid, block, (size_t)0, st, Wf, X, nrm.gain, epi.out, N, K, ldx, M, epi.pos.base, nrm.eps, epi)
 #define STAIRS_F32_ROLE(role)               \
   do {                                      \
     if (M <= 1) STAIRS_F32(1, role);        \
@@ -1393,7 +1398,7 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
     return;
   }
   const int S = gemm_slices(K, 1);
-  const int NTILES = N / 16, KT = K / 32;
+  const int NTILES = N / 16;
   const uint4* Wsw = static_cast<const uint4*>(W);
   if (const size_t rl = rows_path_lds(role, M, N, K)) {
     // gate/up has several times more tiles than the chip has CUs: one work-group per CU that walks through its
@@ -1413,7 +1418,7 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
     const size_t rl_launch = tpw > 1 ? std::max(rl, (size_t)81 * 1024) : rl;
 #define STAIRS_ROWS(r, role, nw, gp)                                                                                    \
   launch_gemm_kernel(epi.stream_weights ? rows_kernel<r, role, nw, gp, true>(K, tpw > 1) : rows_kernel<r, role, nw, gp, false>(K, tpw > 1), rgrid, \
-                     dim3(64 * nw), rl_launch, st, Wsw, NTILES, X, ldx, nrm, K, N, epi)
+                     dim3(64 * nw), rl_launch, st, Wsw, X, nrm.gain, nrm.ssq_part, K, N, ldx, nrm.ssq_n, epi.out, nrm.eps, epi)
 #define STAIRS_ROWS_ROLE4(role, nw, gp)          \
   if (M <= 1) STAIRS_ROWS(1, role, nw, gp);      \
   else if (M == 2) STAIRS_ROWS(2, role, nw, gp); \
@@ -1452,11 +1457,11 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
 #define STAIRS_WIDE(ct, nt, dp)                                                                                          \
   do {                                                                                                                   \
     if (epi.stream_weights)                                                                                              \
-      launch_gemm_kernel(k_gemm_bf16_wide<ct, nt, dp, true>, grid, block, lds, st, Wsw, NTILES, xfrag, M, nrm, K, N,     \
-                         role, epi);                                                                                     \
+      launch_gemm_kernel(k_gemm_bf16_wide<ct, nt, dp, true>, grid, block, lds, st, Wsw, xfrag, nrm.gain, nrm.ssq_part,   \
+                         K, N, M, role, nrm.ssq_n, nrm.eps, epi);                                                                                     \
     else                                                                                                                 \
-      launch_gemm_kernel(k_gemm_bf16_wide<ct, nt, dp, false>, grid, block, lds, st, Wsw, NTILES, xfrag, M, nrm, K, N,    \
-                         role, epi);                                                                                     \
+      launch_gemm_kernel(k_gemm_bf16_wide<ct, nt, dp, false>, grid, block, lds, st, Wsw, xfrag, nrm.gain, nrm.ssq_part,  \
+                         K, N, M, role, nrm.ssq_n, nrm.eps, epi);                                                                                     \
   } while (0)
   // (two column tiles hold one k-step less in flight: a deeper ring would not fit the 256 registers of a wave)
   // (three and four column tiles, one more: see shared_takes)
@@ -1494,11 +1499,11 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
 #define STAIRS_GEMM(ct, nt, role, spw) \
   do {                                                                                                                \
     if (epi.stream_weights)                                                                                           \
-      launch_gemm_kernel(k_gemm_bf16<ct, nt, role, spw, true>, grid, block, lds, st, Wsw, KT, NTILES, X, ldx, M, nrm, K, \
-                         partial, N, epi);                                                                            \
+      launch_gemm_kernel(k_gemm_bf16<ct, nt, role, spw, true>, grid, block, lds, st, Wsw, X, nrm.gain, partial, K, N,    \
+                         ldx, M, nrm.ssq_part, nrm.ssq_n, nrm.eps, epi);                                                                            \
     else                                                                                                              \
-      launch_gemm_kernel(k_gemm_bf16<ct, nt, role, spw, false>, grid, block, lds, st, Wsw, KT, NTILES, X, ldx, M, nrm,   \
-                         K, partial, N, epi);                                                                         \
+      launch_gemm_kernel(k_gemm_bf16<ct, nt, role, spw, false>, grid, block, lds, st, Wsw, X, nrm.gain, partial, K, N,   \
+                         ldx, M, nrm.ssq_part, nrm.ssq_n, nrm.eps, epi);                                                                         \
   } while (0)
 #define STAIRS_GEMM_NT(ct, role, spw)             \
   if (NT == 1) STAIRS_GEMM(ct, 1, role, spw);     \
@@ -1560,11 +1565,11 @@ __device__ __forceinline__ void next_embed(const NextEmbed& n, int p, int id, in
   }
 }
 template <typename E>
-__global__ __launch_bounds__(256) void k_embed(const E* __restrict__ emb, const int* __restrict__ tokens,
-                                               int tok_slot_stride, int tok_cap, int vocab, PosRef pos, int d,
-                                               float* __restrict__ x, float* __restrict__ ssq_part, int ssq_n, int hd,
-                                               const float2* __restrict__ tab, int tab_len, float2* __restrict__ cs, uint4* frag,
-                                               const float* __restrict__ frag_gain) {
+__global__ __launch_bounds__(256) void k_embed(const E* __restrict__ emb, const int* __restrict__ tokens, const int* __restrict__ pos_base,
+                                               int pos_offset, int pos_rps, int tok_slot_stride, int tok_cap, int vocab, int d, int ssq_n,
+                                               float* __restrict__ x, float* __restrict__ ssq_part, int hd, const float2* __restrict__ tab,
+                                               int tab_len, float2* __restrict__ cs, uint4* frag, const float* __restrict__ frag_gain) {
+  const PosRef pos{pos_base, pos_offset, pos_rps};
   const int m = blockIdx.y;
   const int p = pos_of(pos, m);
   tokens += (size_t)slot_of(pos, m) * tok_slot_stride;
@@ -1584,10 +1589,10 @@ void launch_embed(const void* emb, int emb_bf16, const int* tokens, int tok_slot
   const int sn = ssq_groups(d);
   if (emb_bf16)
     hipLaunchKernelGGL((k_embed<uint16_t>), grid, block, 0, st, static_cast<const uint16_t*>(emb), tokens,
-                       tok_slot_stride, tok_cap, vocab, pos, d, x, ssq_part, sn, hd, tab, tab_len, cs, frag, frag_gain);
+                       pos.base, pos.offset, pos.rps, tok_slot_stride, tok_cap, vocab, d, sn, x, ssq_part, hd, tab, tab_len, cs, frag, frag_gain);
   else
     hipLaunchKernelGGL((k_embed<float>), grid, block, 0, st, static_cast<const float*>(emb), tokens,
-                       tok_slot_stride, tok_cap, vocab, pos, d, x, ssq_part, sn, hd, tab, tab_len, cs, nullptr, nullptr);
+                       pos.base, pos.offset, pos.rps, tok_slot_stride, tok_cap, vocab, d, sn, x, ssq_part, hd, tab, tab_len, cs, nullptr, nullptr);
 }
 
 // tab[p][i] = (cos, sin)(p * theta^(-2i/hd)), angle in double, once per model: formed in front of every forward the
@@ -1619,9 +1624,9 @@ void launch_rope_rows(PosRef pos, int M, int hd, const float2* tab, int tab_len,
 // ---------------------------------------------------------------------------------------
 template <int HD, int MR, bool DIRECT>
 __global__ __launch_bounds__(256) void k_attn(const float* __restrict__ q, const float* __restrict__ Kc,
-                                              const float* __restrict__ Vc, int cap, int d, int H, int M, PosRef pos,
-                                              float scale, int nchunk_cap, float* __restrict__ part_o,
-                                              float* __restrict__ part_ml, float* __restrict__ out) {
+                                              const float* __restrict__ Vc, const int* __restrict__ pos_base, int pos_offset, int cap, int d, int M,
+                                              float* __restrict__ out, float scale, int H, int nchunk_cap, float* __restrict__ part_o,
+                                              float* __restrict__ part_ml) {
   constexpr int ROW = HD + 4;              // padded LDS row
   constexpr int VPR = HD / 4;              // 16-byte vectors per key
   constexpr int VPT = VPR / 2;             // vectors per thread of a chunk
@@ -1635,7 +1640,7 @@ __global__ __launch_bounds__(256) void k_attn(const float* __restrict__ q, const
 
   const int c = blockIdx.x, h = blockIdx.y, row0 = blockIdx.z * MR;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int pos0 = *pos.base + pos.offset;
+  const int pos0 = *pos_base + pos_offset;
   const int rows = min(MR, M - row0);      // valid query rows of this group
   const int kv_len = MR == 1 ? pos0 + row0 + 1 : pos0 + M;
   const int key0 = c * kAttnChunk;
@@ -1981,10 +1986,12 @@ __device__ __forceinline__ void attn_merge(const float* part_o, const float* par
 // (two work-groups per CU: the register budget that keeps both resident)
 template <int HD, int CT, bool FUSED>
 __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q, const _Float16* __restrict__ Kc,
-                                                  const _Float16* __restrict__ Vc, int cap, int d, int H, int M,
-                                                  PosRef pos, size_t kv_slot_stride, float scale, AttnMode am, int nchunk_cap,
-                                                  int early_keys, int rows_per_pass, float* part_o, float* part_ml, int* counters,
+                                                  const _Float16* __restrict__ Vc, const int* __restrict__ pos_base, int pos_offset, int pos_rps,
+                                                  int cap, int d, int M, int early_keys, size_t kv_slot_stride, float scale, int H, AttnMode am,
+                                                  int nchunk_cap, int rows_per_pass, float* part_o, float* part_ml, int* counters,
                                                   float* __restrict__ out) {
+  const PosRef pos{pos_base, pos_offset, pos_rps};
+  const int kv_fixed = max(0, -early_keys);
   constexpr int KK = HD / 32;   // k-steps of the score MFMA
   constexpr int ET = HD / 16;   // output-dim tiles of the value MFMA
   __shared__ float s_o[4][16][HD + 4];               // (+4: the 16 rows a wave writes at once fall into different banks)
@@ -2001,8 +2008,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
   part_o += (size_t)row0 * H * nchunk_cap * HD;
   part_ml += (size_t)row0 * H * nchunk_cap * 2;
   counters += blockIdx.z * H;
-  Kc += blockIdx.z * kv_slot_stride;
-  Vc += blockIdx.z * kv_slot_stride;
+  if (blockIdx.z > 0) {                              // (one slot: no wait for the stride)
+    Kc += blockIdx.z * kv_slot_stride;
+    Vc += blockIdx.z * kv_slot_stride;
+  }
   // a wave owns 64 keys of the chunk as two blocks of 32 (the tiles of the cache layout)
   const int kb = c * kAttnChunkH + wave * 64;         // first key of this wave
   // The first query tile's rows are requested before the keys and values (they come from L2 and are converted while the
@@ -2053,12 +2062,12 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
     }
   };
   // (one request site: with a second one for the other chunks the registers of both spill)
-  const int len0 = am.kv_fixed > 0 ? am.kv_fixed : kb + 32 < early_keys ? early_keys : pos_of(pos, row0) + M;
+  const int len0 = kv_fixed > 0 ? kv_fixed : kb + 32 < early_keys ? early_keys : pos_of(pos, row0) + M;
   request(kb < len0, kb + 32 < len0);
-  // causal: row i sees the keys 0 .. qpos0 + i; fixed key set (am.kv_fixed > 0): every row sees the keys 0 .. kv_fixed-1
+  // causal: row i sees the keys 0 .. qpos0 + i; fixed key set (kv_fixed > 0): every row sees the keys 0 .. kv_fixed-1
   const int qpos0 = pos_of(pos, row0);
-  const bool fixed = am.kv_fixed > 0;   // (then also for rows that sit nowhere: their result is unused)
-  const int pos0 = fixed ? am.kv_fixed - 1 : qpos0;   // last key row 0 sees
+  const bool fixed = kv_fixed > 0;   // (then also for rows that sit nowhere: their result is unused)
+  const int pos0 = fixed ? kv_fixed - 1 : qpos0;   // last key row 0 sees
   const int step = fixed ? 0 : 1;
   const int kv_len = pos0 + (fixed ? 1 : M);
   const float* brow = am.bias ? am.bias + (size_t)h * am.bias_ld + am.bias_zero : nullptr;
@@ -2214,9 +2223,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
 
 // the merge alone (long contexts: the attention work-groups then leave without waiting for their stores)
 template <int HD>
-__global__ __launch_bounds__(256) void k_attn_merge(const float* part_o, const float* part_ml, int d, int H, int M, PosRef pos,
-                                                    int kv_fixed, int nchunk_cap, int nch_lds, int rows_per_pass,
+__global__ __launch_bounds__(256) void k_attn_merge(const float* part_o, const float* part_ml, const int* __restrict__ pos_base, int pos_offset,
+                                                    int pos_rps, int d, int H, int M, int kv_fixed, int nchunk_cap, int nch_lds, int rows_per_pass,
                                                     float* __restrict__ out, uint4* frag, int frag_rt) {
+  const PosRef pos{pos_base, pos_offset, pos_rps};
   extern __shared__ float s_ml[];
   const int h = blockIdx.x, row0 = blockIdx.y * M;
   const bool fixed = kv_fixed > 0;
@@ -2240,8 +2250,8 @@ static void attn_dispatch(const float* q, const float* K, const float* V, int ca
   const dim3 grid(nchunk_launch, H, (M + mr - 1) / mr), block(256);
   const size_t lds = (size_t)(128 * (HD + 4) + mr * (HD + 128 + 2 + 256) + 2) * sizeof(float);
 #define STAIRS_ATTN(mrv, direct)                                                                                          \
-  hipLaunchKernelGGL((k_attn<HD, mrv, direct>), grid, block, lds, st, q, K, V, cap, d, H, M, pos, scale, nchunk_cap, part_o, \
-                     part_ml, out)
+  hipLaunchKernelGGL((k_attn<HD, mrv, direct>), grid, block, lds, st, q, K, V, pos.base, pos.offset, cap, d, M, out, scale, H, \
+                     nchunk_cap, part_o, part_ml)
   if (nchunk_launch == 1) {
     if (mr == 1) STAIRS_ATTN(1, true);
     else STAIRS_ATTN(16, true);
@@ -2277,7 +2287,7 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
     const int units = nchunk_launch;
     nchunk_launch = (nchunk_launch * kAttnChunk + kAttnChunkH - 1) / kAttnChunkH;
     dim3 grid(nchunk_launch, H, nslots), block(256);
-    const int early = attn_early_keys(units, nslots);
+    const int early = am.kv_fixed > 0 ? -am.kv_fixed : attn_early_keys(units, nslots);   // (k_attn_f16: one argument for both)
     // merge step's LDS: (max, sum) table, row maxima, and for more than kMergeCB chunks the group sums of as many
     // rows per pass as fit in 48 KiB, less when the table is large (the whole stays under kAttnMergeMaxLds)
     const int G = (nchunk_launch + kMergeCB - 1) / kMergeCB;
@@ -2290,13 +2300,13 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
     const bool fused = nchunk_launch <= kAttnFusedMaxChunks;
 #define STAIRS_ATTN16(hdv, ct)                                                                                              \
   if (fused)                                                                                                                \
-    hipLaunchKernelGGL((k_attn_f16<hdv, ct, true>), grid, block, lds, st, q_rot, K, V, cap, d, H, M, pos, kv_slot_stride,   \
-                       scale, am, nchunk_cap, early, rpp, part_o, part_ml, counters, out);                                         \
+    hipLaunchKernelGGL((k_attn_f16<hdv, ct, true>), grid, block, lds, st, q_rot, K, V, pos.base, pos.offset, pos.rps, cap, d, M, early, \
+                       kv_slot_stride, scale, H, am, nchunk_cap, rpp, part_o, part_ml, counters, out);                                         \
   else {                                                                                                                    \
-    hipLaunchKernelGGL((k_attn_f16<hdv, ct, false>), grid, block, 0, st, q_rot, K, V, cap, d, H, M, pos, kv_slot_stride,    \
-                       scale, am, nchunk_cap, early, rpp, part_o, part_ml, counters, out);                                         \
-    hipLaunchKernelGGL((k_attn_merge<hdv>), dim3(H, nslots), dim3(256), lds, st, part_o, part_ml, d, H, M, pos,             \
-                       am.kv_fixed, nchunk_cap, nchunk_launch, rpp, out, am.frag_out, am.frag_rt);                                      \
+    hipLaunchKernelGGL((k_attn_f16<hdv, ct, false>), grid, block, 0, st, q_rot, K, V, pos.base, pos.offset, pos.rps, cap, d, M, early, \
+                       kv_slot_stride, scale, H, am, nchunk_cap, rpp, part_o, part_ml, counters, out);                                         \
+    hipLaunchKernelGGL((k_attn_merge<hdv>), dim3(H, nslots), dim3(256), lds, st, part_o, part_ml, pos.base, pos.offset,    \
+                       pos.rps, d, H, M, am.kv_fixed, nchunk_cap, nchunk_launch, rpp, out, am.frag_out, am.frag_rt);         \
   }
     if (hd == 128) {
       if (M <= 16) STAIRS_ATTN16(128, 1) else STAIRS_ATTN16(128, 2)
@@ -2333,8 +2343,10 @@ __device__ __forceinline__ void argmax_swap(float& best, int& bi, bool far) {   
   argmax_take(best, bi, __uint_as_float(second ? rb[0] : rb[1]), (int)(second ? ri[0] : ri[1]));
 }
 template <bool NEXT>
-__global__ __launch_bounds__(1024) void k_argmax(const float* __restrict__ logits, int ld, int V, int row0, int row_stride,
-                                                 int* __restrict__ out, PosRef out_pos, int out_slot_stride, NextEmbed next) {
+__global__ __launch_bounds__(1024) void k_argmax(const float* __restrict__ logits, int* __restrict__ out, const int* __restrict__ pos_base,
+                                                 int pos_offset, int pos_rps, int ld, int V, int row0, int row_stride, int out_slot_stride,
+                                                 NextEmbed next) {
+  const PosRef out_pos{pos_base, pos_offset, pos_rps};
   __shared__ __align__(16) float sv[16];
   __shared__ __align__(16) int si[16];
   __shared__ int s_id;
@@ -2401,8 +2413,8 @@ __global__ __launch_bounds__(1024) void k_argmax(const float* __restrict__ logit
 
 void launch_argmax(const float* logits, int ld, int V, int nrows, int row0, int row_stride, int* out, PosRef out_pos,
                    int out_slot_stride, hipStream_t st, const NextEmbed& next) {
-  hipLaunchKernelGGL(next.emb ? k_argmax<true> : k_argmax<false>, dim3(nrows), dim3(1024), 0, st, logits, ld, V, row0, row_stride, out, out_pos,
-                     out_slot_stride, next);
+  hipLaunchKernelGGL(next.emb ? k_argmax<true> : k_argmax<false>, dim3(nrows), dim3(1024), 0, st, logits, out, out_pos.base,
+                     out_pos.offset, out_pos.rps, ld, V, row0, row_stride, out_slot_stride, next);
 }
 
 // (a lane per draft token: one round trip behind the state's, whatever k)
