@@ -64,6 +64,7 @@ struct Model {
   char* Kc = nullptr;               // [slots][layers][H][cap][hd]
   char* Vc = nullptr;
   size_t kv_layer_bytes = 0;
+  size_t kv_slot_bytes = 0;         // between the caches of consecutive slots
   int valid = 0;                    // positions 0..valid-1 of the cache hold the current sequence
   size_t esz() const { return bf16 ? 2 : 4; }
 };
@@ -78,6 +79,7 @@ struct stairs_ctx {
   hipStream_t st = nullptr;
   int k_max = 0;
   bool have_draft = false;
+  bool shared_kv = false;                         // the draft's caches are the target's (see prefix_draft)
   Model T, D;
   std::vector<void*> owned;                       // every device allocation, freed in stairs_free
   std::map<std::pair<const void*, int>, const void*> dedup;   // (first host ptr, kind) -> device copy
@@ -286,11 +288,45 @@ int build_model(stairs_ctx* c, Model* m, const stairs_model_cfg* cfg, const stai
   HIPCHK(c, hipGetLastError());
   m->stream_weights = m->bf16 && ((size_t)cfg->n_layers * (4 * (size_t)d * d + 3 * (size_t)d * f) + (size_t)V * d) * 2 > kStreamHintBytes;
   m->kv_layer_bytes = (size_t)cfg->n_heads * m->cap * m->hd * m->esz();
-  if ((rc = dev_alloc(c, &m->Kc, m->kv_layer_bytes * cfg->n_layers))) return rc;
-  if ((rc = dev_alloc(c, &m->Vc, m->kv_layer_bytes * cfg->n_layers))) return rc;
-  // positions that were never written are multiplied by probability 0 in the value product: they must be finite
-  HIPCHK(c, hipMemsetAsync(m->Kc, 0, m->kv_layer_bytes * cfg->n_layers, c->st));
-  HIPCHK(c, hipMemsetAsync(m->Vc, 0, m->kv_layer_bytes * cfg->n_layers, c->st));
+  m->kv_slot_bytes = m->kv_layer_bytes * cfg->n_layers;
+  return STAIRS_OK;
+}
+
+// Whether the draft is the target's first layers (their weights are one copy on the device).  Then keys and values of a
+// position are the same numbers for both, and one set of caches serves both: prompts are ingested once, and a proposal's first
+// step is the one row at L - 1, as everything in front of it was left by a verification.  What a proposal writes, positions
+// L - 1 .. L + k - 2, the verification behind it writes again before it reads it, so the caches are the target's alone at
+// every other time.  (2048-token prompt, 7B widths, 3 + 1 layers: the draft's embedding, QKV projection and its 5 % of the
+// call leave; 64 sequences, 1B widths: 128 rows of every first step on the block kernels become 64 on the decode kernels.)
+bool prefix_draft(const Model& t, const stairs_weights* tw, const Model& d, const stairs_weights* dw) {
+  const stairs_model_cfg &a = t.cfg, &b = d.cfg;
+  if (a.dtype != b.dtype || a.d_model != b.d_model || a.n_heads != b.n_heads || a.d_ffn != b.d_ffn || a.rope_theta != b.rope_theta ||
+      a.rms_eps != b.rms_eps || t.cap != d.cap || b.n_layers > a.n_layers || t.tok_emb != d.tok_emb)
+    return false;
+  const size_t norm = (size_t)a.d_model * sizeof(float);
+  for (int l = 0; l < b.n_layers; ++l) {
+    const Layer &x = t.layers[l], &y = d.layers[l];
+    if (x.wqkv != y.wqkv || x.wo != y.wo || x.wgu != y.wgu || x.wdown != y.wdown || memcmp(tw->attn_norm[l], dw->attn_norm[l], norm) ||
+        memcmp(tw->ffn_norm[l], dw->ffn_norm[l], norm))
+      return false;
+  }
+  return true;
+}
+
+void share_caches(stairs_ctx* c) {
+  c->D.Kc = c->T.Kc;
+  c->D.Vc = c->T.Vc;
+  c->D.kv_slot_bytes = c->T.kv_slot_bytes;
+}
+
+// a model's caches for n_slots sequences (zeroed: positions that were never written are multiplied by probability 0 in the
+// value product and must be finite)
+int alloc_caches(stairs_ctx* c, const Model* m, int n_slots, char** K, char** V) {
+  const size_t bytes = (size_t)n_slots * m->kv_slot_bytes;
+  int rc;
+  if ((rc = dev_alloc(c, K, bytes)) || (rc = dev_alloc(c, V, bytes))) return rc;
+  HIPCHK(c, hipMemsetAsync(*K, 0, bytes, c->st));
+  HIPCHK(c, hipMemsetAsync(*V, 0, bytes, c->st));
   return STAIRS_OK;
 }
 
@@ -486,7 +522,7 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
   } while (0)
   const int nslots = pos.rps ? M / pos.rps : 1;
   const int rows_per_slot = pos.rps ? pos.rps : M;
-  const size_t slot_bytes = (size_t)g.n_layers * m->kv_layer_bytes;
+  const size_t slot_bytes = m->kv_slot_bytes;
   const size_t slot_off = pos.rps ? 0 : (size_t)slot * slot_bytes;
   if (slot < 0 || slot >= c->n_slots || nslots > c->n_slots || nslots * H > kAttnCounters || (pos.rps && (M % pos.rps || !b)))
     return fail(c, STAIRS_EINVAL, "forward: slots outside what the context holds");
@@ -591,7 +627,7 @@ int block_layers(stairs_ctx* c, Model* m, int R, bool pieced, bool outputs, F at
   p.eps = g.rms_eps;
   p.rows = c->pf_rowinfo;
   p.cs = c->pf_cs;
-  p.slot_stride = (size_t)g.n_layers * m->kv_layer_bytes / m->esz();
+  p.slot_stride = m->kv_slot_bytes / m->esz();
   p.cap = m->cap;
   p.hd = m->hd;
   p.da = d;
@@ -644,7 +680,7 @@ int forward_block(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int lo
   const int nslots = M / pos.rps;
   if (nchunk < 1 || nchunk > c->nchunk_cap || nslots > c->n_slots || nslots * H > kAttnCounters)
     return fail(c, STAIRS_EINVAL, "forward: launch shape outside the workspaces");
-  const size_t slot_stride = (size_t)g.n_layers * m->kv_layer_bytes / m->esz();
+  const size_t slot_stride = m->kv_slot_bytes / m->esz();
   launch_blk_rows_pos(pos, M, m->hd, m->rope_tab, m->cap, c->pf_rowinfo, c->pf_cs, st);
   launch_blk_embed(static_cast<const uint16_t*>(m->tok_emb), c->tokens, c->tok_stride, c->tok_stride, V, c->pf_rowinfo, M, d, c->pf_x,
                    m->layers[0].attn_norm, c->pf_fa, c->pf_ssq, st);
@@ -914,7 +950,7 @@ int encode_model(stairs_ctx* c, Model* m) {
 int ingest_segs(stairs_ctx* c, Model* m, const BlkSegs& segs, int R, bool pieced) {
   const stairs_model_cfg& g = m->cfg;
   const int d = g.d_model, H = g.n_heads;
-  const size_t slot_stride = (size_t)g.n_layers * m->kv_layer_bytes / m->esz();
+  const size_t slot_stride = m->kv_slot_bytes / m->esz();
   launch_blk_rows(segs, R, m->hd, m->rope_tab, m->cap, c->pf_rowinfo, c->pf_cs, c->st);
   launch_blk_embed(static_cast<const uint16_t*>(m->tok_emb), c->tokens, c->tok_stride, c->tok_stride, g.vocab, c->pf_rowinfo, R, d,
                    c->pf_x, m->layers[0].attn_norm, c->pf_fa, c->pf_ssq, c->st);
@@ -1009,14 +1045,18 @@ NextEmbed next_embed(const stairs_ctx* c, const Model* m) {
                    m->encdec ? nullptr : m->rope_tab, m->encdec ? 0 : m->cap, c->rope_cs};
 }
 
+// rows of a sequence in a proposal's first step
+int first_rows(const stairs_ctx* c) { return c->shared_kv ? 1 : 2; }
+
 // Enqueue the draft's k greedy steps.  Positions are taken relative to the device-side sequence
 // length (state[0] == L), so the same launches can be replayed for any L; nch = attention chunks to launch.
 int enqueue_propose(stairs_ctx* c, int k, int nch) {
   Model* m = &c->D;
   const int V = m->cfg.vocab;
-  // step 1: rows at L-2, L-1 (row L-2 is recomputed when it is already cached: same values);
+  // step 1: rows at L-2, L-1 (row L-2 is recomputed when it is already cached: same values; shared caches: row L-1 alone);
   // its argmax is d_1 -> tokens[L].  Steps 2..k: one row each.
-  int rc = forward(c, m, rel_pos(c, -2), nch, 2, 1);
+  const int r1 = first_rows(c);
+  int rc = forward(c, m, rel_pos(c, -r1), nch, r1, 1);
   if (rc) return rc;
   auto decide = [&](int j) {                // d_{j+1}; for another step, its embedding too
     launch_argmax(c->logits, V, V, 1, 0, 1, c->tokens, rel_pos(c, j), 0, c->st, j + 1 < k ? next_embed(c, m) : NextEmbed{});
@@ -1048,7 +1088,8 @@ int enqueue_verify(stairs_ctx* c, int k, int nch) {
 int enqueue_propose_sampled(stairs_ctx* c, int k, int nch) {
   Model* m = &c->D;
   const int V = m->cfg.vocab;
-  int rc = forward(c, m, rel_pos(c, -2), nch, 2, 1, 0, c->dlogits);
+  const int r1 = first_rows(c);
+  int rc = forward(c, m, rel_pos(c, -r1), nch, r1, 1, 0, c->dlogits);
   if (rc) return rc;
   auto decide = [&](int j) {
     launch_sample(c->dlogits + (size_t)j * V, V, c->samp, 0, c->tokens, rel_pos(c, j), c->samp_ws, c->st,
@@ -1096,14 +1137,15 @@ int set_sampling(stairs_ctx* c, float temperature, uint64_t seed) {
   return STAIRS_OK;
 }
 
-// The same two halves for B sequences at once: every forward holds the rows of all slots (2, then 1, then k+1 per
-// slot), positions, token arrays and caches are looked up per slot on the device.
+// The same two halves for B sequences at once: every forward holds the rows of all slots (2, or 1 with shared caches, then 1,
+// then k+1 per slot), positions, token arrays and caches are looked up per slot on the device.
 int enqueue_propose_batch(stairs_ctx* c, int B, int k, int nch) {
   Model* m = &c->D;
   const int V = m->cfg.vocab;
-  int rc = forward(c, m, PosRef{c->state, -2, 2}, nch, 2 * B, 2 * B);
+  const int r1 = first_rows(c);
+  int rc = forward(c, m, PosRef{c->state, -r1, r1}, nch, r1 * B, r1 * B);
   if (rc) return rc;
-  launch_argmax(c->logits, V, V, B, 1, 2, c->tokens, PosRef{c->state, 0, 1}, c->tok_stride, c->st);   // each slot's 2nd row
+  launch_argmax(c->logits, V, V, B, r1 - 1, r1, c->tokens, PosRef{c->state, 0, 1}, c->tok_stride, c->st);   // each slot's last row
   for (int j = 1; j < k; ++j) {
     rc = forward(c, m, PosRef{c->state, j - 1, 1}, nch, B, B);
     if (rc) return rc;
@@ -1127,8 +1169,9 @@ int enqueue_verify_batch(stairs_ctx* c, int B, int k, int nch) {
 int do_propose(stairs_ctx* c, int k, bool sampled = false) {
   Model* m = &c->D;
   const int L = c->L;
-  // the draft's cache must hold positions 0..L-3; the 2-row first step covers L-2 and L-1
-  if (m->valid < L - 2) {
+  // the draft's cache must hold positions 0..L-3; the 2-row first step covers L-2 and L-1 (shared caches: the target's hold
+  // 0..L-2)
+  if (!c->shared_kv && m->valid < L - 2) {
     int rc = ingest(c, m, m->valid, L - 2);
     if (rc) return rc;
   }
@@ -1300,6 +1343,12 @@ int stairs_init(stairs_ctx** out, const stairs_model_cfg* tcfg, const stairs_wei
   }
   rc = build_model(c, &c->T, tcfg, tw, staging);
   if (!rc && have_draft) rc = build_model(c, &c->D, dcfg, dw, staging);
+  if (!rc) rc = alloc_caches(c, &c->T, 1, &c->T.Kc, &c->T.Vc);
+  if (!rc && have_draft) {
+    c->shared_kv = prefix_draft(c->T, tw, c->D, dw);
+    if (c->shared_kv) share_caches(c);
+    else rc = alloc_caches(c, &c->D, 1, &c->D.Kc, &c->D.Vc);
+  }
   (void)hipFree(staging);
   if (rc) return bail(rc);
 
@@ -1518,7 +1567,7 @@ int stairs_prefill(stairs_ctx* c, const int32_t* prompt, int32_t P) {
   c->L = c->P = P;
   c->T.valid = c->D.valid = 0;
   int rc = ingest(c, &c->T, 0, P - 1);
-  if (!rc && c->have_draft) rc = ingest(c, &c->D, 0, P - 1);
+  if (!rc && c->have_draft && !c->shared_kv) rc = ingest(c, &c->D, 0, P - 1);
   if (rc) return rc;
   HIPCHK(c, hipStreamSynchronize(c->st));
   c->prefilled = true;
@@ -1648,7 +1697,7 @@ static int decode_loop(stairs_ctx* c, int32_t G, int32_t k, bool adaptive, int32
   for (;;) {
     const int L_most = c->L + in_flight * (k + 1);
     if (in_flight < depth && L_most - L0 < G) {
-      if (in_flight == 0 && k > 0 && c->D.valid < c->L - 2 && (rc = ingest(c, &c->D, c->D.valid, c->L - 2))) return rc;
+      if (in_flight == 0 && k > 0 && !c->shared_kv && c->D.valid < c->L - 2 && (rc = ingest(c, &c->D, c->D.valid, c->L - 2))) return rc;
       if ((rc = enqueue((oldest + in_flight) & 1, L_most))) return failed(rc);
       ++in_flight;
       continue;
@@ -1844,16 +1893,14 @@ int stairs_reserve_batch(stairs_ctx* c, int32_t max_batch) {
   // new, larger arrays; the old ones are released
   int rc;
   for (Model* m : {&c->T, &c->D}) {
-    if (m == &c->D && !c->have_draft) continue;
-    const size_t bytes = (size_t)max_batch * m->cfg.n_layers * m->kv_layer_bytes;
+    if (m == &c->D && (!c->have_draft || c->shared_kv)) continue;
     char *K = nullptr, *V = nullptr;
-    if ((rc = dev_alloc(c, &K, bytes)) || (rc = dev_alloc(c, &V, bytes))) return rc;
-    HIPCHK(c, hipMemsetAsync(K, 0, bytes, c->st));
-    HIPCHK(c, hipMemsetAsync(V, 0, bytes, c->st));
+    if ((rc = alloc_caches(c, m, max_batch, &K, &V))) return rc;
     release(c, m->Kc);
     release(c, m->Vc);
     m->Kc = K;
     m->Vc = V;
+    if (c->shared_kv) share_caches(c);
     m->valid = 0;
   }
   // several sequences: the decode kernels take forwards of up to kMaxFwdRows rows (k up to 16384: gemm_takes_rows), the block
@@ -1962,7 +2009,7 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
   HIPCHK(c, hipMemcpyAsync(c->state, hstate.data(), hstate.size() * sizeof(int), hipMemcpyHostToDevice, c->st));
   HIPCHK(c, hipStreamSynchronize(c->st));
   for (Model* m : {&c->T, &c->D}) {
-    if (m == &c->D && !c->have_draft) continue;
+    if (m == &c->D && (!c->have_draft || c->shared_kv)) continue;
     if ((rc = ingest_prompts(c, m, P, B))) return rc;
   }
   c->T.valid = c->D.valid = 0;     // nothing the single-sequence calls could rely on
