@@ -1124,7 +1124,7 @@ int set_sampling(stairs_ctx* c, float temperature, uint64_t seed) {
   if (!c->samp) {
     const size_t V = c->T.cfg.vocab;
     if ((rc = dev_alloc(c, &c->samp, 1)) || (rc = dev_alloc(c, &c->samp_ws, 1)) ||
-        (rc = dev_alloc(c, &c->dlogits, (size_t)kMaxRows * V)) || (rc = dev_alloc(c, &c->lse, (size_t)2 * kMaxRows)))
+        (rc = dev_alloc(c, &c->dlogits, (size_t)kMaxRows * V)) || (rc = dev_alloc(c, &c->lse, (size_t)2 * kMaxRows * kLseParts * 2)))
       return rc;
     HIPCHK(c, hipMemsetAsync(c->samp_ws, 0, sizeof(SampleWs), c->st));
   }

@@ -228,7 +228,9 @@ struct SampleWs {
   unsigned long long score[kSampleBlocksMax];
   int idx[kSampleBlocksMax];
 };
-// lse[r] = log sum_v exp(row_r[v] * inv_temp) for the n_a rows of a followed by the n_b rows of b (row stride ld)
+// lse[r][part] = (maximum, sum of exponentials relative to it) of a share of row_r * inv_temp, for the n_a rows of a followed by
+// the n_b rows of b (row stride ld)
+constexpr int kLseParts = 8;
 void launch_row_lse(const float* a, int n_a, const float* b, int n_b, int ld, int V, const SampleParams* sp, float* lse,
                     hipStream_t st);
 // tokens[o] = one draw from softmax(logits / T) by Gumbel-max with the random numbers of (o, stream), o = out_pos; next: as for

@@ -2434,7 +2434,7 @@ __global__ __launch_bounds__(64) void k_accept(int* __restrict__ tokens, const i
     state[1] = n;
   }
 }
-static_assert(kMaxRows <= 64, "k_accept: a lane per stair row");
+static_assert(kMaxRows <= 64, "k_accept, k_accept_sampled: a lane per stair row");
 
 void launch_accept(int* tokens, const int* tgt, int k, int* state, int nslots, int tok_slot_stride, hipStream_t st) {
   hipLaunchKernelGGL(k_accept, dim3(nslots), dim3(64), 0, st, tokens, tgt, k, state, tok_slot_stride);
@@ -2501,44 +2501,64 @@ __device__ __forceinline__ bool grid_argmax(double& best, int& bi, SampleWs* ws,
   return true;
 }
 
-// lse[r] = log sum_v exp(rows[r][v] * inv_temp): one 1024-thread block per row; rows 0..n_a-1 from a, the rest from b
-__global__ __launch_bounds__(1024) void k_row_lse(const float* __restrict__ a, int n_a, const float* __restrict__ b, int ld,
-                                                  int V, const SampleParams* __restrict__ sp, float* __restrict__ lse) {
-  __shared__ float red[16];
+// (maximum, sum of exponentials) of a share of a row times inv_temp: kLseParts blocks per row, rows 0..n_a-1 from a, the rest
+// from b; whoever needs a row's log-sum-exp puts its parts together (row_lse).  A block holds its values in registers, 16 loads a
+// thread in flight (one block per row, two loops of one load a turn over 32000 values: 20 us; now 5).
+__global__ __launch_bounds__(256) void k_row_lse(const float* __restrict__ a, const float* __restrict__ b, const SampleParams* __restrict__ sp,
+                                                 float* __restrict__ lse, int n_a, int ld, int V) {
+  __shared__ float red[8];
   const int r = blockIdx.x, tid = threadIdx.x;
   const float* row = r < n_a ? a + (size_t)r * ld : b + (size_t)(r - n_a) * ld;
+  const int share = (V + kLseParts - 1) / kLseParts, v0 = blockIdx.y * share, v1 = min(V, v0 + share);
   const float it = sp->inv_temp;
-  float mx = -INFINITY;
-  for (int v = tid; v < V; v += 1024) mx = fmaxf(mx, row[v] * it);
+  float mx = -INFINITY, sum = 0.f;
+  for (int base = v0; base < v1; base += 16 * 256) {     // (one turn up to 32768 values a row)
+    float x[16], m = -INFINITY;
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-  if ((tid & 63) == 0) red[tid >> 6] = mx;
-  __syncthreads();
-  mx = red[0];
-  for (int w = 1; w < 16; ++w) mx = fmaxf(mx, red[w]);
-  __syncthreads();
-  float sum = 0.f;
-  for (int v = tid; v < V; v += 1024) sum += expf(row[v] * it - mx);
+    for (int i = 0; i < 16; ++i) x[i] = row[min(base + i * 256 + tid, v1 - 1)];
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) sum += __shfl_xor(sum, off);
-  if ((tid & 63) == 0) red[tid >> 6] = sum;
-  __syncthreads();
-  if (tid == 0) {
-    float t = 0.f;
-    for (int w = 0; w < 16; ++w) t += red[w];
-    lse[r] = mx + logf(t);
+    for (int i = 0; i < 16; ++i) {
+      x[i] = base + i * 256 + tid < v1 ? x[i] * it : -INFINITY;
+      m = fmaxf(m, x[i]);
+    }
+    m = wave_max(m);
+    if ((tid & 63) == 0) red[tid >> 6] = m;
+    __syncthreads();
+    const float mn = fmaxf(mx, fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3])));
+    sum *= mx == -INFINITY ? 0.f : expf(mx - mn);
+    mx = mn;
+    if (mx != -INFINITY)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sum += expf(x[i] - mx);
+    __syncthreads();
   }
+  sum = wave_sum(sum);
+  if ((tid & 63) == 0) red[4 + (tid >> 6)] = sum;
+  __syncthreads();
+  if (tid == 0)
+    reinterpret_cast<float2*>(lse)[r * kLseParts + blockIdx.y] = make_float2(mx, ((red[4] + red[5]) + red[6]) + red[7]);
+}
+__device__ __forceinline__ float row_lse(const float* lse, int r) {
+  float2 p[kLseParts];
+#pragma unroll
+  for (int i = 0; i < kLseParts; ++i) p[i] = reinterpret_cast<const float2*>(lse)[r * kLseParts + i];
+  float mx = p[0].x, sum = 0.f;
+#pragma unroll
+  for (int i = 1; i < kLseParts; ++i) mx = fmaxf(mx, p[i].x);
+#pragma unroll
+  for (int i = 0; i < kLseParts; ++i) sum += p[i].x == -INFINITY ? 0.f : p[i].y * expf(p[i].x - mx);
+  return mx + logf(sum);
 }
 
 // tokens[o] = argmax_v(logits[v] / T + gumbel(o, stream, v)) with o = the position out_pos gives: one categorical
 // draw, one candidate per thread (grid-stride for very large vocabularies)
-__global__ __launch_bounds__(256) void k_sample(const float* __restrict__ logits, int V, const SampleParams* __restrict__ sp,
-                                                int stream, int* __restrict__ tokens, PosRef out_pos, SampleWs* ws, NextEmbed next) {
+__global__ __launch_bounds__(256) void k_sample(const float* __restrict__ logits, const SampleParams* __restrict__ sp, const int* __restrict__ pos_base,
+                                                int pos_offset, int V, int stream, int* __restrict__ tokens, SampleWs* ws, NextEmbed next) {
   __shared__ int s_id;
   __shared__ double sv[4];
   __shared__ int si[4];
   __shared__ int s_flag;
-  const int o = *out_pos.base + out_pos.offset;
+  const int o = *pos_base + pos_offset;
   const float it = sp->inv_temp;
   const uint64_t key = sp->key;
   double best = -INFINITY;
@@ -2562,37 +2582,45 @@ __global__ __launch_bounds__(256) void k_sample(const float* __restrict__ logits
 // the logits d_j was drawn from, tl[i] the main model's logits of stair row i, lse[0..k] / lse[k+1..2k] their
 // log-sum-exps at the temperature.  d_i is kept while u_i * q_i(d_i) < p_{i-1}(d_i); at the first one that is not,
 // tokens[L+n] is drawn from the positive part of p_n - q_{n+1}; with all kept, tokens[L+k] from p_k.
-// state = {L + n + 1, n}; emitted[0..n] = the n + 1 tokens of this iteration.  Every block repeats the (cheap) walk
+// state = {L + n + 1, n}; emitted[0..n] = the n + 1 tokens of this iteration.  Every block repeats the (cheap) decisions
 // and scores its share of the vocabulary; the block that arrives last picks the winner and writes the results.
-__global__ __launch_bounds__(256) void k_accept_sampled(int* __restrict__ tokens, const float* __restrict__ tl,
-                                                        const float* __restrict__ dl, int ld, int V, int k,
-                                                        const float* __restrict__ lse, const SampleParams* __restrict__ sp,
-                                                        int* __restrict__ state, int* __restrict__ emitted, SampleWs* ws) {
+__global__ __launch_bounds__(256) void k_accept_sampled(int* __restrict__ tokens, int* __restrict__ state, const float* __restrict__ lse,
+                                                        const SampleParams* __restrict__ sp, const float* __restrict__ tl,
+                                                        const float* __restrict__ dl, int ld, int V, int k, int* __restrict__ emitted,
+                                                        SampleWs* ws) {
   __shared__ double sv[4];
   __shared__ int si[4];
   __shared__ int s_n, s_flag, s_empty;
+  __shared__ float s_lse[2 * kMaxRows];
   const int tid = threadIdx.x;
   const int L = state[0];
   const float it = sp->inv_temp;
   const uint64_t key = sp->key;
-  if (tid == 0) {
-    int n = 0;
-    while (n < k) {
-      const int d = tokens[L + n];
-      const float logp = tl[(size_t)n * ld + d] * it - lse[n];
-      const float logq = dl[(size_t)n * ld + d] * it - lse[k + 1 + n];
-      const double u = sample_uniform(L + n, 1, 0, key);
-      if (!(u < (double)expf(logp - logq))) break;
-      ++n;
+  if (tid <= 2 * k) s_lse[tid] = row_lse(lse, tid);
+  // a lane per draft token, all of them in the round trips of one (one after the other they were two each)
+  float lp = 0.f, lq1 = 0.f;
+  if (tid < k) {
+    const int d = tokens[L + tid];
+    lp = tl[(size_t)tid * ld + d];
+    lq1 = dl[(size_t)tid * ld + d];
+  }
+  __syncthreads();
+  if (tid < 64) {
+    bool kept = true;
+    if (tid < k) {
+      const float logp = lp * it - s_lse[tid];
+      const float logq = lq1 * it - s_lse[k + 1 + tid];
+      kept = sample_uniform(L + tid, 1, 0, key) < (double)expf(logp - logq);
     }
-    s_n = n;
+    const unsigned long long out = __ballot(!kept);
+    if (tid == 0) s_n = out ? __builtin_ctzll(out) : k;
   }
   __syncthreads();
   const int n = s_n;
   const int pos = L + n;
   const float* trow = tl + (size_t)n * ld;
   const float* drow = dl + (size_t)n * ld;     // only read when n < k
-  const float lt = lse[n], lq = n < k ? lse[k + 1 + n] : 0.f;
+  const float lt = s_lse[n], lq = n < k ? s_lse[k + 1 + n] : 0.f;
   double best = -INFINITY;
   int bi = 0x7fffffff;
   for (int v = blockIdx.x * 256 + tid; v < V; v += gridDim.x * 256) {
@@ -2619,8 +2647,8 @@ __global__ __launch_bounds__(256) void k_accept_sampled(int* __restrict__ tokens
     }
     block_argmax_256(best, bi, sv, si);
   }
+  if (tid < n) emitted[tid] = tokens[L + tid];
   if (tid == 0) {
-    for (int i = 0; i < n; ++i) emitted[i] = tokens[L + i];
     emitted[n] = bi;
     tokens[pos] = bi;
     state[0] = L + n + 1;
@@ -2630,16 +2658,17 @@ __global__ __launch_bounds__(256) void k_accept_sampled(int* __restrict__ tokens
 
 void launch_row_lse(const float* a, int n_a, const float* b, int n_b, int ld, int V, const SampleParams* sp, float* lse,
                     hipStream_t st) {
-  hipLaunchKernelGGL(k_row_lse, dim3(n_a + n_b), dim3(1024), 0, st, a, n_a, b, ld, V, sp, lse);
+  hipLaunchKernelGGL(k_row_lse, dim3(n_a + n_b, kLseParts), dim3(256), 0, st, a, b, sp, lse, n_a, ld, V);
 }
 static int sample_blocks(int V) { return std::min(kSampleBlocksMax, (V + 255) / 256); }
 void launch_sample(const float* logits, int V, const SampleParams* sp, int stream, int* tokens, PosRef out_pos,
                    SampleWs* ws, hipStream_t st, const NextEmbed& next) {
-  hipLaunchKernelGGL(k_sample, dim3(sample_blocks(V)), dim3(256), 0, st, logits, V, sp, stream, tokens, out_pos, ws, next);
+  hipLaunchKernelGGL(k_sample, dim3(sample_blocks(V)), dim3(256), 0, st, logits, sp, out_pos.base, out_pos.offset, V, stream, tokens, ws,
+                     next);
 }
 void launch_accept_sampled(int* tokens, const float* tl, const float* dl, int ld, int V, int k, const float* lse,
                            const SampleParams* sp, int* state, int* emitted, SampleWs* ws, hipStream_t st) {
-  hipLaunchKernelGGL(k_accept_sampled, dim3(sample_blocks(V)), dim3(256), 0, st, tokens, tl, dl, ld, V, k, lse, sp, state,
+  hipLaunchKernelGGL(k_accept_sampled, dim3(sample_blocks(V)), dim3(256), 0, st, tokens, state, lse, sp, tl, dl, ld, V, k,
                      emitted, ws);
 }
 
