@@ -62,7 +62,7 @@ void launch_swizzle_bf16(const uint16_t* W, uint4* Wsw, int N, int K, int perm, 
 // Sum of the split-K partial sums of one element (or 4 adjacent ones).  The order is fixed for every GEMM variant:
 // the 512-wide k chunks are added in pairs, (c0 + c1), (c2 + c3), ..., and the pair sums one after the other.
 // PAIRS = true: the S partials are single chunks (the pairs are formed here); false: they already are pair sums.
-// The loads of up to 8 partials are issued together (they are full round trips to the memory side).
+// The loads of up to 8 (slice_sum4: 16) partials are issued together (they are full round trips to the memory side).
 template <bool PAIRS>
 __device__ __forceinline__ float slice_sum(const float* partial, int S, size_t stride, size_t off) {
   float a = 0.f;
@@ -84,17 +84,17 @@ __device__ __forceinline__ float slice_sum(const float* partial, int S, size_t s
 template <bool PAIRS>
 __device__ __forceinline__ float4 slice_sum4(const float* partial, int S, size_t stride, size_t off) {
   float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
-  for (int s0 = 0; s0 < S; s0 += 8) {
-    float2 p[8], q[8];
+  for (int s0 = 0; s0 < S; s0 += 16) {
+    float2 p[16], q[16];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < 16; ++i) {
       const float* src = partial + (size_t)min(s0 + i, S - 1) * stride + off;
       p[i] = ld_dev2(src);
       q[i] = ld_dev2(src + 2);
     }
     if (PAIRS) {
 #pragma unroll
-      for (int i = 0; i < 8; i += 2) {
+      for (int i = 0; i < 16; i += 2) {
         if (s0 + i < S) {
           const bool two = s0 + i + 1 < S;
           a.x += two ? (p[i].x + p[i + 1].x) : p[i].x; a.y += two ? (p[i].y + p[i + 1].y) : p[i].y;
@@ -103,7 +103,7 @@ __device__ __forceinline__ float4 slice_sum4(const float* partial, int S, size_t
       }
     } else {
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
+      for (int i = 0; i < 16; ++i) {
         const bool ok = s0 + i < S;
         a.x += ok ? p[i].x : 0.f; a.y += ok ? p[i].y : 0.f; a.z += ok ? q[i].x : 0.f; a.w += ok ? q[i].y : 0.f;
       }
