@@ -1162,123 +1162,242 @@ bool launch_gemm_shared(int role, const void* W, int N, int K, const uint4* xfra
 }
 
 // Attention of a row block without partial results (the rows of a 16-row tile belong to one sequence, see BlkSegs): a
-// wave owns 16 query rows of one head and walks over the keys 0 .. its last row's position (kv_fixed > 0: over the keys
-// 0 .. kv_fixed - 1 whatever the row, encoder), 32 at a time, keeping the running maximum, the running sum and the
-// running output of its rows in registers (rescaled whenever the maximum grows).  Same operands and splits as
-// k_attn_f16 (scores^T = K q^T with q as half high + low, out^T = V^T p^T with p as half high + low); the order of
-// the additions differs from the decode kernels, which only ever see their own results.  The output is left as the
-// block fragments the output projection reads.
-template <int HD, bool BIAS>
+// wave owns QT tiles of 16 query rows of one head and walks over the keys 0 .. its last row's position (kv_fixed > 0: over the
+// keys 0 .. kv_fixed - 1 whatever the row, encoder), 64 at a time, keeping the running maximum, each lane's share of the
+// running sum and the running output of its rows in registers (rescaled where the maximum grows).  Same operands and splits
+// as k_attn_f16 (scores^T = K q^T with q as half high + low, out^T = V^T p^T with p as half high + low); the order of the
+// additions differs from the decode kernels, which only ever see their own results, and depends on the row alone.  The output
+// is left as the block fragments the output projection reads.
+//   The 4 waves share the keys and values: 64 of them (32 KiB at head_dim 128) are copied into one of two LDS buffers while the
+//   other is worked on.  A wave of 16 rows that loads 16 KiB for every 32 MFMAs itself asks for twice what the CU's path to
+//   L2 gives, and per 32 keys the masks, lane exchanges and rescaling of every step were more vector instructions than the
+//   MFMAs leave room for: now masks only at the diagonal, sums over the lanes at the end, rescaling where a maximum grew.
+//   Tiles of several sequences in one work-group: the runs of tiles of one sequence one after the other.
+//   Launches by themselves, before -> now, us: 32 heads of 128, 2048 rows behind nothing / behind 6144 keys 118 -> 87 / 663 -> 462
+//   (1.04 PFLOP/s issued), 333 rows 14.0 -> 12.3, 777 rows of an encoder 59 -> 49; 16 heads of 64, 2048 rows behind 6144 keys
+//   232 -> 156.  What bounds it then: MFMAs and the softmax's vector instructions on a SIMD, which overlap only in part.
+//   QT = 2 where that leaves two work-groups per CU, else 1.  Row blocks come longest first; where all work-groups are
+//   resident at once, the second half shortest first, so that a long one shares its CU with a short one.
+template <int HD, bool BIAS, int QT>
 __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__ q, const _Float16* __restrict__ Kc,
                                                     const _Float16* __restrict__ Vc, int cap, int d, size_t slot_stride,
                                                     const int2* __restrict__ rows, int R, float scale, AttnMode am,
                                                     uint4* __restrict__ frag, int RT) {
-  constexpr int KK = HD / 32, ET = HD / 16;
+  constexpr int KK = HD / 32, ET = HD / 16, TILES = 4 * QT;
+  constexpr int KP = 4 * KK, VP = 2 * ET, STAGE = (KP + VP) * 64;      // KiB pieces of 64 keys and of their values
+  static_assert(KP % 4 == 0 && VP % 4 == 0, "whole pieces per wave");
+  __shared__ uint4 lds[2 * STAGE];
   const int h = blockIdx.x;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int j = lane & 15, g = lane >> 4;
-  const int r0 = blockIdx.y * 64 + wave * 16;         // first row of this wave's tile
-  if (r0 >= R) return;                                // no barriers in this kernel: waves are independent
-  const int row = r0 + j;
-  const int2 at = row < R ? rows[row] : make_int2(0, -1);
-  const int slot = rows[r0].x;
-  const int pos = at.y;
-  const bool row_ok = pos >= 0;
-  const int seen_to = am.kv_fixed > 0 ? am.kv_fixed - 1 : pos;   // last key this lane's row sees
-  int tile_last = row_ok ? seen_to : -1;                         // last key any row of the tile sees
+  int yb = gridDim.y - 1 - blockIdx.y;
+  if (gridDim.x * gridDim.y <= 512 && blockIdx.y >= (gridDim.y + 1) / 2) yb = blockIdx.y - (gridDim.y + 1) / 2;
+  const int r00 = yb * TILES * 16;                    // first row of the work-group
+  // every tile's sequence and the last key any of its rows sees (-1: none)
+  int tslot[TILES], tlast[TILES];
 #pragma unroll
-  for (int off = 1; off < 16; off <<= 1) tile_last = max(tile_last, __shfl_xor(tile_last, off));
-  tile_last = __builtin_amdgcn_readfirstlane(tile_last);
-  f16x8 qh[KK], ql[KK];
+  for (int t4 = 0; t4 < QT; ++t4) {
+    const int r = r00 + t4 * 64 + lane;
+    const int2 at = r < R ? rows[r] : make_int2(-1, -1);
+    int last = at.y < 0 ? -1 : am.kv_fixed > 0 ? am.kv_fixed - 1 : at.y;
 #pragma unroll
-  for (int kk = 0; kk < KK; ++kk) {
-    float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
-    if (row_ok) {
-      const float4* qp = reinterpret_cast<const float4*>(q + (size_t)row * d + h * HD + kk * 32 + g * 8);
-      a = qp[0];
-      b = qp[1];
+    for (int off = 1; off < 16; off <<= 1) last = max(last, __shfl_xor(last, off));
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      tslot[t4 * 4 + i] = __builtin_amdgcn_readlane(at.x, i * 16);
+      tlast[t4 * 4 + i] = __builtin_amdgcn_readlane(last, i * 16);
     }
-    const float v[8] = {a.x * scale, a.y * scale, a.z * scale, a.w * scale, b.x * scale, b.y * scale, b.z * scale, b.w * scale};
-    split_half8(v, qh[kk], ql[kk]);
   }
-  const float* brow = BIAS ? am.bias + (size_t)h * am.bias_ld + am.bias_zero - pos : nullptr;   // bias by key position - query position
-  const uint4* Kh = reinterpret_cast<const uint4*>(Kc + slot * slot_stride + (size_t)h * cap * HD) + lane;
-  const uint4* Vh = reinterpret_cast<const uint4*>(Vc + slot * slot_stride + (size_t)h * cap * HD) + lane;
-  f32x4 oacc[ET];
+  int pos[QT], seen[QT], all_see[QT];                 // the lane's row; keys up to all_see are seen by the tile's 16 rows
+  f16x8 qh[QT][KK], ql[QT][KK];
+  const float qscale = scale * 1.44269504088896340736f;                // scores in units of log 2
 #pragma unroll
-  for (int et = 0; et < ET; ++et) oacc[et] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;
-  // two register sets: the keys and values of the next step are requested before this step's arithmetic
-  uint4 kA[2][KK], vA[ET], kB[2][KK], vB[ET];
-  auto load_kv = [&](int kb, uint4 (&kreg)[2][KK], uint4 (&vreg)[ET]) {
+  for (int t = 0; t < QT; ++t) {
+    const int row = r00 + (wave * QT + t) * 16 + j;
+    pos[t] = row < R ? rows[row].y : -1;
+    const bool ok = pos[t] >= 0;
+    seen[t] = !ok ? -1 : am.kv_fixed > 0 ? am.kv_fixed - 1 : pos[t];
+    int m = seen[t];
 #pragma unroll
-    for (int t = 0; t < 2; ++t)
+    for (int off = 1; off < 16; off <<= 1) m = min(m, __shfl_xor(m, off));
+    all_see[t] = __builtin_amdgcn_readfirstlane(m);
 #pragma unroll
-      for (int kk = 0; kk < KK; ++kk) kreg[t][kk] = Kh[((size_t)((kb >> 4) + t) * KK + kk) * 64];
-#pragma unroll
-    for (int et = 0; et < ET; ++et) vreg[et] = Vh[((size_t)(kb >> 5) * ET + et) * 64];
-  };
-  auto step = [&](int kb, const uint4 (&kreg)[2][KK], const uint4 (&vreg)[ET]) {
-    float sc[8];
-#pragma unroll
-    for (int t = 0; t < 2; ++t) {
-      f32x4 sacc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-      for (int kk = 0; kk < KK; ++kk) {
-        const f16x8 a = __builtin_bit_cast(f16x8, kreg[t][kk]);
-        sacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, qh[kk], sacc, 0, 0, 0);
-        sacc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, ql[kk], sacc, 0, 0, 0);
+    for (int kk = 0; kk < KK; ++kk) {
+      float4 a = make_float4(0.f, 0.f, 0.f, 0.f), b = a;
+      if (ok) {
+        const float4* qp = reinterpret_cast<const float4*>(q + (size_t)row * d + h * HD + kk * 32 + g * 8);
+        a = qp[0];
+        b = qp[1];
       }
-#pragma unroll
-      for (int v = 0; v < 4; ++v) {
-        const int key = kb + t * 16 + g * 4 + v;
-        const bool seen = row_ok && key <= seen_to;
-        const float bv = (BIAS && seen) ? brow[key] : 0.f;
-        sc[t * 4 + v] = seen ? sacc[v] + bv : -INFINITY;
-      }
+      const float v[8] = {a.x * qscale, a.y * qscale, a.z * qscale, a.w * qscale, b.x * qscale, b.y * qscale, b.z * qscale, b.w * qscale};
+      split_half8(v, qh[t][kk], ql[t][kk]);
     }
-    float mx = sc[0];
-#pragma unroll
-    for (int i = 1; i < 8; ++i) mx = fmaxf(mx, sc[i]);
-    mx = fmaxf(mx, __shfl_xor(mx, 16));
-    mx = fmaxf(mx, __shfl_xor(mx, 32));
-    const float m_new = fmaxf(m_run, mx);
-    const float alpha = (m_run == -INFINITY) ? 0.f : exp_fast(m_run - m_new);   // m_new >= m_run > -inf there
-    float pv[8], sum = 0.f;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      pv[i] = (m_new == -INFINITY) ? 0.f : exp_fast(sc[i] - m_new);
-      sum += pv[i];
-    }
-    sum += __shfl_xor(sum, 16);
-    sum += __shfl_xor(sum, 32);
-    l_run = l_run * alpha + sum;
-    m_run = m_new;
-    f16x8 ph, pl;
-    split_half8(pv, ph, pl);
-#pragma unroll
-    for (int et = 0; et < ET; ++et) {
-      oacc[et][0] *= alpha; oacc[et][1] *= alpha; oacc[et][2] *= alpha; oacc[et][3] *= alpha;
-      const f16x8 a = __builtin_bit_cast(f16x8, vreg[et]);
-      oacc[et] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, ph, oacc[et], 0, 0, 0);
-      oacc[et] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a, pl, oacc[et], 0, 0, 0);
-    }
-  };
-  load_kv(0, kA, vA);
-#pragma nounroll
-  for (int kb = 0; kb <= tile_last; kb += 64) {
-    if (kb + 32 <= tile_last) load_kv(kb + 32, kB, vB);
-    step(kb, kA, vA);
-    if (kb + 32 > tile_last) break;
-    if (kb + 64 <= tile_last) load_kv(kb + 64, kA, vA);
-    step(kb + 32, kB, vB);
   }
-  if (row < R) {
-    const float inv = row_ok ? 1.0f / l_run : 0.f;    // (a padding row sees no key: zeros)
+  f32x4 oacc[QT][ET];
+  float m_run[QT], l_run[QT];
 #pragma unroll
-    for (int et = 0; et < ET; ++et)
-      blk_store_frag4(frag, RT, row, h * HD + et * 16 + g * 4,
-                      make_float4(oacc[et][0] * inv, oacc[et][1] * inv, oacc[et][2] * inv, oacc[et][3] * inv));
+  for (int t = 0; t < QT; ++t) {
+#pragma unroll
+    for (int et = 0; et < ET; ++et) oacc[t][et] = f32x4{0.f, 0.f, 0.f, 0.f};
+    m_run[t] = -INFINITY;
+    l_run[t] = 0.f;
+  }
+  const float* brow = BIAS ? am.bias + (size_t)h * am.bias_ld + am.bias_zero : nullptr;   // bias by key position - query position
+
+  // 64 keys from LDS; tiles that see none of them (sees[t] < kb) add exactly nothing
+  auto step = [&](int kb, const uint4* buf, const int (&sees)[QT], const int (&all)[QT]) {
+    f32x4 sacc[QT][4];
+#pragma unroll
+    for (int t = 0; t < QT; ++t)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) sacc[t][i] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // (reads run ahead of the MFMAs that need them: a k-step of keys, four pieces of values)
+    f16x8 a[2][4], va[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) a[0][i] = __builtin_bit_cast(f16x8, buf[i * KK * 64 + lane]);
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        if (kk + 1 < KK) a[(kk + 1) & 1][i] = __builtin_bit_cast(f16x8, buf[(i * KK + kk + 1) * 64 + lane]);
+        else va[i] = __builtin_bit_cast(f16x8, buf[(KP + i) * 64 + lane]);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < QT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sacc[t][i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[kk & 1][i], qh[t][kk], sacc[t][i], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < QT; ++t)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sacc[t][i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[kk & 1][i], ql[t][kk], sacc[t][i], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    f16x8 ph[QT][2], pl[QT][2];
+#pragma unroll
+    for (int t = 0; t < QT; ++t) {
+      if (BIAS) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            const int key = kb + i * 16 + g * 4 + v;
+            if (key <= sees[t]) sacc[t][i][v] += brow[key - pos[t]] * 1.44269504088896340736f;
+          }
+      }
+      if (all[t] < kb + 63) {                          // (uniform: some row does not see some key)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) sacc[t][i][v] = kb + i * 16 + g * 4 + v <= sees[t] ? sacc[t][i][v] : -INFINITY;
+      }
+      float mx = fmaxf(fmaxf(sacc[t][0][0], sacc[t][0][1]), fmaxf(sacc[t][0][2], sacc[t][0][3]));
+#pragma unroll
+      for (int i = 1; i < 4; ++i) mx = fmaxf(mx, fmaxf(fmaxf(sacc[t][i][0], sacc[t][i][1]), fmaxf(sacc[t][i][2], sacc[t][i][3])));
+      auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+      mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+      sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+      mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+      if (__any(mx > m_run[t])) {
+        const float m_new = fmaxf(m_run[t], mx);
+        const float alpha = m_run[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[t] - m_new);
+        l_run[t] *= alpha;
+#pragma unroll
+        for (int et = 0; et < ET; ++et) {
+          oacc[t][et][0] *= alpha; oacc[t][et][1] *= alpha; oacc[t][et][2] *= alpha; oacc[t][et][3] *= alpha;
+        }
+        m_run[t] = m_new;
+      }
+      const float m = m_run[t] == -INFINITY ? 0.f : m_run[t];
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        float pv[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) pv[i] = __builtin_amdgcn_exp2f(sacc[t][2 * b + (i >> 2)][i & 3] - m);
+        l_run[t] += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
+        split_half8(pv, ph[t][b], pl[t][b]);
+      }
+    }
+#pragma unroll
+    for (int p0 = 0; p0 < VP; p0 += 2) {               // (two pieces: no product waits for the one in front of it)
+#pragma unroll
+      for (int t = 0; t < QT; ++t)
+#pragma unroll
+        for (int p = p0; p < p0 + 2; ++p)
+          oacc[t][p % ET] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[p & 3], ph[t][p / ET], oacc[t][p % ET], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < QT; ++t)
+#pragma unroll
+        for (int p = p0; p < p0 + 2; ++p)
+          oacc[t][p % ET] = __builtin_amdgcn_mfma_f32_16x16x32_f16(va[p & 3], pl[t][p / ET], oacc[t][p % ET], 0, 0, 0);
+      if (p0 + 4 < VP) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int p = p0 + 4; p < p0 + 6; ++p) va[p & 3] = __builtin_bit_cast(f16x8, buf[(KP + p) * 64 + lane]);
+      }
+    }
+  };
+
+  for (int t0 = 0; t0 < TILES;) {                     // runs of tiles of one sequence
+    const int slot = tslot[t0];
+    int t1 = t0, last = -1;
+#pragma unroll
+    for (int t = 0; t < TILES; ++t)
+      if (t == t1 && tslot[t] == slot) {
+        last = max(last, tlast[t]);
+        ++t1;
+      }
+    if (last >= 0) {                                  // (rows past the block's last and sequences of padding see nothing)
+      const uint4* Kh = reinterpret_cast<const uint4*>(Kc + slot * slot_stride + (size_t)h * cap * HD);
+      const uint4* Vh = reinterpret_cast<const uint4*>(Vc + slot * slot_stride + (size_t)h * cap * HD);
+      // (cap is whole blocks of 32 keys: where the second half of 64 lies past it, the first half comes twice, unseen)
+      auto request = [&](int kb, uint4* buf) {
+        const int past = __builtin_amdgcn_readfirstlane(kb + 32 >= cap ? 1 : 0);
+#pragma unroll
+        for (int i = 0; i < KP / 4; ++i) {
+          const int p = wave + 4 * i, src = past && p >= KP / 2 ? p - KP / 2 : p;
+          copy_to_lds_16(Kh, (uint32_t)((kb >> 4) * KK + src) * 1024u, buf + p * 64, lane * 16);
+        }
+#pragma unroll
+        for (int i = 0; i < VP / 4; ++i) {
+          const int p = wave + 4 * i, src = past && p >= VP / 2 ? p - VP / 2 : p;
+          copy_to_lds_16(Vh, (uint32_t)((kb >> 5) * ET + src) * 1024u, buf + (KP + p) * 64, lane * 16);
+        }
+      };
+      int sees[QT], all[QT], mine = -1;
+#pragma unroll
+      for (int t = 0; t < QT; ++t) {
+        const bool in = wave * QT + t >= t0 && wave * QT + t < t1;
+        sees[t] = in ? seen[t] : -1;
+        all[t] = in ? all_see[t] : -1;
+#pragma unroll
+        for (int u = 0; u < TILES; ++u)
+          if (u == wave * QT + t && in) mine = max(mine, tlast[u]);
+      }
+      __syncthreads();                                // (the run before this one has been read)
+      request(0, lds);
+      int cur = 0;
+      for (int kb = 0; kb <= last; kb += 64, cur ^= 1) {
+        wait_copies_and_sync<0>();                    // these 64 keys are there, the 64 before them have been read
+        if (kb + 64 <= last) request(kb + 64, lds + (cur ^ 1) * STAGE);
+        if (kb <= mine) step(kb, lds + cur * STAGE, sees, all);
+      }
+    }
+    t0 = t1;
+  }
+#pragma unroll
+  for (int t = 0; t < QT; ++t) {
+    const int row = r00 + (wave * QT + t) * 16 + j;
+    float l = l_run[t];
+    l += __shfl_xor(l, 16);
+    l += __shfl_xor(l, 32);
+    if (row < R) {
+      const float inv = pos[t] >= 0 ? 1.0f / l : 0.f;  // (a padding row sees no key: zeros)
+#pragma unroll
+      for (int et = 0; et < ET; ++et)
+        blk_store_frag4(frag, RT, row, h * HD + et * 16 + g * 4,
+                        make_float4(oacc[t][et][0] * inv, oacc[t][et][1] * inv, oacc[t][et][2] * inv, oacc[t][et][3] * inv));
+    }
   }
 }
 
@@ -1288,9 +1407,11 @@ void launch_attention_flash(const float* q, const void* Kc, const void* Vc, int 
   const float scale = am.scale > 0.f ? am.scale : 1.0f / sqrtf((float)hd);
   const _Float16* K = static_cast<const _Float16*>(Kc);
   const _Float16* V = static_cast<const _Float16*>(Vc);
-  dim3 grid(H, (R + 63) / 64);
-#define STAIRS_FLASH(hdv, bias) \
-  hipLaunchKernelGGL((k_attn_flash<hdv, bias>), grid, dim3(256), 0, st, q, K, V, cap, d, slot_stride, rows, R, scale, am, frag, pf_col_tiles(R))
+  const int qt = H * ((R + 127) / 128) >= 512 ? 2 : 1;
+  dim3 grid(H, (R + 64 * qt - 1) / (64 * qt));
+#define STAIRS_FLASH(hdv, bias)                                                                                                    \
+  hipLaunchKernelGGL((qt == 2 ? k_attn_flash<hdv, bias, 2> : k_attn_flash<hdv, bias, 1>), grid, dim3(256), 0, st, q, K, V, cap, d, \
+                     slot_stride, rows, R, scale, am, frag, pf_col_tiles(R))
   if (hd == 128) {
     if (am.bias) STAIRS_FLASH(128, true); else STAIRS_FLASH(128, false);
   } else {
