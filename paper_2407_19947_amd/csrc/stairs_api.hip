@@ -87,6 +87,8 @@ struct stairs_ctx {
   float *x = nullptr, *ssq = nullptr, *q_rot = nullptr, *attn_out = nullptr, *h = nullptr, *logits = nullptr;
   float *partial = nullptr, *part_o = nullptr, *part_ml = nullptr;
   float2* rope_cs = nullptr;
+  float2* cand = nullptr;      // the unembedding's candidates, [8][vocab / 16] ...
+  bool has_cand = false;       // ... which the forward enqueued last leaves
   // activation fragments of x, attn_out and h for forwards of more than 4 rows (bf16 models), see frag_bytes()
   uint4 *xf = nullptr, *af = nullptr, *hf = nullptr;
   // block prefill (bf16 models, env STAIRS_NO_BLOCK_PREFILL=1 turns it off): [kPfRows, .] workspaces
@@ -598,6 +600,8 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
     e.stream_weights = m->stream_weights;
     e.out = logits_dst ? logits_dst : c->logits;
     e.hd = m->hd;
+    c->has_cand = m->bf16 && !logits_dst && logits_rows <= 8 && rows_path_lds(kRoleHead, logits_rows, V, d) > 0;
+    e.cand = c->has_cand ? c->cand : nullptr;
     // (the fragments hold all M rows: usable when the unembedding takes them all)
     launch_gemm(kRoleHead, b, m->lm_head, V, d, c->x + (size_t)r0 * d, d, logits_rows,
                 RowNorm{m->final_norm, c->ssq + r0 * sn, sn, g.rms_eps}, c->partial, e, st, (fr && r0 == 0) ? c->xf : nullptr);
@@ -819,6 +823,8 @@ int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logit
     e.stream_weights = m->stream_weights;
     e.out = logits_dst ? logits_dst : c->logits;
     e.hd = m->hd;
+    c->has_cand = m->bf16 && !logits_dst && logits_rows <= 8 && rows_path_lds(kRoleHead, logits_rows, V, d) > 0;
+    e.cand = c->has_cand ? c->cand : nullptr;
     launch_gemm(kRoleHead, 1, m->lm_head, V, d, c->x + (size_t)r0 * d, d, logits_rows,
                 RowNorm{m->final_norm, c->ssq + r0 * sn, sn, g.rms_eps}, c->partial, e, st, r0 == 0 ? xf : nullptr);
     SYNCPOINT();
@@ -1048,18 +1054,35 @@ NextEmbed next_embed(const stairs_ctx* c, const Model* m) {
 // rows of a sequence in a proposal's first step
 int first_rows(const stairs_ctx* c) { return c->shared_kv ? 1 : 2; }
 
+// the model a greedy or sampled iteration with draft length k starts with, and the rows of its first forward
+Model* first_model(stairs_ctx* c, int k) { return k > 0 ? &c->D : &c->T; }
+int first_model_rows(const stairs_ctx* c, int k) { return k > 0 ? first_rows(c) : 1; }
+
+// the embeddings of that forward (in a generation loop the launch that ends an iteration leaves them for the next)
+void embed_first(stairs_ctx* c, int k) {
+  const Model* m = first_model(c, k);
+  const NextEmbed n = next_embed(c, m);
+  const int r = first_model_rows(c, k);
+  launch_embed(n.emb, n.bf16, c->tokens, 0, c->tok_stride, n.vocab, rel_pos(c, -r), r, n.d, n.x, n.ssq_part, n.hd, n.tab, n.tab_len, n.cs, c->st);
+}
+
 // Enqueue the draft's k greedy steps.  Positions are taken relative to the device-side sequence
 // length (state[0] == L), so the same launches can be replayed for any L; nch = attention chunks to launch.
-int enqueue_propose(stairs_ctx* c, int k, int nch) {
+// embedded: embed_first's work is done
+int enqueue_propose(stairs_ctx* c, int k, int nch, bool embedded) {
   Model* m = &c->D;
   const int V = m->cfg.vocab;
   // step 1: rows at L-2, L-1 (row L-2 is recomputed when it is already cached: same values; shared caches: row L-1 alone);
   // its argmax is d_1 -> tokens[L].  Steps 2..k: one row each.
   const int r1 = first_rows(c);
-  int rc = forward(c, m, rel_pos(c, -r1), nch, r1, 1);
+  int rc = forward(c, m, rel_pos(c, -r1), nch, r1, 1, 0, nullptr, embedded);
   if (rc) return rc;
   auto decide = [&](int j) {                // d_{j+1}; for another step, its embedding too
-    launch_argmax(c->logits, V, V, 1, 0, 1, c->tokens, rel_pos(c, j), 0, c->st, j + 1 < k ? next_embed(c, m) : NextEmbed{});
+    const NextEmbed next = j + 1 < k ? next_embed(c, m) : NextEmbed{};
+    if (decide_takes(c->has_cand, 1, V))
+      launch_decide(c->has_cand ? reinterpret_cast<const float*>(c->cand) : c->logits, c->has_cand, V, 1, c->tokens, rel_pos(c, j), c->st, next);
+    else
+      launch_argmax(c->logits, V, V, 1, 0, 1, c->tokens, rel_pos(c, j), 0, c->st, next);
   };
   decide(0);
   for (int j = 1; j < k; ++j) {
@@ -1072,24 +1095,32 @@ int enqueue_propose(stairs_ctx* c, int k, int nch) {
 }
 
 // Enqueue the stair batch for the k draft tokens sitting in tokens[L..L+k), its per-row argmax and the validation.
-int enqueue_verify(stairs_ctx* c, int k, int nch) {
+// in_loop: another iteration with this k may follow; this one's last launch leaves what it starts from (and k = 0: found its
+// own there)
+int enqueue_verify(stairs_ctx* c, int k, int nch, bool in_loop) {
   Model* m = &c->T;
   const int M = k + 1, V = m->cfg.vocab;
-  int rc = forward(c, m, rel_pos(c, -1), nch, M, M);
+  int rc = forward(c, m, rel_pos(c, -1), nch, M, M, 0, nullptr, in_loop && k == 0);
   if (rc) return rc;
-  launch_argmax(c->logits, V, V, M, 0, 1, c->tgt_tok, PosRef{nullptr, 0}, 0, c->st);
-  launch_accept(c->tokens, c->tgt_tok, k, c->state, 1, 0, c->st);
+  if (decide_takes(c->has_cand, M, V)) {
+    launch_decide_accept(c->has_cand ? reinterpret_cast<const float*>(c->cand) : c->logits, c->has_cand, V, k, c->tokens, c->tgt_tok, c->state, c->st,
+                         in_loop ? next_embed(c, first_model(c, k)) : NextEmbed{}, first_model_rows(c, k));
+  } else {
+    launch_argmax(c->logits, V, V, M, 0, 1, c->tgt_tok, PosRef{nullptr, 0}, 0, c->st);
+    launch_accept(c->tokens, c->tgt_tok, k, c->state, 1, 0, c->st);
+    if (in_loop) embed_first(c, k);
+  }
   HIPCHK(c, hipGetLastError());
   return STAIRS_OK;
 }
 
 // The two halves of a SAMPLED iteration: the assistant draws its k tokens one by one (its logits rows stay in
 // c->dlogits for the validation), then the stair batch, the rows' log-sum-exps and the keep / replace walk.
-int enqueue_propose_sampled(stairs_ctx* c, int k, int nch) {
+int enqueue_propose_sampled(stairs_ctx* c, int k, int nch, bool embedded) {
   Model* m = &c->D;
   const int V = m->cfg.vocab;
   const int r1 = first_rows(c);
-  int rc = forward(c, m, rel_pos(c, -r1), nch, r1, 1, 0, c->dlogits);
+  int rc = forward(c, m, rel_pos(c, -r1), nch, r1, 1, 0, c->dlogits, embedded);
   if (rc) return rc;
   auto decide = [&](int j) {
     launch_sample(c->dlogits + (size_t)j * V, V, c->samp, 0, c->tokens, rel_pos(c, j), c->samp_ws, c->st,
@@ -1105,13 +1136,14 @@ int enqueue_propose_sampled(stairs_ctx* c, int k, int nch) {
   return STAIRS_OK;
 }
 
-int enqueue_verify_sampled(stairs_ctx* c, int k, int nch) {
+int enqueue_verify_sampled(stairs_ctx* c, int k, int nch, bool in_loop) {
   Model* m = &c->T;
   const int M = k + 1, V = m->cfg.vocab;
-  int rc = forward(c, m, rel_pos(c, -1), nch, M, M);
+  int rc = forward(c, m, rel_pos(c, -1), nch, M, M, 0, nullptr, in_loop && k == 0);
   if (rc) return rc;
   launch_row_lse(c->logits, M, c->dlogits, k, V, V, c->samp, c->lse, c->st);
-  launch_accept_sampled(c->tokens, c->logits, c->dlogits, V, V, k, c->lse, c->samp, c->state, c->tgt_tok, c->samp_ws, c->st);
+  launch_accept_sampled(c->tokens, c->logits, c->dlogits, V, V, k, c->lse, c->samp, c->state, c->tgt_tok, c->samp_ws, c->st,
+                        in_loop ? next_embed(c, first_model(c, k)) : NextEmbed{}, first_model_rows(c, k));
   HIPCHK(c, hipGetLastError());
   return STAIRS_OK;
 }
@@ -1175,7 +1207,7 @@ int do_propose(stairs_ctx* c, int k, bool sampled = false) {
     int rc = ingest(c, m, m->valid, L - 2);
     if (rc) return rc;
   }
-  int rc = sampled ? enqueue_propose_sampled(c, k, chunks_for(L + k - 1)) : enqueue_propose(c, k, chunks_for(L + k - 1));
+  int rc = sampled ? enqueue_propose_sampled(c, k, chunks_for(L + k - 1), false) : enqueue_propose(c, k, chunks_for(L + k - 1), false);
   if (rc) return rc;
   m->valid = L + k - 1;      // tokens S, d_1..d_{k-1} are in the cache
   c->pending_k = k;
@@ -1200,7 +1232,7 @@ int finish_verify(stairs_ctx* c, int k, int* n_out) {
 }
 
 int do_verify(stairs_ctx* c, int k, int* n_out, bool sampled = false) {
-  int rc = sampled ? enqueue_verify_sampled(c, k, chunks_for(c->L + k)) : enqueue_verify(c, k, chunks_for(c->L + k));
+  int rc = sampled ? enqueue_verify_sampled(c, k, chunks_for(c->L + k), false) : enqueue_verify(c, k, chunks_for(c->L + k), false);
   if (rc) return rc;
   return finish_verify(c, k, n_out);
 }
@@ -1217,8 +1249,8 @@ int iteration_graph(stairs_ctx* c, int half, int k, int nch, hipGraphExec_t* out
   hipGraph_t graph = nullptr;
   HIPCHK(c, hipStreamBeginCapture(c->st, hipStreamCaptureModeThreadLocal));
   const int rc = B > 0 ? (half == 0 ? enqueue_propose_batch(c, B, k, nch) : enqueue_verify_batch(c, B, k, nch))
-                 : B < 0 ? (half == 0 ? enqueue_propose_sampled(c, k, nch) : enqueue_verify_sampled(c, k, nch))
-                         : (half == 0 ? enqueue_propose(c, k, nch) : enqueue_verify(c, k, nch));
+                 : B < 0 ? (half == 0 ? enqueue_propose_sampled(c, k, nch, true) : enqueue_verify_sampled(c, k, nch, true))
+                         : (half == 0 ? enqueue_propose(c, k, nch, true) : enqueue_verify(c, k, nch, true));
   hipError_t e = hipStreamEndCapture(c->st, &graph);
   if (rc) {
     if (graph) (void)hipGraphDestroy(graph);
@@ -1422,7 +1454,7 @@ static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
   if (frag_bytes(std::max(wide, fmax)) > kFragHalfU4 * 16) return fail(c, STAIRS_EINVAL, "d_model / d_ffn too large for the activation fragment blocks");
   if ((rc = dev_alloc(c, &c->x, (size_t)kMaxFwdRows * dmax)) || (rc = dev_alloc(c, &c->ssq, (size_t)kMaxFwdRows * ssq_groups(dmax))) ||
       (rc = dev_alloc(c, &c->q_rot, (size_t)kMaxFwdRows * wide)) || (rc = dev_alloc(c, &c->attn_out, (size_t)kMaxFwdRows * wide)) ||
-      (rc = dev_alloc(c, &c->h, (size_t)kMaxFwdRows * fmax)) || (rc = dev_alloc(c, &c->logits, (size_t)kMaxRows * w.vocab)) ||
+      (rc = dev_alloc(c, &c->h, (size_t)kMaxFwdRows * fmax)) || (rc = dev_alloc(c, &c->logits, (size_t)kMaxRows * w.vocab)) || (rc = dev_alloc(c, &c->cand, (size_t)8 * (w.vocab / 16))) ||
       (rc = dev_alloc(c, &c->partial, w.partial_floats)) ||
       (rc = dev_alloc(c, &c->xf, frag_alloc_bytes(dmax) / sizeof(uint4))) || (rc = dev_alloc(c, &c->af, frag_alloc_bytes(wide) / sizeof(uint4))) ||
       (rc = dev_alloc(c, &c->hf, frag_alloc_bytes(fmax) / sizeof(uint4))) ||
@@ -1665,10 +1697,10 @@ static int decode_loop(stairs_ctx* c, int32_t G, int32_t k, bool adaptive, int32
       HIPCHK(c, hipEventRecord(ev[1], c->st));
       HIPCHK(c, hipGraphLaunch(gv, c->st));
     } else {
-      if (k > 0 && (rc = sampled ? enqueue_propose_sampled(c, k, chunks_for(L + k - 1)) : enqueue_propose(c, k, chunks_for(L + k - 1))))
+      if (k > 0 && (rc = sampled ? enqueue_propose_sampled(c, k, chunks_for(L + k - 1), true) : enqueue_propose(c, k, chunks_for(L + k - 1), true)))
         return rc;
       HIPCHK(c, hipEventRecord(ev[1], c->st));
-      if ((rc = sampled ? enqueue_verify_sampled(c, k, chunks_for(L + k)) : enqueue_verify(c, k, chunks_for(L + k)))) return rc;
+      if ((rc = sampled ? enqueue_verify_sampled(c, k, chunks_for(L + k), true) : enqueue_verify(c, k, chunks_for(L + k), true))) return rc;
     }
     HIPCHK(c, hipEventRecord(ev[2], c->st));
     HIPCHK(c, hipMemcpyAsync(c->h_pinned + 2 * set, c->state, 2 * sizeof(int), hipMemcpyDeviceToHost, c->st));
@@ -1694,10 +1726,15 @@ static int decode_loop(stairs_ctx* c, int32_t G, int32_t k, bool adaptive, int32
     }
     return code;
   };
+  // what the first iteration starts from: the draft's rows of earlier positions (later ones find them), then the embeddings
+  if (G > 0) {
+    if (k > 0 && !c->shared_kv && c->D.valid < c->L - 2 && (rc = ingest(c, &c->D, c->D.valid, c->L - 2))) return rc;
+    embed_first(c, k);
+    HIPCHK(c, hipGetLastError());
+  }
   for (;;) {
     const int L_most = c->L + in_flight * (k + 1);
     if (in_flight < depth && L_most - L0 < G) {
-      if (in_flight == 0 && k > 0 && !c->shared_kv && c->D.valid < c->L - 2 && (rc = ingest(c, &c->D, c->D.valid, c->L - 2))) return rc;
       if ((rc = enqueue((oldest + in_flight) & 1, L_most))) return failed(rc);
       ++in_flight;
       continue;

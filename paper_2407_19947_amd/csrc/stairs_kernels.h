@@ -108,6 +108,7 @@ struct GemmEpi {
   uint4* frag_out;
   const float* frag_gain;
   int act;                  // Head role only: kActNone / kActRelu
+  float2* cand;             // Head role on k_gemm_bf16_rows: [M][N / 16] (largest value, its column) of each tile's outputs; nullptr: none
   int stream_weights;       // bf16: read the weights with the streaming hint (models far larger than the memory-side cache)
 };
 
@@ -208,6 +209,15 @@ int attn_f32_rows(int units, int H, int M);
 // forward whose only row is that token at that position.
 void launch_argmax(const float* logits, int ld, int V, int nrows, int row0, int row_stride, int* out, PosRef out_pos,
                    int out_slot_stride, hipStream_t st, const NextEmbed& next = NextEmbed{});
+// The same and what follows it in one launch, for M <= 8 rows of one sequence (decide_takes).  src: the unembedding's candidates
+// (cand: GemmEpi::cand, V / 16 pairs a row), else the rows of V logits themselves.
+//   launch_decide       : M = 1, tokens[out_pos] = the choice; next: its embedding
+//   launch_decide_accept: the choices of k + 1 stair rows (to tgt as well), launch_accept, and the embeddings of the last
+//                         next_rows (1 or 2) tokens then, as rows 0 .. of a forward
+bool decide_takes(bool cand, int M, int V);
+void launch_decide(const float* src, bool cand, int V, int M, int* tokens, PosRef out_pos, hipStream_t st, const NextEmbed& next);
+void launch_decide_accept(const float* src, bool cand, int V, int k, int* tokens, int* tgt, int* state, hipStream_t st, const NextEmbed& next,
+                          int next_rows);
 // stairs validation on device, one block per slot s (one sequence: nslots = 1, strides unused): state = {L, n, 0,
 // active}.  n = longest run with tokens[L+i] == tgt[i]; tokens[L+n] = tgt[n]; state[0] = L+n+1; state[1] = n.
 // tokens of slot s start at s * tok_slot_stride, its tgt at s * (k+1), its state at s * kSlotState.
@@ -240,7 +250,8 @@ void launch_sample(const float* logits, int V, const SampleParams* sp, int strea
 // keep / replace walk over a sampled stair batch of one sequence (see k_accept_sampled); lse = launch_row_lse over
 // the k+1 rows of tl followed by the k rows of dl
 void launch_accept_sampled(int* tokens, const float* tl, const float* dl, int ld, int V, int k, const float* lse,
-                           const SampleParams* sp, int* state, int* emitted, SampleWs* ws, hipStream_t st);
+                           const SampleParams* sp, int* state, int* emitted, SampleWs* ws, hipStream_t st, const NextEmbed& next = NextEmbed{},
+                           int next_rows = 1);
 
 // ---- row blocks (bf16 models): prompts, forwards of many sequences, encoders -------------------------------------
 // The projections of a block of up to kPfRows rows run on the MFMA-bound kernel k_gemm_bf16_block: the weights in the

@@ -499,6 +499,22 @@ __device__ __forceinline__ float lds_chunk_sum(const float* base, int stride, in
   return a;
 }
 
+// (value, index) pairs: the larger value, of equal ones the lower index
+__device__ __forceinline__ void argmax_take(float& best, int& bi, float ov, int oi) {
+  if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
+}
+template <int CTRL>
+__device__ __forceinline__ void argmax_dpp(float& best, int& bi) {
+  argmax_take(best, bi, dpp<CTRL>(best), __builtin_amdgcn_update_dpp(0, bi, CTRL, 0xF, 0xF, true));
+}
+__device__ __forceinline__ void argmax_swap(float& best, int& bi, bool far) {      // lanes at distance 32 or 16
+  const uint32_t b = __float_as_uint(best), i = (uint32_t)bi;
+  const auto rb = far ? __builtin_amdgcn_permlane32_swap(b, b, false, false) : __builtin_amdgcn_permlane16_swap(b, b, false, false);
+  const auto ri = far ? __builtin_amdgcn_permlane32_swap(i, i, false, false) : __builtin_amdgcn_permlane16_swap(i, i, false, false);
+  const bool second = threadIdx.x & (far ? 32 : 16);     // (this lane's own value is in the other half of the pair)
+  argmax_take(best, bi, __uint_as_float(second ? rb[0] : rb[1]), (int)(second ? ri[0] : ri[1]));
+}
+
 // ROWMAJOR: W as the caller has it, [N, K] row-major: lane r + 16 g reads row 16 tile + r, k 32 kt + 8 g .. + 8, the very
 // operand the tile layout holds in one piece (a wave's load is then 16 runs of 64 bytes; for a matrix used once that is
 // far less than laying it out first).
@@ -746,6 +762,15 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
       }
       out[(size_t)m * N + col] = a;
       out[(size_t)m * N + col + 8] = b;
+      if (epi.cand) {                                      // the tile's largest value, for k_decide
+        float v = a;
+        int ix = col;
+        if (b > v) { v = b; ix = col + 8; }
+        argmax_dpp<kDppXor1>(v, ix);
+        argmax_dpp<kDppXor2>(v, ix);
+        argmax_dpp<kDppHalfMirror>(v, ix);
+        if (j == 0) epi.cand[(size_t)m * NTILES + tile] = make_float2(v, __int_as_float(ix));
+      }
       if (R > 4 && epi.frag_out) {
         const float4 va = make_float4(dpp<kDppQuad0>(a), dpp<kDppQuad1>(a), dpp<kDppQuad2>(a), dpp<kDppQuad3>(a));
         const float4 vb = make_float4(dpp<kDppQuad0>(b), dpp<kDppQuad1>(b), dpp<kDppQuad2>(b), dpp<kDppQuad3>(b));
@@ -1555,13 +1580,16 @@ __device__ __forceinline__ void embed_cols(const E* emb, int id, int vocab, int 
 }
 // The embedding the next forward of one row starts from, by a work-group of nth threads that all know the token: position p,
 // token id (kernel that decided them: no launch of its own, no round trip through the token array).
-__device__ __forceinline__ void next_embed(const NextEmbed& n, int p, int id, int nth) {
+__device__ __forceinline__ void next_embed(const NextEmbed& n, int p, int id, int nth, int row = 0) {
   const int tid = threadIdx.x;
+  float2* const cs = n.cs + row * 64;
+  float* const x = n.x + (size_t)row * n.d;
+  float* const ssq = n.ssq_part + row * ((n.d + kSsqGroup - 1) / kSsqGroup);
   if (p < 0 || p >= n.tok_cap) id = -1;
-  if (tid < n.hd / 2) n.cs[tid] = n.tab && p >= 0 && p < n.tab_len ? n.tab[(size_t)p * 64 + tid] : make_float2(1.f, 0.f);
+  if (tid < n.hd / 2) cs[tid] = n.tab && p >= 0 && p < n.tab_len ? n.tab[(size_t)p * 64 + tid] : make_float2(1.f, 0.f);
   for (int c = tid * 4; c - tid * 4 < n.d; c += nth * 4) {
-    if (n.bf16) embed_cols(static_cast<const uint16_t*>(n.emb), id, n.vocab, n.d, c, n.x, n.ssq_part, nullptr, 0, nullptr);
-    else embed_cols(static_cast<const float*>(n.emb), id, n.vocab, n.d, c, n.x, n.ssq_part, nullptr, 0, nullptr);
+    if (n.bf16) embed_cols(static_cast<const uint16_t*>(n.emb), id, n.vocab, n.d, c, x, ssq, nullptr, 0, nullptr);
+    else embed_cols(static_cast<const float*>(n.emb), id, n.vocab, n.d, c, x, ssq, nullptr, 0, nullptr);
   }
 }
 template <typename E>
@@ -2328,20 +2356,6 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
 // The position is requested first, the exchanges stay out of the LDS unit and the last thread reads the waves' results at once
 // (32000 logits, launches of 1 and 5 rows inside a 125M call: 5.4 -> 4.8 us).  NEXT: the same work-group goes on with the token's
 // embedding (5.4 us and a launch of 4.6 become 6.4 per draft token).
-__device__ __forceinline__ void argmax_take(float& best, int& bi, float ov, int oi) {
-  if (ov > best || (ov == best && oi < bi)) { best = ov; bi = oi; }
-}
-template <int CTRL>
-__device__ __forceinline__ void argmax_dpp(float& best, int& bi) {
-  argmax_take(best, bi, dpp<CTRL>(best), __builtin_amdgcn_update_dpp(0, bi, CTRL, 0xF, 0xF, true));
-}
-__device__ __forceinline__ void argmax_swap(float& best, int& bi, bool far) {      // lanes at distance 32 or 16
-  const uint32_t b = __float_as_uint(best), i = (uint32_t)bi;
-  const auto rb = far ? __builtin_amdgcn_permlane32_swap(b, b, false, false) : __builtin_amdgcn_permlane16_swap(b, b, false, false);
-  const auto ri = far ? __builtin_amdgcn_permlane32_swap(i, i, false, false) : __builtin_amdgcn_permlane16_swap(i, i, false, false);
-  const bool second = threadIdx.x & (far ? 32 : 16);     // (this lane's own value is in the other half of the pair)
-  argmax_take(best, bi, __uint_as_float(second ? rb[0] : rb[1]), (int)(second ? ri[0] : ri[1]));
-}
 template <bool NEXT>
 __global__ __launch_bounds__(1024) void k_argmax(const float* __restrict__ logits, int* __restrict__ out, const int* __restrict__ pos_base,
                                                  int pos_offset, int pos_rps, int ld, int V, int row0, int row_stride, int out_slot_stride,
@@ -2415,6 +2429,110 @@ void launch_argmax(const float* logits, int ld, int V, int nrows, int row0, int 
                    int out_slot_stride, hipStream_t st, const NextEmbed& next) {
   hipLaunchKernelGGL(next.emb ? k_argmax<true> : k_argmax<false>, dim3(nrows), dim3(1024), 0, st, logits, out, out_pos.base,
                      out_pos.offset, out_pos.rps, ld, V, row0, row_stride, out_slot_stride, next);
+}
+
+// The greedy choice of M <= 8 rows of one sequence and what follows from it, by one work-group whose waves share the rows:
+//   ACCEPT: validation of the stair batch (k_accept) and the embeddings the next iteration starts from;
+//   else  : a draft token (M = 1) and the embedding of the step it leads to.
+// CAND: src holds a (value, index) pair per row and 16 columns, left by the unembedding's work-groups (GemmEpi::cand); else the
+// rows of logits themselves, where they are short (decide_takes).  A row of 32000 logits through one CU took longer than all its
+// candidates, and the validation and the first embedding of a proposal were launches of their own (125M, k = 4, us: a draft token
+// 5.9 -> 4.7; choice of five rows, validation and embedding 4.6 + 2.1 + 2.2 -> 6.3; tiny fp32 pair 3.3 -> 3.2 and 2.7 + 1.3 + 2.2
+// -> 3.9).  What bounds it: the chain of three round trips (candidates, the token's embedding, its store).
+template <bool CAND, bool ACCEPT>
+__global__ __launch_bounds__(1024) void k_decide(const float* __restrict__ src, int* __restrict__ tokens, const int* __restrict__ pos_base,
+                                                 int pos_offset, int n, int M, int next_rows, int* __restrict__ tgt, int* __restrict__ state,
+                                                 NextEmbed next) {
+  __shared__ float s_v[16];
+  __shared__ int s_i[16], s_id[2], s_pos;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int base = *pos_base;                              // ACCEPT: L
+  const int wpr = 16 / (unsigned)M, m = wave / (unsigned)wpr, seg = wave - m * wpr;
+  int mine = 0, prev = 0, active = 0;
+  if (ACCEPT && wave == 0) {                               // lane i: draft token i
+    mine = tokens[base + min(lane, M - 1)];
+    prev = tokens[max(base - 1, 0)];
+    active = state[3];
+  }
+  float best = -INFINITY;
+  int bi = 0x7fffffff;
+  if (m < M) {
+    const float* row = src + (size_t)m * n * (CAND ? 2 : 1);
+    constexpr int NL = ACCEPT ? 16 : 2;                    // (2000 pairs a row: one round trip up to 7 rows)
+    for (int e0 = seg * 64 + lane; e0 < n; e0 += wpr * 64 * NL) {
+      float2 x[NL];
+#pragma unroll
+      for (int i = 0; i < NL; ++i) {
+        const int e = min(e0 + i * wpr * 64, n - 1);
+        x[i] = CAND ? reinterpret_cast<const float2*>(row)[e] : make_float2(row[e], __int_as_float(e));
+      }
+#pragma unroll
+      for (int i = 0; i < NL; ++i)
+        if (e0 + i * wpr * 64 < n && (x[i].x > best || bi == 0x7fffffff)) { best = x[i].x; bi = __float_as_int(x[i].y); }
+    }
+  }
+  argmax_swap(best, bi, true);
+  argmax_swap(best, bi, false);
+  argmax_dpp<kDppRor8>(best, bi);
+  argmax_dpp<kDppRor4>(best, bi);
+  argmax_dpp<kDppXor2>(best, bi);
+  argmax_dpp<kDppXor1>(best, bi);
+  if (lane == 0) { s_v[wave] = best; s_i[wave] = bi; }
+  __syncthreads();
+  if (wave == 0) {
+    // 16 lanes put a row's shares together, then lane i takes row i's
+    auto row_choice = [&](int first) {
+      const int r = first + (lane >> 4), q = lane & 15;
+      const bool has = r < M && q < wpr;
+      float v = has ? s_v[r * wpr + q] : -INFINITY;
+      int ix = has ? s_i[r * wpr + q] : 0x7fffffff;
+      argmax_dpp<kDppRor8>(v, ix);
+      argmax_dpp<kDppRor4>(v, ix);
+      argmax_dpp<kDppXor2>(v, ix);
+      argmax_dpp<kDppXor1>(v, ix);
+      return ix;
+    };
+    bi = row_choice(0);
+    if (ACCEPT) {
+      const int k = M - 1;
+      bi = __shfl(bi, (lane & 3) * 16);
+      if (M > 4) {
+        const int hi = __shfl(row_choice(4), (lane & 3) * 16);
+        if (lane & 4) bi = hi;
+      }
+      if (lane < M) tgt[lane] = bi;
+      const unsigned long long differ = __ballot(lane < k && mine != bi);
+      const int acc = differ ? __builtin_ctzll(differ) : k;
+      const int before = __shfl(bi, max(acc - 1, 0));
+      if (lane == acc) {
+        if (active) {
+          tokens[base + acc] = bi;
+          state[0] = base + acc + 1;
+          state[1] = acc;
+        }
+        s_id[0] = acc > 0 ? before : prev;
+        s_id[1] = bi;
+        s_pos = base + acc;
+      }
+    } else if (lane == 0) {
+      tokens[base + pos_offset] = bi;
+      s_id[1] = bi;
+      s_pos = base + pos_offset;
+    }
+  }
+  if (!next.emb) return;
+  __syncthreads();
+  for (int i = 0; i < next_rows; ++i) next_embed(next, s_pos - (next_rows - 1 - i), s_id[2 - next_rows + i], 1024, i);
+}
+bool decide_takes(bool cand, int M, int V) { return M <= 8 && (cand || M * V <= 16384); }
+void launch_decide(const float* src, bool cand, int V, int M, int* tokens, PosRef out_pos, hipStream_t st, const NextEmbed& next) {
+  hipLaunchKernelGGL((cand ? k_decide<true, false> : k_decide<false, false>), dim3(1), dim3(1024), 0, st, src, tokens, out_pos.base, out_pos.offset,
+                     cand ? V / 16 : V, M, 1, nullptr, nullptr, next);
+}
+void launch_decide_accept(const float* src, bool cand, int V, int k, int* tokens, int* tgt, int* state, hipStream_t st, const NextEmbed& next,
+                          int next_rows) {
+  hipLaunchKernelGGL((cand ? k_decide<true, true> : k_decide<false, true>), dim3(1), dim3(1024), 0, st, src, tokens, state, 0, cand ? V / 16 : V, k + 1,
+                     next_rows, tgt, state, next);
 }
 
 // (a lane per draft token: one round trip behind the state's, whatever k)
@@ -2587,10 +2705,10 @@ __global__ __launch_bounds__(256) void k_sample(const float* __restrict__ logits
 __global__ __launch_bounds__(256) void k_accept_sampled(int* __restrict__ tokens, int* __restrict__ state, const float* __restrict__ lse,
                                                         const SampleParams* __restrict__ sp, const float* __restrict__ tl,
                                                         const float* __restrict__ dl, int ld, int V, int k, int* __restrict__ emitted,
-                                                        SampleWs* ws) {
+                                                        SampleWs* ws, NextEmbed next, int next_rows) {
   __shared__ double sv[4];
   __shared__ int si[4];
-  __shared__ int s_n, s_flag, s_empty;
+  __shared__ int s_n, s_flag, s_empty, s_id[2];
   __shared__ float s_lse[2 * kMaxRows];
   const int tid = threadIdx.x;
   const int L = state[0];
@@ -2650,10 +2768,15 @@ __global__ __launch_bounds__(256) void k_accept_sampled(int* __restrict__ tokens
   if (tid < n) emitted[tid] = tokens[L + tid];
   if (tid == 0) {
     emitted[n] = bi;
+    s_id[0] = tokens[max(pos - 1, 0)];
+    s_id[1] = bi;
     tokens[pos] = bi;
     state[0] = L + n + 1;
     state[1] = n;
   }
+  if (!next.emb) return;                                 // (the block that decided the last token, as in k_decide)
+  __syncthreads();
+  for (int i = 0; i < next_rows; ++i) next_embed(next, pos - (next_rows - 1 - i), s_id[2 - next_rows + i], 256, i);
 }
 
 void launch_row_lse(const float* a, int n_a, const float* b, int n_b, int ld, int V, const SampleParams* sp, float* lse,
@@ -2667,9 +2790,9 @@ void launch_sample(const float* logits, int V, const SampleParams* sp, int strea
                      next);
 }
 void launch_accept_sampled(int* tokens, const float* tl, const float* dl, int ld, int V, int k, const float* lse,
-                           const SampleParams* sp, int* state, int* emitted, SampleWs* ws, hipStream_t st) {
+                           const SampleParams* sp, int* state, int* emitted, SampleWs* ws, hipStream_t st, const NextEmbed& next, int next_rows) {
   hipLaunchKernelGGL(k_accept_sampled, dim3(sample_blocks(V)), dim3(256), 0, st, tokens, state, lse, sp, tl, dl, ld, V, k,
-                     emitted, ws);
+                     emitted, ws, next, next_rows);
 }
 
 // plain streaming copy, the calibration kernel for HBM traffic counters

@@ -1,0 +1,49 @@
+"""The launch that chooses, validates and embeds in one: ties go to the lowest id wherever the equal logits lie (in one work-group's
+16 columns, in different ones), at every number of rows it takes and just beyond."""
+import numpy as np
+import pytest
+
+import paper_2407_19947_amd as pkg
+import synth_inputs as si
+
+pytestmark = pytest.mark.gpu
+
+
+def _pair(dtype, vocab):
+    if dtype == "fp32":
+        w = si.scaled_workload("cfg1_tiny_fp32", target=dict(n_layers=2, d_model=256, n_heads=4, d_ffn=512, vocab=vocab),
+                               draft=dict(kind="prefix", n_layers=1))
+    else:
+        w = si.scaled_workload("cfg2_125m", target=dict(n_layers=2, d_model=256, n_heads=4, d_ffn=512, vocab=vocab),
+                               draft=dict(kind="prefix", n_layers=1))
+    target, draft = si.make_pair(w)
+    return w, target, draft
+
+
+@pytest.mark.parametrize("dtype,vocab", [("bf16", 2048), ("bf16", 4112), ("bf16", 32), ("fp32", 1024), ("fp32", 4100)])
+@pytest.mark.parametrize("step", ["neighbours", "halves"])
+def test_ties_go_to_the_lowest_id(dtype, vocab, step):
+    w, target, draft = _pair(dtype, vocab)
+    head = np.array(target.lm_head)
+    if step == "neighbours":
+        head[1::2] = head[0::2]
+    else:
+        head[vocab // 2:] = head[:vocab // 2]
+    target.lm_head = head
+    draft.lm_head = head
+    prompt = si.make_prompt(w, 21) % vocab
+    for k in (0, 1, 2, 3, 4, 5, 6, 7, 8):
+        with pkg.Stairs(target, draft, k_max=8, max_seq=96) as s:
+            tokens, st = s.generate(prompt, 30, k)
+            s.prefill(prompt)                          # the same step by step: no launch does more than its own part there
+            steps = []
+            while len(steps) < 30:
+                if k:
+                    s.propose(k)
+                tgt, n = s.verify(k)[:2]
+                steps += [int(t) for t in tgt[:n + 1]]
+        assert list(tokens) == steps[:30]
+        if k == 0:
+            want = list(tokens)
+        assert list(tokens) == want
+        assert all(t % 2 == 0 for t in tokens) if step == "neighbours" else all(t < vocab // 2 for t in tokens)
