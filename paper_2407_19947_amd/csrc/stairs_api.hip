@@ -554,8 +554,8 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
     e.pos = pos;
     e.Kc = reinterpret_cast<_Float16*>(Kl);
     e.Vc = reinterpret_cast<_Float16*>(Vl);
-    e.Kc32 = reinterpret_cast<float*>(Kl);
-    e.Vc32 = reinterpret_cast<float*>(Vl);
+    e.Kc32 = b ? nullptr : reinterpret_cast<float*>(Kl);
+    e.Vc32 = b ? nullptr : reinterpret_cast<float*>(Vl);
     e.cap = m->cap;
     e.H = H;
     e.hd = m->hd;
@@ -2375,8 +2375,8 @@ int stairs_time_kernel(stairs_ctx* c, int32_t which, int32_t M, int32_t ctx_len,
       e.pos = tpos;
       e.Kc = reinterpret_cast<_Float16*>(Kl);
       e.Vc = reinterpret_cast<_Float16*>(Vl);
-      e.Kc32 = reinterpret_cast<float*>(Kl);
-      e.Vc32 = reinterpret_cast<float*>(Vl);
+      e.Kc32 = b ? nullptr : reinterpret_cast<float*>(Kl);
+      e.Vc32 = b ? nullptr : reinterpret_cast<float*>(Vl);
       e.cap = m->cap;
       e.H = g.n_heads;
       e.hd = m->hd;

@@ -99,7 +99,10 @@ struct GemmEpi {
   PosRef pos;
   _Float16* Kc;             // bf16 models: half caches of this layer, tiled layout
   _Float16* Vc;
-  float* Kc32;              // fp32 models: float caches of this layer, [H][cap][hd]
+  union {
+    float* Kc32;            // fp32 models: float caches of this layer, [H][cap][hd]
+    float2* cand;           // Head role on k_gemm_bf16_rows: [M][N / 16] (largest value, its column) of each tile's outputs; nullptr: none
+  };
   float* Vc32;
   int cap, H, hd;
   size_t kv_slot_stride;    // elements between the caches of consecutive slots (several sequences), else unused
@@ -108,7 +111,6 @@ struct GemmEpi {
   uint4* frag_out;
   const float* frag_gain;
   int act;                  // Head role only: kActNone / kActRelu
-  float2* cand;             // Head role on k_gemm_bf16_rows: [M][N / 16] (largest value, its column) of each tile's outputs; nullptr: none
   int stream_weights;       // bf16: read the weights with the streaming hint (models far larger than the memory-side cache)
 };
 
