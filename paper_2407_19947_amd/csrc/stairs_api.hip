@@ -121,7 +121,7 @@ struct stairs_ctx {
   int eos_id = -1;             // end token of the generation loops (stairs_set_eos); -1: none
   int* h_pinned = nullptr;     // pinned host: [0..1] state, [2..2+kMaxRows) target tokens (decode_loop with two iterations in
                                // flight: [2..3] the second one's state); batch: [n_slots][kSlotState] state
-  int h_pinned_ints = 0;
+  int h_pinned_ints = 0;       // ints of it; four more behind them take the results of iterations in flight (HostResult)
   // host mirror
   int L = 0, P = 0;
   bool prefilled = false;
@@ -1094,6 +1094,13 @@ int enqueue_propose(stairs_ctx* c, int k, int nch, bool embedded) {
   return STAIRS_OK;
 }
 
+// where an iteration of one sequence leaves its result for the host; its count of turns is the state's spare slot
+HostResult host_result(const stairs_ctx* c, bool in_loop) {
+  void* at = nullptr;
+  if (!in_loop || hipHostGetDevicePointer(&at, c->h_pinned, 0) != hipSuccess) return HostResult{};
+  return HostResult{static_cast<int*>(at) + c->h_pinned_ints, c->state + c->n_slots * kSlotState};
+}
+
 // Enqueue the stair batch for the k draft tokens sitting in tokens[L..L+k), its per-row argmax and the validation.
 // in_loop: another iteration with this k may follow; this one's last launch leaves what it starts from (and k = 0: found its
 // own there)
@@ -1104,7 +1111,7 @@ int enqueue_verify(stairs_ctx* c, int k, int nch, bool in_loop) {
   if (rc) return rc;
   if (decide_takes(c->has_cand, M, V)) {
     launch_decide_accept(c->has_cand ? reinterpret_cast<const float*>(c->cand) : c->logits, c->has_cand, V, k, c->tokens, c->tgt_tok, c->state, c->st,
-                         in_loop ? next_embed(c, first_model(c, k)) : NextEmbed{}, first_model_rows(c, k));
+                         in_loop ? next_embed(c, first_model(c, k)) : NextEmbed{}, first_model_rows(c, k), host_result(c, in_loop));
   } else {
     launch_argmax(c->logits, V, V, M, 0, 1, c->tgt_tok, PosRef{nullptr, 0}, 0, c->st);
     launch_accept(c->tokens, c->tgt_tok, k, c->state, 1, 0, c->st);
@@ -1143,7 +1150,7 @@ int enqueue_verify_sampled(stairs_ctx* c, int k, int nch, bool in_loop) {
   if (rc) return rc;
   launch_row_lse(c->logits, M, c->dlogits, k, V, V, c->samp, c->lse, c->st);
   launch_accept_sampled(c->tokens, c->logits, c->dlogits, V, V, k, c->lse, c->samp, c->state, c->tgt_tok, c->samp_ws, c->st,
-                        in_loop ? next_embed(c, first_model(c, k)) : NextEmbed{}, first_model_rows(c, k));
+                        in_loop ? next_embed(c, first_model(c, k)) : NextEmbed{}, first_model_rows(c, k), host_result(c, in_loop));
   HIPCHK(c, hipGetLastError());
   return STAIRS_OK;
 }
@@ -1477,7 +1484,7 @@ static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
   if (hipMemsetAsync(c->state, 0, 2 * kSlotState * sizeof(int), c->st) != hipSuccess) return bail(STAIRS_EHIP);
   if (hipMemsetAsync(c->counters, 0, kCounters * sizeof(int), c->st) != hipSuccess) return bail(STAIRS_EHIP);
   c->h_pinned_ints = 2 * kSlotState + kMaxRows;     // single sequence: 2 + rows; a batch of one slot: state + rows
-  if (hipHostMalloc(reinterpret_cast<void**>(&c->h_pinned), c->h_pinned_ints * sizeof(int), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc(reinterpret_cast<void**>(&c->h_pinned), (c->h_pinned_ints + 4) * sizeof(int), hipHostMallocDefault) != hipSuccess) {
     c->h_pinned = nullptr;
     return bail(STAIRS_ENOMEM);
   }
@@ -1684,6 +1691,10 @@ static int decode_loop(stairs_ctx* c, int32_t G, int32_t k, bool adaptive, int32
   // Not with an end token or a draft length that follows the results, nor without graphs (attention grids are then exact).
   const int depth = c->use_graphs && !adaptive && c->eos_id < 0 ? 2 : 1;
   int in_flight = 0, oldest = 0;
+  // results: written to host memory by the iteration's last launch where it is one of those that do, else copied behind it
+  const bool direct = depth == 2 &&
+                      (sampled || decide_takes(c->T.bf16 && rows_path_lds(kRoleHead, k + 1, c->T.cfg.vocab, c->T.cfg.d_model) > 0, k + 1, c->T.cfg.vocab));
+  if (direct) HIPCHK(c, hipMemsetAsync(c->state + c->n_slots * kSlotState, 0, sizeof(int), c->st));
   auto enqueue = [&](int set, int L) -> int {      // L: the longest the sequence can be by then
     hipEvent_t* const ev = c->ev + 8 + 4 * set;
     HIPCHK(c, hipEventRecord(ev[0], c->st));
@@ -1703,6 +1714,7 @@ static int decode_loop(stairs_ctx* c, int32_t G, int32_t k, bool adaptive, int32
       if ((rc = sampled ? enqueue_verify_sampled(c, k, chunks_for(L + k), true) : enqueue_verify(c, k, chunks_for(L + k), true))) return rc;
     }
     HIPCHK(c, hipEventRecord(ev[2], c->st));
+    if (direct) return STAIRS_OK;
     HIPCHK(c, hipMemcpyAsync(c->h_pinned + 2 * set, c->state, 2 * sizeof(int), hipMemcpyDeviceToHost, c->st));
     if (c->eos_id >= 0)                            // (one in flight: behind the state of the only set)
       HIPCHK(c, hipMemcpyAsync(c->h_pinned + 2, c->tgt_tok, (k + 1) * sizeof(int), hipMemcpyDeviceToHost, c->st));
@@ -1741,9 +1753,9 @@ static int decode_loop(stairs_ctx* c, int32_t G, int32_t k, bool adaptive, int32
     }
     if (in_flight == 0) break;
     hipEvent_t* const ev = c->ev + 8 + 4 * oldest;
-    const int* const res = c->h_pinned + 2 * oldest;
+    const int* const res = (direct ? c->h_pinned + c->h_pinned_ints : c->h_pinned) + 2 * oldest;
     float a = 0.f, b = 0.f;
-    hipError_t e = hipEventSynchronize(ev[3]);
+    hipError_t e = hipEventSynchronize(ev[direct ? 2 : 3]);
     if (e == hipSuccess) e = hipEventElapsedTime(&a, ev[0], ev[1]);
     if (e == hipSuccess) e = hipEventElapsedTime(&b, ev[1], ev[2]);
     if (e != hipSuccess) {
@@ -1986,7 +1998,7 @@ int stairs_reserve_batch(stairs_ctx* c, int32_t max_batch) {
   c->state = state;
   int* hp = nullptr;
   const int ints = std::max(2 + kMaxRows, max_batch * kSlotState + c->rows_cap);
-  if (hipHostMalloc(reinterpret_cast<void**>(&hp), ints * sizeof(int), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc(reinterpret_cast<void**>(&hp), (ints + 4) * sizeof(int), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     return fail(c, STAIRS_ENOMEM, "hipHostMalloc failed");
   }

@@ -216,10 +216,15 @@ void launch_argmax(const float* logits, int ld, int V, int nrows, int row0, int 
 //   launch_decide       : M = 1, tokens[out_pos] = the choice; next: its embedding
 //   launch_decide_accept: the choices of k + 1 stair rows (to tgt as well), launch_accept, and the embeddings of the last
 //                         next_rows (1 or 2) tokens then, as rows 0 .. of a forward
+// host (at nullptr: none): {L, n} also go to at[0 .. 1] or at[2 .. 3], memory of the host, as *turn, which counts up, is even or odd
+struct HostResult {
+  int* at;
+  int* turn;
+};
 bool decide_takes(bool cand, int M, int V);
 void launch_decide(const float* src, bool cand, int V, int M, int* tokens, PosRef out_pos, hipStream_t st, const NextEmbed& next);
 void launch_decide_accept(const float* src, bool cand, int V, int k, int* tokens, int* tgt, int* state, hipStream_t st, const NextEmbed& next,
-                          int next_rows);
+                          int next_rows, const HostResult& host);
 // stairs validation on device, one block per slot s (one sequence: nslots = 1, strides unused): state = {L, n, 0,
 // active}.  n = longest run with tokens[L+i] == tgt[i]; tokens[L+n] = tgt[n]; state[0] = L+n+1; state[1] = n.
 // tokens of slot s start at s * tok_slot_stride, its tgt at s * (k+1), its state at s * kSlotState.
@@ -253,7 +258,7 @@ void launch_sample(const float* logits, int V, const SampleParams* sp, int strea
 // the k+1 rows of tl followed by the k rows of dl
 void launch_accept_sampled(int* tokens, const float* tl, const float* dl, int ld, int V, int k, const float* lse,
                            const SampleParams* sp, int* state, int* emitted, SampleWs* ws, hipStream_t st, const NextEmbed& next = NextEmbed{},
-                           int next_rows = 1);
+                           int next_rows = 1, const HostResult& host = HostResult{});
 
 // ---- row blocks (bf16 models): prompts, forwards of many sequences, encoders -------------------------------------
 // The projections of a block of up to kPfRows rows run on the MFMA-bound kernel k_gemm_bf16_block: the weights in the

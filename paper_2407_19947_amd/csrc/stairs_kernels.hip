@@ -2439,20 +2439,29 @@ void launch_argmax(const float* logits, int ld, int V, int nrows, int row0, int 
 // candidates, and the validation and the first embedding of a proposal were launches of their own (125M, k = 4, us: a draft token
 // 5.9 -> 4.7; choice of five rows, validation and embedding 4.6 + 2.1 + 2.2 -> 6.3; tiny fp32 pair 3.3 -> 3.2 and 2.7 + 1.3 + 2.2
 // -> 3.9).  What bounds it: the chain of three round trips (candidates, the token's embedding, its store).
+// {L, n} of an iteration to the host, in turn to two places: no copy behind the iteration, which was a launch of 3 us
+__device__ __forceinline__ void host_result(const HostResult& h, int turn, int L, int n) {
+  if (!h.at) return;
+  int* const at = h.at + 2 * (turn & 1);
+  __hip_atomic_store(at, L, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(at + 1, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  *h.turn = turn + 1;
+}
 template <bool CAND, bool ACCEPT>
 __global__ __launch_bounds__(1024) void k_decide(const float* __restrict__ src, int* __restrict__ tokens, const int* __restrict__ pos_base,
                                                  int pos_offset, int n, int M, int next_rows, int* __restrict__ tgt, int* __restrict__ state,
-                                                 NextEmbed next) {
+                                                 HostResult host, NextEmbed next) {
   __shared__ float s_v[16];
   __shared__ int s_i[16], s_id[2], s_pos;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int base = *pos_base;                              // ACCEPT: L
   const int wpr = 16 / (unsigned)M, m = wave / (unsigned)wpr, seg = wave - m * wpr;
-  int mine = 0, prev = 0, active = 0;
+  int mine = 0, prev = 0, active = 0, turn = 0;
   if (ACCEPT && wave == 0) {                               // lane i: draft token i
     mine = tokens[base + min(lane, M - 1)];
     prev = tokens[max(base - 1, 0)];
     active = state[3];
+    if (host.at) turn = *host.turn;
   }
   float best = -INFINITY;
   int bi = 0x7fffffff;
@@ -2509,6 +2518,7 @@ __global__ __launch_bounds__(1024) void k_decide(const float* __restrict__ src, 
           tokens[base + acc] = bi;
           state[0] = base + acc + 1;
           state[1] = acc;
+          host_result(host, turn, base + acc + 1, acc);
         }
         s_id[0] = acc > 0 ? before : prev;
         s_id[1] = bi;
@@ -2527,12 +2537,12 @@ __global__ __launch_bounds__(1024) void k_decide(const float* __restrict__ src, 
 bool decide_takes(bool cand, int M, int V) { return M <= 8 && (cand || M * V <= 16384); }
 void launch_decide(const float* src, bool cand, int V, int M, int* tokens, PosRef out_pos, hipStream_t st, const NextEmbed& next) {
   hipLaunchKernelGGL((cand ? k_decide<true, false> : k_decide<false, false>), dim3(1), dim3(1024), 0, st, src, tokens, out_pos.base, out_pos.offset,
-                     cand ? V / 16 : V, M, 1, nullptr, nullptr, next);
+                     cand ? V / 16 : V, M, 1, nullptr, nullptr, HostResult{}, next);
 }
 void launch_decide_accept(const float* src, bool cand, int V, int k, int* tokens, int* tgt, int* state, hipStream_t st, const NextEmbed& next,
-                          int next_rows) {
+                          int next_rows, const HostResult& host) {
   hipLaunchKernelGGL((cand ? k_decide<true, true> : k_decide<false, true>), dim3(1), dim3(1024), 0, st, src, tokens, state, 0, cand ? V / 16 : V, k + 1,
-                     next_rows, tgt, state, next);
+                     next_rows, tgt, state, host, next);
 }
 
 // (a lane per draft token: one round trip behind the state's, whatever k)
@@ -2705,7 +2715,7 @@ __global__ __launch_bounds__(256) void k_sample(const float* __restrict__ logits
 __global__ __launch_bounds__(256) void k_accept_sampled(int* __restrict__ tokens, int* __restrict__ state, const float* __restrict__ lse,
                                                         const SampleParams* __restrict__ sp, const float* __restrict__ tl,
                                                         const float* __restrict__ dl, int ld, int V, int k, int* __restrict__ emitted,
-                                                        SampleWs* ws, NextEmbed next, int next_rows) {
+                                                        SampleWs* ws, HostResult host, NextEmbed next, int next_rows) {
   __shared__ double sv[4];
   __shared__ int si[4];
   __shared__ int s_n, s_flag, s_empty, s_id[2];
@@ -2773,6 +2783,7 @@ __global__ __launch_bounds__(256) void k_accept_sampled(int* __restrict__ tokens
     tokens[pos] = bi;
     state[0] = L + n + 1;
     state[1] = n;
+    if (host.at) host_result(host, *host.turn, L + n + 1, n);
   }
   if (!next.emb) return;                                 // (the block that decided the last token, as in k_decide)
   __syncthreads();
@@ -2790,9 +2801,10 @@ void launch_sample(const float* logits, int V, const SampleParams* sp, int strea
                      next);
 }
 void launch_accept_sampled(int* tokens, const float* tl, const float* dl, int ld, int V, int k, const float* lse,
-                           const SampleParams* sp, int* state, int* emitted, SampleWs* ws, hipStream_t st, const NextEmbed& next, int next_rows) {
+                           const SampleParams* sp, int* state, int* emitted, SampleWs* ws, hipStream_t st, const NextEmbed& next, int next_rows,
+                           const HostResult& host) {
   hipLaunchKernelGGL(k_accept_sampled, dim3(sample_blocks(V)), dim3(256), 0, st, tokens, state, lse, sp, tl, dl, ld, V, k,
-                     emitted, ws, next, next_rows);
+                     emitted, ws, host, next, next_rows);
 }
 
 // plain streaming copy, the calibration kernel for HBM traffic counters

@@ -47,3 +47,28 @@ def test_ties_go_to_the_lowest_id(dtype, vocab, step):
             want = list(tokens)
         assert list(tokens) == want
         assert all(t % 2 == 0 for t in tokens) if step == "neighbours" else all(t < vocab // 2 for t in tokens)
+
+
+@pytest.mark.parametrize("k", [0, 2, 8])
+def test_results_on_the_host_in_every_kind_of_loop(k):
+    """Odd and even numbers of iterations, one call after the other, with an end token in between (results copied again), draft
+    lengths that follow the acceptance, and behind a reservation, which moves what the launches write to."""
+    w, target, draft = _pair("bf16", 2048)
+    prompt = si.make_prompt(w, 21)
+    with pkg.Stairs(target, draft, k_max=8, max_seq=160) as s:
+        want, st = s.generate(prompt, 40, k)
+        s.prefill(prompt)
+        parts = []
+        for g in (1, 2, 3, 14, 20):
+            parts += list(s.decode(g, k)[0])
+        assert parts == list(want)
+        never = next(t for t in range(2048) if t not in want)
+        s.set_eos(never)
+        assert list(s.generate(prompt, 40, k)[0]) == list(want)
+        s.set_eos(-1)
+        s.prefill(prompt)
+        if k:
+            assert list(s.decode_adaptive(40, k)[0]) == list(want)
+        s.reserve_batch(3)
+        again, st2 = s.generate(prompt, 40, k)
+        assert list(again) == list(want) and st2.iterations == st.iterations
