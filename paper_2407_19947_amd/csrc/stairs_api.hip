@@ -117,17 +117,18 @@ struct stairs_ctx {
   int pf_rows = 0;             // rows the block workspaces (pf_*) hold
   int* counters = nullptr;     // [kCounters] split-K / attention hand-off tickets, zero between launches
   int* tgt_tok = nullptr;      // [kMaxRows]
-  int* state = nullptr;        // per slot kSlotState ints: [0] = L, [1] = n of last iteration, [2] = constant 0, [3] = active
+  int* state = nullptr;        // per slot kSlotState ints: [0] = L, [1] = n of last iteration, [2] = constant 0, [3] = active; a spare
+                               // slot (HostResult::turn) and, batches, the length at which each sequence stops (slot_limits)
   int eos_id = -1;             // end token of the generation loops (stairs_set_eos); -1: none
   int* h_pinned = nullptr;     // pinned host: [0..1] state, [2..2+kMaxRows) target tokens (decode_loop with two iterations in
-                               // flight: [2..3] the second one's state); batch: [n_slots][kSlotState] state
+                               // flight: [2..3] the second one's state); batch: two times [B][kSlotState] state, target tokens
   int h_pinned_ints = 0;       // ints of it; four more behind them take the results of iterations in flight (HostResult)
   // host mirror
   int L = 0, P = 0;
   bool prefilled = false;
   int pending_k = -1;          // draft length of the outstanding proposal, -1 = none
-  hipEvent_t ev[16] = {};      // 0,1,2: general; 5,6,7: iteration of a batch: start / after the proposal / after validation;
-                               // 8..11, 12..15: iterations of one sequence, two in flight: the same and results on the host
+  hipEvent_t ev[16] = {};      // 0,1,2: general; 8..11, 12..15: iterations, two in flight: start / after the proposal / after
+                               // validation / results on the host
   struct IterGraph { int half, k, nch, B; hipGraphExec_t exec; };   // B = 0: the single-sequence path, -1: its sampled variant
   std::vector<IterGraph> graphs;   // captured iterations, see iteration_graph()
   std::vector<hipEvent_t> probe_ev;   // stairs_time_kernel(8): event pairs around one projection inside a forward
@@ -1114,7 +1115,7 @@ int enqueue_verify(stairs_ctx* c, int k, int nch, bool in_loop) {
                          in_loop ? next_embed(c, first_model(c, k)) : NextEmbed{}, first_model_rows(c, k), host_result(c, in_loop));
   } else {
     launch_argmax(c->logits, V, V, M, 0, 1, c->tgt_tok, PosRef{nullptr, 0}, 0, c->st);
-    launch_accept(c->tokens, c->tgt_tok, k, c->state, 1, 0, c->st);
+    launch_accept(c->tokens, c->tgt_tok, k, c->state, 1, 0, nullptr, c->st);
     if (in_loop) embed_first(c, k);
   }
   HIPCHK(c, hipGetLastError());
@@ -1194,13 +1195,14 @@ int enqueue_propose_batch(stairs_ctx* c, int B, int k, int nch) {
   return STAIRS_OK;
 }
 
+int* slot_limits(const stairs_ctx* c) { return c->state + (c->n_slots + 1) * kSlotState; }
 int enqueue_verify_batch(stairs_ctx* c, int B, int k, int nch) {
   Model* m = &c->T;
   const int M = k + 1, V = m->cfg.vocab;
   int rc = forward(c, m, PosRef{c->state, -1, M}, nch, B * M, B * M);
   if (rc) return rc;
   launch_argmax(c->logits, V, V, B * M, 0, 1, c->tgt_tok, PosRef{nullptr, 0}, 0, c->st);
-  launch_accept(c->tokens, c->tgt_tok, k, c->state, B, c->tok_stride, c->st);
+  launch_accept(c->tokens, c->tgt_tok, k, c->state, B, c->tok_stride, slot_limits(c), c->st);
   HIPCHK(c, hipGetLastError());
   return STAIRS_OK;
 }
@@ -1468,7 +1470,7 @@ static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
       (rc = dev_alloc(c, &c->part_o, (size_t)kMaxRows * Hmax * c->nchunk_cap * 128)) ||
       (rc = dev_alloc(c, &c->part_ml, (size_t)kMaxRows * Hmax * c->nchunk_cap * 2)) ||
       (rc = dev_alloc(c, &c->rope_cs, (size_t)kMaxFwdRows * 64)) || (rc = dev_alloc(c, &c->tokens, (size_t)c->tok_cap + kMaxRows)) ||
-      (rc = dev_alloc(c, &c->tgt_tok, (size_t)kMaxRows)) || (rc = dev_alloc(c, &c->counters, (size_t)kCounters)) || (rc = dev_alloc(c, &c->state, 2 * kSlotState)))
+      (rc = dev_alloc(c, &c->tgt_tok, (size_t)kMaxRows)) || (rc = dev_alloc(c, &c->counters, (size_t)kCounters)) || (rc = dev_alloc(c, &c->state, 3 * kSlotState)))
     return bail(rc);
   if (c->block_prefill || c->encdec) {
     // rows per block: what the longest sequence needs, at most kPfRows; encoders take the whole source as one block
@@ -1481,9 +1483,9 @@ static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
   // every slot of the token array always holds a valid id: a diagnostic forward may run at positions the current
   // sequence has not reached, and the embedding gather takes whatever id it finds there
   if (hipMemsetAsync(c->tokens, 0, ((size_t)c->tok_cap + kMaxRows) * sizeof(int), c->st) != hipSuccess) return bail(STAIRS_EHIP);
-  if (hipMemsetAsync(c->state, 0, 2 * kSlotState * sizeof(int), c->st) != hipSuccess) return bail(STAIRS_EHIP);
+  if (hipMemsetAsync(c->state, 0, 3 * kSlotState * sizeof(int), c->st) != hipSuccess) return bail(STAIRS_EHIP);
   if (hipMemsetAsync(c->counters, 0, kCounters * sizeof(int), c->st) != hipSuccess) return bail(STAIRS_EHIP);
-  c->h_pinned_ints = 2 * kSlotState + kMaxRows;     // single sequence: 2 + rows; a batch of one slot: state + rows
+  c->h_pinned_ints = 2 * kSlotState + kMaxRows;     // single sequence: 2 + rows; a batch of one slot: two states + rows
   if (hipHostMalloc(reinterpret_cast<void**>(&c->h_pinned), (c->h_pinned_ints + 4) * sizeof(int), hipHostMallocDefault) != hipSuccess) {
     c->h_pinned = nullptr;
     return bail(STAIRS_ENOMEM);
@@ -1988,16 +1990,16 @@ int stairs_reserve_batch(stairs_ctx* c, int32_t max_batch) {
     if (gemm_takes_rows(kMaxFwdRows, kmax)) c->fwd_rows = kMaxFwdRows;
   }
   int *tok = nullptr, *state = nullptr;
-  if ((rc = dev_alloc(c, &tok, (size_t)max_batch * c->tok_stride)) || (rc = dev_alloc(c, &state, (size_t)(max_batch + 1) * kSlotState)))
+  if ((rc = dev_alloc(c, &tok, (size_t)max_batch * c->tok_stride)) || (rc = dev_alloc(c, &state, (size_t)(max_batch + 1) * kSlotState + max_batch)))
     return rc;
   HIPCHK(c, hipMemsetAsync(tok, 0, (size_t)max_batch * c->tok_stride * sizeof(int), c->st));
-  HIPCHK(c, hipMemsetAsync(state, 0, (size_t)(max_batch + 1) * kSlotState * sizeof(int), c->st));
+  HIPCHK(c, hipMemsetAsync(state, 0, ((size_t)(max_batch + 1) * kSlotState + max_batch) * sizeof(int), c->st));
   release(c, c->tokens);
   release(c, c->state);
   c->tokens = tok;
   c->state = state;
   int* hp = nullptr;
-  const int ints = std::max(2 + kMaxRows, max_batch * kSlotState + c->rows_cap);
+  const int ints = std::max(2 + kMaxRows, 2 * max_batch * kSlotState + c->rows_cap);
   if (hipHostMalloc(reinterpret_cast<void**>(&hp), (ints + 4) * sizeof(int), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     return fail(c, STAIRS_ENOMEM, "hipHostMalloc failed");
@@ -2056,6 +2058,9 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
   HIPCHK(c, hipMemcpy2DAsync(c->tokens, (size_t)c->tok_stride * sizeof(int), packed.get(), (size_t)Pmax * sizeof(int), (size_t)Pmax * sizeof(int), B,
                              hipMemcpyHostToDevice, c->st));
   HIPCHK(c, hipMemcpyAsync(c->state, hstate.data(), hstate.size() * sizeof(int), hipMemcpyHostToDevice, c->st));
+  std::vector<int> limits(B);
+  for (int b = 0; b < B; ++b) limits[b] = L0[b] + G;
+  HIPCHK(c, hipMemcpyAsync(slot_limits(c), limits.data(), (size_t)B * sizeof(int), hipMemcpyHostToDevice, c->st));
   HIPCHK(c, hipStreamSynchronize(c->st));
   for (Model* m : {&c->T, &c->D}) {
     if (m == &c->D && (!c->have_draft || c->shared_kv)) continue;
@@ -2063,36 +2068,68 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
   }
   c->T.valid = c->D.valid = 0;     // nothing the single-sequence calls could rely on
   HIPCHK(c, hipEventRecord(c->ev[1], c->st));
-  int n_active = G > 0 ? B : 0;
-  while (n_active > 0) {
+  // As in decode_loop, an iteration that is needed whatever the one before it keeps is launched while that one runs: validation
+  // itself ends a sequence that has its G tokens.  Not with an end token (the host cuts such a sequence) or without graphs.
+  const int depth = c->use_graphs && c->eos_id < 0 ? 2 : 1;
+  int in_flight = 0, oldest = 0;
+  auto longest = [&](int b) { return std::min(L[b] + in_flight * (k + 1), L0[b] + G - 1); };   // an active sequence's length by then
+  auto enqueue = [&](int set) -> int {
+    hipEvent_t* const ev = c->ev + 8 + 4 * set;
     int Lmax = 0;
     for (int b = 0; b < B; ++b)
-      if (active[b]) Lmax = std::max(Lmax, L[b]);
-    HIPCHK(c, hipEventRecord(c->ev[5], c->st));
+      if (active[b]) Lmax = std::max(Lmax, longest(b));
+    HIPCHK(c, hipEventRecord(ev[0], c->st));
     if (c->use_graphs) {
       const int nch = std::min((chunks_for(Lmax + k) + 3) / 4 * 4, c->nchunk_cap);
       hipGraphExec_t gp = nullptr, gv = nullptr;
       if (k > 0 && (rc = iteration_graph(c, 0, k, nch, &gp, B))) return rc;
       if ((rc = iteration_graph(c, 1, k, nch, &gv, B))) return rc;
       if (k > 0) HIPCHK(c, hipGraphLaunch(gp, c->st));
-      HIPCHK(c, hipEventRecord(c->ev[6], c->st));
+      HIPCHK(c, hipEventRecord(ev[1], c->st));
       HIPCHK(c, hipGraphLaunch(gv, c->st));
     } else {
       if (k > 0 && (rc = enqueue_propose_batch(c, B, k, chunks_for(Lmax + k - 1)))) return rc;
-      HIPCHK(c, hipEventRecord(c->ev[6], c->st));
+      HIPCHK(c, hipEventRecord(ev[1], c->st));
       if ((rc = enqueue_verify_batch(c, B, k, chunks_for(Lmax + k)))) return rc;
     }
-    HIPCHK(c, hipEventRecord(c->ev[7], c->st));
-    HIPCHK(c, hipMemcpyAsync(c->h_pinned, c->state, (size_t)B * kSlotState * sizeof(int), hipMemcpyDeviceToHost, c->st));
-    int* emitted = c->h_pinned + (size_t)B * kSlotState;       // [B][k + 1] target tokens (with an end token only)
-    if (c->eos_id >= 0)
-      HIPCHK(c, hipMemcpyAsync(emitted, c->tgt_tok, (size_t)B * (k + 1) * sizeof(int), hipMemcpyDeviceToHost, c->st));
-    HIPCHK(c, hipStreamSynchronize(c->st));
-    bool any_done = false;
+    HIPCHK(c, hipEventRecord(ev[2], c->st));
+    HIPCHK(c, hipMemcpyAsync(c->h_pinned + (size_t)set * B * kSlotState, c->state, (size_t)B * kSlotState * sizeof(int), hipMemcpyDeviceToHost, c->st));
+    if (c->eos_id >= 0)                                      // [B][k + 1] target tokens (with an end token only)
+      HIPCHK(c, hipMemcpyAsync(c->h_pinned + (size_t)2 * B * kSlotState, c->tgt_tok, (size_t)B * (k + 1) * sizeof(int), hipMemcpyDeviceToHost, c->st));
+    HIPCHK(c, hipEventRecord(ev[3], c->st));
+    return STAIRS_OK;
+  };
+  auto failed = [&](int code) {                              // what is in flight ends before the caller may touch the context
+    (void)hipStreamSynchronize(c->st);
+    return code;
+  };
+  for (;;) {
+    bool needed = false;
+    for (int b = 0; b < B; ++b) needed |= active[b] && L[b] + in_flight * (k + 1) - L0[b] < G;
+    if (in_flight < depth && needed) {
+      if ((rc = enqueue((oldest + in_flight) & 1))) return failed(rc);
+      ++in_flight;
+      continue;
+    }
+    if (in_flight == 0) break;
+    hipEvent_t* const ev = c->ev + 8 + 4 * oldest;
+    const int* const res = c->h_pinned + (size_t)oldest * B * kSlotState;
+    const int* const emitted = c->h_pinned + (size_t)2 * B * kSlotState;
+    float a = 0.f, bms = 0.f;
+    hipError_t e = hipEventSynchronize(ev[3]);
+    if (e == hipSuccess) e = hipEventElapsedTime(&a, ev[0], ev[1]);
+    if (e == hipSuccess) e = hipEventElapsedTime(&bms, ev[1], ev[2]);
+    if (e != hipSuccess) {
+      c->err = std::string("waiting for an iteration: ") + hipGetErrorString(e);
+      return failed(STAIRS_EHIP);
+    }
+    --in_flight;
+    if (depth == 2) oldest ^= 1;
+    bool any_ended = false;
     for (int b = 0; b < B; ++b) {
       if (!active[b]) continue;
-      const int n = c->h_pinned[b * kSlotState + 1];
-      if (c->h_pinned[b * kSlotState] != L[b] + n + 1 || n < 0 || n > k) return fail(c, STAIRS_EHIP, "device state out of sync with host");
+      const int n = res[b * kSlotState + 1];
+      if (res[b * kSlotState] != L[b] + n + 1 || n < 0 || n > k) return failed(fail(c, STAIRS_EHIP, "device state out of sync with host"));
       L[b] += n + 1;
       s.accepted += n;
       s.accept_hist[n] += 1;
@@ -2102,15 +2139,14 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
         if (j <= n) {
           L[b] += j - n;
           ended[b] = 1;
+          any_ended = true;
         }
       }
       if (ended[b] || L[b] - L0[b] >= G) {
         active[b] = 0;
-        --n_active;
-        any_done = true;
       }
     }
-    if (any_done) {                                   // finished slots stop: their rows get no position any more
+    if (any_ended) {                                    // (those that have their G tokens have stopped by themselves)
       for (int b = 0; b < B; ++b) {
         hstate[b * kSlotState + 0] = L[b];
         hstate[b * kSlotState + 3] = active[b];
@@ -2118,9 +2154,6 @@ int stairs_generate_batch(stairs_ctx* c, const int32_t* const* prompts, const in
       HIPCHK(c, hipMemcpyAsync(c->state, hstate.data(), hstate.size() * sizeof(int), hipMemcpyHostToDevice, c->st));
       HIPCHK(c, hipStreamSynchronize(c->st));
     }
-    float a = 0.f, bms = 0.f;
-    HIPCHK(c, hipEventElapsedTime(&a, c->ev[5], c->ev[6]));
-    HIPCHK(c, hipEventElapsedTime(&bms, c->ev[6], c->ev[7]));
     s.ms_draft += a;
     s.ms_verify += bms;
     s.iterations += 1;

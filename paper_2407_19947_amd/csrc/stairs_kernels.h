@@ -227,8 +227,9 @@ void launch_decide_accept(const float* src, bool cand, int V, int k, int* tokens
                           int next_rows, const HostResult& host);
 // stairs validation on device, one block per slot s (one sequence: nslots = 1, strides unused): state = {L, n, 0,
 // active}.  n = longest run with tokens[L+i] == tgt[i]; tokens[L+n] = tgt[n]; state[0] = L+n+1; state[1] = n.
-// tokens of slot s start at s * tok_slot_stride, its tgt at s * (k+1), its state at s * kSlotState.
-void launch_accept(int* tokens, const int* tgt, int k, int* state, int nslots, int tok_slot_stride, hipStream_t st);
+// tokens of slot s start at s * tok_slot_stride, its tgt at s * (k+1), its state at s * kSlotState.  limits (nullptr: none): the
+// slot stops being active where its sequence reaches limits[s] tokens.
+void launch_accept(int* tokens, const int* tgt, int k, int* state, int nslots, int tok_slot_stride, const int* limits, hipStream_t st);
 
 // ---- sampling variant -------------------------------------------------------------------------------------
 // Device-resident parameters of a sampled generation (so that captured launches stay valid across seeds)

@@ -2547,12 +2547,12 @@ void launch_decide_accept(const float* src, bool cand, int V, int k, int* tokens
 
 // (a lane per draft token: one round trip behind the state's, whatever k)
 __global__ __launch_bounds__(64) void k_accept(int* __restrict__ tokens, const int* __restrict__ tgt, int k, int* __restrict__ state,
-                                               int tok_slot_stride) {
+                                               int tok_slot_stride, const int* __restrict__ limits) {
   const int s = blockIdx.x, i = threadIdx.x;   // slot
   state += s * kSlotState;
   tokens += (size_t)s * tok_slot_stride;
   const int t = tgt[s * (k + 1) + min(i, k)];
-  const int L = state[0];
+  const int L = state[0], limit = limits ? limits[s] : 0x7fffffff;
   if (!state[3]) return;                    // the slot is not generating (any more)
   const unsigned long long differ = __ballot(i < k && tokens[L + min(i, k)] != t);
   const int n = differ ? __builtin_ctzll(differ) : k;
@@ -2560,12 +2560,13 @@ __global__ __launch_bounds__(64) void k_accept(int* __restrict__ tokens, const i
     tokens[L + n] = t;
     state[0] = L + n + 1;
     state[1] = n;
+    if (L + n + 1 >= limit) state[3] = 0;
   }
 }
 static_assert(kMaxRows <= 64, "k_accept, k_accept_sampled: a lane per stair row");
 
-void launch_accept(int* tokens, const int* tgt, int k, int* state, int nslots, int tok_slot_stride, hipStream_t st) {
-  hipLaunchKernelGGL(k_accept, dim3(nslots), dim3(64), 0, st, tokens, tgt, k, state, tok_slot_stride);
+void launch_accept(int* tokens, const int* tgt, int k, int* state, int nslots, int tok_slot_stride, const int* limits, hipStream_t st) {
+  hipLaunchKernelGGL(k_accept, dim3(nslots), dim3(64), 0, st, tokens, tgt, k, state, tok_slot_stride, limits);
 }
 
 // ---------------------------------------------------------------------------------------
