@@ -2249,19 +2249,18 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
   if (tid == 0) counters[h] = 0;
 }
 
-// the merge alone (long contexts: the attention work-groups then leave without waiting for their stores)
+// the merge alone (long contexts: the attention work-groups then leave without waiting for their stores), a work-group per head and
+// row (a head's rows one after the other in one: 32 heads of 128, 33 chunks, 5 rows 8.1 -> 4.9 us)
 template <int HD>
 __global__ __launch_bounds__(256) void k_attn_merge(const float* part_o, const float* part_ml, const int* __restrict__ pos_base, int pos_offset,
-                                                    int pos_rps, int d, int H, int M, int kv_fixed, int nchunk_cap, int nch_lds, int rows_per_pass,
+                                                    int pos_rps, int d, int H, int M, int kv_fixed, int nchunk_cap, int nch_lds,
                                                     float* __restrict__ out, uint4* frag, int frag_rt) {
   const PosRef pos{pos_base, pos_offset, pos_rps};
   extern __shared__ float s_ml[];
-  const int h = blockIdx.x, row0 = blockIdx.y * M;
-  const bool fixed = kv_fixed > 0;
-  const int pos0 = fixed ? kv_fixed - 1 : pos_of(pos, row0);
-  attn_merge<HD>(part_o + (size_t)row0 * H * nchunk_cap * HD, part_ml + (size_t)row0 * H * nchunk_cap * 2, H, h, M, pos0,
-                 fixed ? 0 : 1, pos0 + (fixed ? 1 : M), nchunk_cap, nch_lds, rows_per_pass, out + (size_t)row0 * d, d, s_ml,
-                 frag, frag_rt, row0);
+  const int h = blockIdx.x, row = blockIdx.y * M + blockIdx.z;
+  const int last = kv_fixed > 0 ? kv_fixed - 1 : pos_of(pos, row);     // last key the row sees
+  attn_merge<HD>(part_o + (size_t)row * H * nchunk_cap * HD, part_ml + (size_t)row * H * nchunk_cap * 2, H, h, 1, last, 0, last + 1,
+                 nchunk_cap, nch_lds, 1, out + (size_t)row * d, d, s_ml, frag, frag_rt, row);
 }
 
 // Query rows a work-group of the fp32 attention takes.  Up to 8 rows: one, as long as that makes fewer than 1024 groups (four
@@ -2324,6 +2323,7 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
     const size_t budget = std::min<size_t>(48 * 1024, kAttnMergeMaxLds > table ? kAttnMergeMaxLds - table : 0);
     const int rpp = G > 1 ? std::max(1, std::min(M, (int)(budget / per_row))) : M;
     const size_t lds = table + (G > 1 ? (size_t)rpp * per_row : 0);
+    const size_t lds_row = ((size_t)nchunk_launch * 2 + kMaxRows) * sizeof(float) + (G > 1 ? per_row : 0);   // of one row
     // long contexts: attention work-groups only store their partials, a second kernel merges (no wait, no ticket)
     const bool fused = nchunk_launch <= kAttnFusedMaxChunks;
 #define STAIRS_ATTN16(hdv, ct)                                                                                              \
@@ -2333,8 +2333,8 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
   else {                                                                                                                    \
     hipLaunchKernelGGL((k_attn_f16<hdv, ct, false>), grid, block, 0, st, q_rot, K, V, pos.base, pos.offset, pos.rps, cap, d, M, early, \
                        kv_slot_stride, scale, H, am, nchunk_cap, rpp, part_o, part_ml, counters, out);                                         \
-    hipLaunchKernelGGL((k_attn_merge<hdv>), dim3(H, nslots), dim3(256), lds, st, part_o, part_ml, pos.base, pos.offset,    \
-                       pos.rps, d, H, M, am.kv_fixed, nchunk_cap, nchunk_launch, rpp, out, am.frag_out, am.frag_rt);         \
+    hipLaunchKernelGGL((k_attn_merge<hdv>), dim3(H, nslots, M), dim3(256), lds_row, st, part_o, part_ml, pos.base, pos.offset, \
+                       pos.rps, d, H, M, am.kv_fixed, nchunk_cap, nchunk_launch, out, am.frag_out, am.frag_rt);              \
   }
     if (hd == 128) {
       if (M <= 16) STAIRS_ATTN16(128, 1) else STAIRS_ATTN16(128, 2)
