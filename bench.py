@@ -117,6 +117,12 @@ def encdec_leg(name):
     return out
 
 
+def ingested_weights(m):
+    """Projection weights a prompt's rows go through: all layers, of the last one the query, key and value matrices."""
+    d, f = m.d_model, m.d_ffn
+    return m.n_layers * (4 * d * d + 3 * d * f) - (d * d + 3 * d * f)
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -152,6 +158,7 @@ def main():
     prompt = si.make_prompt(w)
     log(f"[bench] {args.workload}: weights drawn in {time.time() - t0:.1f}s "
         f"(target {target.n_params() / 1e9:.2f}B, draft {draft.n_params() / 1e9:.2f}B params)")
+    ingested = (target,) if w["draft"]["kind"] == "prefix" else (target, draft)
     k_max = 16
     t0 = time.time()
     eng = pkg.Stairs(target, draft, k_max=k_max, max_seq=P + G + k_max + 8)
@@ -340,10 +347,11 @@ def main():
         "accept_hist": list(stats_last.accept_hist)[:k + 1],
         "ms_draft_per_step": stats_last.ms_draft, "ms_verify_per_step": stats_last.ms_verify,
         "prefill_ms": prefill_ms, "k_sweep": k_table,
-        # prompt ingestion (outside the timed region): the layer projections of both models over the P-1 ingested rows,
-        # each activation issued as a high and a low bf16 part, against the dense bf16 MFMA peak
+        # prompt ingestion (outside the timed region): the layer projections over the P-1 ingested rows of every model that
+        # ingests (a draft that is the target's first layers shares its caches) up to its last layer's keys and values, each
+        # activation issued as a high and a low bf16 part, against the dense bf16 MFMA peak
         "prefill": {"ms": prefill_ms, "rows": P - 1, "tokens_per_s": (P - 1) / (prefill_ms * 1e-3),
-                    "issued_mfma_frac_of_2.5PFLOPs": (2.0 * 2.0 * (P - 1) * sum(m.n_params() - m.vocab * m.d_model for m in (target, draft))
+                    "issued_mfma_frac_of_2.5PFLOPs": (2.0 * 2.0 * (P - 1) * sum(ingested_weights(m) for m in ingested)
                                                       / (prefill_ms * 1e-3) / 2.5e15) if w["dtype"] == "bf16" else None},
         "plain_greedy_tokens_per_s": G / plain_s,
         "time_reduction_vs_plain_greedy_pct": 100.0 * (1.0 - (total / len(decode_s)) / plain_s),

@@ -103,6 +103,8 @@ const char *stairs_last_error(const stairs_ctx *ctx);
  * k = 0 is then legal, which is plain greedy generation of the target -- the paper's
  * "batch size 1", Sec. 4.3).  k_max: largest draft length that will be used, 0 <= k_max <
  * STAIRS_MAX_ROWS.  Both models must have the same vocab.  hip_stream: a hipStream_t or NULL.
+ * A draft that is the target's first layers (the same arrays for embedding and layer matrices, norm gains
+ * and dimensions alike, the same max_seq) shares the target's weights and KV caches.
  * Errors: EINVAL (shapes, NULLs), ENOMEM, EHIP.  On error *out is NULL. */
 int stairs_init(stairs_ctx **out, const stairs_model_cfg *tcfg, const stairs_weights *tw,
                 const stairs_model_cfg *dcfg, const stairs_weights *dw, int32_t k_max,
