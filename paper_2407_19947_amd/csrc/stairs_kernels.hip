@@ -58,6 +58,10 @@ void launch_swizzle_bf16(const uint16_t* W, uint4* Wsw, int N, int K, int perm, 
 //   Split-K: every work-group writes its partial sums; the one that arrives last at the column
 //   group's counter adds the slices up in slice order (so the result does not depend on which
 //   one that is) and applies the epilogue of the projection (ROLE).
+//   What bounds it is a chain of round trips: activations, weights, partial sums, ticket, sums.  So all activations (of both
+//   chunks) are requested at the start behind the first weight unit, two units stay requested at every time, and nothing
+//   is requested under a condition.  2048 x 8192, 9 rows (one work-group per CU): 16.2 -> 13.5 us; 1024 x 16384, 1..4 rows:
+//   12.7 -> 11.6 us; 4096 x 11008, 16 rows (three work-groups per CU hide it already): 24.0 -> 23.9 us.
 // ---------------------------------------------------------------------------------------
 // Sum of the split-K partial sums of one element (or 4 adjacent ones).  The order is fixed for every GEMM variant:
 // the 512-wide k chunks are added in pairs, (c0 + c1), (c2 + c3), ..., and the pair sums one after the other.
@@ -176,10 +180,11 @@ __device__ __forceinline__ void gemm_epilogue(const float* partial, int S, int M
       const int m = idx / PR, col = c0 + (idx - m * PR) * 4;
       float ss = 0.f;
       if (idx < total && col < N) {
+        float4* xp = reinterpret_cast<float4*>(epi.out + (size_t)m * N + col);
+        const float4 r = *xp;                           // requested ahead of the partial sums
+        __builtin_amdgcn_sched_barrier(0);
         float4 a = slice_sum4<PAIRS>(partial, S, stride, (size_t)m * N + col);
         if (rs) { const float q = rs[m]; a.x *= q; a.y *= q; a.z *= q; a.w *= q; }
-        float4* xp = reinterpret_cast<float4*>(epi.out + (size_t)m * N + col);
-        const float4 r = *xp;
         a.x += r.x; a.y += r.y; a.z += r.z; a.w += r.w;
         *xp = a;
         ss = sumsq4(a.x, a.y, a.z, a.w);
@@ -316,7 +321,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
   extern __shared__ uint4 lds[];   // [16 k-steps][CT][hi,lo][64 lanes]
   __shared__ int s_last;
   __shared__ float s_rstd[kMaxRows];
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int sp = blockIdx.y, SG = gridDim.y;               // this work-group's partial slice, number of them
   const int units_total = K / kUnitK;
   // weights are stored slice-major: [k chunk][row tile][k-step][lane]; the four waves take adjacent tiles, so
@@ -328,52 +333,53 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
     const int j = u / (kSliceUnits * NT), t = (u / kSliceUnits) % NT, ku = u % kSliceUnits;
     return ku < chunk_units(j) && (tile0 + 4 * t) < NTILES;
   };
-  auto unit_ptr = [&](int u) {
-    const int j = u / (kSliceUnits * NT), t = (u / kSliceUnits) % NT, ku = u % kSliceUnits;
-    return Wsw + (size_t)(sp * SPW + j) * NTILES * (kSliceUnits * 8) * 64 +
-           ((size_t)(tile0 + 4 * t) * chunk_units(j) + ku) * 8 * 64 + lane;
-  };
-
+  // requested whatever the condition says (a request inside a condition would make every wait behind it one for all
+  // requests); a unit that is not there is not fetched
   uint4 wb[2][8];
+  auto request = [&](int u) {
+    const int j = u / (kSliceUnits * NT), t = (u / kSliceUnits) % NT, ku = u % kSliceUnits;
+    const uint4* p = Wsw + (size_t)(sp * SPW + j) * NTILES * (kSliceUnits * 8) * 64 + ((size_t)(tile0 + 4 * t) * chunk_units(j) + ku) * 8 * 64;
+    load_unit_in<STREAM, 64>(p, lane * 16, unit_ok(u) ? 8 * 64 * 16 : 0, wb[u & 1]);
+  };
   // first weight unit goes out before anything else: it depends on nothing
-  if (unit_ok(0)) {
-    const uint4* p = unit_ptr(0);
-    load_unit<STREAM>(p, wb[0]);
+  request(0);
+
+  // the X chunks: this thread's items are (row m, 8 consecutive k)
+  constexpr int ITEMS = 4 * CT;          // 16*CT rows x 64 groups / 256 threads (a full chunk)
+  float4 xa[SPW][ITEMS], xb[SPW][ITEMS], g0[SPW], g1[SPW];
+#pragma unroll
+  for (int j = 0; j < SPW; ++j) {
+    const int units = chunk_units(j), kgs = max(units, 1) * 32, k0 = (sp * SPW + j) * kSliceUnits * kUnitK;
+#pragma unroll
+    for (int it = 0; it < ITEMS; ++it) {
+      const int w = tid + 256 * it;
+      const int m = w / kgs, kg = w - m * kgs;
+      xa[j][it] = make_float4(0.f, 0.f, 0.f, 0.f);
+      xb[j][it] = xa[j][it];
+      if (units > 0 && w < 16 * CT * kgs && m < M) {
+        const float4* xp = reinterpret_cast<const float4*>(X + (size_t)m * ldx + k0 + kg * 8);
+        xa[j][it] = xp[0];
+        xb[j][it] = xp[1];
+      }
+    }
+    // the norm gain of this thread's k group (every item of a thread has kg = lane modulo the 64 or 32 groups of the chunk)
+    g0[j] = make_float4(1.f, 1.f, 1.f, 1.f);
+    g1[j] = g0[j];
+    if (nrm.gain && units > 0) {
+      const float4* gp = reinterpret_cast<const float4*>(nrm.gain + k0 + (lane & (kgs - 1)) * 8);
+      g0[j] = gp[0];
+      g1[j] = gp[1];
+    }
   }
+  __builtin_amdgcn_sched_barrier(0);
+  request(1);
+  __builtin_amdgcn_sched_barrier(0);
 
   f32x4 sum[NT][CT];
 #pragma unroll
   for (int j = 0; j < SPW; ++j) {
-    const int units = chunk_units(j);
-    const int unit0 = (sp * SPW + j) * kSliceUnits;
-    // the X chunk: this thread's items are (row m, 8 consecutive k)
-    const int kgs = max(units, 1) * 32;    // groups of 8 k per row
-    const int k0 = unit0 * kUnitK;
-    constexpr int ITEMS = 4 * CT;          // 16*CT rows x 64 groups / 256 threads (a full chunk)
-    float4 xa[ITEMS], xb[ITEMS];
+    const int units = chunk_units(j), kgs = max(units, 1) * 32;    // groups of 8 k per row
     if (j > 0) __syncthreads();            // the previous chunk's fragments have been read
-    if (units > 0) {
-#pragma unroll
-      for (int it = 0; it < ITEMS; ++it) {
-        const int w = tid + 256 * it;
-        const int m = w / kgs, kg = w - m * kgs;
-        xa[it] = make_float4(0.f, 0.f, 0.f, 0.f);
-        xb[it] = xa[it];
-        if (w < 16 * CT * kgs && m < M) {
-          const float4* xp = reinterpret_cast<const float4*>(X + (size_t)m * ldx + k0 + kg * 8);
-          xa[it] = xp[0];
-          xb[it] = xp[1];
-        }
-      }
-    }
-    // the norm gain of this thread's k group (every item of a thread has kg = lane modulo the 64 or 32 groups of the chunk)
-    float4 g0 = make_float4(1.f, 1.f, 1.f, 1.f), g1 = g0;
-    if (nrm.gain && units > 0) {
-      const float4* gp = reinterpret_cast<const float4*>(nrm.gain + k0 + (lane & (kgs - 1)) * 8);
-      g0 = gp[0];
-      g1 = gp[1];
-    }
-
     // fp32 -> (x * gain) -> bf16 hi + lo, stored in B-fragment order
     if (units > 0) {
 #pragma unroll
@@ -383,7 +389,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
         if (w < 16 * CT * kgs) {
           const bool scale = nrm.gain && m < M;
           uint4 hi, lo;
-          split_bf16x8(xa[it], xb[it], g0, g1, scale, hi, lo);
+          split_bf16x8(xa[j][it], xb[j][it], g0[j], g1[j], scale, hi, lo);
           const int kt = kg >> 2, g = kg & 3, ct = m >> 4, jj = m & 15;
           const int base = ((kt * CT + ct) * 2) * 64 + g * 16 + jj;
           lds[base] = hi;
@@ -402,13 +408,6 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
 #pragma unroll
       for (int ku = 0; ku < kSliceUnits; ++ku) {
         const int u = (j * NT + t) * kSliceUnits + ku;
-        // prefetch the next unit into the other buffer (it may belong to the next chunk)
-        if (u + 1 < SPW * NT * kSliceUnits) {
-          if (unit_ok(u + 1)) {
-            const uint4* p = unit_ptr(u + 1);
-            load_unit<STREAM>(p, wb[(u + 1) & 1]);
-          }
-        }
         if (ku < units && tile_ok) {
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
@@ -422,6 +421,11 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
               acc[ct] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, bl, acc[ct], 0, 0, 0);
             }
           }
+        }
+        // the unit after the next (it may belong to the next chunk) into this one's registers
+        if (u + 2 < SPW * NT * kSliceUnits) {
+          request(u + 2);
+          __builtin_amdgcn_sched_barrier(0);
         }
       }
       // chunk sums of a pair are added once, first + second
