@@ -59,9 +59,17 @@ void launch_swizzle_bf16(const uint16_t* W, uint4* Wsw, int N, int K, int perm, 
 //   group's counter adds the slices up in slice order (so the result does not depend on which
 //   one that is) and applies the epilogue of the projection (ROLE).
 //   What bounds it is a chain of round trips: activations, weights, partial sums, ticket, sums.  So all activations (of both
-//   chunks) are requested at the start behind the first weight unit, two units stay requested at every time, and nothing
-//   is requested under a condition.  2048 x 8192, 9 rows (one work-group per CU): 16.2 -> 13.5 us; 1024 x 16384, 1..4 rows:
-//   12.7 -> 11.6 us; 4096 x 11008, 16 rows (three work-groups per CU hide it already): 24.0 -> 23.9 us.
+//   chunks) are requested at the start behind the first weight unit, two units stay requested at every time, and no weight
+//   unit is requested under a condition.  That takes registers, and with two chunks a grid may have two to three work-groups
+//   per CU (4096 x 12288: 768), which must all be resident: 3 waves per SIMD, held to 168 registers by fetching the second
+//   chunk's gains when the first's are used up (residual projections have none).  Launches one after the other over several
+//   layers' weights, us: one unit and one chunk's activations at a time (3 waves) / all at once (174 registers, 2 waves) / now:
+//     2048 x 8192   9 / 16 rows  15.7 / 12.9 / 12.8    16.3 / 13.6 / 13.4      4096 x 11008  9 / 16  20.1 / 21.4 / 20.0    21.8 / 22.5 / 21.6
+//     1024 x 16384  9 / 16 rows  14.3 / 12.3 / 12.0    14.9 / 13.0 / 12.6      4096 x 12288  9 / 16  21.1 / 24.0 / 21.2    22.6 / 25.9 / 22.7
+//     3072 x 8192   9 / 16 rows  15.4 / 14.5 / 14.4    16.6 / 15.8 / 15.4      5120 x 13824  9 / 16  30.2 / 29.5 / 29.9    32.6 / 31.5 / 32.6
+//   One chunk per work-group, before / now: 1024 x 16384 at 1 / 4 / 8 rows 12.2 / 11.3, 13.0 / 12.1, 14.3 / 13.5; 2048 x 8192 at 5 / 8
+//   12.3 / 11.4, 12.7 / 11.8; 4096 x 9216 at 5 rows 18.1 / 18.5, where it is 2 % behind; 17..32 rows (two work-groups per CU by
+//   their LDS) 1024 x 8192 12.5 / 11.5 .. 14.0 / 13.1.
 // ---------------------------------------------------------------------------------------
 // Sum of the split-K partial sums of one element (or 4 adjacent ones).  The order is fixed for every GEMM variant:
 // the 512-wide k chunks are added in pairs, (c0 + c1), (c2 + c3), ..., and the pair sums one after the other.
@@ -311,11 +319,13 @@ __device__ __forceinline__ void load_unit_in(const uint4* base, uint32_t off, ui
 }
 
 template <int CT, int NT, int ROLE, int SPW, bool STREAM>
-__global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw, const float* __restrict__ X,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SPW == 2 ? 3 : 1, 8))) void k_gemm_bf16(const uint4* __restrict__ Wsw, const float* __restrict__ X,
                                                   const float* __restrict__ gain, float* partial, int K, int N, int ldx, int M,
                                                   const float* ssq_part, int ssq_n, float eps, GemmEpi epi) {
+  constexpr bool NORMED = ROLE != kRoleWo && ROLE != kRoleDown;      // (the residual-writing projections' inputs are not)
   const RowNorm nrm{gain, ssq_part, ssq_n, eps};
-  const int KT = K >> 5, NTILES = N >> 4;
+  const bool scaled = NORMED && gain != nullptr;
+  const int NTILES = N >> 4;
   // SPW = k chunks (512 wide) a work-group takes, one after the other through the same LDS buffer: 1, or 2 (then
   // it writes the sum of its two chunk sums, which halves the partial sums in memory; used for many rows)
   extern __shared__ uint4 lds[];   // [16 k-steps][CT][hi,lo][64 lanes]
@@ -346,7 +356,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
 
   // the X chunks: this thread's items are (row m, 8 consecutive k)
   constexpr int ITEMS = 4 * CT;          // 16*CT rows x 64 groups / 256 threads (a full chunk)
-  float4 xa[SPW][ITEMS], xb[SPW][ITEMS], g0[SPW], g1[SPW];
+  float4 xa[SPW][ITEMS], xb[SPW][ITEMS];
 #pragma unroll
   for (int j = 0; j < SPW; ++j) {
     const int units = chunk_units(j), kgs = max(units, 1) * 32, k0 = (sp * SPW + j) * kSliceUnits * kUnitK;
@@ -362,15 +372,19 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
         xb[j][it] = xp[1];
       }
     }
-    // the norm gain of this thread's k group (every item of a thread has kg = lane modulo the 64 or 32 groups of the chunk)
-    g0[j] = make_float4(1.f, 1.f, 1.f, 1.f);
-    g1[j] = g0[j];
-    if (nrm.gain && units > 0) {
-      const float4* gp = reinterpret_cast<const float4*>(nrm.gain + k0 + (lane & (kgs - 1)) * 8);
-      g0[j] = gp[0];
-      g1[j] = gp[1];
-    }
   }
+  // the norm gain of this thread's k group (every item of a thread has kg = lane modulo the 64 or 32 groups of the chunk)
+  float4 g0, g1;
+  auto request_gain = [&](int j) {
+    const int units = chunk_units(j), kgs = max(units, 1) * 32;
+    if (scaled && units > 0) {
+      const float4* gp = reinterpret_cast<const float4*>(gain + (sp * SPW + j) * kSliceUnits * kUnitK + (lane & (kgs - 1)) * 8);
+      g0 = gp[0];
+      g1 = gp[1];
+    }
+  };
+  g0 = g1 = make_float4(1.f, 1.f, 1.f, 1.f);
+  request_gain(0);
   __builtin_amdgcn_sched_barrier(0);
   request(1);
   __builtin_amdgcn_sched_barrier(0);
@@ -387,9 +401,9 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
         const int w = tid + 256 * it;                       // w < 16*CT*kgs is uniform per wave
         const int m = min(w / kgs, 16 * CT - 1), kg = w - (w / kgs) * kgs;
         if (w < 16 * CT * kgs) {
-          const bool scale = nrm.gain && m < M;
+          const bool scale = scaled && m < M;
           uint4 hi, lo;
-          split_bf16x8(xa[j][it], xb[j][it], g0[j], g1[j], scale, hi, lo);
+          split_bf16x8(xa[j][it], xb[j][it], g0, g1, scale, hi, lo);
           const int kt = kg >> 2, g = kg & 3, ct = m >> 4, jj = m & 15;
           const int base = ((kt * CT + ct) * 2) * 64 + g * 16 + jj;
           lds[base] = hi;
@@ -397,6 +411,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
         }
       }
     }
+    if (j + 1 < SPW) request_gain(j + 1);
     __syncthreads();
 
 #pragma unroll
@@ -460,7 +475,7 @@ __global__ __launch_bounds__(256) void k_gemm_bf16(const uint4* __restrict__ Wsw
   // split-K hand-off: the partial sums are out, take a ticket; the last arrival finishes the group
   if (!last_arrival(&epi.counters[blockIdx.x], SG, &s_last)) return;
   // the rows' 1/rms is needed here only: the work-group that finishes a column group forms it
-  const bool normed = nrm.gain && nrm.ssq_part;
+  const bool normed = scaled && ssq_part;
   if (normed) {
     rows_rstd<2 * CT>(nrm, M, K, s_rstd);
     __syncthreads();
