@@ -1173,9 +1173,10 @@ bool launch_gemm_shared(int role, const void* W, int N, int K, const uint4* xfra
 //   L2 gives, and per 32 keys the masks, lane exchanges and rescaling of every step were more vector instructions than the
 //   MFMAs leave room for: now masks only at the diagonal, sums over the lanes at the end, rescaling where a maximum grew.
 //   Tiles of several sequences in one work-group: the runs of tiles of one sequence one after the other.
-//   Launches by themselves, before -> now, us: 32 heads of 128, 2048 rows behind nothing / behind 6144 keys 118 -> 87 / 663 -> 462
-//   (1.04 PFLOP/s issued), 333 rows 14.0 -> 12.3, 777 rows of an encoder 59 -> 49; 16 heads of 64, 2048 rows behind 6144 keys
-//   232 -> 156.  What bounds it then: MFMAs and the softmax's vector instructions on a SIMD, which overlap only in part.
+//   Launches by themselves, before -> now, us: 32 heads of 128, 2048 rows behind nothing / behind 6144 keys 110 -> 84 / 592 -> 404
+//   (1.19 PFLOP/s issued), 333 rows 13.4 -> 12.0, 777 rows of an encoder 54.2 -> 46.4; 16 heads of 64, 2048 rows behind 6144 keys
+//   200 -> 140.  (log2 e goes onto the differences from the maximum, 16 multiplications a step: onto the queries they overflow
+//   the half at 45400 instead of 65504, onto the scores a bias of the lowest float becomes infinite; 82 / 397 us.)  What bounds it then: MFMAs and the softmax's vector instructions on a SIMD, which overlap only in part.
 //   QT = 2 where that leaves two work-groups per CU, else 1.  Row blocks come longest first; where all work-groups are
 //   resident at once, the second half shortest first, so that a long one shares its CU with a short one.
 template <int HD, bool BIAS, int QT>
@@ -1210,7 +1211,6 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
   }
   int pos[QT], seen[QT], all_see[QT];                 // the lane's row; keys up to all_see are seen by the tile's 16 rows
   f16x8 qh[QT][KK], ql[QT][KK];
-  const float qscale = scale * 1.44269504088896340736f;                // scores in units of log 2
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
     const int row = r00 + (wave * QT + t) * 16 + j;
@@ -1229,7 +1229,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
         a = qp[0];
         b = qp[1];
       }
-      const float v[8] = {a.x * qscale, a.y * qscale, a.z * qscale, a.w * qscale, b.x * qscale, b.y * qscale, b.z * qscale, b.w * qscale};
+      const float v[8] = {a.x * scale, a.y * scale, a.z * scale, a.w * scale, b.x * scale, b.y * scale, b.z * scale, b.w * scale};
       split_half8(v, qh[t][kk], ql[t][kk]);
     }
   }
@@ -1282,7 +1282,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
 #pragma unroll
           for (int v = 0; v < 4; ++v) {
             const int key = kb + i * 16 + g * 4 + v;
-            if (key <= sees[t]) sacc[t][i][v] += brow[key - pos[t]] * 1.44269504088896340736f;
+            if (key <= sees[t]) sacc[t][i][v] += brow[key - pos[t]];
           }
       }
       if (all[t] < kb + 63) {                          // (uniform: some row does not see some key)
@@ -1300,7 +1300,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
       mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
       if (__any(mx > m_run[t])) {
         const float m_new = fmaxf(m_run[t], mx);
-        const float alpha = m_run[t] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m_run[t] - m_new);
+        const float alpha = m_run[t] == -INFINITY ? 0.f : exp_fast(m_run[t] - m_new);
         l_run[t] *= alpha;
 #pragma unroll
         for (int et = 0; et < ET; ++et) {
@@ -1313,7 +1313,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
       for (int b = 0; b < 2; ++b) {
         float pv[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) pv[i] = __builtin_amdgcn_exp2f(sacc[t][2 * b + (i >> 2)][i & 3] - m);
+        for (int i = 0; i < 8; ++i) pv[i] = exp_fast(sacc[t][2 * b + (i >> 2)][i & 3] - m);
         l_run[t] += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
         split_half8(pv, ph[t][b], pl[t][b]);
       }

@@ -121,3 +121,40 @@ def test_rows_do_not_depend_on_what_they_share_a_block_with(hd):
     one.launch(pkg.lib())
     torch.cuda.synchronize()
     assert torch.equal(one.result(), many.result()[r0:r0 + 105])
+
+
+@pytest.mark.parametrize("hd,scale", [(64, 1.0), (128, 1.0), (64, 0.0)])
+def test_queries_up_to_the_largest_half(hd, scale):
+    """A scaled query of 65000 is a half (the decode kernels' range, whatever the softmax's base).  One such dimension against keys
+    of 1e-4 .. 2e-4 adds 8 .. 16 to a score; what its low part leaves out, 2^-22 of that, is within the tolerance above."""
+    c = Case(4, hd, 160, 1, [(0, 0, 150)], seed=hd)
+    c.mode.scale = scale
+    head_scale = scale or hd ** -0.5
+    big = torch.zeros(4, hd, dtype=torch.bool, device="cuda")
+    big[:, 5] = True
+    c.q[:, big.view(-1)] = c.q[:, big.view(-1)].sign() * (65000.0 / head_scale)
+    c.q[:, ~big.view(-1)] *= hd ** -0.5 / head_scale
+    c.k[..., 5] = c.k[..., 5].sign() * (1 + c.k[..., 5].abs().clamp(max=1)) * 2.0 ** -13
+    c.kt = key_tiles(c.k)
+    c.launch(pkg.lib())
+    torch.cuda.synchronize()
+    c.q = c.q * (head_scale / hd ** -0.5)              # (exact() scales by hd^-0.5)
+    got, want = c.result(), c.exact()
+    assert torch.isfinite(got).all()
+    assert (got - want).norm() / want.norm() < 2e-5
+
+
+@pytest.mark.parametrize("hd", [64, 128])
+def test_biases_of_the_lowest_value(hd):
+    """The lowest float as a bias hides a key from the rows that see another one; rows whose keys all have it see them equally."""
+    cap, n = 224, 211
+    c = Case(4, hd, cap, 1, [(0, 0, n)], n, True, seed=hd)
+    c.q.zero_()
+    c.bias.fill_(0)
+    c.bias[0].fill_(torch.finfo(torch.float32).min)    # head 0: every key; the others: those behind the row
+    c.bias[1:, cap:] = torch.finfo(torch.float32).min
+    c.launch(pkg.lib())
+    torch.cuda.synchronize()
+    got, want = c.result(), c.exact()
+    assert torch.isfinite(got).all()
+    assert (got - want).norm() / want.norm() < 2e-5
