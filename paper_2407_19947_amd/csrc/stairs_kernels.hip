@@ -781,8 +781,8 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
       }
       out[(size_t)m * N + col] = a;
       out[(size_t)m * N + col + 8] = b;
-      if (epi.cand) {                                      // the tile's largest value, for k_decide
-        float v = a;
+      if (epi.cand) {                                      // the tile's largest value, for k_decide (a NaN is none)
+        float v = fmaxf(a, -INFINITY);
         int ix = col;
         if (b > v) { v = b; ix = col + 8; }
         argmax_dpp<kDppXor1>(v, ix);
@@ -2492,7 +2492,7 @@ __global__ __launch_bounds__(1024) void k_decide(const float* __restrict__ src, 
 #pragma unroll
       for (int i = 0; i < NL; ++i) {
         const int e = min(e0 + i * wpr * 64, n - 1);
-        x[i] = CAND ? reinterpret_cast<const float2*>(row)[e] : make_float2(row[e], __int_as_float(e));
+        x[i] = CAND ? reinterpret_cast<const float2*>(row)[e] : make_float2(fmaxf(row[e], -INFINITY), __int_as_float(e));
       }
 #pragma unroll
       for (int i = 0; i < NL; ++i)

@@ -72,3 +72,27 @@ def test_results_on_the_host_in_every_kind_of_loop(k):
         s.reserve_batch(3)
         again, st2 = s.generate(prompt, 40, k)
         assert list(again) == list(want) and st2.iterations == st.iterations
+
+
+@pytest.mark.parametrize("dtype,vocab", [("bf16", 2048), ("fp32", 1024)])
+def test_logits_that_are_not_numbers_are_not_chosen(dtype, vocab):
+    """One NaN in each 16 columns: the choice is the largest of the numbers, on the joined launch (up to 8 rows) and behind it."""
+    w, target, draft = _pair(dtype, vocab)
+    head = np.array(target.lm_head)
+    head[5::16] = 0x7FC0 if dtype == "bf16" else np.nan
+    target.lm_head = head
+    draft.lm_head = head
+    prompt = si.make_prompt(w, 21) % vocab
+    for k in (0, 2, 4, 6, 8):
+        with pkg.Stairs(target, draft, k_max=8, max_seq=96) as s:
+            s.prefill(prompt)
+            steps = []
+            while len(steps) < 60:
+                if k:
+                    s.propose(k)
+                tgt, n, logits = s.verify(k, logits=True)
+                assert np.isnan(logits[:, 5::16]).all()
+                assert [int(t) for t in tgt] == np.nanargmax(logits, axis=1).tolist(), k
+                steps += [int(t) for t in tgt[:n + 1]]
+            s.prefill(prompt)
+            assert list(s.decode(60, k)[0]) == steps[:60]
