@@ -2450,14 +2450,6 @@ void launch_argmax(const float* logits, int ld, int V, int nrows, int row0, int 
                      out_pos.offset, out_pos.rps, ld, V, row0, row_stride, out_slot_stride, next);
 }
 
-// The greedy choice of M <= 8 rows of one sequence and what follows from it, by one work-group whose waves share the rows:
-//   ACCEPT: validation of the stair batch (k_accept) and the embeddings the next iteration starts from;
-//   else  : a draft token (M = 1) and the embedding of the step it leads to.
-// CAND: src holds a (value, index) pair per row and 16 columns, left by the unembedding's work-groups (GemmEpi::cand); else the
-// rows of logits themselves, where they are short (decide_takes).  A row of 32000 logits through one CU took longer than all its
-// candidates, and the validation and the first embedding of a proposal were launches of their own (125M, k = 4, us: a draft token
-// 5.9 -> 4.7; choice of five rows, validation and embedding 4.6 + 2.1 + 2.2 -> 6.3; tiny fp32 pair 3.3 -> 3.2 and 2.7 + 1.3 + 2.2
-// -> 3.9).  What bounds it: the chain of three round trips (candidates, the token's embedding, its store).
 // {L, n} of an iteration to the host, in turn to two places: no copy behind the iteration, which was a launch of 3 us
 __device__ __forceinline__ void host_result(const HostResult& h, int turn, int L, int n) {
   if (!h.at) return;
@@ -2466,14 +2458,23 @@ __device__ __forceinline__ void host_result(const HostResult& h, int turn, int L
   __hip_atomic_store(at + 1, n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
   *h.turn = turn + 1;
 }
+
+// The greedy choice of M <= 8 rows of one sequence and what follows from it, by one work-group whose waves share the rows:
+//   ACCEPT: validation of the stair batch (k_accept) and the embeddings the next iteration starts from;
+//   else  : a draft token (M = 1) and the embedding of the step it leads to.
+// CAND: src holds a (value, index) pair per row and 16 columns, left by the unembedding's work-groups (GemmEpi::cand); else the
+// rows of logits themselves, where they are short (decide_takes).  A row of 32000 logits through one CU took longer than all its
+// candidates, and the validation and the first embedding of a proposal were launches of their own (125M, k = 4, us: a draft token
+// 5.9 -> 4.7; choice of five rows, validation and embedding 4.6 + 2.1 + 2.2 -> 6.3; tiny fp32 pair 3.3 -> 3.2 and 2.7 + 1.3 + 2.2
+// -> 3.9).  What bounds it: the chain of three round trips (candidates, the token's embedding, its store).
 template <bool CAND, bool ACCEPT>
-__global__ __launch_bounds__(1024) void k_decide(const float* __restrict__ src, int* __restrict__ tokens, const int* __restrict__ pos_base,
-                                                 int pos_offset, int n, int M, int next_rows, int* __restrict__ tgt, int* __restrict__ state,
+__global__ __launch_bounds__(1024) void k_decide(const float* __restrict__ src, int* __restrict__ tokens, const int* pos_base,
+                                                 int pos_offset, int n, int M, int next_rows, int* __restrict__ tgt, int* state,
                                                  HostResult host, NextEmbed next) {
   __shared__ float s_v[16];
   __shared__ int s_i[16], s_id[2], s_pos;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int base = *pos_base;                              // ACCEPT: L
+  const int base = *pos_base;                              // ACCEPT: L, state[0] itself, written below
   const int wpr = 16 / (unsigned)M, m = wave / (unsigned)wpr, seg = wave - m * wpr;
   int mine = 0, prev = 0, active = 0, turn = 0;
   if (ACCEPT && wave == 0) {                               // lane i: draft token i
