@@ -87,8 +87,7 @@ struct stairs_ctx {
   float *x = nullptr, *ssq = nullptr, *q_rot = nullptr, *attn_out = nullptr, *h = nullptr, *logits = nullptr;
   float *partial = nullptr, *part_o = nullptr, *part_ml = nullptr;
   float2* rope_cs = nullptr;
-  float2* cand = nullptr;      // the unembedding's candidates, [8][vocab / 16] ...
-  bool has_cand = false;       // ... which the forward enqueued last leaves
+  float2* cand = nullptr;      // the unembedding's candidates, [8][vocab / 16] (leaves_candidates)
   // activation fragments of x, attn_out and h for forwards of more than 4 rows (bf16 models), see frag_bytes()
   uint4 *xf = nullptr, *af = nullptr, *hf = nullptr;
   // block prefill (bf16 models, env STAIRS_NO_BLOCK_PREFILL=1 turns it off): [kPfRows, .] workspaces
@@ -122,7 +121,8 @@ struct stairs_ctx {
   int eos_id = -1;             // end token of the generation loops (stairs_set_eos); -1: none
   int* h_pinned = nullptr;     // pinned host: [0..1] state, [2..2+kMaxRows) target tokens (decode_loop with two iterations in
                                // flight: [2..3] the second one's state); batch: two times [B][kSlotState] state, target tokens
-  int h_pinned_ints = 0;       // ints of it; four more behind them take the results of iterations in flight (HostResult)
+  int* d_results = nullptr;    // device address of four more ints behind them: the results of iterations in flight (HostResult)
+  const int* h_results = nullptr;   // the same on the host
   // host mirror
   int L = 0, P = 0;
   bool prefilled = false;
@@ -497,6 +497,12 @@ size_t max_partial_floats(const stairs_model_cfg* m) {
 //              M = every row -> c->logits rows 0..M-1.
 // Several sequences: pos.rps > 0 rows per slot, M = rps * (number of slots), slots 0..M/rps-1; otherwise the
 // rows belong to sequence slot `slot`.
+// Whether the unembedding of so many rows into c->logits leaves candidates in c->cand (not that of several sequences' rows on the
+// block kernels, which take more).
+bool leaves_candidates(const Model* m, int rows) {
+  return m->bf16 && rows <= 8 && rows_path_lds(kRoleHead, rows, m->cfg.vocab, m->cfg.d_model) > 0;
+}
+
 int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows, float* logits_dst, bool embedded);
 int forward_block(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows);
 
@@ -601,8 +607,7 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
     e.stream_weights = m->stream_weights;
     e.out = logits_dst ? logits_dst : c->logits;
     e.hd = m->hd;
-    c->has_cand = m->bf16 && !logits_dst && logits_rows <= 8 && rows_path_lds(kRoleHead, logits_rows, V, d) > 0;
-    e.cand = c->has_cand ? c->cand : nullptr;
+    e.cand = !logits_dst && leaves_candidates(m, logits_rows) ? c->cand : nullptr;
     // (the fragments hold all M rows: usable when the unembedding takes them all)
     launch_gemm(kRoleHead, b, m->lm_head, V, d, c->x + (size_t)r0 * d, d, logits_rows,
                 RowNorm{m->final_norm, c->ssq + r0 * sn, sn, g.rms_eps}, c->partial, e, st, (fr && r0 == 0) ? c->xf : nullptr);
@@ -824,8 +829,7 @@ int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logit
     e.stream_weights = m->stream_weights;
     e.out = logits_dst ? logits_dst : c->logits;
     e.hd = m->hd;
-    c->has_cand = m->bf16 && !logits_dst && logits_rows <= 8 && rows_path_lds(kRoleHead, logits_rows, V, d) > 0;
-    e.cand = c->has_cand ? c->cand : nullptr;
+    e.cand = !logits_dst && leaves_candidates(m, logits_rows) ? c->cand : nullptr;
     launch_gemm(kRoleHead, 1, m->lm_head, V, d, c->x + (size_t)r0 * d, d, logits_rows,
                 RowNorm{m->final_norm, c->ssq + r0 * sn, sn, g.rms_eps}, c->partial, e, st, r0 == 0 ? xf : nullptr);
     SYNCPOINT();
@@ -1078,10 +1082,11 @@ int enqueue_propose(stairs_ctx* c, int k, int nch, bool embedded) {
   const int r1 = first_rows(c);
   int rc = forward(c, m, rel_pos(c, -r1), nch, r1, 1, 0, nullptr, embedded);
   if (rc) return rc;
+  const bool cand = leaves_candidates(m, 1);
   auto decide = [&](int j) {                // d_{j+1}; for another step, its embedding too
     const NextEmbed next = j + 1 < k ? next_embed(c, m) : NextEmbed{};
-    if (decide_takes(c->has_cand, 1, V))
-      launch_decide(c->has_cand ? reinterpret_cast<const float*>(c->cand) : c->logits, c->has_cand, V, 1, c->tokens, rel_pos(c, j), c->st, next);
+    if (decide_takes(cand, 1, V))
+      launch_decide(cand ? reinterpret_cast<const float*>(c->cand) : c->logits, cand, V, 1, c->tokens, rel_pos(c, j), c->st, next);
     else
       launch_argmax(c->logits, V, V, 1, 0, 1, c->tokens, rel_pos(c, j), 0, c->st, next);
   };
@@ -1097,10 +1102,11 @@ int enqueue_propose(stairs_ctx* c, int k, int nch, bool embedded) {
 
 // where an iteration of one sequence leaves its result for the host; its count of turns is the state's spare slot
 HostResult host_result(const stairs_ctx* c, bool in_loop) {
-  void* at = nullptr;
-  if (!in_loop || hipHostGetDevicePointer(&at, c->h_pinned, 0) != hipSuccess) return HostResult{};
-  return HostResult{static_cast<int*>(at) + c->h_pinned_ints, c->state + c->n_slots * kSlotState};
+  return in_loop ? HostResult{c->d_results, c->state + c->n_slots * kSlotState} : HostResult{};
 }
+
+// Whether a greedy verification ends in the one launch that chooses, validates and, in a loop, leaves {L, n} with the host
+bool verify_decides(const stairs_ctx* c, int k) { return decide_takes(leaves_candidates(&c->T, k + 1), k + 1, c->T.cfg.vocab); }
 
 // Enqueue the stair batch for the k draft tokens sitting in tokens[L..L+k), its per-row argmax and the validation.
 // in_loop: another iteration with this k may follow; this one's last launch leaves what it starts from (and k = 0: found its
@@ -1110,8 +1116,9 @@ int enqueue_verify(stairs_ctx* c, int k, int nch, bool in_loop) {
   const int M = k + 1, V = m->cfg.vocab;
   int rc = forward(c, m, rel_pos(c, -1), nch, M, M, 0, nullptr, in_loop && k == 0);
   if (rc) return rc;
-  if (decide_takes(c->has_cand, M, V)) {
-    launch_decide_accept(c->has_cand ? reinterpret_cast<const float*>(c->cand) : c->logits, c->has_cand, V, k, c->tokens, c->tgt_tok, c->state, c->st,
+  if (verify_decides(c, k)) {
+    const bool cand = leaves_candidates(m, M);
+    launch_decide_accept(cand ? reinterpret_cast<const float*>(c->cand) : c->logits, cand, V, k, c->tokens, c->tgt_tok, c->state, c->st,
                          in_loop ? next_embed(c, first_model(c, k)) : NextEmbed{}, first_model_rows(c, k), host_result(c, in_loop));
   } else {
     launch_argmax(c->logits, V, V, M, 0, 1, c->tgt_tok, PosRef{nullptr, 0}, 0, c->st);
@@ -1448,6 +1455,27 @@ static int alloc_block_rows(stairs_ctx* c, int rows) {
   return STAIRS_OK;
 }
 
+// the pinned host mirror, of so many ints and four for the results of iterations in flight; an earlier one is given back
+static int alloc_pinned(stairs_ctx* c, int ints) {
+  int* host = nullptr;
+  void* dev = nullptr;
+  if (hipHostMalloc(reinterpret_cast<void**>(&host), (ints + 4) * sizeof(int), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(c, STAIRS_ENOMEM, "hipHostMalloc failed");
+  }
+  if (const hipError_t e = hipHostGetDevicePointer(&dev, host, 0); e != hipSuccess) {
+    (void)hipGetLastError();
+    (void)hipHostFree(host);
+    c->err = std::string("hipHostGetDevicePointer: ") + hipGetErrorString(e);
+    return STAIRS_EHIP;
+  }
+  if (c->h_pinned) (void)hipHostFree(c->h_pinned);
+  c->h_pinned = host;
+  c->h_results = host + ints;
+  c->d_results = static_cast<int*>(dev) + ints;
+  return STAIRS_OK;
+}
+
 // workspaces, token array, state, counters, pinned host mirror, events
 static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
   int rc;
@@ -1485,11 +1513,7 @@ static int alloc_workspaces(stairs_ctx* c, const WsDims& w) {
   if (hipMemsetAsync(c->tokens, 0, ((size_t)c->tok_cap + kMaxRows) * sizeof(int), c->st) != hipSuccess) return bail(STAIRS_EHIP);
   if (hipMemsetAsync(c->state, 0, 3 * kSlotState * sizeof(int), c->st) != hipSuccess) return bail(STAIRS_EHIP);
   if (hipMemsetAsync(c->counters, 0, kCounters * sizeof(int), c->st) != hipSuccess) return bail(STAIRS_EHIP);
-  c->h_pinned_ints = 2 * kSlotState + kMaxRows;     // single sequence: 2 + rows; a batch of one slot: two states + rows
-  if (hipHostMalloc(reinterpret_cast<void**>(&c->h_pinned), (c->h_pinned_ints + 4) * sizeof(int), hipHostMallocDefault) != hipSuccess) {
-    c->h_pinned = nullptr;
-    return bail(STAIRS_ENOMEM);
-  }
+  if ((rc = alloc_pinned(c, 2 * kSlotState + kMaxRows))) return bail(rc);   // single sequence: 2 + rows; a batch of one slot: two states + rows
   for (auto& e : c->ev)
     if (hipEventCreate(&e) != hipSuccess) return bail(STAIRS_EHIP);
   if (hipStreamSynchronize(c->st) != hipSuccess) return bail(STAIRS_EHIP);
@@ -1694,8 +1718,7 @@ static int decode_loop(stairs_ctx* c, int32_t G, int32_t k, bool adaptive, int32
   const int depth = c->use_graphs && !adaptive && c->eos_id < 0 ? 2 : 1;
   int in_flight = 0, oldest = 0;
   // results: written to host memory by the iteration's last launch where it is one of those that do, else copied behind it
-  const bool direct = depth == 2 &&
-                      (sampled || decide_takes(c->T.bf16 && rows_path_lds(kRoleHead, k + 1, c->T.cfg.vocab, c->T.cfg.d_model) > 0, k + 1, c->T.cfg.vocab));
+  const bool direct = depth == 2 && (sampled || verify_decides(c, k));
   if (direct) HIPCHK(c, hipMemsetAsync(c->state + c->n_slots * kSlotState, 0, sizeof(int), c->st));
   auto enqueue = [&](int set, int L) -> int {      // L: the longest the sequence can be by then
     hipEvent_t* const ev = c->ev + 8 + 4 * set;
@@ -1755,7 +1778,7 @@ static int decode_loop(stairs_ctx* c, int32_t G, int32_t k, bool adaptive, int32
     }
     if (in_flight == 0) break;
     hipEvent_t* const ev = c->ev + 8 + 4 * oldest;
-    const int* const res = (direct ? c->h_pinned + c->h_pinned_ints : c->h_pinned) + 2 * oldest;
+    const int* const res = (direct ? c->h_results : c->h_pinned) + 2 * oldest;
     float a = 0.f, b = 0.f;
     hipError_t e = hipEventSynchronize(ev[direct ? 2 : 3]);
     if (e == hipSuccess) e = hipEventElapsedTime(&a, ev[0], ev[1]);
@@ -1998,15 +2021,7 @@ int stairs_reserve_batch(stairs_ctx* c, int32_t max_batch) {
   release(c, c->state);
   c->tokens = tok;
   c->state = state;
-  int* hp = nullptr;
-  const int ints = std::max(2 + kMaxRows, 2 * max_batch * kSlotState + c->rows_cap);
-  if (hipHostMalloc(reinterpret_cast<void**>(&hp), (ints + 4) * sizeof(int), hipHostMallocDefault) != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(c, STAIRS_ENOMEM, "hipHostMalloc failed");
-  }
-  (void)hipHostFree(c->h_pinned);
-  c->h_pinned = hp;
-  c->h_pinned_ints = ints;
+  if ((rc = alloc_pinned(c, std::max(2 + kMaxRows, 2 * max_batch * kSlotState + c->rows_cap)))) return rc;
   HIPCHK(c, hipStreamSynchronize(c->st));
   c->n_slots = max_batch;
   return STAIRS_OK;

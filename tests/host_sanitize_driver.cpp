@@ -45,7 +45,7 @@ void* operator new[](size_t n, const std::nothrow_t&) noexcept {
 }
 
 // a call of the runtime that is refused: the n-th from now on (0: none), without reaching the runtime
-static int g_refuse_launch = 0, g_refuse_time = 0;
+static int g_refuse_launch = 0, g_refuse_time = 0, g_refuse_address = 0;
 static bool refused(int& left) { return left > 0 && --left == 0; }
 extern "C" hipError_t hipGraphLaunch(hipGraphExec_t exec, hipStream_t st) {
   if (refused(g_refuse_launch)) return hipErrorOutOfMemory;
@@ -56,6 +56,12 @@ extern "C" hipError_t hipEventElapsedTime(float* ms, hipEvent_t start, hipEvent_
   if (refused(g_refuse_time)) return hipErrorOutOfMemory;
   static const auto real = reinterpret_cast<hipError_t (*)(float*, hipEvent_t, hipEvent_t)>(dlsym(RTLD_NEXT, "hipEventElapsedTime"));
   return real(ms, start, stop);
+}
+
+extern "C" hipError_t hipHostGetDevicePointer(void** dev, void* host, unsigned int flags) {
+  if (refused(g_refuse_address)) return hipErrorInvalidValue;
+  static const auto real = reinterpret_cast<hipError_t (*)(void**, void*, unsigned int)>(dlsym(RTLD_NEXT, "hipHostGetDevicePointer"));
+  return real(dev, host, flags);
 }
 
 struct Rng {
@@ -220,6 +226,8 @@ static void part2_decoder_only() {
   D.point(1);
   D.w = T.w;                            // same host addresses as the target's
   stairs_ctx* c = nullptr;
+  g_refuse_address = 1;                 // nowhere to leave an iteration's result: said here, not by an iteration
+  CHECK(stairs_init(&c, &T.cfg, &T.w, &D.cfg, &T.w, 8, nullptr) == STAIRS_EHIP && c == nullptr && g_refuse_address == 0);
   CHECK(stairs_init(&c, &T.cfg, &T.w, &D.cfg, &T.w, 8, nullptr) == STAIRS_OK && c != nullptr);
   if (!c) return;
   const int G = 40;
@@ -317,6 +325,10 @@ static void part2_decoder_only() {
   std::vector<int32_t> alone((size_t)ps.size() * G), both((size_t)ps.size() * G);
   for (size_t b = 0; b < ps.size(); ++b) CHECK(stairs_generate(c, pp[b], PP[b], G, 3, alone.data() + b * G, &st) == STAIRS_OK);
   CHECK(stairs_generate_batch(c, pp.data(), PP.data(), 2, G, 3, both.data(), &st) == STAIRS_EINVAL);   // nothing reserved
+  g_refuse_address = 1;
+  CHECK(stairs_reserve_batch(c, 6) == STAIRS_EHIP && g_refuse_address == 0);
+  CHECK(std::strstr(stairs_last_error(c), "hipHostGetDevicePointer") != nullptr);
+  CHECK(stairs_generate(c, pp[0], PP[0], G, 3, both.data(), &st) == STAIRS_OK && std::memcmp(both.data(), alone.data(), G * sizeof(int32_t)) == 0);
   CHECK(stairs_reserve_batch(c, 6) == STAIRS_OK);
   CHECK(stairs_generate_batch(c, pp.data(), PP.data(), 6, G, 3, both.data(), &st) == STAIRS_OK);
   CHECK(both == alone && st.tokens == 6 * G);
