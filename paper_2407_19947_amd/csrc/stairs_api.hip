@@ -506,8 +506,8 @@ bool leaves_candidates(const Model* m, int rows) {
 int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows, float* logits_dst, bool embedded);
 int forward_block(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows);
 
-// logits_dst: where the logits rows go (nullptr: c->logits); embedded: the launch in front has left the row's embedding
-// (next_embed(m)), M = 1
+// logits_dst: where the logits rows go (nullptr: c->logits); embedded: the launch in front has left the embeddings of the M <=
+// kMaxNextRows rows (next_embed(m)), which come without fragments
 int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_rows, int slot = 0, float* logits_dst = nullptr,
             bool embedded = false) {
   if (m->encdec) {
@@ -515,7 +515,7 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
     return forward_ed(c, m, pos, nchunk, M, logits_rows, logits_dst, embedded);
   }
   if (M > c->fwd_rows) {                    // many sequences at once: the block kernels
-    if (slot != 0 || logits_dst) return fail(c, STAIRS_EINVAL, "forward: launch shape outside the workspaces");
+    if (slot != 0 || logits_dst || embedded) return fail(c, STAIRS_EINVAL, "forward: launch shape outside the workspaces");
     return forward_block(c, m, pos, nchunk, M, logits_rows);
   }
   const stairs_model_cfg& g = m->cfg;
@@ -523,7 +523,8 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
   const int b = m->bf16 ? 1 : 0;
   const int sn = ssq_groups(d);
   hipStream_t st = c->st;
-  if (nchunk < 1 || nchunk > c->nchunk_cap || M < 1 || M > c->fwd_rows || M > c->rows_cap || (M > kMaxRows && !b))
+  if (nchunk < 1 || nchunk > c->nchunk_cap || M < 1 || M > c->fwd_rows || M > c->rows_cap || (M > kMaxRows && !b) ||
+      (embedded && (M > kMaxNextRows || pos.rps)))
     return fail(c, STAIRS_EINVAL, "forward: launch shape outside the workspaces");
 #define SYNCPOINT()                                             \
   do {                                                          \
@@ -756,7 +757,7 @@ int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logit
   const int sn = ssq_groups(d);
   hipStream_t st = c->st;
   const int nch_src = chunks_for(c->S);
-  if (nchunk < 1 || nchunk > c->nchunk_cap || nch_src > c->nchunk_cap || M < 1 || M > kMaxRows || c->S < 1)
+  if (nchunk < 1 || nchunk > c->nchunk_cap || nch_src > c->nchunk_cap || M < 1 || M > kMaxRows || c->S < 1 || (embedded && M > kMaxNextRows))
     return fail(c, STAIRS_EINVAL, "forward: launch shape outside the workspaces");
 #define SYNCPOINT()                                             \
   do {                                                          \
@@ -1050,7 +1051,7 @@ int ingest_prompts(stairs_ctx* c, Model* m, const int32_t* P, int B) {
   return flush();
 }
 
-// where a forward of one row of model m (one sequence) finds its embedding, for the launch that decides the row's token
+// where a forward of up to kMaxNextRows rows of model m (one sequence) finds its embeddings, for the launch that decides the last token
 NextEmbed next_embed(const stairs_ctx* c, const Model* m) {
   return NextEmbed{m->tok_emb, m->bf16 ? 1 : 0, c->tok_stride, m->cfg.vocab, m->cfg.d_model, m->hd, c->x, c->ssq,
                    m->encdec ? nullptr : m->rope_tab, m->encdec ? 0 : m->cap, c->rope_cs};

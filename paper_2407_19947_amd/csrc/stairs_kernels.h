@@ -168,8 +168,9 @@ void set_gemm_launch_events(hipEvent_t start, hipEvent_t stop);
 void launch_embed(const void* emb, int emb_bf16, const int* tokens, int tok_slot_stride, int tok_cap, int vocab, PosRef pos,
                   int M, int d, float* x, float* ssq_part, int hd, const float2* tab, int tab_len, float2* cs, hipStream_t st,
                   uint4* frag = nullptr, const float* frag_gain = nullptr);   // bf16: also the fragments of x * frag_gain
-// Where the next forward of one row finds its embedding (launch_embed's outputs for M = 1): a launch that decides a token can
-// leave the token's row there itself.  emb == nullptr: it does not.
+// Where the next forward of one sequence finds its embeddings (launch_embed's outputs, without fragments): a launch that decides
+// a token can leave them itself, the token's row alone or behind that of the token in front of it.  emb == nullptr: it does not.
+constexpr int kMaxNextRows = 2;
 struct NextEmbed {
   const void* emb;
   int bf16, tok_cap, vocab, d, hd;
@@ -215,7 +216,7 @@ void launch_argmax(const float* logits, int ld, int V, int nrows, int row0, int 
 // (cand: GemmEpi::cand, V / 16 pairs a row), else the rows of V logits themselves.
 //   launch_decide       : M = 1, tokens[out_pos] = the choice; next: its embedding
 //   launch_decide_accept: the choices of k + 1 stair rows (to tgt as well), launch_accept, and the embeddings of the last
-//                         next_rows (1 or 2) tokens then, as rows 0 .. of a forward
+//                         next_rows (1 .. kMaxNextRows) tokens then, as rows 0 .. of a forward
 // host (at nullptr: none): {L, n} also go to at[0 .. 1] or at[2 .. 3], memory of the host, as *turn, which counts up, is even or odd
 struct HostResult {
   int* at;

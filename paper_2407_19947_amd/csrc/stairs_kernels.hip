@@ -1597,7 +1597,7 @@ __device__ __forceinline__ void embed_cols(const E* emb, int id, int vocab, int 
     if ((c & 12) == 0 && c < d) ssq_part[c / 16] = ss;
   }
 }
-// The embedding the next forward of one row starts from, by a work-group of nth threads that all know the token: position p,
+// Row `row` of the embeddings the next forward starts from, by a work-group of nth threads that all know the token: position p,
 // token id (kernel that decided them: no launch of its own, no round trip through the token array).
 __device__ __forceinline__ void next_embed(const NextEmbed& n, int p, int id, int nth, int row = 0) {
   const int tid = threadIdx.x;
@@ -2472,7 +2472,7 @@ __global__ __launch_bounds__(1024) void k_decide(const float* __restrict__ src, 
                                                  int pos_offset, int n, int M, int next_rows, int* __restrict__ tgt, int* state,
                                                  HostResult host, NextEmbed next) {
   __shared__ float s_v[16];
-  __shared__ int s_i[16], s_id[2], s_pos;
+  __shared__ int s_i[16], s_id[kMaxNextRows], s_pos;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int base = *pos_base;                              // ACCEPT: L, state[0] itself, written below
   const int wpr = 16 / (unsigned)M, m = wave / (unsigned)wpr, seg = wave - m * wpr;
@@ -2552,7 +2552,7 @@ __global__ __launch_bounds__(1024) void k_decide(const float* __restrict__ src, 
   }
   if (!next.emb) return;
   __syncthreads();
-  for (int i = 0; i < next_rows; ++i) next_embed(next, s_pos - (next_rows - 1 - i), s_id[2 - next_rows + i], 1024, i);
+  for (int i = 0; i < next_rows; ++i) next_embed(next, s_pos - (next_rows - 1 - i), s_id[kMaxNextRows - next_rows + i], 1024, i);
 }
 bool decide_takes(bool cand, int M, int V) { return M <= 8 && (cand || M * V <= 16384); }
 void launch_decide(const float* src, bool cand, int V, int M, int* tokens, PosRef out_pos, hipStream_t st, const NextEmbed& next) {
@@ -2739,7 +2739,7 @@ __global__ __launch_bounds__(256) void k_accept_sampled(int* __restrict__ tokens
                                                         SampleWs* ws, HostResult host, NextEmbed next, int next_rows) {
   __shared__ double sv[4];
   __shared__ int si[4];
-  __shared__ int s_n, s_flag, s_empty, s_id[2];
+  __shared__ int s_n, s_flag, s_empty, s_id[kMaxNextRows];
   __shared__ float s_lse[2 * kMaxRows];
   const int tid = threadIdx.x;
   const int L = state[0];
@@ -2808,7 +2808,7 @@ __global__ __launch_bounds__(256) void k_accept_sampled(int* __restrict__ tokens
   }
   if (!next.emb) return;                                 // (the block that decided the last token, as in k_decide)
   __syncthreads();
-  for (int i = 0; i < next_rows; ++i) next_embed(next, pos - (next_rows - 1 - i), s_id[2 - next_rows + i], 256, i);
+  for (int i = 0; i < next_rows; ++i) next_embed(next, pos - (next_rows - 1 - i), s_id[kMaxNextRows - next_rows + i], 256, i);
 }
 
 void launch_row_lse(const float* a, int n_a, const float* b, int n_b, int ld, int V, const SampleParams* sp, float* lse,
