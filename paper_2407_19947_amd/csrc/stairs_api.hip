@@ -562,8 +562,8 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
     e.pos = pos;
     e.Kc = reinterpret_cast<_Float16*>(Kl);
     e.Vc = reinterpret_cast<_Float16*>(Vl);
-    e.Kc32 = b ? nullptr : reinterpret_cast<float*>(Kl);
-    e.Vc32 = b ? nullptr : reinterpret_cast<float*>(Vl);
+    e.Kc32 = reinterpret_cast<float*>(Kl);
+    e.Vc32 = reinterpret_cast<float*>(Vl);
     e.cap = m->cap;
     e.H = H;
     e.hd = m->hd;
@@ -608,10 +608,9 @@ int forward(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logits_r
     e.stream_weights = m->stream_weights;
     e.out = logits_dst ? logits_dst : c->logits;
     e.hd = m->hd;
-    e.cand = !logits_dst && leaves_candidates(m, logits_rows) ? c->cand : nullptr;
     // (the fragments hold all M rows: usable when the unembedding takes them all)
-    launch_gemm(kRoleHead, b, m->lm_head, V, d, c->x + (size_t)r0 * d, d, logits_rows,
-                RowNorm{m->final_norm, c->ssq + r0 * sn, sn, g.rms_eps}, c->partial, e, st, (fr && r0 == 0) ? c->xf : nullptr);
+    launch_unembed(b, m->lm_head, V, d, c->x + (size_t)r0 * d, logits_rows, RowNorm{m->final_norm, c->ssq + r0 * sn, sn, g.rms_eps},
+                   c->partial, e, st, (fr && r0 == 0) ? c->xf : nullptr, !logits_dst && leaves_candidates(m, logits_rows) ? c->cand : nullptr);
     SYNCPOINT();
   }
   HIPCHK(c, hipGetLastError());
@@ -830,9 +829,8 @@ int forward_ed(stairs_ctx* c, Model* m, PosRef pos, int nchunk, int M, int logit
     e.stream_weights = m->stream_weights;
     e.out = logits_dst ? logits_dst : c->logits;
     e.hd = m->hd;
-    e.cand = !logits_dst && leaves_candidates(m, logits_rows) ? c->cand : nullptr;
-    launch_gemm(kRoleHead, 1, m->lm_head, V, d, c->x + (size_t)r0 * d, d, logits_rows,
-                RowNorm{m->final_norm, c->ssq + r0 * sn, sn, g.rms_eps}, c->partial, e, st, r0 == 0 ? xf : nullptr);
+    launch_unembed(1, m->lm_head, V, d, c->x + (size_t)r0 * d, logits_rows, RowNorm{m->final_norm, c->ssq + r0 * sn, sn, g.rms_eps},
+                   c->partial, e, st, r0 == 0 ? xf : nullptr, !logits_dst && leaves_candidates(m, logits_rows) ? c->cand : nullptr);
     SYNCPOINT();
   }
   HIPCHK(c, hipGetLastError());
@@ -2436,8 +2434,8 @@ int stairs_time_kernel(stairs_ctx* c, int32_t which, int32_t M, int32_t ctx_len,
       e.pos = tpos;
       e.Kc = reinterpret_cast<_Float16*>(Kl);
       e.Vc = reinterpret_cast<_Float16*>(Vl);
-      e.Kc32 = b ? nullptr : reinterpret_cast<float*>(Kl);
-      e.Vc32 = b ? nullptr : reinterpret_cast<float*>(Vl);
+      e.Kc32 = reinterpret_cast<float*>(Kl);
+      e.Vc32 = reinterpret_cast<float*>(Vl);
       e.cap = m->cap;
       e.H = g.n_heads;
       e.hd = m->hd;

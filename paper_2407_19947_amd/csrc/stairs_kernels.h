@@ -99,10 +99,7 @@ struct GemmEpi {
   PosRef pos;
   _Float16* Kc;             // bf16 models: half caches of this layer, tiled layout
   _Float16* Vc;
-  union {
-    float* Kc32;            // fp32 models: float caches of this layer, [H][cap][hd]
-    float2* cand;           // Head role on k_gemm_bf16_rows: [M][N / 16] (largest value, its column) of each tile's outputs; nullptr: none
-  };
+  float* Kc32;              // fp32 models: float caches of this layer, [H][cap][hd]
   float* Vc32;
   int cap, H, hd;
   size_t kv_slot_stride;    // elements between the caches of consecutive slots (several sequences), else unused
@@ -122,6 +119,10 @@ struct GemmEpi {
 // them the launch takes the hand-off-free kernel k_gemm_bf16_wide (no partial sums), without them the split-K kernel.
 void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const float* X, int ldx, int M,
                  RowNorm nrm, float* partial, const GemmEpi& epi, hipStream_t st, const uint4* xfrag = nullptr);
+// The Head role, which where rows_path_lds takes it also leaves cand (nullptr: not): [M][N / 16] (largest value, its column) of
+// the outputs of each 16 columns; a NaN counts as the lowest.
+void launch_unembed(int dtype_bf16, const void* W, int N, int K, const float* X, int M, RowNorm nrm, float* partial, const GemmEpi& epi,
+                    hipStream_t st, const uint4* xfrag, float2* cand);
 
 // dynamic LDS of the kernel that keeps the whole activation block of up to 7 rows in LDS; 0: the projection does not take it
 size_t rows_path_lds(int role, int M, int N, int K);
@@ -213,7 +214,7 @@ int attn_f32_rows(int units, int H, int M);
 void launch_argmax(const float* logits, int ld, int V, int nrows, int row0, int row_stride, int* out, PosRef out_pos,
                    int out_slot_stride, hipStream_t st, const NextEmbed& next = NextEmbed{});
 // The same and what follows it in one launch, for M <= 8 rows of one sequence (decide_takes).  src: the unembedding's candidates
-// (cand: GemmEpi::cand, V / 16 pairs a row), else the rows of V logits themselves.
+// (cand: launch_unembed's, V / 16 pairs a row), else the rows of V logits themselves.
 //   launch_decide       : M = 1, tokens[out_pos] = the choice; next: its embedding
 //   launch_decide_accept: the choices of k + 1 stair rows (to tgt as well), launch_accept, and the embeddings of the last
 //                         next_rows (1 .. kMaxNextRows) tokens then, as rows 0 .. of a forward

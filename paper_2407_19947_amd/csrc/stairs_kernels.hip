@@ -542,7 +542,8 @@ __device__ __forceinline__ void argmax_swap(float& best, int& bi, bool far) {   
 template <int R, int ROLE, int NW, int GP, int Q, bool WALK, bool STREAM, bool ROWMAJOR = false>
 __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restrict__ Wsw, const float* __restrict__ X,
                                                             const float* __restrict__ gain, const float* __restrict__ ssq_part,
-                                                            int K, int N, int ldx, int ssq_n, float* out, float eps, GemmEpi epi) {
+                                                            int K, int N, int ldx, int ssq_n, float* out, float eps, float2* cand,
+                                                            GemmEpi epi) {
   constexpr int NTH = 64 * NW, NG = NTH / Q, RP = (R + Q - 1) / Q;
   constexpr bool NORMED = ROLE != kRoleWo && ROLE != kRoleDown;      // (the residual-writing projections' inputs are not)
   extern __shared__ uint4 lds[];
@@ -781,14 +782,14 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
       }
       out[(size_t)m * N + col] = a;
       out[(size_t)m * N + col + 8] = b;
-      if (epi.cand) {                                      // the tile's largest value, for k_decide (a NaN is none)
+      if (cand) {                                          // the tile's largest value, for k_decide (a NaN is none)
         float v = fmaxf(a, -INFINITY);
         int ix = col;
         if (b > v) { v = b; ix = col + 8; }
         argmax_dpp<kDppXor1>(v, ix);
         argmax_dpp<kDppXor2>(v, ix);
         argmax_dpp<kDppHalfMirror>(v, ix);
-        if (j == 0) epi.cand[(size_t)m * NTILES + tile] = make_float2(v, __int_as_float(ix));
+        if (j == 0) cand[(size_t)m * NTILES + tile] = make_float2(v, __int_as_float(ix));
       }
       if (R > 4 && epi.frag_out) {
         const float4 va = make_float4(dpp<kDppQuad0>(a), dpp<kDppQuad1>(a), dpp<kDppQuad2>(a), dpp<kDppQuad3>(a));
@@ -1235,7 +1236,7 @@ bool launch_gemm_rowmajor(const uint16_t* W, int N, int K, const float* X, int M
   const size_t rl = rows_path_lds(kRoleHead, M, N, K);
   if (rl && M <= 4) {
 #define STAIRS_ROWM(r) \
-  hipLaunchKernelGGL((rows_kernel<r, kRoleHead, 4, 2, false, true>(K, false)), dim3(NTILES), dim3(256), rl, st, Wr, X, none.gain, none.ssq_part, K, N, K, none.ssq_n, e.out, none.eps, e)
+  hipLaunchKernelGGL((rows_kernel<r, kRoleHead, 4, 2, false, true>(K, false)), dim3(NTILES), dim3(256), rl, st, Wr, X, none.gain, none.ssq_part, K, N, K, none.ssq_n, e.out, none.eps, nullptr, e)
     if (M == 1) STAIRS_ROWM(1);
     else if (M == 2) STAIRS_ROWM(2);
     else if (M == 3) STAIRS_ROWM(3);
@@ -1410,8 +1411,8 @@ bool gemm_takes_rows(int M, int K) {
   return M <= kMaxFwdRows && (size_t)gemm_slices(K, 1) * M * 16 * sizeof(float) <= kWideMaxLds;
 }
 
-void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const float* X, int ldx, int M, RowNorm nrm,
-                 float* partial, const GemmEpi& epi, hipStream_t st, const uint4* xfrag) {
+static void gemm(int role, int dtype_bf16, const void* W, int N, int K, const float* X, int ldx, int M, RowNorm nrm,
+                 float* partial, const GemmEpi& epi, hipStream_t st, const uint4* xfrag, float2* cand) {
   if (!dtype_bf16) {
     const dim3 grid((N / 2 + 3) / 4), block(256);
     const float* Wf = static_cast<const float*>(W);
@@ -1462,7 +1463,7 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
     const size_t rl_launch = tpw > 1 ? std::max(rl, (size_t)81 * 1024) : rl;
 #define STAIRS_ROWS(r, role, nw, gp)                                                                                    \
   launch_gemm_kernel(epi.stream_weights ? rows_kernel<r, role, nw, gp, true>(K, tpw > 1) : rows_kernel<r, role, nw, gp, false>(K, tpw > 1), rgrid, \
-                     dim3(64 * nw), rl_launch, st, Wsw, X, nrm.gain, nrm.ssq_part, K, N, ldx, nrm.ssq_n, epi.out, nrm.eps, epi)
+                     dim3(64 * nw), rl_launch, st, Wsw, X, nrm.gain, nrm.ssq_part, K, N, ldx, nrm.ssq_n, epi.out, nrm.eps, cand, epi)
 #define STAIRS_ROWS_ROLE4(role, nw, gp)          \
   if (M <= 1) STAIRS_ROWS(1, role, nw, gp);      \
   else if (M == 2) STAIRS_ROWS(2, role, nw, gp); \
@@ -1566,6 +1567,14 @@ void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
 #undef STAIRS_GEMM_NT
 #undef STAIRS_GEMM_ROLE
 #undef STAIRS_GEMM
+}
+void launch_gemm(int role, int dtype_bf16, const void* W, int N, int K, const float* X, int ldx, int M, RowNorm nrm,
+                 float* partial, const GemmEpi& epi, hipStream_t st, const uint4* xfrag) {
+  gemm(role, dtype_bf16, W, N, K, X, ldx, M, nrm, partial, epi, st, xfrag, nullptr);
+}
+void launch_unembed(int dtype_bf16, const void* W, int N, int K, const float* X, int M, RowNorm nrm, float* partial, const GemmEpi& epi,
+                    hipStream_t st, const uint4* xfrag, float2* cand) {
+  gemm(kRoleHead, dtype_bf16, W, N, K, X, K, M, nrm, partial, epi, st, xfrag, cand);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2462,7 +2471,7 @@ __device__ __forceinline__ void host_result(const HostResult& h, int turn, int L
 // The greedy choice of M <= 8 rows of one sequence and what follows from it, by one work-group whose waves share the rows:
 //   ACCEPT: validation of the stair batch (k_accept) and the embeddings the next iteration starts from;
 //   else  : a draft token (M = 1) and the embedding of the step it leads to.
-// CAND: src holds a (value, index) pair per row and 16 columns, left by the unembedding's work-groups (GemmEpi::cand); else the
+// CAND: src holds a (value, index) pair per row and 16 columns, left by the unembedding's work-groups (launch_unembed); else the
 // rows of logits themselves, where they are short (decide_takes).  A row of 32000 logits through one CU took longer than all its
 // candidates, and the validation and the first embedding of a proposal were launches of their own (125M, k = 4, us: a draft token
 // 5.9 -> 4.7; choice of five rows, validation and embedding 4.6 + 2.1 + 2.2 -> 6.3; tiny fp32 pair 3.3 -> 3.2 and 2.7 + 1.3 + 2.2

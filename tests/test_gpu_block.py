@@ -347,3 +347,25 @@ def test_projections_of_17_to_64_rows_have_the_bits_of_one_row(role, tiles, K, h
         kept = torch.ones(M, dtype=torch.bool)
         kept[inactive] = False
         assert torch.isfinite(got[0][kept.cuda()]).all() and torch.isnan(got[0][~kept.cuda()]).all()
+
+
+@pytest.mark.parametrize("M", [1, 4, 7])
+def test_unembedding_writes_its_output_alone(M):
+    """A caller's structure may name its caches for every role: an unembedding touches none of them."""
+    import torch
+    assert _cxx("_ZN6stairs17configure_kernelsEv", C.c_int)() == 0
+    gemm = _cxx("_ZN6stairs11launch_gemmEiiPKviiPKfiiNS_7RowNormEPfRKNS_7GemmEpiEP12ihipStream_tPK15HIP_vector_typeIjLj4EE", None,
+                C.c_int, C.c_int, C.c_void_p, C.c_int, C.c_int, C.c_void_p, C.c_int, C.c_int, _RowNorm, C.c_void_p,
+                C.POINTER(_GemmEpi), C.c_void_p, C.c_void_p)
+    N, K = 4096, 512
+    assert _cxx("_ZN6stairs13rows_path_ldsEiiii", C.c_size_t, *[C.c_int] * 4)(R_HEAD, M, N, K) > 0
+    W, X = torch.ones(N * K, dtype=torch.bfloat16, device="cuda"), torch.ones(M, K, device="cuda")
+    out, partial = torch.zeros(M, N, device="cuda"), torch.zeros(2 * M * N, device="cuda")
+    counters = torch.zeros(4096, dtype=torch.int32, device="cuda")
+    caches = [torch.full((M * N,), 7.0, device="cuda") for _ in range(4)]
+    e = _GemmEpi(counters=counters.data_ptr(), out=out.data_ptr(), hd=64,
+                 **{n: t.data_ptr() for n, t in zip(("Kc", "Vc", "Kc32", "Vc32"), caches)})
+    torch.cuda.synchronize()
+    gemm(R_HEAD, 1, W.data_ptr(), N, K, X.data_ptr(), K, M, _RowNorm(), partial.data_ptr(), C.byref(e), None, None)
+    torch.cuda.synchronize()
+    assert (out == K).all() and all((t == 7).all() for t in caches)
