@@ -187,7 +187,7 @@ const char* check_cfg(const stairs_model_cfg* m) {
   if (!(m->rope_theta > 0.f) || !(m->rms_eps >= 0.f)) return "rope_theta must be > 0 and rms_eps >= 0";
   if (std::max({m->vocab, 3 * m->d_model, 2 * m->d_ffn}) / 64 + 1 > kGemmCounters || m->n_heads > kAttnCounters)
     return "model too wide for the hand-off counters";
-  if (m->max_seq > 60000) return "max_seq above 60000 is not supported (attention merge table lives in LDS)";
+  if (m->max_seq > 60000) return "max_seq above 60000 is not supported (the longest context that is tested)";
   return nullptr;
 }
 
@@ -348,7 +348,7 @@ const char* check_encdec_cfg(const stairs_encdec_cfg* m) {
     return "rel_buckets must be a multiple of 4 and rel_max_distance above rel_buckets / 2";
   if (std::max<long>({(long)m->vocab, 3 * a, (long)m->d_ffn}) / 64 + 1 > kGemmCounters || m->n_heads > kAttnCounters)
     return "model too wide for the hand-off counters";
-  if (m->max_seq > 60000) return "max_seq above 60000 is not supported (attention merge table lives in LDS)";
+  if (m->max_seq > 60000) return "max_seq above 60000 is not supported (the longest context that is tested)";
   if (m->max_src > 4096) return "max_src above 4096 is not supported";
   return nullptr;
 }

@@ -13,7 +13,6 @@ constexpr int kMaxBlockRows = 256;  // rows one forward of several sequences can
 constexpr int kAttnChunk = 128;     // keys per attention work-group of the fp32-cache kernels and the unit callers count chunks in; boundaries are absolute positions
 constexpr int kAttnChunkH = 256;    // keys per attention work-group of the half-cache kernels (a wave owns 64)
 constexpr int kAttnFusedMaxChunks = 24;   // more chunks per head than this: the chunk merge runs as a second kernel
-constexpr size_t kAttnMergeMaxLds = 150 * 1024;   // most dynamic LDS the chunk merge may take
 constexpr int kSsqGroup = 16;       // residual columns per sum-of-squares partial, bf16 models (= one weight tile of the residual-writing GEMMs)
 constexpr int kUnitK = 256;         // k extent of one weight "unit" (8 MFMA k-steps of 32)
 constexpr int kSliceUnits = 2;      // units per split-K slice (512 k)

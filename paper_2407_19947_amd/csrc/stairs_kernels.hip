@@ -296,18 +296,11 @@ __device__ __forceinline__ uint4 ld_nt(const uint4* p) {
   const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
   return make_uint4(v.x, v.y, v.z, v.w);
 }
-// One 8 KiB weight unit of a wave (8 loads of 1 KiB).  STREAM (a template argument: a run-time choice between the two
-// load forms cost the whole gain in the kernels' prologues): weights of a model far larger than the
+// One 8 KiB weight unit of a wave (8 loads of 1 KiB) from a base that is the same in all lanes: lane l reads base + off + i * STEP *
+// 16 bytes; what lies outside [base, base + span) is not fetched and reads as zeros.  STREAM (a template argument: a run-time
+// choice between the two load forms cost the whole gain in the kernels' prologues): weights of a model far larger than the
 // 256 MB memory-side cache are read once per forward and gain from the streaming hint (a bare 2 GB read: 6.2 -> 7.05
 // TB/s); a model that about fits that cache is served from it forward after forward and must keep plain loads.
-template <bool STREAM, int STEP = 64>
-__device__ __forceinline__ void load_unit(const uint4* p, uint4 (&wb)[8]) {
-#pragma unroll
-  for (int i = 0; i < 8; ++i) wb[i] = STREAM ? ld_nt(&p[i * STEP]) : p[i * STEP];
-}
-
-// The same with a base that is the same in all lanes: lane l reads base + off + i * STEP * 16 bytes; what lies outside
-// [base, base + span) is not fetched and reads as zeros.
 template <bool STREAM, int STEP>
 __device__ __forceinline__ void load_unit_in(const uint4* base, uint32_t off, uint32_t span, uint4 (&wb)[8]) {
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint4*>(base), 0, span, 0x00027000);
@@ -1858,7 +1851,7 @@ __device__ __forceinline__ void store_attn_frag4(uint4* frag, int frag_rt, int m
 // flight together.
 // More chunks: groups of kMergeCB chunks are summed by different threads in parallel (each as above, from zero) and the
 // group sums added in group order; the grouping depends only on the row's own position.  Dynamic LDS:
-// [M][nch_lds][2] pairs (weight, sum), [kMaxRows] unused, [rows_per_pass][HD/4][groups][5] group sums.
+// [M][nch_lds][2] pairs (weight, sum), [kMaxRows] unused, [M][HD/4][groups][5] group sums (see launch_attention).
 constexpr int kMergeCB = 20;
 // Step A of the merge: the (weight, sum) table of all rows and chunks in LDS (see attn_merge)
 __device__ __forceinline__ void attn_merge_table(const float* part_ml, int H, int h, int M, int pos0, int step, int nch_max,
@@ -1965,8 +1958,8 @@ __device__ __forceinline__ void attn_merge_direct(const float* part_o, const flo
 
 template <int HD>
 __device__ __forceinline__ void attn_merge(const float* part_o, const float* part_ml, int H, int h, int M, int pos0, int step,
-                                           int kv_len, int nchunk_cap, int nch_lds, int rows_per_pass, float* out, int d,
-                                           float* s_ml, uint4* frag, int frag_rt, int frag_row0) {
+                                           int kv_len, int nchunk_cap, int nch_lds, float* out, int d, float* s_ml,
+                                           uint4* frag, int frag_rt, int frag_row0) {
   const int tid = threadIdx.x;
   const int nch_max = (kv_len > 0) ? (kv_len - 1) / kAttnChunkH + 1 : 0;
   if (nch_max <= kMergeCB / 2)                        // (no chunk at all: every row gets zeros)
@@ -2002,40 +1995,36 @@ __device__ __forceinline__ void attn_merge(const float* part_o, const float* par
       }
     }
   };
-  for (int m0 = 0; m0 < M; m0 += rows_per_pass) {
-    const int rows = min(rows_per_pass, M - m0);
-    for (int idx = tid; idx < rows * QPR * G; idx += 256) {
-      const int g = idx % G, rq = idx / G;
-      const int ml = rq / QPR, e = (rq - ml * QPR) * 4, m = m0 + ml;
-      const int p = pos0 + m * step;
+  for (int idx = tid; idx < M * QPR * G; idx += 256) {
+    const int g = idx % G, rq = idx / G;
+    const int m = rq / QPR, e = (rq - m * QPR) * 4;
+    const int p = pos0 + m * step;
+    float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
+    float den = 0.f;
+    if (p >= 0) {
+      const int nch = p / kAttnChunkH + 1;
+      if (g * CB < nch) group_sum(m, e, g * CB, min(nch, (g + 1) * CB), num, den);
+    }
+    float* o = grp + (size_t)idx * 5;
+    o[0] = num.x; o[1] = num.y; o[2] = num.z; o[3] = num.w; o[4] = den;
+  }
+  __syncthreads();
+  for (int idx = tid; idx < M * QPR; idx += 256) {
+    const int m = idx / QPR, e = (idx - m * QPR) * 4;
+    const int p = pos0 + m * step;
+    float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (p >= 0) {
+      const int ng = (p / kAttnChunkH + 1 + CB - 1) / CB;
       float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
       float den = 0.f;
-      if (p >= 0) {
-        const int nch = p / kAttnChunkH + 1;
-        if (g * CB < nch) group_sum(m, e, g * CB, min(nch, (g + 1) * CB), num, den);
+      for (int g = 0; g < ng; ++g) {
+        const float* o = grp + ((size_t)idx * G + g) * 5;
+        num.x += o[0]; num.y += o[1]; num.z += o[2]; num.w += o[3]; den += o[4];
       }
-      float* o = grp + (size_t)idx * 5;
-      o[0] = num.x; o[1] = num.y; o[2] = num.z; o[3] = num.w; o[4] = den;
+      res = make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
     }
-    __syncthreads();
-    for (int idx = tid; idx < rows * QPR; idx += 256) {
-      const int ml = idx / QPR, e = (idx - ml * QPR) * 4, m = m0 + ml;
-      const int p = pos0 + m * step;
-      float4 res = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (p >= 0) {
-        const int ng = (p / kAttnChunkH + 1 + CB - 1) / CB;
-        float4 num = make_float4(0.f, 0.f, 0.f, 0.f);
-        float den = 0.f;
-        for (int g = 0; g < ng; ++g) {
-          const float* o = grp + ((size_t)idx * G + g) * 5;
-          num.x += o[0]; num.y += o[1]; num.z += o[2]; num.w += o[3]; den += o[4];
-        }
-        res = make_float4(num.x / den, num.y / den, num.z / den, num.w / den);
-      }
-      *reinterpret_cast<float4*>(out + (size_t)m * d + h * HD + e) = res;
-      if (frag) store_attn_frag4(frag, frag_rt, frag_row0 + m, h * HD + e, res);
-    }
-    __syncthreads();
+    *reinterpret_cast<float4*>(out + (size_t)m * d + h * HD + e) = res;
+    if (frag) store_attn_frag4(frag, frag_rt, frag_row0 + m, h * HD + e, res);
   }
 }
 
@@ -2044,7 +2033,7 @@ template <int HD, int CT, bool FUSED>
 __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q, const _Float16* __restrict__ Kc,
                                                   const _Float16* __restrict__ Vc, const int* __restrict__ pos_base, int pos_offset, int pos_rps,
                                                   int cap, int d, int M, int early_keys, size_t kv_slot_stride, float scale, int H, AttnMode am,
-                                                  int nchunk_cap, int rows_per_pass, float* part_o, float* part_ml, int* counters,
+                                                  int nchunk_cap, float* part_o, float* part_ml, int* counters,
                                                   float* __restrict__ out) {
   const PosRef pos{pos_base, pos_offset, pos_rps};
   const int kv_fixed = max(0, -early_keys);
@@ -2272,7 +2261,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_f16(const float* __restrict__ q
   if (!FUSED || single) return;
   if (!last_arrival(&counters[h], (int)gridDim.x, &s_last)) return;
   extern __shared__ float s_ml[];
-  attn_merge<HD>(part_o, part_ml, H, h, M, pos0, step, kv_len, nchunk_cap, (int)gridDim.x, rows_per_pass, out, d, s_ml,
+  attn_merge<HD>(part_o, part_ml, H, h, M, pos0, step, kv_len, nchunk_cap, (int)gridDim.x, out, d, s_ml,
                  am.frag_out, am.frag_rt, row0);
   if (tid == 0) counters[h] = 0;
 }
@@ -2288,7 +2277,7 @@ __global__ __launch_bounds__(256) void k_attn_merge(const float* part_o, const f
   const int h = blockIdx.x, row = blockIdx.y * M + blockIdx.z;
   const int last = kv_fixed > 0 ? kv_fixed - 1 : pos_of(pos, row);     // last key the row sees
   attn_merge<HD>(part_o + (size_t)row * H * nchunk_cap * HD, part_ml + (size_t)row * H * nchunk_cap * 2, H, h, 1, last, 0, last + 1,
-                 nchunk_cap, nch_lds, 1, out + (size_t)row * d, d, s_ml, frag, frag_rt, row);
+                 nchunk_cap, nch_lds, out + (size_t)row * d, d, s_ml, frag, frag_rt, row);
 }
 
 // Query rows a work-group of the fp32 attention takes.  Up to 8 rows: one, as long as that makes fewer than 1024 groups (four
@@ -2343,25 +2332,22 @@ void launch_attention(const float* q_rot, const void* Kc, const void* Vc, int kv
     nchunk_launch = (nchunk_launch * kAttnChunk + kAttnChunkH - 1) / kAttnChunkH;
     dim3 grid(nchunk_launch, H, nslots), block(256);
     const int early = am.kv_fixed > 0 ? -am.kv_fixed : attn_early_keys(units, nslots);   // (k_attn_f16: one argument for both)
-    // merge step's LDS: (max, sum) table, row maxima, and for more than kMergeCB chunks the group sums of as many
-    // rows per pass as fit in 48 KiB, less when the table is large (the whole stays under kAttnMergeMaxLds)
-    const int G = (nchunk_launch + kMergeCB - 1) / kMergeCB;
-    const size_t table = ((size_t)M * nchunk_launch * 2 + kMaxRows) * sizeof(float);
-    const size_t per_row = (size_t)(hd / 4) * G * 5 * sizeof(float);
-    const size_t budget = std::min<size_t>(48 * 1024, kAttnMergeMaxLds > table ? kAttnMergeMaxLds - table : 0);
-    const int rpp = G > 1 ? std::max(1, std::min(M, (int)(budget / per_row))) : M;
-    const size_t lds = table + (G > 1 ? (size_t)rpp * per_row : 0);
-    const size_t lds_row = ((size_t)nchunk_launch * 2 + kMaxRows) * sizeof(float) + (G > 1 ? per_row : 0);   // of one row
     // long contexts: attention work-groups only store their partials, a second kernel merges (no wait, no ticket)
     const bool fused = nchunk_launch <= kAttnFusedMaxChunks;
+    // LDS of a merge of so many rows: their (max, sum) table and, for more than kMergeCB chunks, their group sums.  Fused: at most
+    // 47 KiB (32 rows, 24 chunks); by itself, a row a work-group: 17 KiB at 60000 keys.
+    const int G = (nchunk_launch + kMergeCB - 1) / kMergeCB;
+    auto merge_lds = [&](int rows) {
+      return ((size_t)rows * (nchunk_launch * 2 + (G > 1 ? hd / 4 * G * 5 : 0)) + kMaxRows) * sizeof(float);
+    };
 #define STAIRS_ATTN16(hdv, ct)                                                                                              \
   if (fused)                                                                                                                \
-    hipLaunchKernelGGL((k_attn_f16<hdv, ct, true>), grid, block, lds, st, q_rot, K, V, pos.base, pos.offset, pos.rps, cap, d, M, early, \
-                       kv_slot_stride, scale, H, am, nchunk_cap, rpp, part_o, part_ml, counters, out);                                         \
+    hipLaunchKernelGGL((k_attn_f16<hdv, ct, true>), grid, block, merge_lds(M), st, q_rot, K, V, pos.base, pos.offset, pos.rps, cap, d, M, early, \
+                       kv_slot_stride, scale, H, am, nchunk_cap, part_o, part_ml, counters, out);                                              \
   else {                                                                                                                    \
     hipLaunchKernelGGL((k_attn_f16<hdv, ct, false>), grid, block, 0, st, q_rot, K, V, pos.base, pos.offset, pos.rps, cap, d, M, early, \
-                       kv_slot_stride, scale, H, am, nchunk_cap, rpp, part_o, part_ml, counters, out);                                         \
-    hipLaunchKernelGGL((k_attn_merge<hdv>), dim3(H, nslots, M), dim3(256), lds_row, st, part_o, part_ml, pos.base, pos.offset, \
+                       kv_slot_stride, scale, H, am, nchunk_cap, part_o, part_ml, counters, out);                                              \
+    hipLaunchKernelGGL((k_attn_merge<hdv>), dim3(H, nslots, M), dim3(256), merge_lds(1), st, part_o, part_ml, pos.base, pos.offset, \
                        pos.rps, d, H, M, am.kv_fixed, nchunk_cap, nchunk_launch, out, am.frag_out, am.frag_rt);              \
   }
     if (hd == 128) {
@@ -2920,15 +2906,11 @@ hipError_t configure_kernels() {
 #undef STAIRS_OPTIN_WIDE
 #undef STAIRS_OPTIN_WIDE_
   if (configure_block_kernels() != hipSuccess) e = hipErrorInvalidValue;
-  // the stand-alone attention merge keeps a table of all chunks in LDS: large for long contexts (the fused
-  // merge runs for at most kAttnFusedMaxChunks chunks and stays small)
   optin((const void*)k_attn<128, 1, true>, 128 * 1024);
   optin((const void*)k_attn<128, 1, false>, 128 * 1024);
   optin((const void*)k_attn<128, 4, false>, 128 * 1024);
   optin((const void*)k_attn<128, 16, true>, 128 * 1024);
   optin((const void*)k_attn<128, 16, false>, 128 * 1024);
-  optin((const void*)k_attn_merge<128>, kAttnMergeMaxLds);
-  optin((const void*)k_attn_merge<64>, kAttnMergeMaxLds);
   if (counted && e == hipSuccess) done[dev] = true;
   return e;
 }
