@@ -1173,10 +1173,12 @@ bool launch_gemm_shared(int role, const void* W, int N, int K, const uint4* xfra
 //   L2 gives, and per 32 keys the masks, lane exchanges and rescaling of every step were more vector instructions than the
 //   MFMAs leave room for: now masks only at the diagonal, sums over the lanes at the end, rescaling where a maximum grew.
 //   Tiles of several sequences in one work-group: the runs of tiles of one sequence one after the other.
-//   Launches by themselves, before -> now, us: 32 heads of 128, 2048 rows behind nothing / behind 6144 keys 110 -> 84 / 592 -> 404
-//   (1.19 PFLOP/s issued), 333 rows 13.4 -> 12.0, 777 rows of an encoder 54.2 -> 46.4; 16 heads of 64, 2048 rows behind 6144 keys
-//   200 -> 140.  (log2 e goes onto the differences from the maximum, 16 multiplications a step: onto the queries they overflow
-//   the half at 45400 instead of 65504, onto the scores a bias of the lowest float becomes infinite; 82 / 397 us.)  What bounds it then: MFMAs and the softmax's vector instructions on a SIMD, which overlap only in part.
+//   Launches by themselves, before -> now, us: 32 heads of 128, 2048 rows behind nothing / behind 6144 keys 110 -> 83 / 597 -> 400
+//   (1.2 PFLOP/s issued), 333 rows 13.4 -> 11.8, 777 rows of an encoder 54.3 -> 46.3; 16 heads of 64, 2048 rows behind 6144 keys
+//   199 -> 135.  What bounds it then: MFMAs and the softmax's vector instructions on a SIMD, which overlap only in part.
+//   Where log2 e goes: on the queries it makes them overflow their half from 45400 on instead of 65504.  Without a bias, where
+//   scores of half queries and keys stay far inside a float, the exponent is one s * log2 e - m with m in units of log 2; with one,
+//   whose lowest float must not become infinite, the difference from the maximum is multiplied as in the decode kernel.
 //   QT = 2 where that leaves two work-groups per CU, else 1.  Row blocks come longest first; where all work-groups are
 //   resident at once, the second half shortest first, so that a long one shares its CU with a short one.
 template <int HD, bool BIAS, int QT>
@@ -1234,7 +1236,8 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
     }
   }
   f32x4 oacc[QT][ET];
-  float m_run[QT], l_run[QT];
+  constexpr float kLog2e = 1.44269504088896340736f;
+  float m_run[QT], l_run[QT];                         // (the maximum times log2 e but with a bias, see above)
 #pragma unroll
   for (int t = 0; t < QT; ++t) {
 #pragma unroll
@@ -1298,9 +1301,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
       mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
       sw = __builtin_amdgcn_permlane16_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
       mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+      if (!BIAS) mx *= kLog2e;
       if (__any(mx > m_run[t])) {
         const float m_new = fmaxf(m_run[t], mx);
-        const float alpha = m_run[t] == -INFINITY ? 0.f : exp_fast(m_run[t] - m_new);
+        const float alpha = m_run[t] == -INFINITY ? 0.f : BIAS ? exp_fast(m_run[t] - m_new) : __builtin_amdgcn_exp2f(m_run[t] - m_new);
         l_run[t] *= alpha;
 #pragma unroll
         for (int et = 0; et < ET; ++et) {
@@ -1313,7 +1317,10 @@ __global__ __launch_bounds__(256, 2) void k_attn_flash(const float* __restrict__
       for (int b = 0; b < 2; ++b) {
         float pv[8];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) pv[i] = exp_fast(sacc[t][2 * b + (i >> 2)][i & 3] - m);
+        for (int i = 0; i < 8; ++i) {
+          const float s = sacc[t][2 * b + (i >> 2)][i & 3];
+          pv[i] = BIAS ? exp_fast(s - m) : __builtin_amdgcn_exp2f(fmaf(s, kLog2e, -m));
+        }
         l_run[t] += ((pv[0] + pv[1]) + (pv[2] + pv[3])) + ((pv[4] + pv[5]) + (pv[6] + pv[7]));
         split_half8(pv, ph[t][b], pl[t][b]);
       }
