@@ -82,7 +82,7 @@ struct stairs_ctx {
   bool shared_kv = false;                         // the draft's caches are the target's (see prefix_draft)
   Model T, D;
   std::vector<void*> owned;                       // every device allocation, freed in stairs_free
-  std::map<std::pair<const void*, int>, const void*> dedup;   // (first host ptr, kind) -> device copy
+  std::map<std::vector<uintptr_t>, const void*> dedup;   // what a device copy is made from (upload_matrix, upload_plain) -> the copy
   // workspaces (sized for the larger of the two models)
   float *x = nullptr, *ssq = nullptr, *q_rot = nullptr, *attn_out = nullptr, *h = nullptr, *logits = nullptr;
   float *partial = nullptr, *part_o = nullptr, *part_ml = nullptr;
@@ -214,7 +214,9 @@ int upload_matrix(stairs_ctx* c, bool bf16, const void* const* parts, int nparts
                   int hd, char* staging, const void** out) {
   // gate/up and q/k rows are reordered so that SwiGLU and rotation pairs share a 16-row tile
   const int perm = (kind == KIND_GU) ? kPermGateUp : (kind == KIND_QKV) ? kPermQKV : kPermNone;
-  auto key = std::make_pair(parts[0], kind);
+  // every part, the shape, the type and, where rows are reordered by heads, their size: else it is another operand
+  std::vector<uintptr_t> key{(uintptr_t)kind, (uintptr_t)bf16, (uintptr_t)rows_each, (uintptr_t)K, (uintptr_t)(perm == kPermQKV ? hd : 0)};
+  for (int p = 0; p < nparts; ++p) key.push_back(reinterpret_cast<uintptr_t>(parts[p]));
   auto it = c->dedup.find(key);
   if (it != c->dedup.end()) {
     *out = it->second;
@@ -240,7 +242,7 @@ int upload_matrix(stairs_ctx* c, bool bf16, const void* const* parts, int nparts
 }
 
 int upload_plain(stairs_ctx* c, const void* host, size_t bytes, int kind, const void** out) {
-  auto key = std::make_pair(host, kind);
+  const std::vector<uintptr_t> key{(uintptr_t)kind, bytes, reinterpret_cast<uintptr_t>(host)};
   auto it = c->dedup.find(key);
   if (it != c->dedup.end()) {
     *out = it->second;

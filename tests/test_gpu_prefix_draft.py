@@ -89,3 +89,46 @@ def test_batches(B, k):
         assert list(a) == list(b)
     if B * (k + 1) <= 64:
         _same_stats(xa, xb)
+
+
+def _alike(draft, what):
+    """a draft that has the target's arrays but for one thing"""
+    d = copy.copy(draft)
+    d.layers = [dict(l) for l in draft.layers]
+    rng = np.random.default_rng(5)
+    if what == "heads":
+        d.n_heads = draft.n_heads // 2
+    elif what in ("rms_eps", "rope_theta"):
+        setattr(d, what, getattr(draft, what) * 30)
+    elif what == "layers swapped":
+        d.layers[0], d.layers[1] = d.layers[1], d.layers[0]
+    elif what.endswith("norm"):
+        d.layers[-1][what] = (draft.layers[-1][what] * rng.uniform(0.5, 1.5, draft.d_model)).astype(np.float32)
+    else:
+        d.layers[-1][what] = np.ascontiguousarray(draft.layers[-1][what][::-1])
+    return d
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("what", ["wk", "wv", "w_up", "w_down", "attn_norm", "ffn_norm", "rms_eps", "rope_theta", "heads", "layers swapped"])
+def test_drafts_that_differ_in_one_thing(dtype, what):
+    """Nothing of the target's that is not the draft's too: the proposals and tokens of the same draft in arrays of its own."""
+    w, target, draft, _ = _pair(dtype, 2)
+    if what == "heads" and target.head_dim != 64:
+        pytest.skip("head_dim 128 is the largest there is")
+    near = _alike(draft, what)
+    prompt = si.make_prompt(w, 70)
+    def use(s):
+        tokens, stats = s.generate(prompt, 33, 3)
+        s.prefill(prompt)
+        steps = []
+        for i in range(4):
+            drawn, logits = s.propose_sampled(3, 0.7, 11 + i)
+            steps += [drawn, logits, s.verify_sampled(3, 0.7, 11 + i)[0]]
+        return list(tokens), stats, steps
+    (ta, xa, sa), (tb, xb, sb), (tc, xc, sc) = _both(target, (near, copy.deepcopy(near), draft), 3, 70 + 80, use)
+    assert ta == tb
+    _same_stats(xa, xb)
+    for a, b in zip(sa, sb):
+        assert np.array_equal(a, b)
+    assert not np.array_equal(sa[1], sc[1])            # (the difference shows)
