@@ -1086,7 +1086,7 @@ int enqueue_propose(stairs_ctx* c, int k, int nch, bool embedded) {
   const bool cand = leaves_candidates(m, 1);
   auto decide = [&](int j) {                // d_{j+1}; for another step, its embedding too
     const NextEmbed next = j + 1 < k ? next_embed(c, m) : NextEmbed{};
-    if (decide_takes(cand, 1, V))
+    if (decide_takes(cand, V))
       launch_decide(cand ? reinterpret_cast<const float*>(c->cand) : c->logits, cand, V, 1, c->tokens, rel_pos(c, j), c->st, next);
     else
       launch_argmax(c->logits, V, V, 1, 0, 1, c->tokens, rel_pos(c, j), 0, c->st, next);
@@ -1107,7 +1107,7 @@ HostResult host_result(const stairs_ctx* c, bool in_loop) {
 }
 
 // Whether a greedy verification ends in the one launch that chooses, validates and, in a loop, leaves {L, n} with the host
-bool verify_decides(const stairs_ctx* c, int k) { return decide_takes(leaves_candidates(&c->T, k + 1), k + 1, c->T.cfg.vocab); }
+bool verify_decides(const stairs_ctx* c, int k) { return decide_accept_takes(leaves_candidates(&c->T, k + 1), k + 1, c->T.cfg.vocab); }
 
 // Enqueue the stair batch for the k draft tokens sitting in tokens[L..L+k), its per-row argmax and the validation.
 // in_loop: another iteration with this k may follow; this one's last launch leaves what it starts from (and k = 0: found its

@@ -212,7 +212,7 @@ int attn_f32_rows(int units, int H, int M);
 // forward whose only row is that token at that position.
 void launch_argmax(const float* logits, int ld, int V, int nrows, int row0, int row_stride, int* out, PosRef out_pos,
                    int out_slot_stride, hipStream_t st, const NextEmbed& next = NextEmbed{});
-// The same and what follows it in one launch, for M <= 8 rows of one sequence (decide_takes).  src: the unembedding's candidates
+// The same and what follows it in one launch, for M <= 8 rows of one sequence (where ..._takes).  src: the unembedding's candidates
 // (cand: launch_unembed's, V / 16 pairs a row), else the rows of V logits themselves.
 //   launch_decide       : M = 1, tokens[out_pos] = the choice; next: its embedding
 //   launch_decide_accept: the choices of k + 1 stair rows (to tgt as well), launch_accept, and the embeddings of the last
@@ -222,7 +222,8 @@ struct HostResult {
   int* at;
   int* turn;
 };
-bool decide_takes(bool cand, int M, int V);
+bool decide_takes(bool cand, int V);
+bool decide_accept_takes(bool cand, int M, int V);
 void launch_decide(const float* src, bool cand, int V, int M, int* tokens, PosRef out_pos, hipStream_t st, const NextEmbed& next);
 void launch_decide_accept(const float* src, bool cand, int V, int k, int* tokens, int* tgt, int* state, hipStream_t st, const NextEmbed& next,
                           int next_rows, const HostResult& host);

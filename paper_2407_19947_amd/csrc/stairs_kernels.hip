@@ -2458,7 +2458,7 @@ __device__ __forceinline__ void host_result(const HostResult& h, int turn, int L
 //   ACCEPT: validation of the stair batch (k_accept) and the embeddings the next iteration starts from;
 //   else  : a draft token (M = 1) and the embedding of the step it leads to.
 // CAND: src holds a (value, index) pair per row and 16 columns, left by the unembedding's work-groups (launch_unembed); else the
-// rows of logits themselves, where they are short (decide_takes).  A row of 32000 logits through one CU took longer than all its
+// rows of logits themselves, where they are short (decide_takes, decide_accept_takes).  A row of 32000 logits through one CU took longer than all its
 // candidates, and the validation and the first embedding of a proposal were launches of their own (125M, k = 4, us: a draft token
 // 5.9 -> 4.7; choice of five rows, validation and embedding 4.6 + 2.1 + 2.2 -> 6.3; tiny fp32 pair 3.3 -> 3.2 and 2.7 + 1.3 + 2.2
 // -> 3.9).  What bounds it: the chain of three round trips (candidates, the token's embedding, its store).
@@ -2549,7 +2549,14 @@ __global__ __launch_bounds__(1024) void k_decide(const float* __restrict__ src, 
   __syncthreads();
   for (int i = 0; i < next_rows; ++i) next_embed(next, s_pos - (next_rows - 1 - i), s_id[kMaxNextRows - next_rows + i], 1024, i);
 }
-bool decide_takes(bool cand, int M, int V) { return M <= 8 && (cand || M * V <= 16384); }
+// Rows of logits themselves are read by one CU, so joined launches pay while they are short.  Launches before / joined, generation of
+// a pair of 2 + 1 fp32 layers (d 256): a draft token (its step) at 1024 / 4096 / 8192 / 16384 logits 23.8 / 23.7, 24.2 / 24.2, 24.8 /
+// 25.1, 25.8 / 27.3 us; a verification of 1 row at 16384 / 32768 51.4 / 49.1, 57.4 / 55.1, of 2 at 8192 / 16384 54.4 / 51.9, 55.5 /
+// 54.2, of 8 at 2048 / 4096 / 8192 58.9 / 57.3, 59.9 / 59.1, 61.7 / 63.4 (bf16, 8 rows: 78.2 / 76.6, 78.8 / 77.9, 78.7 / 80.5).
+// Candidates are ahead at every size: 32000 logits, a draft token 30.2 / 29.2, 1 / 4 / 7 rows 55.8 / 53.6, 60.2 / 58.1, 65.5 / 63.5;
+// 130944, 48.5 / 45.3, 74.3 / 67.9, 80.9 / 77.1, 87.2 / 85.4.
+bool decide_takes(bool cand, int V) { return cand || V <= 4096; }
+bool decide_accept_takes(bool cand, int M, int V) { return M <= 8 && (cand || M * V <= 16384); }
 void launch_decide(const float* src, bool cand, int V, int M, int* tokens, PosRef out_pos, hipStream_t st, const NextEmbed& next) {
   hipLaunchKernelGGL((cand ? k_decide<true, false> : k_decide<false, false>), dim3(1), dim3(1024), 0, st, src, tokens, out_pos.base, out_pos.offset,
                      cand ? V / 16 : V, M, 1, nullptr, nullptr, HostResult{}, next);

@@ -20,7 +20,7 @@ def _pair(dtype, vocab):
     return w, target, draft
 
 
-@pytest.mark.parametrize("dtype,vocab", [("bf16", 2048), ("bf16", 4112), ("bf16", 32), ("fp32", 1024), ("fp32", 4100)])
+@pytest.mark.parametrize("dtype,vocab", [("bf16", 2048), ("bf16", 4112), ("bf16", 32), ("fp32", 1024), ("fp32", 4096), ("fp32", 4100)])
 @pytest.mark.parametrize("step", ["neighbours", "halves"])
 def test_ties_go_to_the_lowest_id(dtype, vocab, step):
     w, target, draft = _pair(dtype, vocab)
