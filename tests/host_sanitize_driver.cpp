@@ -13,6 +13,7 @@
 
 #include <dlfcn.h>
 
+#include <algorithm>
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
@@ -336,6 +337,21 @@ static void part2_decoder_only() {
   CHECK(stairs_generate_batch(c, pp.data(), PP.data(), 6, G, 3, both.data(), &st) == STAIRS_ENOMEM);
   g_refuse = 0;
   CHECK(stairs_generate_batch(c, pp.data(), PP.data(), 6, G, 3, both.data(), &st) == STAIRS_OK && both == alone);
+  // an iteration of a batch that cannot be launched (its proposal, its verification; with none and with one in front of it) or whose
+  // time cannot be read while two are in flight: the error is the call's, and the next call finds everything as it has to be
+  for (int k : {0, 3})
+    for (int at = 1; at <= (k > 0 ? 5 : 3); ++at) {
+      const bool launch = at <= (k > 0 ? 4 : 2);
+      (launch ? g_refuse_launch : g_refuse_time) = launch ? at : 1;
+      std::fill(both.begin(), both.end(), -1);
+      CHECK(stairs_generate_batch(c, pp.data(), PP.data(), 6, G, k, both.data(), &st) == STAIRS_EHIP);
+      CHECK(g_refuse_launch == 0 && g_refuse_time == 0);
+      CHECK(std::strstr(stairs_last_error(c), hipGetErrorString(hipErrorOutOfMemory)) != nullptr);
+      CHECK(stairs_decode(c, 4, k, both.data(), &st) == STAIRS_ESTATE);     // a batch leaves no sequence, nor does its error
+      CHECK(stairs_generate_batch(c, pp.data(), PP.data(), 6, G, k, both.data(), &st) == STAIRS_OK && both == alone);
+      CHECK(stairs_generate(c, pp[0], PP[0], G, k, both.data(), &st) == STAIRS_OK);
+      CHECK(std::memcmp(both.data(), alone.data(), G * sizeof(int32_t)) == 0);
+    }
   CHECK(stairs_generate_batch(c, pp.data(), PP.data(), 7, G, 3, both.data(), &st) == STAIRS_EINVAL);
   CHECK(stairs_reserve_batch(c, STAIRS_MAX_BATCH + 1) == STAIRS_EINVAL);
   CHECK(stairs_reserve_batch(c, 24) == STAIRS_OK);

@@ -38,3 +38,24 @@ def test_ahead_and_one_by_one(B, k, monkeypatch):
             assert np.array_equal(ta, tb), mode
             for key in ("iterations", "tokens", "accepted", "accept_hist"):
                 assert sa[key] == sb[key], (mode, key)
+
+
+@pytest.mark.parametrize("P", [487, 491, 494, 497, 498, 499, 500, 501, 502, 503])
+def test_lengths_that_outgrow_the_attention_launch_while_two_iterations_run(P, monkeypatch):
+    """512 keys are four units of 128, a launch for more has five: an iteration that is launched while the one before it runs must
+    cover the keys that one can still add.  Prompts that cross the line at different iterations; without graphs every launch is
+    sized for the length it has."""
+    w = si.scaled_workload("cfg2_125m", target=dict(n_layers=3, d_model=256, n_heads=4, d_ffn=768, vocab=2048),
+                           draft=dict(kind="prefix", n_layers=1))
+    target, draft = si.make_pair(w)
+    prompts = [si.make_prompt(w, n) for n in (P, P - 7, 30)]
+    got = []
+    for mode in ("0", "1"):
+        monkeypatch.setenv("STAIRS_NO_GRAPH", mode)
+        with pkg.Stairs(target, draft, k_max=3, max_seq=640) as s:
+            s.reserve_batch(3)
+            toks, st = s.generate_batch(prompts, 40, 3)
+            one, st1 = s.generate(prompts[0], 40, 3)
+            got.append((toks, st.as_dict()["accept_hist"], one, st1.as_dict()["accept_hist"]))
+    for a, b in zip(*got):
+        assert np.array_equal(a, b)
