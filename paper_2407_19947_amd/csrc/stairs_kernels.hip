@@ -527,6 +527,10 @@ __device__ __forceinline__ void argmax_swap(float& best, int& bi, bool far) {   
   argmax_take(best, bi, __uint_as_float(second ? rb[0] : rb[1]), (int)(second ? ri[0] : ri[1]));
 }
 
+// what a launch of k_gemm_bf16_rows takes behind its leading arguments (one structure: every argument more costs the host 0.1 us a launch)
+struct RowsEpi : GemmEpi {
+  float2* cand;
+};
 // ROWMAJOR: W as the caller has it, [N, K] row-major: lane r + 16 g reads row 16 tile + r, k 32 kt + 8 g .. + 8, the very
 // operand the tile layout holds in one piece (a wave's load is then 16 runs of 64 bytes; for a matrix used once that is
 // far less than laying it out first).
@@ -535,8 +539,7 @@ __device__ __forceinline__ void argmax_swap(float& best, int& bi, bool far) {   
 template <int R, int ROLE, int NW, int GP, int Q, bool WALK, bool STREAM, bool ROWMAJOR = false>
 __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restrict__ Wsw, const float* __restrict__ X,
                                                             const float* __restrict__ gain, const float* __restrict__ ssq_part,
-                                                            int K, int N, int ldx, int ssq_n, float* out, float eps, float2* cand,
-                                                            GemmEpi epi) {
+                                                            int K, int N, int ldx, int ssq_n, float* out, float eps, RowsEpi epi) {
   constexpr int NTH = 64 * NW, NG = NTH / Q, RP = (R + Q - 1) / Q;
   constexpr bool NORMED = ROLE != kRoleWo && ROLE != kRoleDown;      // (the residual-writing projections' inputs are not)
   extern __shared__ uint4 lds[];
@@ -775,14 +778,14 @@ __global__ __launch_bounds__(64 * NW) void k_gemm_bf16_rows(const uint4* __restr
       }
       out[(size_t)m * N + col] = a;
       out[(size_t)m * N + col + 8] = b;
-      if (cand) {                                          // the tile's largest value, for k_decide (a NaN is none)
+      if (!ROWMAJOR && epi.cand) {                         // the tile's largest value, for k_decide (a NaN is none)
         float v = fmaxf(a, -INFINITY);
         int ix = col;
         if (b > v) { v = b; ix = col + 8; }
         argmax_dpp<kDppXor1>(v, ix);
         argmax_dpp<kDppXor2>(v, ix);
         argmax_dpp<kDppHalfMirror>(v, ix);
-        if (j == 0) cand[(size_t)m * NTILES + tile] = make_float2(v, __int_as_float(ix));
+        if (j == 0) epi.cand[(size_t)m * NTILES + tile] = make_float2(v, __int_as_float(ix));
       }
       if (R > 4 && epi.frag_out) {
         const float4 va = make_float4(dpp<kDppQuad0>(a), dpp<kDppQuad1>(a), dpp<kDppQuad2>(a), dpp<kDppQuad3>(a));
@@ -1229,7 +1232,7 @@ bool launch_gemm_rowmajor(const uint16_t* W, int N, int K, const float* X, int M
   const size_t rl = rows_path_lds(kRoleHead, M, N, K);
   if (rl && M <= 4) {
 #define STAIRS_ROWM(r) \
-  hipLaunchKernelGGL((rows_kernel<r, kRoleHead, 4, 2, false, true>(K, false)), dim3(NTILES), dim3(256), rl, st, Wr, X, none.gain, none.ssq_part, K, N, K, none.ssq_n, e.out, none.eps, nullptr, e)
+  hipLaunchKernelGGL((rows_kernel<r, kRoleHead, 4, 2, false, true>(K, false)), dim3(NTILES), dim3(256), rl, st, Wr, X, none.gain, none.ssq_part, K, N, K, none.ssq_n, e.out, none.eps, RowsEpi{e, nullptr})
     if (M == 1) STAIRS_ROWM(1);
     else if (M == 2) STAIRS_ROWM(2);
     else if (M == 3) STAIRS_ROWM(3);
@@ -1456,7 +1459,7 @@ static void gemm(int role, int dtype_bf16, const void* W, int N, int K, const fl
     const size_t rl_launch = tpw > 1 ? std::max(rl, (size_t)81 * 1024) : rl;
 #define STAIRS_ROWS(r, role, nw, gp)                                                                                    \
   launch_gemm_kernel(epi.stream_weights ? rows_kernel<r, role, nw, gp, true>(K, tpw > 1) : rows_kernel<r, role, nw, gp, false>(K, tpw > 1), rgrid, \
-                     dim3(64 * nw), rl_launch, st, Wsw, X, nrm.gain, nrm.ssq_part, K, N, ldx, nrm.ssq_n, epi.out, nrm.eps, cand, epi)
+                     dim3(64 * nw), rl_launch, st, Wsw, X, nrm.gain, nrm.ssq_part, K, N, ldx, nrm.ssq_n, epi.out, nrm.eps, RowsEpi{epi, cand})
 #define STAIRS_ROWS_ROLE4(role, nw, gp)          \
   if (M <= 1) STAIRS_ROWS(1, role, nw, gp);      \
   else if (M == 2) STAIRS_ROWS(2, role, nw, gp); \
