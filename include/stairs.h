@@ -62,8 +62,8 @@ typedef struct {
 
 /* Host pointers to the weights.  Matrices are [out_features, in_features] row-major in
  * cfg.dtype; norm gains are float[d_model].  The per-layer members point to arrays of
- * n_layers pointers.  Two models may share tensors (same host address): the library keeps
- * one device copy per distinct address. */
+ * n_layers pointers.  Two models may share tensors (same host address and shape): the library
+ * keeps one device copy of each, of wq, wk, wv and of w_gate, w_up where all of them are shared. */
 typedef struct {
   const void *tok_emb;          /* [vocab, d_model] */
   const void *lm_head;          /* [vocab, d_model] */
